@@ -453,38 +453,107 @@ __global__ void __launch_bounds__(256) glm_update_kernel(float* __restrict__ the
 }
 
 // Evaluation: sum over rows of the per-sample loss at theta (least squares: (x'theta - y)^2 / 2; logistic:
-// log(1 + e^u) - y u with u = x'theta), one row per wavefront at a time, fp64 sums, one partial sum per workgroup
-// (the host adds them in index order: reproducible).
+// log(1 + e^u) - y u with u = x'theta), fp64 sums, one partial sum per workgroup (added in index order afterwards:
+// reproducible).
 constexpr int kLossBlock = 256;
 
-__global__ void __launch_bounds__(kLossBlock) glm_loss_kernel(const float* __restrict__ X, const float* __restrict__ y,
-                                                              const float* __restrict__ theta, int rows, int p, int model,
-                                                              double* __restrict__ partial)
+__device__ __forceinline__ float sample_loss(int model, float u, float yi)
 {
-    extern __shared__ __align__(16) float th[];      // [p]
+    if (model == kLogistic) return fmaxf(u, 0.f) + log1pf(expf(-fabsf(u))) - yi * u;
+    return 0.5f * (u - yi) * (u - yi);
+}
+
+__device__ __forceinline__ void store_partial(double acc, double* partial)
+{
     __shared__ double wsum[kLossBlock / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int c = threadIdx.x; c < p; c += kLossBlock) th[c] = theta[c];
-    __syncthreads();
-    double acc = 0.0;
-    for (int i = blockIdx.x * (kLossBlock / 64) + wave; i < rows; i += gridDim.x * (kLossBlock / 64)) {
-        const float* row = X + (size_t)i * p;
-        float d = 0.f;
-        for (int c = lane; c < p; c += 64) d = fmaf(row[c], th[c], d);
-        const float u = group_sum(d, 64);
-        const float yi = y[i];
-        float l;
-        if (model == kLogistic) l = fmaxf(u, 0.f) + log1pf(expf(-fabsf(u))) - yi * u;
-        else l = 0.5f * (u - yi) * (u - yi);
-        acc += (double)l;
-    }
-    if (lane == 0) wsum[wave] = acc;
+    for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
         for (int w = 0; w < kLossBlock / 64; ++w) t += wsum[w];
         partial[blockIdx.x] = t;
     }
+}
+
+// Bound by memory: the rows are read once, in order.  A row is held by L lanes as in the chain kernel (CPL vector loads
+// of V floats per lane, theta's slice in registers), U rows per lane group are requested together (up to 8 x 16 bytes
+// in flight per lane; with one row at a time and 4-byte loads a wavefront stood in its own latency: 1.5 TB/s), and the
+// U losses, whose exp and log1p cost more than a row's products, are evaluated by U different lanes at once.
+// 1,000,000 rows of 200 floats: 541 -> 146 us (5.5 TB/s; a large copy reaches 4.8 TB/s here).
+template <int V, int CPL, int U>
+__global__ void __launch_bounds__(kLossBlock) glm_loss_rows_kernel(const float* __restrict__ X, const float* __restrict__ y,
+                                                                   const float* __restrict__ theta, int rows, int p, int model,
+                                                                   int logL, double* __restrict__ partial)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int L = 1 << logL, rpw = 64 >> logL;
+    const int lsub = lane & (L - 1), slot = lane >> logL;
+    int off[CPL];
+    float th[CPL * V];
+#pragma unroll
+    for (int k = 0; k < CPL; ++k) {
+        const int c = V * (lsub + L * k);
+        off[k] = c < p ? c : 0;                      // beyond p: column 0 again, with a zero in theta's place
+#pragma unroll
+        for (int v = 0; v < V; ++v) th[k * V + v] = c < p ? theta[c + v] : 0.f;   // (a caller's theta may be 4-byte aligned only)
+    }
+    const int per = U * rpw;                         // consecutive rows a wavefront takes at a time
+    const int64_t stride = (int64_t)gridDim.x * (kLossBlock / 64) * per;
+    auto clamped = [&](int64_t r) { return (size_t)(r < rows ? r : rows - 1); };
+    double acc = 0.0;
+    for (int64_t base = ((int64_t)blockIdx.x * (kLossBlock / 64) + wave) * per; base < rows; base += stride) {
+        float x[U][CPL * V], yv[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const float* row = X + clamped(base + q * rpw + slot) * (size_t)p;
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) load_vec<V>(row + off[k], &x[q][k * V]);
+        }
+        // lane l of a group looks after the rows q = l, l + L, ... of its slot
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            if (j * L < U) yv[j] = y[clamped(base + (int64_t)(j * L + lsub) * rpw + slot)];
+        float d[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            float t = 0.f;
+#pragma unroll
+            for (int e = 0; e < CPL * V; ++e) t = fmaf(x[q][e], th[e], t);
+            d[q] = group_sum(t, L);
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j)
+            if (j * L < U) {
+                const int mine = j * L + lsub;
+                float u = d[0];
+#pragma unroll
+                for (int q = 1; q < U; ++q) u = mine == q ? d[q] : u;
+                if (mine < U && base + (int64_t)mine * rpw + slot < rows) acc += (double)sample_loss(model, u, yv[j]);
+            }
+    }
+    store_partial(acc, partial);
+}
+
+// Rows beyond 16 vector loads per lane (only bmgd_eval_loss_static takes them): theta in shared memory, one row per
+// wavefront at a time.
+__global__ void __launch_bounds__(kLossBlock) glm_loss_kernel(const float* __restrict__ X, const float* __restrict__ y,
+                                                              const float* __restrict__ theta, int rows, int p, int model,
+                                                              double* __restrict__ partial)
+{
+    extern __shared__ __align__(16) float th[];      // [p]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int c = threadIdx.x; c < p; c += kLossBlock) th[c] = theta[c];
+    __syncthreads();
+    double acc = 0.0;
+    for (int64_t i = (int64_t)blockIdx.x * (kLossBlock / 64) + wave; i < rows; i += (int64_t)gridDim.x * (kLossBlock / 64)) {
+        const float* row = X + (size_t)i * p;
+        float d = 0.f;
+        for (int c = lane; c < p; c += 64) d = fmaf(row[c], th[c], d);
+        const float u = group_sum(d, 64);
+        if (lane == 0) acc += (double)sample_loss(model, u, y[i]);
+    }
+    store_partial(acc, partial);
 }
 
 using KernelFn = void (*)(GlmArgs);
@@ -732,11 +801,44 @@ hipError_t glm_launch_step(const GlmLaunchShape& s, const GlmArgs& args, int nb,
     return hipGetLastError();
 }
 
+namespace {
+
+using LossFn = void (*)(const float*, const float*, const float*, int, int, int, int, double*);
+
+template <int V, int CPL>
+LossFn pick_loss()
+{
+    constexpr int fit = 32 / (V * CPL);              // rows together: 32 floats per lane, at most 8 rows
+    return glm_loss_rows_kernel<V, CPL, (fit < 1 ? 1 : fit > 8 ? 8 : fit)>;
+}
+
+template <int V>
+LossFn pick_loss_v(int64_t cpl)
+{
+    if (cpl <= 1) return pick_loss<V, 1>();
+    if (cpl <= 2) return pick_loss<V, 2>();
+    if (cpl <= 4) return pick_loss<V, 4>();
+    if (cpl <= 8) return pick_loss<V, 8>();
+    if (cpl <= 16) return pick_loss<V, 16>();
+    return nullptr;
+}
+
+}  // namespace
+
 hipError_t glm_launch_loss(const float* X, const float* y, const float* theta, int rows, int p, int model, double* partial,
                            int nblocks, hipStream_t stream)
 {
-    hipLaunchKernelGGL(glm_loss_kernel, dim3(nblocks), dim3(kLossBlock), (size_t)p * sizeof(float), stream, X, y, theta, rows, p,
-                       model, partial);
+    const int V = p % 4 == 0 ? 4 : p % 2 == 0 ? 2 : 1;
+    const int64_t chunks = p / V;
+    int logL = 0;
+    while (logL < 6 && (1 << logL) < chunks) ++logL;
+    const int64_t cpl = (chunks + 63) / 64;
+    LossFn fn = V == 4 ? pick_loss_v<4>(cpl) : V == 2 ? pick_loss_v<2>(cpl) : pick_loss_v<1>(cpl);
+    if (fn)
+        hipLaunchKernelGGL(fn, dim3(nblocks), dim3(kLossBlock), 0, stream, X, y, theta, rows, p, model, logL, partial);
+    else
+        hipLaunchKernelGGL(glm_loss_kernel, dim3(nblocks), dim3(kLossBlock), (size_t)p * sizeof(float), stream, X, y, theta, rows, p,
+                           model, partial);
     return hipGetLastError();
 }
 

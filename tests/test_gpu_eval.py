@@ -61,3 +61,23 @@ def test_global_loss_goes_down_over_iterations():
     ctx.close()
     assert abs(losses[0] - np.log(2.0)) < 1e-6                  # theta = 0: every row costs log 2
     assert all(b < a for a, b in zip(losses, losses[1:])), losses
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 6, 36, 129, 258, 1000, 1023, 2046, 4095])
+def test_loss_at_every_row_layout_and_remainder(p):
+    """Each vector width and number of chunks per lane (and rows beyond them), with rows that fill no wavefront, one
+    group exactly, and one more: sums of p products in fp32 (2^-24 sqrt(p) relative to the terms, far below 2e-5)."""
+    import torch
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    out = torch.empty(1, dtype=torch.float64, device="cuda")
+    rng = np.random.default_rng(p)
+    theta = (rng.standard_normal(p) / np.sqrt(p)).astype(np.float32)
+    for model, rows in ((wl.LINEAR, 1), (wl.LOGISTIC, 31), (wl.LOGISTIC, 2048), (wl.LINEAR, 2049)):
+        X = rng.standard_normal((rows, p)).astype(np.float32)
+        y = (rng.random(rows) < 0.5).astype(np.float32)
+        rc = B.bmgd_eval_loss_static(model, torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(),
+                                     torch.from_numpy(theta).cuda(), rows, p, None, out)
+        assert rc == B.BMGD_OK
+        want = O.loss(model, X.astype(np.float64), y.astype(np.float64), theta.astype(np.float64))
+        assert abs(float(out.cpu()[0]) - want) <= 2e-5 * abs(want), (p, model, rows)
