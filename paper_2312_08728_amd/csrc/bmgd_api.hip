@@ -53,6 +53,9 @@ struct RunRecord {                                 // events of one buffer, for 
     int n_chain = 0, n_prep = 0;                   // launches of this run with an entry in open_chain / open_prep
 };
 
+// Pinned host memory of a context, for what blocking calls bring from the device: flags, then two areas for rows of theta.
+constexpr size_t kMailHead = 256;
+constexpr size_t kMailArea = size_t(1) << 20;      // at most; contexts with a smaller theta take what they need
 constexpr size_t kMaxOpenRuns = 4096;              // runs whose events are held before the oldest half is folded
 
 }  // namespace
@@ -144,6 +147,9 @@ struct bmgd_ctx {
     RunRecord pending_copy;                        // copy events of the buffer that is loaded but not run
     hipStream_t last_copy = nullptr, last_compute = nullptr;
     bool used_copy = false, used_compute = false;
+    char* mail = nullptr;                          // pinned: kMailHead bytes of flags, two areas of mail_area bytes
+    size_t mail_area = 0;
+    hipEvent_t mail_done[2] = {nullptr, nullptr};  // the export that filled an area (large estimates only)
     bool poisoned = false;                         // a run failed or was abandoned: theta is not valid until it is set again
     std::string err;
 };
@@ -416,16 +422,48 @@ int trim_records(bmgd_ctx* ctx)
     return BMGD_OK;
 }
 
-int drain(bmgd_ctx* ctx)
+// The stream whose work comes last: the library's chain stream in the moment form, else the caller's compute stream.
+hipStream_t tail_stream(const bmgd_ctx* ctx)
+{
+    if (ctx->chain_stream) return ctx->chain_stream;
+    return ctx->used_compute ? ctx->last_compute : nullptr;
+}
+
+// Wait for everything enqueued, and bring `rows` rows of C floats of `src` (row stride ld) to host_out (rows = 0: nothing) and
+// the failure flags, which are turned into an error.  A kernel behind the last run writes both into the context's pinned
+// memory, so a call costs one launch and one wait (a hipMemcpy each for the flags and for theta cost as much again; a strided
+// hipMemcpy2D of 3,072 rows into ordinary memory took 21 ms).  More than an area holds goes through the two areas in turn: the
+// host copies one out while the device fills the other.
+int drain_and_fetch(bmgd_ctx* ctx, const float* src, int64_t rows, int64_t C, int64_t ld, float* host_out)
 {
     HIP_TRY(ctx, hipSetDevice(ctx->device));
+    hipStream_t ts = tail_stream(ctx);
+    unsigned* flags = reinterpret_cast<unsigned*>(ctx->mail);
+    float* area[2] = {reinterpret_cast<float*>(ctx->mail + kMailHead), reinterpret_cast<float*>(ctx->mail + kMailHead + ctx->mail_area)};
+    const int64_t per = rows ? std::min<int64_t>(rows, (int64_t)(ctx->mail_area / ((size_t)C * 4))) : 0;
+    const int64_t parts = rows ? (rows + per - 1) / per : 1;
+    for (int64_t k = 0; k <= parts; ++k) {
+        if (k < parts) {
+            const int64_t r0 = k * per, n = rows ? std::min(per, rows - r0) : 0;
+            HIP_TRY(ctx, launch_export(area[k & 1], src, r0, n, C, ld, flags, ctx->sync + 1, ts));
+            if (parts > 1) {
+                if (!ctx->mail_done[k & 1]) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->mail_done[k & 1], hipEventDisableTiming));
+                HIP_TRY(ctx, hipEventRecord(ctx->mail_done[k & 1], ts));
+            }
+        }
+        if (k > 0 && rows) {
+            if (parts > 1) HIP_TRY(ctx, hipEventSynchronize(ctx->mail_done[(k - 1) & 1]));
+            else HIP_TRY(ctx, hipStreamSynchronize(ts));
+            const int64_t r0 = (k - 1) * per, n = std::min(per, rows - r0);
+            memcpy(host_out + r0 * C, area[(k - 1) & 1], (size_t)(n * C) * 4);
+        }
+    }
+    HIP_TRY(ctx, hipStreamSynchronize(ts));
     if (ctx->used_copy) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_copy));
-    if (ctx->used_compute) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_compute));
-    if (ctx->chain_stream) HIP_TRY(ctx, hipStreamSynchronize(ctx->chain_stream));
+    if (ctx->used_compute && ctx->last_compute != ts) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_compute));
     ctx->chain_pending[0] = ctx->chain_pending[1] = false;
     settle_records(ctx, ctx->open_records.size());
-    unsigned flag[2] = {0, 0};
-    HIP_TRY(ctx, hipMemcpy(flag, ctx->sync + 1, sizeof flag, hipMemcpyDeviceToHost));
+    const unsigned flag[2] = {flags[0], flags[1]};
     if (flag[0] != 0 || flag[1] != 0) {
         HIP_TRY(ctx, hipMemset(ctx->sync, 0, 64));
         ctx->poisoned = true;
@@ -434,6 +472,21 @@ int drain(bmgd_ctx* ctx)
         return fail(ctx, BMGD_EINVAL, "a row subset held an index outside its buffer (row 0 was used in its place); theta is not valid (set it again with bmgd_set_theta before the next run)");
     }
     return BMGD_OK;
+}
+
+int drain(bmgd_ctx* ctx) { return drain_and_fetch(ctx, nullptr, 0, 1, 1, nullptr); }
+
+// theta or an array laid out like it: rows, values per row and row stride
+void theta_rows(const bmgd_ctx* ctx, int64_t* rows, int64_t* C, int64_t* ld)
+{
+    if (ctx->cfg.model == BMGD_SOFTMAX) {
+        *rows = ctx->cfg.p;
+        *C = ctx->cfg.n_classes;
+        *ld = softmax_dims(ctx->cfg.p, ctx->cfg.batch_n, ctx->cfg.n_classes).c_pad;
+    } else {
+        *rows = 1;
+        *C = *ld = ctx->cfg.p;
+    }
 }
 
 int64_t batches_of(int64_t rows, int64_t n) { return (rows + n - 1) / n; }
@@ -803,6 +856,9 @@ void destroy_ctx(bmgd_ctx* ctx)
         if (s.compute_done) (void)hipEventDestroy(s.compute_done);
     }
     if (ctx->base) (void)hipEventDestroy(ctx->base);
+    for (hipEvent_t e : ctx->mail_done)
+        if (e) (void)hipEventDestroy(e);
+    if (ctx->mail) (void)hipHostFree(ctx->mail);
     if (ctx->lr_tab_dev) (void)hipFree(ctx->lr_tab_dev);
     if (ctx->owns_ws && ctx->ws) (void)hipFree(ctx->ws);
     delete ctx;
@@ -916,6 +972,8 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     ctx->opt_s = reinterpret_cast<float*>(base + ctx->lay.opt_s);
     if (ctx->lay.total > ctx->lay.opt_m) CREATE_TRY(hipMemset(ctx->opt_m, 0, ctx->lay.total - ctx->lay.opt_m));
     CREATE_TRY(hipMemset(ctx->sync, 0, 64));
+    ctx->mail_area = std::min(align_up((size_t)ctx->theta_len * 4), kMailArea);   // (at least one row: C <= 2048, p <= 4096)
+    CREATE_TRY(hipHostMalloc(reinterpret_cast<void**>(&ctx->mail), kMailHead + 2 * ctx->mail_area, hipHostMallocDefault));
     if (cfg->model == BMGD_SOFTMAX) {
         // theta = 0 (padding classes included), bf16 copy = 0, residual scratch = 0
         CREATE_TRY(hipMemset(ctx->theta, 0, ctx->lay.sync - ctx->lay.theta));
@@ -1277,16 +1335,9 @@ BMGD_API int bmgd_get_theta(bmgd_ctx* ctx, float* host_out, int64_t len)
     if (!ctx) return BMGD_EINVAL;
     if (!host_out) return fail(ctx, BMGD_EINVAL, "host_out must not be NULL");
     if (len != ctx->theta_len) return fail(ctx, BMGD_EINVAL, "len must equal p (p * n_classes for softmax)");
-    const int rc = drain(ctx);
-    if (rc != BMGD_OK) return rc;
-    if (ctx->cfg.model == BMGD_SOFTMAX) {
-        const SoftmaxDims d = softmax_dims(ctx->cfg.p, ctx->cfg.batch_n, ctx->cfg.n_classes);
-        const size_t C = (size_t)ctx->cfg.n_classes;
-        HIP_TRY(ctx, hipMemcpy2D(host_out, C * 4, ctx->theta, (size_t)d.c_pad * 4, C * 4, (size_t)ctx->cfg.p, hipMemcpyDeviceToHost));
-        return BMGD_OK;
-    }
-    HIP_TRY(ctx, hipMemcpy(host_out, ctx->theta, (size_t)len * 4, hipMemcpyDeviceToHost));
-    return BMGD_OK;
+    int64_t rows, C, ld;
+    theta_rows(ctx, &rows, &C, &ld);
+    return drain_and_fetch(ctx, ctx->theta, rows, C, ld, host_out);
 }
 
 BMGD_API int bmgd_set_theta(bmgd_ctx* ctx, const float* host_in, int64_t len)
@@ -1297,15 +1348,21 @@ BMGD_API int bmgd_set_theta(bmgd_ctx* ctx, const float* host_in, int64_t len)
     const int rc = drain(ctx);                           // (an abandoned run found only now is what this call is the remedy for)
     if (rc != BMGD_OK && !ctx->poisoned) return rc;
     ctx->poisoned = false;
+    int64_t rows, C, ld;
+    theta_rows(ctx, &rows, &C, &ld);
+    const int64_t per = std::min<int64_t>(rows, (int64_t)(ctx->mail_area / ((size_t)C * 4)));
+    float* area = reinterpret_cast<float*>(ctx->mail + kMailHead);
+    for (int64_t r0 = 0; r0 < rows; r0 += per) {
+        const int64_t n = std::min(per, rows - r0);
+        memcpy(area, host_in + r0 * C, (size_t)(n * C) * 4);
+        HIP_TRY(ctx, launch_import(ctx->theta, area, r0, n, C, ld, nullptr));
+        HIP_TRY(ctx, hipStreamSynchronize(nullptr));
+    }
     if (ctx->cfg.model == BMGD_SOFTMAX) {
         const SoftmaxDims d = softmax_dims(ctx->cfg.p, ctx->cfg.batch_n, ctx->cfg.n_classes);
-        const size_t C = (size_t)ctx->cfg.n_classes;
-        HIP_TRY(ctx, hipMemcpy2D(ctx->theta, (size_t)d.c_pad * 4, host_in, C * 4, C * 4, (size_t)ctx->cfg.p, hipMemcpyHostToDevice));
         HIP_TRY(ctx, softmax_refresh_shadow(ctx->theta, ctx->wbt, (int)ctx->cfg.p, d, nullptr));
-        HIP_TRY(ctx, hipDeviceSynchronize());
-        return BMGD_OK;
     }
-    HIP_TRY(ctx, hipMemcpy(ctx->theta, host_in, (size_t)len * 4, hipMemcpyHostToDevice));
+    HIP_TRY(ctx, hipDeviceSynchronize());
     return BMGD_OK;
 }
 
@@ -1361,16 +1418,9 @@ BMGD_API int bmgd_get_swa(bmgd_ctx* ctx, float* host_out, int64_t len, int64_t* 
     if (!host_out) return fail(ctx, BMGD_EINVAL, "host_out must not be NULL");
     if (len != ctx->theta_len) return fail(ctx, BMGD_EINVAL, "len must equal p (p * n_classes for softmax)");
     if (ctx->swa_count == 0) return fail(ctx, BMGD_ESTATE, "no estimate has been averaged yet");
-    const int rc = drain(ctx);
-    if (rc != BMGD_OK) return rc;
-    if (ctx->cfg.model == BMGD_SOFTMAX) {
-        const SoftmaxDims d = softmax_dims(ctx->cfg.p, ctx->cfg.batch_n, ctx->cfg.n_classes);
-        const size_t C = (size_t)ctx->cfg.n_classes;
-        HIP_TRY(ctx, hipMemcpy2D(host_out, C * 4, ctx->swa, (size_t)d.c_pad * 4, C * 4, (size_t)ctx->cfg.p, hipMemcpyDeviceToHost));
-        return BMGD_OK;
-    }
-    HIP_TRY(ctx, hipMemcpy(host_out, ctx->swa, (size_t)len * 4, hipMemcpyDeviceToHost));
-    return BMGD_OK;
+    int64_t rows, C, ld;
+    theta_rows(ctx, &rows, &C, &ld);
+    return drain_and_fetch(ctx, ctx->swa, rows, C, ld, host_out);
 }
 
 BMGD_API int bmgd_swa_reset(bmgd_ctx* ctx)

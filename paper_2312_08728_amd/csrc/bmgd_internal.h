@@ -38,6 +38,12 @@ hipError_t launch_perm(int32_t* out, int64_t rows, int npass, const PermKeys& ke
 // Device: zero `bytes` bytes at dst (both multiples of 16) with a kernel, in stream order.
 hipError_t launch_fill_zero(void* dst, size_t bytes, hipStream_t stream);
 
+// Device: rows [row0, row0 + rows) of C values (row stride ld) packed into `dst`, and the two failure flags into `flags_out`
+// (both pinned host memory), in stream order; launch_import unpacks such rows.  rows * C < 2^31.
+hipError_t launch_export(float* dst, const float* src, int64_t row0, int64_t rows, int64_t C, int64_t ld, unsigned* flags_out,
+                         const unsigned* flags, hipStream_t stream);
+hipError_t launch_import(float* dst, const float* src, int64_t row0, int64_t rows, int64_t C, int64_t ld, hipStream_t stream);
+
 // Device: running mean of snapshots of theta (n floats), in stream order: avg <- theta if `first`, else
 // avg <- avg + (theta - avg) * inv.
 hipError_t launch_running_mean(float* avg, const float* theta, size_t n, float inv, bool first, hipStream_t stream);

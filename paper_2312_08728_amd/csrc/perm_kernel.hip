@@ -81,7 +81,51 @@ __global__ void __launch_bounds__(256) running_mean_kernel(float* __restrict__ a
     }
 }
 
+// Rows of C values out of rows of ld, packed, and the two words of failure flags, into host memory the device can write:
+// dst[i] = src[(row0 + i / C) ld + i % C].  Bound by the link (3,072 rows of 1,000 floats, in 1 MB parts: 0.7 ms with the copies on the host).
+__global__ void __launch_bounds__(256) export_kernel(float* __restrict__ dst, const float* __restrict__ src, unsigned row0, unsigned C,
+                                                     unsigned ld, unsigned count, unsigned* __restrict__ flags_out,
+                                                     const unsigned* __restrict__ flags)
+{
+    if (blockIdx.x == 0 && threadIdx.x < 2) flags_out[threadIdx.x] = flags[threadIdx.x];
+    const unsigned stride = gridDim.x * blockDim.x;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) {
+        const unsigned r = i / C;
+        dst[i] = src[(size_t)(row0 + r) * ld + (i - r * C)];
+    }
+}
+
+// The other way: dst[(row0 + i / C) ld + i % C] = src[i].
+__global__ void __launch_bounds__(256) import_kernel(float* __restrict__ dst, const float* __restrict__ src, unsigned row0, unsigned C,
+                                                     unsigned ld, unsigned count)
+{
+    const unsigned stride = gridDim.x * blockDim.x;
+    for (unsigned i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) {
+        const unsigned r = i / C;
+        dst[(size_t)(row0 + r) * ld + (i - r * C)] = src[i];
+    }
+}
+
 }  // namespace
+
+hipError_t launch_export(float* dst, const float* src, int64_t row0, int64_t rows, int64_t C, int64_t ld, unsigned* flags_out,
+                         const unsigned* flags, hipStream_t stream)
+{
+    const unsigned count = (unsigned)(rows * C);
+    const unsigned blocks = std::max(1u, std::min((count + 255) / 256, 1024u));
+    hipLaunchKernelGGL(export_kernel, dim3(blocks), dim3(256), 0, stream, dst, src, (unsigned)row0, (unsigned)std::max<int64_t>(C, 1),
+                       (unsigned)ld, count, flags_out, flags);
+    return hipGetLastError();
+}
+
+hipError_t launch_import(float* dst, const float* src, int64_t row0, int64_t rows, int64_t C, int64_t ld, hipStream_t stream)
+{
+    const unsigned count = (unsigned)(rows * C);
+    if (count == 0) return hipSuccess;
+    const unsigned blocks = std::min((count + 255) / 256, 1024u);
+    hipLaunchKernelGGL(import_kernel, dim3(blocks), dim3(256), 0, stream, dst, src, (unsigned)row0, (unsigned)C, (unsigned)ld, count);
+    return hipGetLastError();
+}
 
 hipError_t launch_running_mean(float* avg, const float* theta, size_t n, float inv, bool first, hipStream_t stream)
 {
