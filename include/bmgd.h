@@ -115,7 +115,10 @@ enum {
                                     its mini-batches, then logits, residual and gradient + update per mini-batch - are captured
                                     once into a HIP graph per (buffer address, rows, partition slot) and replayed; learning
                                     rate and update counts are read from device memory, so a replay needs no new capture.
-                                    BMGD_CHAIN_LAUNCH issues the same launches one by one. */
+                                    BMGD_CHAIN_LAUNCH issues the same launches one by one.  BMGD_CHAIN_AUTO (reported
+                                    as this mode) runs all updates of a pass in one persistent kernel instead where
+                                    mini-batches are small (batch_n, p <= 1024 and batch_n p <= 2^18; with a
+                                    buffered method of its own state p <= 512 and batch_n p <= 2^17). */
     BMGD_CHAIN_PRODUCT = 5       /* least squares with p <= 128 and plain steps (BMGD_OPT_SGD) only: the moment form of
                                     BMGD_CHAIN_GRAM with steps multiplied together.  A step of eq. (3.1) is the affine map
                                     [theta; 1] <- A_m [theta; 1], A_m = [[I - alpha Sxx_m, alpha Sxy_m], [0, 1]], and no A_m

@@ -33,7 +33,7 @@ constexpr int kMaxGroups = 256;                    // upper bound used to size t
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t slot_x[2], slot_y[2], perm, theta, partial, ll_part, ll_theta, sync, sm_state, wbt, u, rt, xt, gram[2], prod[2], gram_perm, gram_cache, gram_cache_set, prod_cache, prod_cache_set, opt_m, opt_s, opt_len, eval, swa, total;
+    size_t slot_x[2], slot_y[2], perm, theta, partial, ll_part, ll_theta, sync, sm_state, wbt, u, rt, xt, sm_words, gram[2], prod[2], gram_perm, gram_cache, gram_cache_set, prod_cache, prod_cache_set, opt_m, opt_s, opt_len, eval, swa, total;
 };
 
 struct Slot {
@@ -86,7 +86,9 @@ struct bmgd_ctx {
     void* wbt = nullptr;                           // softmax: bf16 copy of W, transposed
     float* u = nullptr;                            // softmax: logits scratch
     void* rt = nullptr;                            // softmax: residual scratch
-    void* xt = nullptr;                            // softmax: transposed mini-batches of one pass
+    void* xt = nullptr;                            // softmax: transposed mini-batches of one pass (sm_chain: in the order of that kernel)
+    bool sm_chain = false;                         // softmax: a pass is one persistent kernel (softmax_chain_kernel.hip)
+    unsigned long long* sm_words = nullptr;        // ... and its flagged words
     // eq. (3.1) form.  The pre-pass over the buffer (partitions, moment matrices) runs on the caller's compute
     // stream and the one-workgroup chain on a stream of the library's own, so that the pre-pass of the next
     // buffer overlaps the chain of this one; two sets of partitions and matrices alternate.
@@ -223,6 +225,13 @@ bool valid_config(const bmgd_config& c, std::string* why)
 
 int resolve_chain(const bmgd_config& c);
 
+// Softmax with small mini-batches, left to the library: one persistent kernel per pass.  The two modes that can be asked for
+// by name keep to their launches.
+bool wants_softmax_chain(const bmgd_config& c)
+{
+    return c.model == BMGD_SOFTMAX && c.chain == BMGD_CHAIN_AUTO && softmax_chain_eligible(c.p, c.batch_n, c.n_classes, c.optimizer != BMGD_OPT_SGD);
+}
+
 // BMGD_CHAIN_PRODUCT, asked for or picked: BMGD_CHAIN_AUTO takes it for plain steps of least squares in the moment form
 // when a launch has enough steps for the halved chain to matter (measured at 300 steps per launch: 0.151 against 0.175 ms
 // per buffer) and nothing is cached (with cached matrices the caller chooses between the two forms).
@@ -257,7 +266,9 @@ Layout make_layout(const bmgd_config& c)
         l.wbt = off;     off += align_up((size_t)d.c_pad * d.p_pad * 2);
         l.u = off;       off += align_up((size_t)8 * d.m_pad * d.c_pad * 4);
         l.rt = off;      off += align_up((size_t)d.c_pad * d.n_pad * 2);
-        l.xt = off;      off += align_up(m_max * (size_t)c.p * d.n_pad * 2);
+        const bool one_kernel = wants_softmax_chain(c);
+        l.xt = off;      off += align_up(std::max(m_max * (size_t)c.p * d.n_pad * 2, one_kernel ? softmax_chain_pack_bytes(c.p, c.batch_n, (int64_t)m_max) : 0));
+        l.sm_words = off; off += one_kernel ? align_up(softmax_chain_words_bytes(c.batch_n, C)) : 0;
     } else {
         l.theta = off;   off += align_up((size_t)c.p * 4);
         l.partial = off; off += align_up((size_t)2 * kMaxGroups * c.p * 4);
@@ -265,7 +276,7 @@ Layout make_layout(const bmgd_config& c)
         l.ll_part = off; off += align_up((size_t)2 * kMaxGroups * pp * 8);
         l.ll_theta = off; off += align_up((size_t)2 * kThetaCopies * pp * 8);
         l.sync = off;    off += align_up(64);
-        l.sm_state = l.wbt = l.u = l.rt = l.xt = off;
+        l.sm_state = l.wbt = l.u = l.rt = l.xt = l.sm_words = off;
     }
     l.gram[0] = l.gram[1] = l.gram_perm = off;
     if (resolve_chain(c) == BMGD_CHAIN_GRAM) {
@@ -695,6 +706,33 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             };
             for (int i = 0; i < np; ++i) {
                 const int32_t* pm = ctx->perm + (fixed ? 0 : (size_t)i * rows);
+                if (ctx->sm_chain) {
+                    if ((uint64_t)ctx->tag_epoch + (uint64_t)M + 1 >= 0xFFFFFFFFull) {
+                        // tag space used up: clear the flagged words (stream-ordered) and start over
+                        HIP_TRY(ctx, launch_fill_zero(ctx->sm_words, ctx->lay.gram[0] - ctx->lay.sm_words, stream));
+                        ctx->tag_epoch = 0;
+                    }
+                    SoftmaxChainArgs sa{};
+                    sa.W = ctx->theta;
+                    sa.WbT = static_cast<unsigned short*>(ctx->wbt);
+                    sa.ldw = dmax.c_pad;
+                    sa.ldwt = dmax.p_pad;
+                    sa.rows = (int)rows; sa.n = (int)n; sa.p = (int)c.p; sa.C = c.n_classes;
+                    sa.words = ctx->sm_words;
+                    sa.tag_base = ctx->tag_epoch;
+                    sa.sync = ctx->sync;
+                    sa.timeout_ticks = ticks;
+                    sa.alpha = (float)c.lr;
+                    sa.lr_tab = lr_len ? ctx->lr_tab_dev : nullptr;
+                    sa.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
+                    sa.lr_len = lr_len;
+                    sa.opt = opt_args(ctx, 0);
+                    ctx->tag_epoch += (uint32_t)M;
+                    HIP_TRY(ctx, softmax_chain_pass(x, static_cast<const int32_t*>(y), pm, ctx->xt, sa, stream));
+                    ctx->lr_pos += M;
+                    ctx->opt_k += M;
+                    continue;
+                }
                 // what differs between two passes with the same launches: read by the kernels from device memory
                 HIP_TRY(ctx, softmax_set_state(ctx->sm_state, (float)c.lr, (int)std::min<int64_t>(ctx->lr_pos, 0x7FFFFFF0),
                                                (int)std::min<int64_t>(ctx->opt_k, 0x7FFFFFF0), stream));
@@ -956,6 +994,7 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     ctx->u = reinterpret_cast<float*>(base + ctx->lay.u);
     ctx->rt = base + ctx->lay.rt;
     ctx->xt = base + ctx->lay.xt;
+    ctx->sm_words = reinterpret_cast<unsigned long long*>(base + ctx->lay.sm_words);
     ctx->gram[0] = reinterpret_cast<float*>(base + ctx->lay.gram[0]);
     ctx->gram[1] = reinterpret_cast<float*>(base + ctx->lay.gram[1]);
     ctx->prod[0] = reinterpret_cast<float*>(base + ctx->lay.prod[0]);
@@ -978,6 +1017,8 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
         // theta = 0 (padding classes included), bf16 copy = 0, residual scratch = 0
         CREATE_TRY(hipMemset(ctx->theta, 0, ctx->lay.sync - ctx->lay.theta));
         CREATE_TRY(hipMemset(ctx->wbt, 0, ctx->lay.xt - ctx->lay.wbt));
+        // flagged words start with tag 0, which no step ever waits for
+        if (ctx->lay.gram[0] > ctx->lay.sm_words) CREATE_TRY(hipMemset(ctx->sm_words, 0, ctx->lay.gram[0] - ctx->lay.sm_words));
     } else {
         CREATE_TRY(hipMemset(ctx->theta, 0, (size_t)ctx->theta_len * 4));
         // flagged words start with tag 0, which no step ever waits for
@@ -992,7 +1033,9 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     if (cfg->model == BMGD_SOFTMAX) {
         CREATE_TRY(softmax_prepare(softmax_dims(cfg->p, cfg->batch_n, cfg->n_classes)));
         ctx->chain = resolve_chain(ctx->cfg);        // three launches per mini-batch update, replayed from a graph or issued one by one
-        if (ctx->chain == BMGD_CHAIN_GRAPH) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
+        if (wants_softmax_chain(ctx->cfg))
+            CREATE_TRY(softmax_chain_prepare(cfg->p, cfg->batch_n, cfg->n_classes, cfg->optimizer != BMGD_OPT_SGD, ctx->num_cus, &ctx->sm_chain));
+        if (ctx->chain == BMGD_CHAIN_GRAPH && !ctx->sm_chain) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
     } else {
         char msg[160];
         if (!glm_plan(cfg->p, cfg->batch_n, cfg->n_workgroups, ctx->num_cus, &ctx->shape, msg, sizeof msg)) {

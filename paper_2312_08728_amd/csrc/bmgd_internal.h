@@ -261,6 +261,35 @@ hipError_t softmax_set_state(SoftmaxState* state, float alpha, int lr_pos, int o
 // was created with) at the bf16 copy of W: partial[b] for b < ceil(nb / 8) workgroups.
 hipError_t softmax_launch_loss(const void* X, const int32_t* y, int nb, int p, int C, const void* WbT, float* U,
                                const SoftmaxDims& d, double* partial, hipStream_t stream);
+// Small mini-batches: the updates of a pass in one persistent kernel (softmax_chain_kernel.hip).
+struct SoftmaxChainArgs {
+    float* W;               // fp32 master [p][ldw]
+    unsigned short* WbT;    // bf16 copy, transposed [ldw][ldwt]: written at the end of the pass
+    int ldw, ldwt;
+    int rows, n, p, C;
+    unsigned long long* words;     // [2][G][word_stride] flagged words, by step parity
+    unsigned tag_base;      // tag of update s of the pass is tag_base + s + 1
+    unsigned* sync;         // [1] abort flag
+    long long timeout_ticks;
+    float alpha;
+    const float* lr_tab;    // optional learning rate per update: update s uses lr_tab[min(lr_base + s, lr_len - 1)]
+    int lr_base, lr_len;
+    OptArgs opt;            // state arrays laid out like W; k_base = updates made before the pass
+    // filled in by softmax_chain_pass
+    int M, n32, p32, word_stride;
+    const unsigned short* XP;
+    const unsigned short* XTP;
+    const int* YL;
+};
+// opt: an update rule with state
+bool softmax_chain_eligible(int64_t p, int64_t n, int64_t C, bool opt);
+// bytes of the packed mini-batches of a pass / of the flagged words
+size_t softmax_chain_pack_bytes(int64_t p, int64_t n, int64_t batches);
+size_t softmax_chain_words_bytes(int64_t n, int64_t C);
+// *fits: all workgroups can be resident at once on num_cus compute units
+hipError_t softmax_chain_prepare(int64_t p, int64_t n, int64_t C, bool opt, int num_cus, bool* fits);
+// One pass (two launches in stream order): the mini-batches of `perm` packed into `pack`, then their updates.
+hipError_t softmax_chain_pass(const void* X, const int32_t* y, const int32_t* perm, void* pack, SoftmaxChainArgs args, hipStream_t stream);
 // WbT <- bf16(W) transposed, whole matrix.
 hipError_t softmax_refresh_shadow(const float* W, void* WbT, int p, const SoftmaxDims& d, hipStream_t stream);
 

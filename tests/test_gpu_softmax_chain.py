@@ -1,0 +1,81 @@
+"""The persistent softmax kernel (small mini-batches, 32 classes per workgroup) at the edges of its tiles: class counts around
+one and two workgroups, rows and features around the tiles of 16 and 32 and the tiles per wavefront, ragged last mini-batches
+and a shorter last buffer.  Compared with the fp64 oracle within the bound of the bf16 path (2e-3: bf16 copy of W, bf16
+residual; 5e-3 with Adam, which normalises their rounding), and with the three-launch path, whose roundings are the same
+up to the order of fp32 sums."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from gpu_util import gpu_run, oracle_run, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(N, p, C, N0, n, T=2, R=1, alpha=0.05):
+    return wl.CONFIGS["cfg5"].scaled(name="case", N=N, p=p, C=C, N0=N0, n=n, T=T, R=R, alpha=alpha)
+
+
+@pytest.mark.parametrize("N,p,C,N0,n", [
+    (70, 8, 2, 40, 1),                 # mini-batches of one row, one feature chunk
+    (200, 16, 32, 130, 16),            # exactly one workgroup, one row tile
+    (200, 24, 33, 130, 17),            # one class in the second workgroup
+    (600, 128, 64, 400, 128),          # one tile per wavefront both ways, exactly
+    (600, 136, 65, 400, 129),          # one more of everything
+    (1500, 512, 40, 900, 300),         # several tiles per wavefront
+    (2100, 248, 300, 2100, 1024),      # most rows, ten workgroups
+    (900, 1024, 130, 600, 200),        # most features
+    (300, 40, 2000, 200, 48),          # 63 workgroups
+])
+def test_edges(N, p, C, N0, n):
+    w = _case(N, p, C, N0, n)
+    X, y = wl.dataset(w)
+    want = oracle_run(w, X, y)
+    got, st = gpu_run(w, X, y)
+    assert st.steps == w.steps and np.isfinite(got).all()
+    assert rel_l2(got, want) <= 2e-3
+    import paper_2312_08728_amd as B
+    three, _ = gpu_run(w, X, y, chain=B.BMGD_CHAIN_LAUNCH)
+    assert rel_l2(got, three) <= 2e-3
+
+
+@pytest.mark.parametrize("optimizer", [1, 2, 3])
+def test_update_rules_with_a_table_of_rates(optimizer):
+    import torch
+    import paper_2312_08728_amd as B
+    w = _case(1100, 72, 40, 600, 100)
+    X, y = wl.dataset(w)
+    xd, yd = torch.from_numpy(X.view(np.int16)).cuda(), torch.from_numpy(y).cuda()
+    s = torch.cuda.Stream()
+    got = []
+    for chain in (B.BMGD_CHAIN_AUTO, B.BMGD_CHAIN_LAUNCH):
+        ctx = B.Context(w.p, w.N0, w.n, 0.02, w.T, model=w.model, n_classes=w.C, chain=chain, optimizer=optimizer)
+        ctx.set_lr_schedule(np.linspace(0.02, 0.002, 9).astype(np.float32))
+        for k in range(2):
+            lo, hi = wl.buffer_rows(w, k)
+            ctx.run_device_buffer(xd[lo:hi], yd[lo:hi], hi - lo, s)
+        loss = ctx.eval_loss(xd, yd, w.N, s)                  # reads the bf16 copy the kernel leaves
+        got.append((ctx.get_theta(), loss))
+        ctx.close()
+    assert rel_l2(got[0][0], got[1][0]) <= 5e-3
+    assert abs(got[0][1] - got[1][1]) <= 2e-3 * abs(got[1][1])
+
+
+@pytest.mark.parametrize("bad,C", [(np.inf, 40), (-np.inf, 40), (np.nan, 40), (np.inf, 20), (np.nan, 20)])
+def test_values_that_are_not_finite_spread_as_in_three_launches(bad, C):
+    import torch
+    import paper_2312_08728_amd as B
+    w = _case(64, 32, C, 64, 64, T=1)
+    X, y = wl.dataset(w)
+    x = torch.from_numpy(X.view(np.int16)).view(torch.bfloat16).cuda()
+    x[5, 3] = float(bad)
+    yd = torch.from_numpy(y).cuda()
+    w0 = (np.random.default_rng(0).standard_normal((w.p, C)) * 0.1).astype(np.float32)
+    got = []
+    for chain in (B.BMGD_CHAIN_AUTO, B.BMGD_CHAIN_LAUNCH):
+        ctx = B.Context(w.p, 64, 64, 0.05, 1, model=w.model, n_classes=C, chain=chain)
+        ctx.set_theta(w0)
+        ctx.run_device_buffer(x, yd, 64, torch.cuda.Stream())
+        got.append(ctx.get_theta())
+        ctx.close()
+    assert np.array_equal(np.isnan(got[0]), np.isnan(got[1]))
