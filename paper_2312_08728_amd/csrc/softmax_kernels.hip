@@ -11,8 +11,8 @@
 //   logits    A = gathered rows of X (K = features),          B = WbT [C_pad][p]  (bf16 copy, transposed)
 //   gradient  A = XT [p][n_pad] (the batch, transposed once per pass, K = rows), B = Rt [C_pad][n_pad]
 // XT is written by a permute-and-transpose pass over the slot that does not depend on W, so it sits outside
-// the sequential chain.  Tiles are 128 x 128 x 32 per workgroup of four wavefronts, each wavefront owning a
-// 64 x 64 quadrant as 2 x 2 v_mfma_f32_32x32x16_bf16 tiles.
+// the sequential chain.  Tiles are 128 x 128 x 64 per workgroup of eight wavefronts, each wavefront owning a
+// 64 x 32 part as 2 x 1 v_mfma_f32_32x32x16_bf16 tiles.
 #include "bmgd_internal.h"
 
 namespace bmgd {
@@ -22,9 +22,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-constexpr int TM = 128, TN = 128, TK = 32;
-constexpr int LDS_STRIDE = 40;                     // bf16 elements per tile row in LDS (80 bytes: 16-byte aligned, spreads banks)
-
+constexpr int TM = 128, TN = 128, TK = 64;
 __device__ __forceinline__ unsigned short f32_to_bf16_rne(float f)
 {
     unsigned u = __builtin_bit_cast(unsigned, f);
@@ -83,6 +81,7 @@ struct GemmArgs {
     int N;                      // valid rows of B
     int K;                      // valid K (multiple of 8)
     int k_per_split;            // multiple of TK
+    const unsigned short* zeros;    // 16 bytes of zeros (read if K is not a multiple of TK)
     // epilogue: logits
     float* U;                   // [splits][m_pad][ldu]
     int ldu, m_pad;
@@ -102,31 +101,49 @@ struct GemmArgs {
     int tiles_m, tiles_n, splits;   // work items = splits * tiles_m * tiles_n, dealt to XCDs in contiguous runs
 };
 
-// K tiles are pipelined: up to kDepth tiles are requested ahead into registers, one tile sits in each of two
-// LDS buffers, and one is being multiplied.  A tile's arithmetic takes ~0.1 us while a trip to L2/HBM takes
-// ~1 us, so the loop would otherwise run at memory latency.
-constexpr int kDepth = 4;
-// Eight wavefronts per workgroup, two per SIMD, each with a 64 x 32 part of the 128 x 128 tile: a wavefront's waits (global ->
-// register -> shared memory -> register -> MFMA) are covered by its SIMD mate.
+// A workgroup of eight wavefronts (two per SIMD) owns a 128 x 128 tile of the result and walks its K range in tiles of 64, each
+// wavefront with a 64 x 32 part.  Tiles travel from memory to shared memory without passing through registers
+// (global_load_lds, 16 bytes per lane: a wavefront's instruction fills 1 KiB, eight rows of 128 bytes), kStages - 1 of them under
+// way while one is multiplied, with one barrier per tile.  Rows lie without padding, as the instruction writes them; 16-byte chunk
+// c of row r is kept at position c ^ (r mod 8), so that the eight rows of an operand read fall on different banks.  (The lane
+// picks which chunk it fetches, so the swizzle costs nothing: it is a fixed offset per lane.)
 constexpr int kGemmThreads = 512;
-constexpr int kWN = 32;                             // columns of the tile per wavefront (one MFMA tile wide, two high)
+constexpr int kGemmWaves = kGemmThreads / 64;
+constexpr int kWN = TN * 2 / kGemmWaves;            // columns of the tile per wavefront: 32 (64 rows high)
+constexpr int kStages = 4;
+constexpr int kStageElems = (TM + TN) * TK;         // A rows, then B rows
+constexpr int kLoads = (TM + TN) / 8 / kGemmWaves;  // instructions per wavefront and tile: the first half A, the second B
+constexpr int kLateTiles = 4;                       // the update's master weights are requested this many tiles before the end
+constexpr size_t kGemmLds = (size_t)kStages * kStageElems * 2;
+static_assert(kGemmLds >= (size_t)TN * (TM + 8) * 2, "the update's transposed tile takes the place of the stages");
+
+// 16 bytes per lane from its own address to shared memory at lds + 16 * lane.  Written as assembly because the compiler makes
+// every later read of shared memory wait for all such loads; the waits are counted by hand instead (wait_tiles).
+__device__ __forceinline__ void load_to_lds(const unsigned short* src, unsigned lds)
+{
+    asm volatile("s_mov_b32 m0, %1\n\t"
+                 "s_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, off"
+                 :: "v"(src), "s"(lds) : "memory", "m0");
+}
+// until at most TILES tiles' loads of this wavefront are under way (and all its reads of shared memory have returned)
+template <int TILES>
+__device__ __forceinline__ void wait_tiles() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(TILES * kLoads) : "memory"); }
 
 // OPT (with UPDATE): an update rule other than the plain step, in an instantiation of its own.
 template <bool UPDATE, bool OPT = false>
-__global__ void __launch_bounds__(kGemmThreads) gemm_nt_kernel(GemmArgs g)
+__global__ void __launch_bounds__(kGemmThreads, 2) gemm_nt_kernel(GemmArgs g)
 {
-    __shared__ __align__(16) unsigned short As[2][TM * LDS_STRIDE];
-    __shared__ __align__(16) unsigned short Bs[2][TN * LDS_STRIDE];
-    __shared__ __align__(16) unsigned short Ts[UPDATE ? TN * (TM + 8) : 8];
+    extern __shared__ __align__(1024) unsigned short stages[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are handed to the 8 XCDs round robin, each XCD with its own L2.  Work items are ordered
     // (split, tile row, tile column) and XCD x takes the x-th contiguous eighth, so the tiles that share
     // rows of A and the whole of B for one K range meet in one L2.
     const int total = g.splits * g.tiles_m * g.tiles_n;
     const int per = (total + 7) / 8;
     const int item = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
-    if (item >= total) return;
+    if ((int)(blockIdx.x / 8) >= per || item >= total) return;
     const int split = item / (g.tiles_m * g.tiles_n);
     const int tile = item - split * (g.tiles_m * g.tiles_n);
     const int m0 = (tile / g.tiles_n) * TM, n0 = (tile % g.tiles_n) * TN;
@@ -134,38 +151,32 @@ __global__ void __launch_bounds__(kGemmThreads) gemm_nt_kernel(GemmArgs g)
     const int ke = min(g.K, kb + g.k_per_split);
     const int ntiles = (ke - kb + TK - 1) / TK;
 
-    // Each thread moves one 16-byte chunk of A and one of B per K tile.  Every request is unconditional, from a
-    // clamped row and a clamped K offset; what lies outside the operands is zeroed when the chunk goes to LDS.
-    // (A branch or a select next to the load would make the compiler wait for the load on the spot.)
-    constexpr int CPT = TM * (TK / 8) / kGemmThreads;   // chunks per thread and operand
-    const unsigned short* a_ptr[CPT];
-    const unsigned short* b_ptr[CPT];
-    int lds_off[CPT], kc[CPT];
-    bool a_ok[CPT], b_ok[CPT];
+    // Lane l of a load instruction fills position l % 8 of row l / 8 of its eight rows.  Rows beyond an operand are read from
+    // its last row (what they give is never used); the part of the last K tile beyond K comes from a place that holds zeros
+    // for A, and B is zero there by itself.
+    const int kc = ((lane & 7) ^ (lane >> 3)) * 8;
+    const unsigned short* src[kLoads];
 #pragma unroll
-    for (int h = 0; h < CPT; ++h) {
-        const int chunk = tid + h * kGemmThreads;
-        const int row = chunk >> 2;
-        kc[h] = (chunk & 3) * 8;
-        lds_off[h] = row * LDS_STRIDE + kc[h];
-        const int am = m0 + row, bn = n0 + row;
-        a_ok[h] = am < g.M;
-        b_ok[h] = bn < g.N;
-        const int amc = min(am, g.M - 1), bnc = min(bn, g.N - 1);
-        a_ptr[h] = g.A + (size_t)(g.a_idx ? g.a_idx[amc] : amc) * g.a_stride;
-        b_ptr[h] = g.B + (size_t)bnc * g.b_stride;
+    for (int h = 0; h < kLoads; ++h) {
+        const int row = 8 * (wave + kGemmWaves * (h % (kLoads / 2))) + (lane >> 3);
+        if (h < kLoads / 2) {
+            const int am = min(m0 + row, g.M - 1);
+            src[h] = g.A + (size_t)(g.a_idx ? g.a_idx[am] : am) * g.a_stride + kb + kc;
+        } else {
+            src[h] = g.B + (size_t)min(n0 + row, g.N - 1) * g.b_stride + kb + kc;
+        }
     }
-    const int klast = g.K - 8;                       // K is a multiple of 8
-    auto fetch = [&](int tile_k, uint4 (&ra)[CPT], uint4 (&rb)[CPT]) {
-        const int k0 = kb + tile_k * TK;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned short*)stages;
+    auto request = [&](int t) {
+        const unsigned at = lds0 + (unsigned)(t % kStages) * (kStageElems * 2) + (unsigned)wave * 1024;
+        const int k0 = kb + t * TK;
 #pragma unroll
-        for (int h = 0; h < CPT; ++h) {
-            const int k = min(k0 + kc[h], klast);
-            ra[h] = *reinterpret_cast<const uint4*>(a_ptr[h] + k);
-            rb[h] = *reinterpret_cast<const uint4*>(b_ptr[h] + k);
+        for (int h = 0; h < kLoads; ++h) {
+            const unsigned short* p = src[h] + t * TK;
+            if (h < kLoads / 2 && k0 + TK > g.K) p = k0 + kc < g.K ? p : g.zeros;
+            load_to_lds(p, at + (unsigned)(h / (kLoads / 2) * TM * TK * 2 + h % (kLoads / 2) * kGemmWaves * 1024));
         }
     };
-    auto masked = [](uint4 v, bool ok) { return ok ? v : make_uint4(0, 0, 0, 0); };
 
     constexpr int NJ = kWN / 32;                     // MFMA tiles side by side per wavefront
     f32x16 acc[2][NJ];
@@ -178,52 +189,51 @@ __global__ void __launch_bounds__(kGemmThreads) gemm_nt_kernel(GemmArgs g)
 
     constexpr int WCOLS = TN / kWN;                  // wavefronts side by side
     const int wm = (wave / WCOLS) * 64, wn = (wave % WCOLS) * kWN;
-    const int frow = lane & 31, fk = (lane >> 5) * 8;
+    const int frow = lane & 31;
 
-    // Ring of kDepth register slots.  A slot goes to LDS, and only then is requested again, so no copy of it is
-    // ever live across a request; the first requests are waited for before the loop (the compiler is free to
-    // reorder them) so that the waits inside the loop count the loop's own requests, oldest slot first.  The
-    // loop has no branch: tiles past the last one are all zeros and add nothing.
-    uint4 ra[kDepth][CPT], rb[kDepth][CPT];
+    auto run = [&](int t0, int t1) {
+        for (int t = t0; t < t1; ++t) {
+            // tile t has landed for this wavefront, then for all; the stage that tile t + kStages - 1 goes to was last read before
+            // the barrier
+            const int newer = min(ntiles - 1 - t, kStages - 2);
+            if (newer >= 2) wait_tiles<2>();
+            else if (newer == 1) wait_tiles<1>();
+            else wait_tiles<0>();
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (t + kStages - 1 < ntiles) request(t + kStages - 1);
+            const unsigned short* st = stages + (t % kStages) * kStageElems;
+            // all operands of the tile first: the matrix instructions then wait for them one after the other
+            constexpr int NK = TK / 16;
+            bf16x8 fa[NK][2], fb[NK][NJ];
 #pragma unroll
-    for (int d = 0; d < kDepth; ++d) fetch(d, ra[d], rb[d]);
-    __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
-    for (int tb = 0; tb < ntiles; tb += kDepth) {
+            for (int ks = 0; ks < NK; ++ks) {
+                const int c = ((2 * ks + (lane >> 5)) ^ (lane & 7)) * 8;
 #pragma unroll
-        for (int d = 0; d < kDepth; ++d) {
-            const int t = tb + d;
-            const int buf = d & 1;                   // kDepth is even, so tile t uses buffer t % 2
-            const int k0 = kb + t * TK;
+                for (int i = 0; i < 2; ++i) fa[ks][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(st + (wm + i * 32 + frow) * TK + c));
 #pragma unroll
-            for (int h = 0; h < CPT; ++h) {
-                const bool kin = k0 + kc[h] < ke;
-                *reinterpret_cast<uint4*>(&As[buf][lds_off[h]]) = masked(ra[d][h], a_ok[h] && kin);
-                *reinterpret_cast<uint4*>(&Bs[buf][lds_off[h]]) = masked(rb[d][h], b_ok[h] && kin);
+                for (int j = 0; j < NJ; ++j) fb[ks][j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(st + (TM + wn + j * 32 + frow) * TK + c));
             }
-            fetch(t + kDepth, ra[d], rb[d]);
-            __syncthreads();                         // tile t visible; the other buffer was last read before this point
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int ks = 0; ks < TK; ks += 16) {
-                bf16x8 fa[2], fb[NJ];
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    fa[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&As[buf][(wm + i * 32 + frow) * LDS_STRIDE + ks + fk]));
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    fb[j] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(&Bs[buf][(wn + j * 32 + frow) * LDS_STRIDE + ks + fk]));
+            for (int ks = 0; ks < NK; ++ks)
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int j = 0; j < NJ; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-            }
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
+            asm volatile("" ::: "memory");
         }
-    }
+    };
+#pragma unroll
+    for (int t = 0; t < kStages - 1; ++t)
+        if (t < ntiles) request(t);
 
     // accumulator layout of the 32 x 32 tile: lane holds column (lane % 32); value v is row
     // 8 * (v / 4) + 4 * (lane / 32) + (v % 4)
     const int ccol = lane & 31, rbase = (lane >> 5) * 4;
     if constexpr (!UPDATE) {
+        run(0, ntiles);
         float* U = g.U + (size_t)split * g.m_pad * g.ldu;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -236,24 +246,33 @@ __global__ void __launch_bounds__(kGemmThreads) gemm_nt_kernel(GemmArgs g)
                     if (r < g.m_pad && c < g.ldu) U[(size_t)r * g.ldu + c] = acc[i][j][v];
                 }
     } else {
-        const float alpha = g.lr_tab ? g.lr_tab[min(g.state->lr_pos + g.u, g.lr_len - 1)] : g.state->alpha;
-        const float scale = alpha * g.inv_nb;
-        float oc1 = 1.f, oc2 = 1.f;
-        if (OPT && g.opt.kind == kOptAdam) opt_corrections(g.opt, g.state->opt_k + g.u + 1, oc1, oc2);
-        // rows are features, columns are classes: W[r][c] -= scale * acc; bf16 copy goes out transposed.
-        // The 32 master weights of a half-quadrant are requested together, from clamped addresses and without a
-        // branch, and only then combined and stored (a branch around each load would wait for it on the spot).
+        // rows are features, columns are classes: W[r][c] -= scale * acc; bf16 copy goes out transposed.  The master weights
+        // are requested from clamped addresses and without a branch (a branch around each load would wait for it on the spot),
+        // a few tiles before they are needed.
+        const int late = max(0, ntiles - kLateTiles);
+        run(0, late);
+        float wv[2][NJ][16];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            float wv[NJ][16];
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const int r = min(m0 + wm + i * 32 + 8 * (v >> 2) + rbase + (v & 3), g.M - 1);
                     const int c = min(n0 + wn + j * 32 + ccol, g.ldw - 1);
-                    wv[j][v] = g.W[(size_t)r * g.ldw + c];
+                    wv[i][j][v] = g.W[(size_t)r * g.ldw + c];
                 }
+        run(late, ntiles);
+        wait_tiles<0>();
+        __builtin_amdgcn_s_barrier();                // all operands read: the stages become the transposed tile
+        asm volatile("" ::: "memory");
+        unsigned short* Ts = stages;
+        const float alpha = g.lr_tab ? g.lr_tab[min(g.state->lr_pos + g.u, g.lr_len - 1)] : g.state->alpha;
+        const float scale = alpha * g.inv_nb;
+        float oc1 = 1.f, oc2 = 1.f;
+        if (OPT && g.opt.kind == kOptAdam) opt_corrections(g.opt, g.state->opt_k + g.u + 1, oc1, oc2);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -264,12 +283,12 @@ __global__ void __launch_bounds__(kGemmThreads) gemm_nt_kernel(GemmArgs g)
                     const bool ok = r < g.M && c < g.ldw;
                     float w = 0.f;
                     if constexpr (!OPT) {
-                        w = ok ? wv[j][v] - scale * acc[i][j][v] : 0.f;
+                        w = ok ? wv[i][j][v] - scale * acc[i][j][v] : 0.f;
                     } else if (ok) {
                         // the state is read here, element by element: this path trades speed for the extra arrays
                         const size_t at = (size_t)r * g.ldw + c;
                         float m = g.opt.m[at], sv = g.opt.kind == kOptAdam ? g.opt.s[at] : 0.f;
-                        w = opt_update(g.opt, wv[j][v], acc[i][j][v] * g.inv_nb, alpha, m, sv, oc1, oc2);
+                        w = opt_update(g.opt, wv[i][j][v], acc[i][j][v] * g.inv_nb, alpha, m, sv, oc1, oc2);
                         g.opt.m[at] = m;
                         if (g.opt.kind == kOptAdam) g.opt.s[at] = sv;
                     }
@@ -476,7 +495,7 @@ SoftmaxDims softmax_dims(int64_t p, int64_t n, int64_t C)
     const int tiles = (d.m_pad / TM) * (d.c_pad / TN);
     int splits = 1;
     const int ktiles = (int)((p + TK - 1) / TK);
-    while (tiles * splits < 256 && splits < 8 && ktiles / (splits * 2) >= 8) splits *= 2;
+    while (tiles * splits < 256 && splits < 8 && ktiles / (splits * 2) >= 4) splits *= 2;
     d.splits = splits;
     d.k_per_split = ((ktiles + splits - 1) / splits) * TK;
     return d;
@@ -539,13 +558,14 @@ hipError_t softmax_step(const SoftmaxStep& s, const SoftmaxDims& d, hipStream_t 
     g.N = d.c_pad;
     g.K = s.p;
     g.k_per_split = d.k_per_split;
+    g.zeros = static_cast<const unsigned short*>(s.WbT) + s.p;   // (padding of the copy's first row: there is some if p is not a multiple of TK)
     g.U = s.U;
     g.ldu = d.c_pad;
     g.m_pad = d.m_pad;
     g.tiles_m = (s.nb + TM - 1) / TM;
     g.tiles_n = d.c_pad / TN;
     g.splits = d.splits;
-    hipLaunchKernelGGL(gemm_nt_kernel<false>, dim3((g.tiles_m * g.tiles_n * g.splits + 7) / 8 * 8), dim3(kGemmThreads), 0, stream, g);
+    hipLaunchKernelGGL(gemm_nt_kernel<false>, dim3((g.tiles_m * g.tiles_n * g.splits + 7) / 8 * 8), dim3(kGemmThreads), kGemmLds, stream, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // 2. residual
@@ -561,7 +581,7 @@ hipError_t softmax_step(const SoftmaxStep& s, const SoftmaxDims& d, hipStream_t 
     h.b_stride = d.n_pad;
     h.N = d.c_pad;
     h.K = d.n_pad;
-    h.k_per_split = d.n_pad;
+    h.k_per_split = d.n_pad;                         // (a multiple of TK)
     h.W = s.W;
     h.WbT = static_cast<unsigned short*>(s.WbT);
     h.ldw = d.c_pad;
@@ -576,9 +596,9 @@ hipError_t softmax_step(const SoftmaxStep& s, const SoftmaxDims& d, hipStream_t 
     h.tiles_n = d.c_pad / TN;
     h.splits = 1;
     if (s.opt.kind != kOptSgd)
-        hipLaunchKernelGGL((gemm_nt_kernel<true, true>), dim3((h.tiles_m * h.tiles_n + 7) / 8 * 8), dim3(kGemmThreads), 0, stream, h);
+        hipLaunchKernelGGL((gemm_nt_kernel<true, true>), dim3((h.tiles_m * h.tiles_n + 7) / 8 * 8), dim3(kGemmThreads), kGemmLds, stream, h);
     else
-        hipLaunchKernelGGL((gemm_nt_kernel<true, false>), dim3((h.tiles_m * h.tiles_n + 7) / 8 * 8), dim3(kGemmThreads), 0, stream, h);
+        hipLaunchKernelGGL((gemm_nt_kernel<true, false>), dim3((h.tiles_m * h.tiles_n + 7) / 8 * 8), dim3(kGemmThreads), kGemmLds, stream, h);
     return hipGetLastError();
 }
 
@@ -595,13 +615,14 @@ hipError_t softmax_launch_loss(const void* X, const int32_t* y, int nb, int p, i
     g.N = d.c_pad;
     g.K = p;
     g.k_per_split = d.k_per_split;
+    g.zeros = static_cast<const unsigned short*>(WbT) + p;
     g.U = U;
     g.ldu = d.c_pad;
     g.m_pad = d.m_pad;
     g.tiles_m = (nb + TM - 1) / TM;
     g.tiles_n = d.c_pad / TN;
     g.splits = d.splits;
-    hipLaunchKernelGGL(gemm_nt_kernel<false>, dim3((g.tiles_m * g.tiles_n * g.splits + 7) / 8 * 8), dim3(kGemmThreads), 0, stream, g);
+    hipLaunchKernelGGL(gemm_nt_kernel<false>, dim3((g.tiles_m * g.tiles_n * g.splits + 7) / 8 * 8), dim3(kGemmThreads), kGemmLds, stream, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(softmax_loss_kernel, dim3((nb + SM_ROWS - 1) / SM_ROWS), dim3(SM_THREADS), 0, stream, U, d.splits, d.m_pad,
@@ -611,7 +632,13 @@ hipError_t softmax_launch_loss(const void* X, const int32_t* y, int nb, int p, i
 
 hipError_t softmax_prepare(const SoftmaxDims& d)
 {
-    // every kernel here stays within the default 64 KiB of LDS (residual kernel: 8 rows of at most 2056 bf16)
+    // the other kernels here stay within the default 64 KiB of LDS (residual kernel: 8 rows of at most 2056 bf16)
+    const void* gemms[3] = {reinterpret_cast<const void*>(gemm_nt_kernel<false>), reinterpret_cast<const void*>(gemm_nt_kernel<true, false>),
+                            reinterpret_cast<const void*>(gemm_nt_kernel<true, true>)};
+    for (const void* k : gemms) {
+        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemmLds);
+        if (e != hipSuccess) return e;
+    }
     return d.c_pad <= 256 * SM_MAXB ? hipSuccess : hipErrorInvalidValue;
 }
 
