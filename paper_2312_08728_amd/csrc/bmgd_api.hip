@@ -53,8 +53,10 @@ struct RunRecord {                                 // events of one buffer, for 
     int n_chain = 0, n_prep = 0;                   // launches of this run with an entry in open_chain / open_prep
 };
 
-// Pinned host memory of a context, for what blocking calls bring from the device: flags, then two areas for rows of theta.
-constexpr size_t kMailHead = 256;
+// Pinned host memory of a context, for what blocking calls bring from the device: flags, sums of an evaluation, then two areas for
+// rows of theta.
+constexpr size_t kMailFlags = 256;
+constexpr size_t kMailHead = kMailFlags + kEvalBlocks * sizeof(double);
 constexpr size_t kMailArea = size_t(1) << 20;      // at most; contexts with a smaller theta take what they need
 constexpr size_t kMaxOpenRuns = 4096;              // runs whose events are held before the oldest half is folded
 
@@ -149,7 +151,7 @@ struct bmgd_ctx {
     RunRecord pending_copy;                        // copy events of the buffer that is loaded but not run
     hipStream_t last_copy = nullptr, last_compute = nullptr;
     bool used_copy = false, used_compute = false;
-    char* mail = nullptr;                          // pinned: kMailHead bytes of flags, two areas of mail_area bytes
+    char* mail = nullptr;                          // pinned: kMailHead bytes of flags and sums, two areas of mail_area bytes
     size_t mail_area = 0;
     hipEvent_t mail_done[2] = {nullptr, nullptr};  // the export that filled an area (large estimates only)
     bool poisoned = false;                         // a run failed or was abandoned: theta is not valid until it is set again
@@ -1340,29 +1342,22 @@ BMGD_API int bmgd_eval_loss(bmgd_ctx* ctx, const void* dev_x, const void* dev_y,
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bmgd_config& c = ctx->cfg;
     double* partial = reinterpret_cast<double*>(static_cast<char*>(ctx->ws) + ctx->lay.eval);
-    std::vector<double> host(kEvalBlocks);
+    // the workgroups' sums go straight to the context's pinned memory, unless several launches add to them
+    double* host = reinterpret_cast<double*>(ctx->mail + kMailFlags);
     double total = 0.0;
+    int nblocks = 0;
     if (c.model == BMGD_SOFTMAX) {
         const SoftmaxDims d = softmax_dims(c.p, c.batch_n, c.n_classes);
-        const int64_t chunk = std::min<int64_t>(c.batch_n, (int64_t)kEvalBlocks * 8);
-        for (int64_t r0 = 0; r0 < rows; r0 += chunk) {
-            const int nb = (int)std::min<int64_t>(chunk, rows - r0);
-            HIP_TRY(ctx, softmax_launch_loss(static_cast<const char*>(dev_x) + (size_t)r0 * c.p * 2,
-                                             static_cast<const int32_t*>(dev_y) + r0, nb, (int)c.p, c.n_classes, ctx->wbt, ctx->u,
-                                             d, partial, s));
-            const int nblocks = (nb + 7) / 8;
-            HIP_TRY(ctx, hipMemcpyAsync(host.data(), partial, (size_t)nblocks * sizeof(double), hipMemcpyDeviceToHost, s));
-            HIP_TRY(ctx, hipStreamSynchronize(s));
-            for (int b = 0; b < nblocks; ++b) total += host[(size_t)b];
-        }
+        HIP_TRY(ctx, softmax_launch_loss(dev_x, static_cast<const int32_t*>(dev_y), rows, (int)c.p, c.n_classes, ctx->wbt, ctx->u, d,
+                                         partial, &nblocks, s));
+        HIP_TRY(ctx, hipMemcpyAsync(host, partial, (size_t)nblocks * sizeof(double), hipMemcpyDeviceToHost, s));
     } else {
-        const int nblocks = (int)std::min<int64_t>(kEvalBlocks, (rows + 3) / 4);
+        nblocks = (int)std::min<int64_t>(kEvalBlocks, (rows + 3) / 4);
         HIP_TRY(ctx, glm_launch_loss(static_cast<const float*>(dev_x), static_cast<const float*>(dev_y), ctx->theta, (int)rows,
-                                     (int)c.p, c.model, partial, nblocks, s));
-        HIP_TRY(ctx, hipMemcpyAsync(host.data(), partial, (size_t)nblocks * sizeof(double), hipMemcpyDeviceToHost, s));
-        HIP_TRY(ctx, hipStreamSynchronize(s));
-        for (int b = 0; b < nblocks; ++b) total += host[(size_t)b];
+                                     (int)c.p, c.model, host, nblocks, s));
     }
+    HIP_TRY(ctx, hipStreamSynchronize(s));
+    for (int b = 0; b < nblocks; ++b) total += host[b];
     *host_out = total / (double)rows;
     return BMGD_OK;
 }

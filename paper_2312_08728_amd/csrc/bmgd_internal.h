@@ -257,10 +257,10 @@ hipError_t softmax_permute_transpose(const void* X, const int32_t* perm, void* X
 hipError_t softmax_step(const SoftmaxStep& s, const SoftmaxDims& d, hipStream_t stream);
 // *state <- (alpha, lr_pos, opt_k), in stream order.
 hipError_t softmax_set_state(SoftmaxState* state, float alpha, int lr_pos, int opt_k, hipStream_t stream);
-// Evaluation: cross-entropy summed over `nb` rows X[row0 .. row0 + nb) (contiguous, nb <= the batch size the context
-// was created with) at the bf16 copy of W: partial[b] for b < ceil(nb / 8) workgroups.
-hipError_t softmax_launch_loss(const void* X, const int32_t* y, int nb, int p, int C, const void* WbT, float* U,
-                               const SoftmaxDims& d, double* partial, hipStream_t stream);
+// Evaluation: cross-entropy summed over `rows` contiguous rows at the bf16 copy of W: partial[b] for b < *nblocks
+// (<= kEvalBlocks) workgroups, after all launches.  U: 8 d.m_pad x d.c_pad floats.
+hipError_t softmax_launch_loss(const void* X, const int32_t* y, int64_t rows, int p, int C, const void* WbT, float* U,
+                               const SoftmaxDims& d, double* partial, int* nblocks, hipStream_t stream);
 // Small mini-batches: the updates of a pass in one persistent kernel (softmax_chain_kernel.hip).
 struct SoftmaxChainArgs {
     float* W;               // fp32 master [p][ldw]

@@ -15,6 +15,8 @@
 // 64 x 32 part as 2 x 1 v_mfma_f32_32x32x16_bf16 tiles.
 #include "bmgd_internal.h"
 
+#include <algorithm>
+
 namespace bmgd {
 
 namespace {
@@ -397,44 +399,45 @@ __global__ void __launch_bounds__(SM_THREADS) softmax_residual_kernel(const floa
 }
 
 // Evaluation: cross-entropy -log softmax(u)[label] of SM_ROWS rows per workgroup from the (split) logits, one row per
-// wavefront, summed in fp64 into partial[blockIdx.x].  Not on the hot path: plain loops.
-__global__ void __launch_bounds__(SM_THREADS) softmax_loss_kernel(const float* __restrict__ U, int splits, int m_pad, int ldu,
+// wavefront with all loads of the row issued up front (as in the residual kernel), summed in fp64; partial[blockIdx.x] is set,
+// or added to if `add` (rows beyond what the logits scratch holds come in further launches, in stream order).
+template <int KB, int SPLITS>
+__global__ void __launch_bounds__(SM_THREADS) softmax_loss_kernel(const float* __restrict__ U, int m_pad, int ldu,
                                                                   const int* __restrict__ y, int nb, int C,
-                                                                  double* __restrict__ partial)
+                                                                  double* __restrict__ partial, int add)
 {
     __shared__ double wsum[SM_ROWS];
     const int lane = threadIdx.x & 63, rr = threadIdx.x >> 6;
     const int i = blockIdx.x * SM_ROWS + rr;
     double l = 0.0;
     if (i < nb) {
+        float4 q[SPLITS][KB];
+#pragma unroll
+        for (int sp = 0; sp < SPLITS; ++sp)
+#pragma unroll
+            for (int k = 0; k < KB; ++k)
+                q[sp][k] = *reinterpret_cast<const float4*>(U + ((size_t)sp * m_pad + i) * ldu + min(4 * lane + 256 * k, ldu - 4));
         const int label = y[i];
-        float u[SM_MAXB][4];
+        float u[KB][4];
         float mx = -INFINITY, ul = 0.f;
 #pragma unroll
-        for (int k = 0; k < SM_MAXB; ++k) {
+        for (int k = 0; k < KB; ++k) {
             const int c = 4 * lane + 256 * k;
+            float4 t = q[0][k];
 #pragma unroll
-            for (int v = 0; v < 4; ++v) u[k][v] = -INFINITY;
-            if (c < ldu) {
-                float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                for (int sp = 0; sp < splits; ++sp) {
-                    const float4 q = *reinterpret_cast<const float4*>(U + ((size_t)sp * m_pad + i) * ldu + c);
-                    t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
-                }
-                const float tv[4] = {t.x, t.y, t.z, t.w};
+            for (int sp = 1; sp < SPLITS; ++sp) { t.x += q[sp][k].x; t.y += q[sp][k].y; t.z += q[sp][k].z; t.w += q[sp][k].w; }
+            const float tv[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (c + v < C) {
-                        u[k][v] = tv[v];
-                        mx = fmaxf(mx, tv[v]);
-                        if (c + v == label) ul = tv[v];
-                    }
+            for (int v = 0; v < 4; ++v) {
+                u[k][v] = c + v < C ? tv[v] : -INFINITY;      // padding classes (and clamped reads) count as -inf
+                mx = fmaxf(mx, u[k][v]);
+                if (c + v < C && c + v == label) ul = tv[v];
             }
         }
         for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
         float sum = 0.f;
 #pragma unroll
-        for (int k = 0; k < SM_MAXB; ++k)
+        for (int k = 0; k < KB; ++k)
 #pragma unroll
             for (int v = 0; v < 4; ++v) sum += expf(u[k][v] - mx);
         for (int o = 32; o >= 1; o >>= 1) {
@@ -446,7 +449,7 @@ __global__ void __launch_bounds__(SM_THREADS) softmax_loss_kernel(const float* _
     if (lane == 0) wsum[rr] = l;
     __syncthreads();
     if (threadIdx.x == 0) {
-        double t = 0.0;
+        double t = add ? partial[blockIdx.x] : 0.0;
         for (int q = 0; q < SM_ROWS; ++q) t += wsum[q];
         partial[blockIdx.x] = t;
     }
@@ -602,32 +605,70 @@ hipError_t softmax_step(const SoftmaxStep& s, const SoftmaxDims& d, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t softmax_launch_loss(const void* X, const int32_t* y, int nb, int p, int C, const void* WbT, float* U,
-                               const SoftmaxDims& d, double* partial, hipStream_t stream)
+namespace {
+
+template <int KB>
+hipError_t launch_loss_k(int splits, int m_pad, int ldu, const float* U, const int32_t* y, int nb, int C, double* partial, bool add,
+                         hipStream_t stream)
 {
-    GemmArgs g{};
-    g.A = static_cast<const unsigned short*>(X);
-    g.a_idx = nullptr;
-    g.a_stride = p;
-    g.M = nb;
-    g.B = static_cast<const unsigned short*>(WbT);
-    g.b_stride = d.p_pad;
-    g.N = d.c_pad;
-    g.K = p;
-    g.k_per_split = d.k_per_split;
-    g.zeros = static_cast<const unsigned short*>(WbT) + p;
-    g.U = U;
-    g.ldu = d.c_pad;
-    g.m_pad = d.m_pad;
-    g.tiles_m = (nb + TM - 1) / TM;
-    g.tiles_n = d.c_pad / TN;
-    g.splits = d.splits;
-    hipLaunchKernelGGL(gemm_nt_kernel<false>, dim3((g.tiles_m * g.tiles_n * g.splits + 7) / 8 * 8), dim3(kGemmThreads), kGemmLds, stream, g);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(softmax_loss_kernel, dim3((nb + SM_ROWS - 1) / SM_ROWS), dim3(SM_THREADS), 0, stream, U, d.splits, d.m_pad,
-                       d.c_pad, y, nb, C, partial);
+    const dim3 grid((nb + SM_ROWS - 1) / SM_ROWS), block(SM_THREADS);
+#define LOSS(S) hipLaunchKernelGGL((softmax_loss_kernel<KB, S>), grid, block, 0, stream, U, m_pad, ldu, y, nb, C, partial, add ? 1 : 0)
+    switch (splits) {
+    case 1: LOSS(1); break;
+    case 2: LOSS(2); break;
+    case 4: LOSS(4); break;
+    case 8: LOSS(8); break;
+    default: return hipErrorInvalidValue;
+    }
+#undef LOSS
     return hipGetLastError();
+}
+
+}  // namespace
+
+// Rows of a chunk: what the logits scratch of the context holds (eight times its mini-batch) in one piece, at most 8192; K is
+// split only where one chunk's tiles leave compute units idle and the scratch has room for the parts.  (A launch pair and a
+// wait per mini-batch-sized chunk cost 25 us each: 0.5 ms for 2,000 rows in mini-batches of 100, 0.03 ms in two chunks.)
+hipError_t softmax_launch_loss(const void* X, const int32_t* y, int64_t rows, int p, int C, const void* WbT, float* U,
+                               const SoftmaxDims& d, double* partial, int* nblocks, hipStream_t stream)
+{
+    const int64_t cap = std::min<int64_t>((int64_t)8 * d.m_pad, 8192);
+    const int chunk = (int)std::min<int64_t>(cap, (rows + TM - 1) / TM * TM);
+    const int tiles = chunk / TM * (d.c_pad / TN), ktiles = (p + TK - 1) / TK;
+    int splits = 1;
+    while (tiles * splits < 256 && (int64_t)chunk * splits * 2 <= cap && ktiles / (splits * 2) >= 4) splits *= 2;
+    *nblocks = (int)((std::min<int64_t>(rows, chunk) + SM_ROWS - 1) / SM_ROWS);
+    for (int64_t r0 = 0; r0 < rows; r0 += chunk) {
+        const int nb = (int)std::min<int64_t>(chunk, rows - r0);
+        GemmArgs g{};
+        g.A = static_cast<const unsigned short*>(X) + (size_t)r0 * p;
+        g.a_idx = nullptr;
+        g.a_stride = p;
+        g.M = nb;
+        g.B = static_cast<const unsigned short*>(WbT);
+        g.b_stride = d.p_pad;
+        g.N = d.c_pad;
+        g.K = p;
+        g.k_per_split = (ktiles + splits - 1) / splits * TK;
+        g.zeros = static_cast<const unsigned short*>(WbT) + p;
+        g.U = U;
+        g.ldu = d.c_pad;
+        g.m_pad = chunk;
+        g.tiles_m = (nb + TM - 1) / TM;
+        g.tiles_n = d.c_pad / TN;
+        g.splits = splits;
+        hipLaunchKernelGGL(gemm_nt_kernel<false>, dim3((g.tiles_m * g.tiles_n * g.splits + 7) / 8 * 8), dim3(kGemmThreads), kGemmLds, stream, g);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        const int blocks = (d.c_pad + 255) / 256;
+        const int32_t* yr = y + r0;
+        e = blocks <= 1   ? launch_loss_k<1>(splits, chunk, d.c_pad, U, yr, nb, C, partial, r0 > 0, stream)
+            : blocks <= 2 ? launch_loss_k<2>(splits, chunk, d.c_pad, U, yr, nb, C, partial, r0 > 0, stream)
+            : blocks <= 4 ? launch_loss_k<4>(splits, chunk, d.c_pad, U, yr, nb, C, partial, r0 > 0, stream)
+                          : launch_loss_k<8>(splits, chunk, d.c_pad, U, yr, nb, C, partial, r0 > 0, stream);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t softmax_prepare(const SoftmaxDims& d)

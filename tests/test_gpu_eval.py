@@ -81,3 +81,28 @@ def test_loss_at_every_row_layout_and_remainder(p):
         assert rc == B.BMGD_OK
         want = O.loss(model, X.astype(np.float64), y.astype(np.float64), theta.astype(np.float64))
         assert abs(float(out.cpu()[0]) - want) <= 2e-5 * abs(want), (p, model, rows)
+
+
+@pytest.mark.parametrize("p,C,batch,rows", [
+    (8, 2, 64, 1),                 # one row
+    (200, 130, 64, 1024),          # exactly what the scratch of 64-row mini-batches holds
+    (200, 130, 64, 1025),          # one row in a second launch
+    (72, 300, 100, 3100),          # several launches, the last one ragged
+    (2048, 40, 300, 500),          # few tiles: K split over workgroups
+    (520, 1100, 128, 700),         # more than 1,024 classes, K not a multiple of the tile
+])
+def test_softmax_loss_in_one_or_several_launches(p, C, batch, rows):
+    """Logits from the bf16 copy of W, taken from the same copy by the reference: what is left are sums of p products in fp32
+    (2^-24 sqrt(p) of their size) and a logarithm, far below 1e-5."""
+    import torch
+    import paper_2312_08728_amd as B
+    gen = torch.Generator().manual_seed(p + rows)
+    X = torch.randn((rows, p), generator=gen).bfloat16()
+    y = torch.randint(0, C, (rows,), generator=gen, dtype=torch.int32)
+    W = (torch.randn((p, C), generator=gen) / p ** 0.5).bfloat16()
+    want = torch.nn.functional.cross_entropy(X.double() @ W.double(), y.long()).item()
+    ctx = B.Context(p, max(rows, batch), batch, 0.1, 1, model=B.BMGD_SOFTMAX, n_classes=C)
+    ctx.set_theta(W.float().numpy())
+    got = ctx.eval_loss(X.cuda(), y.cuda(), rows)
+    ctx.close()
+    assert abs(got - want) <= 1e-5 * abs(want)
