@@ -206,13 +206,19 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_mfma_kernel(const float*
 
 // The chain: one workgroup, theta in LDS (two copies, alternating), the matrices of the coming AHEAD steps
 // already in registers.  Thread (i, seg) = (t / TPR, t % TPR); the TPR lanes of a row add up their parts.
-// OPT: an update rule other than the plain step: separate instantiations, the plain path carries none of it.
-template <int TPR, int KQ, int KS, int AHEAD, bool TAB, bool OPT>
+// RULE: plain steps, momentum / NAG, or Adam: separate instantiations, none carries anything of the others.  What a rule adds
+// sits on the step's critical path, so nothing of it is decided or read late: us per step at p = 37 for NAG 0.31 -> 0.23, for
+// Adam 2.2 -> 0.37 (p = 100: 0.57 -> 0.53 and 2.4 -> 0.70), against one instantiation for all rules.
+enum { kRulePlain = 0, kRuleMomentum = 1, kRuleAdam = 2 };
+constexpr int kCorrSteps = 64;                    // steps whose bias corrections are formed together
+
+template <int TPR, int KQ, int KS, int AHEAD, bool TAB, int RULE>
 __global__ void __launch_bounds__(1024) gram_chain_kernel(const float* __restrict__ gram, float* __restrict__ theta,
                                                           GramLayout L, int nsteps, int period, float alpha,
                                                           const float* __restrict__ lr_tab, int lr_base, int lr_len, OptArgs opt)
 {
     __shared__ __align__(16) float th[2][kGramMaxP + 4 * 16];
+    __shared__ float2 corr[2][RULE == kRuleAdam ? kCorrSteps : 1];
     const int t = threadIdx.x;
     const int i = t / TPR, seg = t % TPR;
     const int p = L.p;
@@ -256,15 +262,34 @@ __global__ void __launch_bounds__(1024) gram_chain_kernel(const float* __restric
     // optimizer state of coordinate i lives in the registers of the lane that updates it
     const bool owner = seg == 0 && row_ok;
     float om = 0.f, os = 0.f;
-    if (OPT && owner) {
+    if (RULE != kRulePlain && owner) {
         om = opt.m[i];
-        if (opt.kind == kOptAdam) os = opt.s[i];
+        if (RULE == kRuleAdam) os = opt.s[i];
     }
+    // Adam's bias corrections do not depend on theta: a wavefront forms those of kCorrSteps steps at once, one block ahead of
+    // their use (two powers in every step, on its critical path, took 0.8 to 2 us of it)
+    auto corrections = [&](int block) {
+        if constexpr (RULE == kRuleAdam) {
+            if (t < kCorrSteps) {
+                float c1, c2;
+                opt_corrections(opt, opt.k_base + block * kCorrSteps + t + 1, c1, c2);
+                corr[block & 1][t] = make_float2(c1, c2);
+            }
+        }
+    };
+    if constexpr (RULE == kRuleAdam) {
+        corrections(0);
+        __syncthreads();
+    }
+    const float nag = RULE == kRuleMomentum && opt.kind == kOptNag ? 1.f : 0.f;
     int cur = 0;
     for (int sb = 0; sb < nsteps; sb += AHEAD) {
 #pragma unroll
         for (int d = 0; d < AHEAD; ++d) {
-            const float a_eff = sb + d < nsteps ? (TAB ? aa[d] : alpha) : 0.f;
+            const int step = sb + d;
+            const float a_eff = step < nsteps ? (TAB ? aa[d] : alpha) : 0.f;
+            // (steps come in order: the block after this one is formed at this one's first step, barriers away from its use)
+            if (RULE == kRuleAdam && step % kCorrSteps == 0) corrections(step / kCorrSteps + 1);
             // Request step s + AHEAD - 1 into the ring slot the previous step has just used up, before this step's
             // arithmetic: the memory pipeline works on the requests of all wavefronts while they compute.
             const int prev = (d + AHEAD - 1) % AHEAD;
@@ -284,30 +309,40 @@ __global__ void __launch_bounds__(1024) gram_chain_kernel(const float* __restric
                 if (j & 1) dot1 = fmaf(ss[d][j], tv, dot1); else dot0 = fmaf(ss[d][j], tv, dot0);
             }
             float dot = dot0 + dot1;
-            const float base = fmaf(a_eff, bb[d], th[cur][ib]);
+            const float own = th[cur][ib];           // (read ahead of the sums below)
+            const float base = fmaf(a_eff, bb[d], own);
+            float2 c = make_float2(1.f, 1.f);
+            if constexpr (RULE == kRuleAdam) c = corr[(step / kCorrSteps) & 1][step % kCorrSteps];
             if (TPR >= 2) dot += dpp_mov<0xB1>(dot);      // lanes ^1
             if (TPR >= 4) dot += dpp_mov<0x4E>(dot);      // lanes ^2
             if (TPR >= 8) dot += dpp_mov<0x141>(dot);     // mirror within 8
             if (TPR >= 16) dot += dpp_mov<0x140>(dot);    // mirror within 16
-            if constexpr (!OPT) {
+            // (steps past the last one leave theta and the state alone)
+            if constexpr (RULE == kRulePlain) {
                 if (owner) th[cur ^ 1][i] = fmaf(-a_eff, dot, base);
-            } else if (owner) {
-                float nv = th[cur][i];
-                if (sb + d < nsteps) {               // steps past the last one leave theta and the state alone
-                    float c1 = 1.f, c2 = 1.f;
-                    if (opt.kind == kOptAdam) opt_corrections(opt, opt.k_base + sb + d + 1, c1, c2);
-                    nv = opt_update(opt, nv, dot - bb[d], a_eff, om, os, c1, c2);
+            } else {
+                const bool active = step < nsteps;
+                const float grad = dot - bb[d];
+                float nm, ns = os, nv;
+                if constexpr (RULE == kRuleMomentum) {
+                    nm = opt.mu * om - a_eff * grad;
+                    nv = nag != 0.f ? own + opt.mu * nm - a_eff * grad : own + nm;
+                } else {
+                    nm = om;
+                    nv = opt_update(opt, own, grad, a_eff, nm, ns, c.x, c.y);
                 }
-                th[cur ^ 1][i] = nv;
+                om = active ? nm : om;
+                os = active ? ns : os;
+                if (owner) th[cur ^ 1][i] = active ? nv : own;
             }
             __syncthreads();
             cur ^= 1;
         }
     }
     for (int c = t; c < p; c += blockDim.x) theta[c] = th[cur][c];
-    if (OPT && owner) {
+    if (RULE != kRulePlain && owner) {
         opt.m[i] = om;
-        if (opt.kind == kOptAdam) opt.s[i] = os;
+        if (RULE == kRuleAdam) opt.s[i] = os;
     }
 }
 
@@ -356,11 +391,16 @@ hipError_t launch_chain(const GramLayout& L, const float* gram, float* theta, in
         hipExtLaunchKernelGGL(kernel, dim3(1), dim3(L.nthr), 0u, stream, start, stop, 0u, gram, theta, L, nsteps, period, alpha, lr_tab,
                               lr_base, lr_len, opt);
     };
-    const bool with_opt = opt.kind != kOptSgd;
-    if (lr_tab && with_opt) go(gram_chain_kernel<TPR, KQ, KS, AHEAD, true, true>);
-    else if (lr_tab) go(gram_chain_kernel<TPR, KQ, KS, AHEAD, true, false>);
-    else if (with_opt) go(gram_chain_kernel<TPR, KQ, KS, AHEAD, false, true>);
-    else go(gram_chain_kernel<TPR, KQ, KS, AHEAD, false, false>);
+    const int rule = opt.kind == kOptSgd ? kRulePlain : opt.kind == kOptAdam ? kRuleAdam : kRuleMomentum;
+    if (lr_tab) {
+        if (rule == kRulePlain) go(gram_chain_kernel<TPR, KQ, KS, AHEAD, true, kRulePlain>);
+        else if (rule == kRuleMomentum) go(gram_chain_kernel<TPR, KQ, KS, AHEAD, true, kRuleMomentum>);
+        else go(gram_chain_kernel<TPR, KQ, KS, AHEAD, true, kRuleAdam>);
+    } else {
+        if (rule == kRulePlain) go(gram_chain_kernel<TPR, KQ, KS, AHEAD, false, kRulePlain>);
+        else if (rule == kRuleMomentum) go(gram_chain_kernel<TPR, KQ, KS, AHEAD, false, kRuleMomentum>);
+        else go(gram_chain_kernel<TPR, KQ, KS, AHEAD, false, kRuleAdam>);
+    }
     return hipGetLastError();
 }
 
@@ -454,10 +494,13 @@ hipError_t gram_launch_chain_steps(const float* gram, float* theta, int p, int n
 {
     if (p < 1 || p > kGramMaxP || nsteps < 1 || period < 1) return hipErrorInvalidValue;
     const GramLayout L = make_layout(p);
-    if (L.tpr == 16) {
+    if (L.tpr == 4) {
         switch (L.kq) {
-        case 0: return launch_chain_ks<16, 0>(L, gram, theta, nsteps, period, alpha, lr_tab, lr_base, lr_len, opt, stream, start, stop);
-        case 1: return launch_chain_ks<16, 1>(L, gram, theta, nsteps, period, alpha, lr_tab, lr_base, lr_len, opt, stream, start, stop);
+        case 0: return launch_chain_ks<4, 0>(L, gram, theta, nsteps, period, alpha, lr_tab, lr_base, lr_len, opt, stream, start, stop);
+        case 1: return launch_chain_ks<4, 1>(L, gram, theta, nsteps, period, alpha, lr_tab, lr_base, lr_len, opt, stream, start, stop);
+        case 2: return launch_chain_ks<4, 2>(L, gram, theta, nsteps, period, alpha, lr_tab, lr_base, lr_len, opt, stream, start, stop);
+        case 3: return launch_chain_ks<4, 3>(L, gram, theta, nsteps, period, alpha, lr_tab, lr_base, lr_len, opt, stream, start, stop);
+        case 4: return launch_chain_ks<4, 4>(L, gram, theta, nsteps, period, alpha, lr_tab, lr_base, lr_len, opt, stream, start, stop);
         }
     } else {
         switch (L.kq) {

@@ -32,7 +32,10 @@ inline GramLayout make_layout(int p)
 {
     GramLayout L{};
     L.p = p;
-    L.tpr = p <= 64 ? 16 : 8;
+    // Up to 64 features a step is bound by its chain of latencies, not by what it reads: fewer wavefronts meet sooner at the
+    // barrier (one, for p <= 16) and the sums of a row take two lane exchanges: 0.115 against 0.142 us per step for 16
+    // threads a row at p = 37, equal at p = 10 and 64.  Beyond, the load path of the one compute unit decides.
+    L.tpr = p <= 64 ? 4 : 8;
     L.nthr = (p * L.tpr + 63) / 64 * 64;
     L.kq = p / (4 * L.tpr);
     const int rem = p - 4 * L.tpr * L.kq;
