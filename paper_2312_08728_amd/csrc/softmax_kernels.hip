@@ -109,6 +109,12 @@ struct GemmArgs {
 // way while one is multiplied, with one barrier per tile.  Rows lie without padding, as the instruction writes them; 16-byte chunk
 // c of row r is kept at position c ^ (r mod 8), so that the eight rows of an operand read fall on different banks.  (The lane
 // picks which chunk it fetches, so the swizzle costs nothing: it is a fixed offset per lane.)
+// Bound by the arrival of the operands: 393 KB per workgroup and launch of the logits at about 50 GB/s per compute unit, 0.64 us
+// per K tile, where the matrix instructions take 512 cycles (without them, loads alone: 13.2 of 15.0 us; reading 64 instead of
+// 96 KB per tile from shared memory, by wavefronts that halve K, changed nothing).  Per launch at n = 1024, p = 3072, C = 1000:
+// logits 16.7 -> 15.0 us (6.6 of it are the launch, the first tile and 16 MB of partial logits), gradient + update 20.8 -> 19.0 us
+// (9.2), against K tiles of 32 staged through registers.  Slower: three stages (+0.4 us per update), four wavefronts of 64 x 64
+// (+2.9), K ranges walked from different starts by different workgroups (+2).
 constexpr int kGemmThreads = 512;
 constexpr int kGemmWaves = kGemmThreads / 64;
 constexpr int kWN = TN * 2 / kGemmWaves;            // columns of the tile per wavefront: 32 (64 rows high)

@@ -79,3 +79,47 @@ def test_values_that_are_not_finite_spread_as_in_three_launches(bad, C):
         got.append(ctx.get_theta())
         ctx.close()
     assert np.array_equal(np.isnan(got[0]), np.isnan(got[1]))
+
+
+def test_row_subset_and_fixed_partitions():
+    import torch
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    w = _case(900, 64, 40, 900, 100, T=3)
+    X, y = wl.dataset(w)
+    sel = np.random.default_rng(3).permutation(900)[:430].astype(np.int32)
+    ref = O.BMGD(w.model, w.p, w.n, w.alpha, w.T, C=w.C, reshuffle=O.FIXED, K_fixed=1)
+    ref.run_buffer(X[sel], y[sel])
+    ref.run_buffer(X, y)
+    ctx = B.Context(w.p, w.N0, w.n, w.alpha, w.T, model=w.model, n_classes=w.C, reshuffle=B.BMGD_RESHUFFLE_FIXED, n_buffers=1)
+    xd, yd, sd = torch.from_numpy(X.view(np.int16)).cuda(), torch.from_numpy(y).cuda(), torch.from_numpy(sel).cuda()
+    s = torch.cuda.Stream()
+    ctx.set_row_subset(sd, len(sel))
+    ctx.run_device_buffer(xd, yd, 900, s)
+    ctx.run_device_buffer(xd, yd, 900, s)
+    got = ctx.get_theta().reshape(ref.theta.shape)
+    ctx.close()
+    assert rel_l2(got, ref.theta) <= 2e-3
+
+
+def test_a_wait_that_runs_out_is_reported_and_recovered_from():
+    """A limit of one microsecond on the exchange, shorter than a trip between workgroups: the kernel gives up by itself."""
+    import torch
+    import paper_2312_08728_amd as B
+    w = _case(1000, 64, 130, 1000, 100, T=2)
+    X, y = wl.dataset(w)
+    xd, yd = torch.from_numpy(X.view(np.int16)).cuda(), torch.from_numpy(y).cuda()
+    s = torch.cuda.Stream()
+    ctx = B.Context(w.p, w.N0, w.n, w.alpha, w.T, model=w.model, n_classes=w.C, barrier_timeout_us=1)
+    try:
+        ctx.run_device_buffer(xd, yd, 1000, s)
+        try:
+            assert np.isfinite(ctx.get_theta()).all()             # (every wait was shorter after all)
+        except B.BmgdError as e:
+            assert e.code == B.BMGD_EHIP
+            with pytest.raises(B.BmgdError):
+                ctx.run_device_buffer(xd, yd, 1000, s)
+            ctx.set_theta(np.zeros((w.p, w.C), dtype=np.float32))
+            assert np.isfinite(ctx.eval_loss(xd, yd, 1000, s))
+    finally:
+        ctx.close()
