@@ -216,7 +216,8 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     const size_t batch = (size_t)a.n32 * a.p32;      // elements of a mini-batch in XP and XTP
 
     if (tid == 0) s_abort = 0;
-    // master weights: lane holds class c0 + 16 j + l16, features 16 tile + 4 lq + v
+    // master weights: lane holds class c0 + 16 j + l16, features 16 tile + 4 lq + v.  Classes beyond C stay zero whatever their
+    // gradient is (0 x Inf is NaN): their logits go through the same row sums as the others', as -infinity.
     float w[FT][NJ][4];
 #pragma unroll
     for (int t = 0; t < FT; ++t)
@@ -224,7 +225,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         for (int j = 0; j < NJ; ++j) {
             const int f0 = 16 * (wave + kWaves * t) + 4 * lq, c = c0 + 16 * j + l16;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) w[t][j][v] = f0 + v < a.p ? a.W[(size_t)(f0 + v) * a.ldw + c] : 0.f;
+            for (int v = 0; v < 4; ++v) w[t][j][v] = f0 + v < a.p && c < a.C ? a.W[(size_t)(f0 + v) * a.ldw + c] : 0.f;
             if (wave + kWaves * t < n_ft) *reinterpret_cast<uint2*>(&Wt[(16 * j + l16) * ws + f0]) = to_bf16x4(w[t][j]);
         }
 
@@ -485,7 +486,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
                 const int c = c0 + 16 * j + l16;
                 if constexpr (!OPT) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) w[t][j][v] -= scale * acc[t][j][v];   // (padding features and classes: their gradient is 0)
+                    for (int v = 0; v < 4; ++v) w[t][j][v] = c < a.C ? w[t][j][v] - scale * acc[t][j][v] : 0.f;
                 } else {
                     float m[4], sv[4];
                     if constexpr (STATE) {

@@ -123,3 +123,33 @@ def test_a_wait_that_runs_out_is_reported_and_recovered_from():
             assert np.isfinite(ctx.eval_loss(xd, yd, 1000, s))
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("optimizer", [0, 1, 3])
+@pytest.mark.parametrize("bad,C", [(np.inf, 10), (np.nan, 10), (-np.inf, 33), (np.nan, 130)])
+def test_a_new_estimate_ends_what_values_that_are_not_finite_left_behind(bad, C, optimizer):
+    """Classes that only fill up the last workgroup stay zero whatever the rows hold: after bmgd_set_theta a run over clean rows
+    is the run of a new context."""
+    import torch
+    import paper_2312_08728_amd as B
+    w = _case(128, 40, C, 128, 64)
+    X, y = wl.dataset(w)
+    clean = torch.from_numpy(X.view(np.int16)).view(torch.bfloat16).cuda()
+    x = clean.clone()
+    x[5, 3] = float(bad)
+    yd, s = torch.from_numpy(y).cuda(), torch.cuda.Stream()
+    w0 = (np.random.default_rng(0).standard_normal((w.p, C)) * 0.1).astype(np.float32)
+    got = []
+    for first in (x, None):
+        ctx = B.Context(w.p, 128, 64, 0.02, 1, model=w.model, n_classes=C, optimizer=optimizer)
+        if first is not None:
+            ctx.set_theta(w0)
+            ctx.run_device_buffer(first, yd, 128, s)
+            assert np.isnan(ctx.get_theta()).any()
+            ctx.reset_optimizer()
+            ctx.set_position(0)
+        ctx.set_theta(w0)
+        ctx.run_device_buffer(clean, yd, 128, s)
+        got.append(ctx.get_theta())
+        ctx.close()
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
