@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(kLossBlock) glm_loss_rows_kernel(const float* 
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
         const int c = V * (lsub + L * k);
-        off[k] = c < p ? c : 0;                      // beyond p: column 0 again, with a zero in theta's place
+        off[k] = c < p ? c : 0;                      // beyond p: column 0 again, dropped below
 #pragma unroll
         for (int v = 0; v < V; ++v) th[k * V + v] = c < p ? theta[c + v] : 0.f;   // (a caller's theta may be 4-byte aligned only)
     }
@@ -519,7 +519,7 @@ __global__ void __launch_bounds__(kLossBlock) glm_loss_rows_kernel(const float* 
         for (int q = 0; q < U; ++q) {
             float t = 0.f;
 #pragma unroll
-            for (int e = 0; e < CPL * V; ++e) t = fmaf(x[q][e], th[e], t);
+            for (int e = 0; e < CPL * V; ++e) t = fmaf(V * (lsub + L * (e / V)) < p ? x[q][e] : 0.f, th[e], t);   // (0 x Inf is NaN)
             d[q] = group_sum(t, L);
         }
 #pragma unroll

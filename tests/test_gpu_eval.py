@@ -106,3 +106,25 @@ def test_softmax_loss_in_one_or_several_launches(p, C, batch, rows):
     got = ctx.eval_loss(X.cuda(), y.cuda(), rows)
     ctx.close()
     assert abs(got - want) <= 1e-5 * abs(want)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf])
+@pytest.mark.parametrize("p", [3, 6, 37, 100, 130, 516, 1000, 2046])
+def test_an_infinite_predictor_gives_an_infinite_loss(p, bad):
+    """Least squares: (x'theta - y)^2 / 2 with one infinite product is infinite, at row lengths that do not fill the lanes which
+    hold a row (what those hold beyond p takes no part, whatever the row's first column is)."""
+    import torch
+    import paper_2312_08728_amd as B
+    rng = np.random.default_rng(p)
+    X = rng.standard_normal((50, p)).astype(np.float32)
+    X[7, 0] = bad
+    y = rng.standard_normal(50).astype(np.float32)
+    theta = (rng.standard_normal(p) / np.sqrt(p)).astype(np.float32)
+    xd, yd, out = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda(), torch.empty(1, dtype=torch.float64, device="cuda")
+    assert B.bmgd_eval_loss_static(B.BMGD_LINEAR, xd, yd, torch.from_numpy(theta).cuda(), 50, p, None, out) == B.BMGD_OK
+    assert float(out.cpu()[0]) == np.inf
+    ctx = B.Context(p, 50, 10, 0.1, 1)
+    ctx.set_theta(theta)
+    got = ctx.eval_loss(xd, yd, 50)
+    ctx.close()
+    assert got == np.inf
