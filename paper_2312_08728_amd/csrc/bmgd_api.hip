@@ -443,10 +443,10 @@ hipStream_t tail_stream(const bmgd_ctx* ctx)
 }
 
 // Wait for everything enqueued, and bring `rows` rows of C floats of `src` (row stride ld) to host_out (rows = 0: nothing) and
-// the failure flags, which are turned into an error.  A kernel behind the last run writes both into the context's pinned
-// memory, so a call costs one launch and one wait (a hipMemcpy each for the flags and for theta cost as much again; a strided
-// hipMemcpy2D of 3,072 rows into ordinary memory took 21 ms).  More than an area holds goes through the two areas in turn: the
-// host copies one out while the device fills the other.
+// the failure flags, which are turned into an error; host_out is written only if there is none.  A kernel behind the last run
+// writes both into the context's pinned memory, so a call costs one launch and one wait (a hipMemcpy each for the flags and for
+// theta cost as much again; a strided hipMemcpy2D of 3,072 rows into ordinary memory took 21 ms).  More than an area holds goes
+// through the two areas in turn: the host copies one out while the device fills the other.
 int drain_and_fetch(bmgd_ctx* ctx, const float* src, int64_t rows, int64_t C, int64_t ld, float* host_out)
 {
     HIP_TRY(ctx, hipSetDevice(ctx->device));
@@ -455,34 +455,38 @@ int drain_and_fetch(bmgd_ctx* ctx, const float* src, int64_t rows, int64_t C, in
     float* area[2] = {reinterpret_cast<float*>(ctx->mail + kMailHead), reinterpret_cast<float*>(ctx->mail + kMailHead + ctx->mail_area)};
     const int64_t per = rows ? std::min<int64_t>(rows, (int64_t)(ctx->mail_area / ((size_t)C * 4))) : 0;
     const int64_t parts = rows ? (rows + per - 1) / per : 1;
-    for (int64_t k = 0; k <= parts; ++k) {
-        if (k < parts) {
-            const int64_t r0 = k * per, n = rows ? std::min(per, rows - r0) : 0;
-            HIP_TRY(ctx, launch_export(area[k & 1], src, r0, n, C, ld, flags, ctx->sync + 1, ts));
-            if (parts > 1) {
-                if (!ctx->mail_done[k & 1]) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->mail_done[k & 1], hipEventDisableTiming));
-                HIP_TRY(ctx, hipEventRecord(ctx->mail_done[k & 1], ts));
-            }
+    auto rows_of = [&](int64_t k) { return rows ? std::min(per, rows - k * per) : 0; };
+    auto request = [&](int64_t k) -> int {
+        HIP_TRY(ctx, launch_export(area[k & 1], src, k * per, rows_of(k), C, ld, flags, ctx->sync + 1, ts));
+        if (parts > 1) {
+            if (!ctx->mail_done[k & 1]) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->mail_done[k & 1], hipEventDisableTiming));
+            HIP_TRY(ctx, hipEventRecord(ctx->mail_done[k & 1], ts));
         }
-        if (k > 0 && rows) {
-            if (parts > 1) HIP_TRY(ctx, hipEventSynchronize(ctx->mail_done[(k - 1) & 1]));
-            else HIP_TRY(ctx, hipStreamSynchronize(ts));
-            const int64_t r0 = (k - 1) * per, n = std::min(per, rows - r0);
-            memcpy(host_out + r0 * C, area[(k - 1) & 1], (size_t)(n * C) * 4);
-        }
-    }
-    HIP_TRY(ctx, hipStreamSynchronize(ts));
+        return BMGD_OK;
+    };
+    int rc = request(0);
+    if (rc != BMGD_OK) return rc;
+    if (parts > 1 && (rc = request(1)) != BMGD_OK) return rc;
+    // Once the first part has arrived so have the flags: all work of the runs precedes it, on this stream or waited for here.
+    if (parts > 1) HIP_TRY(ctx, hipEventSynchronize(ctx->mail_done[0]));
+    else HIP_TRY(ctx, hipStreamSynchronize(ts));
     if (ctx->used_copy) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_copy));
     if (ctx->used_compute && ctx->last_compute != ts) HIP_TRY(ctx, hipStreamSynchronize(ctx->last_compute));
     ctx->chain_pending[0] = ctx->chain_pending[1] = false;
     settle_records(ctx, ctx->open_records.size());
     const unsigned flag[2] = {flags[0], flags[1]};
     if (flag[0] != 0 || flag[1] != 0) {
+        if (parts > 1) HIP_TRY(ctx, hipStreamSynchronize(ts));
         HIP_TRY(ctx, hipMemset(ctx->sync, 0, 64));
         ctx->poisoned = true;
         if (flag[0] != 0)
             return fail(ctx, BMGD_EHIP, "a device-side wait exceeded barrier_timeout_us; the run was abandoned and theta is not valid (set it again with bmgd_set_theta before the next run)");
         return fail(ctx, BMGD_EINVAL, "a row subset held an index outside its buffer (row 0 was used in its place); theta is not valid (set it again with bmgd_set_theta before the next run)");
+    }
+    for (int64_t k = 0; rows && k < parts; ++k) {
+        if (k > 0) HIP_TRY(ctx, hipEventSynchronize(ctx->mail_done[k & 1]));
+        memcpy(host_out + k * per * C, area[k & 1], (size_t)(rows_of(k) * C) * 4);
+        if (k + 2 < parts && (rc = request(k + 2)) != BMGD_OK) return rc;
     }
     return BMGD_OK;
 }

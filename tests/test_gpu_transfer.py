@@ -31,3 +31,30 @@ def test_glm_estimates_come_back_bit_for_bit(p, model):
         assert np.array_equal(ctx.get_theta(), w)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("p,C,model", [(37, 1, 0), (64, 20, 2), (520, 513, 2)])
+def test_a_failed_run_leaves_the_output_alone(p, C, model):
+    """A run that failed (a row subset with an index outside its buffer) is reported before anything is written to the caller's
+    array, also where an estimate comes back in several parts."""
+    import torch
+    import paper_2312_08728_amd as B
+    rows = 64
+    bf16 = model == B.BMGD_SOFTMAX
+    x = torch.randn((rows, p), device="cuda", generator=torch.Generator(device="cuda").manual_seed(p))
+    x = x.bfloat16() if bf16 else x
+    y = torch.zeros(rows, dtype=torch.int32 if bf16 else torch.float32, device="cuda")
+    bad = torch.arange(rows, dtype=torch.int32, device="cuda")
+    bad[3] = rows
+    ctx = B.Context(p, rows, 32, 0.01, 1, model=model, n_classes=C)
+    try:
+        for fetch in (lambda out: B.bmgd_get_theta(ctx.h, out, out.size), lambda out: B.bmgd_get_swa(ctx.h, out, out.size)[0]):
+            ctx.set_row_subset(bad, rows)
+            ctx.run_device_buffer(x, y, rows, None)
+            ctx.swa_update()
+            out = np.full(p * C, 7.0, dtype=np.float32)
+            assert fetch(out) == B.BMGD_EINVAL
+            assert (out == 7.0).all()
+            ctx.set_theta(np.zeros(p * C, dtype=np.float32))
+    finally:
+        ctx.close()
