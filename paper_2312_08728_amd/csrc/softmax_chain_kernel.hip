@@ -5,10 +5,12 @@
 // CLASSES are split over workgroups, 16 to each: a workgroup keeps its columns of W for the whole pass (fp32 master in
 // registers, in the accumulator layout of its gradient tiles; bf16 copy in shared memory, where the logits read it), so
 //     U = X_b W[:, mine]                    needs all features of a row, but nothing of other workgroups;
-//     R = softmax_rows(U) - onehot(y)       needs one number per row from each of the others: log sum exp over its classes;
+//     R = softmax_rows(U) - onehot(y)       needs two numbers per row from each of the others: the maximum of its classes and
+//                                           their sum of e^(u - maximum);
 //     W[:, mine] -= (alpha / n_b) X_b' R    is again the workgroup's own.
-// One number per row and workgroup is all that is exchanged (flagged words, glm_device.h: one trip over the fabric per update;
-// none at all for up to 16 classes).  The mini-batch is read by every workgroup from its L2, twice per update (rows for the
+// Two numbers per row and workgroup are all that is exchanged (flagged words, glm_device.h: one trip over the fabric per update;
+// none at all for up to 16 classes).  (Joined into one, the log of the sum on top of the maximum, they would cost a word less, but
+// the probabilities would be off by the spacing of fp32 at the size of the logits.)  The mini-batch is read by every workgroup from its L2, twice per update (rows for the
 // logits, transposed for the gradient), laid out once per pass in the order in which the matrix instructions take their
 // operands (pack_kernel): one contiguous KiB per load instruction, requested ahead, the next update's first ones before
 // this update's gradient.
@@ -45,16 +47,16 @@ __device__ __forceinline__ uint2 to_bf16x4(const float (&v)[4])
     return __builtin_bit_cast(uint2, __builtin_convertvector((f32x4_{v[0], v[1], v[2], v[3]}), bf16x4_));
 }
 
-// e^x for x <= 0 or NaN: 2^t with t = x log2 e rounded, times 1 + what the rounding lost.  Relative error below 2^-22 down to
-// x = -87, where expf is as good, at half its instructions (results below 2^-126, which expf would still give, become 0).
+// e^x for x <= 0 or NaN: 2^n 2^f with n = x log2 e rounded to a whole number and f what is left (log2 e in two parts), in eight
+// instructions.  As good as expf: over [-87, 0] a relative error of at most 8.5e-8 (2.7e-8 rms; expf 8.4e-8 and 2.6e-8), and the
+// subnormal numbers below to their last unit.
 __device__ __forceinline__ float exp_neg(float x)
 {
-    constexpr float kLog2e = 1.44269502f, kLog2eLo = 1.92596299e-8f, kLn2 = 0.693147182f;
-    x = x < -126.f ? -126.f : x;                     // (keeps a NaN; e^-126 is 0 here)
-    const float t = x * kLog2e;
-    const float lost = fmaf(x, kLog2eLo, fmaf(x, kLog2e, -t));
-    const float e = __builtin_amdgcn_exp2f(t);
-    return fmaf(e, lost * kLn2, e);
+    constexpr float kLog2e = 1.44269502f, kLog2eLo = 1.92596299e-8f, kRound = 12582912.f;   // 1.5 x 2^23: the sum's last bit is 1
+    x = x < -200.f ? -200.f : x;                     // (keeps a NaN; e^-200 is 0)
+    const float t = fmaf(x, kLog2e, kRound);
+    const float f = fmaf(x, kLog2eLo, fmaf(x, kLog2e, kRound - t));
+    return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), __builtin_bit_cast(int, t) - __builtin_bit_cast(int, kRound));
 }
 
 // The mini-batches of a pass in operand order, zeros beyond their rows and features:
@@ -131,17 +133,32 @@ __device__ __forceinline__ float quad_select(float x0, float x1, float x2, float
 
 __device__ __forceinline__ float as_float(unsigned v) { return __builtin_bit_cast(float, v); }
 
-// Pairs of flagged words requested back to back and awaited together (see ll_load4).
+// Pairs of flagged words (one row's two numbers each) requested back to back and awaited together (see ll_load4).
 constexpr int kPolls = 4;
-__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[4], u32x4 (&w)[4])
+__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[1][4], u32x4 (&w)[1][4])
 {
     asm volatile("global_load_dwordx4 %0, %4, off sc1\n\t"
                  "global_load_dwordx4 %1, %5, off sc1\n\t"
                  "global_load_dwordx4 %2, %6, off sc1\n\t"
                  "global_load_dwordx4 %3, %7, off sc1\n\t"
                  "s_waitcnt vmcnt(0)"
-                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
-                 : "v"(src[0]), "v"(src[1]), "v"(src[2]), "v"(src[3])
+                 : "=&v"(w[0][0]), "=&v"(w[0][1]), "=&v"(w[0][2]), "=&v"(w[0][3])
+                 : "v"(src[0][0]), "v"(src[0][1]), "v"(src[0][2]), "v"(src[0][3])
+                 : "memory");
+}
+__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[2][4], u32x4 (&w)[2][4])
+{
+    asm volatile("global_load_dwordx4 %0, %8, off sc1\n\t"
+                 "global_load_dwordx4 %1, %9, off sc1\n\t"
+                 "global_load_dwordx4 %2, %10, off sc1\n\t"
+                 "global_load_dwordx4 %3, %11, off sc1\n\t"
+                 "global_load_dwordx4 %4, %12, off sc1\n\t"
+                 "global_load_dwordx4 %5, %13, off sc1\n\t"
+                 "global_load_dwordx4 %6, %14, off sc1\n\t"
+                 "global_load_dwordx4 %7, %15, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(w[0][0]), "=&v"(w[0][1]), "=&v"(w[0][2]), "=&v"(w[0][3]), "=&v"(w[1][0]), "=&v"(w[1][1]), "=&v"(w[1][2]), "=&v"(w[1][3])
+                 : "v"(src[0][0]), "v"(src[0][1]), "v"(src[0][2]), "v"(src[0][3]), "v"(src[1][0]), "v"(src[1][1]), "v"(src[1][2]), "v"(src[1][3])
                  : "memory");
 }
 
@@ -205,7 +222,8 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     const int ws = a.p32 + 8, rs = a.n32 + 8;        // row strides: 16 bytes past a multiple of 64, so that eight rows fall on different banks
     unsigned short* Wt = smem;                       // [16][ws] bf16 copy of W, class-major
     unsigned short* Rt = Wt + kClasses * ws;         // [16][rs] residual, class-major
-    float* lse = reinterpret_cast<float*>(Rt + kClasses * rs);   // [J][R] log sum exp of a row over the classes of a share of the workgroups
+    float* rmax = reinterpret_cast<float*>(Rt + kClasses * rs);  // [J][R] a row's maximum over the classes of a share of the workgroups
+    float* rsum = rmax + kMaxRows;                               // [J][R] ... and its sum of e^(u - that)
     __shared__ int s_abort;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -228,6 +246,10 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
             for (int v = 0; v < 4; ++v) w[t][j][v] = f0 + v < a.p && c < a.C ? a.W[(size_t)(f0 + v) * a.ldw + c] : 0.f;
             if (wave + kWaves * t < n_ft) *reinterpret_cast<uint2*>(&Wt[(16 * j + l16) * ws + f0]) = to_bf16x4(w[t][j]);
         }
+
+    unsigned real[NJ];                               // all bits for a class, none for one that fills up the workgroup
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) real[j] = c0 + 16 * j + l16 < a.C ? ~0u : 0u;
 
     // state of the update rule, laid out like W: in registers beside W where there is room, else read and written in memory
     constexpr bool STATE = OPT && FT <= 2;
@@ -292,9 +314,10 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     start_l(a.XP);
     if constexpr (EARLY_G) start_g(a.XTP);
 
-    // polling: RB consecutive threads take two neighbouring rows each, J such groups share the workgroups
-    const int R = (a.n32 + 127) / 128 * 128, RB = R / 2, J = min(G, kThreads / RB);
-    const int pj = tid / RB, pr = 2 * (tid - pj * RB);
+    // polling: a thread per row, J such groups share the workgroups; for more than 512 rows two rows a thread, 512 apart
+    constexpr int ROWS = RT == kMaxTiles ? 2 : 1;
+    const int R = (a.n32 + 63) / 64 * 64, J = min(G, max(1, kThreads / R));
+    const int pj = tid / R, pr = tid - pj * R;
     const size_t words_set = (size_t)G * a.word_stride;
     PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
     __syncthreads();
@@ -334,7 +357,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         if constexpr (EARLY_L) start_l(next);
         if constexpr (!EARLY_G) start_g(xt);
 
-        // u <- exp(u - mx) (0 for padding classes); mx and log sum exp of every row over this workgroup's classes
+        // u <- exp(u - mx) (0 for padding classes); mx and sum of every row over this workgroup's classes
         float mx[RT], own[RT];
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
@@ -356,53 +379,62 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
                 sv[v] = sum16(sum);
             }
             mx[t] = quad_select(sm[0], sm[1], sm[2], sm[3], l16);
-            own[t] = mx[t] + logf(quad_select(sv[0], sv[1], sv[2], sv[3], l16));
+            own[t] = quad_select(sv[0], sv[1], sv[2], sv[3], l16);
             __builtin_amdgcn_sched_barrier(0);           // (one tile's exponentials at a time: all of them together take too many registers)
         }
         if (G > 1) {
             unsigned long long* out = a.words + (size_t)(s & 1) * words_set + (size_t)g * a.word_stride;
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
+                // lanes 0 .. 3 of each 16 hold the four rows' maxima, lanes 4 .. 7 publish their sums
                 const int row = 16 * (wave + kWaves * t) + 4 * lq + (l16 & 3);
-                if (t < my_rt && l16 < 4 && row < nb) ll_store(out + row, own[t], tag);
+                if (t < my_rt && l16 < 8 && row < nb) ll_store(out + 2 * row + (l16 >> 2), l16 < 4 ? mx[t] : own[t], tag);
             }
             const unsigned long long* in = a.words + (size_t)(s & 1) * words_set;
             bool gave_up = false;
             if (pj < J && pr < nb) {
-                // two flagged words per load; a second row beyond the mini-batch is never published and not waited for
-                const bool second = pr + 1 < nb;
                 __builtin_amdgcn_s_sleep(8);             // (0.2 us: a poll sent at once comes back a moment before the words do)
-                float m[2] = {-FLT_MAX, -FLT_MAX}, sum[2] = {0.f, 0.f};
-                for (int q0 = pj; q0 < G && !gave_up; q0 += kPolls * J) {
-                    const unsigned long long* src[kPolls];
-                    u32x4 word[kPolls];
+                float m[ROWS], sum[ROWS];
 #pragma unroll
-                    for (int q = 0; q < kPolls; ++q) src[q] = in + (size_t)min(q0 + q * J, G - 1) * a.word_stride + pr;
+                for (int i = 0; i < ROWS; ++i) { m[i] = -FLT_MAX; sum[i] = 0.f; }
+                for (int q0 = pj; q0 < G && !gave_up; q0 += kPolls * J) {
+                    const unsigned long long* src[ROWS][kPolls];
+                    u32x4 word[ROWS][kPolls];
+#pragma unroll
+                    for (int i = 0; i < ROWS; ++i)       // (a second row beyond the mini-batch: its last one again)
+#pragma unroll
+                        for (int q = 0; q < kPolls; ++q) src[i][q] = in + (size_t)min(q0 + q * J, G - 1) * a.word_stride + 2 * min(pr + kThreads * i, nb - 1);
                     guard.arm();
                     while (true) {
                         load_pairs(src, word);
                         bool ok = true;
 #pragma unroll
-                        for (int q = 0; q < kPolls; ++q) ok = ok && word[q].y == tag && (word[q].w == tag || !second);
+                        for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+                            for (int q = 0; q < kPolls; ++q) ok = ok && word[i][q].y == tag && word[i][q].w == tag;
                         if (ok) break;
                         if (guard.expired()) { gave_up = true; break; }
                     }
 #pragma unroll
-                    for (int i = 0; i < 2; ++i) {
+                    for (int i = 0; i < ROWS; ++i) {
                         float v[kPolls], top = m[i];
 #pragma unroll
                         for (int q = 0; q < kPolls; ++q) {
-                            v[q] = q0 + q * J < G ? as_float(i ? word[q].z : word[q].x) : -INFINITY;
+                            v[q] = q0 + q * J < G ? as_float(word[i][q].x) : -INFINITY;
                             top = fmaxf(top, v[q]);
                         }
                         sum[i] *= exp_neg(m[i] - top);
 #pragma unroll
-                        for (int q = 0; q < kPolls; ++q) sum[i] += exp_neg(v[q] - top);
+                        for (int q = 0; q < kPolls; ++q) sum[i] = fmaf(as_float(word[i][q].z), exp_neg(v[q] - top), sum[i]);
                         m[i] = top;
                     }
                 }
-                lse[pj * R + pr] = m[0] + logf(sum[0]);
-                lse[pj * R + pr + 1] = m[1] + logf(sum[1]);
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i)
+                    if (pr + kThreads * i < nb) {
+                        rmax[pj * R + pr + kThreads * i] = m[i];
+                        rsum[pj * R + pr + kThreads * i] = sum[i];
+                    }
                 if (gave_up) s_abort = 1;
             }
             __syncthreads();
@@ -413,25 +445,25 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         for (int t = 0; t < RT; ++t) {
             if (t >= my_rt) break;
             const int r0 = 16 * (wave + kWaves * t) + 4 * lq;
-            float total = own[t];
+            float top = mx[t], sum = own[t];
             if (G > 1) {
-                const int r = min(r0 + (l16 & 3), a.n32 - 1);
+                const int r = min(r0 + (l16 & 3), nb - 1);
                 if (J == 1) {
-                    total = lse[r];
+                    top = rmax[r];
+                    sum = rsum[r];
                 } else {
                     // the four lanes that keep the same row take every fourth share, then meet
-                    const int j0 = l16 >> 2;
-                    const float v0 = j0 < J ? lse[j0 * R + r] : -INFINITY, v1 = j0 + 4 < J ? lse[(j0 + 4) * R + r] : -INFINITY;
-                    float m = fmaxf(fmaxf(v0, v1), -FLT_MAX);
-                    m = fmaxf(m, dpp_mov<0x124>(m));
-                    m = fmaxf(m, dpp_mov<0x128>(m));
-                    float sum = exp_neg(v0 - m) + exp_neg(v1 - m);
+                    const int j0 = min(l16 >> 2, J - 1) * R + r, j1 = min((l16 >> 2) + 4, J - 1) * R + r;
+                    const float v0 = (l16 >> 2) < J ? rmax[j0] : -INFINITY, v1 = (l16 >> 2) + 4 < J ? rmax[j1] : -INFINITY;
+                    top = fmaxf(fmaxf(v0, v1), -FLT_MAX);
+                    top = fmaxf(top, dpp_mov<0x124>(top));
+                    top = fmaxf(top, dpp_mov<0x128>(top));
+                    sum = rsum[j0] * exp_neg(v0 - top) + rsum[j1] * exp_neg(v1 - top);
                     sum += dpp_mov<0x124>(sum);
                     sum += dpp_mov<0x128>(sum);
-                    total = m + logf(sum);
                 }
             }
-            const float fq = exp_neg(mx[t] - total);
+            const float fq = exp_neg(mx[t] - top) / sum;
             const float f[4] = {dpp_mov<0x00>(fq), dpp_mov<0x55>(fq), dpp_mov<0xAA>(fq), dpp_mov<0xFF>(fq)};
             const float lq_ = __builtin_bit_cast(float, label[t]);
             const int y[4] = {__builtin_bit_cast(int, dpp_mov<0x00>(lq_)), __builtin_bit_cast(int, dpp_mov<0x55>(lq_)),
@@ -486,7 +518,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
                 const int c = c0 + 16 * j + l16;
                 if constexpr (!OPT) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) w[t][j][v] = c < a.C ? w[t][j][v] - scale * acc[t][j][v] : 0.f;
+                    for (int v = 0; v < 4; ++v) w[t][j][v] = as_float(__builtin_bit_cast(unsigned, w[t][j][v] - scale * acc[t][j][v]) & real[j]);
                 } else {
                     float m[4], sv[4];
                     if constexpr (STATE) {
@@ -536,7 +568,7 @@ int round32(int64_t v) { return (int)((v + 31) / 32 * 32); }
 
 size_t chain_lds(int n32, int p32)
 {
-    return (size_t)kClasses * (size_t)(p32 + 8 + n32 + 8) * 2 + kMaxRows * 4;
+    return (size_t)kClasses * (size_t)(p32 + 8 + n32 + 8) * 2 + 2 * kMaxRows * 4;
 }
 
 // tiles per wavefront, rounded up to a compiled variant: index into {1, 2, 4, 8}
@@ -586,7 +618,7 @@ size_t softmax_chain_pack_bytes(int64_t p, int64_t n, int64_t batches)
 
 size_t softmax_chain_words_bytes(int64_t n, int64_t C)
 {
-    return (size_t)2 * ((C + kClasses - 1) / kClasses) * round32(n) * 8;
+    return (size_t)2 * ((C + kClasses - 1) / kClasses) * round32(n) * 16;
 }
 
 hipError_t softmax_chain_prepare(int64_t p, int64_t n, int64_t C, bool opt, int num_cus, bool* fits)
@@ -615,7 +647,7 @@ hipError_t softmax_chain_pass(const void* X, const int32_t* y, const int32_t* pe
     a.n32 = round32(a.n);
     a.p32 = round32(a.p);
     a.M = (a.rows + a.n - 1) / a.n;
-    a.word_stride = a.n32;
+    a.word_stride = 2 * a.n32;
     if (a.n32 > kMaxRows || a.p32 > kMaxRows || a.C > a.ldw) return hipErrorInvalidValue;
     const size_t half = (size_t)a.M * a.n32 * a.p32;
     unsigned short* xp = static_cast<unsigned short*>(pack);

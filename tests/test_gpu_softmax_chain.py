@@ -153,3 +153,29 @@ def test_a_new_estimate_ends_what_values_that_are_not_finite_left_behind(bad, C,
         got.append(ctx.get_theta())
         ctx.close()
     assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
+
+
+def test_rows_that_are_all_but_certain_keep_their_residual():
+    """P - 1 of a class whose logit stands 12 above all others, at logits of 340: 1.2e-4, which a normaliser kept as one fp32
+    number of that size (spacing 3e-5) would lose.  The residual is rounded to bf16 (2^-9 of it), 1 - P to fp32 (2^-24, 2^-11 of
+    the difference): 2^-8 in all."""
+    import torch
+    import paper_2312_08728_amd as B
+    n, p, C = 64, 8, 20
+    gen = torch.Generator().manual_seed(1)
+    x = torch.zeros((n, p))
+    x[:, 0] = 1.0
+    x[:, 1:] = torch.rand((n, p - 1), generator=gen) + 0.5
+    x = x.bfloat16()
+    w0 = np.zeros((p, C), dtype=np.float32)
+    w0[0], w0[0, 0] = 328.0, 340.0                         # exact in bf16
+    prob = torch.softmax(torch.from_numpy(w0[0]).double(), 0)
+    prob[0] = -prob[1:].sum()                              # the residual of class 0, the label of every row
+    want = -0.5 * x.double().mean(0)[1:, None] * prob[None, :]
+    for chain in (B.BMGD_CHAIN_AUTO, B.BMGD_CHAIN_LAUNCH):
+        ctx = B.Context(p, n, n, 0.5, 1, model=B.BMGD_SOFTMAX, n_classes=C, chain=chain)
+        ctx.set_theta(w0)
+        ctx.run_device_buffer(x.cuda(), torch.zeros(n, dtype=torch.int32, device="cuda"), n, None)
+        got = ctx.get_theta()[1:]
+        ctx.close()
+        assert np.abs(got / want.numpy() - 1.0).max() <= 2.0 ** -8, chain
