@@ -49,9 +49,9 @@
  *   - If no usable GPU is present every call that needs one fails with
  *     BMGD_EHIP; there is no CPU fallback.
  *   - A run that fails after part of its work has been enqueued, a device-side wait that exceeds
- *     barrier_timeout_us (the persistent kernels need all their workgroups resident at once: work of
- *     other streams that holds compute units for longer than the limit makes a run give up; it exits by
- *     itself and the next blocking call returns BMGD_EHIP) and a row subset with an index outside its
+ *     barrier_timeout_us (the persistent kernels of least squares and logistic regression need all their
+ *     workgroups resident at once: work of other streams that holds compute units for longer than the limit
+ *     makes a run give up; it exits by itself and the next blocking call returns BMGD_EHIP) and a row subset with an index outside its
  *     buffer leave theta undefined.  From then on every run call returns BMGD_ESTATE until theta has been
  *     set again with bmgd_set_theta() (bmgd_set_position() and bmgd_reset_optimizer() restore the rest of
  *     a checkpoint); nothing is retried automatically, because runs enqueued behind the failed one have
@@ -118,7 +118,10 @@ enum {
                                     BMGD_CHAIN_LAUNCH issues the same launches one by one.  BMGD_CHAIN_AUTO (reported
                                     as this mode) runs all updates of a pass in one persistent kernel instead where
                                     mini-batches are small (batch_n, p <= 1024 and batch_n p <= 2^18; with a
-                                    buffered method of its own state p <= 512 and batch_n p <= 2^17). */
+                                    buffered method of its own state p <= 512 and batch_n p <= 2^17).  Its workgroups
+                                    meet before the first update; where other work keeps some of them from running
+                                    (for an eighth of barrier_timeout_us, or for about the time that follows), one of them
+                                    makes the pass alone: slower, the same sums, and not an error. */
     BMGD_CHAIN_PRODUCT = 5       /* least squares with p <= 128 and plain steps (BMGD_OPT_SGD) only: the moment form of
                                     BMGD_CHAIN_GRAM with steps multiplied together.  A step of eq. (3.1) is the affine map
                                     [theta; 1] <- A_m [theta; 1], A_m = [[I - alpha Sxx_m, alpha Sxy_m], [0, 1]], and no A_m
@@ -165,7 +168,7 @@ typedef struct bmgd_config {
                               reports what is used) */
     int64_t  barrier_timeout_us; /* upper bound on any single device-side wait; 0 = default (2 s).
                               A wait that exceeds it makes the kernel exit and the next blocking call
-                              return BMGD_EHIP. */
+                              return BMGD_EHIP (softmax: see BMGD_CHAIN_GRAPH). */
     void*    workspace;    /* optional device memory for everything the context needs on the device;
                               NULL = the library allocates (and frees) it.  Must be 256-byte aligned and
                               stay valid until bmgd_destroy(). */

@@ -727,7 +727,14 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                     sa.words = ctx->sm_words;
                     sa.tag_base = ctx->tag_epoch;
                     sa.sync = ctx->sync;
-                    sa.timeout_ticks = ticks;
+                    // Workgroups that have met are all running, so their waits end by themselves: the limit is only there to end a
+                    // kernel on a device that fails.  They are given as long to meet as the pass takes a workgroup alone (about
+                    // 10 us per update and share of the classes), but give way well before another persistent kernel of this
+                    // library, which may be waiting for the units they hold, runs out of its limit.
+                    sa.timeout_ticks = 1000000000LL;
+                    sa.meeting = ctx->sync + 8;
+                    sa.meeting_ticks = ticks < 1000 ? 0 : std::min<long long>(std::min<long long>(ticks / 8, 200000000LL),
+                                                                              std::max<long long>(100000, 1000 * M * ((c.n_classes + 15) / 16)));
                     sa.alpha = (float)c.lr;
                     sa.lr_tab = lr_len ? ctx->lr_tab_dev : nullptr;
                     sa.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));

@@ -270,7 +270,9 @@ struct SoftmaxChainArgs {
     unsigned long long* words;     // [2][G][word_stride] flagged words, by step parity: two per row, its maximum and its sum
     unsigned tag_base;      // tag of update s of the pass is tag_base + s + 1
     unsigned* sync;         // [1] abort flag
-    long long timeout_ticks;
+    long long timeout_ticks;       // of a wait for workgroups known to be running
+    unsigned* meeting;      // where the workgroups count themselves before the first update (cleared by the pass's first launch)
+    long long meeting_ticks;       // how long the first one waits for the others before it makes the pass alone; 0: not at all
     float alpha;
     const float* lr_tab;    // optional learning rate per update: update s uses lr_tab[min(lr_base + s, lr_len - 1)]
     int lr_base, lr_len;

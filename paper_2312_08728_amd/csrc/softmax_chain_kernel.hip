@@ -15,6 +15,10 @@
 // operands (pack_kernel): one contiguous KiB per load instruction, requested ahead, the next update's first ones before
 // this update's gradient.
 //
+// The exchange needs all workgroups of the launch resident at once, which work of other streams and processes can prevent.  So they
+// meet before the first update (gather_workgroups): where they do not within a given time, one of them makes the whole pass by
+// itself, class share by class share (pass_alone, the same sums in the same order), and the others leave.
+//
 // What bounds it: the trip over the fabric for small mini-batches, and one compute unit's load path (4 n p bytes per update)
 // for larger ones (softmax_chain_eligible says where the line to the three launches lies).
 #include "bmgd_internal.h"
@@ -67,8 +71,9 @@ __device__ __forceinline__ float exp_neg(float x)
 __global__ void __launch_bounds__(256) pack_kernel(const unsigned short* __restrict__ X, const int* __restrict__ y,
                                                    const int* __restrict__ perm, unsigned short* __restrict__ XP,
                                                    unsigned short* __restrict__ XTP, int* __restrict__ YL, int rows, int p, int n,
-                                                   int n32, int p32, int jtiles)
+                                                   int n32, int p32, int jtiles, unsigned* __restrict__ meeting)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *meeting = 0;    // (of the launch that follows)
     constexpr int TS = 72;                           // tile row stride in elements: 16-byte aligned rows
     __shared__ __align__(16) unsigned short tile[64 * TS];
     const int m = blockIdx.x / jtiles, jt = blockIdx.x % jtiles;
@@ -208,6 +213,293 @@ __device__ __forceinline__ void stream(int n, Fetch fetch, Use use)
         if (k + D + d < n) use(k + D + d, d);
 }
 
+// The workgroups of a launch meet: every one counts itself in `meeting`, and the first one may close the meeting for all if some
+// have not come in time.  Called by one thread of each workgroup: enter first, then (after whatever can be done meanwhile) wait.
+enum { kTogether, kAlone, kLeave };
+constexpr unsigned kClosed = 1u << 31;
+__device__ __forceinline__ unsigned enter_meeting(unsigned* meeting)
+{
+    return __hip_atomic_fetch_add(meeting, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ int wait_for_meeting(unsigned* meeting, unsigned ticket, unsigned G, long long ticks, PollGuard& guard)
+{
+    if (ticket & kClosed) return kLeave;
+    const long long t0 = wall_clock64();
+    unsigned seen = ticket + 1;
+    guard.arm();
+    while (seen != G) {
+        if (seen & kClosed) return kLeave;
+        if (ticket == 0 && wall_clock64() - t0 > ticks) {
+            // (a workgroup that comes in between makes the exchange fail, and the loop looks again)
+            if (__hip_atomic_compare_exchange_strong(meeting, &seen, seen | kClosed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                return kAlone;
+            continue;
+        }
+        if (guard.expired()) return kLeave;          // (the first one always decides long before this)
+        seen = __hip_atomic_load(meeting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return kTogether;
+}
+
+// u <- exp(u - mx) (0 for padding classes) for a tile's four rows per lane; mx and sum of every row over a workgroup's classes.
+// (What is kept per row sits in lane l16 & 3 = v of each quad for row 4 lq + v; the residual hands it round.)
+__device__ __forceinline__ void row_sums(f32x4 (&u)[NJ], int l16, float& mx, float& own)
+{
+    float sm[4], sv[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        float m = -FLT_MAX;                          // (finite: a row of nothing but -infinity gets zeros here, not NaN)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) m = fmaxf(m, u[j][v]);
+        m = max16(m);
+        float sum = 0.f;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            u[j][v] = exp_neg(u[j][v] - m);
+            sum += u[j][v];
+        }
+        sm[v] = m;
+        sv[v] = sum16(sum);
+    }
+    mx = quad_select(sm[0], sm[1], sm[2], sm[3], l16);
+    own = quad_select(sv[0], sv[1], sv[2], sv[3], l16);
+}
+
+// lanes 0 .. 3 of each 16 hold the maxima of a tile's rows row0 .. row0 + 3, lanes 4 .. 7 publish their sums
+__device__ __forceinline__ void publish_rows(unsigned long long* out, int row0, int nb, int l16, float mx, float own, unsigned tag)
+{
+    const int row = row0 + (l16 & 3);
+    if (l16 < 8 && row < nb) ll_store(out + 2 * row + (l16 >> 2), l16 < 4 ? mx : own, tag);
+}
+
+// How the threads of a workgroup share the polling: a thread per row, J groups of R threads that share the workgroups; for
+// more than 512 rows two rows a thread, 512 apart.
+struct PollShape {
+    int R, J, pj, pr;
+    __device__ __forceinline__ PollShape(int n32, int G, int tid)
+    {
+        R = (n32 + 63) / 64 * 64;
+        J = min(G, max(1, kThreads / R));
+        pj = tid / R;
+        pr = tid - pj * R;
+    }
+};
+
+// Every row's maximum and sum over the workgroups of this thread's share, into rmax and rsum [J][R].  False: given up.
+template <int ROWS>
+__device__ __forceinline__ bool collect_rows(const unsigned long long* in, int word_stride, int G, int nb, unsigned tag, const PollShape& ps,
+                                             PollGuard& guard, float* rmax, float* rsum)
+{
+    if (ps.pj >= ps.J || ps.pr >= nb) return true;
+    bool gave_up = false;
+    float m[ROWS], sum[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) { m[i] = -FLT_MAX; sum[i] = 0.f; }
+    for (int q0 = ps.pj; q0 < G && !gave_up; q0 += kPolls * ps.J) {
+        const unsigned long long* src[ROWS][kPolls];
+        u32x4 word[ROWS][kPolls];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)               // (a second row beyond the mini-batch: its last one again)
+#pragma unroll
+            for (int q = 0; q < kPolls; ++q) src[i][q] = in + (size_t)min(q0 + q * ps.J, G - 1) * word_stride + 2 * min(ps.pr + kThreads * i, nb - 1);
+        guard.arm();
+        while (true) {
+            load_pairs(src, word);
+            bool ok = true;
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+                for (int q = 0; q < kPolls; ++q) ok = ok && word[i][q].y == tag && word[i][q].w == tag;
+            if (ok) break;
+            if (guard.expired()) { gave_up = true; break; }
+        }
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) {
+            float v[kPolls], top = m[i];
+#pragma unroll
+            for (int q = 0; q < kPolls; ++q) {
+                v[q] = q0 + q * ps.J < G ? as_float(word[i][q].x) : -INFINITY;
+                top = fmaxf(top, v[q]);
+            }
+            sum[i] *= exp_neg(m[i] - top);
+#pragma unroll
+            for (int q = 0; q < kPolls; ++q) sum[i] = fmaf(as_float(word[i][q].z), exp_neg(v[q] - top), sum[i]);
+            m[i] = top;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+        if (ps.pr + kThreads * i < nb) {
+            rmax[ps.pj * ps.R + ps.pr + kThreads * i] = m[i];
+            rsum[ps.pj * ps.R + ps.pr + kThreads * i] = sum[i];
+        }
+    return !gave_up;
+}
+
+// e^(mx - top) / sum with top and sum of row r over all workgroups, where mx is its maximum here
+__device__ __forceinline__ float row_scale(const float* rmax, const float* rsum, const PollShape& ps, int r, int l16, float mx)
+{
+    float top, sum;
+    if (ps.J == 1) {
+        top = rmax[r];
+        sum = rsum[r];
+    } else {
+        // the four lanes that keep the same row take every fourth share, then meet
+        const int j0 = min(l16 >> 2, ps.J - 1) * ps.R + r, j1 = min((l16 >> 2) + 4, ps.J - 1) * ps.R + r;
+        const float v0 = (l16 >> 2) < ps.J ? rmax[j0] : -INFINITY, v1 = (l16 >> 2) + 4 < ps.J ? rmax[j1] : -INFINITY;
+        top = fmaxf(fmaxf(v0, v1), -FLT_MAX);
+        top = fmaxf(top, dpp_mov<0x124>(top));
+        top = fmaxf(top, dpp_mov<0x128>(top));
+        sum = rsum[j0] * exp_neg(v0 - top) + rsum[j1] * exp_neg(v1 - top);
+        sum += dpp_mov<0x124>(sum);
+        sum += dpp_mov<0x128>(sum);
+    }
+    return exp_neg(mx - top) / sum;
+}
+
+// residual of a tile's rows r0 .. r0 + 3 per lane (scale and label as row_sums keeps them), transposed into shared memory
+__device__ __forceinline__ void residual_tile(const f32x4 (&u)[NJ], float scale, int label, int r0, int c0, int nb, int C, int l16, unsigned short* Rt, int rs)
+{
+    const float f[4] = {dpp_mov<0x00>(scale), dpp_mov<0x55>(scale), dpp_mov<0xAA>(scale), dpp_mov<0xFF>(scale)};
+    const float lq_ = __builtin_bit_cast(float, label);
+    const int y[4] = {__builtin_bit_cast(int, dpp_mov<0x00>(lq_)), __builtin_bit_cast(int, dpp_mov<0x55>(lq_)),
+                      __builtin_bit_cast(int, dpp_mov<0xAA>(lq_)), __builtin_bit_cast(int, dpp_mov<0xFF>(lq_))};
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        float r[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int c = c0 + 16 * j + l16;
+            r[v] = u[j][v] * f[v] - (c == y[v] ? 1.f : 0.f);
+            if (r0 + v >= nb || c >= C) r[v] = 0.f;
+        }
+        *reinterpret_cast<uint2*>(&Rt[(16 * j + l16) * rs + r0]) = to_bf16x4(r);
+    }
+}
+
+// state of the update rule of features f0 .. f0 + 3 and class c, in memory laid out like W (loads from clamped addresses)
+__device__ __forceinline__ void load_state(const SoftmaxChainArgs& a, int f0, int c, float (&m)[4], float (&sv)[4])
+{
+    const float* second = a.opt.kind == kOptAdam ? a.opt.s : a.opt.m;        // (no second array: the first again, not written)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const size_t at = (size_t)min(f0 + v, a.p - 1) * a.ldw + c;
+        m[v] = a.opt.m[at];
+        sv[v] = second[at];
+    }
+}
+__device__ __forceinline__ void store_state(const SoftmaxChainArgs& a, int f0, int c, const float (&m)[4], const float (&sv)[4])
+{
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        if (f0 + v < a.p && c < a.C) {
+            const size_t at = (size_t)(f0 + v) * a.ldw + c;
+            a.opt.m[at] = m[v];
+            if (a.opt.kind == kOptAdam) a.opt.s[at] = sv[v];
+        }
+}
+
+// The whole pass in one workgroup: every share of 16 classes in turn does what its workgroup would do, W and the state in memory, the
+// bf16 copy in memory as well.  Only where the workgroups could not be resident together, so nothing here is done for speed but the
+// sums are those of softmax_chain_kernel, in the same order.
+template <bool OPT>
+__device__ __forceinline__ void pass_alone(const SoftmaxChainArgs& a, int G, unsigned short* Wt, unsigned short* Rt, float* rmax, float* rsum)
+{
+    const int KS = a.p32 / 32, NS = a.n32 / 32, ws = a.p32 + 8, rs = a.n32 + 8;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const size_t batch = (size_t)a.n32 * a.p32, words_set = (size_t)G * a.word_stride;
+    const PollShape ps(a.n32, G, tid);
+    PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
+    __shared__ int s_gave_up;
+    if (tid == 0) s_gave_up = 0;
+    __syncthreads();
+    for (int s = 0; s < a.M; ++s) {
+        const int nb = min(a.n, a.rows - s * a.n);
+        const unsigned tag = a.tag_base + (unsigned)s + 1u;
+        const float alpha = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
+        unsigned long long* words = a.words + (size_t)(s & 1) * words_set;
+        auto load_w = [&](int c0) {                  // the bf16 copy of a share's columns
+            const int chunks = a.p32 / 8;
+            for (int e = tid; e < kClasses * chunks; e += kThreads) {
+                const int c = e / chunks, f = 8 * (e - c * chunks);
+                *reinterpret_cast<uint4*>(&Wt[c * ws + f]) = *reinterpret_cast<const uint4*>(a.WbT + (size_t)(c0 + c) * a.ldwt + f);
+            }
+            __syncthreads();
+        };
+        auto logits = [&](int rt, int c0, f32x4 (&u)[NJ]) {
+            const unsigned short* x = a.XP + batch * s + (size_t)rt * KS * 512 + lane * 8;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const float z = c0 + 16 * j + l16 < a.C ? 0.f : -INFINITY;
+                u[j] = f32x4{z, z, z, z};
+            }
+            for (int k = 0; k < KS; ++k)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    u[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(*reinterpret_cast<const uint4*>(x + k * 512)),
+                                                                   as_frag(*reinterpret_cast<const uint4*>(&Wt[(16 * j + l16) * ws + 32 * k + 8 * lq])), u[j], 0, 0, 0);
+        };
+        for (int g = 0; g < G; ++g) {
+            load_w(g * kClasses);
+            for (int rt = wave; rt < a.n32 / 16; rt += kWaves) {
+                f32x4 u[NJ];
+                float mx, own;
+                logits(rt, g * kClasses, u);
+                row_sums(u, l16, mx, own);
+                publish_rows(words + (size_t)g * a.word_stride, 16 * rt + 4 * lq, nb, l16, mx, own, tag);
+            }
+            __syncthreads();
+        }
+        if (!collect_rows<2>(words, a.word_stride, G, nb, tag, ps, guard, rmax, rsum)) s_gave_up = 1;
+        __syncthreads();
+        if (s_gave_up) return;
+        const float inv_nb = 1.f / (float)nb, scale = alpha * inv_nb;
+        float oc1 = 1.f, oc2 = 1.f;
+        if (OPT && a.opt.kind == kOptAdam) opt_corrections(a.opt, a.opt.k_base + s + 1, oc1, oc2);
+        for (int g = 0; g < G; ++g) {
+            const int c0 = g * kClasses;
+            load_w(c0);
+            for (int rt = wave; rt < a.n32 / 16; rt += kWaves) {
+                f32x4 u[NJ];
+                float mx, own;
+                logits(rt, c0, u);
+                row_sums(u, l16, mx, own);
+                const int r0 = 16 * rt + 4 * lq;
+                const int label = a.YL[(size_t)s * a.n32 + r0 + (l16 & 3)];
+                residual_tile(u, row_scale(rmax, rsum, ps, min(r0 + (l16 & 3), nb - 1), l16, mx), label, r0, c0, nb, a.C, l16, Rt, rs);
+            }
+            __syncthreads();
+            for (int ft = wave; ft < a.p32 / 16; ft += kWaves) {
+                const unsigned short* x = a.XTP + batch * s + (size_t)ft * NS * 512 + lane * 8;
+                const int f0 = 16 * ft + 4 * lq;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+                    for (int k = 0; k < NS; ++k)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_frag(*reinterpret_cast<const uint4*>(x + k * 512)),
+                                                                      as_frag(*reinterpret_cast<const uint4*>(&Rt[(16 * j + l16) * rs + 32 * k + 8 * lq])), acc, 0, 0, 0);
+                    const int c = c0 + 16 * j + l16;
+                    float w[4], m[4], sv[4];
+                    if constexpr (OPT) load_state(a, f0, c, m, sv);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        w[v] = 0.f;
+                        if (f0 + v >= a.p || c >= a.C) continue;
+                        w[v] = a.W[(size_t)(f0 + v) * a.ldw + c];
+                        if constexpr (OPT) w[v] = opt_update(a.opt, w[v], acc[v] * inv_nb, alpha, m[v], sv[v], oc1, oc2);
+                        else w[v] -= scale * acc[v];
+                        a.W[(size_t)(f0 + v) * a.ldw + c] = w[v];
+                    }
+                    if constexpr (OPT) store_state(a, f0, c, m, sv);
+                    *reinterpret_cast<uint2*>(a.WbT + (size_t)c * a.ldwt + f0) = to_bf16x4(w);
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // RT, FT: row tiles and feature tiles per wavefront (tile w, w + 8, ... belong to wavefront w); OPT: an update rule other
 // than the plain step.
 template <int RT, int FT, bool OPT>
@@ -224,7 +516,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     unsigned short* Rt = Wt + kClasses * ws;         // [16][rs] residual, class-major
     float* rmax = reinterpret_cast<float*>(Rt + kClasses * rs);  // [J][R] a row's maximum over the classes of a share of the workgroups
     float* rsum = rmax + kMaxRows;                               // [J][R] ... and its sum of e^(u - that)
-    __shared__ int s_abort;
+    __shared__ int s_abort, s_role;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
@@ -233,7 +525,15 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     const int n_rt = a.n32 / 16, n_ft = a.p32 / 16;
     const size_t batch = (size_t)a.n32 * a.p32;      // elements of a mini-batch in XP and XTP
 
-    if (tid == 0) s_abort = 0;
+    unsigned ticket = 0;
+    if (G > 1 && a.meeting_ticks == 0) {
+        if (g == 0) pass_alone<OPT>(a, G, Wt, Rt, rmax, rsum);
+        return;
+    }
+    if (tid == 0) {
+        s_abort = 0;
+        if (G > 1) ticket = enter_meeting(a.meeting);
+    }
     // master weights: lane holds class c0 + 16 j + l16, features 16 tile + 4 lq + v.  Classes beyond C stay zero whatever their
     // gradient is (0 x Inf is NaN): their logits go through the same row sums as the others', as -infinity.
     float w[FT][NJ][4];
@@ -253,30 +553,12 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
 
     // state of the update rule, laid out like W: in registers beside W where there is room, else read and written in memory
     constexpr bool STATE = OPT && FT <= 2;
-    float* const state_s = OPT && a.opt.kind == kOptAdam ? a.opt.s : a.opt.m;     // (no second array: the first again, not written)
-    auto load_state = [&](int f0, int c, float (&m)[4], float (&sv)[4]) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const size_t at = (size_t)min(f0 + v, a.p - 1) * a.ldw + c;
-            m[v] = a.opt.m[at];
-            sv[v] = state_s[at];
-        }
-    };
-    auto store_state = [&](int f0, int c, const float (&m)[4], const float (&sv)[4]) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (f0 + v < a.p && c < a.C) {
-                const size_t at = (size_t)(f0 + v) * a.ldw + c;
-                a.opt.m[at] = m[v];
-                if (a.opt.kind == kOptAdam) a.opt.s[at] = sv[v];
-            }
-    };
     float om[STATE ? FT : 1][NJ][4], os[STATE ? FT : 1][NJ][4];
     if constexpr (STATE) {
 #pragma unroll
         for (int t = 0; t < FT; ++t)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) load_state(16 * (wave + kWaves * t) + 4 * lq, c0 + 16 * j + l16, om[t][j], os[t][j]);
+            for (int j = 0; j < NJ; ++j) load_state(a, 16 * (wave + kWaves * t) + 4 * lq, c0 + 16 * j + l16, om[t][j], os[t][j]);
     }
 
     // operand streams: wavefront w's tiles, clamped to the last one (what a clamped tile gives is dropped)
@@ -314,20 +596,22 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     start_l(a.XP);
     if constexpr (EARLY_G) start_g(a.XTP);
 
-    // polling: a thread per row, J such groups share the workgroups; for more than 512 rows two rows a thread, 512 apart
     constexpr int ROWS = RT == kMaxTiles ? 2 : 1;
-    const int R = (a.n32 + 63) / 64 * 64, J = min(G, max(1, kThreads / R));
-    const int pj = tid / R, pr = tid - pj * R;
+    const PollShape ps(a.n32, G, tid);
     const size_t words_set = (size_t)G * a.word_stride;
     PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
+    if (G > 1 && tid == 0) s_role = wait_for_meeting(a.meeting, ticket, (unsigned)G, a.meeting_ticks, guard);
     __syncthreads();
+    if (G > 1 && s_role != kTogether) {
+        if (s_role == kAlone) pass_alone<OPT>(a, G, Wt, Rt, rmax, rsum);
+        return;
+    }
 
     for (int s = 0; s < a.M; ++s) {
         const int nb = min(a.n, a.rows - s * a.n);
         const unsigned tag = a.tag_base + (unsigned)s + 1u;
         const unsigned short* xt = a.XTP + batch * s;
         const float alpha = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
-        // (what is kept per row sits in lane l16 & 3 = v of each quad for row 4 lq + v; the residual hands it round)
         int label[RT];
 #pragma unroll
         for (int t = 0; t < RT; ++t)
@@ -357,86 +641,20 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         if constexpr (EARLY_L) start_l(next);
         if constexpr (!EARLY_G) start_g(xt);
 
-        // u <- exp(u - mx) (0 for padding classes); mx and sum of every row over this workgroup's classes
         float mx[RT], own[RT];
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
             if (t >= my_rt) break;
-            float sm[4], sv[4];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                float m = -FLT_MAX;                      // (finite: a row of nothing but -infinity gets zeros here, not NaN)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) m = fmaxf(m, u[t][j][v]);
-                m = max16(m);
-                float sum = 0.f;
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    u[t][j][v] = exp_neg(u[t][j][v] - m);
-                    sum += u[t][j][v];
-                }
-                sm[v] = m;
-                sv[v] = sum16(sum);
-            }
-            mx[t] = quad_select(sm[0], sm[1], sm[2], sm[3], l16);
-            own[t] = quad_select(sv[0], sv[1], sv[2], sv[3], l16);
+            row_sums(u[t], l16, mx[t], own[t]);
             __builtin_amdgcn_sched_barrier(0);           // (one tile's exponentials at a time: all of them together take too many registers)
         }
         if (G > 1) {
-            unsigned long long* out = a.words + (size_t)(s & 1) * words_set + (size_t)g * a.word_stride;
+            unsigned long long* words = a.words + (size_t)(s & 1) * words_set;
 #pragma unroll
-            for (int t = 0; t < RT; ++t) {
-                // lanes 0 .. 3 of each 16 hold the four rows' maxima, lanes 4 .. 7 publish their sums
-                const int row = 16 * (wave + kWaves * t) + 4 * lq + (l16 & 3);
-                if (t < my_rt && l16 < 8 && row < nb) ll_store(out + 2 * row + (l16 >> 2), l16 < 4 ? mx[t] : own[t], tag);
-            }
-            const unsigned long long* in = a.words + (size_t)(s & 1) * words_set;
-            bool gave_up = false;
-            if (pj < J && pr < nb) {
-                __builtin_amdgcn_s_sleep(8);             // (0.2 us: a poll sent at once comes back a moment before the words do)
-                float m[ROWS], sum[ROWS];
-#pragma unroll
-                for (int i = 0; i < ROWS; ++i) { m[i] = -FLT_MAX; sum[i] = 0.f; }
-                for (int q0 = pj; q0 < G && !gave_up; q0 += kPolls * J) {
-                    const unsigned long long* src[ROWS][kPolls];
-                    u32x4 word[ROWS][kPolls];
-#pragma unroll
-                    for (int i = 0; i < ROWS; ++i)       // (a second row beyond the mini-batch: its last one again)
-#pragma unroll
-                        for (int q = 0; q < kPolls; ++q) src[i][q] = in + (size_t)min(q0 + q * J, G - 1) * a.word_stride + 2 * min(pr + kThreads * i, nb - 1);
-                    guard.arm();
-                    while (true) {
-                        load_pairs(src, word);
-                        bool ok = true;
-#pragma unroll
-                        for (int i = 0; i < ROWS; ++i)
-#pragma unroll
-                            for (int q = 0; q < kPolls; ++q) ok = ok && word[i][q].y == tag && word[i][q].w == tag;
-                        if (ok) break;
-                        if (guard.expired()) { gave_up = true; break; }
-                    }
-#pragma unroll
-                    for (int i = 0; i < ROWS; ++i) {
-                        float v[kPolls], top = m[i];
-#pragma unroll
-                        for (int q = 0; q < kPolls; ++q) {
-                            v[q] = q0 + q * J < G ? as_float(word[i][q].x) : -INFINITY;
-                            top = fmaxf(top, v[q]);
-                        }
-                        sum[i] *= exp_neg(m[i] - top);
-#pragma unroll
-                        for (int q = 0; q < kPolls; ++q) sum[i] = fmaf(as_float(word[i][q].z), exp_neg(v[q] - top), sum[i]);
-                        m[i] = top;
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < ROWS; ++i)
-                    if (pr + kThreads * i < nb) {
-                        rmax[pj * R + pr + kThreads * i] = m[i];
-                        rsum[pj * R + pr + kThreads * i] = sum[i];
-                    }
-                if (gave_up) s_abort = 1;
-            }
+            for (int t = 0; t < RT; ++t)
+                if (t < my_rt) publish_rows(words + (size_t)g * a.word_stride, 16 * (wave + kWaves * t) + 4 * lq, nb, l16, mx[t], own[t], tag);
+            __builtin_amdgcn_s_sleep(8);                 // (0.2 us: a poll sent at once comes back a moment before the words do)
+            if (!collect_rows<ROWS>(words, a.word_stride, G, nb, tag, ps, guard, rmax, rsum)) s_abort = 1;
             __syncthreads();
             if (s_abort) return;                    // (every thread sees the same value: it is not written after this barrier)
         }
@@ -445,42 +663,8 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         for (int t = 0; t < RT; ++t) {
             if (t >= my_rt) break;
             const int r0 = 16 * (wave + kWaves * t) + 4 * lq;
-            float top = mx[t], sum = own[t];
-            if (G > 1) {
-                const int r = min(r0 + (l16 & 3), nb - 1);
-                if (J == 1) {
-                    top = rmax[r];
-                    sum = rsum[r];
-                } else {
-                    // the four lanes that keep the same row take every fourth share, then meet
-                    const int j0 = min(l16 >> 2, J - 1) * R + r, j1 = min((l16 >> 2) + 4, J - 1) * R + r;
-                    const float v0 = (l16 >> 2) < J ? rmax[j0] : -INFINITY, v1 = (l16 >> 2) + 4 < J ? rmax[j1] : -INFINITY;
-                    top = fmaxf(fmaxf(v0, v1), -FLT_MAX);
-                    top = fmaxf(top, dpp_mov<0x124>(top));
-                    top = fmaxf(top, dpp_mov<0x128>(top));
-                    sum = rsum[j0] * exp_neg(v0 - top) + rsum[j1] * exp_neg(v1 - top);
-                    sum += dpp_mov<0x124>(sum);
-                    sum += dpp_mov<0x128>(sum);
-                }
-            }
-            const float fq = exp_neg(mx[t] - top) / sum;
-            const float f[4] = {dpp_mov<0x00>(fq), dpp_mov<0x55>(fq), dpp_mov<0xAA>(fq), dpp_mov<0xFF>(fq)};
-            const float lq_ = __builtin_bit_cast(float, label[t]);
-            const int y[4] = {__builtin_bit_cast(int, dpp_mov<0x00>(lq_)), __builtin_bit_cast(int, dpp_mov<0x55>(lq_)),
-                              __builtin_bit_cast(int, dpp_mov<0xAA>(lq_)), __builtin_bit_cast(int, dpp_mov<0xFF>(lq_))};
-            {
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    float r[4];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int c = c0 + 16 * j + l16;
-                        r[v] = u[t][j][v] * f[v] - (c == y[v] ? 1.f : 0.f);
-                        if (r0 + v >= nb || c >= a.C) r[v] = 0.f;
-                    }
-                    *reinterpret_cast<uint2*>(&Rt[(16 * j + l16) * rs + r0]) = to_bf16x4(r);
-                }
-            }
+            const float scale = G > 1 ? row_scale(rmax, rsum, ps, min(r0 + (l16 & 3), nb - 1), l16, mx[t]) : 1.f / own[t];
+            residual_tile(u[t], scale, label[t], r0, c0, nb, a.C, l16, Rt, rs);
             __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();
@@ -525,7 +709,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
 #pragma unroll
                         for (int v = 0; v < 4; ++v) { m[v] = om[t][j][v]; sv[v] = os[t][j][v]; }
                     } else {
-                        load_state(f0, c, m, sv);    // (all of a tile's at once, from clamped addresses)
+                        load_state(a, f0, c, m, sv);    // (all of a tile's at once, from clamped addresses)
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
@@ -534,7 +718,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
 #pragma unroll
                         for (int v = 0; v < 4; ++v) { om[t][j][v] = m[v]; os[t][j][v] = sv[v]; }
                     } else {
-                        store_state(f0, c, m, sv);
+                        store_state(a, f0, c, m, sv);
                     }
                 }
                 *reinterpret_cast<uint2*>(&Wt[(16 * j + l16) * ws + f0]) = to_bf16x4(w[t][j]);
@@ -549,7 +733,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         const int f0 = 16 * (wave + kWaves * t) + 4 * lq;
         if constexpr (OPT && STATE) {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) store_state(f0, c0 + 16 * j + l16, om[t][j], os[t][j]);
+            for (int j = 0; j < NJ; ++j) store_state(a, f0, c0 + 16 * j + l16, om[t][j], os[t][j]);
         }
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
@@ -656,7 +840,7 @@ hipError_t softmax_chain_pass(const void* X, const int32_t* y, const int32_t* pe
     a.XP = xp; a.XTP = xtp; a.YL = yl;
     const int jtiles = (a.n32 + 63) / 64;
     hipLaunchKernelGGL(pack_kernel, dim3((unsigned)(a.M * jtiles), (unsigned)((a.p32 + 63) / 64)), dim3(256), 0, stream,
-                       static_cast<const unsigned short*>(X), y, perm, xp, xtp, yl, a.rows, a.p, a.n, a.n32, a.p32, jtiles);
+                       static_cast<const unsigned short*>(X), y, perm, xp, xtp, yl, a.rows, a.p, a.n, a.n32, a.p32, jtiles, a.meeting);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int G = (a.C + kClasses - 1) / kClasses;
