@@ -247,7 +247,8 @@ bool wants_products(const bmgd_config& c)
     return steps >= 64 && gram_products_scratch_floats(c.p, (int64_t)kMaxPassesPerLaunch * M) <= (size_t(1) << 26);
 }
 
-Layout make_layout(const bmgd_config& c)
+// one_kernel: with room for the persistent softmax kernel (its mini-batches in operand order and its flagged words)
+Layout make_layout(const bmgd_config& c, bool one_kernel)
 {
     Layout l{};
     const size_t item = c.x_dtype == BMGD_BF16 ? 2 : 4;
@@ -268,7 +269,6 @@ Layout make_layout(const bmgd_config& c)
         l.wbt = off;     off += align_up((size_t)d.c_pad * d.p_pad * 2);
         l.u = off;       off += align_up((size_t)8 * d.m_pad * d.c_pad * 4);
         l.rt = off;      off += align_up((size_t)d.c_pad * d.n_pad * 2);
-        const bool one_kernel = wants_softmax_chain(c);
         l.xt = off;      off += align_up(std::max(m_max * (size_t)c.p * d.n_pad * 2, one_kernel ? softmax_chain_pack_bytes(c.p, c.batch_n, (int64_t)m_max) : 0));
         l.sm_words = off; off += one_kernel ? align_up(softmax_chain_words_bytes(c.batch_n, C)) : 0;
     } else {
@@ -941,7 +941,7 @@ BMGD_API size_t bmgd_workspace_bytes(const bmgd_config* cfg)
 {
     std::string why;
     if (!cfg || !valid_config(*cfg, &why)) return 0;
-    return make_layout(*cfg).total;
+    return make_layout(*cfg, wants_softmax_chain(*cfg)).total;
 }
 
 BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
@@ -963,7 +963,8 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     if (ctx->cfg.model != BMGD_SOFTMAX) ctx->cfg.n_classes = 1;
     ctx->x_itemsize = cfg->x_dtype == BMGD_BF16 ? 2 : 4;
     ctx->theta_len = cfg->p * ctx->cfg.n_classes;
-    ctx->lay = make_layout(ctx->cfg);
+    bool one_kernel = wants_softmax_chain(ctx->cfg);
+    ctx->lay = make_layout(ctx->cfg, one_kernel);
 
     auto bail = [&](int code) {
         g_create_error = ctx->err;
@@ -980,14 +981,27 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     hipDeviceProp_t prop;
     CREATE_TRY(hipGetDeviceProperties(&prop, ctx->device));
     ctx->num_cus = prop.multiProcessorCount;
+    // Softmax in one kernel needs more memory than separate launches (up to eight times the transposed mini-batches, for rows of 8
+    // features): where that is not to be had the context takes the launches.
+    auto without_one_kernel = [&]() {
+        if (!one_kernel) return false;
+        one_kernel = false;
+        ctx->lay = make_layout(ctx->cfg, false);
+        return true;
+    };
     if (cfg->workspace) {
-        if (cfg->workspace_bytes < ctx->lay.total) {
+        if (cfg->workspace_bytes < ctx->lay.total && (!without_one_kernel() || cfg->workspace_bytes < ctx->lay.total)) {
             ctx->err = "workspace smaller than bmgd_workspace_bytes()";
             return bail(BMGD_ENOMEM);
         }
         ctx->ws = cfg->workspace;
     } else {
-        CREATE_TRY(hipMalloc(&ctx->ws, ctx->lay.total));
+        hipError_t me = hipMalloc(&ctx->ws, ctx->lay.total);
+        if (me == hipErrorOutOfMemory && without_one_kernel()) {
+            (void)hipGetLastError();
+            me = hipMalloc(&ctx->ws, ctx->lay.total);
+        }
+        CREATE_TRY(me);
         ctx->owns_ws = true;
     }
     char* base = static_cast<char*>(ctx->ws);
@@ -1046,7 +1060,7 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     if (cfg->model == BMGD_SOFTMAX) {
         CREATE_TRY(softmax_prepare(softmax_dims(cfg->p, cfg->batch_n, cfg->n_classes)));
         ctx->chain = resolve_chain(ctx->cfg);        // three launches per mini-batch update, replayed from a graph or issued one by one
-        if (wants_softmax_chain(ctx->cfg))
+        if (one_kernel)
             CREATE_TRY(softmax_chain_prepare(cfg->p, cfg->batch_n, cfg->n_classes, cfg->optimizer != BMGD_OPT_SGD, ctx->num_cus, &ctx->sm_chain));
         if (ctx->chain == BMGD_CHAIN_GRAPH && !ctx->sm_chain) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
     } else {

@@ -225,3 +225,23 @@ def test_rows_that_are_all_but_certain_keep_their_residual():
         got = ctx.get_theta()[1:]
         ctx.close()
         assert np.abs(got / want.numpy() - 1.0).max() <= 2.0 ** -8, chain
+
+
+def test_a_workspace_of_the_size_that_separate_launches_need_is_taken():
+    """Its size without the mini-batches in operand order and the exchange: then the updates are separate launches."""
+    import torch
+    import paper_2312_08728_amd as B
+    w = _case(900, 8, 20, 900, 16)
+    X, y = wl.dataset(w)
+    cfg = B.bmgd_default_config()
+    cfg.p, cfg.buffer_n, cfg.batch_n, cfg.lr, cfg.passes = w.p, w.N0, w.n, w.alpha, w.T
+    cfg.model, cfg.n_classes, cfg.x_dtype, cfg.chain = B.BMGD_SOFTMAX, w.C, B.BMGD_BF16, B.BMGD_CHAIN_LAUNCH
+    size = B.bmgd_workspace_bytes(cfg)
+    cfg.chain = B.BMGD_CHAIN_AUTO
+    assert size < B.bmgd_workspace_bytes(cfg)
+    area = torch.zeros(size, dtype=torch.uint8, device="cuda")
+    got, _ = gpu_run(w, X, y, workspace=area, workspace_bytes=size)
+    assert rel_l2(got, oracle_run(w, X, y)) <= 2e-3
+    with pytest.raises(B.BmgdError) as e:
+        gpu_run(w, X, y, workspace=area, workspace_bytes=size - 256)
+    assert e.value.code == B.BMGD_ENOMEM
