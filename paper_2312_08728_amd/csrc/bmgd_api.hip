@@ -713,11 +713,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             for (int i = 0; i < np; ++i) {
                 const int32_t* pm = ctx->perm + (fixed ? 0 : (size_t)i * rows);
                 if (ctx->sm_chain) {
-                    if ((uint64_t)ctx->tag_epoch + (uint64_t)M + 1 >= 0xFFFFFFFFull) {
-                        // tag space used up: clear the flagged words (stream-ordered) and start over
-                        HIP_TRY(ctx, launch_fill_zero(ctx->sm_words, ctx->lay.gram[0] - ctx->lay.sm_words, stream));
-                        ctx->tag_epoch = 0;
-                    }
                     SoftmaxChainArgs sa{};
                     sa.W = ctx->theta;
                     sa.WbT = static_cast<unsigned short*>(ctx->wbt);
@@ -725,7 +720,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                     sa.ldwt = dmax.p_pad;
                     sa.rows = (int)rows; sa.n = (int)n; sa.p = (int)c.p; sa.C = c.n_classes;
                     sa.words = ctx->sm_words;
-                    sa.tag_base = ctx->tag_epoch;
                     sa.sync = ctx->sync;
                     // Workgroups that have met are all running, so their waits end by themselves: the limit is only there to end a
                     // kernel on a device that fails.  They are given as long to meet as the pass takes a workgroup alone (about
@@ -740,7 +734,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                     sa.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
                     sa.lr_len = lr_len;
                     sa.opt = opt_args(ctx, 0);
-                    ctx->tag_epoch += (uint32_t)M;
                     HIP_TRY(ctx, softmax_chain_pass(x, static_cast<const int32_t*>(y), pm, ctx->xt, sa, stream));
                     ctx->lr_pos += M;
                     ctx->opt_k += M;
@@ -1044,8 +1037,6 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
         // theta = 0 (padding classes included), bf16 copy = 0, residual scratch = 0
         CREATE_TRY(hipMemset(ctx->theta, 0, ctx->lay.sync - ctx->lay.theta));
         CREATE_TRY(hipMemset(ctx->wbt, 0, ctx->lay.xt - ctx->lay.wbt));
-        // flagged words start with tag 0, which no step ever waits for
-        if (ctx->lay.gram[0] > ctx->lay.sm_words) CREATE_TRY(hipMemset(ctx->sm_words, 0, ctx->lay.gram[0] - ctx->lay.sm_words));
     } else {
         CREATE_TRY(hipMemset(ctx->theta, 0, (size_t)ctx->theta_len * 4));
         // flagged words start with tag 0, which no step ever waits for

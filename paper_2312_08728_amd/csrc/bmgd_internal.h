@@ -267,8 +267,7 @@ struct SoftmaxChainArgs {
     unsigned short* WbT;    // bf16 copy, transposed [ldw][ldwt]: written at the end of the pass
     int ldw, ldwt;
     int rows, n, p, C;
-    unsigned long long* words;     // [2][G][word_stride] flagged words, by step parity: two per row, its maximum and its sum
-    unsigned tag_base;      // tag of update s of the pass is tag_base + s + 1
+    unsigned long long* words;     // [2][G][word_stride] flagged words, by step parity, one per row (cleared by the pass's first launch)
     unsigned* sync;         // [1] abort flag
     long long timeout_ticks;       // of a wait for workgroups known to be running
     unsigned* meeting;      // where the workgroups count themselves before the first update (cleared by the pass's first launch)

@@ -5,12 +5,11 @@
 // CLASSES are split over workgroups, 16 to each: a workgroup keeps its columns of W for the whole pass (fp32 master in
 // registers, in the accumulator layout of its gradient tiles; bf16 copy in shared memory, where the logits read it), so
 //     U = X_b W[:, mine]                    needs all features of a row, but nothing of other workgroups;
-//     R = softmax_rows(U) - onehot(y)       needs two numbers per row from each of the others: the maximum of its classes and
-//                                           their sum of e^(u - maximum);
+//     R = softmax_rows(U) - onehot(y)       needs one number per row from each of the others, its sum of e^u over their classes
+//                                           (as 2^k f, see exp2_rest);
 //     W[:, mine] -= (alpha / n_b) X_b' R    is again the workgroup's own.
-// Two numbers per row and workgroup are all that is exchanged (flagged words, glm_device.h: one trip over the fabric per update;
-// none at all for up to 16 classes).  (Joined into one, the log of the sum on top of the maximum, they would cost a word less, but
-// the probabilities would be off by the spacing of fp32 at the size of the logits.)  The mini-batch is read by every workgroup from its L2, twice per update (rows for the
+// Those sums are all that is exchanged (a flagged word each, store_sum: one trip over the fabric per update; none at all for
+// up to 16 classes).  The mini-batch is read by every workgroup from its L2, twice per update (rows for the
 // logits, transposed for the gradient), laid out once per pass in the order in which the matrix instructions take their
 // operands (pack_kernel): one contiguous KiB per load instruction, requested ahead, the next update's first ones before
 // this update's gradient.
@@ -51,16 +50,35 @@ __device__ __forceinline__ uint2 to_bf16x4(const float (&v)[4])
     return __builtin_bit_cast(uint2, __builtin_convertvector((f32x4_{v[0], v[1], v[2], v[3]}), bf16x4_));
 }
 
-// e^x for x <= 0 or NaN: 2^n 2^f with n = x log2 e rounded to a whole number and f what is left (log2 e in two parts), in eight
+constexpr float kLog2e = 1.44269502f, kLog2eLo = 1.92596299e-8f;   // log2 e in two parts
+constexpr float kRound = 12582912.f;                // 1.5 x 2^23: the last bit of a sum with it is 1
+
+// 2^n f for whole n <= 0 (or anything if f is NaN)
+__device__ __forceinline__ float scale_down(float f, float n)
+{
+    return __builtin_ldexpf(f, __builtin_bit_cast(int, fmaxf(n, -300.f) + kRound) - __builtin_bit_cast(int, kRound));
+}
+
+// e^x for x <= 0 or NaN: 2^n 2^f with n = x log2 e rounded to a whole number and f what is left, in eight
 // instructions.  As good as expf: over [-87, 0] a relative error of at most 8.5e-8 (2.7e-8 rms; expf 8.4e-8 and 2.6e-8), and the
 // subnormal numbers below to their last unit.
 __device__ __forceinline__ float exp_neg(float x)
 {
-    constexpr float kLog2e = 1.44269502f, kLog2eLo = 1.92596299e-8f, kRound = 12582912.f;   // 1.5 x 2^23: the sum's last bit is 1
     x = x < -200.f ? -200.f : x;                     // (keeps a NaN; e^-200 is 0)
     const float t = fmaf(x, kLog2e, kRound);
     const float f = fmaf(x, kLog2eLo, fmaf(x, kLog2e, kRound - t));
     return __builtin_ldexpf(__builtin_amdgcn_exp2f(f), __builtin_bit_cast(int, t) - __builtin_bit_cast(int, kRound));
+}
+
+// A row's sum of e^u over some classes is kept as 2^k f, k a whole number near their maximum times log2 e: exact to the last bits of
+// f whatever the size of the logits (the log of the sum would be off by the spacing of fp32 there), and sums of several workgroups
+// add up without an exponential.  e^m = 2^k * (what exp2_rest returns); from |k| = 2^23 on, where neighbouring numbers are further
+// apart than that, the rest is left out.
+__device__ __forceinline__ float exp2_rest(float m, float& k)
+{
+    k = fminf(fmaxf(rintf(m * kLog2e), -FLT_MAX), FLT_MAX);
+    const float rest = fmaf(m, kLog2eLo, fmaf(m, kLog2e, -k));
+    return __builtin_amdgcn_exp2f(fabsf(k) < 8388608.f ? rest : 0.f);
 }
 
 // The mini-batches of a pass in operand order, zeros beyond their rows and features:
@@ -71,9 +89,13 @@ __device__ __forceinline__ float exp_neg(float x)
 __global__ void __launch_bounds__(256) pack_kernel(const unsigned short* __restrict__ X, const int* __restrict__ y,
                                                    const int* __restrict__ perm, unsigned short* __restrict__ XP,
                                                    unsigned short* __restrict__ XTP, int* __restrict__ YL, int rows, int p, int n,
-                                                   int n32, int p32, int jtiles, unsigned* __restrict__ meeting)
+                                                   int n32, int p32, int jtiles, unsigned* __restrict__ meeting,
+                                                   unsigned long long* __restrict__ words, int nwords)
 {
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *meeting = 0;    // (of the launch that follows)
+    // for the launch that follows: nobody has come to the meeting, no word has been written
+    const int64_t first = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
+    if (first == 0) *meeting = 0;
+    for (int64_t i = first; i < nwords; i += (int64_t)gridDim.x * gridDim.y * blockDim.x) words[i] = 0;
     constexpr int TS = 72;                           // tile row stride in elements: 16-byte aligned rows
     __shared__ __align__(16) unsigned short tile[64 * TS];
     const int m = blockIdx.x / jtiles, jt = blockIdx.x % jtiles;
@@ -138,32 +160,50 @@ __device__ __forceinline__ float quad_select(float x0, float x1, float x2, float
 
 __device__ __forceinline__ float as_float(unsigned v) { return __builtin_bit_cast(float, v); }
 
-// Pairs of flagged words (one row's two numbers each) requested back to back and awaited together (see ll_load4).
-constexpr int kPolls = 4;
-__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[1][4], u32x4 (&w)[1][4])
+// What a workgroup tells the others about a row, in one 64-bit word that is written and read as a whole: its sum 2^k f as k (32 bits)
+// and f (26), and a tag (6).  f lies between 0.7 and 23; f / 32 is positive, at least 2^-7 and below 2, so its fp32 pattern without
+// the six leading bits, which are always the same, is all of it.  A sum of 0 (all classes at -infinity) is k = -infinity, NaN is
+// k = +infinity: the first adds nothing, the second takes all there is from the others, and 0 / 0 is NaN.
+// Words are cleared before a pass; every update writes all rows of its mini-batch, and only the last one can have fewer.  So a word
+// of another update that a reader can find is that of two updates before, or none, and six bits tell it from the one awaited.
+// (Two words a row with 32-bit tags took 28.2 against 22.4 us per update at n = 512, p = 256, C = 2000.)
+constexpr unsigned kSumBits = 26, kSumMask = (1u << kSumBits) - 1u, kSumBase = 0x3C000000u;
+constexpr float kSumScale = 1.f / 32.f;
+__device__ __forceinline__ unsigned row_tag(int s) { return (unsigned)s % 63u + 1u; }
+__device__ __forceinline__ void store_sum(unsigned long long* dst, float k, float f, unsigned tag)
+{
+    const unsigned low = (__builtin_bit_cast(unsigned, f * kSumScale) & kSumMask) | tag << kSumBits;
+    __hip_atomic_store(dst, (unsigned long long)__builtin_bit_cast(unsigned, k) << 32 | low, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float sum_of(unsigned low) { return as_float((low & kSumMask) | kSumBase); }     // (of 2^5 sums)
+
+// Pairs of words (two neighbouring rows each) requested back to back and awaited together (see ll_load4).
+__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[1], u32x4 (&w)[1])
+{
+    asm volatile("global_load_dwordx4 %0, %1, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(w[0])
+                 : "v"(src[0])
+                 : "memory");
+}
+__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[2], u32x4 (&w)[2])
+{
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\t"
+                 "global_load_dwordx4 %1, %3, off sc1\n\t"
+                 "s_waitcnt vmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1])
+                 : "v"(src[0]), "v"(src[1])
+                 : "memory");
+}
+__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[4], u32x4 (&w)[4])
 {
     asm volatile("global_load_dwordx4 %0, %4, off sc1\n\t"
                  "global_load_dwordx4 %1, %5, off sc1\n\t"
                  "global_load_dwordx4 %2, %6, off sc1\n\t"
                  "global_load_dwordx4 %3, %7, off sc1\n\t"
                  "s_waitcnt vmcnt(0)"
-                 : "=&v"(w[0][0]), "=&v"(w[0][1]), "=&v"(w[0][2]), "=&v"(w[0][3])
-                 : "v"(src[0][0]), "v"(src[0][1]), "v"(src[0][2]), "v"(src[0][3])
-                 : "memory");
-}
-__device__ __forceinline__ void load_pairs(const unsigned long long* const (&src)[2][4], u32x4 (&w)[2][4])
-{
-    asm volatile("global_load_dwordx4 %0, %8, off sc1\n\t"
-                 "global_load_dwordx4 %1, %9, off sc1\n\t"
-                 "global_load_dwordx4 %2, %10, off sc1\n\t"
-                 "global_load_dwordx4 %3, %11, off sc1\n\t"
-                 "global_load_dwordx4 %4, %12, off sc1\n\t"
-                 "global_load_dwordx4 %5, %13, off sc1\n\t"
-                 "global_load_dwordx4 %6, %14, off sc1\n\t"
-                 "global_load_dwordx4 %7, %15, off sc1\n\t"
-                 "s_waitcnt vmcnt(0)"
-                 : "=&v"(w[0][0]), "=&v"(w[0][1]), "=&v"(w[0][2]), "=&v"(w[0][3]), "=&v"(w[1][0]), "=&v"(w[1][1]), "=&v"(w[1][2]), "=&v"(w[1][3])
-                 : "v"(src[0][0]), "v"(src[0][1]), "v"(src[0][2]), "v"(src[0][3]), "v"(src[1][0]), "v"(src[1][1]), "v"(src[1][2]), "v"(src[1][3])
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+                 : "v"(src[0]), "v"(src[1]), "v"(src[2]), "v"(src[3])
                  : "memory");
 }
 
@@ -241,9 +281,9 @@ __device__ __forceinline__ int wait_for_meeting(unsigned* meeting, unsigned tick
     return kTogether;
 }
 
-// u <- exp(u - mx) (0 for padding classes) for a tile's four rows per lane; mx and sum of every row over a workgroup's classes.
-// (What is kept per row sits in lane l16 & 3 = v of each quad for row 4 lq + v; the residual hands it round.)
-__device__ __forceinline__ void row_sums(f32x4 (&u)[NJ], int l16, float& mx, float& own)
+// u <- exp(u - maximum) (0 for padding classes) for a tile's four rows per lane; each row's sum of e^u over a workgroup's classes is
+// 2^k rest total.  (What is kept per row sits in lane l16 & 3 = v of each quad for row 4 lq + v; the residual hands it round.)
+__device__ __forceinline__ void row_sums(f32x4 (&u)[NJ], int l16, float& k, float& rest, float& total)
 {
     float sm[4], sv[4];
 #pragma unroll
@@ -261,103 +301,98 @@ __device__ __forceinline__ void row_sums(f32x4 (&u)[NJ], int l16, float& mx, flo
         sm[v] = m;
         sv[v] = sum16(sum);
     }
-    mx = quad_select(sm[0], sm[1], sm[2], sm[3], l16);
-    own = quad_select(sv[0], sv[1], sv[2], sv[3], l16);
+    rest = exp2_rest(quad_select(sm[0], sm[1], sm[2], sm[3], l16), k);
+    total = quad_select(sv[0], sv[1], sv[2], sv[3], l16);
+    k = total > 0.f ? k : total == 0.f ? -INFINITY : INFINITY;
 }
 
-// lanes 0 .. 3 of each 16 hold the maxima of a tile's rows row0 .. row0 + 3, lanes 4 .. 7 publish their sums
-__device__ __forceinline__ void publish_rows(unsigned long long* out, int row0, int nb, int l16, float mx, float own, unsigned tag)
+// lanes 0 .. 3 of each 16 publish a tile's rows row0 .. row0 + 3
+__device__ __forceinline__ void publish_rows(unsigned long long* out, int row0, int nb, int l16, float k, float f, unsigned tag)
 {
     const int row = row0 + (l16 & 3);
-    if (l16 < 8 && row < nb) ll_store(out + 2 * row + (l16 >> 2), l16 < 4 ? mx : own, tag);
+    if (l16 < 4 && row < nb) store_sum(out + row, k, f, tag);
 }
 
-// How the threads of a workgroup share the polling: a thread per row, J groups of R threads that share the workgroups; for
-// more than 512 rows two rows a thread, 512 apart.
+// How the threads of a workgroup share the polling: a thread takes two neighbouring rows, J groups of R / 2 threads share the
+// workgroups.
 struct PollShape {
     int R, J, pj, pr;
     __device__ __forceinline__ PollShape(int n32, int G, int tid)
     {
-        R = (n32 + 63) / 64 * 64;
-        J = min(G, max(1, kThreads / R));
-        pj = tid / R;
-        pr = tid - pj * R;
+        R = (n32 + 127) / 128 * 128;
+        J = min(G, kThreads / (R / 2));
+        pj = tid / (R / 2);
+        pr = 2 * (tid - pj * (R / 2));
     }
 };
 
-// Every row's maximum and sum over the workgroups of this thread's share, into rmax and rsum [J][R].  False: given up.
-template <int ROWS>
+// Every row's sum over the workgroups of this thread's share, into rk and rf [J][R], POLLS of them a trip.  False: given up.
+template <int POLLS>
 __device__ __forceinline__ bool collect_rows(const unsigned long long* in, int word_stride, int G, int nb, unsigned tag, const PollShape& ps,
-                                             PollGuard& guard, float* rmax, float* rsum)
+                                             PollGuard& guard, float* rk, float* rf)
 {
     if (ps.pj >= ps.J || ps.pr >= nb) return true;
     bool gave_up = false;
-    float m[ROWS], sum[ROWS];
+    const bool second = ps.pr + 1 < nb;              // a second row beyond the mini-batch is never published and not waited for
+    float m[2] = {-FLT_MAX, -FLT_MAX}, sum[2] = {0.f, 0.f};
+    for (int q0 = ps.pj; q0 < G && !gave_up; q0 += POLLS * ps.J) {
+        const unsigned long long* src[POLLS];
+        u32x4 word[POLLS];
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i) { m[i] = -FLT_MAX; sum[i] = 0.f; }
-    for (int q0 = ps.pj; q0 < G && !gave_up; q0 += kPolls * ps.J) {
-        const unsigned long long* src[ROWS][kPolls];
-        u32x4 word[ROWS][kPolls];
-#pragma unroll
-        for (int i = 0; i < ROWS; ++i)               // (a second row beyond the mini-batch: its last one again)
-#pragma unroll
-            for (int q = 0; q < kPolls; ++q) src[i][q] = in + (size_t)min(q0 + q * ps.J, G - 1) * word_stride + 2 * min(ps.pr + kThreads * i, nb - 1);
+        for (int q = 0; q < POLLS; ++q) src[q] = in + (size_t)min(q0 + q * ps.J, G - 1) * word_stride + ps.pr;
         guard.arm();
         while (true) {
             load_pairs(src, word);
             bool ok = true;
 #pragma unroll
-            for (int i = 0; i < ROWS; ++i)
-#pragma unroll
-                for (int q = 0; q < kPolls; ++q) ok = ok && word[i][q].y == tag && word[i][q].w == tag;
+            for (int q = 0; q < POLLS; ++q) ok = ok && word[q].x >> kSumBits == tag && (word[q].z >> kSumBits == tag || !second);
             if (ok) break;
             if (guard.expired()) { gave_up = true; break; }
         }
 #pragma unroll
-        for (int i = 0; i < ROWS; ++i) {
-            float v[kPolls], top = m[i];
+        for (int i = 0; i < 2; ++i) {
+            float k[POLLS], top = m[i];
 #pragma unroll
-            for (int q = 0; q < kPolls; ++q) {
-                v[q] = q0 + q * ps.J < G ? as_float(word[i][q].x) : -INFINITY;
-                top = fmaxf(top, v[q]);
+            for (int q = 0; q < POLLS; ++q) {
+                k[q] = q0 + q * ps.J < G ? as_float(i ? word[q].w : word[q].y) : -INFINITY;
+                top = fmaxf(top, k[q]);
             }
-            sum[i] *= exp_neg(m[i] - top);
+            sum[i] = scale_down(sum[i], m[i] - top);
 #pragma unroll
-            for (int q = 0; q < kPolls; ++q) sum[i] = fmaf(as_float(word[i][q].z), exp_neg(v[q] - top), sum[i]);
+            for (int q = 0; q < POLLS; ++q) sum[i] += scale_down(sum_of(i ? word[q].z : word[q].x), k[q] - top);
             m[i] = top;
         }
     }
 #pragma unroll
-    for (int i = 0; i < ROWS; ++i)
-        if (ps.pr + kThreads * i < nb) {
-            rmax[ps.pj * ps.R + ps.pr + kThreads * i] = m[i];
-            rsum[ps.pj * ps.R + ps.pr + kThreads * i] = sum[i];
-        }
+    for (int i = 0; i < 2; ++i) {
+        rk[ps.pj * ps.R + ps.pr + i] = m[i];
+        rf[ps.pj * ps.R + ps.pr + i] = sum[i];
+    }
     return !gave_up;
 }
 
-// e^(mx - top) / sum with top and sum of row r over all workgroups, where mx is its maximum here
-__device__ __forceinline__ float row_scale(const float* rmax, const float* rsum, const PollShape& ps, int r, int l16, float mx)
+// what e^(u - maximum) of row r is to be multiplied with: 2^k rest over the row's sum over all workgroups
+__device__ __forceinline__ float row_scale(const float* rk, const float* rf, const PollShape& ps, int r, int l16, float k, float rest)
 {
     float top, sum;
     if (ps.J == 1) {
-        top = rmax[r];
-        sum = rsum[r];
+        top = rk[r];
+        sum = rf[r];
     } else {
         // the four lanes that keep the same row take every fourth share, then meet
         const int j0 = min(l16 >> 2, ps.J - 1) * ps.R + r, j1 = min((l16 >> 2) + 4, ps.J - 1) * ps.R + r;
-        const float v0 = (l16 >> 2) < ps.J ? rmax[j0] : -INFINITY, v1 = (l16 >> 2) + 4 < ps.J ? rmax[j1] : -INFINITY;
-        top = fmaxf(fmaxf(v0, v1), -FLT_MAX);
+        const float v0 = rk[j0], v1 = rk[j1];        // (one taken twice is the last one)
+        top = fmaxf(v0, v1);
         top = fmaxf(top, dpp_mov<0x124>(top));
         top = fmaxf(top, dpp_mov<0x128>(top));
-        sum = rsum[j0] * exp_neg(v0 - top) + rsum[j1] * exp_neg(v1 - top);
+        sum = ((l16 >> 2) < ps.J ? scale_down(rf[j0], v0 - top) : 0.f) + ((l16 >> 2) + 4 < ps.J ? scale_down(rf[j1], v1 - top) : 0.f);
         sum += dpp_mov<0x124>(sum);
         sum += dpp_mov<0x128>(sum);
     }
-    return exp_neg(mx - top) / sum;
+    return scale_down(rest * kSumScale, k - top) / sum;
 }
 
-// residual of a tile's rows r0 .. r0 + 3 per lane (scale and label as row_sums keeps them), transposed into shared memory
+// residual of a tile's rows r0 .. r0 + 3 per lane (scale and label as row_sums keeps its results), transposed into shared memory
 __device__ __forceinline__ void residual_tile(const f32x4 (&u)[NJ], float scale, int label, int r0, int c0, int nb, int C, int l16, unsigned short* Rt, int rs)
 {
     const float f[4] = {dpp_mov<0x00>(scale), dpp_mov<0x55>(scale), dpp_mov<0xAA>(scale), dpp_mov<0xFF>(scale)};
@@ -403,20 +438,20 @@ __device__ __forceinline__ void store_state(const SoftmaxChainArgs& a, int f0, i
 // bf16 copy in memory as well.  Only where the workgroups could not be resident together, so nothing here is done for speed but the
 // sums are those of softmax_chain_kernel, in the same order.
 template <bool OPT>
-__device__ __forceinline__ void pass_alone(const SoftmaxChainArgs& a, int G, unsigned short* Wt, unsigned short* Rt, float* rmax, float* rsum)
+__device__ __attribute__((noinline)) void pass_alone(const SoftmaxChainArgs* args, int G, unsigned short* Wt, unsigned short* Rt, float* rk, float* rf, int* gave_up)
 {
+    const SoftmaxChainArgs a = *args;
     const int KS = a.p32 / 32, NS = a.n32 / 32, ws = a.p32 + 8, rs = a.n32 + 8;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
     const size_t batch = (size_t)a.n32 * a.p32, words_set = (size_t)G * a.word_stride;
     const PollShape ps(a.n32, G, tid);
     PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
-    __shared__ int s_gave_up;
-    if (tid == 0) s_gave_up = 0;
+    if (tid == 0) *gave_up = 0;
     __syncthreads();
     for (int s = 0; s < a.M; ++s) {
         const int nb = min(a.n, a.rows - s * a.n);
-        const unsigned tag = a.tag_base + (unsigned)s + 1u;
+        const unsigned tag = row_tag(s);
         const float alpha = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
         unsigned long long* words = a.words + (size_t)(s & 1) * words_set;
         auto load_w = [&](int c0) {                  // the bf16 copy of a share's columns
@@ -444,16 +479,16 @@ __device__ __forceinline__ void pass_alone(const SoftmaxChainArgs& a, int G, uns
             load_w(g * kClasses);
             for (int rt = wave; rt < a.n32 / 16; rt += kWaves) {
                 f32x4 u[NJ];
-                float mx, own;
+                float k, rest, total;
                 logits(rt, g * kClasses, u);
-                row_sums(u, l16, mx, own);
-                publish_rows(words + (size_t)g * a.word_stride, 16 * rt + 4 * lq, nb, l16, mx, own, tag);
+                row_sums(u, l16, k, rest, total);
+                publish_rows(words + (size_t)g * a.word_stride, 16 * rt + 4 * lq, nb, l16, k, total * rest, tag);
             }
             __syncthreads();
         }
-        if (!collect_rows<2>(words, a.word_stride, G, nb, tag, ps, guard, rmax, rsum)) s_gave_up = 1;
+        if (!collect_rows<4>(words, a.word_stride, G, nb, tag, ps, guard, rk, rf)) *gave_up = 1;
         __syncthreads();
-        if (s_gave_up) return;
+        if (*gave_up) return;
         const float inv_nb = 1.f / (float)nb, scale = alpha * inv_nb;
         float oc1 = 1.f, oc2 = 1.f;
         if (OPT && a.opt.kind == kOptAdam) opt_corrections(a.opt, a.opt.k_base + s + 1, oc1, oc2);
@@ -462,12 +497,12 @@ __device__ __forceinline__ void pass_alone(const SoftmaxChainArgs& a, int G, uns
             load_w(c0);
             for (int rt = wave; rt < a.n32 / 16; rt += kWaves) {
                 f32x4 u[NJ];
-                float mx, own;
+                float k, rest, total;
                 logits(rt, c0, u);
-                row_sums(u, l16, mx, own);
+                row_sums(u, l16, k, rest, total);
                 const int r0 = 16 * rt + 4 * lq;
                 const int label = a.YL[(size_t)s * a.n32 + r0 + (l16 & 3)];
-                residual_tile(u, row_scale(rmax, rsum, ps, min(r0 + (l16 & 3), nb - 1), l16, mx), label, r0, c0, nb, a.C, l16, Rt, rs);
+                residual_tile(u, row_scale(rk, rf, ps, min(r0 + (l16 & 3), nb - 1), l16, k, rest), label, r0, c0, nb, a.C, l16, Rt, rs);
             }
             __syncthreads();
             for (int ft = wave; ft < a.p32 / 16; ft += kWaves) {
@@ -514,8 +549,8 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     const int ws = a.p32 + 8, rs = a.n32 + 8;        // row strides: 16 bytes past a multiple of 64, so that eight rows fall on different banks
     unsigned short* Wt = smem;                       // [16][ws] bf16 copy of W, class-major
     unsigned short* Rt = Wt + kClasses * ws;         // [16][rs] residual, class-major
-    float* rmax = reinterpret_cast<float*>(Rt + kClasses * rs);  // [J][R] a row's maximum over the classes of a share of the workgroups
-    float* rsum = rmax + kMaxRows;                               // [J][R] ... and its sum of e^(u - that)
+    float* rk = reinterpret_cast<float*>(Rt + kClasses * rs);  // [J][R] a row's sum over a share of the workgroups: k
+    float* rf = rk + kMaxRows;                                 // [J][R] ... and f
     __shared__ int s_abort, s_role;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -525,9 +560,10 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     const int n_rt = a.n32 / 16, n_ft = a.p32 / 16;
     const size_t batch = (size_t)a.n32 * a.p32;      // elements of a mini-batch in XP and XTP
 
+    const SoftmaxChainArgs* args = (const SoftmaxChainArgs*)__builtin_amdgcn_kernarg_segment_ptr();   // (a itself, without a copy on the stack)
     unsigned ticket = 0;
     if (G > 1 && a.meeting_ticks == 0) {
-        if (g == 0) pass_alone<OPT>(a, G, Wt, Rt, rmax, rsum);
+        if (g == 0) pass_alone<OPT>(args, G, Wt, Rt, rk, rf, &s_abort);
         return;
     }
     if (tid == 0) {
@@ -596,20 +632,19 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
     start_l(a.XP);
     if constexpr (EARLY_G) start_g(a.XTP);
 
-    constexpr int ROWS = RT == kMaxTiles ? 2 : 1;
     const PollShape ps(a.n32, G, tid);
     const size_t words_set = (size_t)G * a.word_stride;
     PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
     if (G > 1 && tid == 0) s_role = wait_for_meeting(a.meeting, ticket, (unsigned)G, a.meeting_ticks, guard);
     __syncthreads();
     if (G > 1 && s_role != kTogether) {
-        if (s_role == kAlone) pass_alone<OPT>(a, G, Wt, Rt, rmax, rsum);
+        if (s_role == kAlone) pass_alone<OPT>(args, G, Wt, Rt, rk, rf, &s_abort);
         return;
     }
 
     for (int s = 0; s < a.M; ++s) {
         const int nb = min(a.n, a.rows - s * a.n);
-        const unsigned tag = a.tag_base + (unsigned)s + 1u;
+        const unsigned tag = row_tag(s);
         const unsigned short* xt = a.XTP + batch * s;
         const float alpha = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
         int label[RT];
@@ -641,20 +676,25 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         if constexpr (EARLY_L) start_l(next);
         if constexpr (!EARLY_G) start_g(xt);
 
-        float mx[RT], own[RT];
+        // k and rest of the rows' sums over this workgroup's classes; where it is alone, rest is the scale
+        float k[RT], rest[RT];
+        unsigned long long* words = a.words + (size_t)(s & 1) * words_set;
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
             if (t >= my_rt) break;
-            row_sums(u[t], l16, mx[t], own[t]);
+            float total;
+            row_sums(u[t], l16, k[t], rest[t], total);
+            if (G > 1) publish_rows(words + (size_t)g * a.word_stride, 16 * (wave + kWaves * t) + 4 * lq, nb, l16, k[t], total * rest[t], tag);
+            else rest[t] = 1.f / total;
             __builtin_amdgcn_sched_barrier(0);           // (one tile's exponentials at a time: all of them together take too many registers)
         }
         if (G > 1) {
-            unsigned long long* words = a.words + (size_t)(s & 1) * words_set;
-#pragma unroll
-            for (int t = 0; t < RT; ++t)
-                if (t < my_rt) publish_rows(words + (size_t)g * a.word_stride, 16 * (wave + kWaves * t) + 4 * lq, nb, l16, mx[t], own[t], tag);
             __builtin_amdgcn_s_sleep(8);                 // (0.2 us: a poll sent at once comes back a moment before the words do)
-            if (!collect_rows<ROWS>(words, a.word_stride, G, nb, tag, ps, guard, rmax, rsum)) s_abort = 1;
+            // (as many words a trip as a thread has: asking for four where there is one cost 0.6 us per update at G = 7)
+            const bool got = G <= ps.J       ? collect_rows<1>(words, a.word_stride, G, nb, tag, ps, guard, rk, rf)
+                             : G <= 2 * ps.J ? collect_rows<2>(words, a.word_stride, G, nb, tag, ps, guard, rk, rf)
+                                             : collect_rows<4>(words, a.word_stride, G, nb, tag, ps, guard, rk, rf);
+            if (!got) s_abort = 1;
             __syncthreads();
             if (s_abort) return;                    // (every thread sees the same value: it is not written after this barrier)
         }
@@ -663,7 +703,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_chain_kernel(SoftmaxChain
         for (int t = 0; t < RT; ++t) {
             if (t >= my_rt) break;
             const int r0 = 16 * (wave + kWaves * t) + 4 * lq;
-            const float scale = G > 1 ? row_scale(rmax, rsum, ps, min(r0 + (l16 & 3), nb - 1), l16, mx[t]) : 1.f / own[t];
+            const float scale = G > 1 ? row_scale(rk, rf, ps, min(r0 + (l16 & 3), nb - 1), l16, k[t], rest[t]) : rest[t];
             residual_tile(u[t], scale, label[t], r0, c0, nb, a.C, l16, Rt, rs);
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -802,7 +842,7 @@ size_t softmax_chain_pack_bytes(int64_t p, int64_t n, int64_t batches)
 
 size_t softmax_chain_words_bytes(int64_t n, int64_t C)
 {
-    return (size_t)2 * ((C + kClasses - 1) / kClasses) * round32(n) * 16;
+    return (size_t)2 * ((C + kClasses - 1) / kClasses) * round32(n) * 8;
 }
 
 hipError_t softmax_chain_prepare(int64_t p, int64_t n, int64_t C, bool opt, int num_cus, bool* fits)
@@ -831,7 +871,7 @@ hipError_t softmax_chain_pass(const void* X, const int32_t* y, const int32_t* pe
     a.n32 = round32(a.n);
     a.p32 = round32(a.p);
     a.M = (a.rows + a.n - 1) / a.n;
-    a.word_stride = 2 * a.n32;
+    a.word_stride = a.n32;
     if (a.n32 > kMaxRows || a.p32 > kMaxRows || a.C > a.ldw) return hipErrorInvalidValue;
     const size_t half = (size_t)a.M * a.n32 * a.p32;
     unsigned short* xp = static_cast<unsigned short*>(pack);
@@ -840,7 +880,8 @@ hipError_t softmax_chain_pass(const void* X, const int32_t* y, const int32_t* pe
     a.XP = xp; a.XTP = xtp; a.YL = yl;
     const int jtiles = (a.n32 + 63) / 64;
     hipLaunchKernelGGL(pack_kernel, dim3((unsigned)(a.M * jtiles), (unsigned)((a.p32 + 63) / 64)), dim3(256), 0, stream,
-                       static_cast<const unsigned short*>(X), y, perm, xp, xtp, yl, a.rows, a.p, a.n, a.n32, a.p32, jtiles, a.meeting);
+                       static_cast<const unsigned short*>(X), y, perm, xp, xtp, yl, a.rows, a.p, a.n, a.n32, a.p32, jtiles, a.meeting, a.words,
+                       2 * ((a.C + kClasses - 1) / kClasses) * a.word_stride);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int G = (a.C + kClasses - 1) / kClasses;

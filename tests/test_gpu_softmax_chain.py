@@ -26,6 +26,7 @@ def _case(N, p, C, N0, n, T=2, R=1, alpha=0.05):
     (2100, 248, 300, 2100, 1024),      # most rows, ten workgroups
     (900, 1024, 130, 600, 200),        # most features
     (300, 40, 2000, 200, 48),          # 63 workgroups
+    (1000, 24, 33, 710, 7),            # 102 updates a pass: the exchange's tags come round; a last mini-batch of 3 rows, a shorter buffer
 ])
 def test_edges(N, p, C, N0, n):
     w = _case(N, p, C, N0, n)
@@ -104,6 +105,7 @@ def test_row_subset_and_fixed_partitions():
 
 @pytest.mark.parametrize("N,p,C,N0,n,optimizer", [
     (70, 8, 17, 40, 1, 0),             # one row, one feature chunk, one class in the second workgroup
+    (1000, 24, 33, 710, 7, 0),         # more updates a pass than the exchange has tags
     (1000, 200, 130, 700, 100, 0),     # ragged mini-batches, a shorter second buffer
     (900, 264, 40, 500, 130, 1),       # state in memory
     (900, 200, 300, 500, 100, 2),
