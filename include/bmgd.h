@@ -117,11 +117,12 @@ enum {
                                     rate and update counts are read from device memory, so a replay needs no new capture.
                                     BMGD_CHAIN_LAUNCH issues the same launches one by one.  BMGD_CHAIN_AUTO (reported
                                     as this mode) runs all updates of a pass in one persistent kernel instead where
-                                    mini-batches are small (batch_n, p <= 1024 and batch_n p <= 2^18; with a
-                                    buffered method of its own state p <= 512 and batch_n p <= 2^17).  Its workgroups
-                                    meet before the first update; where other work keeps some of them from running
-                                    (for an eighth of barrier_timeout_us, or for about the time that follows), one of them
-                                    makes the pass alone: slower, the same sums, and not an error. */
+                                    mini-batches are small (batch_n, p <= 1024 and batch_n p <= 2^18, less with more than
+                                    256 rows a mini-batch or, beyond 512, many classes; with a buffered method of its own
+                                    state p <= 512 and batch_n p <= 2^17).  Its workgroups meet before the first update; where
+                                    other work keeps some of them from running for as long as one alone would need for the pass,
+                                    or for an eighth of barrier_timeout_us, one of them makes the pass alone: slower, the same
+                                    sums, and not an error. */
     BMGD_CHAIN_PRODUCT = 5       /* least squares with p <= 128 and plain steps (BMGD_OPT_SGD) only: the moment form of
                                     BMGD_CHAIN_GRAM with steps multiplied together.  A step of eq. (3.1) is the affine map
                                     [theta; 1] <- A_m [theta; 1], A_m = [[I - alpha Sxx_m, alpha Sxy_m], [0, 1]], and no A_m

@@ -823,16 +823,25 @@ ChainKernel chain_kernel(bool opt, int rt, int ft) { return opt ? chain_kernel<t
 
 }  // namespace
 
-// Where one kernel is the faster way (us per update, this kernel / three launches): 3.2 / 14.4 at n = 128, p = 64, C = 10;
-// 6.3 / 16.9 at 100, 200, 130; 10.3 / 21.8 at 320, 320, 45; 11.1 / 22.0 at 256, 256, 1000; at n p = 2^18 what a workgroup reads
-// per update has caught up: 13.4 / 22.2 at 512, 512, 10, but 17.9 / 21.1 at 256, 1000, 200 and 24.9 / 28.0 at 1000, 256, 300.
-// With state (momentum, NAG, Adam) registers run out earlier: 16.2 / 31.3 at 320, 320, 45, 30.6 / 34.5 at 600, 320, 45 and
-// 44.9 / 30.7 at 256, 1000, 10 (Adam).
+// Where one kernel is the faster way (us per update, this kernel / three launches; n, p, C).  Small mini-batches gain most: 3.4 / 14.9
+// at 100, 200, 10; 7.6 / 19.8 at 100, 200, 2000; 12.0 / 21.3 at 256, 512, 1000.  What a workgroup reads per update, 4 n p bytes, catches up
+// around n p = 2^18: 13.6 / 20.6 at 512, 512, 10 and 26.3 / 31.1 with 2,000 classes, 20.3 / 23.7 at 256, 1000, 1000.
+//   256 < n <= 512, p > 768 (eight feature tiles beside four row tiles: registers run out): 16.8 / 21.2 at 340, 760, 10, but 20.2 / 19.6
+//     at 270, 968, 10 and 21.9 / 21.2 at 300, 872, 100.
+//   n > 512: one group of threads collects the sums of all workgroups, four a trip of 0.7 us, so classes cost more, and less is left for them
+//     the larger n p is.  As many classes as break even: 1140-1500 for n p up to 2^17 (950 at 600, 200), 710 at 1000, 192, 620 at 700, 280,
+//     300 at 1000, 256, 250 at 800, 320; none at 560, 464, where with one workgroup and no exchange it is 20.9 / 24.1 (600, 432, 10).
+//   State (momentum, NAG, Adam): registers run out earlier: 21.9 / 32.7 at 256, 512, 2000, 23.6 / 31.3 with Adam and 1,000 classes; n > 512 breaks even
+//     at 1,000 to 1,600 classes (31.2 / 31.0 at 640, 200, 1000; 42.0 / 40.0 at 600, 216, 2000).
 bool softmax_chain_eligible(int64_t p, int64_t n, int64_t C, bool opt)
 {
     if (p > kMaxRows || n > kMaxRows || C > 2048) return false;
-    if (opt) return p <= kMaxRows / 2 && p * n <= (int64_t(1) << 17);
-    return p * n <= (int64_t(1) << 18) && !(p > kMaxRows / 2 && n > kMaxRows / 2);
+    if (opt) return p <= kMaxRows / 2 && p * n <= (int64_t(1) << 17) && (n <= kMaxRows / 2 || C <= 1000);
+    if (p * n > (int64_t(1) << 18)) return false;
+    if (n <= kMaxRows / 4) return true;
+    if (n <= kMaxRows / 2) return p <= 768;
+    if (p > 384) return p <= kMaxRows / 2 && C <= kClasses;
+    return C <= std::min<int64_t>(1000, 1750 - 1500 * n * p / (int64_t(1) << 18));
 }
 
 size_t softmax_chain_pack_bytes(int64_t p, int64_t n, int64_t batches)

@@ -60,6 +60,20 @@ def test_workspace_size_needs_no_gpu_and_grows_with_the_buffer():
     assert a % 256 == 0
 
 
+@pytest.mark.parametrize("n,p,C,optimizer,one_kernel", [
+    (100, 200, 2000, 0, True), (256, 1024, 10, 0, True), (512, 512, 2000, 0, True), (340, 760, 300, 0, True),
+    (270, 968, 10, 0, False),                                  # registers run out
+    (600, 432, 16, 0, True), (600, 432, 17, 0, False),         # no exchange, or too little left for one
+    (1000, 128, 1000, 0, True), (1000, 128, 1001, 0, False), (1000, 256, 200, 0, True), (1000, 256, 1000, 0, False),
+    (512, 256, 2000, 3, True), (600, 200, 1000, 1, True), (600, 216, 2000, 1, False), (1000, 136, 10, 1, False),
+])
+def test_softmax_in_one_kernel_only_where_it_was_measured_to_be_faster(n, p, C, optimizer, one_kernel):
+    """Which way a configuration goes shows in its workspace: the persistent kernel has areas of its own."""
+    sizes = [B.bmgd_workspace_bytes(_cfg(p=p, buffer_n=4 * n, batch_n=n, model=B.BMGD_SOFTMAX, n_classes=C, x_dtype=B.BMGD_BF16,
+                                         optimizer=optimizer, chain=chain)) for chain in (B.BMGD_CHAIN_AUTO, B.BMGD_CHAIN_LAUNCH)]
+    assert sizes[1] > 0 and (sizes[0] > sizes[1]) == one_kernel
+
+
 def test_invalid_arguments_are_rejected_without_a_device():
     bad = [dict(p=0), dict(buffer_n=0), dict(buffer_n=1 << 30), dict(batch_n=0), dict(batch_n=1001),
            dict(lr=0.0), dict(lr=float("nan")), dict(lr=float("inf")), dict(lr=-1.0), dict(passes=0),

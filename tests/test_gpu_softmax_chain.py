@@ -24,6 +24,7 @@ def _case(N, p, C, N0, n, T=2, R=1, alpha=0.05):
     (600, 136, 65, 400, 129),          # one more of everything
     (1500, 512, 40, 900, 300),         # several tiles per wavefront
     (2100, 248, 300, 2100, 1024),      # most rows, ten workgroups
+    (2100, 248, 250, 2100, 1024),      # most rows that one kernel takes with that many classes
     (900, 1024, 130, 600, 200),        # most features
     (300, 40, 2000, 200, 48),          # 63 workgroups
     (1000, 24, 33, 710, 7),            # 102 updates a pass: the exchange's tags come round; a last mini-batch of 3 rows, a shorter buffer
