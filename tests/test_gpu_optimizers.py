@@ -68,6 +68,16 @@ def test_softmax_optimizers(kind):
     assert rel_l2(got, want) <= (5e-3 if kind == 3 else 2e-3)
 
 
+@pytest.mark.parametrize("kind", KINDS)
+def test_softmax_optimizers_in_separate_launches(kind):
+    """The same through the contractions with the update in their write-out, for which this size is no longer large enough by itself."""
+    w = wl.CONFIGS["cfg5"].scaled(name="case", N=2000, p=136, C=140, N0=1000, n=256, T=2, R=1)
+    X, y = wl.dataset(w)
+    got, want, st = _run_both(w, X, y, kind, 2, 0.002 if kind == 3 else 0.02, buffers=2)
+    assert st.chain == 2
+    assert rel_l2(got, want) <= (5e-3 if kind == 3 else 2e-3)
+
+
 def test_invalid_optimizer_settings():
     import paper_2312_08728_amd as B
     for kw in (dict(optimizer=7), dict(optimizer=1, momentum=1.0), dict(optimizer=3, beta1=1.0), dict(optimizer=3, eps=-1.0)):

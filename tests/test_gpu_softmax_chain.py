@@ -1,5 +1,5 @@
-"""The persistent softmax kernel (small mini-batches, 32 classes per workgroup) at the edges of its tiles: class counts around
-one and two workgroups, rows and features around the tiles of 16 and 32 and the tiles per wavefront, ragged last mini-batches
+"""The persistent softmax kernel (small mini-batches, 16 classes per workgroup) at the edges of its tiles: class counts around
+one, two and more workgroups, rows and features around the tiles of 16 and 32 and the tiles per wavefront, ragged last mini-batches
 and a shorter last buffer.  Compared with the fp64 oracle within the bound of the bf16 path (2e-3: bf16 copy of W, bf16
 residual; 5e-3 with Adam, which normalises their rounding), and with the three-launch path, whose roundings are the same
 up to the order of fp32 sums."""
@@ -18,15 +18,18 @@ def _case(N, p, C, N0, n, T=2, R=1, alpha=0.05):
 
 @pytest.mark.parametrize("N,p,C,N0,n", [
     (70, 8, 2, 40, 1),                 # mini-batches of one row, one feature chunk
-    (200, 16, 32, 130, 16),            # exactly one workgroup, one row tile
-    (200, 24, 33, 130, 17),            # one class in the second workgroup
+    (200, 16, 15, 130, 16),            # one workgroup, not full; one row tile
+    (200, 16, 16, 130, 16),            # exactly one workgroup: nothing is exchanged
+    (200, 24, 17, 130, 17),            # one class in the second workgroup
+    (200, 16, 32, 130, 16),            # exactly two workgroups
+    (200, 24, 33, 130, 17),            # one class in the third workgroup
     (600, 128, 64, 400, 128),          # one tile per wavefront both ways, exactly
     (600, 136, 65, 400, 129),          # one more of everything
     (1500, 512, 40, 900, 300),         # several tiles per wavefront
-    (2100, 248, 300, 2100, 1024),      # most rows, ten workgroups
-    (2100, 248, 250, 2100, 1024),      # most rows that one kernel takes with that many classes
+    (2100, 248, 300, 2100, 1024),      # most rows, 19 workgroups: so many classes go to separate launches
+    (2100, 248, 250, 2100, 1024),      # most rows that one kernel takes with 16 workgroups
     (900, 1024, 130, 600, 200),        # most features
-    (300, 40, 2000, 200, 48),          # 63 workgroups
+    (300, 40, 2000, 200, 48),          # 125 workgroups
     (1000, 24, 33, 710, 7),            # 102 updates a pass: the exchange's tags come round; a last mini-batch of 3 rows, a shorter buffer
 ])
 def test_edges(N, p, C, N0, n):
@@ -63,7 +66,45 @@ def test_update_rules_with_a_table_of_rates(optimizer):
     assert abs(got[0][1] - got[1][1]) <= 2e-3 * abs(got[1][1])
 
 
-@pytest.mark.parametrize("bad,C", [(np.inf, 40), (-np.inf, 40), (np.nan, 40), (np.inf, 20), (np.nan, 20)])
+@pytest.mark.parametrize("optimizer", [1, 2, 3])
+@pytest.mark.parametrize("p,n", [(72, 900), (200, 100), (200, 300), (200, 600), (264, 130), (264, 490), (504, 256), (512, 100)])
+def test_update_rules_at_every_number_of_tiles(optimizer, p, n):
+    """Feature tiles per wavefront 1, 2 (state in registers) and 4 (in memory) beside row tiles 1, 2, 4 and 8, with a ragged mini-batch, a
+    shorter second buffer and a third run behind it: the state is carried from launch to launch.  Against the oracle and the launches."""
+    import torch
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    w = _case(5 * n + n // 3, p, 35, 3 * n + 5, n)
+    X, y = wl.dataset(w)
+    settings = dict(momentum=0.8, beta1=0.9, beta2=0.99, eps=1e-6)
+    top = 0.002 if optimizer == 3 else 0.02
+    rates = np.linspace(top, top / 10, 13).astype(np.float32)
+    ref = O.BMGD(w.model, w.p, w.n, top, w.T, C=w.C)
+    ref.set_optimizer(optimizer, **settings)
+    ref.set_lr_schedule(rates)
+    spans = [wl.buffer_rows(w, k) for k in (0, 1, 0)]
+    for lo, hi in spans:
+        ref.run_buffer(X[lo:hi], y[lo:hi])
+    xd, yd = torch.from_numpy(X.view(np.int16)).cuda(), torch.from_numpy(y).cuda()
+    s = torch.cuda.Stream()
+    # Adam's first update is alpha times the sign of the gradient, so where the rounding of the residual (2^-9) decides the sign, for
+    # about 2^-9 of the coordinates, it is off by twice its size: 2 x 2^-4.5 = 9e-2 of that update, one of 22 here whose
+    # rates add up to more than seven times the first one's: 1.2e-2
+    bound = 1.2e-2 if optimizer == 3 else 2e-3
+    got = []
+    for chain in (B.BMGD_CHAIN_AUTO, B.BMGD_CHAIN_LAUNCH):
+        ctx = B.Context(w.p, w.N0, w.n, top, w.T, model=w.model, n_classes=w.C, chain=chain, optimizer=optimizer, **settings)
+        ctx.set_lr_schedule(rates)
+        for lo, hi in spans:
+            ctx.run_device_buffer(xd[lo:hi], yd[lo:hi], hi - lo, s)
+        got.append(ctx.get_theta().reshape(ref.theta.shape))
+        ctx.close()
+        assert rel_l2(got[-1], ref.theta) <= bound, chain
+    assert rel_l2(got[0], got[1]) <= bound
+
+
+@pytest.mark.parametrize("bad,C", [(np.inf, 40), (-np.inf, 40), (np.nan, 40), (np.inf, 20), (np.nan, 20),
+                                   (np.inf, 16), (-np.inf, 10), (np.nan, 16), (np.nan, 17), (np.inf, 130)])
 def test_values_that_are_not_finite_spread_as_in_three_launches(bad, C):
     import torch
     import paper_2312_08728_amd as B
