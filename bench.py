@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # HBM traffic of one launch of the chain kernel on the primary workload, from rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE (see profiles/), scaled by the copy calibration; valid only for the source of the kernel it was measured on
 # (the line reports null once that file has changed: measure again and update the entry).
-TRAFFIC = {"cfg2": {"sources": ('gram_kernels.hip', 'gram_layout.h', 'gram_products.hip'), "kernel_sha256": "c5a25ec6a3db67ff4eaedb207055baec6f4cc6cbd01c8f94818cb9a656a95779", "bytes_per_launch": 217072615}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "45fef1bf3ccf41c027138800dba42d12c1e5535d30ae6f2492f523b280ed68fe", "bytes_per_launch": 2473478069}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "8d8c2fd79cd5ea4e1c2d85d65948ba501b3f0dcb49b443ac8ecd2b5b9677dfeb", "bytes_per_launch": 9428150173}}
+TRAFFIC = {"cfg2": {"sources": ('gram_kernels.hip', 'gram_layout.h', 'gram_products.hip'), "kernel_sha256": "327a68b047e5ccc8ef4f365882473e7f103ab0bee9ed0a044cb23bdb7f8b7f7b", "bytes_per_launch": 217086377}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "45fef1bf3ccf41c027138800dba42d12c1e5535d30ae6f2492f523b280ed68fe", "bytes_per_launch": 2473478069}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "8d8c2fd79cd5ea4e1c2d85d65948ba501b3f0dcb49b443ac8ecd2b5b9677dfeb", "bytes_per_launch": 9428150173}}
 
 
 def _kernel_sha(sources) -> str:
