@@ -480,7 +480,7 @@ __device__ __forceinline__ void store_partial(double acc, double* partial)
 // of V floats per lane, theta's slice in registers), U rows per lane group are requested together (up to 8 x 16 bytes
 // in flight per lane; with one row at a time and 4-byte loads a wavefront stood in its own latency: 1.5 TB/s), and the
 // U losses, whose exp and log1p cost more than a row's products, are evaluated by U different lanes at once.
-// 1,000,000 rows of 200 floats: 541 -> 146 us (5.5 TB/s; a large copy reaches 4.8 TB/s here).
+// 1,000,000 rows of 200 floats: 541 -> 146 us (5.5 TB/s; a large copy moves 5.1 TB/s here, reads and writes together).
 template <int V, int CPL, int U>
 __global__ void __launch_bounds__(kLossBlock) glm_loss_rows_kernel(const float* __restrict__ X, const float* __restrict__ y,
                                                                    const float* __restrict__ theta, int rows, int p, int model,
