@@ -289,3 +289,30 @@ def test_a_workspace_of_the_size_that_separate_launches_need_is_taken():
     with pytest.raises(B.BmgdError) as e:
         gpu_run(w, X, y, workspace=area, workspace_bytes=size - 256)
     assert e.value.code == B.BMGD_ENOMEM
+
+
+@pytest.mark.parametrize("size", [30.0, 1e4, 1e7, 1e20, 2e38])
+def test_logits_of_any_size(size):
+    """Logits of -size, 0 and size in turn over the classes of three workgroups: the classes at the top share each row alike, up to the
+    rounding of the residual to bf16 (2^-9) and of the fp32 update (2^-24 of it per row): 2^-8."""
+    import torch
+    import paper_2312_08728_amd as B
+    n, p, C = 40, 8, 37
+    x = torch.zeros((n, p))
+    x[:, 0] = 1.0
+    x[:, 1:] = torch.rand((n, p - 1), generator=torch.Generator().manual_seed(2)) + 0.5
+    x = x.bfloat16()
+    w0 = np.zeros((p, C), dtype=np.float32)
+    w0[0] = torch.tensor([size * (c % 3 - 1) for c in range(C)]).bfloat16().float().numpy()
+    prob = torch.softmax(torch.from_numpy(w0[0]).double(), 0)
+    prob[2] -= 1.0                                         # every row's label
+    want = (-0.5 * x.double().mean(0)[1:, None] * prob[None, :]).numpy()
+    for limit in (0, 1):                                   # (1: by one workgroup alone)
+        ctx = B.Context(p, n, n, 0.5, 1, model=B.BMGD_SOFTMAX, n_classes=C, barrier_timeout_us=limit)
+        ctx.set_theta(w0)
+        ctx.run_device_buffer(x.cuda(), torch.full((n,), 2, dtype=torch.int32, device="cuda"), n, None)
+        got = ctx.get_theta()[1:]
+        ctx.close()
+        assert np.abs(got - want).max() <= 2.0 ** -8 * np.abs(want).max()
+        some = np.abs(want) > 1e-12
+        assert np.abs(got[some] / want[some] - 1.0).max() <= 2.0 ** -8 and np.abs(got[~some]).max(initial=0.0) <= 1e-12
