@@ -2,9 +2,8 @@
 //
 // Three launches per update (logits, residual, gradient + update; softmax_kernels.hip) cost 14 us even for 16 rows, and 35 us for 1,000 rows
 // of 256 features and 2,000 classes: each small kernel is a chain of dependent trips to memory, and the weights go out to memory and
-// back between them.  Here the
-// CLASSES are split over workgroups, 16 to each: a workgroup keeps its columns of W for the whole pass (fp32 master in
-// registers, in the accumulator layout of its gradient tiles; bf16 copy in shared memory, where the logits read it), so
+// back between them.  Here the CLASSES are split over workgroups, 16 to each: a workgroup keeps its columns of W for the whole pass (fp32
+// master in registers, in the accumulator layout of its gradient tiles; bf16 copy in shared memory, where the logits read it), so
 //     U = X_b W[:, mine]                    needs all features of a row, but nothing of other workgroups;
 //     R = softmax_rows(U) - onehot(y)       needs one number per row from each of the others, its sum of e^u over their classes
 //                                           (as 2^k f, see exp2_rest);
@@ -16,7 +15,7 @@
 // this update's gradient.
 //
 // The exchange needs all workgroups of the launch resident at once, which work of other streams and processes can prevent.  So they
-// meet before the first update (gather_workgroups): where they do not within a given time, one of them makes the whole pass by
+// meet before the first update (wait_for_meeting): where they do not within a given time, one of them makes the whole pass by
 // itself, class share by class share (pass_alone, the same sums in the same order), and the others leave.
 //
 // What bounds it: the trip over the fabric for small mini-batches, and one compute unit's load path (4 n p bytes per update)
@@ -54,7 +53,7 @@ __device__ __forceinline__ uint2 to_bf16x4(const float (&v)[4])
 constexpr float kLog2e = 1.44269502f, kLog2eLo = 1.92596299e-8f;   // log2 e in two parts
 constexpr float kRound = 12582912.f;                // 1.5 x 2^23: the last bit of a sum with it is 1
 
-// 2^n f for whole n <= 0 (or anything if f is NaN)
+// 2^n f for whole n <= 0; 0 for n = -infinity and, as between two sums that are NaN (store_sum), for n = NaN
 __device__ __forceinline__ float scale_down(float f, float n)
 {
     return __builtin_ldexpf(f, __builtin_bit_cast(int, fmaxf(n, -300.f) + kRound) - __builtin_bit_cast(int, kRound));
