@@ -104,8 +104,9 @@ struct GlmLaunchShape {
                         // G is a multiple of 8, split_ch = float4 chunks of a row per lane (1: p <= 2048, 2: p <= 4096)
     int split_ch;
     int narrow;         // 1: the persistent chain runs the kernel for rows of up to 1024 floats whose share of a step fits a
-                        // workgroup's registers (glm_narrow_kernel.hip): G is a multiple of 8, narrow_pf rows per row slot
-    int narrow_pf;
+                        // workgroup's registers (glm_narrow_kernel.hip): narrow_pf rows per row slot of narrow_rw row wavefronts
+                        // (8: sliced reduction, G a multiple of 8; 12: redundant reduction, or odd p)
+    int narrow_pf, narrow_rw;
     int64_t n;          // mini-batch size and row length the shape was planned for
     int p;
     int chain_block;    // threads per workgroup of the persistent chain's kernel
@@ -152,11 +153,13 @@ int glm_split_block();
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups);
 hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream);
 
-// Persistent chain for rows of up to 1024 floats (p even) on G = 8, 16, ... workgroups when a step's rows fit the
-// registers of the grid (glm_narrow_kernel.hip).  glm_narrow_rows_in_flight: rows per row slot that a step of n rows
-// needs on G workgroups, 0 if that is more than the kernel holds.
-int glm_narrow_block();
-int glm_narrow_rows_in_flight(int v, int cpl, int L, int G, int64_t n);
+// Persistent chain for rows of up to 1024 floats when a step's rows fit the registers of the grid (glm_narrow_kernel.hip), with
+// rw row wavefronts per workgroup.  glm_narrow_rows_in_flight: rows per row slot that a step of n rows needs on G workgroups, 0 if
+// that is more than the kernel holds.
+constexpr int kNarrowMoreRows = 12;        // row wavefronts where the sums are added up by every workgroup, or p is odd
+constexpr int kNarrowOneTripMaxP = 512;    // widest rows of the redundant reduction in this kernel
+int glm_narrow_block(int rw);
+int glm_narrow_rows_in_flight(int v, int cpl, int L, int rw, int G, int64_t n);
 hipError_t glm_narrow_prepare(const GlmLaunchShape& shape, int p, int* max_groups);
 hipError_t glm_narrow_launch(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream);
 

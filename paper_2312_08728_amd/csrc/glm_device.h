@@ -63,24 +63,21 @@ __device__ __forceinline__ float slot_sum(float v, int L)
 }
 
 // The same two sums without branches on L (every stage is executed and its result kept or dropped): for code whose
-// control flow must stay a straight line.
-__device__ __forceinline__ float group_sum_flat(float v, int L)
+// control flow must stay a straight line.  row_group_sum: 4 <= L <= 16.
+__device__ __forceinline__ float row_group_sum(float v, int L)
 {
     float t;
-    t = dpp_mov<0xB1>(v); v += L >= 2 ? t : 0.f;
-    t = dpp_mov<0x4E>(v); v += L >= 4 ? t : 0.f;
+    v += dpp_mov<0xB1>(v);
+    v += dpp_mov<0x4E>(v);
     t = dpp_mov<0x141>(v); v += L >= 8 ? t : 0.f;
     t = dpp_mov<0x140>(v); v += L >= 16 ? t : 0.f;
-    t = swap16_sum(v); v = L >= 32 ? t : v;
-    t = swap32_sum(v); v = L >= 64 ? t : v;
     return v;
 }
 
+// (L >= 4)
 __device__ __forceinline__ float slot_sum_flat(float v, int L)
 {
     float t;
-    t = dpp_mov<0x121>(v); v += L <= 1 ? t : 0.f;
-    t = dpp_mov<0x122>(v); v += L <= 2 ? t : 0.f;
     t = dpp_mov<0x124>(v); v += L <= 4 ? t : 0.f;
     t = dpp_mov<0x128>(v); v += L <= 8 ? t : 0.f;
     t = swap16_sum(v); v = L <= 16 ? t : v;
@@ -106,8 +103,7 @@ __device__ __forceinline__ float residual(int model, float u, float y)
 {
     if (model == kLogistic) {
         const float e = expf(-fabsf(u));
-        const float s = (u >= 0.f) ? 1.f / (1.f + e) : e / (1.f + e);
-        return s - y;
+        return (u >= 0.f ? 1.f : e) / (1.f + e) - y;
     }
     return u - y;
 }

@@ -1,28 +1,36 @@
-// The exchange wavefront of the persistent GLM kernels, and what they share around it.
+// The exchange wavefronts of the persistent GLM kernels, and what they share around them.
 //
 // A workgroup of these kernels is a set of "row" wavefronts, which read rows and accumulate the gradient sums of a
-// step of eq. (2.1), and one exchange wavefront, which carries those sums to the other workgroups and brings the
+// step of eq. (2.1), and one or four exchange wavefronts, which carry those sums to the other workgroups and bring the
 // new theta back.  The two kinds meet only through flags in shared memory:
 //   s_published      counts publications of row wavefronts over all steps (each stores its sums to shared memory first);
-//   s_theta_version  versions of theta the exchange wavefront has delivered to shared memory (version v = theta
-//                    after v steps of the launch, kept in the copy v & 1);
-//   s_abort          set by the exchange wavefront when a wait ran out: everybody leaves.
+//   s_theta_version  versions of theta the exchange wavefronts have delivered to shared memory (version v = theta
+//                    after v steps of the launch, kept in the copy v & 1), each of them counted;
+//   s_abort          set by an exchange wavefront when a wait ran out: everybody leaves.
 // A row wavefront must not poll global memory itself: loads return to a wavefront in the order it issued them, so
 // its poll would come back behind the newest rows it has in flight.
 //
-// Per step the exchange wavefront makes two trips over the fabric, asking for everything a trip needs at once
-// (32 loads of 16 bytes per lane in flight):
+// Two forms.  exchange_wavefront: two trips over the fabric per step, asking for everything a trip needs at once:
 //   0. the workgroup's sums leave as flagged words {value : tag};
 //   1. workgroup g adds up, for the g-th slice of the columns (whole 128-byte lines of words), the words of all G
 //      workgroups in a fixed order, applies the update to its slice of theta and publishes the new values in
 //      kThetaCopies copies of theta (a workgroup later reads copy g mod kThetaCopies, so no set of words is polled
 //      by the whole grid);
 //   2. it collects the whole new theta from its copy into shared memory and raises the version.
-// Its polls are bounded by the wall clock (PollGuard).
+// exchange_one_trip: every workgroup adds up all words itself and makes the whole update.
+// Polls are bounded by the wall clock.
+//
+// What bounds a step of short rows is latency: two trips of about 0.6 us, in each the time until the slowest workgroup has stored
+// its words, and the instructions between them.  us per update before / now (the loops, waits and state of the exchange as it was
+// before / written as ExchangeCommon says, residuals worked out once per row): 4.3 / 3.3 at p = 200, n = 4096 (256 workgroups); 5.1 / 3.6
+// at p = 512, n = 1000 with Adam (160); one trip, 32 workgroups: 5.2 / 2.9 at p = 123, n = 777 with momentum, 4.5 / 2.9 at
+// p = 128, n = 1024 (before: two trips, 40).
 #pragma once
 
 #include "bmgd_internal.h"
 #include "glm_device.h"
+
+#include <type_traits>
 
 namespace bmgd {
 namespace {
@@ -87,6 +95,52 @@ __device__ __forceinline__ void lds_wait_ge(unsigned addr, unsigned want, unsign
                  : "=&v"(t) : "v"(addr), "v"(want), "v"(abort_addr) : "vcc", "memory");
 }
 
+// The same for an exchange wavefront, which must not go on with the step if a wait ran out anywhere in the workgroup: until every
+// lane's word (one address per lane) is >= want, or the word at `abort_addr` is non-zero; that word is returned.  It looks at both in
+// one trip to shared memory.  No limit of its own is needed: the row wavefronts wait on shared memory only, and of the exchange
+// wavefronts each either goes on or ends its poll with the abort word set.
+template <bool SLEEP>
+__device__ __forceinline__ unsigned lds_wait_all_ge(unsigned addr, unsigned want, unsigned abort_addr)
+{
+    unsigned t, stop;
+    if constexpr (SLEEP)                             // a wait as long as a step's rows
+        asm volatile("s_branch 3f\n"
+                     "1:\n\t"
+                     "s_sleep 1\n"
+                     "3:\n\t"
+                     "ds_read_b32 %0, %2\n\t"
+                     "ds_read_b32 %1, %4\n\t"
+                     "s_waitcnt lgkmcnt(0)\n\t"
+                     "v_cmp_lt_u32_e32 vcc, %0, %3\n\t"
+                     "s_cbranch_vccz 2f\n\t"
+                     "v_cmp_ne_u32_e32 vcc, 0, %1\n\t"
+                     "s_cbranch_vccz 1b\n"
+                     "2:"
+                     : "=&v"(t), "=&v"(stop) : "v"(addr), "v"(want), "v"(abort_addr) : "vcc", "memory");
+    else
+        asm volatile("1:\n\t"
+                     "ds_read_b32 %0, %2\n\t"
+                     "ds_read_b32 %1, %4\n\t"
+                     "s_waitcnt lgkmcnt(0)\n\t"
+                     "v_cmp_lt_u32_e32 vcc, %0, %3\n\t"
+                     "s_cbranch_vccz 2f\n\t"
+                     "v_cmp_ne_u32_e32 vcc, 0, %1\n\t"
+                     "s_cbranch_vccz 1b\n"
+                     "2:"
+                     : "=&v"(t), "=&v"(stop) : "v"(addr), "v"(want), "v"(abort_addr) : "vcc", "memory");
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)stop);
+}
+
+// One is added to the word at shared-memory address `addr`, behind everything this wavefront has asked of shared memory.  For one lane.
+// (An atomic add of the language counts the active lanes first.)
+__device__ __forceinline__ void lds_add_one(unsigned addr)
+{
+    asm volatile("ds_add_u32 %0, %1" :: "v"(addr), "v"(1u) : "memory");
+}
+
+template <class T>
+__device__ __forceinline__ unsigned lds_address(const T* word) { return (unsigned)(uintptr_t)word; }
+
 // Mini-batches of the steps of a launch: step s is mini-batch m = s mod M of pass t = s / M.
 struct StepGeometry {
     int M, n, n_tail, perm_stride;
@@ -117,255 +171,507 @@ struct StepGeometry {
     }
 };
 
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
+
 // The exchange wavefronts' view of the workgroup's shared memory.
 struct ExchangeLds {
     lds_f32* th;                  // [2][th_stride]: theta by version parity (th_stride even, >= p rounded up to even)
     int th_stride;
-    lds_f32* red;                 // [kExchangeScratch * NX] scratch of the exchange wavefronts
-    const lds_f32* sums;          // [nsum][sums_stride]: the workgroup's gradient sums of a step; column c is the sum over
-    int nsum, sums_stride;        //   the nsum arrays, added in their order (columns [p, p rounded up to even) hold 0)
+    lds_f32* state;               // [NX][3][64][2]: for each exchange wavefront Adam's bias corrections of the coming steps, and the state
+                                  //   of the pairs of columns it updates
+    lds_f32* red;                 // [2][NX][64][2]: the exchange wavefronts' partial sums, by parity (NX > 1 only)
+    const lds_f32* sums;          // [NSUM][sums_stride]: the workgroup's gradient sums of a step; column c is the sum over
+    int sums_stride;              //   the NSUM arrays (even; columns [p, p rounded up to even) hold 0)
     unsigned publishers;          // publications of row wavefronts that complete a step
     lds_u32* s_published;
     lds_u32* s_theta_version;     // raised by every exchange wavefront once per step: NX v when version v is complete
     lds_i32* s_abort;
-    lds_u32* s_xarrived;          // NX > 1: [NX] chunks of slices each exchange wavefront has handed its partial sums of to
-    lds_u32* s_xconsumed;         //         the first one, and chunks that one has added up
+    lds_u32* s_xarrived;          // NX > 1: [NX] sets of partial sums each exchange wavefront has left in `red`
+    lds_u32* s_xconsumed;         //         sets that the first one has added up (two-trip form)
 };
-constexpr int kExchangeScratch = 3 * 128;            // floats of `red` per exchange wavefront
+constexpr int kExchangeState = 3 * 128, kExchangeRed = 2 * 128;     // floats of `state` and `red` per exchange wavefront
 
-// All steps [a.s_begin, a.s_end) of a launch, by exchange wavefront xw of NX of workgroup blockIdx.x of gridDim.x (a
-// multiple of 8).  p is even.  Returns when the last version of theta has been delivered (workgroup 0 also writes it to
-// a.theta), or with s_abort and the global abort flag set when a wait ran out.
+// What the exchange wavefronts of both forms do the same way.  NSUM: arrays of sums in shared memory.
+//
+// All of this stands on the critical path of a step, between the last row and the first of the next step, where one wavefront
+// on its SIMD issues an instruction in four clocks at best and a branch taken costs more: 100 instructions are 0.2 us.  So it is written
+// for few instructions: loops have one exit at the bottom and constant bounds (all reads of shared memory in one go; as run-time
+// loops each turn waited for its own read, 8 x 130 clocks), a wait that ran out is a flag that is looked at once per step, lanes
+// are summed with DPP, and shared memory's order (a wavefront's requests are served in the order they were made) stands where fences
+// would wait for stores to global memory as well.
+template <bool OPT, int NX, int NSUM>
+struct ExchangeCommon {
+    const GlmArgs& a;
+    const ExchangeLds& x;
+    const int lane, xw;
+    const int G, g, p, pp;
+    const StepGeometry geo;
+    const unsigned words_bytes;
+    const unsigned abort_addr;
+    long long poll_start = 0;                        // when the words of a trip were first asked for
+
+    __device__ __forceinline__ ExchangeCommon(const GlmArgs& a_, const ExchangeLds& x_, int lane_, int xw_)
+        : a(a_), x(x_), lane(lane_), xw(xw_), G(gridDim.x), g(blockIdx.x), p(a_.p), pp((a_.p + 15) & ~15), geo(a_),
+          words_bytes((unsigned)((size_t)gridDim.x * (size_t)((a_.p + 15) & ~15) * 8)), abort_addr(lds_address(x_.s_abort))
+    {
+    }
+
+    // until the word of every lane is >= want; non-zero: a wait ran out
+    template <bool SLEEP>
+    __device__ __forceinline__ unsigned wait_ge(const lds_u32* word, unsigned want) const
+    {
+        return lds_wait_all_ge<SLEEP>(lds_address(word), want, abort_addr);
+    }
+
+    // After a failed poll whose requests were sent at time `sent`: go on polling?  (The abort flag in global memory is looked at now and
+    // then: a load from it costs a trip over the fabric, as much as the poll itself.)
+    __device__ __forceinline__ bool go_on(unsigned& misses, long long sent)
+    {
+        if (misses == 0u) poll_start = sent;
+        ++misses;
+        if (sent - poll_start > a.timeout_ticks) return false;
+        return (misses & 31u) != 0u || __hip_atomic_load(a.sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+    }
+
+    // U pairs of words per lane (`ask(u)` loads the u-th), asked for all together until all that the lane needs carry the tag
+    // (`tags(w, u)`: the smaller of the u-th pair's tags, or `tag` where the lane does not need it).  Non-zero: the wait ran out.  (No tag
+    // beyond the one waited for can be there yet, so all are equal to it if the smallest is.)  Measured against it and not kept: two or
+    // three sets of requests under way one behind the other (3.3 -> 3.7 us per update at p = 200, n = 4096: the polls slow the stores they wait
+    // for), and asking again only for what has not come (3.7: a branch around each request).
+    template <int U, class Ask, class Tags>
+    __device__ __forceinline__ unsigned poll(unsigned tag, u32x4 (&w)[U], Ask&& ask, Tags&& tags)
+    {
+        unsigned misses = 0u;
+        bool miss;
+        long long sent;
+        do {
+            sent = wall_clock64();   // (looked at only if the poll fails, when it has long come)
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int u = 0; u < U; ++u) w[u] = ask(u);
+            asm volatile("" ::: "memory");
+            unsigned least = tag;
+#pragma unroll
+            for (int u = 0; u < U; ++u) least = min(least, tags(w[u], u));
+            miss = __builtin_amdgcn_ballot_w64(least != tag) != 0ull;
+        } while (miss && go_on(misses, sent));
+        return miss ? 1u : 0u;
+    }
+
+    // a wait of this wavefront ran out: the others of the workgroup and the other workgroups are told
+    __device__ __forceinline__ void give_up() const
+    {
+        if (lane == 0) {
+            __hip_atomic_store(a.sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(x.s_abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+    }
+
+    // the workgroup's sums of columns c and c + 1, added up as a fixed tree
+    __device__ __forceinline__ f32x2 sum_of(int c) const
+    {
+        f32x2 v[NSUM];
+#pragma unroll
+        for (int k = 0; k < NSUM; ++k) v[k] = *(const lds_f32x2*)(x.sums + k * x.sums_stride + c);
+#pragma unroll
+        for (int w = 1; w < NSUM; w *= 2) {
+#pragma unroll
+            for (int k = 0; k + w < NSUM; k += 2 * w) { v[k].x += v[k + w].x; v[k].y += v[k + w].y; }
+        }
+        return v[0];
+    }
+
+    // this wavefront's share of the workgroup's sums, as flagged words: what the others wait for
+    __device__ __forceinline__ void send_sums(__amdgpu_buffer_rsrc_t part, unsigned tag) const
+    {
+        auto send = [&](int c) {
+            if (c < p) {
+                const f32x2 v = sum_of(c);
+                __builtin_amdgcn_raw_buffer_store_b128(word_pair(v.x, v.y, tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, kAgentScope);
+            }
+        };
+        asm volatile("" ::: "memory");
+        if constexpr (NX == 1) {
+#pragma unroll 8
+            for (int c = 2 * lane; c < p; c += 128) send(c);
+        } else {
+#pragma unroll 1
+            for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) send(c0 + 2 * lane);
+        }
+    }
+
+    // What an update rule with state needs waits in shared memory, where reading it costs the update next to nothing (two powers a
+    // step and state in global memory stood on its critical path: logistic regression with Adam, p = 512, n = 1000: 5.3 us per
+    // update): Adam's bias corrections, which depend on the update's number alone, of 64 steps at a time, formed by 64 lanes
+    // at once; and the state of the pair of columns that this wavefront's lane (or slot) `k` updates.
+    __device__ __forceinline__ void corrections(int done)
+    {
+        if constexpr (OPT) {
+            if (a.opt.kind == kOptAdam && (done & 63) == 0) {
+                float f1, f2;
+                opt_corrections(a.opt, a.opt.k_base + done + lane + 1, f1, f2);
+                ((lds_f32x2*)(x.state + xw * 384))[lane] = f32x2{f1, f2};
+            }
+        }
+    }
+    __device__ __forceinline__ void load_state(int k, const float* m, const float* s) const
+    {
+        lds_f32x2* keep = (lds_f32x2*)(x.state + xw * 384 + 128) + k;
+        keep[0] = f32x2{m[0], m[1]};
+        if (a.opt.kind == kOptAdam) keep[64] = f32x2{s[0], s[1]};
+    }
+    __device__ __forceinline__ void store_state(int k, float* m, float* s) const
+    {
+        const lds_f32x2* keep = (const lds_f32x2*)(x.state + xw * 384 + 128) + k;
+        const f32x2 v = keep[0], w = keep[64];
+        m[0] = v.x; m[1] = v.y;
+        if (a.opt.kind == kOptAdam) { s[0] = w.x; s[1] = w.y; }
+    }
+    // The update of one pair of columns: new values from the old ones and the pair's sums.  k: where its state is kept (`writes`: by
+    // this lane; lanes that hold the same pair make the same update).
+    __device__ __forceinline__ f32x2 update(f32x2 old, f32x2 sum, float nb, float scale, float alpha, int done, int k, bool writes) const
+    {
+        if constexpr (!OPT) {
+            return f32x2{old.x - scale * sum.x, old.y - scale * sum.y};
+        } else {
+            asm volatile("" ::: "memory");
+            lds_f32x2* keep = (lds_f32x2*)(x.state + xw * 384 + 128) + k;
+            const f32x2 c = ((const lds_f32x2*)(x.state + xw * 384))[done & 63];   // (not looked at but by Adam)
+            const f32x2 m = keep[0], s = keep[64];
+            float m0 = m.x, m1 = m.y, s0 = s.x, s1 = s.y;
+            const float n0 = opt_update(a.opt, old.x, sum.x / nb, alpha, m0, s0, c.x, c.y);
+            const float n1 = opt_update(a.opt, old.y, sum.y / nb, alpha, m1, s1, c.x, c.y);
+            if (writes) {
+                keep[0] = f32x2{m0, m1};
+                if (a.opt.kind == kOptAdam) keep[64] = f32x2{s0, s1};
+            }
+            return f32x2{n0, n1};
+        }
+    }
+
+    // (everything this wavefront has stored to shared memory stays in front of the count)
+    __device__ __forceinline__ void raise_version() const
+    {
+        asm volatile("" ::: "memory");
+        if (lane == 0) lds_add_one(lds_address(x.s_theta_version));
+    }
+    __device__ __forceinline__ void mark_arrived(unsigned count) const
+    {
+        asm volatile("" ::: "memory");
+        if (lane == 0) __hip_atomic_store(x.s_xarrived + xw, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+
+    // the end of a launch: theta to global memory
+    __device__ __forceinline__ void finish(int steps) const
+    {
+        if (g == 0 && xw == 0) {
+            if (wait_ge<true>(x.s_theta_version, NX * (unsigned)steps)) return;
+            asm volatile("" ::: "memory");
+            const lds_f32* fin = x.th + ((unsigned)steps & 1u) * x.th_stride;
+            for (int c = lane; c < p; c += 64) a.theta[c] = fin[c];
+        }
+    }
+};
+
+// The sum over the lanes with the same lane % PPc (8 <= PPc <= 64, uniform), in all of them.
+__device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
+{
+    if (PPc == 8) {                                  // the usual case as one straight line
+        v.x += dpp_mov<0x128>(v.x); v.y += dpp_mov<0x128>(v.y);
+        v.x = swap16_sum(v.x); v.y = swap16_sum(v.y);
+        v.x = swap32_sum(v.x); v.y = swap32_sum(v.y);
+    } else if (PPc < 64) {
+        if (PPc == 16) { v.x = swap16_sum(v.x); v.y = swap16_sum(v.y); }
+        v.x = swap32_sum(v.x); v.y = swap32_sum(v.y);
+    }
+    return v;
+}
+
+// All steps [a.s_begin, a.s_end) of a launch in two trips over the fabric each, by exchange wavefront xw of NX of workgroup
+// blockIdx.x of gridDim.x (a multiple of 8).  Returns when the last version of theta has been delivered (workgroup 0 also writes it
+// to a.theta), or with s_abort and the global abort flag set when a wait ran out.
 // With NX > 1 the wavefronts share every phase: each sends a part of the workgroup's sums, adds up a part of the
 // workgroups for the slice (the first one then adds the NX partial sums in their order and applies the update) and
 // collects a part of theta.  A wavefront pulls freshly written lines at a fraction of what a compute unit can take,
 // so where no row traffic competes (narrow rows) four wavefronts on the four SIMDs finish a trip sooner.
 // U1, U2: pairs of words a lane requests per trip when it sums the slice / collects theta.
-template <bool OPT, int NX, int U1, int U2>
+template <bool OPT, int NX, int NSUM, int U1, int U2>
 __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
 {
-    const int G = gridDim.x;
-    const int g = blockIdx.x;
-    const int p = a.p;
-    const int pp = (p + 15) & ~15;                   // stride of a row of words
+    ExchangeCommon<OPT, NX, NSUM> ex(a, x, lane, xw);
+    const int G = ex.G, g = ex.g, p = ex.p, pp = ex.pp;
     const int first = a.s_begin, last = a.s_end;
-    const StepGeometry geo(a);
-    const unsigned words_bytes = (unsigned)((size_t)G * pp * 8);
     const unsigned copies_bytes = (unsigned)((size_t)kThetaCopies * pp * 8);
     // Workgroup g owns the columns [c_lo, c_hi) of theta (whole 128-byte lines of words, so no line has two writers).
     const int cw = (((p + G - 1) / G) + 15) & ~15;
     const int c_lo = min(p, g * cw), c_hi = min(p, c_lo + cw);
     const int npair = cw / 2;                        // column pairs of a slice (a multiple of 8)
-    const int PPc = min(npair, 64);                  // pairs taken side by side by the lanes ...
+    int PPc = 8;                                     // pairs taken side by side by the lanes (a power of two) ...
+    while (PPc < npair && PPc < 64) PPc *= 2;
     const int SG = 64 / PPc;                         // ... by SG groups of lanes, each group taking every SG-th workgroup
-    const int my_pair = lane % PPc, my_sg = lane / PPc;
-    const bool lane_used = my_sg < SG;
-    lds_f32* red = x.red + xw * 128;                 // [64][2]: this wavefront's own scratch
-    lds_f32* xpart = x.red + NX * 128;               // [2][NX][64][2]: the wavefronts' partial sums of a chunk of the slice, by parity
-    PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
-    bool dead = false;
-    unsigned phase = 0u;                             // chunks of slices summed so far (the same in all NX wavefronts)
-    // A wait on shared memory alone (the wall clock and the global abort flag are looked at now and then: a load from
-    // global memory would return after microseconds).  False: give up.
-    auto spin_ge = [&](lds_u32* word, unsigned want) -> bool {
-        long long t0 = 0;
-        unsigned spins = 0u;
-        while (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) < want) {
-            __builtin_amdgcn_s_sleep(1);
-            if constexpr (NX > 1) {
-                if (__hip_atomic_load(x.s_abort, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0) return false;
-            }
-            if ((++spins & 1023u) == 0u) {
-                const long long now = wall_clock64();
-                if (t0 == 0) t0 = now;
-                if (now - t0 > a.timeout_ticks ||
-                    __hip_atomic_load(a.sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0u) return false;
-            }
+    const int my_pair = lane & (PPc - 1), my_sg = lane / PPc;
+    // State of an update rule: a slice of one chunk keeps it in shared memory from step to step (a wider one, chunk by chunk, does not)
+    const bool one_chunk = npair <= PPc;
+    auto load_state = [&](int c) {                   // (the arrays reach to p rounded up to 16)
+        if constexpr (OPT) {
+            if (xw == 0 && my_sg == 0 && c < c_hi) ex.load_state(my_pair, a.opt.m + c, a.opt.s + c);
         }
-        return true;
     };
-    for (int s = first; s < last && !dead; ++s) {
+    auto store_state = [&](int c) {
+        if constexpr (OPT) {
+            asm volatile("" ::: "memory");
+            if (xw == 0 && my_sg == 0 && c < c_hi) ex.store_state(my_pair, a.opt.m + c, a.opt.s + c);
+        }
+    };
+    if (one_chunk) load_state(c_lo + 2 * my_pair);
+    unsigned dead = 0u;
+    unsigned phase = 0u;                             // chunks of slices summed so far (the same in all NX wavefronts)
+    int s = first;
+#pragma clang loop unroll(disable)
+    do {
         const unsigned tag = a.tag_base + (unsigned)(s - first) + 1u;
         const float alpha_s = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
-        const int nb = geo.batch_rows(s);
-        const float scale = alpha_s / (float)nb;
+        const float nb = (float)ex.geo.batch_rows(s);
+        const float scale = alpha_s / nb;
         const unsigned ver = (unsigned)(s - first);
         const lds_f32* th_old = x.th + (ver & 1u) * x.th_stride;
         lds_f32* th_new = x.th + ((ver + 1u) & 1u) * x.th_stride;
-        float oc1 = 1.f, oc2 = 1.f;
-        if constexpr (OPT) {
-            if (a.opt.kind == kOptAdam) opt_corrections(a.opt, a.opt.k_base + (s - first) + 1, oc1, oc2);
-        }
-        // This workgroup's own rows first: until they have been summed nothing can be complete, and polling the
-        // fabric meanwhile would only take bandwidth from the rows.
-        if (!spin_ge(x.s_published, (ver + 1u) * x.publishers)) { dead = true; break; }
-        guard.arm();
-        const __amdgpu_buffer_rsrc_t part = words_rsrc(a.ll_part + (size_t)(s & 1) * G * pp, words_bytes);
-        // 0. this workgroup's sums out of shared memory, as flagged words: what the others wait for
-        asm volatile("" ::: "memory");
-        if (x.nsum == 1) {
-#pragma unroll 8
-            for (int c = 2 * (lane + 64 * xw); c < p; c += 128 * NX)
-                __builtin_amdgcn_raw_buffer_store_b128(word_pair(x.sums[c], x.sums[c + 1], tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, kAgentScope);
-        } else {
-            for (int c = 2 * (lane + 64 * xw); c < p; c += 128 * NX) {
-                float v0 = 0.f, v1 = 0.f;
-                for (int k = 0; k < x.nsum; ++k) {
-                    v0 += x.sums[k * x.sums_stride + c];
-                    v1 += x.sums[k * x.sums_stride + c + 1];
-                }
-                __builtin_amdgcn_raw_buffer_store_b128(word_pair(v0, v1, tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, kAgentScope);
-            }
-        }
+        ex.corrections(s - first);
+        const __amdgpu_buffer_rsrc_t part = words_rsrc(a.ll_part + (size_t)(s & 1) * G * pp, ex.words_bytes);
         const __amdgpu_buffer_rsrc_t thw = words_rsrc(a.ll_theta + (size_t)(s & 1) * kThetaCopies * pp, copies_bytes);
+        // (the buffer of the copy this workgroup reads is that copy alone, so loads beyond its row of words are answered with
+        // zeros by the range check without going to memory, and are not looked at)
+        const __amdgpu_buffer_rsrc_t mine = words_rsrc(a.ll_theta + ((size_t)(s & 1) * kThetaCopies + (size_t)(g % kThetaCopies)) * pp, (unsigned)(pp * 8));
+        // This workgroup's own rows first: until they have been summed nothing can be complete, and polling the
+        // fabric meanwhile would only take bandwidth from the rows.  (The rows were multiplied by a complete theta, so
+        // every exchange wavefront has delivered its part of the version that this step's update starts from.)
+        dead |= ex.template wait_ge<(NX == 1)>(x.s_published, (ver + 1u) * x.publishers);
+        // 0. this workgroup's sums out of shared memory
+        ex.send_sums(part, tag);
 
         // 1. this workgroup's slice, if it has one: sum over all workgroups, in a fixed order; the update; the new
         //    values into every copy of theta
-        for (int pb = 0; pb < npair && c_lo < c_hi && !dead; pb += PPc) {
-            const int c = c_lo + 2 * (pb + my_pair);
-            const bool mine = lane_used && c < c_hi;             // (a slice ends on a multiple of 16 or at p)
-            // One address register per lane (its pair of columns in the row of words of workgroup my_sg); what differs
-            // between a lane's loads is uniform and goes into the scalar offset.  Load u of wavefront xw takes the
-            // workgroups SG (xw + NX u) + my_sg.  G is a multiple of SG, so whether a load is beyond the last
-            // workgroup is uniform too (such loads repeat the last group and are not added).
-            const unsigned voff = (unsigned)min(c, pp - 2) * 8u + (unsigned)my_sg * (unsigned)(pp * 8);
-            float t0 = 0.f, t1 = 0.f;
-            for (int i0 = 0; i0 < G && !dead; i0 += SG * NX * U1) {
-                u32x4 w[U1];
-                for (;;) {
-                    asm volatile("" ::: "memory");
-#pragma unroll
-                    for (int u = 0; u < U1; ++u)
-                        w[u] = __builtin_amdgcn_raw_buffer_load_b128(part, voff, (unsigned)min(i0 + SG * (xw + NX * u), G - SG) * (unsigned)(pp * 8), kAgentScope);
-                    asm volatile("" ::: "memory");
-                    unsigned miss = 0u;
-#pragma unroll
-                    for (int u = 0; u < U1; ++u) miss |= (w[u].y ^ tag) | (w[u].w ^ tag);
-                    if (!mine) miss = 0u;
-                    if (__builtin_amdgcn_ballot_w64(miss != 0u) == 0ull) break;
-                    if (guard.expired()) { dead = true; break; }
-                }
-                if (dead) break;
-#pragma unroll
-                for (int u = 0; u < U1; ++u)
-                    if (i0 + SG * (xw + NX * u) < G) {
-                        t0 += as_float(w[u].x);
-                        t1 += as_float(w[u].z);
-                    }
-            }
-            if (dead) break;
-            // the SG groups' sums meet in shared memory (this wavefront alone uses its `red`; its requests are served in order)
-            if (lane_used) {
-                red[(my_sg * PPc + my_pair) * 2] = t0;
-                red[(my_sg * PPc + my_pair) * 2 + 1] = t1;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            const bool upd = lane < PPc && c < c_hi;             // this lane ends up with a pair of the slice
-            float b0 = 0.f, b1 = 0.f;
-            if (upd) {
-                for (int q = 0; q < SG; ++q) {
-                    b0 += red[(q * PPc + lane) * 2];
-                    b1 += red[(q * PPc + lane) * 2 + 1];
-                }
-            }
-            if constexpr (NX > 1) {
-                // the NX wavefronts' sums meet in the first one (two sets of partial sums alternate; a wavefront does
-                // not overwrite a set before the first one has added it up)
-                if (phase >= 2u && !spin_ge(x.s_xconsumed, phase - 1u)) { dead = true; break; }
-                lds_f32* out = xpart + ((phase & 1u) * NX + xw) * 128;
-                if (upd) { out[lane * 2] = b0; out[lane * 2 + 1] = b1; }
-                asm volatile("" ::: "memory");
-                if (lane == 0) __hip_atomic_store(x.s_xarrived + xw, phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                if (xw == 0) {
-                    // (also: every wavefront has delivered its part of the theta this update starts from)
-                    bool all = spin_ge(x.s_theta_version, NX * ver);
-                    for (int k = 1; k < NX && all; ++k) all = spin_ge(x.s_xarrived + k, phase + 1u);
-                    if (!all) { dead = true; break; }
-                    asm volatile("" ::: "memory");
-                    b0 = 0.f; b1 = 0.f;
-                    if (upd) {
-                        for (int k = 0; k < NX; ++k) {
-                            b0 += xpart[((phase & 1u) * NX + k) * 128 + lane * 2];
-                            b1 += xpart[((phase & 1u) * NX + k) * 128 + lane * 2 + 1];
-                        }
+        if (c_lo < c_hi) {
+            int pb = 0;
+#pragma clang loop unroll(disable)
+            do {
+                const int c = c_lo + 2 * (pb + my_pair);
+                const bool own = c < c_hi;                       // (a slice ends on a multiple of 16 or at p)
+                if (!one_chunk) {
+                    load_state(c);
+                    // two sets of partial sums alternate: a wavefront does not overwrite a set before the first one has added
+                    // it up (a slice of one chunk cannot come to that: its theta has been collected since)
+                    if constexpr (NX > 1) {
+                        if (phase >= 2u) dead |= ex.template wait_ge<false>(x.s_xconsumed, phase - 1u);
                     }
                 }
-            }
-            if (upd && xw == 0) {
-                float n0, n1;
-                if constexpr (!OPT) {
-                    n0 = th_old[c] - scale * b0;
-                    n1 = th_old[c + 1] - scale * b1;
-                } else {
-                    float m0 = a.opt.m[c], m1 = a.opt.m[c + 1];
-                    float s0 = a.opt.kind == kOptAdam ? a.opt.s[c] : 0.f, s1 = a.opt.kind == kOptAdam ? a.opt.s[c + 1] : 0.f;
-                    n0 = opt_update(a.opt, th_old[c], b0 / (float)nb, alpha_s, m0, s0, oc1, oc2);
-                    n1 = opt_update(a.opt, th_old[c + 1], b1 / (float)nb, alpha_s, m1, s1, oc1, oc2);
-                    a.opt.m[c] = m0; a.opt.m[c + 1] = m1;
-                    if (a.opt.kind == kOptAdam) { a.opt.s[c] = s0; a.opt.s[c + 1] = s1; }
-                }
-                const u32x4 nw = word_pair(n0, n1, tag);
+                // One address register per lane (its pair of columns in the row of words of workgroup my_sg); what differs
+                // between a lane's loads is uniform and goes into the scalar offset.  Load u of wavefront xw takes the
+                // workgroups SG (xw + NX u) + my_sg.  G is a multiple of SG, so whether a load is beyond the last
+                // workgroup is uniform too (such loads repeat the last group and are not added).
+                const unsigned voff = (unsigned)min(c, pp - 2) * 8u + (unsigned)my_sg * (unsigned)(pp * 8);
+                f32x2 t = {0.f, 0.f};
+                int i0 = SG * xw;
+#pragma clang loop unroll(disable)
+                do {
+                    u32x4 w[U1];
+                    dead |= ex.poll(tag, w,
+                        [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(part, voff, (unsigned)min(i0 + SG * NX * u, G - SG) * (unsigned)(pp * 8), kAgentScope); },
+                        [&](const u32x4& v, int) { return own ? min(v.y, v.w) : tag; });
 #pragma unroll
-                for (int r = 0; r < kThetaCopies; ++r)
-                    __builtin_amdgcn_raw_buffer_store_b128(nw, thw, (unsigned)c * 8u, (unsigned)(r * pp * 8), kAgentScope);
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // `red` is reused by the next chunk of pairs
-            if constexpr (NX > 1) {
-                if (xw == 0 && lane == 0) __hip_atomic_store(x.s_xconsumed, phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    for (int u = 0; u < U1; ++u) {
+                        const bool there = i0 + SG * NX * u < G;
+                        t.x += there ? as_float(w[u].x) : 0.f;
+                        t.y += there ? as_float(w[u].z) : 0.f;
+                    }
+                    i0 += SG * NX * U1;
+                } while (i0 - SG * xw < G && dead == 0u);
+                t = pair_slot_sum(t, PPc);           // the SG groups' sums meet over the lanes: every lane has its pair's
+                if constexpr (NX > 1) {
+                    // the NX wavefronts' sums meet in the first one
+                    lds_f32x2* set = (lds_f32x2*)(x.red + (phase & 1u) * NX * 128);
+                    if (xw != 0) {
+                        if (lane < PPc) set[xw * 64 + lane] = t;
+                        ex.mark_arrived(phase + 1u);
+                    } else {
+                        dead |= ex.template wait_ge<false>(x.s_xarrived + 1 + min(lane, NX - 2), phase + 1u);
+                        asm volatile("" ::: "memory");
+                        f32x2 v[NX - 1];
+#pragma unroll
+                        for (int k = 1; k < NX; ++k) v[k - 1] = set[k * 64 + my_pair];
+#pragma unroll
+                        for (int k = 1; k < NX; ++k) { t.x += v[k - 1].x; t.y += v[k - 1].y; }
+                    }
+                }
+                if (own && xw == 0) {
+                    const f32x2 old = *(const lds_f32x2*)(th_old + c);
+                    const f32x2 now = ex.update(old, t, nb, scale, alpha_s, s - first, my_pair, my_sg == 0);
+                    const u32x4 nw = word_pair(now.x, now.y, tag);
+                    // the groups of lanes share the copies between them
+                    const unsigned to = (unsigned)c * 8u + (unsigned)(my_sg * pp * 8);
+                    static_assert(kThetaCopies == 8, "as many copies as groups of lanes at most");
+                    __builtin_amdgcn_raw_buffer_store_b128(nw, thw, to, 0u, kAgentScope);
+                    for (int r = SG; r < kThetaCopies; r += SG)
+                        __builtin_amdgcn_raw_buffer_store_b128(nw, thw, to, (unsigned)(r * pp * 8), kAgentScope);
+                }
+                if (!one_chunk) {
+                    store_state(c);
+                    if constexpr (NX > 1) {
+                        asm volatile("" ::: "memory");
+                        if (xw == 0 && lane == 0) __hip_atomic_store(x.s_xconsumed, phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                }
                 ++phase;
-            }
+                pb += PPc;
+            } while (pb < npair && dead == 0u);
         }
-        if (dead) break;
         // 2. the whole new theta, from this workgroup's copy
-        // (one address register per lane again; the buffer is that copy alone, so loads beyond its row of words are
-        // answered with zeros by the range check without going to memory, and are not looked at)
-        const __amdgpu_buffer_rsrc_t mine = words_rsrc(a.ll_theta + ((size_t)(s & 1) * kThetaCopies + (size_t)(g % kThetaCopies)) * pp, (unsigned)(pp * 8));
-        const unsigned copy_off = (unsigned)lane * 16u;
-        for (int c0 = 128 * xw; c0 < p && !dead; c0 += 128 * NX * U2) {
-            u32x4 w[U2];
-            for (;;) {
-                asm volatile("" ::: "memory");
+        if (128 * xw < p && dead == 0u) {
+            const unsigned copy_off = (unsigned)lane * 16u;
+            auto collect = [&](auto count, int c0) {
+                constexpr int U = decltype(count)::value;
+                u32x4 w[U];
+                dead |= ex.poll(tag, w,
+                    [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(mine, copy_off, (unsigned)(c0 + 128 * NX * u) * 8u, kAgentScope); },
+                    [&](const u32x4& v, int u) { return c0 + 2 * (lane + 64 * NX * u) < p ? min(v.y, v.w) : tag; });
 #pragma unroll
-                for (int u = 0; u < U2; ++u)
-                    w[u] = __builtin_amdgcn_raw_buffer_load_b128(mine, copy_off, (unsigned)(c0 + 128 * NX * u) * 8u, kAgentScope);
-                asm volatile("" ::: "memory");
-                unsigned miss = 0u;
-#pragma unroll
-                for (int u = 0; u < U2; ++u)
-                    if (c0 + 2 * (lane + 64 * NX * u) < p) miss |= (w[u].y ^ tag) | (w[u].w ^ tag);
-                if (__builtin_amdgcn_ballot_w64(miss != 0u) == 0ull) break;
-                if (guard.expired()) { dead = true; break; }
-            }
-            if (dead) break;
-#pragma unroll
-            for (int u = 0; u < U2; ++u) {
-                const int c = c0 + 2 * (lane + 64 * NX * u);
-                if (c < p) {
-                    th_new[c] = as_float(w[u].x);
-                    th_new[c + 1] = as_float(w[u].z);
+                for (int u = 0; u < U; ++u) {
+                    const int c = c0 + 2 * (lane + 64 * NX * u);
+                    if (c < p) *(lds_f32x2*)(th_new + c) = f32x2{as_float(w[u].x), c + 1 < p ? as_float(w[u].z) : 0.f};
                 }
+            };
+            if (p <= 128 * NX) {
+                collect(std::integral_constant<int, 1>{}, 128 * xw);
+            } else {
+                int c0 = 128 * xw;
+#pragma clang loop unroll(disable)
+                do {
+                    collect(std::integral_constant<int, U2>{}, c0);
+                    c0 += 128 * NX * U2;
+                } while (c0 < p && dead == 0u);
             }
         }
-        if (dead) break;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        if (lane == 0) __hip_atomic_fetch_add(x.s_theta_version, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (dead != 0u) ex.give_up();
+        ex.raise_version();
+        ++s;
+    } while (s < last && dead == 0u);
+    if (dead != 0u) return;
+    if (one_chunk) store_state(c_lo + 2 * my_pair);
+    ex.finish(last - first);
+}
+
+// The same steps in ONE trip over the fabric: every workgroup adds up all sums of all workgroups itself, in the same order, and keeps
+// its own copy of theta and of an update rule's state (at m + g pp).  For few words (G p of them come in per step and workgroup).
+// p <= 128 NX.  The NX wavefronts split the columns into chunks of 64 pairs and, where there are fewer chunks than wavefronts, the
+// workgroups of a chunk; the partial sums meet in shared memory, and every wavefront updates its part of theta.
+template <bool OPT, int NX, int NSUM>
+__device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
+{
+    ExchangeCommon<OPT, NX, NSUM> ex(a, x, lane, xw);
+    const int G = ex.G, g = ex.g, p = ex.p, pp = ex.pp;
+    const int first = a.s_begin, last = a.s_end;
+    const int npair = (p + 1) / 2;
+    int nc = 1;                                      // chunks of columns (a power of two <= NX)
+    while (64 * nc < npair) nc *= 2;
+    int PPc = 64;                                    // pairs side by side (a power of two >= 2 NX)
+    while (nc == 1 && PPc > 2 * NX && PPc / 2 >= npair) PPc /= 2;
+    const int SG = 64 / PPc;                         // groups of lanes, each taking every SG-th workgroup
+    const int my_pair = lane & (PPc - 1), my_sg = lane / PPc;
+    const int wpc = NX / nc;                         // wavefronts per chunk
+    const int chunk = xw / wpc, share = xw % wpc;
+    const int c = 2 * (64 * chunk + my_pair);        // the pair of columns this lane adds up
+    const bool mine = c < p && my_sg < G;
+    const unsigned voff = (unsigned)min(c, pp - 2) * 8u + (unsigned)min(my_sg, G - 1) * (unsigned)(pp * 8);
+    const int loads = (G + SG * wpc - 1) / (SG * wpc);            // pairs of words a lane asks for per step (as one, two, four, or eight at a time)
+    const int PW = PPc / wpc;                        // pairs a wavefront of a chunk updates
+    const int up = share * PW + lane;                // the pair of the chunk this lane updates (lane < PW)
+    const int uc = 2 * (64 * chunk + up);
+    const bool upd = lane < PW && uc < p;
+    if constexpr (OPT) {
+        if (upd) ex.load_state(lane, a.opt.m + (size_t)g * pp + uc, a.opt.s + (size_t)g * pp + uc);   // (the arrays reach to p rounded up to 16, per workgroup)
     }
-    if (dead) {
-        if (lane == 0) {
-            __hip_atomic_store(a.sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(x.s_abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        return;
-    }
-    if (g == 0 && xw == 0) {
-        if constexpr (NX > 1) {
-            if (!spin_ge(x.s_theta_version, NX * (unsigned)(last - first))) return;
+    unsigned dead = 0u;
+    int s = first;
+#pragma clang loop unroll(disable)
+    do {
+        const unsigned tag = a.tag_base + (unsigned)(s - first) + 1u;
+        const float alpha_s = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
+        const float nb = (float)ex.geo.batch_rows(s);
+        const float scale = alpha_s / nb;
+        const unsigned ver = (unsigned)(s - first);
+        const lds_f32* th_old = x.th + (ver & 1u) * x.th_stride;
+        lds_f32* th_new = x.th + ((ver + 1u) & 1u) * x.th_stride;
+        ex.corrections(s - first);
+        const __amdgpu_buffer_rsrc_t part = words_rsrc(a.ll_part + (size_t)(s & 1) * G * pp, ex.words_bytes);
+        dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
+        f32x2 t = {0.f, 0.f};
+        if (G == 1) {
             asm volatile("" ::: "memory");
+            if (upd) t = ex.sum_of(uc);
+        } else {
+            ex.send_sums(part, tag);
+            // Words of many workgroups take a wavefront long to fetch: asked for at once they would be fetched twice, none of the others'
+            // having come yet (2.91 against 3.18 us per update with 32 workgroups at p = 128, n = 1024; nothing with few)
+            if (loads > 2) __builtin_amdgcn_s_sleep(15);
+            // Load u of this wavefront takes the workgroups i + my_sg, i = i0 + SG wpc u.  The last loads start at G - SG at most;
+            // what they bring a second time (workgroups below i) is not added.
+            f32x2 r = {0.f, 0.f};
+            auto trips = [&](auto count) {
+                constexpr int U = decltype(count)::value;
+                int i0 = SG * share;
+#pragma clang loop unroll(disable)
+                do {
+                    u32x4 w[U];
+                    dead |= ex.poll(tag, w,
+                        [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(part, voff, (unsigned)max(0, min(i0 + SG * wpc * u, G - SG)) * (unsigned)(pp * 8), kAgentScope); },
+                        [&](const u32x4& v, int) { return mine ? min(v.y, v.w) : tag; });
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = i0 + SG * wpc * u;
+                        const bool add = mine && i < G && max(0, min(i, G - SG)) + my_sg >= i;
+                        r.x += add ? as_float(w[u].x) : 0.f;
+                        r.y += add ? as_float(w[u].z) : 0.f;
+                    }
+                    i0 += SG * wpc * U;
+                } while (i0 - SG * share < G && dead == 0u);
+            };
+            if (loads <= 1) trips(std::integral_constant<int, 1>{});
+            else if (loads <= 2) trips(std::integral_constant<int, 2>{});
+            else if (loads <= 4) trips(std::integral_constant<int, 4>{});
+            else trips(std::integral_constant<int, 8>{});
+            r = pair_slot_sum(r, PPc);
+            // The chunk's wavefronts meet in shared memory.  (Two sets alternate; a set is written again two steps later, behind
+            // rows that waited for the theta made from it.)
+            lds_f32x2* set = (lds_f32x2*)(x.red + (ver & 1u) * NX * 128) + chunk * wpc * 64;
+            if (lane < PPc) set[share * 64 + lane] = r;
+            ex.mark_arrived(ver + 1u);
+            dead |= ex.template wait_ge<false>(x.s_xarrived + chunk * wpc + min(lane, wpc - 1), ver + 1u);
+            asm volatile("" ::: "memory");
+            f32x2 v[NX];
+#pragma unroll
+            for (int k = 0; k < NX; ++k) v[k] = set[min(k, wpc - 1) * 64 + min(up, PPc - 1)];
+#pragma unroll
+            for (int k = 0; k < NX; ++k) {
+                t.x += k < wpc ? v[k].x : 0.f;
+                t.y += k < wpc ? v[k].y : 0.f;
+            }
         }
-        const lds_f32* fin = x.th + ((unsigned)(last - first) & 1u) * x.th_stride;
-        for (int c = lane; c < p; c += 64) a.theta[c] = fin[c];
+        if (upd) {
+            const f32x2 old = *(const lds_f32x2*)(th_old + uc);
+            const f32x2 now = ex.update(old, t, nb, scale, alpha_s, s - first, lane, true);
+            *(lds_f32x2*)(th_new + uc) = f32x2{now.x, uc + 1 < p ? now.y : 0.f};
+        }
+        if (dead != 0u) ex.give_up();
+        ex.raise_version();
+        ++s;
+    } while (s < last && dead == 0u);
+    if (dead != 0u) return;
+    if constexpr (OPT) {
+        asm volatile("" ::: "memory");
+        if (upd) ex.store_state(lane, a.opt.m + (size_t)g * pp + uc, a.opt.s + (size_t)g * pp + uc);
     }
+    ex.finish(last - first);
 }
 
 }  // namespace

@@ -640,6 +640,13 @@ KernelFn pick_kernel(const GlmLaunchShape& s)
 
 }  // namespace
 
+namespace {
+
+// Words that a workgroup fetches per step when every workgroup adds up the sums of all of them.
+constexpr int64_t kRedundantMaxWords = 4096;
+
+}  // namespace
+
 bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape* out, char* why, size_t why_len)
 {
     GlmLaunchShape s{};
@@ -661,7 +668,6 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
         }
     }
     s.block = s.CPL >= 8 ? 512 : 1024;
-    const int slots_per_group = (s.block / 64) * (64 / s.L);
     int G = requested_G;
     if (G <= 0) {
         // measured on MI355X: a compute unit sustains ~19 GB/s of gathered rows, one exchange costs 1.5-3 us;
@@ -671,15 +677,30 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
     }
     if (G < 1) G = 1;
     if (G > num_cus) G = num_cus;
-    // narrow rows on eight or more workgroups, a step's rows fitting the registers: the kernel with an exchange wavefront
-    // (not where the sums of all workgroups are few enough for every workgroup to add them up itself: one trip
-    // over the fabric per step instead of two)
-    if (s.CPL < 8 && s.V >= 2 && G >= 8 && (int64_t)G * p > 4096) {
-        const int pf = glm_narrow_rows_in_flight(s.V, s.CPL, s.L, G & ~7, n);
+    // Narrow rows, a step's rows fitting the registers: the kernel with exchange wavefronts.  Where the sums of all workgroups are few
+    // enough every workgroup adds them up itself, in one trip over the fabric per step instead of two.
+    const int L = std::max(s.L, 4);                  // (that kernel's lanes work out residuals in fours)
+    auto rows_held = [&](int rw, int groups) { return s.CPL < 8 ? glm_narrow_rows_in_flight(s.V, s.CPL, L, rw, groups, n) : 0; };
+    if (requested_G <= 0 && p <= kNarrowOneTripMaxP) {
+        // Left to choose: one workgroup if it holds a step's rows (no exchange: 1.9 us per update at p = 30, n = 200, 2.5 to 2.7 on two
+        // to eight), and not more than 32 for rows of up to 128 floats (one trip: 2.9 us at p = 128, n = 1024; 43 workgroups in two
+        // trips 3.2; 2.9 against 3.0 at p = 50, n = 3000; with eight rows per lane slot they gather for longer than two trips take:
+        // 3.8 against 3.3 at p = 90, n = 2500).  More rows than those hold need more workgroups.
+        const int held = rows_held(kNarrowMoreRows, 32);
+        if (rows_held(kNarrowMoreRows, 1) > 0) G = 1;
+        else if (G > 32 && 32 * p <= kRedundantMaxWords && held > 0 && held <= 4) G = 32;
+    }
+    const bool few_sums = (int64_t)G * p <= kRedundantMaxWords;
+    if (few_sums ? p <= kNarrowOneTripMaxP : G >= 8) {
+        const int rw = few_sums || s.V == 1 ? kNarrowMoreRows : 8;
+        const int Gn = few_sums ? G : G & ~7;
+        const int pf = rows_held(rw, Gn);
         if (pf > 0) {
             s.narrow = 1;
             s.narrow_pf = pf;
-            G &= ~7;
+            s.narrow_rw = rw;
+            s.L = L;
+            G = Gn;
         }
     }
     s.G = G;
@@ -687,6 +708,7 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
     s.p = (int)p;
     // Rows each row slot must take per step.  If one register-resident group covers it, the whole next
     // batch is prefetched across the exchange (no look-ahead needed); otherwise iterate with look-ahead.
+    const int slots_per_group = (s.block / 64) * (64 / s.L);
     const int64_t need = (n + (int64_t)G * slots_per_group - 1) / ((int64_t)G * slots_per_group);
     if (s.CPL >= 8) {
         s.PF = 1; s.pipe = kPipeWide;
@@ -696,7 +718,7 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
     } else {
         s.PF = max_pf(s.V, s.CPL); s.pipe = kPipeGroups;
     }
-    s.chain_block = s.narrow ? glm_narrow_block() : s.block;
+    s.chain_block = s.narrow ? glm_narrow_block(s.narrow_rw) : s.block;
     if (s.CPL >= 8 && s.V == 4 && G >= 8) {
         // wide rows on eight or more workgroups: the kernel with an exchange wavefront and a two-level exchange
         s.split = 1;
@@ -704,7 +726,7 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
         s.G = G & ~7;
         s.chain_block = glm_split_block();
     }
-    s.reduce_mode = ((int64_t)G * p <= 4096) ? kReduceRedundant : kReduceSliced;
+    s.reduce_mode = few_sums ? kReduceRedundant : kReduceSliced;
     const int64_t th_len = std::max<int64_t>((p + 63) & ~int64_t(63), (int64_t)s.V * s.L * s.CPL);
     s.lds_bytes = (size_t)(th_len + (int64_t)(s.block / 64) * p + s.block + 64) * sizeof(float);
     *out = s;
@@ -748,10 +770,11 @@ hipError_t glm_prepare(GlmLaunchShape* s)
         int cap = 0;
         e = glm_narrow_prepare(*s, s->p, &cap);
         if (e != hipSuccess) return e;
-        cap = std::min(cap, prop.multiProcessorCount) & ~7;
-        const int G = std::min(s->G, cap) & ~7;
+        const bool sliced = s->reduce_mode == kReduceSliced;
+        cap = std::min(cap, prop.multiProcessorCount) & (sliced ? ~7 : ~0);
+        const int G = std::min(s->G, cap) & (sliced ? ~7 : ~0);
         // fewer workgroups than planned hold fewer rows: only if the step still fits
-        if (G >= 8 && glm_narrow_rows_in_flight(s->V, s->CPL, s->L, G, s->n) == s->narrow_pf) {
+        if (G >= (sliced ? 8 : 1) && glm_narrow_rows_in_flight(s->V, s->CPL, s->L, s->narrow_rw, G, s->n) == s->narrow_pf) {
             s->max_G = std::min(s->max_G, cap);
             s->G = G;
         } else {

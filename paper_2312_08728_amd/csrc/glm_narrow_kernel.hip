@@ -1,12 +1,12 @@
 // Fused mini-batch gradient + update for rows of up to 1024 floats (least squares, logistic) when the rows a
-// workgroup takes per step fit its registers; persistent over all steps of up to four passes, on G workgroups
-// (G a multiple of 8, one per compute unit).
+// workgroup takes per step fit its registers; persistent over all steps of up to four passes, on G workgroups, one per
+// compute unit.
 //
 // A step of eq. (2.1) on such rows moves little data (a few KB per workgroup), so the chain of steps is bound by the
 // exchange of the gradient sums between the workgroups, and the kernel's job is to put nothing else on that path:
 //
 //   * A row is held by L cooperating lanes of a row wavefront (L a power of two, 64 / L rows side by side, PF rows
-//     one after the other per lane; lane l owns the columns V (l + L k) .. + V - 1, k < CPL).  Eight row wavefronts
+//     one after the other per lane; lane l owns the columns V (l + L k) .. + V - 1, k < CPL).  RW row wavefronts
 //     per workgroup.
 //   * Each row wavefront holds TWO groups of rows in registers and alternates between them: the group used in step
 //     s is refilled, as soon as it has been used, with the rows of step s + 2 (rows do not depend on theta).  Rows
@@ -15,7 +15,12 @@
 //     that the compiler's count of loads in flight is exact and a step waits only for its own rows.
 //   * The row wavefronts never touch global memory except for rows: their sums go to shared memory, and four
 //     exchange wavefronts (glm_exchange.h), one per SIMD, carry them to the other workgroups and bring the new theta
-//     back, two trips over the fabric per step.  Row wavefronts wait for theta on a flag in shared memory.
+//     back.  Row wavefronts wait for theta on a flag in shared memory.
+//
+// Two forms.  Eight row wavefronts, sums added up slice by slice in two trips over the fabric per step (G a multiple of 8): where G p
+// is large.  Twelve row wavefronts (the workgroup's sixteen fill the unit), one trip per step, any G, p <= 512: where every workgroup
+// can add up the few sums itself; they hold fewer floats of a row each (registers), but fewer workgroups are what is wanted there.
+// Odd rows in two trips take twelve as well.
 #include "glm_exchange.h"
 
 #include <algorithm>
@@ -27,18 +32,24 @@ namespace {
 // Registers: two groups of PF rows of CPL * V floats per lane.  Loads: a group is PF * (CPL + 2) of them (chunks,
 // response, next index), and the two groups' loads together must stay below the 63 that a wavefront's count of
 // loads in flight can hold.
-constexpr bool narrow_shape_ok(int v, int cpl, int pf)
+constexpr bool narrow_shape_ok(int v, int cpl, int pf, int rw)
 {
-    return v >= 2 && cpl <= 4 && pf <= 8 && v * cpl * pf <= 32 && pf * (cpl + 2) <= 24;
+    return (v >= 2 || rw > kRowWaves) && cpl <= 4 && pf <= 8 && v * cpl * pf <= (rw > kRowWaves ? 16 : 32) && pf * (cpl + 2) <= 24;
 }
 
 // Wavefronts 0 .. 3 are the exchange wavefronts (the hardware deals the wavefronts of a workgroup out to the four
-// SIMDs in turn, so each SIMD gets one), wavefronts 4 .. 11 the row wavefronts.
+// SIMDs in turn, so each SIMD gets one), the others the RW row wavefronts.
 constexpr int kXWaves = 4;
-constexpr int kNarrowBlock = 64 * (kXWaves + kRowWaves);
+constexpr int narrow_block(int rw) { return 64 * (kXWaves + rw); }
 
-template <int V, int CPL, int PF, bool OPT>
-__global__ void __launch_bounds__(kNarrowBlock) glm_narrow_kernel(GlmArgs a)
+// The k-th of two or four values.  (Arguments by value: a choice between elements of an array that the compiler has not yet taken apart
+// becomes an indexed load from scratch.)
+__device__ __forceinline__ float pick2(int k, float v0, float v1) { return k == 1 ? v1 : v0; }
+__device__ __forceinline__ float pick4(int k, float v0, float v1, float v2, float v3) { return (k & 2) != 0 ? pick2(k & 1, v2, v3) : pick2(k & 1, v0, v1); }
+
+// ONE: the redundant reduction, one trip over the fabric per step; else the sliced one, two trips.
+template <int V, int CPL, int PF, int RW, bool ONE, bool OPT>
+__global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
 {
     extern __shared__ __align__(16) float smem[];
     __shared__ int s_abort;                          // set by the exchange wavefront when a wait ran out
@@ -56,12 +67,12 @@ __global__ void __launch_bounds__(kNarrowBlock) glm_narrow_kernel(GlmArgs a)
     const int L = a.L;
     const int stride = max((p + 15) & ~15, V * L * CPL);          // of theta and of the sums in shared memory
     lds_f32* th = (lds_f32*)smem;                    // [2][stride]: theta, by version parity
-    lds_f32* sums = th + 2 * stride;                 // [kRowWaves][stride]: each row wavefront's gradient sums of a step
-    lds_f32* red = sums + kRowWaves * stride;        // scratch of the exchange wavefronts
+    lds_f32* sums = th + 2 * stride;                 // [RW][stride]: each row wavefront's gradient sums of a step
+    lds_f32* xstate = sums + RW * stride;            // scratch of the exchange wavefronts
     const int first = a.s_begin, last = a.s_end;
 
     // theta (version 0 in copy 0) and the sums; columns beyond p stay zero for good (rows are read at column 0 there)
-    for (int c = tid; c < (2 + kRowWaves) * stride; c += kNarrowBlock) th[c] = c < p ? a.theta[c] : 0.f;
+    for (int c = tid; c < (2 + RW) * stride; c += narrow_block(RW)) th[c] = c < p ? a.theta[c] : 0.f;
     if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_xconsumed = 0u; }
     if (tid < kXWaves) s_xarrived[tid] = 0u;
     __syncthreads();                                 // the only barrier: from here on the wavefronts meet through flags
@@ -73,8 +84,8 @@ __global__ void __launch_bounds__(kNarrowBlock) glm_narrow_kernel(GlmArgs a)
         const int lsub = lane & (L - 1);
         const int slot = lane >> a.logL;
         const int rpw = 64 >> a.logL;                // rows side by side in a wavefront
-        const int S_total = G * kRowWaves * rpw;     // row slots of the grid: row j of a mini-batch goes to slot j mod S_total
-        const int myslot = (g * kRowWaves + rw) * rpw + slot;
+        const int S_total = G * RW * rpw;    // row slots of the grid: row j of a mini-batch goes to slot j mod S_total
+        const int myslot = (g * RW + rw) * rpw + slot;
         int col[CPL];
 #pragma unroll
         for (int k = 0; k < CPL; ++k) col[k] = V * (lsub + L * k);
@@ -139,25 +150,56 @@ __global__ void __launch_bounds__(kNarrowBlock) glm_narrow_kernel(GlmArgs a)
             const unsigned want = (unsigned)(min(s, last) - first);
             lds_wait_ge(version_addr, want * kXWaves, abort_addr);   // (every exchange wavefront raises it once per version)
             const lds_f32* src = th + (want & 1u) * stride;
-            float thr[E], acc[E];
+            float thr[E], acc[E], dot[PF], r[PF];
 #pragma unroll
             for (int k = 0; k < CPL; ++k) {
 #pragma unroll
                 for (int v = 0; v < V; ++v) thr[k * V + v] = src[col[k] + v];
             }
 #pragma unroll
-            for (int e = 0; e < E; ++e) acc[e] = 0.f;
-#pragma unroll
             for (int q = 0; q < PF; ++q) {
-                float dot = 0.f;
+                dot[q] = S.x[q][0] * thr[0];
 #pragma unroll
-                for (int e = 0; e < E; ++e) dot = fmaf(S.x[q][e], thr[e], dot);
-                dot = group_sum_flat(dot, L);
-                const float r = ((S.ok >> q) & 1u) != 0u ? residual(a.model, dot, S.y[q]) : 0.f;
-#pragma unroll
-                for (int e = 0; e < E; ++e) acc[e] = fmaf(r, S.x[q][e], acc[e]);
+                for (int e = 1; e < E; ++e) dot[q] = fmaf(S.x[q][e], thr[e], dot[q]);
             }
-            if (L < 64) {                            // (no loads inside: the branch does not disturb their count)
+            // (no loads inside: the branches do not disturb their count)
+            if (CPL > 1 || L == 64) {
+#pragma unroll
+                for (int q = 0; q < PF; ++q) dot[q] = group_sum(dot[q], 64);
+            } else if (L == 32) {
+#pragma unroll
+                for (int q = 0; q < PF; ++q) dot[q] = group_sum(dot[q], 32);
+            } else {
+#pragma unroll
+                for (int q = 0; q < PF; ++q) dot[q] = row_group_sum(dot[q], L);
+            }
+            // Residuals: lane l of four works out those of the rows q = l mod 4 and hands them to the others (exp and a division cost
+            // more than the products of a row, and every lane of the group would make the same).
+            constexpr int Q = PF < 3 ? PF : 4;
+            auto residuals_from = [&](auto from) {
+                constexpr int q0 = decltype(from)::value;
+                const int mine = lane & (Q - 1);
+                const float u = Q == 1 ? dot[q0] : Q == 2 ? pick2(mine, dot[q0], dot[q0 + Q - 1]) : pick4(mine, dot[q0], dot[q0 + Q / 4], dot[q0 + Q / 2], dot[PF == 3 ? 2 : q0 + Q - 1]);
+                const float yq = Q == 1 ? S.y[q0] : Q == 2 ? pick2(mine, S.y[q0], S.y[q0 + Q - 1]) : pick4(mine, S.y[q0], S.y[q0 + Q / 4], S.y[q0 + Q / 2], S.y[PF == 3 ? 2 : q0 + Q - 1]);
+                const float res = ((S.ok >> (q0 + mine)) & 1u) != 0u ? residual(a.model, u, yq) : 0.f;
+                if constexpr (Q == 1) r[q0] = res;
+                if constexpr (Q >= 2) { r[q0] = dpp_mov<0x00>(res); r[q0 + 1] = dpp_mov<0x55>(res); }
+                if constexpr (Q == 4) r[q0 + 2] = dpp_mov<0xAA>(res);
+                if constexpr (Q == 4 && PF != 3) r[q0 + 3] = dpp_mov<0xFF>(res);
+            };
+            residuals_from(std::integral_constant<int, 0>{});
+            if constexpr (PF == 8) residuals_from(std::integral_constant<int, 4>{});
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[e] = r[0] * S.x[0][e];
+#pragma unroll
+            for (int q = 1; q < PF; ++q) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = fmaf(r[q], S.x[q][e], acc[e]);
+            }
+            if (CPL == 1 && L == 32) {
+#pragma unroll
+                for (int e = 0; e < E; ++e) acc[e] = swap32_sum(acc[e]);
+            } else if (CPL == 1 && L < 32) {
 #pragma unroll
                 for (int e = 0; e < E; ++e) acc[e] = slot_sum_flat(acc[e], L);
             }                                        // lanes < L: the wavefront's sums
@@ -173,7 +215,7 @@ __global__ void __launch_bounds__(kNarrowBlock) glm_narrow_kernel(GlmArgs a)
                 // (shared memory serves a wavefront's requests in order: the count is raised after the sums are in place;
                 // a release here would wait for the rows in flight as well)
                 asm volatile("" ::: "memory");
-                if (lane == 0) __hip_atomic_fetch_add(&s_published, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (lane == 0) lds_add_one(lds_address((lds_u32*)&s_published));
             }
             request(S);
         };
@@ -193,80 +235,92 @@ __global__ void __launch_bounds__(kNarrowBlock) glm_narrow_kernel(GlmArgs a)
     }
 
     // ------------------------------------------------------------------------------------ exchange wavefronts
-    // (p <= 1024: two loads per lane and trip collect theta; eight cover the slice for up to 256 workgroups)
-    const ExchangeLds x{th, stride, red, sums, kRowWaves, stride, (unsigned)kRowWaves,
+    __builtin_amdgcn_s_setprio(3);                   // (they share their SIMDs with row wavefronts that are requesting rows)
+    const ExchangeLds x{th, stride, xstate, xstate + kExchangeState * kXWaves, sums, stride, (unsigned)RW,
                         (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort,
                         (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
-    exchange_wavefront<OPT, kXWaves, 8, 2>(a, x, lane, wave);
+    if constexpr (ONE) exchange_one_trip<OPT, kXWaves, RW>(a, x, lane, wave);
+    else exchange_wavefront<OPT, kXWaves, RW, 8, 2>(a, x, lane, wave);   // (p <= 1024: two loads per lane collect theta; eight cover the slice for up to 256 workgroups)
 }
 
 using KernelFn = void (*)(GlmArgs);
 
-template <bool OPT, int V, int CPL, int PF>
+template <bool OPT, int RW, bool ONE, int V, int CPL, int PF>
 KernelFn pick()
 {
-    if constexpr (!narrow_shape_ok(V, CPL, PF)) return nullptr;
-    else return glm_narrow_kernel<V, CPL, PF, OPT>;
+    if constexpr (!narrow_shape_ok(V, CPL, PF, RW) || (!ONE && (RW == kRowWaves) == (V == 1))) return nullptr;
+    else return glm_narrow_kernel<V, CPL, PF, RW, ONE, OPT>;
 }
 
-template <bool OPT, int V, int CPL>
+template <bool OPT, int RW, bool ONE, int V, int CPL>
 KernelFn pick_pf(int pf)
 {
     switch (pf) {
-    case 1: return pick<OPT, V, CPL, 1>();
-    case 2: return pick<OPT, V, CPL, 2>();
-    case 4: return pick<OPT, V, CPL, 4>();
-    case 8: return pick<OPT, V, CPL, 8>();
+    case 1: return pick<OPT, RW, ONE, V, CPL, 1>();
+    case 2: return pick<OPT, RW, ONE, V, CPL, 2>();
+    case 3: return pick<OPT, RW, ONE, V, CPL, 3>();
+    case 4: return pick<OPT, RW, ONE, V, CPL, 4>();
+    case 8: return pick<OPT, RW, ONE, V, CPL, 8>();
     }
     return nullptr;
 }
 
-template <bool OPT, int V>
+template <bool OPT, int RW, bool ONE, int V>
 KernelFn pick_cpl(int cpl, int pf)
 {
     switch (cpl) {
-    case 1: return pick_pf<OPT, V, 1>(pf);
-    case 2: return pick_pf<OPT, V, 2>(pf);
-    case 4: return pick_pf<OPT, V, 4>(pf);
+    case 1: return pick_pf<OPT, RW, ONE, V, 1>(pf);
+    case 2: return pick_pf<OPT, RW, ONE, V, 2>(pf);
+    case 4: return pick_pf<OPT, RW, ONE, V, 4>(pf);
     }
     return nullptr;
 }
 
-KernelFn narrow_kernel(int v, int cpl, int pf, bool opt)
+template <bool OPT, int RW, bool ONE>
+KernelFn pick_v(int v, int cpl, int pf)
 {
-    if (v == 4) return opt ? pick_cpl<true, 4>(cpl, pf) : pick_cpl<false, 4>(cpl, pf);
-    if (v == 2) return opt ? pick_cpl<true, 2>(cpl, pf) : pick_cpl<false, 2>(cpl, pf);
-    return nullptr;
+    if (v == 4) return pick_cpl<OPT, RW, ONE, 4>(cpl, pf);
+    if (v == 2) return pick_cpl<OPT, RW, ONE, 2>(cpl, pf);
+    return pick_cpl<OPT, RW, ONE, 1>(cpl, pf);
 }
+
+template <bool OPT>
+KernelFn narrow_kernel_opt(const GlmLaunchShape& s)
+{
+    if (s.narrow_rw == kRowWaves) return s.reduce_mode == kReduceSliced ? pick_v<OPT, kRowWaves, false>(s.V, s.CPL, s.narrow_pf) : nullptr;
+    return s.reduce_mode == kReduceSliced ? pick_v<OPT, kNarrowMoreRows, false>(s.V, s.CPL, s.narrow_pf)
+                                          : pick_v<OPT, kNarrowMoreRows, true>(s.V, s.CPL, s.narrow_pf);
+}
+
+KernelFn narrow_kernel(const GlmLaunchShape& s) { return s.with_optimizer ? narrow_kernel_opt<true>(s) : narrow_kernel_opt<false>(s); }
 
 size_t narrow_lds_bytes(const GlmLaunchShape& s, int p)
 {
     const int stride = std::max((p + 15) & ~15, s.V * s.L * s.CPL);
-    return (size_t)((2 + kRowWaves) * stride + kExchangeScratch * kXWaves + 16) * sizeof(float);
+    return (size_t)((2 + s.narrow_rw) * stride + (kExchangeState + kExchangeRed) * kXWaves + 16) * sizeof(float);
 }
 
 }  // namespace
 
-int glm_narrow_block() { return kNarrowBlock; }
+int glm_narrow_block(int rw) { return narrow_block(rw); }
 
-int glm_narrow_rows_in_flight(int v, int cpl, int L, int G, int64_t n)
+int glm_narrow_rows_in_flight(int v, int cpl, int L, int rw, int G, int64_t n)
 {
-    const int64_t slots = (int64_t)G * kRowWaves * (64 / L);
+    const int64_t slots = (int64_t)G * rw * (64 / L);
     const int64_t need = (n + slots - 1) / slots;
-    int pf = 1;
-    while (pf < need && pf < 16) pf *= 2;
-    return narrow_shape_ok(v, cpl, pf) ? pf : 0;
+    const int pf = need <= 4 ? (int)need : need <= 8 ? 8 : 16;
+    return narrow_shape_ok(v, cpl, pf, rw) ? pf : 0;
 }
 
 hipError_t glm_narrow_prepare(const GlmLaunchShape& s, int p, int* max_groups)
 {
-    KernelFn fn = narrow_kernel(s.V, s.CPL, s.narrow_pf, s.with_optimizer != 0);
+    KernelFn fn = narrow_kernel(s);
     if (!fn) return hipErrorInvalidValue;
     const size_t lds = narrow_lds_bytes(s, p);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), kNarrowBlock, lds);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), narrow_block(s.narrow_rw), lds);
     if (e != hipSuccess) return e;
     int dev = 0;
     hipDeviceProp_t prop;
@@ -278,13 +332,18 @@ hipError_t glm_narrow_prepare(const GlmLaunchShape& s, int p, int* max_groups)
 
 hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream)
 {
-    KernelFn fn = narrow_kernel(s.V, s.CPL, s.narrow_pf, s.with_optimizer != 0);
-    const int64_t slots = (int64_t)s.G * kRowWaves * (64 / s.L);
-    // what the kernel assumes: whole vector chunks, every row of a step in a register slot, words in pairs
-    if (!fn || s.G < 8 || s.G % 8 != 0 || args.s_begin >= args.s_end || args.p % s.V != 0 || args.p % 2 != 0 ||
+    KernelFn fn = narrow_kernel(s);
+    const int64_t slots = (int64_t)s.G * s.narrow_rw * (64 / s.L);
+    const bool one_trip = s.reduce_mode == kReduceRedundant;
+    // what the kernel assumes: whole vector chunks, every row of a step in a register slot; two trips: slices of whole groups of
+    // eight workgroups; one trip: columns that the exchange wavefronts hold as pairs
+    if (!fn || args.s_begin >= args.s_end || args.p % s.V != 0 || args.reduce_mode != s.reduce_mode ||
         args.p > s.V * s.L * s.CPL || args.L != s.L || (1 << args.logL) != s.L || (int64_t)args.n > slots * s.narrow_pf)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fn, dim3(s.G), dim3(kNarrowBlock), narrow_lds_bytes(s, args.p), stream, args);
+    if (one_trip ? s.narrow_rw == kRowWaves || args.p > kNarrowOneTripMaxP || s.G < 1
+                 : s.G < 8 || s.G % 8 != 0 || (s.narrow_rw != kRowWaves && s.V != 1))
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), narrow_lds_bytes(s, args.p), stream, args);
     return hipGetLastError();
 }
 

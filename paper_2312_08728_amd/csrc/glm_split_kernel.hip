@@ -77,8 +77,8 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     // instructions and are counted apart from the row loads)
     volatile lds_f32* pd = (volatile lds_f32*)(smem + 2 * P_PAD);   // [2][kRowWaves][GR]: partial dot products of a group, by group parity
     volatile lds_u32* pd_seq = (volatile lds_u32*)(smem + 2 * P_PAD + 2 * kRowWaves * GR);   // [2][kRowWaves]: their sequence numbers
-    lds_f32* red = (lds_f32*)(smem + 2 * P_PAD + 2 * kRowWaves * GR + 2 * kRowWaves);   // [64][2] scratch of the exchange wavefront
-    lds_f32* sums = red + 2 * 64;                    // [P_PAD]: the workgroup's gradient sums of a step, on their way out
+    lds_f32* xstate = (lds_f32*)(smem + 2 * P_PAD + 2 * kRowWaves * GR + 2 * kRowWaves);   // scratch of the exchange wavefront
+    lds_f32* sums = xstate + kExchangeState;                  // [P_PAD]: the workgroup's gradient sums of a step, on their way out
     const int first = a.s_begin, last = a.s_end;
 
     // both copies of theta: columns beyond p stay zero for good (rows are read at column 0 there)
@@ -244,9 +244,9 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     }
 
     // ------------------------------------------------------------------------------------ exchange wavefront
-    const ExchangeLds x{th, P_PAD, red, sums, 1, P_PAD, (unsigned)kRowWaves,
+    const ExchangeLds x{th, P_PAD, xstate, nullptr, sums, P_PAD, (unsigned)kRowWaves,
                         (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, nullptr, nullptr};
-    exchange_wavefront<OPT, 1, 32, 32>(a, x, lane, 0);
+    exchange_wavefront<OPT, 1, 1, 32, 32>(a, x, lane, 0);
 }
 
 using KernelFn = void (*)(GlmArgs);
@@ -261,7 +261,7 @@ KernelFn split_kernel(int ch, bool opt)
 
 size_t glm_split_lds_bytes(int ch)
 {
-    return (size_t)(3 * kRowWaves * 256 * ch + 2 * kRowWaves * kGroupRows + 2 * kRowWaves + 2 * 64 + 16) * sizeof(float);
+    return (size_t)(3 * kRowWaves * 256 * ch + 2 * kRowWaves * kGroupRows + 2 * kRowWaves + kExchangeState + 16) * sizeof(float);
 }
 
 int glm_split_block() { return kSplitBlock; }

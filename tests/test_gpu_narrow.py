@@ -112,3 +112,46 @@ def test_more_passes_than_one_launch_holds_and_a_rate_per_update():
     ctx.close()
     assert st.threads_per_group == NARROW_THREADS and st.steps == steps and st.chain_launches == 4
     assert rel_l2(got, ref.theta) <= TOL
+
+
+# (model, p, n, G, N0): the form with one trip over the fabric per step (G p <= 4096: twelve row wavefronts, 1024 threads), and odd rows
+# in two trips.  Columns travel as pairs, in chunks of 64 pairs split over four exchange wavefronts; 64 / (pairs, 8 to 64) workgroups
+# side by side.
+ONE_TRIP = [
+    (wl.LOGISTIC, 1, 40, 1, 500),        # one column, one workgroup: no exchange
+    (wl.LOGISTIC, 2, 300, 3, 1_000),     # one pair; fewer workgroups than lane groups (8)
+    (wl.LINEAR, 15, 500, 7, 1_700),      # eight pairs, the last one half; 7 of 8 lane groups
+    (wl.LOGISTIC, 16, 900, 9, 2_000),    # 9 workgroups in groups of 8: the second load repeats seven
+    (wl.LINEAR, 17, 2000, 33, 5_000),    # 16 lanes per pair row; odd G
+    (wl.LOGISTIC, 64, 700, 11, 2_100),   # 32 pairs, two lane groups
+    (wl.LINEAR, 65, 1200, 63, 3_000),    # 33 pairs in a chunk of 64; 16 loads per lane, in two rounds
+    (wl.LOGISTIC, 123, 777, 32, 3_000),  # V 1, CPL 2, PF 3
+    (wl.LOGISTIC, 128, 1024, 32, 3_000), # a full chunk
+    (wl.LINEAR, 129, 600, 31, 2_000),    # two chunks, the second of one half pair: two wavefronts each
+    (wl.LOGISTIC, 255, 300, 16, 1_000),  # V 1, CPL 4
+    (wl.LINEAR, 256, 350, 16, 1_000),    # two full chunks
+    (wl.LOGISTIC, 258, 200, 15, 700),    # three chunks: one wavefront each, the last with nothing
+    (wl.LOGISTIC, 512, 90, 8, 400),      # the widest rows
+    (wl.LOGISTIC, 201, 1500, 64, 4_000), # odd rows in two trips
+    (wl.LINEAR, 33, 4000, 128, 9_000),   # odd rows in two trips, two rows side by side in a wavefront
+]
+
+
+@pytest.mark.parametrize("optimizer", [0, 1, 3])
+@pytest.mark.parametrize("model,p,n,G,N0", ONE_TRIP)
+def test_one_trip_and_odd_rows_against_the_oracle(model, p, n, G, N0, optimizer):
+    """Three launches of theta, state and tags carried over (two buffers, the second run with five passes as two launches)."""
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    w = _case(model, 2 * N0 - 77, p, N0, n, T=5, R=1, alpha=0.01 if optimizer == 3 else 0.05 if model == wl.LOGISTIC else 0.2 / (p + 10))
+    X, y = wl.dataset(w)
+    ref = O.BMGD(w.model, w.p, w.n, w.alpha, w.T)
+    if optimizer:
+        ref.set_optimizer(optimizer)
+    for k in range(2):
+        ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
+    got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
+    assert st.threads_per_group == 1024 and st.n_workgroups == G, (st.threads_per_group, st.n_workgroups)
+    assert rel_l2(got, ref.theta) <= TOL
+    again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
+    assert np.array_equal(got, again)
