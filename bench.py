@@ -169,6 +169,11 @@ def _roofline(w, delta, traffic=None):
         achieved = bytes_per_launch / dominant_s / 1e9
         steps_per_launch = delta["minibatch_steps"] / max(delta["chain_launches"], 1)
         q = w.p + 1
+        if delta["prep_launches"] == 0:
+            # few, small mini-batches: one kernel forms the matrices and applies them
+            return {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic, "kernel": "gram_fused_kernel",
+                    "avg_launch_ms": round(dominant_s * 1e3, 4), "algorithmic_bytes_per_launch": int(bytes_per_launch)}
         return {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic,
                 "kernel": "gram_chain_kernel" if per_launch_s >= prep_s

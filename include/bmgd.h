@@ -72,7 +72,9 @@ typedef struct bmgd_ctx bmgd_ctx;
 /* In BMGD_CHAIN_GRAM mode the sequential chain runs on a stream the library creates (default priority) while
  * everything that reads the caller's buffer stays on compute_stream, so that the pre-pass over buffer k + 1
  * overlaps the chain of buffer k.  The blocking calls listed above wait for that stream too; a caller that
- * synchronises compute_stream by itself has waited for the reads of its buffers, not for the updates. */
+ * synchronises compute_stream by itself has waited for the reads of its buffers, not for the updates.
+ * (BMGD_CHAIN_AUTO with few features and few, small mini-batches per buffer makes a whole launch one kernel on
+ * compute_stream; prep_ms and prep_launches then stay 0.) */
 
 /* status codes */
 enum {

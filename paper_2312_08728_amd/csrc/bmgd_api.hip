@@ -48,6 +48,8 @@ struct Slot {
 
 struct RunRecord {                                 // events of one buffer, for the overlap statistics
     hipEvent_t copy_start = nullptr, copy_end = nullptr, start = nullptr, end = nullptr;
+    hipEvent_t start_done = nullptr;               // not NULL: `start` and this one ride on the run's first kernel (start and end of it)
+    bool owns_start = true;                        // false: those of the run's only launch, which has an entry in open_chain
     bool has_copy = false;
     bool owns_end = true;                          // false: `end` is the stop event of the run's last chain launch
     int n_chain = 0, n_prep = 0;                   // launches of this run with an entry in open_chain / open_prep
@@ -154,6 +156,9 @@ struct bmgd_ctx {
     char* mail = nullptr;                          // pinned: kMailHead bytes of flags and sums, two areas of mail_area bytes
     size_t mail_area = 0;
     hipEvent_t mail_done[2] = {nullptr, nullptr};  // the export that filled an area (large estimates only)
+    bool fused = false;                            // eq. (3.1) form, a launch in one kernel (gram_fused_kernel.hip) on the caller's stream
+    hipEvent_t run_start[2] = {nullptr, nullptr};  // events that the next run's first kernel is to carry ...
+    bool run_marked = false;                       // ... but the first of them was recorded as a marker
     bool poisoned = false;                         // a run failed or was abandoned: theta is not valid until it is set again
     std::string err;
 };
@@ -234,13 +239,22 @@ bool wants_softmax_chain(const bmgd_config& c)
     return c.model == BMGD_SOFTMAX && c.chain == BMGD_CHAIN_AUTO && softmax_chain_eligible(c.p, c.batch_n, c.n_classes, c.optimizer != BMGD_OPT_SGD);
 }
 
+// The moment form left to the library, with few features and few, small mini-batches: partitions, matrices and chain in one kernel.
+// It takes precedence over the products, whose halved chain saves less there than their kernels cost.
+bool wants_fused(const bmgd_config& c)
+{
+    // (fixed partitions keep to the kernels that cached matrices are made with: the same bits with and without a cache)
+    return c.chain == BMGD_CHAIN_AUTO && gram_eligible(c.model, c.p, c.batch_n) && c.reshuffle == BMGD_RESHUFFLE_PER_PASS &&
+           gram_fused_eligible(c.p, c.buffer_n, c.batch_n);
+}
+
 // BMGD_CHAIN_PRODUCT, asked for or picked: BMGD_CHAIN_AUTO takes it for plain steps of least squares in the moment form
 // when a launch has enough steps for the halved chain to matter (measured at 300 steps per launch: 0.151 against 0.175 ms
 // per buffer) and nothing is cached (with cached matrices the caller chooses between the two forms).
 bool wants_products(const bmgd_config& c)
 {
     if (c.chain == BMGD_CHAIN_PRODUCT) return true;
-    if (c.chain != BMGD_CHAIN_AUTO || !gram_eligible(c.model, c.p, c.batch_n) || c.optimizer != BMGD_OPT_SGD || c.cache_moments)
+    if (c.chain != BMGD_CHAIN_AUTO || !gram_eligible(c.model, c.p, c.batch_n) || c.optimizer != BMGD_OPT_SGD || c.cache_moments || wants_fused(c))
         return false;
     const int64_t M = (c.buffer_n + c.batch_n - 1) / c.batch_n;
     const int64_t steps = (int64_t)std::min<int64_t>(kMaxPassesPerLaunch, c.passes) * M;
@@ -285,8 +299,8 @@ Layout make_layout(const bmgd_config& c, bool one_kernel)
         const size_t set = align_up((size_t)kMaxPassesPerLaunch * (size_t)((c.buffer_n + c.batch_n - 1) / c.batch_n) *
                                     (wants_products(c) ? gram_dense_bytes_per_batch(c.p) : gram_bytes_per_batch(c.p)));
         l.gram[0] = off; off += set;
-        l.gram[1] = off; off += set;
-        l.gram_perm = off; off += align_up((size_t)kMaxPassesPerLaunch * c.buffer_n * 4);   // second set of partitions
+        l.gram[1] = off; off += wants_fused(c) ? 0 : set;
+        l.gram_perm = off; off += wants_fused(c) ? 0 : align_up((size_t)kMaxPassesPerLaunch * c.buffer_n * 4);   // second set of partitions
     }
     // BMGD_CHAIN_PRODUCT: two sets of scratch for the products of a launch's steps
     l.prod[0] = l.prod[1] = off;
@@ -386,8 +400,13 @@ void settle_records(bmgd_ctx* ctx, size_t count)
             const double from = std::max<double>(c_start, ctx->busy_until);
             if (c_end > from) ctx->wait_ms += c_end - from;
         }
-        if (hipEventElapsedTime(&t_start, ctx->base, r.start) == hipSuccess &&
-            hipEventElapsedTime(&t_end, ctx->base, r.end) == hipSuccess) {
+        // (between events of different dispatches the runtime measures from end to end)
+        float first = 0.f;
+        const bool started = r.start_done ? hipEventElapsedTime(&t_start, ctx->base, r.start_done) == hipSuccess &&
+                                                hipEventElapsedTime(&first, r.start, r.start_done) == hipSuccess
+                                          : hipEventElapsedTime(&t_start, ctx->base, r.start) == hipSuccess;
+        t_start -= first;
+        if (started && hipEventElapsedTime(&t_end, ctx->base, r.end) == hipSuccess) {
             // runs may overlap (the pre-pass of one with the chain of the one before): count the union
             const double from = std::max<double>(t_start, ctx->busy_until);
             if (t_end > from) ctx->compute_ms += t_end - from;
@@ -415,7 +434,7 @@ void settle_records(bmgd_ctx* ctx, size_t count)
     for (size_t i = 0; i < count; ++i) {
         RunRecord& r = ctx->open_records[i];
         give_event(ctx, r.copy_start); give_event(ctx, r.copy_end);
-        give_event(ctx, r.start);
+        if (r.owns_start) { give_event(ctx, r.start); give_event(ctx, r.start_done); }
         if (r.owns_end) give_event(ctx, r.end);
     }
     ctx->open_records.erase(ctx->open_records.begin(), ctx->open_records.begin() + (ptrdiff_t)count);
@@ -530,6 +549,25 @@ float rate_of(const bmgd_ctx* ctx, int64_t ahead)
     return ctx->lr_tab_host[(size_t)u];
 }
 
+// A run begins on `stream` with something other than a kernel that can carry its events.
+int begin_run(bmgd_ctx* ctx, hipStream_t stream)
+{
+    if (!ctx->run_start[0]) return BMGD_OK;
+    HIP_TRY(ctx, hipEventRecord(ctx->run_start[0], stream));
+    ctx->run_start[0] = ctx->run_start[1] = nullptr;
+    ctx->run_marked = true;
+    return BMGD_OK;
+}
+
+// The partitions of the coming passes in the moment form; a run's first kernel carries its start events (no marker between this buffer's
+// kernels and the last one's: 1.72 -> 1.54 ms per ten buffers of 100,000 rows x 3 passes at p = 100).
+hipError_t start_perm(bmgd_ctx* ctx, int32_t* out, int64_t rows, int nperm, const PermKeys& keys, hipStream_t stream)
+{
+    const hipError_t e = launch_perm(out, rows, nperm, keys, stream, ctx->subset, ctx->subset_limit, ctx->sync + 2, ctx->run_start[0], ctx->run_start[1]);
+    ctx->run_start[0] = ctx->run_start[1] = nullptr;
+    return e;
+}
+
 // The steps of a launch in the moment form, on the library's chain stream: the chain of eq. (3.1) step by step, or
 // (BMGD_CHAIN_PRODUCT) the steps multiplied together and applied once.
 hipError_t launch_steps(bmgd_ctx* ctx, const float* set, int64_t rows, int64_t n, int np, int perm_stride, hipEvent_t ev0,
@@ -575,8 +613,8 @@ hipError_t launch_steps(bmgd_ctx* ctx, const float* set, int64_t rows, int64_t n
 }
 
 // Enqueue passes t = first + 1 .. first + count over (x, y, rows) on `stream`, at most kMaxPassesPerLaunch per launch.
-// *end_event receives the stop event of the last kernel if that kernel carries one (and then runs on the
-// library's chain stream), else NULL: then the passes end with the last work enqueued on `stream`.
+// *end_event receives the stop event of the last kernel if that kernel carries one, else NULL: then the passes end with the last
+// work enqueued on `stream`.
 // *chunk_end (may be NULL) receives an event that completes when the last of these passes has: it stays valid until
 // the run's records are settled.
 int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hipStream_t stream, int first, int count,
@@ -602,7 +640,26 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
         for (int i = 0; i < nperm; ++i) perm_round_keys(c.seed, b, fixed ? 0u : (uint32_t)(t0 + i + 1), keys.key[i]);
         hipEvent_t ev0 = take_event(ctx), ev1 = take_event(ctx);
         if (!ev0 || !ev1) return fail(ctx, BMGD_EHIP, "could not create events");
+        if (ctx->fused) {
+            ctx->run_start[0] = ctx->run_start[1] = nullptr;      // (the launch's own events serve)
+            // theta goes from launch to launch in stream order; a caller that changes streams between runs is not made to see to that
+            if (ctx->used_compute && ctx->last_compute != stream && !ctx->open_chain.empty())
+                HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->open_chain.back().second, 0));
+            HIP_TRY(ctx, gram_launch_fused(static_cast<const float*>(x), static_cast<const float*>(y), keys, ctx->subset, ctx->subset_limit,
+                                           ctx->sync + 2, ctx->gram[0], ctx->theta, ctx->sync + 12, (int)rows, (int)c.p, (int)n, np, (float)c.lr, lr_len ? ctx->lr_tab_dev : nullptr,
+                                           (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0)), lr_len, opt_args(ctx, 0), stream, ev0, ev1));
+            ctx->lr_pos += (int64_t)np * M;
+            ctx->opt_k += (int64_t)np * M;
+            ctx->open_chain.emplace_back(ev0, ev1);
+            ctx->last_compute = stream;
+            ctx->used_compute = true;
+            *end_event = ev1;
+            if (chunk_end) *chunk_end = ev1;
+            continue;
+        }
         if (ctx->chain == BMGD_CHAIN_GRAM && c.cache_moments && !ctx->subset) {
+            const int brc = begin_run(ctx, stream);
+            if (brc != BMGD_OK) return brc;
             // Fixed partitions: the moment matrices of buffer index b are the same in every iteration (Section 3.1.1),
             // so they are formed once and every later run over that buffer is the chain alone.
             bmgd_ctx::CachedMoments& ce = ctx->mcache[b];
@@ -643,7 +700,7 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             ctx->open_prep.emplace_back(pv0, pv1);
             // set i is free once the chain that read it last has finished
             if (ctx->chain_pending[i]) HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->chain_done[i], 0));
-            HIP_TRY(ctx, launch_perm(ctx->gram_perm[i], rows, nperm, keys, stream, ctx->subset, ctx->subset_limit, ctx->sync + 2));
+            HIP_TRY(ctx, start_perm(ctx, ctx->gram_perm[i], rows, nperm, keys, stream));
             // BMGD_CHAIN_PRODUCT (without cached matrices): the steps are multiplied in pairs right behind the moments
             // kernel, on the same stream (both fill the device; the chain, which keeps to one unit, overlaps the next
             // buffer's two), and the chain runs over the pairs.  Set i of the pairs is guarded like set i of the matrices.
@@ -675,6 +732,9 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             if (chunk_end) *chunk_end = ev1;
             continue;
         }
+        // (a marker in front costs less here than the events on the partition's dispatch: softmax_small 771 against 798 us)
+        const int brc = begin_run(ctx, stream);
+        if (brc != BMGD_OK) return brc;
         if (!fixed || t0 == 0)
             HIP_TRY(ctx, launch_perm(ctx->perm, rows, nperm, keys, stream, ctx->subset, ctx->subset_limit, ctx->sync + 2));
         if (c.model == BMGD_SOFTMAX) {
@@ -799,7 +859,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
         a.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
         a.lr_len = lr_len;
         a.opt = opt_args(ctx, 0);
-        HIP_TRY(ctx, hipEventRecord(ev0, stream));
         if (ctx->chain == BMGD_CHAIN_PERSISTENT) {
             const int64_t nsteps = (int64_t)np * M;
             if ((uint64_t)ctx->tag_epoch + (uint64_t)nsteps + 1 >= 0xFFFFFFFFull) {
@@ -811,8 +870,10 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             a.s_begin = 0;
             a.s_end = (int)nsteps;
             ctx->tag_epoch += (uint32_t)nsteps;
-            HIP_TRY(ctx, glm_launch_chain(ctx->shape, a, stream));
+            HIP_TRY(ctx, glm_launch_chain(ctx->shape, a, stream, ev0, ev1));   // (the dispatch carries the events: no markers between kernels)
+            *end_event = ev1;
         } else {
+            HIP_TRY(ctx, hipEventRecord(ev0, stream));
             for (int64_t s = 0; s < (int64_t)np * M; ++s) {
                 a.single_step = (int)s;
                 a.alpha = rate_of(ctx, s);               // this mode passes the rate per launch
@@ -823,7 +884,7 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                 HIP_TRY(ctx, glm_launch_step(ctx->shape, a, nb, stream));
             }
         }
-        HIP_TRY(ctx, hipEventRecord(ev1, stream));
+        if (ctx->chain != BMGD_CHAIN_PERSISTENT) HIP_TRY(ctx, hipEventRecord(ev1, stream));
         ctx->open_chain.emplace_back(ev0, ev1);
         if (chunk_end) *chunk_end = ev1;
         ctx->lr_pos += (int64_t)np * M;
@@ -858,11 +919,37 @@ int64_t rows_of_run(bmgd_ctx* ctx, int64_t buffer_rows)
 // counts as not valid (the kernels already enqueued have updated it for part of the run) until it is set again.
 int abandon_run(bmgd_ctx* ctx, RunRecord& rec, int rc)
 {
-    give_event(ctx, rec.start);
+    give_event(ctx, rec.start); give_event(ctx, rec.start_done);
     if (rec.owns_end) give_event(ctx, rec.end);
-    rec.start = rec.end = nullptr;
+    rec.start = rec.start_done = rec.end = nullptr;
+    ctx->run_start[0] = ctx->run_start[1] = nullptr;
     ctx->poisoned = true;
     return rc;
+}
+
+// The events of a run that is about to be enqueued: its first kernel is to carry `start` and `start_done`.
+bool take_run_events(bmgd_ctx* ctx, RunRecord& rec)
+{
+    rec.start = take_event(ctx); rec.start_done = take_event(ctx); rec.end = take_event(ctx);
+    ctx->run_start[0] = rec.start; ctx->run_start[1] = rec.start_done;
+    ctx->run_marked = false;
+    return rec.start && rec.start_done && rec.end;
+}
+
+// Everything of a run has been enqueued: `last` is the stop event of its last kernel (or NULL), its launches are those in open_chain
+// from chain0 on.
+int end_run(bmgd_ctx* ctx, RunRecord& rec, hipStream_t s, hipEvent_t last, size_t chain0)
+{
+    if (last) { give_event(ctx, rec.end); rec.end = last; rec.owns_end = false; }
+    else HIP_TRY(ctx, hipEventRecord(rec.end, s));
+    if (ctx->run_marked) { give_event(ctx, rec.start_done); rec.start_done = nullptr; }
+    if (ctx->fused) {
+        give_event(ctx, rec.start); give_event(ctx, rec.start_done);
+        rec.start = ctx->open_chain[chain0].first;
+        rec.start_done = ctx->open_chain[chain0].second;
+        rec.owns_start = false;
+    }
+    return BMGD_OK;
 }
 
 int refuse_if_poisoned(bmgd_ctx* ctx)
@@ -1020,6 +1107,7 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     ctx->prod[0] = reinterpret_cast<float*>(base + ctx->lay.prod[0]);
     ctx->prod[1] = reinterpret_cast<float*>(base + ctx->lay.prod[1]);
     ctx->products = wants_products(*cfg);
+    ctx->fused = wants_fused(ctx->cfg);
     if (ctx->products) CREATE_TRY(gram_products_prepare());
     ctx->gram_cache = base + ctx->lay.gram_cache;
     ctx->prod_cache = base + ctx->lay.prod_cache;
@@ -1063,7 +1151,7 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
         ctx->shape.with_optimizer = cfg->optimizer != BMGD_OPT_SGD;
         CREATE_TRY(glm_prepare(&ctx->shape));
         ctx->chain = resolve_chain(ctx->cfg);
-        if (ctx->chain == BMGD_CHAIN_GRAM) {
+        if (ctx->chain == BMGD_CHAIN_GRAM && !ctx->fused) {
             CREATE_TRY(hipStreamCreateWithFlags(&ctx->chain_stream, hipStreamNonBlocking));   // default priority
         }
     }
@@ -1134,10 +1222,8 @@ BMGD_API int bmgd_run_buffer(bmgd_ctx* ctx, void* compute_stream)
     const int64_t run_rows = rows_of_run(ctx, slot.rows);
     if (run_rows == 0) return BMGD_EINVAL;
     RunRecord rec = ctx->pending_copy;
-    rec.start = take_event(ctx); rec.end = take_event(ctx);
-    if (!rec.start || !rec.end) return fail(ctx, BMGD_EHIP, "could not create events");
+    if (!take_run_events(ctx, rec)) return fail(ctx, BMGD_EHIP, "could not create events");
     HIP_TRY(ctx, hipStreamWaitEvent(s, slot.copy_done, 0));       // never read a slot that is still filling
-    HIP_TRY(ctx, hipEventRecord(rec.start, s));
     hipEvent_t last = nullptr;
     const size_t chain0 = ctx->open_chain.size(), prep0 = ctx->open_prep.size();
     const int rc = enqueue_compute(ctx, slot.x, slot.y, run_rows, s, &last);
@@ -1145,8 +1231,7 @@ BMGD_API int bmgd_run_buffer(bmgd_ctx* ctx, void* compute_stream)
     ctx->last_compute = s;
     ctx->used_compute = true;
     if (rc != BMGD_OK) return abandon_run(ctx, rec, rc);
-    if (last) { give_event(ctx, rec.end); rec.end = last; rec.owns_end = false; }
-    else HIP_TRY(ctx, hipEventRecord(rec.end, s));
+    if (const int erc = end_run(ctx, rec, s, last, chain0)) return erc;
     HIP_TRY(ctx, hipEventRecord(slot.compute_done, s));           // every kernel that reads the slot runs on s
     slot.was_read = true;
     rec.n_chain = (int)(ctx->open_chain.size() - chain0);
@@ -1175,10 +1260,8 @@ static int run_adaptive(bmgd_ctx* ctx, hipStream_t s, hipStream_t cs, const void
     if (run_rows == 0) return BMGD_EINVAL;
     RunRecord rec = ctx->pending_copy;
     ctx->pending_copy = RunRecord();
-    rec.start = take_event(ctx); rec.end = take_event(ctx);
-    if (!rec.start || !rec.end) return fail(ctx, BMGD_EHIP, "could not create events");
+    if (!take_run_events(ctx, rec)) return fail(ctx, BMGD_EHIP, "could not create events");
     HIP_TRY(ctx, hipStreamWaitEvent(s, slot.copy_done, 0));
-    HIP_TRY(ctx, hipEventRecord(rec.start, s));
     const size_t chain0 = ctx->open_chain.size(), prep0 = ctx->open_prep.size();
     ctx->last_compute = s;
     ctx->used_compute = true;
@@ -1239,7 +1322,7 @@ static int run_adaptive(bmgd_ctx* ctx, hipStream_t s, hipStream_t cs, const void
                 ctx->pending = next_slot;
             } else {
                 ctx->pending_copy = rec;                 // still the loaded buffer, with its copy events
-                ctx->pending_copy.start = ctx->pending_copy.end = nullptr;
+                ctx->pending_copy.start = ctx->pending_copy.start_done = ctx->pending_copy.end = nullptr;
             }
             return abandon_run(ctx, rec, rc);
         }
@@ -1249,8 +1332,7 @@ static int run_adaptive(bmgd_ctx* ctx, hipStream_t s, hipStream_t cs, const void
     }
     finish_run(ctx, run_rows, passes);
     ctx->subset = nullptr;
-    if (last) { give_event(ctx, rec.end); rec.end = last; rec.owns_end = false; }
-    else HIP_TRY(ctx, hipEventRecord(rec.end, s));
+    if (const int erc = end_run(ctx, rec, s, last, chain0)) return erc;
     HIP_TRY(ctx, hipEventRecord(slot.compute_done, s));
     slot.was_read = true;
     rec.n_chain = (int)(ctx->open_chain.size() - chain0);
@@ -1298,9 +1380,7 @@ static int run_resident(bmgd_ctx* ctx, const void* dev_x, const void* dev_y, int
     const int64_t run_rows = rows_of_run(ctx, rows);
     if (run_rows == 0) return BMGD_EINVAL;
     RunRecord rec;
-    rec.start = take_event(ctx); rec.end = take_event(ctx);
-    if (!rec.start || !rec.end) return fail(ctx, BMGD_EHIP, "could not create events");
-    HIP_TRY(ctx, hipEventRecord(rec.start, s));
+    if (!take_run_events(ctx, rec)) return fail(ctx, BMGD_EHIP, "could not create events");
     hipEvent_t last = nullptr;
     const size_t chain0 = ctx->open_chain.size(), prep0 = ctx->open_prep.size();
     const int rc = enqueue_compute(ctx, dev_x, dev_y, run_rows, s, &last);
@@ -1308,8 +1388,7 @@ static int run_resident(bmgd_ctx* ctx, const void* dev_x, const void* dev_y, int
     ctx->last_compute = s;
     ctx->used_compute = true;
     if (rc != BMGD_OK) return abandon_run(ctx, rec, rc);
-    if (last) { give_event(ctx, rec.end); rec.end = last; rec.owns_end = false; }
-    else HIP_TRY(ctx, hipEventRecord(rec.end, s));
+    if (const int erc = end_run(ctx, rec, s, last, chain0)) return erc;
     rec.n_chain = (int)(ctx->open_chain.size() - chain0);
     rec.n_prep = (int)(ctx->open_prep.size() - prep0);
     ctx->open_records.push_back(rec);
@@ -1454,11 +1533,11 @@ BMGD_API int bmgd_swa_update(bmgd_ctx* ctx, void* compute_stream)
     if (!ctx) return BMGD_EINVAL;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     // behind the last update of theta: in the moment form those run on the library's stream
-    hipStream_t s = ctx->chain == BMGD_CHAIN_GRAM ? ctx->chain_stream : static_cast<hipStream_t>(compute_stream);
+    hipStream_t s = ctx->chain_stream ? ctx->chain_stream : static_cast<hipStream_t>(compute_stream);
     const size_t n = (ctx->lay.total - ctx->lay.swa) / 4;           // whole array, padding included (stays 0)
     HIP_TRY(ctx, launch_running_mean(ctx->swa, ctx->theta, n, 1.0f / (float)(ctx->swa_count + 1), ctx->swa_count == 0, s));
     ctx->swa_count += 1;
-    if (ctx->chain != BMGD_CHAIN_GRAM) {
+    if (!ctx->chain_stream) {
         ctx->last_compute = s;
         ctx->used_compute = true;
     }

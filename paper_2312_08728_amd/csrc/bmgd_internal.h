@@ -33,7 +33,8 @@ int perm_half_width(int64_t rows);
 // subset != NULL: out[pass][j] = subset[PERM(...)[j]] (a partition of the rows subset[0 .. rows) of a buffer of `limit`
 // rows); an entry outside [0, limit) is replaced by 0 and *bad is set to 1.
 hipError_t launch_perm(int32_t* out, int64_t rows, int npass, const PermKeys& keys, hipStream_t stream,
-                       const int32_t* subset = nullptr, int64_t limit = 0, unsigned* bad = nullptr);
+                       const int32_t* subset = nullptr, int64_t limit = 0, unsigned* bad = nullptr, hipEvent_t start = nullptr,
+                       hipEvent_t stop = nullptr);
 
 // Device: zero `bytes` bytes at dst (both multiples of 16) with a kernel, in stream order.
 hipError_t launch_fill_zero(void* dst, size_t bytes, hipStream_t stream);
@@ -142,7 +143,8 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
 // Query co-residency and set attributes; fills shape->max_G and clamps shape->G.
 hipError_t glm_prepare(GlmLaunchShape* shape);
 // One launch of the persistent chain kernel covering steps [s_begin, s_end) of the buffer.
-hipError_t glm_launch_chain(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream);
+// `start` and `stop` (each may be NULL) are completed by the kernel's own dispatch.
+hipError_t glm_launch_chain(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream, hipEvent_t start, hipEvent_t stop);
 // Step-per-launch variant: partial sums for step `args.single_step`, then reduce + update.
 hipError_t glm_launch_step(const GlmLaunchShape& shape, const GlmArgs& args, int nb, hipStream_t stream);
 
@@ -151,7 +153,7 @@ hipError_t glm_launch_step(const GlmLaunchShape& shape, const GlmArgs& args, int
 size_t glm_split_lds_bytes(int ch);
 int glm_split_block();
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups);
-hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream);
+hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream, hipEvent_t start, hipEvent_t stop);
 
 // Persistent chain for rows of up to 1024 floats when a step's rows fit the registers of the grid (glm_narrow_kernel.hip), with
 // rw row wavefronts per workgroup.  glm_narrow_rows_in_flight: rows per row slot that a step of n rows needs on G workgroups, 0 if
@@ -161,7 +163,7 @@ constexpr int kNarrowOneTripMaxP = 512;    // widest rows of the redundant reduc
 int glm_narrow_block(int rw);
 int glm_narrow_rows_in_flight(int v, int cpl, int L, int rw, int G, int64_t n);
 hipError_t glm_narrow_prepare(const GlmLaunchShape& shape, int p, int* max_groups);
-hipError_t glm_narrow_launch(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream);
+hipError_t glm_narrow_launch(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream, hipEvent_t start, hipEvent_t stop);
 
 // Evaluation: partial[b] = sum of the per-sample losses of the rows workgroup b takes (b < nblocks <= kEvalBlocks).
 constexpr int kEvalBlocks = 1024;
@@ -195,6 +197,13 @@ hipError_t gram_launch_chain(const float* gram, float* theta, int rows, int p, i
 hipError_t gram_launch_chain_steps(const float* gram, float* theta, int p, int nsteps, int period, float alpha, const float* lr_tab,
                                    int lr_base, int lr_len, const OptArgs& opt, hipStream_t stream, hipEvent_t start,
                                    hipEvent_t stop);
+// Few features and few, small mini-batches: partitions, moment matrices and chain of a launch in one kernel (gram_fused_kernel.hip).
+// `gram`: room for npass * ceil(rows / n) sets of matrices; `ticket`: zero before the first launch, left so; subset as in launch_perm.
+bool gram_fused_eligible(int64_t p, int64_t buffer_n, int64_t batch_n);
+hipError_t gram_launch_fused(const float* X, const float* y, const PermKeys& keys, const int32_t* subset, int64_t limit, unsigned* bad,
+                             float* gram, float* theta, unsigned* ticket, int rows, int p, int n, int npass, float alpha,
+                             const float* lr_tab, int lr_base, int lr_len, const OptArgs& opt, hipStream_t stream, hipEvent_t start,
+                             hipEvent_t stop);
 // BMGD_CHAIN_PRODUCT (gram_products.hip): the npass * M steps of a launch as affine maps, multiplied together pairwise
 // in log2 rounds and applied to theta once.  `gram`: the dense matrices of gram_launch_moments(..., dense = true).
 // `scratch`: gram_products_scratch_floats(p, npass * M) floats.  Plain steps only.

@@ -25,6 +25,7 @@
 #include "bmgd_internal.h"
 #include "glm_device.h"
 
+#include <hip/hip_ext.h>
 #include <stdio.h>
 
 #include <algorithm>
@@ -744,20 +745,19 @@ hipError_t glm_prepare(GlmLaunchShape* s)
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), s->block,
                                                      s->lds_bytes);
     if (e != hipSuccess) return e;
-    int dev = 0;
-    hipDeviceProp_t prop;
+    int dev = 0, cus = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
-    if ((e = hipGetDeviceProperties(&prop, dev)) != hipSuccess) return e;
-    s->max_G = per_cu * prop.multiProcessorCount;
+    if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
+    s->max_G = per_cu * cus;
     if (s->max_G < 1) return hipErrorLaunchOutOfResources;
     // one workgroup per compute unit at most: the barrier cost grows with the number of arrivals
-    if (s->G > prop.multiProcessorCount) s->G = prop.multiProcessorCount;
+    if (s->G > cus) s->G = cus;
     if (s->G > s->max_G) s->G = s->max_G;
     if (s->split) {
         int cap = 0;
         e = glm_split_prepare(s->split_ch, s->with_optimizer != 0, &cap);
         if (e != hipSuccess) return e;
-        cap = std::min(cap, prop.multiProcessorCount) & ~7;
+        cap = std::min(cap, cus) & ~7;
         if (cap >= 8) {
             s->max_G = std::min(s->max_G, cap);
             s->G = std::min(s->G, cap) & ~7;
@@ -771,7 +771,7 @@ hipError_t glm_prepare(GlmLaunchShape* s)
         e = glm_narrow_prepare(*s, s->p, &cap);
         if (e != hipSuccess) return e;
         const bool sliced = s->reduce_mode == kReduceSliced;
-        cap = std::min(cap, prop.multiProcessorCount) & (sliced ? ~7 : ~0);
+        cap = std::min(cap, cus) & (sliced ? ~7 : ~0);
         const int G = std::min(s->G, cap) & (sliced ? ~7 : ~0);
         // fewer workgroups than planned hold fewer rows: only if the step still fits
         if (G >= (sliced ? 8 : 1) && glm_narrow_rows_in_flight(s->V, s->CPL, s->L, s->narrow_rw, G, s->n) == s->narrow_pf) {
@@ -785,19 +785,19 @@ hipError_t glm_prepare(GlmLaunchShape* s)
     return hipSuccess;
 }
 
-hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream)
+hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream, hipEvent_t start, hipEvent_t stop)
 {
     if (s.split) {
         if (s.G < 8 || s.G > s.max_G) return hipErrorInvalidValue;
         GlmArgs a = args;
         a.single_step = -1;
-        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, a, stream);
+        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, a, stream, start, stop);
     }
     if (s.narrow) {
         if (s.G > s.max_G) return hipErrorInvalidValue;
         GlmArgs a = args;
         a.single_step = -1;
-        return glm_narrow_launch(s, a, stream);
+        return glm_narrow_launch(s, a, stream, start, stop);
     }
     KernelFn fn = pick_kernel(s);
     if (!fn || s.G < 1 || s.G > s.max_G) return hipErrorInvalidValue;
@@ -807,7 +807,7 @@ hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStr
     // so all of them become resident as soon as compute units are free, and each device-side wait is
     // bounded anyway.  (The runtime's cooperative-launch path is avoided: it brings nothing more here and
     // its dedicated queue does not tear down cleanly under the profiler.)
-    hipLaunchKernelGGL(fn, dim3(s.G), dim3(s.block), s.lds_bytes, stream, a);
+    hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(s.block), (uint32_t)s.lds_bytes, stream, start, stop, 0u, a);
     return hipGetLastError();
 }
 

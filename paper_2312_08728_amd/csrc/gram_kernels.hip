@@ -8,7 +8,7 @@
 // then costs p^2 multiply-adds and 4 p^2 bytes per step inside ONE workgroup: no exchange between workgroups
 // at all.  Same arithmetic as the row form up to the order of summation.
 #include "bmgd_internal.h"
-#include "gram_layout.h"
+#include "gram_chain.h"
 
 #include <hip/hip_ext.h>
 
@@ -19,13 +19,6 @@ namespace bmgd {
 namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_mov(float v)
-{
-    return __builtin_bit_cast(float,
-                              __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
 
 struct GramTiles {
     int ntiles;                     // upper-triangle 16 x 16 tiles of the (p + 1) x (p + 1) moment matrix
@@ -204,146 +197,13 @@ __global__ void __launch_bounds__(64 * kGramWaves) gram_mfma_kernel(const float*
     }
 }
 
-// The chain: one workgroup, theta in LDS (two copies, alternating), the matrices of the coming AHEAD steps
-// already in registers.  Thread (i, seg) = (t / TPR, t % TPR); the TPR lanes of a row add up their parts.
-// RULE: plain steps, momentum / NAG, or Adam: separate instantiations, none carries anything of the others.  What a rule adds
-// sits on the step's critical path, so nothing of it is decided or read late: us per step at p = 37 for NAG 0.31 -> 0.23, for
-// Adam 2.2 -> 0.37 (p = 100: 0.57 -> 0.53 and 2.4 -> 0.70), against one instantiation for all rules.
-enum { kRulePlain = 0, kRuleMomentum = 1, kRuleAdam = 2 };
-constexpr int kCorrSteps = 64;                    // steps whose bias corrections are formed together
-
 template <int TPR, int KQ, int KS, int AHEAD, bool TAB, int RULE>
 __global__ void __launch_bounds__(1024) gram_chain_kernel(const float* __restrict__ gram, float* __restrict__ theta,
                                                           GramLayout L, int nsteps, int period, float alpha,
                                                           const float* __restrict__ lr_tab, int lr_base, int lr_len, OptArgs opt)
 {
-    __shared__ __align__(16) float th[2][kGramMaxP + 4 * 16];
-    __shared__ float2 corr[2][RULE == kRuleAdam ? kCorrSteps : 1];
-    const int t = threadIdx.x;
-    const int i = t / TPR, seg = t % TPR;
-    const int p = L.p;
-    const bool row_ok = i < p;
-    constexpr int NQ = KQ > 0 ? KQ : 1, NS = KS > 0 ? KS : 1;
-    float4 sq[AHEAD][NQ];
-    float ss[AHEAD][NS];
-    float bb[AHEAD];
-    float aa[AHEAD];                                  // learning rate of the step, from the optional table
-    const int ib = row_ok ? i : 0;
-    int fidx = 0;                                     // matrices to request next; wraps when passes share one partition
-    // Addresses are a wavefront-uniform base (scalar registers) plus a 32-bit per-thread byte offset that never
-    // changes: no vector arithmetic per request.
-    const unsigned off16 = (unsigned)t * 16u, off4 = (unsigned)t * 4u, offb = (unsigned)ib * 4u;
-    // TAB: the learning rate of a step comes from lr_tab (requested with the step's matrices), else it is alpha.
-    const int lr_last = lr_len - 1;
-    int lr_next = lr_base;
-    auto fetch = [&](float4 (&q)[NQ], float (&sc)[NS], float& bv, float& av) {
-        const char* g = reinterpret_cast<const char*>(gram + (size_t)fidx * L.step_floats);
-        fidx = fidx + 1 == period ? 0 : fidx + 1;
-#pragma unroll
-        for (int k = 0; k < KQ; ++k) q[k] = *reinterpret_cast<const float4*>(g + (size_t)k * L.nthr * 16 + off16);
-#pragma unroll
-        for (int j = 0; j < KS; ++j) sc[j] = *reinterpret_cast<const float*>(g + (size_t)(4 * KQ + j) * L.nthr * 4 + off4);
-        bv = *reinterpret_cast<const float*>(g + (size_t)L.b_off * 4 + offb);
-        if constexpr (TAB) {
-            av = lr_tab[min(lr_next, lr_last)];
-            lr_next += 1;
-        }
-    };
-#pragma unroll
-    for (int d = 0; d + 1 < AHEAD; ++d) fetch(sq[d], ss[d], bb[d], aa[d]);
-    for (int c = t; c < kGramMaxP + 64; c += blockDim.x) { th[0][c] = c < p ? theta[c] : 0.f; th[1][c] = 0.f; }
-    // The compiler is free to reorder these first requests; with all of them landed before the loop, the waits
-    // it places inside the loop count only the requests of the loop itself, which are issued oldest slot first.
-    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
-    __syncthreads();
-
-    // Steps are taken AHEAD at a time without any branch around the loads (a branch would make the compiler
-    // wait for every outstanding load); steps past the last one run with a zero learning rate.
-    // optimizer state of coordinate i lives in the registers of the lane that updates it
-    const bool owner = seg == 0 && row_ok;
-    float om = 0.f, os = 0.f;
-    if (RULE != kRulePlain && owner) {
-        om = opt.m[i];
-        if (RULE == kRuleAdam) os = opt.s[i];
-    }
-    // Adam's bias corrections do not depend on theta: a wavefront forms those of kCorrSteps steps at once, one block ahead of
-    // their use (two powers in every step, on its critical path, took 0.8 to 2 us of it)
-    auto corrections = [&](int block) {
-        if constexpr (RULE == kRuleAdam) {
-            if (t < kCorrSteps) {
-                float c1, c2;
-                opt_corrections(opt, opt.k_base + block * kCorrSteps + t + 1, c1, c2);
-                corr[block & 1][t] = make_float2(c1, c2);
-            }
-        }
-    };
-    if constexpr (RULE == kRuleAdam) {
-        corrections(0);
-        __syncthreads();
-    }
-    const float nag = RULE == kRuleMomentum && opt.kind == kOptNag ? 1.f : 0.f;
-    int cur = 0;
-    for (int sb = 0; sb < nsteps; sb += AHEAD) {
-#pragma unroll
-        for (int d = 0; d < AHEAD; ++d) {
-            const int step = sb + d;
-            const float a_eff = step < nsteps ? (TAB ? aa[d] : alpha) : 0.f;
-            // (steps come in order: the block after this one is formed at this one's first step, barriers away from its use)
-            if (RULE == kRuleAdam && step % kCorrSteps == 0) corrections(step / kCorrSteps + 1);
-            // Request step s + AHEAD - 1 into the ring slot the previous step has just used up, before this step's
-            // arithmetic: the memory pipeline works on the requests of all wavefronts while they compute.
-            const int prev = (d + AHEAD - 1) % AHEAD;
-            fetch(sq[prev], ss[prev], bb[prev], aa[prev]);
-            float dot0 = 0.f, dot1 = 0.f;
-#pragma unroll
-            for (int k = 0; k < KQ; ++k) {
-                const float4 tv = *reinterpret_cast<const float4*>(&th[cur][4 * (seg + TPR * k)]);
-                dot0 = fmaf(sq[d][k].x, tv.x, dot0);
-                dot1 = fmaf(sq[d][k].y, tv.y, dot1);
-                dot0 = fmaf(sq[d][k].z, tv.z, dot0);
-                dot1 = fmaf(sq[d][k].w, tv.w, dot1);
-            }
-#pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                const float tv = th[cur][4 * TPR * KQ + TPR * j + seg];
-                if (j & 1) dot1 = fmaf(ss[d][j], tv, dot1); else dot0 = fmaf(ss[d][j], tv, dot0);
-            }
-            float dot = dot0 + dot1;
-            const float own = th[cur][ib];           // (read ahead of the sums below)
-            const float base = fmaf(a_eff, bb[d], own);
-            float2 c = make_float2(1.f, 1.f);
-            if constexpr (RULE == kRuleAdam) c = corr[(step / kCorrSteps) & 1][step % kCorrSteps];
-            if (TPR >= 2) dot += dpp_mov<0xB1>(dot);      // lanes ^1
-            if (TPR >= 4) dot += dpp_mov<0x4E>(dot);      // lanes ^2
-            if (TPR >= 8) dot += dpp_mov<0x141>(dot);     // mirror within 8
-            if (TPR >= 16) dot += dpp_mov<0x140>(dot);    // mirror within 16
-            // (steps past the last one leave theta and the state alone)
-            if constexpr (RULE == kRulePlain) {
-                if (owner) th[cur ^ 1][i] = fmaf(-a_eff, dot, base);
-            } else {
-                const bool active = step < nsteps;
-                const float grad = dot - bb[d];
-                float nm, ns = os, nv;
-                if constexpr (RULE == kRuleMomentum) {
-                    nm = opt.mu * om - a_eff * grad;
-                    nv = nag != 0.f ? own + opt.mu * nm - a_eff * grad : own + nm;
-                } else {
-                    nm = om;
-                    nv = opt_update(opt, own, grad, a_eff, nm, ns, c.x, c.y);
-                }
-                om = active ? nm : om;
-                os = active ? ns : os;
-                if (owner) th[cur ^ 1][i] = active ? nv : own;
-            }
-            __syncthreads();
-            cur ^= 1;
-        }
-    }
-    for (int c = t; c < p; c += blockDim.x) theta[c] = th[cur][c];
-    if (RULE != kRulePlain && owner) {
-        opt.m[i] = om;
-        if (RULE == kRuleAdam) opt.s[i] = os;
-    }
+    gram_chain_steps<TPR, KQ, KS, AHEAD, TAB ? kRateTable : kRateConstant, RULE>(gram, theta, L, nsteps, period, alpha, lr_tab, lr_base,
+                                                                                 lr_len, nullptr, opt);
 }
 
 // tiles per workgroup for NT tile rows: {few workgroups, many workgroups}

@@ -1,44 +1,17 @@
 // Device-side seeded partition of a buffer into mini-batches.
 //
 // Algorithm 1 draws a fresh random partition of the buffer at the start of every pass; Section 2.2
-// asks for disjoint parts that cover the buffer.  The generator is a keyed 8-round balanced Feistel
-// network on 2h bits (2^(2h) < 4 * rows) restricted to [0, rows) by cycle walking, in uint32 arithmetic
-// only, so that the index arrays are reproducible bit for bit.  Mini-batch m is
-// perm[(m-1) n : min(m n, rows)).
-#include "bmgd_internal.h"
+// asks for disjoint parts that cover the buffer.  The generator (perm_device.h) is integer arithmetic only, so that the
+// index arrays are reproducible bit for bit.  Mini-batch m is perm[(m-1) n : min(m n, rows)).
+#include "perm_device.h"
+
+#include <hip/hip_ext.h>
 
 #include <algorithm>
 
 namespace bmgd {
 
 namespace {
-
-__host__ __device__ inline uint32_t mix32(uint32_t x)
-{
-    x ^= x >> 16;
-    x *= 0x7FEB352Du;
-    x ^= x >> 15;
-    x *= 0x846CA68Bu;
-    x ^= x >> 16;
-    return x;
-}
-
-struct KeyRow {
-    uint32_t k[kPermRounds];
-};
-
-__device__ inline uint32_t feistel(uint32_t x, const KeyRow& key, uint32_t h, uint32_t mask)
-{
-    uint32_t left = x >> h, right = x & mask;
-#pragma unroll
-    for (int i = 0; i < kPermRounds; ++i) {
-        const uint32_t f = mix32(right ^ key.k[i]) & mask;
-        const uint32_t t = left ^ f;
-        left = right;
-        right = t;
-    }
-    return (left << h) | right;
-}
 
 // With `subset` the partition is one of the rows subset[0 .. rows) of a larger buffer: out holds subset[PERM[j]].
 // An entry outside [0, limit) is replaced by row 0 and reported through *bad (the host turns that into an error).
@@ -52,10 +25,7 @@ __global__ void __launch_bounds__(256) perm_kernel(int32_t* __restrict__ out, ui
     KeyRow key;
 #pragma unroll
     for (int i = 0; i < kPermRounds; ++i) key.k[i] = keys.key[pass][i];
-    const uint32_t mask = (1u << h) - 1u;
-    // j < rows lies on a cycle of the bijection that returns to j, so the walk always re-enters [0, rows).
-    uint32_t x = feistel(j, key, h, mask);
-    while (x >= rows) x = feistel(x, key, h, mask);
+    uint32_t x = perm_entry(j, key, h, rows);
     if (subset) {
         const uint32_t v = (uint32_t)subset[x];
         if (v >= limit) __hip_atomic_store(bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -163,14 +133,14 @@ int perm_half_width(int64_t rows)
 }
 
 hipError_t launch_perm(int32_t* out, int64_t rows, int npass, const PermKeys& keys, hipStream_t stream, const int32_t* subset,
-                       int64_t limit, unsigned* bad)
+                       int64_t limit, unsigned* bad, hipEvent_t start, hipEvent_t stop)
 {
     if (rows <= 0 || npass <= 0) return hipSuccess;
     if (npass > kMaxPassesPerLaunch || rows > (int64_t(1) << 30)) return hipErrorInvalidValue;
     if (subset && (!bad || limit < rows || limit > (int64_t(1) << 30))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((rows + 255) / 256), (unsigned)npass);
-    hipLaunchKernelGGL(perm_kernel, grid, dim3(256), 0, stream, out, (uint32_t)rows,
-                       (uint32_t)perm_half_width(rows), keys, subset, (uint32_t)limit, bad);
+    hipExtLaunchKernelGGL(perm_kernel, grid, dim3(256), 0u, stream, start, stop, 0u, out, (uint32_t)rows,
+                          (uint32_t)perm_half_width(rows), keys, subset, (uint32_t)limit, bad);
     return hipGetLastError();
 }
 

@@ -1,0 +1,82 @@
+"""The moment form in one kernel (few features, few and small mini-batches, the mode left to the library): partitions, matrices and
+chain of a launch.  fp32 sums of at most n products per entry and p per update, as in the other tests of this form: 1e-4."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from gpu_util import rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _run(p, N0, n, T, kind, table=None, subset=None, streams=1, **kw):
+    import torch
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    w = wl.CONFIGS["cfg2"].scaled(name="case", N=2 * N0, p=p, N0=N0, n=n, T=T, R=1, x_cov="identity")
+    X, y = wl.dataset(w)
+    rate = 0.01 if kind == 3 else 0.1 / (p + 10)
+    opts = dict(momentum=0.8, beta1=0.9, beta2=0.99, eps=1e-6)
+    ref = O.BMGD(w.model, p, w.n, rate, w.T)
+    ctx = B.Context(p, w.N0, w.n, rate, w.T, model=w.model, optimizer=kind, **opts, **kw)
+    if kind:
+        ref.set_optimizer(kind, **opts)
+    if table is not None:
+        sched = np.linspace(rate, rate / 5, table).astype(np.float32)
+        ref.set_lr_schedule(sched)
+        ctx.set_lr_schedule(sched)
+    xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    idx = None if subset is None else torch.from_numpy(subset).cuda()
+    torch.cuda.synchronize()
+    ss = [torch.cuda.Stream() for _ in range(streams)]
+    keep = []
+    for k in range(2):
+        lo, hi = k * w.N0, (k + 1) * w.N0
+        xk, yk = xd[lo:hi].clone(), yd[lo:hi].clone()
+        torch.cuda.synchronize()
+        keep.append((xk, yk))
+        if subset is not None:
+            ctx.set_row_subset(idx, len(subset))
+            ref.run_buffer(X[lo:hi][subset], y[lo:hi][subset])
+        else:
+            ref.run_buffer(X[lo:hi], y[lo:hi])
+        ctx.run_device_buffer(xk, yk, w.N0, ss[k % streams])
+    got, st = ctx.get_theta(), ctx.stats()
+    ctx.close()
+    return got, ref.theta, st
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2, 3])
+@pytest.mark.parametrize("p", [1, 3, 4, 15, 16, 17, 31, 32, 33, 47, 48, 62, 63])
+def test_layouts_and_rules(p, kind):
+    """Every tile and chain layout; seven mini-batches, the last one of 6 rows, in launches of 28 and 7 steps."""
+    got, want, st = _run(p, N0=6 * 131 + 6, n=131, T=5, kind=kind, table=50 if p % 2 else None)
+    assert st.prep_launches == 0 and st.chain_launches == 4 and st.n_workgroups == 1 and st.steps == 2 * 5 * 7
+    assert rel_l2(got, want) <= 1e-4
+
+
+@pytest.mark.parametrize("N0,n,T", [(126, 2, 4),         # one-row shares, most steps a wavefront's rows are few for
+                                    (504, 2, 4),         # 1,008 steps in a launch: the most
+                                    (512, 512, 1),       # one mini-batch of the largest size: 64 rows a wavefront
+                                    (1030, 511, 3),      # 64 and 63 rows a wavefront; a last mini-batch of 8 rows
+                                    (521, 260, 2)])      # 36 rows: a second request of four rows; a last mini-batch of one row
+def test_shapes(N0, n, T):
+    got, want, st = _run(1, N0=N0, n=n, T=T, kind=0)
+    assert st.prep_launches == 0 and rel_l2(got, want) <= 1e-4
+
+
+def test_beyond_the_rule_other_kernels_run():
+    for N0, n in ((506, 2), (1030, 513)):                # 1,012 steps in a launch of four passes; a mini-batch of 513 rows
+        got, want, st = _run(1, N0=N0, n=n, T=4, kind=0)
+        assert st.prep_launches > 0 and rel_l2(got, want) <= 1e-4
+
+
+def test_row_subset():
+    rng = np.random.default_rng(3)
+    got, want, st = _run(20, N0=900, n=100, T=3, kind=0, subset=rng.choice(900, 333, replace=False).astype(np.int32))
+    assert st.prep_launches == 0 and rel_l2(got, want) <= 1e-4
+
+
+def test_runs_on_alternating_streams_follow_one_another():
+    got, want, st = _run(12, N0=2000, n=100, T=4, kind=1, streams=2)
+    assert st.prep_launches == 0 and rel_l2(got, want) <= 1e-4
