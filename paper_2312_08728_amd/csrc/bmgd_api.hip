@@ -33,7 +33,7 @@ constexpr int kMaxGroups = 256;                    // upper bound used to size t
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t slot_x[2], slot_y[2], perm, theta, partial, ll_part, ll_theta, sync, sm_state, wbt, u, rt, xt, sm_words, gram[2], prod[2], gram_perm, gram_cache, gram_cache_set, prod_cache, prod_cache_set, opt_m, opt_s, opt_len, eval, swa, total;
+    size_t slot_x[2], slot_y[2], perm, theta, partial, ll_part, ll_theta, sync, sm_state, wbt, u, rt, xt, sm_words, gram[2], gram_tickets, gram_cache_tickets, prod[2], gram_perm, gram_cache, gram_cache_set, prod_cache, prod_cache_set, opt_m, opt_s, opt_len, eval, swa, total;
 };
 
 struct Slot {
@@ -295,9 +295,11 @@ Layout make_layout(const bmgd_config& c, bool one_kernel)
         l.sm_state = l.wbt = l.u = l.rt = l.xt = l.sm_words = off;
     }
     l.gram[0] = l.gram[1] = l.gram_perm = off;
+    l.gram_tickets = l.gram_cache_tickets = 0;       // (from the start of a set)
     if (resolve_chain(c) == BMGD_CHAIN_GRAM) {
-        const size_t set = align_up((size_t)kMaxPassesPerLaunch * (size_t)((c.buffer_n + c.batch_n - 1) / c.batch_n) *
-                                    (wants_products(c) ? gram_dense_bytes_per_batch(c.p) : gram_bytes_per_batch(c.p)));
+        const size_t items = (size_t)kMaxPassesPerLaunch * (size_t)((c.buffer_n + c.batch_n - 1) / c.batch_n);
+        l.gram_tickets = align_up(items * (wants_products(c) ? gram_dense_bytes_per_batch(c.p) : gram_bytes_per_batch(c.p)));
+        const size_t set = l.gram_tickets + align_up(items * gram_ticket_bytes);
         l.gram[0] = off; off += set;
         l.gram[1] = off; off += wants_fused(c) ? 0 : set;
         l.gram_perm = off; off += wants_fused(c) ? 0 : align_up((size_t)kMaxPassesPerLaunch * c.buffer_n * 4);   // second set of partitions
@@ -313,8 +315,9 @@ Layout make_layout(const bmgd_config& c, bool one_kernel)
     l.gram_cache = off;
     l.gram_cache_set = 0;
     if (c.cache_moments) {
-        l.gram_cache_set = align_up((size_t)((c.buffer_n + c.batch_n - 1) / c.batch_n) *
-                                    (wants_products(c) ? gram_dense_bytes_per_batch(c.p) : gram_bytes_per_batch(c.p)));
+        const size_t items = (size_t)((c.buffer_n + c.batch_n - 1) / c.batch_n);
+        l.gram_cache_tickets = align_up(items * (wants_products(c) ? gram_dense_bytes_per_batch(c.p) : gram_bytes_per_batch(c.p)));
+        l.gram_cache_set = l.gram_cache_tickets + align_up(items * gram_ticket_bytes);
         off += l.gram_cache_set * (size_t)c.n_buffers;
     }
     // BMGD_CHAIN_PRODUCT with cached moment matrices: per buffer index also the product of a run's steps
@@ -672,9 +675,11 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                 ctx->open_prep.emplace_back(pv0, pv1);
                 // a chain that still reads the old matrices of this index (another row count) must have finished
                 if (ce.valid) HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->cache_chain_done, 0));
-                HIP_TRY(ctx, launch_perm(ctx->gram_perm[0], rows, 1, keys, stream));
-                HIP_TRY(ctx, gram_launch_moments(static_cast<const float*>(x), static_cast<const float*>(y), ctx->gram_perm[0], set,
-                                                 (int)rows, (int)c.p, (int)n, np, 0, stream, pv0, pv1, ctx->products));
+                const bool draw = gram_moments_draw(c.p, rows, n);
+                if (!draw) HIP_TRY(ctx, launch_perm(ctx->gram_perm[0], rows, 1, keys, stream));
+                HIP_TRY(ctx, gram_launch_moments(static_cast<const float*>(x), static_cast<const float*>(y), draw ? nullptr : ctx->gram_perm[0],
+                                                 GramPartition{keys, nullptr, 0, nullptr}, set,
+                                                 reinterpret_cast<unsigned*>(reinterpret_cast<char*>(set) + ctx->lay.gram_cache_tickets), (int)rows, (int)c.p, (int)n, np, 0, stream, pv0, pv1, ctx->products));
                 HIP_TRY(ctx, hipEventRecord(ce.ready, stream));
                 ce.valid = true;
                 ce.prod_valid = false;
@@ -700,13 +705,20 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             ctx->open_prep.emplace_back(pv0, pv1);
             // set i is free once the chain that read it last has finished
             if (ctx->chain_pending[i]) HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->chain_done[i], 0));
-            HIP_TRY(ctx, start_perm(ctx, ctx->gram_perm[i], rows, nperm, keys, stream));
+            const bool draw = gram_moments_draw(c.p, rows, n);
+            if (draw) {
+                const int brc = begin_run(ctx, stream);
+                if (brc != BMGD_OK) return brc;
+            } else {
+                HIP_TRY(ctx, start_perm(ctx, ctx->gram_perm[i], rows, nperm, keys, stream));
+            }
             // BMGD_CHAIN_PRODUCT (without cached matrices): the steps are multiplied in pairs right behind the moments
             // kernel, on the same stream (both fill the device; the chain, which keeps to one unit, overlaps the next
             // buffer's two), and the chain runs over the pairs.  Set i of the pairs is guarded like set i of the matrices.
             const bool pairs_here = ctx->products && !c.cache_moments;
-            HIP_TRY(ctx, gram_launch_moments(static_cast<const float*>(x), static_cast<const float*>(y), ctx->gram_perm[i],
-                                             ctx->gram[i], (int)rows, (int)c.p, (int)n, np, fixed ? 0 : (int)rows, stream,
+            HIP_TRY(ctx, gram_launch_moments(static_cast<const float*>(x), static_cast<const float*>(y), draw ? nullptr : ctx->gram_perm[i],
+                                             GramPartition{keys, ctx->subset, ctx->subset_limit, ctx->sync + 2}, ctx->gram[i],
+                                             reinterpret_cast<unsigned*>(reinterpret_cast<char*>(ctx->gram[i]) + ctx->lay.gram_tickets), (int)rows, (int)c.p, (int)n, np, fixed ? 0 : (int)rows, stream,
                                              pv0, pairs_here ? nullptr : pv1, ctx->products));
             if (pairs_here) {
                 HIP_TRY(ctx, gram_launch_pairs(ctx->gram[i], ctx->prod[i], (int)rows, (int)c.p, (int)n, np, fixed ? 0 : (int)rows,

@@ -182,8 +182,19 @@ size_t gram_bytes_per_batch(int64_t p);
 int gram_chain_threads(int64_t p);
 // Moment matrices of all mini-batches of `npass` passes (partitions at perm + pass * perm_stride) into `gram`.
 // `start` and `stop` (each may be NULL) are completed by the kernel's own dispatch, here and below.
-hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* perm, float* gram, int rows, int p, int n, int npass,
-                               int perm_stride, hipStream_t stream, hipEvent_t start, hipEvent_t stop, bool dense = false);
+// With gram_moments_draw(p, rows, n) `perm` may be NULL: the entries of the partitions are worked out from `from` on the way.  `tickets`: two
+// words per mini-batch and wavefront of a workgroup (gram_ticket_bytes each), zero before the first launch, left so.
+struct GramPartition {
+    PermKeys keys;
+    const int32_t* subset;      // as in launch_perm
+    int64_t limit;
+    unsigned* bad;
+};
+constexpr size_t gram_ticket_bytes = 32;
+bool gram_moments_draw(int64_t p, int64_t rows, int64_t n);
+hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* perm, const GramPartition& from, float* gram, unsigned* tickets,
+                               int rows, int p, int n, int npass, int perm_stride, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
+                               bool dense = false);
 // dense = true: each mini-batch's [Sxx_m | -Sxy_m] as a dense row-major matrix of order gram_dense_order(p) (p + 1 rounded
 // up to 16; what lies beyond row p - 1 or column p is never written and must be zero), for gram_launch_products
 int gram_dense_order(int64_t p);

@@ -9,6 +9,7 @@
 // at all.  Same arithmetic as the row form up to the order of summation.
 #include "bmgd_internal.h"
 #include "gram_chain.h"
+#include "perm_device.h"
 
 #include <hip/hip_ext.h>
 
@@ -206,6 +207,230 @@ __global__ void __launch_bounds__(1024) gram_chain_kernel(const float* __restric
                                                                                  lr_len, nullptr, opt);
 }
 
+// The same matrices with the rows gathered straight into matrix operands, for up to 47 features and launches with mini-batches enough to
+// fill the device.
+//
+// With A = rows' and B = rows a lane's element of both operands is the same, so 16 columns of four rows are one load per lane and serve a
+// whole row and column of tiles: no way through shared memory, and a wavefront keeps ALL tiles of its rows' matrix in registers.  What
+// bounds it is the gather of short rows.  A mini-batch is split over S workgroups by rows, so that few mini-batches fill the device too; the
+// second of two workgroups to finish adds the first one's sums, which it finds where the result goes (a + b = b + a: the same bits
+// whichever comes first).  Rows are requested one stage (U groups of four rows) ahead.  The entries of the partition are worked out here
+// unless `perm` is given, 64 at a time per wavefront: the partition's own kernel and what lies behind it are 10 to 16 us per buffer.
+// us per buffer, wall clock, staged kernel with partitions from memory / this one: 127 / 59 (p = 10, n = 5,000, 100 mini-batches), 86 / 73
+// (p = 10, n = 1,000, 400), 175 / 157 (p = 20, n = 300, 2,000), 68 / 66 (p = 37, n = 600, 300).  Not with more features: from five tile rows on
+// its loads and matrix instructions do not overlap as they should (p = 64: 53 / 86 us of kernel, p = 100: 90 / 136).
+struct DirectArgs {
+    const float* X;
+    const float* y;
+    const int32_t* perm;                             // [pass][perm_stride], or NULL: from the keys
+    PermKeys keys;
+    uint32_t h;
+    const int32_t* subset;
+    uint32_t limit;
+    unsigned* bad;
+    float* out;
+    unsigned* tickets;                               // S = 2: [n_items][4], zero between launches
+    GramLayout L;
+    int rows, n, perm_stride, M, dense_q;
+};
+
+constexpr int kDirectWaves = 4;
+
+template <int NT, int S>
+__global__ void __launch_bounds__(64 * kDirectWaves, 2) gram_direct_kernel(DirectArgs a)
+{
+    constexpr int TILES = NT * (NT + 1) / 2;
+    constexpr int U = 8;                             // groups of four rows per stage
+    constexpr int STAGES = 64 / (4 * U);             // stages per 64 entries of the partition
+    __shared__ __align__(16) float lds[2 * TILES * 256];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int item = blockIdx.x / S, part = blockIdx.x % S;
+    const int pass = item / a.M, m = item - pass * a.M;
+    const int p = a.L.p;
+    const int nb = min(a.n, a.rows - m * a.n);
+    const int i16 = lane & 15, quad = lane >> 4;
+    // this wavefront's rows: whole groups of four, one share of S * kDirectWaves
+    const int share = (nb + 4 * S * kDirectWaves - 1) / (4 * S * kDirectWaves) * 4;
+    const int r_begin = min(nb, (part * kDirectWaves + wave) * share), r_end = min(nb, r_begin + share);
+    const int last_col = min(16 * (NT - 1) + i16, p - 1);             // (beyond p: values that go into entries nobody reads)
+    const bool is_y = 16 * (NT - 1) + i16 == p;
+    KeyRow key;
+#pragma unroll
+    for (int i = 0; i < kPermRounds; ++i) key.k[i] = a.keys.key[pass][i];
+    const int* idx_base = a.perm + (size_t)pass * (size_t)a.perm_stride + (size_t)m * (size_t)a.n;
+
+    floatx4 acc[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    struct Stage {
+        float x[U][NT];
+    };
+    uint32_t idx = 0;                                // lane l: row l of the 64 that are being requested
+    float yv = 0.f, y_use = 0.f;                     // and its response; of the 64 that are being used
+    auto entries = [&](int r0) {                     // rows r0 .. r0 + 63 of this wavefront (clamped)
+        const int j = min(r0 + lane, r_end - 1);
+        if (a.perm) idx = (uint32_t)idx_base[j];
+        else {
+            idx = perm_entry((uint32_t)(m * a.n + j), key, a.h, (uint32_t)a.rows);
+            if (a.subset) {
+                const uint32_t v = (uint32_t)a.subset[idx];
+                if (v >= a.limit) __hip_atomic_store(a.bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                idx = v < a.limit ? v : 0u;
+            }
+        }
+        yv = a.y[idx];
+    };
+    auto request = [&](Stage& st, int k) {           // stage k of the 64 entries
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t r = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (4 * (k * U + u) + quad), (int)idx);
+            const float* row = a.X + (size_t)r * (size_t)p;
+#pragma unroll
+            for (int f = 0; f < NT - 1; ++f) st.x[u][f] = row[i16 + 16 * f];
+            st.x[u][NT - 1] = row[last_col];
+        }
+    };
+    auto use = [&](Stage& st, int k, int left) {     // left: rows from the stage's first on
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float yy = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(4 * (4 * (k * U + u) + quad), __builtin_bit_cast(int, y_use)));
+            st.x[u][NT - 1] = is_y ? yy : st.x[u][NT - 1];
+        }
+        if (left < 4 * U) {                          // (uniform) the last stage: rows beyond the share count as zero
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int f = 0; f < NT; ++f) st.x[u][f] = 4 * u + quad < left ? st.x[u][f] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            int t = 0;
+#pragma unroll
+            for (int I = 0; I < NT; ++I) {
+#pragma unroll
+                for (int J = I; J < NT; ++J, ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(st.x[u][I], st.x[u][J], acc[t], 0, 0, 0);
+            }
+        }
+    };
+    if (r_begin < r_end) {
+        // Two stages in registers, used in turn: a stage is requested while the other is used.  (A stage beyond the last one repeats rows
+        // of the share and is not used.)
+        static_assert(STAGES % 2 == 0, "a stage of each kind in turn");
+        Stage A, B;
+        entries(r_begin);
+        request(A, 0);
+        for (int r0 = r_begin; r0 < r_end; r0 += 64) {
+            y_use = yv;
+#pragma unroll
+            for (int k = 0; k < STAGES; k += 2) {
+                request(B, k + 1);
+                if (r0 + 4 * U * k < r_end) use(A, k, r_end - (r0 + 4 * U * k));
+                if (k + 2 < STAGES) request(A, k + 2);
+                else { entries(min(r0 + 64, r_end - 1)); request(A, 0); }
+                if (r0 + 4 * U * (k + 1) < r_end) use(B, k + 1, r_end - (r0 + 4 * U * (k + 1)));
+            }
+        }
+    }
+
+    // the four wavefronts' sums: two halves through shared memory, then every wavefront a quarter of the tiles
+    floatx4* red = reinterpret_cast<floatx4*>(lds);
+    if (wave >= 2) {
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) red[((wave - 2) * TILES + t) * 64 + lane] = acc[t];
+    }
+    __syncthreads();
+    if (wave < 2) {
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            acc[t] += red[(wave * TILES + t) * 64 + lane];
+            red[(wave * TILES + t) * 64 + lane] = acc[t];
+        }
+    }
+    __syncthreads();
+    float* o = a.out + (size_t)item * (a.dense_q > 0 ? (size_t)a.dense_q * a.dense_q : (size_t)a.L.step_floats);
+    auto where = [&](int r, int c) { return a.dense_q > 0 ? r * a.dense_q + c : c == p ? a.L.b_off + r : gram_pos(a.L, r, c); };
+    constexpr int MINE = (TILES + kDirectWaves - 1) / kDirectWaves;
+    float s[MINE][4];
+    int tI[MINE], tJ[MINE];
+#pragma unroll
+    for (int q = 0; q < MINE; ++q) {
+        const int t = min(q * kDirectWaves + wave, TILES - 1);
+        const floatx4 v = red[t * 64 + lane] + red[(TILES + t) * 64 + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[q][e] = v[e];
+        int I = 0, first = 0;                        // tile t is (I, J): rows of tiles have NT, NT - 1, ... entries
+#pragma unroll
+        for (int k = 0; k < NT - 1; ++k)
+            if (t - first >= NT - I) { first += NT - I; ++I; }
+        tI[q] = 16 * I;
+        tJ[q] = 16 * (I + t - first);
+    }
+    auto each = [&](auto&& f) {
+#pragma unroll
+        for (int q = 0; q < MINE; ++q) {
+            const int c = tJ[q] + i16;
+            const bool here = q * kDirectWaves + wave < TILES && c <= p;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = tI[q] + 4 * quad + e;
+                if (here && r < p) f(q, e, r, c);
+            }
+        }
+    };
+    const float inv = 1.f / (float)nb;
+    const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc(o, 0, (int)((a.dense_q > 0 ? a.dense_q * a.dense_q : a.L.step_floats) * 4), 0x00020000);
+    constexpr int kAgent = 0x10;                     // cache policy sc1: past this die's cache
+    if constexpr (S == 2) {
+        // Per wavefront and mini-batch two words: who comes first leaves its sums and then says so; who comes second (the first one is past
+        // the ticket and waits for nothing, so this wait ends) adds them to its own and clears the words.
+        unsigned* ticket = a.tickets + 2 * (item * kDirectWaves + wave);
+        unsigned order = 0u;
+        if (lane == 0) order = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        order = (unsigned)__builtin_amdgcn_readfirstlane((int)order);
+        if (order == 0u) {
+            each([&](int q, int e, int r, int c) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, s[q][e]), ob, (unsigned)where(r, c) * 4u, 0, kAgent); });
+            __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+            asm volatile("" ::: "memory");
+            if (lane == 0) __hip_atomic_store(ticket + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        while (__hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+        float other[MINE][4];
+        each([&](int q, int e, int r, int c) { other[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ob, (unsigned)where(r, c) * 4u, 0, kAgent)); });
+        each([&](int q, int e, int, int) { s[q][e] += other[q][e]; });
+        if (lane == 0) {
+            __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(ticket + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    // (written past this die's cache as well: a plain store could leave one behind it that the other workgroup's sums would be merged into)
+    each([&](int q, int e, int r, int c) {
+        const float val = s[q][e] * inv;
+        const float put = c == p && a.dense_q > 0 ? -val : val;   // dense: [Sxx | -Sxy], for the kernel that multiplies steps together
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, put), ob, (unsigned)where(r, c) * 4u, 0, S == 2 ? kAgent : 0);
+        if (tI[q] != tJ[q] && c < p)
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, val), ob, (unsigned)where(c, r) * 4u, 0, S == 2 ? kAgent : 0);
+    });
+}
+
+using DirectFn = void (*)(DirectArgs);
+
+template <int S>
+DirectFn direct_kernel(int NT)
+{
+    switch (NT) {
+    case 1: return gram_direct_kernel<1, S>;
+    case 2: return gram_direct_kernel<2, S>;
+    case 3: return gram_direct_kernel<3, S>;
+    }
+    return nullptr;
+}
+
+// By the mini-batches of one pass, so that a pass gives the same bits whatever it is launched with.
+bool direct_moments(int p, int M) { return p <= 47 && M >= 64; }
+
 // tiles per workgroup for NT tile rows: {few workgroups, many workgroups}
 void tile_split(int ntiles, int wgs_per_split, int* tsplit, int* tpw)
 {
@@ -304,14 +529,31 @@ int gram_chain_threads(int64_t p)
     return make_layout((int)p).nthr;
 }
 
-hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* perm, float* gram, int rows, int p, int n, int npass,
-                               int perm_stride, hipStream_t stream, hipEvent_t start, hipEvent_t stop, bool dense)
+bool gram_moments_draw(int64_t p, int64_t rows, int64_t n) { return direct_moments((int)p, (int)((rows + n - 1) / n)); }
+
+hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* perm, const GramPartition& from, float* gram, unsigned* tickets,
+                               int rows, int p, int n, int npass, int perm_stride, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
+                               bool dense)
 {
     const int dense_q = dense ? gram_dense_order(p) : 0;
     if (p < 1 || p > kGramMaxP) return hipErrorInvalidValue;
     const GramLayout L = make_layout(p);
     const int M = (rows + n - 1) / n;
     const int gpass = perm_stride == 0 ? 1 : npass;      // one partition for all passes: one set of matrices
+    if (direct_moments(p, M)) {
+        DirectArgs a{};
+        a.X = X; a.y = y; a.perm = perm; a.keys = from.keys; a.h = (uint32_t)perm_half_width(rows);
+        a.subset = from.subset; a.limit = (uint32_t)from.limit; a.bad = from.bad;
+        a.out = gram; a.tickets = tickets; a.L = L;
+        a.rows = rows; a.n = n; a.perm_stride = perm_stride; a.M = M; a.dense_q = dense_q;
+        // Two workgroups per mini-batch while a launch is a few rounds of workgroups (two per compute unit) at most
+        const int S = M < 512 ? 2 : 1;
+        DirectFn fn = S == 2 ? direct_kernel<2>((p + 1 + 15) / 16) : direct_kernel<1>((p + 1 + 15) / 16);
+        if (!fn || (S == 2 && !tickets)) return hipErrorInvalidValue;
+        hipExtLaunchKernelGGL(fn, dim3((unsigned)(M * gpass * S)), dim3(64 * kDirectWaves), 0u, stream, start, stop, 0u, a);
+        return hipGetLastError();
+    }
+    if (!perm) return hipErrorInvalidValue;
     const int NT = (p + 1 + 15) / 16;                    // tile rows of the moment matrix of [X y]
     GramTiles T{};
     T.ntiles = NT * (NT + 1) / 2;
