@@ -157,6 +157,8 @@ struct bmgd_ctx {
     size_t mail_area = 0;
     hipEvent_t mail_done[2] = {nullptr, nullptr};  // the export that filled an area (large estimates only)
     bool fused = false;                            // eq. (3.1) form, a launch in one kernel (gram_fused_kernel.hip) on the caller's stream
+    hipStream_t theta_stream = nullptr;            // ... then: where the last work that touches theta was enqueued, and the event behind it
+    hipEvent_t theta_done = nullptr;               // (NULL: none since everything enqueued was last waited for)
     hipEvent_t run_start[2] = {nullptr, nullptr};  // events that the next run's first kernel is to carry ...
     bool run_marked = false;                       // ... but the first of them was recorded as a marker
     bool poisoned = false;                         // a run failed or was abandoned: theta is not valid until it is set again
@@ -420,6 +422,7 @@ void settle_records(bmgd_ctx* ctx, size_t count)
     }
     // elapsed times first, hand-backs second: a run's `end` may be the stop event of its last chain launch
     const bool all = count == ctx->open_records.size();     // then also entries of a run that failed half-way
+    if (all) ctx->theta_done = nullptr;
     n_chain = all ? ctx->open_chain.size() : std::min(n_chain, ctx->open_chain.size());
     n_prep = all ? ctx->open_prep.size() : std::min(n_prep, ctx->open_prep.size());
     for (size_t i = 0; i < n_chain; ++i) {
@@ -457,10 +460,19 @@ int trim_records(bmgd_ctx* ctx)
     return BMGD_OK;
 }
 
+// Fused form: launches share theta, the matrices and the ticket, and go to whatever stream the caller names, so each waits for the one
+// before, wherever that is.
+int follow_theta(bmgd_ctx* ctx, hipStream_t stream)
+{
+    if (ctx->theta_done && ctx->theta_stream != stream) HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->theta_done, 0));
+    return BMGD_OK;
+}
+
 // The stream whose work comes last: the library's chain stream in the moment form, else the caller's compute stream.
 hipStream_t tail_stream(const bmgd_ctx* ctx)
 {
     if (ctx->chain_stream) return ctx->chain_stream;
+    if (ctx->theta_done) return ctx->theta_stream;
     return ctx->used_compute ? ctx->last_compute : nullptr;
 }
 
@@ -645,17 +657,16 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
         if (!ev0 || !ev1) return fail(ctx, BMGD_EHIP, "could not create events");
         if (ctx->fused) {
             ctx->run_start[0] = ctx->run_start[1] = nullptr;      // (the launch's own events serve)
-            // theta goes from launch to launch in stream order; a caller that changes streams between runs is not made to see to that
-            if (ctx->used_compute && ctx->last_compute != stream && !ctx->open_chain.empty())
-                HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->open_chain.back().second, 0));
+            const int frc = follow_theta(ctx, stream);
+            if (frc != BMGD_OK) return frc;
             HIP_TRY(ctx, gram_launch_fused(static_cast<const float*>(x), static_cast<const float*>(y), keys, ctx->subset, ctx->subset_limit,
                                            ctx->sync + 2, ctx->gram[0], ctx->theta, ctx->sync + 12, (int)rows, (int)c.p, (int)n, np, (float)c.lr, lr_len ? ctx->lr_tab_dev : nullptr,
                                            (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0)), lr_len, opt_args(ctx, 0), stream, ev0, ev1));
             ctx->lr_pos += (int64_t)np * M;
             ctx->opt_k += (int64_t)np * M;
             ctx->open_chain.emplace_back(ev0, ev1);
-            ctx->last_compute = stream;
-            ctx->used_compute = true;
+            ctx->theta_stream = stream;
+            ctx->theta_done = ev1;
             *end_event = ev1;
             if (chunk_end) *chunk_end = ev1;
             continue;
@@ -984,6 +995,7 @@ void destroy_ctx(bmgd_ctx* ctx)
     (void)hipSetDevice(ctx->device);
     if (ctx->used_copy) (void)hipStreamSynchronize(ctx->last_copy);
     if (ctx->used_compute) (void)hipStreamSynchronize(ctx->last_compute);
+    if (ctx->theta_done) (void)hipEventSynchronize(ctx->theta_done);
     if (ctx->chain_stream) (void)hipStreamSynchronize(ctx->chain_stream);
     settle_records(ctx, ctx->open_records.size());
     if (ctx->chain_stream) (void)hipStreamDestroy(ctx->chain_stream);

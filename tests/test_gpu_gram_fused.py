@@ -9,7 +9,7 @@ from gpu_util import rel_l2
 pytestmark = pytest.mark.gpu
 
 
-def _run(p, N0, n, T, kind, table=None, subset=None, streams=1, **kw):
+def _run(p, N0, n, T, kind, table=None, subset=None, **kw):
     import torch
     import paper_2312_08728_amd as B
     from oracle import bmgd as O
@@ -28,7 +28,7 @@ def _run(p, N0, n, T, kind, table=None, subset=None, streams=1, **kw):
     xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
     idx = None if subset is None else torch.from_numpy(subset).cuda()
     torch.cuda.synchronize()
-    ss = [torch.cuda.Stream() for _ in range(streams)]
+    s = torch.cuda.Stream()
     keep = []
     for k in range(2):
         lo, hi = k * w.N0, (k + 1) * w.N0
@@ -40,7 +40,7 @@ def _run(p, N0, n, T, kind, table=None, subset=None, streams=1, **kw):
             ref.run_buffer(X[lo:hi][subset], y[lo:hi][subset])
         else:
             ref.run_buffer(X[lo:hi], y[lo:hi])
-        ctx.run_device_buffer(xk, yk, w.N0, ss[k % streams])
+        ctx.run_device_buffer(xk, yk, w.N0, s)
     got, st = ctx.get_theta(), ctx.stats()
     ctx.close()
     return got, ref.theta, st
@@ -77,6 +77,58 @@ def test_row_subset():
     assert st.prep_launches == 0 and rel_l2(got, want) <= 1e-4
 
 
-def test_runs_on_alternating_streams_follow_one_another():
-    got, want, st = _run(12, N0=2000, n=100, T=4, kind=1, streams=2)
-    assert st.prep_launches == 0 and rel_l2(got, want) <= 1e-4
+# Calls that name a stream, in the order of their enqueueing: run over a resident buffer (r), over a loaded one (l), the same with
+# its passes left to the library (a); "zX" keeps stream X busy for a while first, so that without an order of its own what follows on
+# the other stream would overtake what waits behind it.
+ORDERS = {
+    "resident": ["zA"] + ["rA", "rB"] * 15 + ["zB", "rB", "rA"],
+    "adaptive_behind_run": ["zA", "lA", "aB", "zB", "lB", "aA"],
+    "run_behind_adaptive": ["zB", "aB", "lA", "rB", "zA", "aA", "rB"],
+}
+
+
+@pytest.mark.parametrize("order", sorted(ORDERS))
+@pytest.mark.parametrize("kind", [0, 1])
+def test_calls_on_two_streams_follow_one_another(kind, order):
+    """Nothing is waited for on the host until the end; theta after every sequence, and the statistics' count of launches."""
+    import torch
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    p, N0, n, T = 12, 2000, 100, 2
+    w = wl.CONFIGS["cfg2"].scaled(name="case", N=4 * N0, p=p, N0=N0, n=n, T=T, R=1, x_cov="identity")
+    X, y = wl.dataset(w)
+    rate = 0.1 / (p + 10)
+    ctx = B.Context(p, N0, n, rate, T, model=w.model, optimizer=kind, momentum=0.8)
+    parts = [slice(k * N0, (k + 1) * N0) for k in range(4)]
+    xp, yp = torch.from_numpy(X).pin_memory(), torch.from_numpy(y).pin_memory()
+    dev = [(xp[part].cuda(), yp[part].cuda()) for part in parts]
+    ss = {"A": torch.cuda.Stream(), "B": torch.cuda.Stream()}
+    copy = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    calls = [c for c in ORDERS[order] if c[0] != "z"]
+    k = 0
+    for what, which in ORDERS[order]:
+        if what == "z":
+            with torch.cuda.stream(ss[which]):
+                torch.cuda._sleep(2_000_000)
+            continue
+        part = parts[k % 4]
+        k += 1
+        if what == "r":
+            ctx.run_device_buffer(*dev[(k - 1) % 4], N0, ss[which])
+            continue
+        ctx.load_buffer_async(xp[part], yp[part], N0, copy)
+        if what == "l":
+            ctx.run_buffer(ss[which])
+        else:
+            assert ctx.run_buffer_adaptive(ss[which], None, None, 0, None, T, T) == T
+    got, st = ctx.get_theta(), ctx.stats()
+    ctx.close()
+    ref = O.BMGD(w.model, p, n, rate, T)
+    if kind:
+        ref.set_optimizer(kind, momentum=0.8)
+    for k in range(len(calls)):
+        ref.run_buffer(X[parts[k % 4]], y[parts[k % 4]])
+    # (an adaptive run is one launch a pass)
+    assert st.prep_launches == 0 and st.chain_launches == sum(T if c[0] == "a" else 1 for c in calls)
+    assert rel_l2(got, ref.theta) <= 1e-4
