@@ -159,6 +159,7 @@ struct bmgd_ctx {
     bool fused = false;                            // eq. (3.1) form, a launch in one kernel (gram_fused_kernel.hip) on the caller's stream
     hipStream_t theta_stream = nullptr;            // ... then: where the last work that touches theta was enqueued, and the event behind it
     hipEvent_t theta_done = nullptr;               // (NULL: none since everything enqueued was last waited for)
+    hipEvent_t swa_done = nullptr;                 // ... behind the latest averaging of theta
     hipEvent_t run_start[2] = {nullptr, nullptr};  // events that the next run's first kernel is to carry ...
     bool run_marked = false;                       // ... but the first of them was recorded as a marker
     bool poisoned = false;                         // a run failed or was abandoned: theta is not valid until it is set again
@@ -1007,6 +1008,7 @@ void destroy_ctx(bmgd_ctx* ctx)
     for (auto& ce : ctx->mcache)
         if (ce.ready) (void)hipEventDestroy(ce.ready);
     if (ctx->cache_chain_done) (void)hipEventDestroy(ctx->cache_chain_done);
+    if (ctx->swa_done) (void)hipEventDestroy(ctx->swa_done);
     for (Slot& s : ctx->slots) {
         if (s.compute_done) (void)hipEventDestroy(s.compute_done);
     }
@@ -1558,9 +1560,17 @@ BMGD_API int bmgd_swa_update(bmgd_ctx* ctx, void* compute_stream)
     HIP_TRY(ctx, hipSetDevice(ctx->device));
     // behind the last update of theta: in the moment form those run on the library's stream
     hipStream_t s = ctx->chain_stream ? ctx->chain_stream : static_cast<hipStream_t>(compute_stream);
+    const int frc = follow_theta(ctx, s);
+    if (frc != BMGD_OK) return frc;
     const size_t n = (ctx->lay.total - ctx->lay.swa) / 4;           // whole array, padding included (stays 0)
     HIP_TRY(ctx, launch_running_mean(ctx->swa, ctx->theta, n, 1.0f / (float)(ctx->swa_count + 1), ctx->swa_count == 0, s));
     ctx->swa_count += 1;
+    if (ctx->fused) {                                    // the next launch, on whatever stream, waits until theta has been read
+        if (!ctx->swa_done) HIP_TRY(ctx, hipEventCreateWithFlags(&ctx->swa_done, hipEventDisableTiming));
+        HIP_TRY(ctx, hipEventRecord(ctx->swa_done, s));
+        ctx->theta_stream = s;
+        ctx->theta_done = ctx->swa_done;
+    }
     if (!ctx->chain_stream) {
         ctx->last_compute = s;
         ctx->used_compute = true;

@@ -78,12 +78,14 @@ def test_row_subset():
 
 
 # Calls that name a stream, in the order of their enqueueing: run over a resident buffer (r), over a loaded one (l), the same with
-# its passes left to the library (a); "zX" keeps stream X busy for a while first, so that without an order of its own what follows on
+# its passes left to the library (a), theta folded into the running average (s); "zX" keeps stream X busy for a while first, so that without an order of its own what follows on
 # the other stream would overtake what waits behind it.
 ORDERS = {
     "resident": ["zA"] + ["rA", "rB"] * 15 + ["zB", "rB", "rA"],
     "adaptive_behind_run": ["zA", "lA", "aB", "zB", "lB", "aA"],
     "run_behind_adaptive": ["zB", "aB", "lA", "rB", "zA", "aA", "rB"],
+    "run_behind_average": ["rA", "rB", "zB", "sB", "rA", "zA", "sA", "rB", "sB", "aA"],
+    "average_behind_run_elsewhere": ["rA", "zB", "rB", "sA", "rA", "zA", "aA", "sB", "sA"],
 }
 
 
@@ -112,6 +114,9 @@ def test_calls_on_two_streams_follow_one_another(kind, order):
             with torch.cuda.stream(ss[which]):
                 torch.cuda._sleep(2_000_000)
             continue
+        if what == "s":
+            ctx.swa_update(ss[which])
+            continue
         part = parts[k % 4]
         k += 1
         if what == "r":
@@ -122,13 +127,23 @@ def test_calls_on_two_streams_follow_one_another(kind, order):
             ctx.run_buffer(ss[which])
         else:
             assert ctx.run_buffer_adaptive(ss[which], None, None, 0, None, T, T) == T
+    averages = sum(c[0] == "s" for c in calls)
+    if averages:                                         # (fetched first: nothing has been waited for yet)
+        avg, count = ctx.get_swa()
     got, st = ctx.get_theta(), ctx.stats()
     ctx.close()
     ref = O.BMGD(w.model, p, n, rate, T)
     if kind:
         ref.set_optimizer(kind, momentum=0.8)
-    for k in range(len(calls)):
+    k = 0
+    for what, _ in calls:
+        if what == "s":
+            ref.swa_update()
+            continue
         ref.run_buffer(X[parts[k % 4]], y[parts[k % 4]])
+        k += 1
+    if averages:
+        assert count == averages and rel_l2(avg, ref.swa) <= 1e-4
     # (an adaptive run is one launch a pass)
-    assert st.prep_launches == 0 and st.chain_launches == sum(T if c[0] == "a" else 1 for c in calls)
+    assert st.prep_launches == 0 and st.chain_launches == sum({"a": T, "s": 0}.get(c[0], 1) for c in calls)
     assert rel_l2(got, ref.theta) <= 1e-4
