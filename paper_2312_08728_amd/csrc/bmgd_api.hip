@@ -48,8 +48,8 @@ struct Slot {
 
 struct RunRecord {                                 // events of one buffer, for the overlap statistics
     hipEvent_t copy_start = nullptr, copy_end = nullptr, start = nullptr, end = nullptr;
-    hipEvent_t start_done = nullptr;               // not NULL: `start` and this one ride on the run's first kernel (start and end of it)
-    bool owns_start = true;                        // false: those of the run's only launch, which has an entry in open_chain
+    hipEvent_t start_done = nullptr;               // not NULL (fused form): `start` and this one are the events of the run's first launch,
+                                                   //   which has an entry in open_chain
     bool has_copy = false;
     bool owns_end = true;                          // false: `end` is the stop event of the run's last chain launch
     int n_chain = 0, n_prep = 0;                   // launches of this run with an entry in open_chain / open_prep
@@ -160,8 +160,6 @@ struct bmgd_ctx {
     hipStream_t theta_stream = nullptr;            // ... then: where the last work that touches theta was enqueued, and the event behind it
     hipEvent_t theta_done = nullptr;               // (NULL: none since everything enqueued was last waited for)
     hipEvent_t swa_done = nullptr;                 // ... behind the latest averaging of theta
-    hipEvent_t run_start[2] = {nullptr, nullptr};  // events that the next run's first kernel is to carry ...
-    bool run_marked = false;                       // ... but the first of them was recorded as a marker
     bool poisoned = false;                         // a run failed or was abandoned: theta is not valid until it is set again
     std::string err;
 };
@@ -441,7 +439,7 @@ void settle_records(bmgd_ctx* ctx, size_t count)
     for (size_t i = 0; i < count; ++i) {
         RunRecord& r = ctx->open_records[i];
         give_event(ctx, r.copy_start); give_event(ctx, r.copy_end);
-        if (r.owns_start) { give_event(ctx, r.start); give_event(ctx, r.start_done); }
+        if (!r.start_done) give_event(ctx, r.start);
         if (r.owns_end) give_event(ctx, r.end);
     }
     ctx->open_records.erase(ctx->open_records.begin(), ctx->open_records.begin() + (ptrdiff_t)count);
@@ -565,25 +563,6 @@ float rate_of(const bmgd_ctx* ctx, int64_t ahead)
     return ctx->lr_tab_host[(size_t)u];
 }
 
-// A run begins on `stream` with something other than a kernel that can carry its events.
-int begin_run(bmgd_ctx* ctx, hipStream_t stream)
-{
-    if (!ctx->run_start[0]) return BMGD_OK;
-    HIP_TRY(ctx, hipEventRecord(ctx->run_start[0], stream));
-    ctx->run_start[0] = ctx->run_start[1] = nullptr;
-    ctx->run_marked = true;
-    return BMGD_OK;
-}
-
-// The partitions of the coming passes in the moment form; a run's first kernel carries its start events (no marker between this buffer's
-// kernels and the last one's: 1.72 -> 1.54 ms per ten buffers of 100,000 rows x 3 passes at p = 100).
-hipError_t start_perm(bmgd_ctx* ctx, int32_t* out, int64_t rows, int nperm, const PermKeys& keys, hipStream_t stream)
-{
-    const hipError_t e = launch_perm(out, rows, nperm, keys, stream, ctx->subset, ctx->subset_limit, ctx->sync + 2, ctx->run_start[0], ctx->run_start[1]);
-    ctx->run_start[0] = ctx->run_start[1] = nullptr;
-    return e;
-}
-
 // The steps of a launch in the moment form, on the library's chain stream: the chain of eq. (3.1) step by step, or
 // (BMGD_CHAIN_PRODUCT) the steps multiplied together and applied once.
 hipError_t launch_steps(bmgd_ctx* ctx, const float* set, int64_t rows, int64_t n, int np, int perm_stride, hipEvent_t ev0,
@@ -657,7 +636,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
         hipEvent_t ev0 = take_event(ctx), ev1 = take_event(ctx);
         if (!ev0 || !ev1) return fail(ctx, BMGD_EHIP, "could not create events");
         if (ctx->fused) {
-            ctx->run_start[0] = ctx->run_start[1] = nullptr;      // (the launch's own events serve)
             const int frc = follow_theta(ctx, stream);
             if (frc != BMGD_OK) return frc;
             HIP_TRY(ctx, gram_launch_fused(static_cast<const float*>(x), static_cast<const float*>(y), keys, ctx->subset, ctx->subset_limit,
@@ -673,8 +651,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             continue;
         }
         if (ctx->chain == BMGD_CHAIN_GRAM && c.cache_moments && !ctx->subset) {
-            const int brc = begin_run(ctx, stream);
-            if (brc != BMGD_OK) return brc;
             // Fixed partitions: the moment matrices of buffer index b are the same in every iteration (Section 3.1.1),
             // so they are formed once and every later run over that buffer is the chain alone.
             bmgd_ctx::CachedMoments& ce = ctx->mcache[b];
@@ -718,12 +694,7 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             // set i is free once the chain that read it last has finished
             if (ctx->chain_pending[i]) HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->chain_done[i], 0));
             const bool draw = gram_moments_draw(c.p, rows, n);
-            if (draw) {
-                const int brc = begin_run(ctx, stream);
-                if (brc != BMGD_OK) return brc;
-            } else {
-                HIP_TRY(ctx, start_perm(ctx, ctx->gram_perm[i], rows, nperm, keys, stream));
-            }
+            if (!draw) HIP_TRY(ctx, launch_perm(ctx->gram_perm[i], rows, nperm, keys, stream, ctx->subset, ctx->subset_limit, ctx->sync + 2));
             // BMGD_CHAIN_PRODUCT (without cached matrices): the steps are multiplied in pairs right behind the moments
             // kernel, on the same stream (both fill the device; the chain, which keeps to one unit, overlaps the next
             // buffer's two), and the chain runs over the pairs.  Set i of the pairs is guarded like set i of the matrices.
@@ -756,9 +727,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             if (chunk_end) *chunk_end = ev1;
             continue;
         }
-        // (a marker in front costs less here than the events on the partition's dispatch: softmax_small 771 against 798 us)
-        const int brc = begin_run(ctx, stream);
-        if (brc != BMGD_OK) return brc;
         if (!fixed || t0 == 0)
             HIP_TRY(ctx, launch_perm(ctx->perm, rows, nperm, keys, stream, ctx->subset, ctx->subset_limit, ctx->sync + 2));
         if (c.model == BMGD_SOFTMAX) {
@@ -943,21 +911,24 @@ int64_t rows_of_run(bmgd_ctx* ctx, int64_t buffer_rows)
 // counts as not valid (the kernels already enqueued have updated it for part of the run) until it is set again.
 int abandon_run(bmgd_ctx* ctx, RunRecord& rec, int rc)
 {
-    give_event(ctx, rec.start); give_event(ctx, rec.start_done);
+    give_event(ctx, rec.start);
     if (rec.owns_end) give_event(ctx, rec.end);
-    rec.start = rec.start_done = rec.end = nullptr;
-    ctx->run_start[0] = ctx->run_start[1] = nullptr;
+    rec.start = rec.end = nullptr;
     ctx->poisoned = true;
     return rc;
 }
 
-// The events of a run that is about to be enqueued: its first kernel is to carry `start` and `start_done`.
-bool take_run_events(bmgd_ctx* ctx, RunRecord& rec)
+// A run begins on `s`: its events, the first of them recorded.  (Not in the fused form, where those of its launches serve and nothing
+// stands between runs.  Elsewhere a marker costs less than events on the dispatch of the partition, which comes first: 52 to 57 against
+// 57 to 73 us per buffer where the host is the bound (p = 20 to 128, 4 to 63 mini-batches), 149 against 153 for 100,000 rows x 3 passes at
+// p = 100; softmax_small 771 against 798 us.)
+int begin_run(bmgd_ctx* ctx, RunRecord& rec, hipStream_t s)
 {
-    rec.start = take_event(ctx); rec.start_done = take_event(ctx); rec.end = take_event(ctx);
-    ctx->run_start[0] = rec.start; ctx->run_start[1] = rec.start_done;
-    ctx->run_marked = false;
-    return rec.start && rec.start_done && rec.end;
+    rec.end = take_event(ctx);
+    if (!ctx->fused) rec.start = take_event(ctx);
+    if (!rec.end || (!ctx->fused && !rec.start)) return fail(ctx, BMGD_EHIP, "could not create events");
+    if (rec.start) HIP_TRY(ctx, hipEventRecord(rec.start, s));
+    return BMGD_OK;
 }
 
 // Everything of a run has been enqueued: `last` is the stop event of its last kernel (or NULL), its launches are those in open_chain
@@ -966,12 +937,9 @@ int end_run(bmgd_ctx* ctx, RunRecord& rec, hipStream_t s, hipEvent_t last, size_
 {
     if (last) { give_event(ctx, rec.end); rec.end = last; rec.owns_end = false; }
     else HIP_TRY(ctx, hipEventRecord(rec.end, s));
-    if (ctx->run_marked) { give_event(ctx, rec.start_done); rec.start_done = nullptr; }
     if (ctx->fused) {
-        give_event(ctx, rec.start); give_event(ctx, rec.start_done);
         rec.start = ctx->open_chain[chain0].first;
         rec.start_done = ctx->open_chain[chain0].second;
-        rec.owns_start = false;
     }
     return BMGD_OK;
 }
@@ -1248,8 +1216,8 @@ BMGD_API int bmgd_run_buffer(bmgd_ctx* ctx, void* compute_stream)
     const int64_t run_rows = rows_of_run(ctx, slot.rows);
     if (run_rows == 0) return BMGD_EINVAL;
     RunRecord rec = ctx->pending_copy;
-    if (!take_run_events(ctx, rec)) return fail(ctx, BMGD_EHIP, "could not create events");
     HIP_TRY(ctx, hipStreamWaitEvent(s, slot.copy_done, 0));       // never read a slot that is still filling
+    if (const int brc = begin_run(ctx, rec, s)) return brc;
     hipEvent_t last = nullptr;
     const size_t chain0 = ctx->open_chain.size(), prep0 = ctx->open_prep.size();
     const int rc = enqueue_compute(ctx, slot.x, slot.y, run_rows, s, &last);
@@ -1286,8 +1254,8 @@ static int run_adaptive(bmgd_ctx* ctx, hipStream_t s, hipStream_t cs, const void
     if (run_rows == 0) return BMGD_EINVAL;
     RunRecord rec = ctx->pending_copy;
     ctx->pending_copy = RunRecord();
-    if (!take_run_events(ctx, rec)) return fail(ctx, BMGD_EHIP, "could not create events");
     HIP_TRY(ctx, hipStreamWaitEvent(s, slot.copy_done, 0));
+    if (const int brc = begin_run(ctx, rec, s)) return brc;
     const size_t chain0 = ctx->open_chain.size(), prep0 = ctx->open_prep.size();
     ctx->last_compute = s;
     ctx->used_compute = true;
@@ -1348,7 +1316,7 @@ static int run_adaptive(bmgd_ctx* ctx, hipStream_t s, hipStream_t cs, const void
                 ctx->pending = next_slot;
             } else {
                 ctx->pending_copy = rec;                 // still the loaded buffer, with its copy events
-                ctx->pending_copy.start = ctx->pending_copy.start_done = ctx->pending_copy.end = nullptr;
+                ctx->pending_copy.start = ctx->pending_copy.end = nullptr;
             }
             return abandon_run(ctx, rec, rc);
         }
@@ -1406,7 +1374,7 @@ static int run_resident(bmgd_ctx* ctx, const void* dev_x, const void* dev_y, int
     const int64_t run_rows = rows_of_run(ctx, rows);
     if (run_rows == 0) return BMGD_EINVAL;
     RunRecord rec;
-    if (!take_run_events(ctx, rec)) return fail(ctx, BMGD_EHIP, "could not create events");
+    if (const int brc = begin_run(ctx, rec, s)) return brc;
     hipEvent_t last = nullptr;
     const size_t chain0 = ctx->open_chain.size(), prep0 = ctx->open_prep.size();
     const int rc = enqueue_compute(ctx, dev_x, dev_y, run_rows, s, &last);

@@ -33,8 +33,7 @@ int perm_half_width(int64_t rows);
 // subset != NULL: out[pass][j] = subset[PERM(...)[j]] (a partition of the rows subset[0 .. rows) of a buffer of `limit`
 // rows); an entry outside [0, limit) is replaced by 0 and *bad is set to 1.
 hipError_t launch_perm(int32_t* out, int64_t rows, int npass, const PermKeys& keys, hipStream_t stream,
-                       const int32_t* subset = nullptr, int64_t limit = 0, unsigned* bad = nullptr, hipEvent_t start = nullptr,
-                       hipEvent_t stop = nullptr);
+                       const int32_t* subset = nullptr, int64_t limit = 0, unsigned* bad = nullptr);
 
 // Device: zero `bytes` bytes at dst (both multiples of 16) with a kernel, in stream order.
 hipError_t launch_fill_zero(void* dst, size_t bytes, hipStream_t stream);

@@ -5,8 +5,6 @@
 // index arrays are reproducible bit for bit.  Mini-batch m is perm[(m-1) n : min(m n, rows)).
 #include "perm_device.h"
 
-#include <hip/hip_ext.h>
-
 #include <algorithm>
 
 namespace bmgd {
@@ -133,14 +131,14 @@ int perm_half_width(int64_t rows)
 }
 
 hipError_t launch_perm(int32_t* out, int64_t rows, int npass, const PermKeys& keys, hipStream_t stream, const int32_t* subset,
-                       int64_t limit, unsigned* bad, hipEvent_t start, hipEvent_t stop)
+                       int64_t limit, unsigned* bad)
 {
     if (rows <= 0 || npass <= 0) return hipSuccess;
     if (npass > kMaxPassesPerLaunch || rows > (int64_t(1) << 30)) return hipErrorInvalidValue;
     if (subset && (!bad || limit < rows || limit > (int64_t(1) << 30))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((rows + 255) / 256), (unsigned)npass);
-    hipExtLaunchKernelGGL(perm_kernel, grid, dim3(256), 0u, stream, start, stop, 0u, out, (uint32_t)rows,
-                          (uint32_t)perm_half_width(rows), keys, subset, (uint32_t)limit, bad);
+    hipLaunchKernelGGL(perm_kernel, grid, dim3(256), 0, stream, out, (uint32_t)rows,
+                       (uint32_t)perm_half_width(rows), keys, subset, (uint32_t)limit, bad);
     return hipGetLastError();
 }
 
