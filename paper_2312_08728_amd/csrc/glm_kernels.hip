@@ -25,7 +25,6 @@
 #include "bmgd_internal.h"
 #include "glm_device.h"
 
-#include <hip/hip_ext.h>
 #include <stdio.h>
 
 #include <algorithm>
@@ -785,19 +784,19 @@ hipError_t glm_prepare(GlmLaunchShape* s)
     return hipSuccess;
 }
 
-hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream, hipEvent_t start, hipEvent_t stop)
+hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream)
 {
     if (s.split) {
         if (s.G < 8 || s.G > s.max_G) return hipErrorInvalidValue;
         GlmArgs a = args;
         a.single_step = -1;
-        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, a, stream, start, stop);
+        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, a, stream);
     }
     if (s.narrow) {
         if (s.G > s.max_G) return hipErrorInvalidValue;
         GlmArgs a = args;
         a.single_step = -1;
-        return glm_narrow_launch(s, a, stream, start, stop);
+        return glm_narrow_launch(s, a, stream);
     }
     KernelFn fn = pick_kernel(s);
     if (!fn || s.G < 1 || s.G > s.max_G) return hipErrorInvalidValue;
@@ -807,7 +806,7 @@ hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStr
     // so all of them become resident as soon as compute units are free, and each device-side wait is
     // bounded anyway.  (The runtime's cooperative-launch path is avoided: it brings nothing more here and
     // its dedicated queue does not tear down cleanly under the profiler.)
-    hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(s.block), (uint32_t)s.lds_bytes, stream, start, stop, 0u, a);
+    hipLaunchKernelGGL(fn, dim3(s.G), dim3(s.block), s.lds_bytes, stream, a);
     return hipGetLastError();
 }
 

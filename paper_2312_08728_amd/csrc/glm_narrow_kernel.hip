@@ -23,8 +23,6 @@
 // Odd rows in two trips take twelve as well.
 #include "glm_exchange.h"
 
-#include <hip/hip_ext.h>
-
 #include <algorithm>
 
 namespace bmgd {
@@ -331,7 +329,7 @@ hipError_t glm_narrow_prepare(const GlmLaunchShape& s, int p, int* max_groups)
     return hipSuccess;
 }
 
-hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream, hipEvent_t start, hipEvent_t stop)
+hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream)
 {
     KernelFn fn = narrow_kernel(s);
     const int64_t slots = (int64_t)s.G * s.narrow_rw * (64 / s.L);
@@ -344,7 +342,7 @@ hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipSt
     if (one_trip ? s.narrow_rw == kRowWaves || args.p > kNarrowOneTripMaxP || s.G < 1
                  : s.G < 8 || s.G % 8 != 0 || (s.narrow_rw != kRowWaves && s.V != 1))
         return hipErrorInvalidValue;
-    hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), (uint32_t)narrow_lds_bytes(s, args.p), stream, start, stop, 0u, args);
+    hipLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), narrow_lds_bytes(s, args.p), stream, args);
     return hipGetLastError();
 }
 
