@@ -222,7 +222,7 @@ bool valid_config(const bmgd_config& c, std::string* why)
     if (c.model != BMGD_SOFTMAX) {
         GlmLaunchShape s;
         char msg[160];
-        if (!glm_plan(c.p, c.batch_n, c.n_workgroups, kMaxGroups, &s, msg, sizeof msg)) {
+        if (!glm_plan(c.p, c.batch_n, c.n_workgroups, kMaxGroups, c.chain != BMGD_CHAIN_LAUNCH, &s, msg, sizeof msg)) {
             *why = msg;
             return false;
         }
@@ -1141,7 +1141,7 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
         if (ctx->chain == BMGD_CHAIN_GRAPH && !ctx->sm_chain) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
     } else {
         char msg[160];
-        if (!glm_plan(cfg->p, cfg->batch_n, cfg->n_workgroups, ctx->num_cus, &ctx->shape, msg, sizeof msg)) {
+        if (!glm_plan(cfg->p, cfg->batch_n, cfg->n_workgroups, ctx->num_cus, cfg->chain != BMGD_CHAIN_LAUNCH, &ctx->shape, msg, sizeof msg)) {
             ctx->err = msg;
             return bail(BMGD_EINVAL);
         }

@@ -647,7 +647,7 @@ constexpr int64_t kRedundantMaxWords = 4096;
 
 }  // namespace
 
-bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape* out, char* why, size_t why_len)
+bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persistent, GlmLaunchShape* out, char* why, size_t why_len)
 {
     GlmLaunchShape s{};
     s.V = (p % 4 == 0) ? 4 : (p % 2 == 0) ? 2 : 1;
@@ -682,12 +682,14 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
     const int L = std::max(s.L, 4);                  // (that kernel's lanes work out residuals in fours)
     auto rows_held = [&](int rw, int groups) { return s.CPL < 8 ? glm_narrow_rows_in_flight(s.V, s.CPL, L, rw, groups, n) : 0; };
     if (requested_G <= 0 && p <= kNarrowOneTripMaxP) {
-        // Left to choose: one workgroup if it holds a step's rows (no exchange: 1.9 us per update at p = 30, n = 200, 2.5 to 2.7 on two
-        // to eight), and not more than 32 for rows of up to 128 floats (one trip: 2.9 us at p = 128, n = 1024; 43 workgroups in two
-        // trips 3.2; 2.9 against 3.0 at p = 50, n = 3000; with eight rows per lane slot they gather for longer than two trips take:
-        // 3.8 against 3.3 at p = 90, n = 2500).  More rows than those hold need more workgroups.
+        // Left to choose: one workgroup if it holds a step's rows (no exchange: with as many rows as it can hold 1.6 to 2.2 us per update
+        // at p = 4 to 63 and 1.1 to 1.5 at p = 64 to 512, against 2.2 to 2.9 on two to sixteen; the general kernel, which steps launched
+        // one by one keep to, has no such gain: 209 against 176 us for 16 of them at p = 16, n = 768), and not more than 32 for rows of up to
+        // 128 floats (one trip: 3.1 us at p = 128, n = 1536, 3.4 on 64 workgroups in two trips; 3.1 against 3.2 at p = 50, n = 3072; with
+        // eight rows per lane slot they gather for longer than two trips take: 4.0 against 3.5 at p = 90, n = 2304; launched step by step
+        // 312 against 576 us for 16 at p = 128, n = 3000, with 120).  More rows than those hold need more workgroups.
         const int held = rows_held(kNarrowMoreRows, 32);
-        if (rows_held(kNarrowMoreRows, 1) > 0) G = 1;
+        if (persistent && rows_held(kNarrowMoreRows, 1) > 0) G = 1;
         else if (G > 32 && 32 * p <= kRedundantMaxWords && held > 0 && held <= 4) G = 32;
     }
     const bool few_sums = (int64_t)G * p <= kRedundantMaxWords;
@@ -695,12 +697,12 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, GlmLaunchShape
         const int rw = few_sums || s.V == 1 ? kNarrowMoreRows : 8;
         const int Gn = few_sums ? G : G & ~7;
         const int pf = rows_held(rw, Gn);
-        if (pf > 0) {
+        if (pf > 0 && (persistent || s.V >= 2)) G = Gn;
+        if (pf > 0 && persistent) {
             s.narrow = 1;
             s.narrow_pf = pf;
             s.narrow_rw = rw;
             s.L = L;
-            G = Gn;
         }
     }
     s.G = G;

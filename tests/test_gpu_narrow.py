@@ -155,3 +155,16 @@ def test_one_trip_and_odd_rows_against_the_oracle(model, p, n, G, N0, optimizer)
     assert rel_l2(got, ref.theta) <= TOL
     again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
     assert np.array_equal(got, again)
+
+
+@pytest.mark.parametrize("p,n,launched", [(16, 768, 4), (30, 384, 4), (64, 96, 2), (15, 96, 1)])
+def test_one_workgroup_is_chosen_for_the_chain_kernel_alone(p, n, launched):
+    """Shapes whose step one workgroup of the chain's kernel holds: steps launched one by one keep 12 KB of rows a workgroup."""
+    import paper_2312_08728_amd as B
+    w = _case(wl.LOGISTIC, 3 * n, p, 2 * n, n, T=2, R=1, alpha=0.05)
+    X, y = wl.dataset(w)
+    want = oracle_run(w, X, y)
+    for chain, G in ((B.BMGD_CHAIN_PERSISTENT, 1), (B.BMGD_CHAIN_LAUNCH, launched)):
+        got, st = gpu_run(w, X, y, chain=chain)
+        assert st.chain == chain and st.n_workgroups == G
+        assert rel_l2(got, want) <= TOL
