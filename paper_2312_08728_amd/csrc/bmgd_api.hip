@@ -241,12 +241,12 @@ bool wants_softmax_chain(const bmgd_config& c)
 }
 
 // The moment form left to the library, with few features and few, small mini-batches: partitions, matrices and chain in one kernel.
-// It takes precedence over the products, whose halved chain saves less there than their kernels cost.
+// It takes precedence over the products.
 bool wants_fused(const bmgd_config& c)
 {
     // (fixed partitions keep to the kernels that cached matrices are made with: the same bits with and without a cache)
     return c.chain == BMGD_CHAIN_AUTO && gram_eligible(c.model, c.p, c.batch_n) && c.reshuffle == BMGD_RESHUFFLE_PER_PASS &&
-           gram_fused_eligible(c.p, c.buffer_n, c.batch_n);
+           gram_fused_eligible(c.p, c.buffer_n, c.batch_n, c.passes, c.optimizer == BMGD_OPT_SGD);
 }
 
 // BMGD_CHAIN_PRODUCT, asked for or picked: BMGD_CHAIN_AUTO takes it for plain steps of least squares in the moment form

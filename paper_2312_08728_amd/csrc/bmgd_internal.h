@@ -209,7 +209,8 @@ hipError_t gram_launch_chain_steps(const float* gram, float* theta, int p, int n
                                    hipEvent_t stop);
 // Few features and few, small mini-batches: partitions, moment matrices and chain of a launch in one kernel (gram_fused_kernel.hip).
 // `gram`: room for npass * ceil(rows / n) sets of matrices; `ticket`: zero before the first launch, left so; subset as in launch_perm.
-bool gram_fused_eligible(int64_t p, int64_t buffer_n, int64_t batch_n);
+// passes: of a run; plain: steps without state.
+bool gram_fused_eligible(int64_t p, int64_t buffer_n, int64_t batch_n, int64_t passes, bool plain);
 hipError_t gram_launch_fused(const float* X, const float* y, const PermKeys& keys, const int32_t* subset, int64_t limit, unsigned* bad,
                              float* gram, float* theta, unsigned* ticket, int rows, int p, int n, int npass, float alpha,
                              const float* lr_tab, int lr_base, int lr_len, const OptArgs& opt, hipStream_t stream, hipEvent_t start,

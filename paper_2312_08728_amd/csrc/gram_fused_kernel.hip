@@ -228,13 +228,26 @@ FusedFn fused_kernel(const GramLayout& L, int kind)
 
 }  // namespace
 
-bool gram_fused_eligible(int64_t p, int64_t buffer_n, int64_t batch_n)
+bool gram_fused_eligible(int64_t p, int64_t buffer_n, int64_t batch_n, int64_t passes, bool plain)
 {
     const int64_t M = (buffer_n + batch_n - 1) / batch_n;
     // A launch of four passes at most.  A mini-batch is one workgroup's, so it must be short; and all rows together few enough that the
     // moments of a buffer need not overlap the chain of the one before.
-    return p <= kFusedMaxP && batch_n <= kFusedMaxBatch && kMaxPassesPerLaunch * M <= kFusedMaxSteps &&
-           kMaxPassesPerLaunch * buffer_n * p * 4 <= (int64_t(1) << 24);
+    if (p > kFusedMaxP || batch_n > kFusedMaxBatch || kMaxPassesPerLaunch * M > kFusedMaxSteps ||
+        kMaxPassesPerLaunch * buffer_n * p * 4 > (int64_t(1) << 24))
+        return false;
+    // Plain steps can be multiplied in pairs by separate kernels, which halves the chain; those kernels take 45 to 60 us a buffer however
+    // few the steps (the host is the bound), this one 15 us and 0.1 to 0.25 us a step.  us per buffer of this one / of the others, 2 p
+    // rows a mini-batch, where buffers follow one another (one that is waited for takes 30 us more here, 40 to 50 more there):
+    //   steps      130       160       200       252       300       360       500       1000
+    //   p = 10   27 / 50   30 / 50   34 / 56   42 / 53   47 / 52   53 / 50   69 / 48   125 / 71
+    //   p = 31   35 / 46   38 / 48   43 / 48   52 / 48   64 / 49   71 / 50
+    //   p = 47   42 / 49   48 / 47   59 / 48   68 / 50   80 / 50   91 / 56
+    //   p = 63   50 / 59   59 / 59   69 / 58   81 / 58   95 / 59  108 / 63
+    // With state the alternative is the chain step by step: as fast or up to a tenth faster from 250 steps on where buffers follow one
+    // another (p = 5, 500 steps: 70 against 75 us), a fifth slower for a buffer that is waited for (129 against 107 us).
+    const int64_t steps = std::min<int64_t>(kMaxPassesPerLaunch, passes) * M;
+    return !plain || steps <= (p <= 32 ? 256 : p <= 48 ? 160 : 128);
 }
 
 hipError_t gram_launch_fused(const float* X, const float* y, const PermKeys& keys, const int32_t* subset, int64_t limit, unsigned* bad,

@@ -55,14 +55,44 @@ def test_layouts_and_rules(p, kind):
     assert rel_l2(got, want) <= 1e-4
 
 
-@pytest.mark.parametrize("N0,n,T", [(126, 2, 4),         # one-row shares, most steps a wavefront's rows are few for
-                                    (504, 2, 4),         # 1,008 steps in a launch: the most
-                                    (512, 512, 1),       # one mini-batch of the largest size: 64 rows a wavefront
-                                    (1030, 511, 3),      # 64 and 63 rows a wavefront; a last mini-batch of 8 rows
-                                    (521, 260, 2)])      # 36 rows: a second request of four rows; a last mini-batch of one row
-def test_shapes(N0, n, T):
-    got, want, st = _run(1, N0=N0, n=n, T=T, kind=0)
+@pytest.mark.parametrize("N0,n,T,kind", [(126, 2, 4, 0),      # one-row shares, most steps a wavefront's rows are few for
+                                         (504, 2, 4, 1),      # 1,008 steps in a launch: the most (with state)
+                                         (512, 512, 1, 0),    # one mini-batch of the largest size: 64 rows a wavefront
+                                         (1030, 511, 3, 0),   # 64 and 63 rows a wavefront; a last mini-batch of 8 rows
+                                         (521, 260, 2, 0)])   # 36 rows: a second request of four rows; a last mini-batch of one row
+def test_shapes(N0, n, T, kind):
+    got, want, st = _run(1, N0=N0, n=n, T=T, kind=kind)
     assert st.prep_launches == 0 and rel_l2(got, want) <= 1e-4
+
+
+@pytest.mark.parametrize("p,most", [(1, 256), (32, 256), (33, 160), (48, 160), (49, 128), (63, 128)])
+def test_plain_steps_up_to_where_products_are_faster(p, most):
+    """At the line and one mini-batch beyond it, by mini-batches and by passes."""
+    n = 2 * p
+    for M, T in ((most // 4, 4), (most // 4 + 1, 4), (most // 2, 2), (most // 2 + 1, 2)):
+        got, want, st = _run(p, N0=M * n, n=n, T=T, kind=0)
+        assert (st.prep_launches == 0) == (M * T <= most) and rel_l2(got, want) <= 1e-4
+
+
+def test_more_passes_than_the_context_was_made_with():
+    """The form is chosen for the passes of the context; a run of more of them fits its workspace (1,000 steps in a launch)."""
+    import torch
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    p, n, N0 = 3, 8, 2000
+    w = wl.CONFIGS["cfg2"].scaled(name="case", N=N0, p=p, N0=N0, n=n, T=1, R=1, x_cov="identity")
+    X, y = wl.dataset(w)
+    ctx, ref = B.Context(p, N0, n, 0.01, 1, model=w.model), O.BMGD(w.model, p, n, 0.01, 1)
+    xd, yd = torch.from_numpy(X).cuda(), torch.from_numpy(y).cuda()
+    torch.cuda.synchronize()
+    for T in (1, 4, 5):
+        ctx.set_passes(T)
+        ref.T = T
+        ctx.run_device_buffer(xd, yd, N0)
+        ref.run_buffer(X, y)
+    got, st = ctx.get_theta(), ctx.stats()
+    ctx.close()
+    assert st.prep_launches == 0 and st.chain_launches == 4 and rel_l2(got, ref.theta) <= 1e-4
 
 
 def test_beyond_the_rule_other_kernels_run():
