@@ -431,6 +431,12 @@ DirectFn direct_kernel(int NT)
 // By the mini-batches of one pass, so that a pass gives the same bits whatever it is launched with.
 bool direct_moments(int p, int M) { return p <= 47 && M >= 64; }
 
+// Two workgroups for a mini-batch, by rows, while a launch is a few rounds of workgroups (two per compute unit) at most, if the mini-batch is
+// long: for a short one the second trip through memory costs more than the rows it spreads.  us of a buffer waited for, three passes, one /
+// two workgroups: 236 / 254 (p = 37, n = 74, 511 mini-batches), 159 / 171 (256), 122 / 122 (p = 33, n = 500, 128), 137 / 131 (n = 1000, 128),
+// 195 / 207 (p = 47, n = 1000, 256), 202 / 191 (p = 33, n = 1500, 192), 198 / 175 (n = 3000, 128), 410 / 391 (384).
+int direct_split(int M, int n) { return n >= (M <= 160 ? 768 : 1024) && M < 512 ? 2 : 1; }
+
 // tiles per workgroup for NT tile rows: {few workgroups, many workgroups}
 void tile_split(int ntiles, int wgs_per_split, int* tsplit, int* tpw)
 {
@@ -546,8 +552,7 @@ hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* pe
         a.subset = from.subset; a.limit = (uint32_t)from.limit; a.bad = from.bad;
         a.out = gram; a.tickets = tickets; a.L = L;
         a.rows = rows; a.n = n; a.perm_stride = perm_stride; a.M = M; a.dense_q = dense_q;
-        // Two workgroups per mini-batch while a launch is a few rounds of workgroups (two per compute unit) at most
-        const int S = M < 512 ? 2 : 1;
+        const int S = direct_split(M, n);
         DirectFn fn = S == 2 ? direct_kernel<2>((p + 1 + 15) / 16) : direct_kernel<1>((p + 1 + 15) / 16);
         if (!fn || (S == 2 && !tickets)) return hipErrorInvalidValue;
         hipExtLaunchKernelGGL(fn, dim3((unsigned)(M * gpass * S)), dim3(64 * kDirectWaves), 0u, stream, start, stop, 0u, a);

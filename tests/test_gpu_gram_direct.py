@@ -14,10 +14,11 @@ def _case(p, N0, n, T, R=1):
 
 
 @pytest.mark.parametrize("chain", [3, 5])            # the chain's layout, and dense for the products
+@pytest.mark.parametrize("n", [101, 773])            # one workgroup per mini-batch, and two
 @pytest.mark.parametrize("p", [1, 2, 15, 16, 17, 31, 32, 46, 47])
-def test_tile_edges_against_the_oracle(p, chain):
-    """65 mini-batches of 101 rows (shares of 16 rows, the last ones short) and one of 3; a second buffer of 5 rows less."""
-    w = _case(p, 65 * 101 + 3, 101, 2)
+def test_tile_edges_against_the_oracle(p, n, chain):
+    """65 mini-batches (shares of 28 and 100 rows, the last ones short) and one of 3 rows; a second buffer of 5 rows less."""
+    w = _case(p, 65 * n + 3, n, 2)
     X, y = wl.dataset(w)
     got, st = gpu_run(w, X, y, chain=chain)
     assert st.chain == chain and rel_l2(got, oracle_run(w, X, y)) <= 1e-4
@@ -25,10 +26,14 @@ def test_tile_edges_against_the_oracle(p, chain):
     assert np.array_equal(got, again)                # whichever workgroup comes first
 
 
-@pytest.mark.parametrize("p,N0,n", [(20, 64 * 40, 40),        # the fewest mini-batches; shares of 8 rows
+@pytest.mark.parametrize("p,N0,n", [(20, 64 * 40, 40),        # the fewest mini-batches; shares of 12 rows
                                     (20, 63 * 40, 40),        # one fewer: the staged kernel
-                                    (7, 512 * 15, 15),        # one workgroup per mini-batch
-                                    (7, 511 * 15, 15),        # two; shares of 4 rows, half of the wavefronts without any
+                                    (7, 511 * 15, 15),        # shares of 4 rows
+                                    (20, 64 * 10, 10),        # and a wavefront without any
+                                    (7, 160 * 768, 768),      # two workgroups per mini-batch (96 rows a share)
+                                    (7, 161 * 768, 768),      # one
+                                    (7, 161 * 1024, 1024),    # two
+                                    (3, 512 * 1024, 1024),    # one: so many mini-batches fill the device
                                     (30, 64 * 2100, 2100)])   # shares of 264 rows: several times 64 entries of the partition
 def test_shapes_against_the_oracle(p, N0, n):
     w = _case(p, N0, n, 2)
