@@ -181,8 +181,8 @@ size_t gram_bytes_per_batch(int64_t p);
 int gram_chain_threads(int64_t p);
 // Moment matrices of all mini-batches of `npass` passes (partitions at perm + pass * perm_stride) into `gram`.
 // `start` and `stop` (each may be NULL) are completed by the kernel's own dispatch, here and below.
-// With gram_moments_draw(p, rows, n) `perm` may be NULL: the entries of the partitions are worked out from `from` on the way.  `tickets`: two
-// words per mini-batch and wavefront of a workgroup (gram_ticket_bytes each), zero before the first launch, left so.
+// With gram_moments_draw(p, rows, n) the entries of the partitions are worked out from `from` on the way, and `perm` is not looked at.
+// `tickets`: two words per mini-batch and wavefront of a workgroup (gram_ticket_bytes each), zero before the first launch, left so.
 struct GramPartition {
     PermKeys keys;
     const int32_t* subset;      // as in launch_perm

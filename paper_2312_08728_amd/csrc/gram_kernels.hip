@@ -207,22 +207,22 @@ __global__ void __launch_bounds__(1024) gram_chain_kernel(const float* __restric
                                                                                  lr_len, nullptr, opt);
 }
 
-// The same matrices with the rows gathered straight into matrix operands, for up to 47 features and launches with mini-batches enough to
-// fill the device.
+// The same matrices with the rows gathered straight into matrix operands, for up to 47 features and 64 mini-batches a pass or more.
 //
 // With A = rows' and B = rows a lane's element of both operands is the same, so 16 columns of four rows are one load per lane and serve a
 // whole row and column of tiles: no way through shared memory, and a wavefront keeps ALL tiles of its rows' matrix in registers.  What
-// bounds it is the gather of short rows.  A mini-batch is split over S workgroups by rows, so that few mini-batches fill the device too; the
-// second of two workgroups to finish adds the first one's sums, which it finds where the result goes (a + b = b + a: the same bits
-// whichever comes first).  Rows are requested one stage (U groups of four rows) ahead.  The entries of the partition are worked out here
-// unless `perm` is given, 64 at a time per wavefront: the partition's own kernel and what lies behind it are 10 to 16 us per buffer.
-// us per buffer, wall clock, staged kernel with partitions from memory / this one: 127 / 59 (p = 10, n = 5,000, 100 mini-batches), 86 / 73
-// (p = 10, n = 1,000, 400), 175 / 157 (p = 20, n = 300, 2,000), 68 / 66 (p = 37, n = 600, 300).  Not with more features: from five tile rows on
-// its loads and matrix instructions do not overlap as they should (p = 64: 53 / 86 us of kernel, p = 100: 90 / 136).
+// bounds it is the gather of short rows.  A mini-batch may be split over S = 2 workgroups by rows (direct_split), so that a few long ones fill
+// the device too; the second of two workgroups to finish adds the first one's sums, which it finds where the result goes (a + b = b + a: the
+// same bits whichever comes first).  Rows are requested one stage (U groups of four rows) ahead.  The entries of the partition are worked
+// out here, 64 at a time per wavefront: the partition's own kernel and what lies behind it are 10 to 16 us per buffer.
+// us per buffer of three passes, products behind it, staged kernel with partitions from memory / this one (p, n, mini-batches): 143 / 78
+// (5, 5000, 128), 111 / 98 (10, 20, 511), 127 / 115 (20, 300, 511), 79 / 75 (20, 1000, 256), 285 / 208 (20, 5000, 256), 80 / 72 (33, 1500,
+// 128), 95 / 97 (33, 300, 256), 93 / 91 (40, 80, 256), 104 / 101 (47, 94, 256), 138 / 108 (47, 3000, 128).  Not with more features: from
+// five tile rows on its loads and matrix instructions do not overlap as they should (p = 64: 53 / 86 us of kernel, p = 100: 90 / 136); four
+// tile rows (p = 48 to 63) were not built.
 struct DirectArgs {
     const float* X;
     const float* y;
-    const int32_t* perm;                             // [pass][perm_stride], or NULL: from the keys
     PermKeys keys;
     uint32_t h;
     const int32_t* subset;
@@ -231,7 +231,7 @@ struct DirectArgs {
     float* out;
     unsigned* tickets;                               // S = 2: [n_items][4], zero between launches
     GramLayout L;
-    int rows, n, perm_stride, M, dense_q;
+    int rows, n, M, dense_q;
 };
 
 constexpr int kDirectWaves = 4;
@@ -257,7 +257,6 @@ __global__ void __launch_bounds__(64 * kDirectWaves, 2) gram_direct_kernel(Direc
     KeyRow key;
 #pragma unroll
     for (int i = 0; i < kPermRounds; ++i) key.k[i] = a.keys.key[pass][i];
-    const int* idx_base = a.perm + (size_t)pass * (size_t)a.perm_stride + (size_t)m * (size_t)a.n;
 
     floatx4 acc[TILES];
 #pragma unroll
@@ -269,14 +268,11 @@ __global__ void __launch_bounds__(64 * kDirectWaves, 2) gram_direct_kernel(Direc
     float yv = 0.f, y_use = 0.f;                     // and its response; of the 64 that are being used
     auto entries = [&](int r0) {                     // rows r0 .. r0 + 63 of this wavefront (clamped)
         const int j = min(r0 + lane, r_end - 1);
-        if (a.perm) idx = (uint32_t)idx_base[j];
-        else {
-            idx = perm_entry((uint32_t)(m * a.n + j), key, a.h, (uint32_t)a.rows);
-            if (a.subset) {
-                const uint32_t v = (uint32_t)a.subset[idx];
-                if (v >= a.limit) __hip_atomic_store(a.bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                idx = v < a.limit ? v : 0u;
-            }
+        idx = perm_entry((uint32_t)(m * a.n + j), key, a.h, (uint32_t)a.rows);
+        if (a.subset) {
+            const uint32_t v = (uint32_t)a.subset[idx];
+            if (v >= a.limit) __hip_atomic_store(a.bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            idx = v < a.limit ? v : 0u;
         }
         yv = a.y[idx];
     };
@@ -548,10 +544,10 @@ hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* pe
     const int gpass = perm_stride == 0 ? 1 : npass;      // one partition for all passes: one set of matrices
     if (direct_moments(p, M)) {
         DirectArgs a{};
-        a.X = X; a.y = y; a.perm = perm; a.keys = from.keys; a.h = (uint32_t)perm_half_width(rows);
+        a.X = X; a.y = y; a.keys = from.keys; a.h = (uint32_t)perm_half_width(rows);
         a.subset = from.subset; a.limit = (uint32_t)from.limit; a.bad = from.bad;
         a.out = gram; a.tickets = tickets; a.L = L;
-        a.rows = rows; a.n = n; a.perm_stride = perm_stride; a.M = M; a.dense_q = dense_q;
+        a.rows = rows; a.n = n; a.M = M; a.dense_q = dense_q;
         const int S = direct_split(M, n);
         DirectFn fn = S == 2 ? direct_kernel<2>((p + 1 + 15) / 16) : direct_kernel<1>((p + 1 + 15) / 16);
         if (!fn || (S == 2 && !tickets)) return hipErrorInvalidValue;

@@ -1,5 +1,5 @@
 """The moment matrices of up to 47 features formed straight from gathered rows (64 mini-batches a pass or more): tile and row-share edges,
-partitions from memory and worked out on the way, one and two workgroups per mini-batch.  fp32 sums, as in the other tests of this form: 1e-4."""
+entries of the partition worked out on the way, one and two workgroups per mini-batch.  fp32 sums, as in the other tests of this form: 1e-4."""
 import numpy as np
 import pytest
 
