@@ -23,7 +23,7 @@
 //     die's L2 without leaving it, other than atomics, do not exist in this mode of the hardware.)
 //
 // Waits: row wavefronts only ever wait on shared-memory flags (which the exchange wavefront always releases, also
-// when it gives up); the exchange wavefront's polls are bounded by the wall clock (PollGuard).
+// when it gives up); the exchange wavefront's polls are bounded by the wall clock (ExchangeCommon::go_on).
 #include "glm_exchange.h"
 
 #include <algorithm>
@@ -71,7 +71,6 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     const int G = gridDim.x;
     const int g = blockIdx.x;
     const int p = a.p;
-    const int pp = (p + 15) & ~15;
     lds_f32* th = (lds_f32*)smem;                    // [2][P_PAD]: theta, by version parity
     // (pointers into shared memory carry its address space, so that accesses through them are shared-memory
     // instructions and are counted apart from the row loads)

@@ -9,7 +9,7 @@
 //
 // Per buffer, wall clock among others, before (three kernels) / now: 49 / 23 us at p = 10, n = 100, 2,000 rows x 2 passes (kernel 12 us: rows
 // 4, to memory and the ticket 3, chain of 40 steps 5); 72 / 57 us at p = 37, n = 300, 20,011 rows x 2 passes with NAG and a table of rates
-// (kernel 41 us: rows 9, staged 14, chain of 134 steps 25; what lies between kernels that carry events is 9 us).
+// (kernel 41 us, 25 of them the chain of 134 steps; what lies between kernels that carry events is 9 us).
 #include "gram_chain.h"
 #include "perm_device.h"
 

@@ -1,6 +1,6 @@
-// The generator of the seeded partitions, for the kernel that writes them out (perm_kernel.hip) and the one that needs an entry at a
-// time (gram_fused_kernel.hip): a keyed 8-round balanced Feistel network on 2 h bits (2^(2h) < 4 * rows) restricted to [0, rows) by
-// cycle walking, in uint32 arithmetic only.
+// The generator of the seeded partitions, for the kernel that writes them out (perm_kernel.hip) and those that work out the entries they
+// need (gram_fused_kernel.hip, gram_direct_kernel in gram_kernels.hip): a keyed 8-round balanced Feistel network on 2 h bits
+// (2^(2h) < 4 * rows) restricted to [0, rows) by cycle walking, in uint32 arithmetic only.
 #pragma once
 
 #include "bmgd_internal.h"
