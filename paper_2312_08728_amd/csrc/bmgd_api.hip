@@ -863,7 +863,10 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             a.s_begin = 0;
             a.s_end = (int)nsteps;
             ctx->tag_epoch += (uint32_t)nsteps;
-            HIP_TRY(ctx, glm_launch_chain(ctx->shape, a, stream));
+            // A marker in front, the stop event on the dispatch.  us per run of n = 1,000, p = 200 and four updates / of n = 500, p = 50 and
+            // 20 updates in two launches, runs following one another: 31 / 87 (a marker behind as well: 32 / 89; both events on the
+            // dispatch: 31 / 86); waited for one by one: 46 / 107 (45 / 103; 55 / 111: a dispatch with a start event costs the host 10 us).
+            HIP_TRY(ctx, glm_launch_chain(ctx->shape, a, stream, ev1));
         } else {
             for (int64_t s = 0; s < (int64_t)np * M; ++s) {
                 a.single_step = (int)s;
@@ -874,12 +877,9 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                 const int nb = (int)std::min<int64_t>(n, rows - m * n);
                 HIP_TRY(ctx, glm_launch_step(ctx->shape, a, nb, stream));
             }
+            HIP_TRY(ctx, hipEventRecord(ev1, stream));
         }
-        // Markers around the launches, the second of which is the run's end as well.  (Events on the dispatch of the persistent kernel save
-        // at most 2 us of a buffer where runs follow one another, 28.7 -> 27.0 us at p = 10 and eight updates, nothing to speak of with wider
-        // rows; a run that is waited for takes 8 to 13 us longer with them: 45.5 against 54.4 us there, 46.2 against 59.2 at p = 2048 and one update.)
-        HIP_TRY(ctx, hipEventRecord(ev1, stream));
-        *end_event = ev1;
+        *end_event = ev1;                            // (the end of the run as well, if no launch follows)
         ctx->open_chain.emplace_back(ev0, ev1);
         if (chunk_end) *chunk_end = ev1;
         ctx->lr_pos += (int64_t)np * M;

@@ -143,7 +143,8 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
 // Query co-residency and set attributes; fills shape->max_G and clamps shape->G.
 hipError_t glm_prepare(GlmLaunchShape* shape);
 // One launch of the persistent chain kernel covering steps [s_begin, s_end) of the buffer.
-hipError_t glm_launch_chain(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream);
+// `stop` (may be NULL) is completed by the kernel's own dispatch.
+hipError_t glm_launch_chain(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream, hipEvent_t stop);
 // Step-per-launch variant: partial sums for step `args.single_step`, then reduce + update.
 hipError_t glm_launch_step(const GlmLaunchShape& shape, const GlmArgs& args, int nb, hipStream_t stream);
 
@@ -152,7 +153,7 @@ hipError_t glm_launch_step(const GlmLaunchShape& shape, const GlmArgs& args, int
 size_t glm_split_lds_bytes(int ch);
 int glm_split_block();
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups);
-hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream);
+hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream, hipEvent_t stop);
 
 // Persistent chain for rows of up to 1024 floats when a step's rows fit the registers of the grid (glm_narrow_kernel.hip), with
 // rw row wavefronts per workgroup.  glm_narrow_rows_in_flight: rows per row slot that a step of n rows needs on G workgroups, 0 if
@@ -162,7 +163,7 @@ constexpr int kNarrowOneTripMaxP = 512;    // widest rows of the redundant reduc
 int glm_narrow_block(int rw);
 int glm_narrow_rows_in_flight(int v, int cpl, int L, int rw, int G, int64_t n);
 hipError_t glm_narrow_prepare(const GlmLaunchShape& shape, int p, int* max_groups);
-hipError_t glm_narrow_launch(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream);
+hipError_t glm_narrow_launch(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream, hipEvent_t stop);
 
 // Evaluation: partial[b] = sum of the per-sample losses of the rows workgroup b takes (b < nblocks <= kEvalBlocks).
 constexpr int kEvalBlocks = 1024;

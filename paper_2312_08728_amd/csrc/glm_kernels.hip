@@ -25,6 +25,7 @@
 #include "bmgd_internal.h"
 #include "glm_device.h"
 
+#include <hip/hip_ext.h>
 #include <stdio.h>
 
 #include <algorithm>
@@ -786,19 +787,19 @@ hipError_t glm_prepare(GlmLaunchShape* s)
     return hipSuccess;
 }
 
-hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream)
+hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream, hipEvent_t stop)
 {
     if (s.split) {
         if (s.G < 8 || s.G > s.max_G) return hipErrorInvalidValue;
         GlmArgs a = args;
         a.single_step = -1;
-        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, a, stream);
+        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, a, stream, stop);
     }
     if (s.narrow) {
         if (s.G > s.max_G) return hipErrorInvalidValue;
         GlmArgs a = args;
         a.single_step = -1;
-        return glm_narrow_launch(s, a, stream);
+        return glm_narrow_launch(s, a, stream, stop);
     }
     KernelFn fn = pick_kernel(s);
     if (!fn || s.G < 1 || s.G > s.max_G) return hipErrorInvalidValue;
@@ -808,7 +809,7 @@ hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStr
     // so all of them become resident as soon as compute units are free, and each device-side wait is
     // bounded anyway.  (The runtime's cooperative-launch path is avoided: it brings nothing more here and
     // its dedicated queue does not tear down cleanly under the profiler.)
-    hipLaunchKernelGGL(fn, dim3(s.G), dim3(s.block), s.lds_bytes, stream, a);
+    hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(s.block), (uint32_t)s.lds_bytes, stream, nullptr, stop, 0u, a);
     return hipGetLastError();
 }
 

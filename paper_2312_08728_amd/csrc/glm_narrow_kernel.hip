@@ -23,6 +23,8 @@
 // Odd rows in two trips take twelve as well.
 #include "glm_exchange.h"
 
+#include <hip/hip_ext.h>
+
 #include <algorithm>
 
 namespace bmgd {
@@ -329,7 +331,7 @@ hipError_t glm_narrow_prepare(const GlmLaunchShape& s, int p, int* max_groups)
     return hipSuccess;
 }
 
-hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream)
+hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream, hipEvent_t stop)
 {
     KernelFn fn = narrow_kernel(s);
     const int64_t slots = (int64_t)s.G * s.narrow_rw * (64 / s.L);
@@ -342,7 +344,7 @@ hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipSt
     if (one_trip ? s.narrow_rw == kRowWaves || args.p > kNarrowOneTripMaxP || s.G < 1
                  : s.G < 8 || s.G % 8 != 0 || (s.narrow_rw != kRowWaves && s.V != 1))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), narrow_lds_bytes(s, args.p), stream, args);
+    hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), (uint32_t)narrow_lds_bytes(s, args.p), stream, nullptr, stop, 0u, args);
     return hipGetLastError();
 }
 

@@ -26,6 +26,8 @@
 // when it gives up); the exchange wavefront's polls are bounded by the wall clock (ExchangeCommon::go_on).
 #include "glm_exchange.h"
 
+#include <hip/hip_ext.h>
+
 #include <algorithm>
 
 namespace bmgd {
@@ -281,11 +283,11 @@ hipError_t glm_split_prepare(int ch, bool opt, int* max_groups)
     return hipSuccess;
 }
 
-hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream)
+hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream, hipEvent_t stop)
 {
     if (G < 8 || G % 8 != 0 || args.s_begin >= args.s_end || args.p % 4 != 0 || args.p > kRowWaves * 256 * ch)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), glm_split_lds_bytes(ch), stream, args);
+    hipExtLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, args);
     return hipGetLastError();
 }
 
