@@ -160,6 +160,7 @@ struct bmgd_ctx {
     hipStream_t theta_stream = nullptr;            // ... then: where the last work that touches theta was enqueued, and the event behind it
     hipEvent_t theta_done = nullptr;               // (NULL: none since everything enqueued was last waited for)
     hipEvent_t swa_done = nullptr;                 // ... behind the latest averaging of theta
+    hipEvent_t run_start = nullptr;                // moment form: the start event of the run being enqueued, not recorded yet
     bool poisoned = false;                         // a run failed or was abandoned: theta is not valid until it is set again
     std::string err;
 };
@@ -563,6 +564,15 @@ float rate_of(const bmgd_ctx* ctx, int64_t ahead)
     return ctx->lr_tab_host[(size_t)u];
 }
 
+// The start of a run in the moment form, recorded where the caller says.
+int mark_start(bmgd_ctx* ctx, hipStream_t stream)
+{
+    if (!ctx->run_start) return BMGD_OK;
+    HIP_TRY(ctx, hipEventRecord(ctx->run_start, stream));
+    ctx->run_start = nullptr;
+    return BMGD_OK;
+}
+
 // The steps of a launch in the moment form, on the library's chain stream: the chain of eq. (3.1) step by step, or
 // (BMGD_CHAIN_PRODUCT) the steps multiplied together and applied once.
 hipError_t launch_steps(bmgd_ctx* ctx, const float* set, int64_t rows, int64_t n, int np, int perm_stride, hipEvent_t ev0,
@@ -651,6 +661,8 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             continue;
         }
         if (ctx->chain == BMGD_CHAIN_GRAM && c.cache_moments && !ctx->subset) {
+            const int src = mark_start(ctx, stream);
+            if (src != BMGD_OK) return src;
             // Fixed partitions: the moment matrices of buffer index b are the same in every iteration (Section 3.1.1),
             // so they are formed once and every later run over that buffer is the chain alone.
             bmgd_ctx::CachedMoments& ce = ctx->mcache[b];
@@ -691,9 +703,15 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             hipEvent_t pv0 = take_event(ctx), pv1 = take_event(ctx);
             if (!pv0 || !pv1) return fail(ctx, BMGD_EHIP, "could not create events");
             ctx->open_prep.emplace_back(pv0, pv1);
-            // set i is free once the chain that read it last has finished
-            if (ctx->chain_pending[i]) HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->chain_done[i], 0));
+            // Set i is free once the chain that read it last has finished.  Where the moments are the first kernel the run's start marker
+            // stands behind that wait: they then come to the device a little behind the chain of the last buffer, which was waiting for
+            // the same event and needs a place on one compute unit (p = 23, 150 mini-batches of 4,359 rows x 4 passes, Adam: chain 206 us, 220 with
+            // the marker in front, the moments' workgroups having taken every place).
             const bool draw = gram_moments_draw(c.p, rows, n);
+            int src = draw ? BMGD_OK : mark_start(ctx, stream);
+            if (src != BMGD_OK) return src;
+            if (ctx->chain_pending[i]) HIP_TRY(ctx, hipStreamWaitEvent(stream, ctx->chain_done[i], 0));
+            if ((src = mark_start(ctx, stream)) != BMGD_OK) return src;
             if (!draw) HIP_TRY(ctx, launch_perm(ctx->gram_perm[i], rows, nperm, keys, stream, ctx->subset, ctx->subset_limit, ctx->sync + 2));
             // BMGD_CHAIN_PRODUCT (without cached matrices): the steps are multiplied in pairs right behind the moments
             // kernel, on the same stream (both fill the device; the chain, which keeps to one unit, overlaps the next
@@ -917,12 +935,13 @@ int abandon_run(bmgd_ctx* ctx, RunRecord& rec, int rc)
     give_event(ctx, rec.start);
     if (rec.owns_end) give_event(ctx, rec.end);
     rec.start = rec.end = nullptr;
+    ctx->run_start = nullptr;
     ctx->poisoned = true;
     return rc;
 }
 
-// A run begins on `s`: its events, the first of them recorded.  (Not in the fused form, where those of its launches serve and nothing
-// stands between runs.  Elsewhere a marker costs less than events on the dispatch of the partition, which comes first: 52 to 57 against
+// A run begins on `s`: its events, the first of them recorded (in the moment form: to be recorded by mark_start).  Not in the fused form,
+// where those of its launches serve and nothing stands between runs.  (Elsewhere a marker costs less than events on the dispatch of the partition, which comes first: 52 to 57 against
 // 57 to 73 us per buffer where the host is the bound (p = 20 to 128, 4 to 63 mini-batches), 149 against 153 for 100,000 rows x 3 passes at
 // p = 100; softmax_small 771 against 798 us.)
 int begin_run(bmgd_ctx* ctx, RunRecord& rec, hipStream_t s)
@@ -930,7 +949,8 @@ int begin_run(bmgd_ctx* ctx, RunRecord& rec, hipStream_t s)
     rec.end = take_event(ctx);
     if (!ctx->fused) rec.start = take_event(ctx);
     if (!rec.end || (!ctx->fused && !rec.start)) return fail(ctx, BMGD_EHIP, "could not create events");
-    if (rec.start) HIP_TRY(ctx, hipEventRecord(rec.start, s));
+    ctx->run_start = ctx->chain == BMGD_CHAIN_GRAM ? rec.start : nullptr;
+    if (rec.start && !ctx->run_start) HIP_TRY(ctx, hipEventRecord(rec.start, s));
     return BMGD_OK;
 }
 
