@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # HBM traffic of one launch of the chain kernel on the primary workload, from rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE (see profiles/), scaled by the copy calibration; valid only for the source of the kernel it was measured on
 # (the line reports null once that file has changed: measure again and update the entry).
-TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641606}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip'), "kernel_sha256": "1e0e0132e0bb7600e5e3758b5c3d08d03d9cc0199f344ec767e63606c273e4b2", "bytes_per_launch": 217072031}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "9a1bbd9ce133274ccc00fac8fa907f00a54932dd21e7ea3bf5c651e14bc665fe", "bytes_per_launch": 2473792876}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "09638bddda74b58352b6e65a4fd69ffcc5dc6732872d7be16bae3476f2059c9a", "bytes_per_launch": 9431224907}}
+TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641623}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip'), "kernel_sha256": "1e0e0132e0bb7600e5e3758b5c3d08d03d9cc0199f344ec767e63606c273e4b2", "bytes_per_launch": 217067689}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "bb929c0c931a574a6211b12606292fef9f6024416c4e07e74403bfa9cdbe2256", "bytes_per_launch": 2473703590}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "cbf89e731fbcf2bca181eda6faffc944306b69253e0ac288b23bce5654809194", "bytes_per_launch": 9431031329}}
 
 
 def _kernel_sha(sources) -> str:

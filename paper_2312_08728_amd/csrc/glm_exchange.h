@@ -22,8 +22,8 @@
 //
 // What bounds a step of short rows is latency: two trips of about 0.6 us, in each the time until the slowest workgroup has stored
 // its words, and the instructions between them.  us per update before / now (the loops, waits and state of the exchange as it was
-// before / written as ExchangeCommon says, residuals worked out once per row): 4.3 / 3.3 at p = 200, n = 4096 (256 workgroups); 5.1 / 3.6
-// at p = 512, n = 1000 with Adam (160); one trip, 32 workgroups: 5.2 / 2.9 at p = 123, n = 777 with momentum, 4.5 / 2.9 at
+// before / written as ExchangeCommon says, residuals worked out once per row): 4.3 / 3.5 at p = 200, n = 4096 (256 workgroups); 5.1 / 3.6
+// at p = 512, n = 1000 with Adam (160); one trip, 32 workgroups: 5.2 / 3.4 at p = 123, n = 777 with momentum, 4.5 / 2.9 at
 // p = 128, n = 1024 (before: two trips, 40).
 #pragma once
 
@@ -237,8 +237,8 @@ struct ExchangeCommon {
     // U pairs of words per lane (`ask(u)` loads the u-th), asked for all together until all that the lane needs carry the tag
     // (`tags(w, u)`: the smaller of the u-th pair's tags, or `tag` where the lane does not need it).  Non-zero: the wait ran out.  (No tag
     // beyond the one waited for can be there yet, so all are equal to it if the smallest is.)  Measured against it and not kept: two or
-    // three sets of requests under way one behind the other (3.3 -> 3.7 us per update at p = 200, n = 4096: the polls slow the stores they wait
-    // for), and asking again only for what has not come (3.7: a branch around each request).
+    // three sets of requests under way one behind the other (0.4 us more per update at p = 200, n = 4096: the polls slow the stores they wait
+    // for), and asking again only for what has not come (0.4 us more: a branch around each request).
     template <int U, class Ask, class Tags>
     __device__ __forceinline__ unsigned poll(unsigned tag, u32x4 (&w)[U], Ask&& ask, Tags&& tags)
     {
