@@ -74,7 +74,8 @@ typedef struct bmgd_ctx bmgd_ctx;
  * overlaps the chain of buffer k.  The blocking calls listed above wait for that stream too; a caller that
  * synchronises compute_stream by itself has waited for the reads of its buffers, not for the updates.
  * (BMGD_CHAIN_AUTO with few features and few, small mini-batches per buffer makes a whole launch one kernel on
- * compute_stream; prep_ms and prep_launches then stay 0.) */
+ * compute_stream; prep_ms and prep_launches then stay 0.)  In both forms runs, and averagings of theta, that are enqueued on
+ * different streams are made in the order of the calls. */
 
 /* status codes */
 enum {
@@ -138,8 +139,8 @@ enum {
                                     intermediate estimates are not formed.  Needs scratch of about 3/4 N matrices of
                                     (p + 1 rounded up to 16)^2 floats, twice, for the N steps of up to four passes; rejected
                                     if that exceeds 1 GiB.  BMGD_CHAIN_AUTO picks it, in place of BMGD_CHAIN_GRAM, for plain
-                                    steps without cache_moments when a launch has at least 64 steps (bmgd_get_stats reports
-                                    the mode in use). */
+                                    steps without cache_moments when a launch has at least 64 steps and is not made in one
+                                    kernel (bmgd_get_stats reports the mode in use). */
 };
 
 /* update rule fed with the mini-batch gradient g of eq. (2.1) (Section 4.3 combines the buffering idea with NAG and
