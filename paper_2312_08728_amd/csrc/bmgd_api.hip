@@ -941,9 +941,9 @@ int abandon_run(bmgd_ctx* ctx, RunRecord& rec, int rc)
 }
 
 // A run begins on `s`: its events, the first of them recorded (in the moment form: to be recorded by mark_start).  Not in the fused form,
-// where those of its launches serve and nothing stands between runs.  (Elsewhere a marker costs less than events on the dispatch of the partition, which comes first: 52 to 57 against
-// 57 to 73 us per buffer where the host is the bound (p = 20 to 128, 4 to 63 mini-batches), 149 against 153 for 100,000 rows x 3 passes at
-// p = 100; softmax_small 771 against 798 us.)
+// where those of its launches serve and nothing stands between runs.  (Elsewhere a marker costs less than events on the dispatch of the
+// partition, which comes first: 52 to 57 against 57 to 73 us per buffer where the host is the bound (p = 20 to 128, 4 to 63 mini-batches), 149
+// against 153 for 100,000 rows x 3 passes at p = 100; softmax_small 771 against 798 us.)
 int begin_run(bmgd_ctx* ctx, RunRecord& rec, hipStream_t s)
 {
     rec.end = take_event(ctx);
