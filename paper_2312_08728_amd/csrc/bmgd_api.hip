@@ -93,6 +93,7 @@ struct bmgd_ctx {
     void* xt = nullptr;                            // softmax: transposed mini-batches of one pass (sm_chain: in the order of that kernel)
     bool sm_chain = false;                         // softmax: a pass is one persistent kernel (softmax_chain_kernel.hip)
     unsigned long long* sm_words = nullptr;        // ... and its flagged words
+    bool sm_pass = false;                          // softmax: up to four passes are one persistent kernel (softmax_pass_kernel.hip; its counters stand in xt)
     // eq. (3.1) form.  The pre-pass over the buffer (partitions, moment matrices) runs on the caller's compute
     // stream and the one-workgroup chain on a stream of the library's own, so that the pre-pass of the next
     // buffer overlaps the chain of this one; two sets of partitions and matrices alternate.
@@ -780,7 +781,34 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                 }
                 return BMGD_OK;
             };
-            for (int i = 0; i < np; ++i) {
+            if (ctx->sm_pass) {
+                SoftmaxPassArgs sa{};
+                sa.X = static_cast<const unsigned short*>(x);
+                sa.y = static_cast<const int*>(y);
+                sa.perm = ctx->perm;
+                sa.perm_stride = fixed ? 0 : (int)rows;
+                sa.npass = np;
+                sa.W = ctx->theta;
+                sa.WbT = static_cast<unsigned short*>(ctx->wbt);
+                sa.U = ctx->u;
+                sa.R = static_cast<unsigned short*>(ctx->rt);
+                sa.ldw = dmax.c_pad;
+                sa.ldwt = dmax.p_pad;
+                sa.rows = (int)rows; sa.n = (int)n; sa.p = (int)c.p; sa.C = c.n_classes;
+                sa.sync = ctx->sync;
+                // (limits as for the kernel of small mini-batches below; an update of all workgroups takes up to 25 us)
+                sa.timeout_ticks = 1000000000LL;
+                sa.meeting_ticks = ticks < 1000 ? 0 : std::min<long long>(std::min<long long>(ticks / 8, 200000000LL), std::max<long long>(100000, 2500 * M * np));
+                sa.alpha = (float)c.lr;
+                sa.lr_tab = lr_len ? ctx->lr_tab_dev : nullptr;
+                sa.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
+                sa.lr_len = lr_len;
+                sa.opt = opt_args(ctx, 0);
+                HIP_TRY(ctx, softmax_pass(sa, d, ctx->xt, ctx->num_cus, stream));
+                ctx->lr_pos += (int64_t)np * M;
+                ctx->opt_k += (int64_t)np * M;
+            }
+            for (int i = 0; i < np && !ctx->sm_pass; ++i) {
                 const int32_t* pm = ctx->perm + (fixed ? 0 : (size_t)i * rows);
                 if (ctx->sm_chain) {
                     SoftmaxChainArgs sa{};
@@ -1158,7 +1186,10 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
         ctx->chain = resolve_chain(ctx->cfg);        // three launches per mini-batch update, replayed from a graph or issued one by one
         if (one_kernel)
             CREATE_TRY(softmax_chain_prepare(cfg->p, cfg->batch_n, cfg->n_classes, cfg->optimizer != BMGD_OPT_SGD, ctx->num_cus, &ctx->sm_chain));
-        if (ctx->chain == BMGD_CHAIN_GRAPH && !ctx->sm_chain) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
+        if (cfg->chain == BMGD_CHAIN_AUTO && !ctx->sm_chain && softmax_pass_eligible(cfg->p, cfg->batch_n, cfg->n_classes) &&
+            softmax_pass_counter_bytes(softmax_dims(cfg->p, cfg->batch_n, cfg->n_classes)) <= ctx->lay.sm_words - ctx->lay.xt)
+            CREATE_TRY(softmax_pass_prepare(cfg->p, cfg->batch_n, cfg->n_classes, cfg->optimizer != BMGD_OPT_SGD, ctx->num_cus, &ctx->sm_pass));
+        if (ctx->chain == BMGD_CHAIN_GRAPH && !ctx->sm_chain && !ctx->sm_pass) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
     } else {
         char msg[160];
         if (!glm_plan(cfg->p, cfg->batch_n, cfg->n_workgroups, ctx->num_cus, cfg->chain != BMGD_CHAIN_LAUNCH, &ctx->shape, msg, sizeof msg)) {

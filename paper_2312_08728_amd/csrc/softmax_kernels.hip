@@ -14,6 +14,7 @@
 // the sequential chain.  Tiles are 128 x 128 x 64 per workgroup of eight wavefronts, each wavefront owning a
 // 64 x 32 part as 2 x 1 v_mfma_f32_32x32x16_bf16 tiles.
 #include "bmgd_internal.h"
+#include "lds_load.h"
 
 #include <algorithm>
 
@@ -125,15 +126,6 @@ constexpr int kLateTiles = 4;                       // the update's master weigh
 constexpr size_t kGemmLds = (size_t)kStages * kStageElems * 2;
 static_assert(kGemmLds >= (size_t)TN * (TM + 8) * 2, "the update's transposed tile takes the place of the stages");
 
-// 16 bytes per lane from its own address to shared memory at lds + 16 * lane.  Written as assembly because the compiler makes
-// every later read of shared memory wait for all such loads; the waits are counted by hand instead (wait_tiles).
-__device__ __forceinline__ void load_to_lds(const unsigned short* src, unsigned lds)
-{
-    asm volatile("s_mov_b32 m0, %1\n\t"
-                 "s_nop 0\n\t"
-                 "global_load_lds_dwordx4 %0, off"
-                 :: "v"(src), "s"(lds) : "memory", "m0");
-}
 // until at most TILES tiles' loads of this wavefront are under way (and all its reads of shared memory have returned)
 template <int TILES>
 __device__ __forceinline__ void wait_tiles() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(TILES * kLoads) : "memory"); }

@@ -1,0 +1,660 @@
+// Softmax regression on large mini-batches: all updates of up to four passes in one persistent kernel.
+//
+// One update of eq. (2.1) has three phases, each of which needs what all workgroups did in the one before:
+//   logits     U = X_b W               128 rows x 128 classes x a share of the features per workgroup; partial sums to memory
+//   residual   R = softmax_rows(U) - onehot(y)   four rows per workgroup, partial sums added up in a fixed order, R as bf16
+//   update     W <- W - (alpha / n_b) X_b' R     FT features x 128 classes per workgroup, all rows; master in fp32, bf16 copy
+// Three launches (softmax_kernels.hip) spend as much on their edges as on their contractions: the launch, the first operands from
+// memory, the last results to it, three times per update.  Here a phase begins when counters in memory say that what it reads is
+// complete, and its rows of X, which depend on nothing, are requested before that.
+//
+// Counters (arrive / await): a workgroup that has written its part waits for its stores, then adds one to the counter of the part;
+// readers poll.  What one workgroup writes and another reads (U, R, the bf16 copy of W) is stored and loaded at device scope, so it
+// is never found in a compute unit's own cache; a die's L2 serves such loads as fast as others (0.30 against 0.29 us per 32 KB and
+// compute unit), whereas invalidating caches between phases costs 2 us and more.  A phase's parts are counted in every update by
+// every workgroup, also where a short last mini-batch leaves nothing to do, and nothing is awaited less often than in every update:
+// so a count can only be reached by arrivals of the update that is waited for.
+//   (an arrival for update s + 1 follows, through the waits in front of it, all arrivals for update s at the same counter)
+//
+// The rows of a mini-batch are gathered from X for both contractions: for the update the contraction runs over rows, and the operands
+// (features or classes by rows) are read from the row-major tiles in shared memory with the transposing read, so nothing is ever
+// stored transposed but the copy of W.
+//
+// All workgroups that take part must be running.  They meet before the first update; if some have not come in time, those that are
+// there share the work among themselves (parts of a phase are dealt round): the same sums in the same order, down to one workgroup.
+#include "bmgd_internal.h"
+#include "glm_device.h"
+#include "lds_load.h"
+
+#include <algorithm>
+
+namespace bmgd {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kThreads = 512, kWaves = kThreads / 64;
+constexpr int TR = 128, TC = 128, TK = 64;          // rows and classes of a tile, and the depth of an operand tile
+constexpr int kRowsPerItem = 4;                     // rows of a residual item: two wavefronts each
+constexpr int kStages = 4;
+constexpr int kStageBytes = (TR + TC) * TK * 2;
+constexpr int kMaxRows = 2048;                      // of a mini-batch: its row numbers are kept in shared memory, twice
+constexpr int kTsAt = 3 * kStageBytes;              // the update's transposed tile: behind the stages that are requested ahead
+constexpr int kIdxAt = kTsAt + TC * (128 + 8) * 2;
+constexpr int kRedAt = kIdxAt + 2 * kMaxRows * 4;
+constexpr int kLds = kRedAt + 128;
+constexpr int kAgentScope = 16;                     // sc1
+constexpr int kLine = 32;                           // counters stand in lines of their own
+constexpr int kSubs = 4, kRSubs = 32;               // counters a part's arrivals are spread over (one address takes 0.04 us per arrival)
+constexpr int kLateTiles = 4;                       // the master weights are requested this many tiles before the end
+
+__device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory"); }
+
+// Until tile t of nt has landed for this wavefront.  Of the first three tiles the rows of X (LX load instructions each) were
+// requested first and the other operand (2 each) behind them; every further tile was requested whole.
+template <int LX>
+__device__ __forceinline__ void wait_tile(int t, int nt)
+{
+    const int left = nt - 1 - t;
+    if (t == 0) {
+        if (left >= 2) wait_loads<4>();
+        else if (left == 1) wait_loads<2>();
+        else wait_loads<0>();
+    } else if (t == 1) {
+        if (left >= 2) wait_loads<4 + LX>();
+        else if (left == 1) wait_loads<2>();
+        else wait_loads<0>();
+    } else {
+        if (left >= 2) wait_loads<2 * (LX + 2)>();
+        else if (left == 1) wait_loads<LX + 2>();
+        else wait_loads<0>();
+    }
+}
+
+__device__ __forceinline__ u32x2 to_bf16x4(const float (&v)[4])
+{
+    typedef __bf16 bf16x4_ __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(u32x2, __builtin_convertvector((f32x4{v[0], v[1], v[2], v[3]}), bf16x4_));
+}
+
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = fmaxf(v, dpp_mov<0xB1>(v));
+    v = fmaxf(v, dpp_mov<0x4E>(v));
+    v = fmaxf(v, dpp_mov<0x141>(v));
+    v = fmaxf(v, dpp_mov<0x140>(v));
+    v = fmaxf(v, __shfl_xor(v, 16));
+    return fmaxf(v, __shfl_xor(v, 32));
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t area(void* base, size_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
+}
+
+// Work items of a phase: part k of those dealt round to the workgroups (workgroup b takes k = b, b + nwg, ...).  Consecutive workgroups
+// go to the eight dies in turn; die x gets the x-th contiguous eighth of the items.
+struct Deal {
+    int items, per;
+    __device__ __forceinline__ explicit Deal(int n) : items(n), per((n + 7) / 8) {}
+    __device__ __forceinline__ int rounds() const { return 8 * per; }
+    __device__ __forceinline__ int item(int k) const      // -1: none
+    {
+        const int i = (k & 7) * per + (k >> 3);
+        return i < items ? i : -1;
+    }
+};
+
+template <int N> struct Counters { static constexpr int value = N; };
+
+// KB groups of 512 classes, SP partial sums: every load of a row is issued up front
+template <int KB, int SP>
+__device__ __forceinline__ void residual_rows(const SoftmaxPassArgs& a, __amdgpu_buffer_rsrc_t U, __amdgpu_buffer_rsrc_t R, const int* idx, int nb, int j0,
+                                              float* red, int wave, int lane)
+{
+    const int rr = wave >> 1, half = wave & 1, j = j0 + rr;
+    const bool real = j < nb;
+    f32x4 q[SP][KB];
+    int label = -1;
+    if (real) {
+#pragma unroll
+        for (int sp = 0; sp < SP; ++sp)
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                const int c = min(4 * (lane + 64 * (half + 2 * k)), a.ldw - 4);
+                q[sp][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(U, (unsigned)c * 4u, (unsigned)(((size_t)sp * a.m_pad + j) * a.ldw * 4), kAgentScope));
+            }
+        label = a.y[idx[j]];
+    }
+    float u[KB][4], mx = -INFINITY;
+    if (real) {
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            f32x4 t = q[0][k];
+#pragma unroll
+            for (int sp = 1; sp < SP; ++sp) t += q[sp][k];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                u[k][v] = 4 * (lane + 64 * (half + 2 * k)) + v < a.C ? t[v] : -INFINITY;      // padding classes (and clamped reads)
+                mx = fmaxf(mx, u[k][v]);
+            }
+        }
+        mx = wave_max(mx);
+    }
+    if (lane == 0) red[wave] = mx;
+    wg_barrier();
+    float sum = 0.f;
+    if (real) {
+        mx = fmaxf(red[wave & ~1], red[wave | 1]);
+#pragma unroll
+        for (int k = 0; k < KB; ++k)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                u[k][v] = expf(u[k][v] - mx);
+                sum += u[k][v];
+            }
+        sum = group_sum(sum, 64);
+    }
+    if (lane == 0) red[8 + wave] = sum;
+    wg_barrier();
+    if (j >= (nb + TK - 1) / TK * TK) return;        // (rows that no operand tile of the update reaches)
+    const float inv = real ? 1.f / (red[8 + (wave & ~1)] + red[8 + (wave | 1)]) : 0.f;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+        const int c = 4 * (lane + 64 * (half + 2 * k));
+        float r[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) r[v] = real && c + v < a.C ? u[k][v] * inv - (c + v == label ? 1.f : 0.f) : 0.f;
+        if (c < a.ldw) __builtin_amdgcn_raw_buffer_store_b64(to_bf16x4(r), R, (unsigned)c * 2u, (unsigned)((size_t)j * a.ldw * 2), kAgentScope);
+    }
+}
+
+template <int KB>
+__device__ __forceinline__ void residual_splits(const SoftmaxPassArgs& a, __amdgpu_buffer_rsrc_t U, __amdgpu_buffer_rsrc_t R, const int* idx, int nb, int j0,
+                                                float* red, int wave, int lane)
+{
+    if (a.splits == 1) residual_rows<KB, 1>(a, U, R, idx, nb, j0, red, wave, lane);
+    else if (a.splits == 2) residual_rows<KB, 2>(a, U, R, idx, nb, j0, red, wave, lane);
+    else if (a.splits == 4) residual_rows<KB, 4>(a, U, R, idx, nb, j0, red, wave, lane);
+    else residual_rows<KB, 8>(a, U, R, idx, nb, j0, red, wave, lane);
+}
+
+// FT: features of an update tile; OPT: an update rule other than the plain step.
+// Eight wavefronts, two per SIMD: each pair w, w + 4 owns a quarter of the workgroup's tile (64 classes by 64 rows or FT / 2 features),
+// and its two wavefronts take half of every operand tile's depth each: an operand is read from shared memory twice, not four times, per
+// tile (shared memory's rate is the contractions' bound: 64 + 32 KB per tile at 128 bytes a clock; 96 + 32 KB took 0.50 against 0.39 us).
+template <int FT, bool OPT>
+__global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassArgs a)
+{
+    extern __shared__ __align__(1024) unsigned char smem[];
+    __shared__ int s_abort, s_rank, s_nwg;
+    constexpr int FW = FT / 2, NF = FW / 16;         // features of a wavefront, in tiles of 16
+    constexpr int NCX = FT / 8;                      // 16-byte chunks of a row's features; load instructions of an operand tile
+    constexpr int LX = (NCX + kWaves - 1) / kWaves, LXLess = NCX / kWaves, kMoreLoads = NCX % kWaves ? NCX % kWaves : kWaves;   // wavefronts with LX of them; the others have LXLess
+    constexpr unsigned kRAt = TK * FT * 2;           // the residual's part of a stage
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int kh = wave >> 2, wm = wave & 1, wn = (wave >> 1) & 1;
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    lds_byte* const lds = (lds_byte*)smem;
+    const unsigned lds0 = (unsigned)(size_t)lds;
+    int* const idx_all = reinterpret_cast<int*>(smem + kIdxAt);
+    float* const red = reinterpret_cast<float*>(smem + kRedAt);
+
+    // the meeting: word = closed (bit 31), workgroups that came in time (bits 16-30, once closed), tickets drawn (bits 0-15)
+    PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
+    if (a.meeting_ticks == 0) {                      // no time to meet: one workgroup alone
+        if (blockIdx.x != 0) return;
+        if (tid == 0) { s_rank = 0; s_nwg = 1; s_abort = 0; }
+    } else if (tid == 0) {
+        const unsigned G = gridDim.x;
+        const unsigned got = __hip_atomic_fetch_add(a.meeting, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned ticket = got & 0xFFFFu;
+        unsigned seen = got + 1;
+        int nwg = 0;
+        const long long t0 = wall_clock64();
+        guard.arm();
+        while (true) {
+            if (seen >> 31) { nwg = (int)((seen >> 16) & 0x7FFFu); break; }
+            if (seen == G) { nwg = (int)G; break; }
+            if (ticket == 0 && wall_clock64() - t0 >= a.meeting_ticks) {
+                // (a workgroup that comes in between makes the exchange fail, and the loop looks again)
+                const unsigned closed = seen | seen << 16 | 1u << 31;
+                if (__hip_atomic_compare_exchange_strong(a.meeting, &seen, closed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) seen = closed;
+                continue;
+            }
+            if (guard.expired()) { nwg = 0; break; } // (the first one always decides long before this)
+            seen = __hip_atomic_load(a.meeting, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        s_rank = nwg == (int)G ? (int)blockIdx.x : (int)ticket;
+        s_nwg = nwg;
+        s_abort = 0;
+    }
+    wg_barrier();
+    const int rank = __builtin_amdgcn_readfirstlane(s_rank), nwg = __builtin_amdgcn_readfirstlane(s_nwg);
+    if (rank >= nwg) return;                         // came too late
+
+    const int S = a.splits, tiles_c = a.ldw / TC, tiles_r = a.m_pad / TR, tiles_f = (a.p + FT - 1) / FT;
+    const Deal dl(S * tiles_r * tiles_c), dr(a.n_pad / kRowsPerItem), dg(tiles_f * tiles_c);
+    const int CG = tiles_c % 2 ? tiles_c : tiles_c / 2, ncg = tiles_c / CG;      // groups of class tiles, and of feature tiles,
+    const int FG = tiles_f % S ? tiles_f : tiles_f / S;                          // that one die's items have in common
+    unsigned* const cnt_u = a.counters;                                          // [tiles_r][kSubs]
+    unsigned* const cnt_r = cnt_u + (size_t)tiles_r * kSubs * kLine;             // [kRSubs]
+    unsigned* const cnt_w = cnt_r + (size_t)kRSubs * kLine;                      // [tiles_c][kSubs]
+    const __amdgpu_buffer_rsrc_t U = area(a.U, (size_t)S * a.m_pad * a.ldw * 4), R = area(a.R, (size_t)a.n_pad * a.ldw * 2);
+
+    // until the NSUB counters at `first` have seen `updates` times `items` arrivals; false: given up
+    auto await = [&](auto NSUB, const unsigned* first, int items, unsigned updates) -> bool {
+        constexpr int n = decltype(NSUB)::value;
+        if (wave == 0) {
+            const int q = min(lane, n - 1);
+            const unsigned target = (unsigned)((items - q + n - 1) / n) * updates;
+            guard.arm();
+            while (true) {
+                const unsigned v = __hip_atomic_load(first + q * kLine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (__all((int)(v - target) >= 0)) break;
+                if (guard.expired()) { s_abort = 1; break; }
+            }
+        }
+        wg_barrier();
+        return __builtin_amdgcn_readfirstlane(s_abort) == 0;
+    };
+    // all stores of the workgroup have reached memory, and its reads of shared memory have returned
+    auto arrive = [&](unsigned* counter) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (tid == 0) __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+
+    // ---- logits -------------------------------------------------------------------------------------
+    struct Logits { int split, rt, ct, kb, nt; } L{0, 0, 0, 0, 0};
+    const unsigned short* lx[2];                     // a lane's rows of X: position lane % 8 of row 8 (wave + 8 h) + lane / 8
+    const int kc = ((lane & 7) ^ (lane >> 3)) * 8;   // (chunk c of row r stands at c ^ (r mod 8))
+    const unsigned short* const zeros = a.WbT + a.p; // (padding of the copy's first row: there is some if p is not a multiple of TK)
+    auto l_at = [&](int item) {
+        const int cc = item % CG, rest = item / CG, rt = rest % tiles_r, sg = rest / tiles_r;
+        L.split = sg / ncg;
+        L.ct = (sg % ncg) * CG + cc;
+        L.rt = rt;
+        L.kb = L.split * a.k_per_split;
+        L.nt = max(0, (min(a.p, L.kb + a.k_per_split) - L.kb + TK - 1) / TK);
+    };
+    auto l_request_x = [&](int t) {
+        const int k0 = L.kb + t * TK;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const unsigned short* p = lx[h] + t * TK;
+            if (k0 + TK > a.p) p = k0 + kc < a.p ? p : zeros;
+            load_to_lds(p, lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
+        }
+    };
+    // the first tiles' rows of X, which wait for nothing
+    auto l_begin = [&](const int* idx, int nb) {
+        if (L.rt * TR >= nb) return;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            lx[h] = a.X + (size_t)idx[min(L.rt * TR + 8 * (wave + kWaves * h) + (lane >> 3), nb - 1)] * a.p + L.kb + kc;
+        for (int t = 0; t < kStages - 1; ++t)
+            if (t < L.nt) l_request_x(t);
+    };
+    // the sums of the two wavefronts of a pair over the halves of the depth: each adds up and keeps two of its four rows of tiles
+    // (classes); acc[0], acc[1] hold them afterwards
+    auto meet_halves = [&](auto& acc) {
+        constexpr int N = sizeof(acc[0]) / sizeof(f32x4);
+        unsigned char* const mine = smem + wave * 8192 + lane * 16;
+        const unsigned char* const other = smem + (wave ^ 4) * 8192 + lane * 16;
+        wg_barrier();                                // all operands read: the stages are free
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < N; ++j) *reinterpret_cast<f32x4*>(mine + (i * N + j) * 1024) = kh ? acc[i][j] : acc[2 + i][j];
+        wg_barrier();
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const f32x4 o = *reinterpret_cast<const f32x4*>(other + (i * N + j) * 1024);
+                const f32x4 s = kh ? acc[2 + i][j] : acc[i][j];
+                acc[i][j] = kh ? o + s : s + o;      // (first half of the depth + second half)
+            }
+    };
+    auto l_rest = [&]() {
+        const unsigned short* ws[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) ws[h] = a.WbT + (size_t)(L.ct * TC + 8 * (wave + kWaves * h) + (lane >> 3)) * a.ldwt + L.kb + kc;
+        auto request_w = [&](int t) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                load_to_lds_agent(ws[h] + t * TK, lds0 + (unsigned)(t % kStages) * kStageBytes + TR * TK * 2 + (unsigned)(wave + kWaves * h) * 1024);
+        };
+        for (int t = 0; t < kStages - 1; ++t)
+            if (t < L.nt) request_w(t);
+        f32x4 acc[4][4];                             // classes 16 i + 4 lq .., row 16 j + l16 of the wavefront's quarter
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int c = ((4 * kh + lq) ^ (l16 & 7)) * 16;
+        for (int t = 0; t < L.nt; ++t) {
+            wait_tile<2>(t, L.nt);
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (t + kStages - 1 < L.nt) {
+                l_request_x(t + kStages - 1);
+                request_w(t + kStages - 1);
+            }
+            const unsigned char* st = smem + (t % kStages) * kStageBytes;
+            bf16x8 fx[4], fw[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                fw[i] = *reinterpret_cast<const bf16x8*>(st + TR * TK * 2 + (wn * 64 + 16 * i + l16) * (TK * 2) + c);
+                fx[i] = *reinterpret_cast<const bf16x8*>(st + (wm * 64 + 16 * i + l16) * (TK * 2) + c);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i], fx[j], acc[i][j], 0, 0, 0);
+            asm volatile("" ::: "memory");
+        }
+        meet_halves(acc);
+        const unsigned lane_at = (unsigned)(l16 * a.ldw + 4 * lq) * 4u;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const size_t row = (size_t)L.split * a.m_pad + L.rt * TR + wm * 64 + 16 * j;
+                const int cls = L.ct * TC + wn * 64 + 16 * (2 * kh + i);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[i][j]), U, lane_at, (unsigned)((row * a.ldw + cls) * 4), kAgentScope);
+            }
+    };
+
+    // ---- update -------------------------------------------------------------------------------------
+    int g_ft = 0, g_ct = 0;
+    auto g_at = [&](int item) {
+        const int cc = item % CG, rest = item / CG, f = rest % FG, fg = rest / FG;
+        g_ct = (fg % ncg) * CG + cc;
+        g_ft = (fg / ncg) * FG + f;
+    };
+    // rows of X for the update: row i of an operand tile stands with its 16-byte chunks in place c ^ swizzle(i), so that the four rows of a
+    // transposing read fall on different banks (rows of 192 and 64 bytes do by themselves)
+    constexpr int kSwz = FT == 128 ? 7 : FT == 64 ? 3 : 0;
+    int gx_row[LX], gx_col[LX];
+#pragma unroll
+    for (int h = 0; h < LX; ++h) {
+        const int q = (wave + kWaves * h) * 64 + lane, r = q / NCX;
+        gx_row[h] = r;
+        gx_col[h] = ((q % NCX) ^ (2 * (r & kSwz))) * 8;
+    }
+    auto g_request_x = [&](int t, const int* idx, int nb) {
+#pragma unroll
+        for (int h = 0; h < LX; ++h) {
+            if (wave + kWaves * h >= NCX) continue;
+            const int row = idx[min(t * TK + gx_row[h], nb - 1)];    // (the residual of rows beyond the mini-batch is zero)
+            load_to_lds(a.X + (size_t)row * a.p + min(g_ft * FT + gx_col[h], a.p - 8),
+                        lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
+        }
+    };
+    auto g_begin = [&](const int* idx, int nb) {
+        const int nt = (nb + TK - 1) / TK;
+        for (int t = 0; t < kStages - 1; ++t)
+            if (t < nt) g_request_x(t, idx, nb);
+    };
+    // transposing reads: lane l points at four elements of row 8 lq + 4 q + l16 / 4, and receives one column of four rows
+    unsigned rd_r[2][4], rd_x[2][NF];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int row = kh * 32 + 8 * lq + 4 * q + (l16 >> 2), half = (l16 & 3) >> 1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rd_r[q][i] = kRAt + (unsigned)(row * TC * 2 + ((2 * (4 * wn + i) + half) ^ (2 * (row & 7))) * 16 + (l16 & 1) * 8);
+#pragma unroll
+        for (int j = 0; j < NF; ++j) rd_x[q][j] = (unsigned)(row * FT * 2 + ((2 * (NF * wm + j) + half) ^ (2 * (row & kSwz))) * 16 + (l16 & 1) * 8);
+    }
+    auto g_rest = [&](int s, const int* idx, int nb) {
+        const int nt = (nb + TK - 1) / TK;
+        const int rrow = 4 * wave + (lane >> 4);
+        const unsigned short* const rs = a.R + (size_t)rrow * a.ldw + g_ct * TC + ((lane & 15) ^ (2 * (rrow & 7))) * 8;
+        auto request_r = [&](int t) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                load_to_lds_agent(rs + (size_t)(t * TK + 32 * h) * a.ldw, lds0 + (unsigned)(t % kStages) * kStageBytes + kRAt + (unsigned)(wave + kWaves * h) * 1024);
+        };
+        for (int t = 0; t < kStages - 1; ++t)
+            if (t < nt) request_r(t);
+        f32x4 acc[4][NF];                            // classes 16 i + 4 lq .., feature 16 j + l16 of the wavefront's quarter
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        auto run = [&](int t0, int t1) {
+            for (int t = t0; t < t1; ++t) {
+                if (LX == LXLess || wave < kMoreLoads) wait_tile<LX>(t, nt);
+                else wait_tile<LXLess>(t, nt);
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                if (t + kStages - 1 < nt) {
+                    g_request_x(t + kStages - 1, idx, nb);
+                    request_r(t + kStages - 1);
+                }
+                lds_byte* st = lds + (t % kStages) * kStageBytes;
+                auto read = [&](unsigned at0, unsigned at1) {
+                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(st + at0));
+                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(st + at1));
+                    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                };
+                bf16x8 fr[4], fx[NF];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) fr[i] = read(rd_r[0][i], rd_r[1][i]);
+#pragma unroll
+                for (int j = 0; j < NF; ++j) fx[j] = read(rd_x[0][j], rd_x[1][j]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < NF; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[i], fx[j], acc[i][j], 0, 0, 0);
+                asm volatile("" ::: "memory");
+            }
+        };
+        const int late = max(0, nt - kLateTiles);
+        run(0, late);
+        // master weights (from clamped addresses): this lane's four classes of each of its features
+        const int f0 = g_ft * FT + wm * FW + l16, c0 = g_ct * TC + wn * 64 + 32 * kh + 4 * lq;
+        f32x4 w[2][NF];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) w[i][j] = *reinterpret_cast<const f32x4*>(a.W + (size_t)min(f0 + 16 * j, a.p - 1) * a.ldw + c0 + 16 * i);
+        run(late, nt);
+        meet_halves(acc);
+        const float alpha = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
+        const float inv_nb = 1.f / (float)nb, scale = alpha * inv_nb;
+        float oc1 = 1.f, oc2 = 1.f;
+        if (OPT && a.opt.kind == kOptAdam) opt_corrections(a.opt, a.opt.k_base + s + 1, oc1, oc2);
+        unsigned short* const Ts = reinterpret_cast<unsigned short*>(smem + kTsAt);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) {
+                const int f = f0 + 16 * j, c = c0 + 16 * i;
+                const size_t at = (size_t)min(f, a.p - 1) * a.ldw + c;
+                float nw[4];
+                if constexpr (!OPT) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) nw[v] = w[i][j][v] - scale * acc[i][j][v];
+                } else {
+                    f32x4 m = *reinterpret_cast<const f32x4*>(a.opt.m + at), sv = {0.f, 0.f, 0.f, 0.f};
+                    if (a.opt.kind == kOptAdam) sv = *reinterpret_cast<const f32x4*>(a.opt.s + at);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        float mv = m[v], s2 = sv[v];
+                        nw[v] = opt_update(a.opt, w[i][j][v], acc[i][j][v] * inv_nb, alpha, mv, s2, oc1, oc2);
+                        m[v] = c + v < a.C ? mv : 0.f;
+                        sv[v] = c + v < a.C ? s2 : 0.f;
+                    }
+                    if (f < a.p) {
+                        *reinterpret_cast<f32x4*>(a.opt.m + at) = m;
+                        if (a.opt.kind == kOptAdam) *reinterpret_cast<f32x4*>(a.opt.s + at) = sv;
+                    }
+                }
+                // (classes beyond C stay zero whatever the rows hold)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) nw[v] = c + v < a.C ? nw[v] : 0.f;
+                if (f < a.p) *reinterpret_cast<f32x4*>(a.W + at) = f32x4{nw[0], nw[1], nw[2], nw[3]};
+                const u32x2 b = to_bf16x4(nw);
+                const int cl = wn * 64 + 32 * kh + 16 * i + 4 * lq, fl = wm * FW + 16 * j + l16;
+                Ts[(cl + 0) * (FT + 8) + fl] = (unsigned short)b.x;
+                Ts[(cl + 1) * (FT + 8) + fl] = (unsigned short)(b.x >> 16);
+                Ts[(cl + 2) * (FT + 8) + fl] = (unsigned short)b.y;
+                Ts[(cl + 3) * (FT + 8) + fl] = (unsigned short)(b.y >> 16);
+            }
+        wg_barrier();
+        const __amdgpu_buffer_rsrc_t copy = area(a.WbT, (size_t)a.ldw * a.ldwt * 2);
+#pragma unroll
+        for (int e0 = 0; e0 < TC * NCX; e0 += kThreads) {
+            const int e = e0 + tid, cl = e / NCX, fc = e - cl * NCX;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(&Ts[cl * (FT + 8) + 8 * fc]);
+            if (g_ft * FT + 8 * fc < a.p)
+                __builtin_amdgcn_raw_buffer_store_b128(v, copy, (unsigned)(((size_t)(g_ct * TC + cl) * a.ldwt + g_ft * FT + 8 * fc) * 2), 0, kAgentScope);
+        }
+    };
+
+    // row numbers of mini-batch m of pass t (repeated beyond its end), in order of the loads of this wavefront
+    auto request_idx = [&](int t, int m, int nb, int which) {
+        const int* src = a.perm + (size_t)t * a.perm_stride + (size_t)m * a.n;
+        for (int c = wave; c * 64 < nb; c += kWaves)
+            load_word_to_lds(src + min(c * 64 + lane, nb - 1), lds0 + kIdxAt + (unsigned)which * (kMaxRows * 4) + (unsigned)c * 256);
+    };
+
+    const int M = a.M, updates = a.npass * M;
+    request_idx(0, 0, min(a.n, a.rows), 0);
+    wait_loads<0>();
+    wg_barrier();
+    const int l_first = rank < dl.rounds() ? dl.item(rank) : -1, g_first = rank < dg.rounds() ? dg.item(rank) : -1;
+    if (l_first >= 0) { l_at(l_first); l_begin(idx_all, min(a.n, a.rows)); }
+    for (int s = 0, t = 0, m = 0; s < updates; ++s) {
+        const int nb = min(a.n, a.rows - m * a.n);
+        const int* const idx = idx_all + (s & 1) * kMaxRows;
+        for (int k = rank; k < dl.rounds(); k += nwg) {
+            const int item = dl.item(k);
+            if (item < 0) continue;
+            if (k != rank) { l_at(item); l_begin(idx, nb); }
+            if (!await(Counters<kSubs>{}, cnt_w + (size_t)L.ct * kSubs * kLine, tiles_f, (unsigned)s)) return;
+            if (L.rt * TR < nb) l_rest();
+            arrive(cnt_u + (size_t)(L.rt * kSubs + (L.split * tiles_c + L.ct) % kSubs) * kLine);
+        }
+        // the next update's row numbers, and the first rows of X for this one's update
+        const int m1 = m + 1 < M ? m + 1 : 0, t1 = m + 1 < M ? t : t + 1, nb1 = min(a.n, a.rows - m1 * a.n);
+        if (s + 1 < updates) request_idx(t1, m1, nb1, (s + 1) & 1);
+        if (g_first >= 0) { g_at(g_first); g_begin(idx, nb); }
+        for (int k = rank; k < dr.rounds(); k += nwg) {
+            const int item = dr.item(k);
+            if (item < 0) continue;
+            const int j0 = item * kRowsPerItem;
+            if (!await(Counters<kSubs>{}, cnt_u + (size_t)(j0 / TR) * kSubs * kLine, S * tiles_c, (unsigned)s + 1)) return;
+            if (a.ldw <= 512) residual_splits<1>(a, U, R, idx, nb, j0, red, wave, lane);
+            else if (a.ldw <= 1024) residual_splits<2>(a, U, R, idx, nb, j0, red, wave, lane);
+            else residual_splits<4>(a, U, R, idx, nb, j0, red, wave, lane);
+            arrive(cnt_r + (size_t)(item % kRSubs) * kLine);
+        }
+        for (int k = rank; k < dg.rounds(); k += nwg) {
+            const int item = dg.item(k);
+            if (item < 0) continue;
+            if (k != rank) { g_at(item); g_begin(idx, nb); }
+            if (!await(Counters<kRSubs>{}, cnt_r, dr.items, (unsigned)s + 1)) return;
+            g_rest(s, idx, nb);
+            arrive(cnt_w + (size_t)(g_ct * kSubs + g_ft % kSubs) * kLine);
+        }
+        t = t1;
+        m = m1;
+        if (s + 1 < updates) {
+            // (the row numbers have landed for this wavefront; for all behind the barrier)
+            wait_loads<0>();
+            wg_barrier();
+            if (l_first >= 0) { l_at(l_first); l_begin(idx_all + ((s + 1) & 1) * kMaxRows, nb1); }
+        }
+    }
+}
+
+typedef void (*PassKernel)(SoftmaxPassArgs);
+
+PassKernel pass_kernel(int ft, bool opt)
+{
+    switch (ft) {
+    case 32: return opt ? softmax_pass_kernel<32, true> : softmax_pass_kernel<32, false>;
+    case 64: return opt ? softmax_pass_kernel<64, true> : softmax_pass_kernel<64, false>;
+    case 96: return opt ? softmax_pass_kernel<96, true> : softmax_pass_kernel<96, false>;
+    default: return opt ? softmax_pass_kernel<128, true> : softmax_pass_kernel<128, false>;
+    }
+}
+
+// Features of an update tile: the width with which the last round of tiles is least in vain
+int pass_features(int p, int tiles_c, int num_cus)
+{
+    int best = 32;
+    long long cost = -1;
+    for (int ft = 32; ft <= 128; ft += 32) {
+        const long long rounds = ((long long)((p + ft - 1) / ft) * tiles_c + num_cus - 1) / num_cus;
+        const long long c = rounds * (ft + TC);
+        if (cost < 0 || c < cost) { cost = c; best = ft; }
+    }
+    return best;
+}
+
+int pass_groups(const SoftmaxDims& d, int p, int num_cus, int ft)
+{
+    const int tiles_c = d.c_pad / TC;
+    const int items = std::max({d.splits * (d.m_pad / TR) * tiles_c, d.n_pad / kRowsPerItem, (p + ft - 1) / ft * tiles_c});
+    return std::min(num_cus, (items + 7) / 8 * 8);
+}
+
+}  // namespace
+
+size_t softmax_pass_counter_bytes(const SoftmaxDims& d)
+{
+    return (size_t)(1 + d.m_pad / TR * kSubs + kRSubs + d.c_pad / TC * kSubs) * kLine * 4;
+}
+
+bool softmax_pass_eligible(int64_t p, int64_t n, int64_t C)
+{
+    return n <= kMaxRows && p <= 16384 && C <= 2048;
+}
+
+hipError_t softmax_pass_prepare(int64_t p, int64_t n, int64_t C, bool opt, int num_cus, bool* fits)
+{
+    *fits = false;
+    const SoftmaxDims d = softmax_dims(p, n, C);
+    const void* k = reinterpret_cast<const void*>(pass_kernel(pass_features((int)p, d.c_pad / TC, num_cus), opt));
+    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    if (e != hipSuccess) return e;
+    int per_cu = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kThreads, kLds);
+    if (e != hipSuccess) return e;
+    *fits = per_cu >= 1;
+    return hipSuccess;
+}
+
+hipError_t softmax_pass(SoftmaxPassArgs a, const SoftmaxDims& d, void* counters, int num_cus, hipStream_t stream)
+{
+    if (a.n > kMaxRows || d.c_pad != a.ldw || d.m_pad / TR * TR != d.m_pad) return hipErrorInvalidValue;
+    a.M = (a.rows + a.n - 1) / a.n;
+    a.m_pad = d.m_pad;
+    a.n_pad = d.n_pad;
+    a.splits = d.splits;
+    a.k_per_split = d.k_per_split;
+    a.meeting = static_cast<unsigned*>(counters);
+    a.counters = a.meeting + kLine;
+    hipError_t e = launch_fill_zero(counters, softmax_pass_counter_bytes(d), stream);
+    if (e != hipSuccess) return e;
+    const int ft = pass_features(a.p, d.c_pad / TC, num_cus);
+    hipLaunchKernelGGL(pass_kernel(ft, a.opt.kind != kOptSgd), dim3((unsigned)pass_groups(d, a.p, num_cus, ft)), dim3(kThreads), kLds, stream, a);
+    return hipGetLastError();
+}
+
+}  // namespace bmgd
