@@ -51,31 +51,90 @@ constexpr int kLds = kRedAt + 128;
 constexpr int kAgentScope = 16;                     // sc1
 constexpr int kLine = 32;                           // counters stand in lines of their own
 constexpr int kSubs = 4, kRSubs = 32;               // counters a part's arrivals are spread over (one address takes 0.04 us per arrival)
-constexpr int kLateTiles = 4;                       // the master weights are requested this many tiles before the end
+
+template <int N> struct IntC { static constexpr int value = N; };
 
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 template <int N>
 __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory"); }
 
-// Until tile t of nt has landed for this wavefront.  Of the first three tiles the rows of X (LX load instructions each) were
-// requested first and the other operand (2 each) behind them; every further tile was requested whole.
-template <int LX>
-__device__ __forceinline__ void wait_tile(int t, int nt)
+// Until the first two tiles of nt have landed for this wavefront.  Of the first three the rows of X were requested first and the other operand
+// (2 load instructions each) behind them; the fourth, and every further one, was requested whole (LT load instructions).
+template <int LT>
+__device__ __forceinline__ void wait_first(int nt)
 {
-    const int left = nt - 1 - t;
-    if (t == 0) {
-        if (left >= 2) wait_loads<4>();
-        else if (left == 1) wait_loads<2>();
-        else wait_loads<0>();
-    } else if (t == 1) {
-        if (left >= 2) wait_loads<4 + LX>();
-        else if (left == 1) wait_loads<2>();
-        else wait_loads<0>();
-    } else {
-        if (left >= 2) wait_loads<2 * (LX + 2)>();
-        else if (left == 1) wait_loads<LX + 2>();
-        else wait_loads<0>();
+    if (nt >= 4) wait_loads<2 + LT>();
+    else if (nt == 3) wait_loads<2>();
+    else wait_loads<0>();
+}
+
+// The operand tiles 0 .. nt - 1 (nt >= 1, the first kStages of them requested) in turn.  While the matrix instructions of a tile run the
+// operands of the next one are read from shared memory (request: the tile that takes the place of this one; read: the operands that stand
+// in two sets of registers; multiply: the products, each followed by the read of what takes the place of its other operand, if there is a
+// next tile).  Everything that would be decided tile by tile is known to the compiler: an iteration's 12 or 16 matrix instructions are
+// 200 cycles, those of two wavefronts to a SIMD 400, and twenty scalar instructions with their branches half of that.
+template <int LT, class Set, class Request, class Read, class Begin, class Multiply>
+struct Walk {
+    int nt;
+    Request& request;
+    Read& read;
+    Begin& begin;
+    Multiply& multiply;
+
+    // LEFT: tiles from t on (any number beyond kStages + 1 is like that)
+    template <int LEFT>
+    __device__ __forceinline__ void step(int t, Set& now, Set& next)
+    {
+        if constexpr (LEFT > 1) {
+            wait_loads<(LEFT - 2 < 2 ? LEFT - 2 : 2) * LT>();
+            __builtin_amdgcn_s_barrier();            // (the wait is for this wavefront's reads of tile t as well)
+            asm volatile("" ::: "memory");
+            if constexpr (LEFT > kStages) request(t + kStages);
+            read(next, t + 1);
+        }
+        multiply(now, t, IntC<(LEFT > 1)>{});
     }
+    template <int LEFT>
+    __device__ __forceinline__ void rest(int t, Set& now, Set& next)
+    {
+        step<LEFT>(t, now, next);
+        if constexpr (LEFT > 1) rest<LEFT - 1>(t + 1, next, now);
+    }
+    __device__ __forceinline__ void all()
+    {
+        Set even, odd;
+        wait_first<LT>(nt);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read(even, 0);
+        begin();
+        int t = 0;
+        for (; t + kStages + 1 < nt; t += 2) {
+            step<kStages + 2>(t, even, odd);
+            step<kStages + 2>(t + 1, odd, even);
+        }
+        switch (nt - t) {
+        case 5: rest<5>(t, even, odd); break;
+        case 4: rest<4>(t, even, odd); break;
+        case 3: rest<3>(t, even, odd); break;
+        case 2: rest<2>(t, even, odd); break;
+        default: rest<1>(t, even, odd); break;
+        }
+    }
+};
+
+template <int LT, class Set, class Request, class Read, class Begin, class Multiply>
+__device__ __forceinline__ void walk_tiles(int nt, Request& request, Read& read, Begin& begin, Multiply& multiply)
+{
+    Walk<LT, Set, Request, Read, Begin, Multiply>{nt, request, read, begin, multiply}.all();
+}
+
+// The same value, but what is worked out from it stays where it is used: left to itself the compiler keeps every address of every phase in
+// registers for the whole kernel, and then has none left
+__device__ __forceinline__ int here(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
 __device__ __forceinline__ u32x2 to_bf16x4(const float (&v)[4])
@@ -112,34 +171,44 @@ struct Deal {
     }
 };
 
-template <int N> struct Counters { static constexpr int value = N; };
-
 // KB groups of 512 classes, SP partial sums: every load of a row is issued up front
 template <int KB, int SP>
 __device__ __forceinline__ void residual_rows(const SoftmaxPassArgs& a, __amdgpu_buffer_rsrc_t U, __amdgpu_buffer_rsrc_t R, const int* idx, int nb, int j0,
-                                              float* red, int wave, int lane)
+                                              float* red, int wave, int lane_)
 {
+    const int lane = here(lane_);
     const int rr = wave >> 1, half = wave & 1, j = j0 + rr;
     const bool real = j < nb;
-    f32x4 q[SP][KB];
+    // (as many loads up front as leave the registers to what the whole kernel keeps in them)
+    constexpr int G = SP * KB > 16 ? 16 / KB : SP;
+    f32x4 sum_q[KB];
     int label = -1;
     if (real) {
+        label = a.y[idx[j]];
 #pragma unroll
-        for (int sp = 0; sp < SP; ++sp)
+        for (int s0 = 0; s0 < SP; s0 += G) {
+            f32x4 q[G][KB];
+#pragma unroll
+            for (int sp = 0; sp < G; ++sp)
+#pragma unroll
+                for (int k = 0; k < KB; ++k) {
+                    const int c = min(4 * (lane + 64 * (half + 2 * k)), a.ldw - 4);
+                    q[sp][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(U, (unsigned)c * 4u, (unsigned)(((size_t)(s0 + sp) * a.m_pad + j) * a.ldw * 4), kAgentScope));
+                }
 #pragma unroll
             for (int k = 0; k < KB; ++k) {
-                const int c = min(4 * (lane + 64 * (half + 2 * k)), a.ldw - 4);
-                q[sp][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(U, (unsigned)c * 4u, (unsigned)(((size_t)sp * a.m_pad + j) * a.ldw * 4), kAgentScope));
+                sum_q[k] = s0 == 0 ? q[0][k] : sum_q[k] + q[0][k];
+#pragma unroll
+                for (int sp = 1; sp < G; ++sp) sum_q[k] += q[sp][k];
             }
-        label = a.y[idx[j]];
+            __builtin_amdgcn_sched_barrier(0);
+        }
     }
     float u[KB][4], mx = -INFINITY;
     if (real) {
 #pragma unroll
         for (int k = 0; k < KB; ++k) {
-            f32x4 t = q[0][k];
-#pragma unroll
-            for (int sp = 1; sp < SP; ++sp) t += q[sp][k];
+            const f32x4 t = sum_q[k];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 u[k][v] = 4 * (lane + 64 * (half + 2 * k)) + v < a.C ? t[v] : -INFINITY;      // padding classes (and clamped reads)
@@ -189,7 +258,9 @@ __device__ __forceinline__ void residual_splits(const SoftmaxPassArgs& a, __amdg
 // FT: features of an update tile; OPT: an update rule other than the plain step.
 // Eight wavefronts, two per SIMD: each pair w, w + 4 owns a quarter of the workgroup's tile (64 classes by 64 rows or FT / 2 features),
 // and its two wavefronts take half of every operand tile's depth each: an operand is read from shared memory twice, not four times, per
-// tile (shared memory's rate is the contractions' bound: 64 + 32 KB per tile at 128 bytes a clock; 96 + 32 KB took 0.50 against 0.39 us).
+// tile (64 + 32 KB per tile at 128 bytes a clock; 96 + 32 KB took 0.50 against 0.39 us).  Those reads run behind the matrix instructions of the tile
+// before (Walk): a tile of the update takes 0.45 us with that, 0.67 without; one of the logits 0.70 and 0.73, most of it the wait for rows of X from
+// memory (0.55 where they come from a die's L2).
 template <int FT, bool OPT>
 __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassArgs a)
 {
@@ -199,6 +270,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     constexpr int NCX = FT / 8;                      // 16-byte chunks of a row's features; load instructions of an operand tile
     constexpr int LX = (NCX + kWaves - 1) / kWaves, LXLess = NCX / kWaves, kMoreLoads = NCX % kWaves ? NCX % kWaves : kWaves;   // wavefronts with LX of them; the others have LXLess
     constexpr unsigned kRAt = TK * FT * 2;           // the residual's part of a stage
+    constexpr bool kEarlyWeights = FT < 128;         // master weights requested ahead of the products (for wider tiles the registers do not suffice)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
@@ -255,7 +327,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     auto await = [&](auto NSUB, const unsigned* first, int items, unsigned updates) -> bool {
         constexpr int n = decltype(NSUB)::value;
         if (wave == 0) {
-            const int q = min(lane, n - 1);
+            const int q = min(here(lane), n - 1);
             const unsigned target = (unsigned)((items - q + n - 1) / n) * updates;
             guard.arm();
             while (true) {
@@ -291,7 +363,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const unsigned short* p = lx[h] + t * TK;
-            if (k0 + TK > a.p) p = k0 + kc < a.p ? p : zeros;
+            if (k0 + TK > a.p) p = k0 + here(kc) < a.p ? p : zeros;
             load_to_lds(p, lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
         }
     };
@@ -300,7 +372,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         if (L.rt * TR >= nb) return;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            lx[h] = a.X + (size_t)idx[min(L.rt * TR + 8 * (wave + kWaves * h) + (lane >> 3), nb - 1)] * a.p + L.kb + kc;
+            lx[h] = a.X + (size_t)idx[min(L.rt * TR + 8 * (wave + kWaves * h) + (here(lane) >> 3), nb - 1)] * a.p + L.kb + here(kc);
         for (int t = 0; t < kStages - 1; ++t)
             if (t < L.nt) l_request_x(t);
     };
@@ -308,6 +380,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     // (classes); acc[0], acc[1] hold them afterwards
     auto meet_halves = [&](auto& acc) {
         constexpr int N = sizeof(acc[0]) / sizeof(f32x4);
+        const int lane = here(tid) & 63;
         unsigned char* const mine = smem + wave * 8192 + lane * 16;
         const unsigned char* const other = smem + (wave ^ 4) * 8192 + lane * 16;
         wg_barrier();                                // all operands read: the stages are free
@@ -326,6 +399,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
             }
     };
     auto l_rest = [&]() {
+        const int lane = here(tid) & 63, l16 = lane & 15, lq = lane >> 4, kc = ((lane & 7) ^ (lane >> 3)) * 8;
         const unsigned short* ws[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) ws[h] = a.WbT + (size_t)(L.ct * TC + 8 * (wave + kWaves * h) + (lane >> 3)) * a.ldwt + L.kb + kc;
@@ -336,34 +410,45 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         };
         for (int t = 0; t < kStages - 1; ++t)
             if (t < L.nt) request_w(t);
+        if (kStages - 1 < L.nt) {
+            l_request_x(kStages - 1);
+            request_w(kStages - 1);
+        }
         f32x4 acc[4][4];                             // classes 16 i + 4 lq .., row 16 j + l16 of the wavefront's quarter
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         const int c = ((4 * kh + lq) ^ (l16 & 7)) * 16;
-        for (int t = 0; t < L.nt; ++t) {
-            wait_tile<2>(t, L.nt);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            if (t + kStages - 1 < L.nt) {
-                l_request_x(t + kStages - 1);
-                request_w(t + kStages - 1);
-            }
-            const unsigned char* st = smem + (t % kStages) * kStageBytes;
-            bf16x8 fx[4], fw[4];
+        struct Rows {
+            bf16x8 f[4];
+        };
+        auto at = [&](int t) -> const unsigned char* { return smem + (t % kStages) * kStageBytes + c; };
+        auto request = [&](int t) {
+            l_request_x(t);
+            request_w(t);
+        };
+        auto read = [&](Rows& x, int t) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x.f[i] = *reinterpret_cast<const bf16x8*>(at(t) + (wm * 64 + 16 * i + l16) * (TK * 2));
+        };
+        bf16x8 fw[4];                                // of the copy of W
+        auto read_w = [&](int t, int i) { fw[i] = *reinterpret_cast<const bf16x8*>(at(t) + TR * TK * 2 + (wn * 64 + 16 * i + l16) * (TK * 2)); };
+        auto multiply = [&](const Rows& x, int t, auto MORE) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                fw[i] = *reinterpret_cast<const bf16x8*>(st + TR * TK * 2 + (wn * 64 + 16 * i + l16) * (TK * 2) + c);
-                fx[i] = *reinterpret_cast<const bf16x8*>(st + (wm * 64 + 16 * i + l16) * (TK * 2) + c);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i], x.f[j], acc[i][j], 0, 0, 0);
+                if constexpr (decltype(MORE)::value) read_w(t + 1, i);
             }
             __builtin_amdgcn_sched_barrier(0);
+        };
+        auto begin = [&]() {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[i], fx[j], acc[i][j], 0, 0, 0);
-            asm volatile("" ::: "memory");
-        }
+            for (int i = 0; i < 4; ++i) read_w(0, i);
+        };
+        if (L.nt > 0) walk_tiles<4, Rows>(L.nt, request, read, begin, multiply);
         meet_halves(acc);
         const unsigned lane_at = (unsigned)(l16 * a.ldw + 4 * lq) * 4u;
 #pragma unroll
@@ -393,15 +478,15 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         gx_row[h] = r;
         gx_col[h] = ((q % NCX) ^ (2 * (r & kSwz))) * 8;
     }
+    auto g_src = [&](int row, int col) { return a.X + (size_t)row * a.p + min(g_ft * FT + col, a.p - 8); };
     auto g_request_x = [&](int t, const int* idx, int nb) {
 #pragma unroll
         for (int h = 0; h < LX; ++h) {
             if (wave + kWaves * h >= NCX) continue;
-            const int row = idx[min(t * TK + gx_row[h], nb - 1)];    // (the residual of rows beyond the mini-batch is zero)
-            load_to_lds(a.X + (size_t)row * a.p + min(g_ft * FT + gx_col[h], a.p - 8),
-                        lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
+            load_to_lds(g_src(idx[min(t * TK + here(gx_row[h]), nb - 1)], here(gx_col[h])), lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
         }
     };
+    // (the residual of rows beyond the mini-batch is zero)
     auto g_begin = [&](const int* idx, int nb) {
         const int nt = (nb + TK - 1) / TK;
         for (int t = 0; t < kStages - 1; ++t)
@@ -417,9 +502,18 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
 #pragma unroll
         for (int j = 0; j < NF; ++j) rd_x[q][j] = (unsigned)(row * FT * 2 + ((2 * (NF * wm + j) + half) ^ (2 * (row & kSwz))) * 16 + (l16 & 1) * 8);
     }
-    auto g_rest = [&](int s, const int* idx, int nb) {
+    // master weights (from clamped addresses): this lane's four classes of each of its features
+    auto g_weights = [&](f32x4 (&w)[2][NF]) {
+        const int lane = here(tid) & 63, l16 = lane & 15, lq = lane >> 4;
+        const int f0 = g_ft * FT + wm * FW + l16, c0 = g_ct * TC + wn * 64 + 32 * kh + 4 * lq;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j) w[i][j] = *reinterpret_cast<const f32x4*>(a.W + (size_t)min(f0 + 16 * j, a.p - 1) * a.ldw + c0 + 16 * i);
+    };
+    auto g_rest = [&](int s, const int* idx, int nb, f32x4 (&w)[2][NF]) {
         const int nt = (nb + TK - 1) / TK;
-        const int rrow = 4 * wave + (lane >> 4);
+        const int lane = here(tid) & 63, rrow = 4 * wave + (lane >> 4);
         const unsigned short* const rs = a.R + (size_t)rrow * a.ldw + g_ct * TC + ((lane & 15) ^ (2 * (rrow & 7))) * 8;
         auto request_r = [&](int t) {
 #pragma unroll
@@ -428,51 +522,64 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         };
         for (int t = 0; t < kStages - 1; ++t)
             if (t < nt) request_r(t);
+        if (kStages - 1 < nt) {
+            g_request_x(kStages - 1, idx, nb);
+            request_r(kStages - 1);
+        }
         f32x4 acc[4][NF];                            // classes 16 i + 4 lq .., feature 16 j + l16 of the wavefront's quarter
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int j = 0; j < NF; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        auto run = [&](int t0, int t1) {
-            for (int t = t0; t < t1; ++t) {
-                if (LX == LXLess || wave < kMoreLoads) wait_tile<LX>(t, nt);
-                else wait_tile<LXLess>(t, nt);
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                if (t + kStages - 1 < nt) {
-                    g_request_x(t + kStages - 1, idx, nb);
-                    request_r(t + kStages - 1);
-                }
-                lds_byte* st = lds + (t % kStages) * kStageBytes;
-                auto read = [&](unsigned at0, unsigned at1) {
-                    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(st + at0));
-                    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(st + at1));
-                    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-                };
-                bf16x8 fr[4], fx[NF];
+        int ahead[LX];                               // row numbers of the tile that is requested next
+        auto look_up = [&](int t) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) fr[i] = read(rd_r[0][i], rd_r[1][i]);
+            for (int h = 0; h < LX; ++h) ahead[h] = idx[min(t * TK + gx_row[h], nb - 1)];
+        };
+        look_up(kStages);
+        auto request = [&](int t) {
 #pragma unroll
-                for (int j = 0; j < NF; ++j) fx[j] = read(rd_x[0][j], rd_x[1][j]);
+            for (int h = 0; h < LX; ++h) {
+                if (wave + kWaves * h >= NCX) continue;
+                load_to_lds(g_src(ahead[h], gx_col[h]), lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
+            }
+            request_r(t);
+            look_up(t + 1);
+        };
+        struct Rows {
+            bf16x8 f[NF];
+        };
+        bf16x8 fr[4];                                // of the residual
+        auto read_tr = [&](int t, unsigned at0, unsigned at1) {
+            lds_byte* st = lds + (t % kStages) * kStageBytes;
+            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(st + at0));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(st + at1));
+            return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+        };
+        auto read = [&](Rows& x, int t) {
+#pragma unroll
+            for (int j = 0; j < NF; ++j) x.f[j] = read_tr(t, rd_x[0][j], rd_x[1][j]);
+        };
+        auto begin = [&]() {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) fr[i] = read_tr(0, rd_r[0][i], rd_r[1][i]);
+        };
+        auto multiply = [&](const Rows& x, int t, auto MORE) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < NF; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[i], fx[j], acc[i][j], 0, 0, 0);
-                asm volatile("" ::: "memory");
+                for (int j = 0; j < NF; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fr[i], x.f[j], acc[i][j], 0, 0, 0);
+                if constexpr (decltype(MORE)::value) fr[i] = read_tr(t + 1, rd_r[0][i], rd_r[1][i]);
             }
+            __builtin_amdgcn_sched_barrier(0);
         };
-        const int late = max(0, nt - kLateTiles);
-        run(0, late);
-        // master weights (from clamped addresses): this lane's four classes of each of its features
-        const int f0 = g_ft * FT + wm * FW + l16, c0 = g_ct * TC + wn * 64 + 32 * kh + 4 * lq;
-        f32x4 w[2][NF];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < NF; ++j) w[i][j] = *reinterpret_cast<const f32x4*>(a.W + (size_t)min(f0 + 16 * j, a.p - 1) * a.ldw + c0 + 16 * i);
-        run(late, nt);
+        if (LX == LXLess || wave < kMoreLoads) walk_tiles<LX + 2, Rows>(nt, request, read, begin, multiply);
+        else walk_tiles<LXLess + 2, Rows>(nt, request, read, begin, multiply);
+        if constexpr (!kEarlyWeights) g_weights(w);
         meet_halves(acc);
+        const int tid_ = here(tid), l16 = tid_ & 15, lq = (tid_ & 63) >> 4;
+        const int f0 = g_ft * FT + wm * FW + l16, c0 = g_ct * TC + wn * 64 + 32 * kh + 4 * lq;
         const float alpha = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
         const float inv_nb = 1.f / (float)nb, scale = alpha * inv_nb;
         float oc1 = 1.f, oc2 = 1.f;
@@ -518,7 +625,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         const __amdgpu_buffer_rsrc_t copy = area(a.WbT, (size_t)a.ldw * a.ldwt * 2);
 #pragma unroll
         for (int e0 = 0; e0 < TC * NCX; e0 += kThreads) {
-            const int e = e0 + tid, cl = e / NCX, fc = e - cl * NCX;
+            const int e = e0 + tid_, cl = e / NCX, fc = e - cl * NCX;
             const u32x4 v = *reinterpret_cast<const u32x4*>(&Ts[cl * (FT + 8) + 8 * fc]);
             if (g_ft * FT + 8 * fc < a.p)
                 __builtin_amdgcn_raw_buffer_store_b128(v, copy, (unsigned)(((size_t)(g_ct * TC + cl) * a.ldwt + g_ft * FT + 8 * fc) * 2), 0, kAgentScope);
@@ -545,7 +652,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
             const int item = dl.item(k);
             if (item < 0) continue;
             if (k != rank) { l_at(item); l_begin(idx, nb); }
-            if (!await(Counters<kSubs>{}, cnt_w + (size_t)L.ct * kSubs * kLine, tiles_f, (unsigned)s)) return;
+            if (!await(IntC<kSubs>{}, cnt_w + (size_t)L.ct * kSubs * kLine, tiles_f, (unsigned)s)) return;
             if (L.rt * TR < nb) l_rest();
             arrive(cnt_u + (size_t)(L.rt * kSubs + (L.split * tiles_c + L.ct) % kSubs) * kLine);
         }
@@ -557,7 +664,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
             const int item = dr.item(k);
             if (item < 0) continue;
             const int j0 = item * kRowsPerItem;
-            if (!await(Counters<kSubs>{}, cnt_u + (size_t)(j0 / TR) * kSubs * kLine, S * tiles_c, (unsigned)s + 1)) return;
+            if (!await(IntC<kSubs>{}, cnt_u + (size_t)(j0 / TR) * kSubs * kLine, S * tiles_c, (unsigned)s + 1)) return;
             if (a.ldw <= 512) residual_splits<1>(a, U, R, idx, nb, j0, red, wave, lane);
             else if (a.ldw <= 1024) residual_splits<2>(a, U, R, idx, nb, j0, red, wave, lane);
             else residual_splits<4>(a, U, R, idx, nb, j0, red, wave, lane);
@@ -567,8 +674,10 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
             const int item = dg.item(k);
             if (item < 0) continue;
             if (k != rank) { g_at(item); g_begin(idx, nb); }
-            if (!await(Counters<kRSubs>{}, cnt_r, dr.items, (unsigned)s + 1)) return;
-            g_rest(s, idx, nb);
+            f32x4 w[2][NF];
+            if constexpr (kEarlyWeights) g_weights(w);
+            if (!await(IntC<kRSubs>{}, cnt_r, dr.items, (unsigned)s + 1)) return;
+            g_rest(s, idx, nb, w);
             arrive(cnt_w + (size_t)(g_ct * kSubs + g_ft % kSubs) * kLine);
         }
         t = t1;

@@ -38,6 +38,15 @@ def test_edges(N, p, C, N0, n):
     assert rel_l2(got, three) <= 2e-3
 
 
+@pytest.mark.parametrize("p,n", [(p, 1100) for p in (40, 72, 136, 200, 264, 328, 392, 456)] + [(1064, n) for n in (50, 100, 150, 200, 300, 350, 400, 500)])
+def test_one_operand_tile_to_eight(p, n):
+    """The depth of the logits, and of the update, in every number of operand tiles that its pipeline starts or ends differently with."""
+    w = _case(n + 30, p, 130, n + 30, n)
+    X, y = wl.dataset(w)
+    got, st = gpu_run(w, X, y)
+    assert st.steps == w.steps and rel_l2(got, oracle_run(w, X, y)) <= 2e-3
+
+
 @pytest.mark.parametrize("N,p,C,N0,n,optimizer", [
     (310, 1064, 129, 200, 65, 0),
     (310, 1064, 129, 200, 65, 1),
