@@ -9,11 +9,13 @@
 // at all.  Same arithmetic as the row form up to the order of summation.
 #include "bmgd_internal.h"
 #include "gram_chain.h"
+#include "lds_load.h"
 #include "perm_device.h"
 
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <utility>
 
 namespace bmgd {
 
@@ -229,12 +231,106 @@ struct DirectArgs {
     uint32_t limit;
     unsigned* bad;
     float* out;
-    unsigned* tickets;                               // S = 2: [n_items][4], zero between launches
+    unsigned* tickets;                               // S = 2: [n_items][2][kDirectWaves], zero between launches
     GramLayout L;
-    int rows, n, M, dense_q;
+    int rows, n, M, dense_q, n_items;
+    const int32_t* perm;                             // (gram_rows_kernel)
+    int perm_stride;
 };
 
-constexpr int kDirectWaves = 4;
+constexpr int kDirectWaves = 4, kSumTiles = 16;
+
+// The end of a workgroup of either moments kernel: its TPW tiles from number t_first on (group h of the mini-batch's tiles), summed over
+// its four wavefronts, joined with the other workgroup's (S = 2), scaled and written.  lds: two KB for each of the tiles summed at a time.
+template <int NT, int TPW, int S>
+__device__ __forceinline__ void finish_tiles(const DirectArgs& a, floatx4 (&acc)[TPW], int t_first, int h, float* lds, int item, int nb, int wave, int lane)
+{
+    constexpr int TILES = NT * (NT + 1) / 2;
+    const int p = a.L.p, i16 = lane & 15, quad = lane >> 4;
+    // the four wavefronts' sums: two halves through shared memory, then every wavefront a quarter of the tiles; as many tiles at a time as
+    // kSumTiles says
+    constexpr int MINE = (TPW + kDirectWaves - 1) / kDirectWaves, PART = TPW < kSumTiles ? TPW : kSumTiles;
+    floatx4* red = reinterpret_cast<floatx4*>(lds);
+    float s[MINE][4];
+    int tI[MINE], tJ[MINE];
+#pragma unroll
+    for (int t0 = 0; t0 < TPW; t0 += kSumTiles) {
+        if (t0 > 0) __syncthreads();
+        if (wave >= 2) {
+#pragma unroll
+            for (int t = t0; t < TPW && t < t0 + PART; ++t) red[((wave - 2) * PART + t - t0) * 64 + lane] = acc[t];
+        }
+        __syncthreads();
+        if (wave < 2) {
+#pragma unroll
+            for (int t = t0; t < TPW && t < t0 + PART; ++t) {
+                acc[t] += red[(wave * PART + t - t0) * 64 + lane];
+                red[(wave * PART + t - t0) * 64 + lane] = acc[t];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = t0 / kDirectWaves; q < MINE && q < (t0 + kSumTiles) / kDirectWaves; ++q) {
+            const int i = min(q * kDirectWaves + wave, TPW - 1), t = min(t_first + i, TILES - 1);
+            const floatx4 v = red[(i - t0) * 64 + lane] + red[(PART + i - t0) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[q][e] = v[e];
+            int I = 0, first = 0;                    // tile t is (I, J): rows of tiles have NT, NT - 1, ... entries
+#pragma unroll
+            for (int k = 0; k < NT - 1; ++k)
+                if (t - first >= NT - I) { first += NT - I; ++I; }
+            tI[q] = 16 * I;
+            tJ[q] = 16 * (I + t - first);
+        }
+    }
+    float* o = a.out + (size_t)item * (a.dense_q > 0 ? (size_t)a.dense_q * a.dense_q : (size_t)a.L.step_floats);
+    auto where = [&](int r, int c) { return a.dense_q > 0 ? r * a.dense_q + c : c == p ? a.L.b_off + r : gram_pos(a.L, r, c); };
+    auto each = [&](auto&& f) {
+#pragma unroll
+        for (int q = 0; q < MINE; ++q) {
+            const int c = tJ[q] + i16;
+            const bool here = q * kDirectWaves + wave < TPW && t_first + q * kDirectWaves + wave < TILES && c <= p;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int r = tI[q] + 4 * quad + e;
+                if (here && r < p) f(q, e, r, c);
+            }
+        }
+    };
+    const float inv = 1.f / (float)nb;
+    const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc(o, 0, (int)((a.dense_q > 0 ? a.dense_q * a.dense_q : a.L.step_floats) * 4), 0x00020000);
+    constexpr int kAgent = 0x10;                     // cache policy sc1: past this die's cache
+    if constexpr (S == 2) {
+        // Per wavefront, group of tiles and mini-batch a word: arrivals add 1, who comes first leaves its sums and then adds kLeft; who comes
+        // second (the first one is past its arrival and waits for nothing, so this wait ends) adds them to its own and clears the word.
+        constexpr unsigned kLeft = 4;
+        unsigned* ticket = a.tickets + (item * 2 + h) * kDirectWaves + wave;
+        unsigned order = 0u;
+        if (lane == 0) order = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        order = (unsigned)__builtin_amdgcn_readfirstlane((int)order);
+        if (order == 0u) {
+            each([&](int q, int e, int r, int c) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, s[q][e]), ob, (unsigned)where(r, c) * 4u, 0, kAgent); });
+            __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+            asm volatile("" ::: "memory");
+            if (lane == 0) __hip_atomic_fetch_add(ticket, kLeft, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return;
+        }
+        while (__hip_atomic_load(ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < kLeft) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+        float other[MINE][4];
+        each([&](int q, int e, int r, int c) { other[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ob, (unsigned)where(r, c) * 4u, 0, kAgent)); });
+        each([&](int q, int e, int, int) { s[q][e] += other[q][e]; });
+        if (lane == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // (written past this die's cache as well: a plain store could leave one behind it that the other workgroup's sums would be merged into)
+    each([&](int q, int e, int r, int c) {
+        const float val = s[q][e] * inv;
+        const float put = c == p && a.dense_q > 0 ? -val : val;   // dense: [Sxx | -Sxy], for the kernel that multiplies steps together
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, put), ob, (unsigned)where(r, c) * 4u, 0, S == 2 ? kAgent : 0);
+        if (tI[q] != tJ[q] && c < p)
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, val), ob, (unsigned)where(c, r) * 4u, 0, S == 2 ? kAgent : 0);
+    });
+}
 
 template <int NT, int S>
 __global__ void __launch_bounds__(64 * kDirectWaves, 2) gram_direct_kernel(DirectArgs a)
@@ -329,86 +425,175 @@ __global__ void __launch_bounds__(64 * kDirectWaves, 2) gram_direct_kernel(Direc
         }
     }
 
-    // the four wavefronts' sums: two halves through shared memory, then every wavefront a quarter of the tiles
-    floatx4* red = reinterpret_cast<floatx4*>(lds);
-    if (wave >= 2) {
+    finish_tiles<NT, TILES, S>(a, acc, 0, 0, lds, item, nb, wave, lane);
+}
+
+// The same matrices for 96 features and more: every wavefront for itself, on its own rows and its own piece of shared memory, without a barrier.
+//
+// The staged kernel reads both operands of every product from shared memory and is bound by the instructions around its matrix instructions
+// (busy for 32 % of its time).  Here a lane's element of both operands is the same, one read for 16 columns of four rows, and the compiler knows
+// the tiles; rows come from memory straight to shared memory, up to three chunks of eight ahead, and the next operands are read while four rows are
+// multiplied.  The tiles are dealt to two workgroups (tile t = H TPW ... of the upper triangle, row by row): their sums leave room for three
+// workgroups per compute unit; all tiles in one need no row twice, but come out less even on the compute units (p = 100, 300 mini-batches of 1,000
+// rows: 68 against 75 us; two workgroups by rows as well: 79; one compute unit then holds three of the 600 workgroups, 41 us of matrix instructions
+// at 2.15 GHz, others two).  The second group does not load the columns that only the first needs.  Both groups of a mini-batch run on one die, next
+// to each other, so its rows come from memory once.  Entries of the partition come from memory: worked out here they cost 10 walks of the generator
+// per 64 rows (94 us).  us per launch, staged kernel / this one: 87 / 69 (p = 100, 300 mini-batches of 1,000 rows), 128 / 104 (p = 127).  For fewer
+// tiles it is not faster (p = 64: 38 / 43, p = 90: 36 / 43): a wavefront's loads and waits are then as long as its products.
+template <int N> struct IntC { static constexpr int value = N; };
+
+constexpr int kTileGroups = 2, kChunkRows = 8, kRing = 3;             // (a third workgroup fits a compute unit with a ring of three)
+static_assert(kChunkRows == 8, "two groups of four rows");
+constexpr int kBlockChunks = 2 * kRing, kBlockRows = kBlockChunks * kChunkRows;   // rows whose entries are fetched together: at most 64
+
+constexpr int tile_row(int NT, int t)                // I of tile t of the upper triangle, row by row
+{
+    int I = 0;
+    while (t >= NT - I) { t -= NT - I; ++I; }
+    return I;
+}
+constexpr int tile_col(int NT, int t)
+{
+    int I = 0;
+    while (t >= NT - I) { t -= NT - I; ++I; }
+    return I + t;
+}
+
+// acc[t] of tiles FROM, FROM + 1, ... += their share of four rows (which values of a lane that is has to be known to the compiler)
+template <int NT, int FROM, int TPW, size_t... I>
+__device__ __forceinline__ void multiply_tiles(floatx4 (&acc)[TPW], const float (&v)[NT], std::index_sequence<I...>)
+{
+    ((acc[I] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[IntC<tile_row(NT, FROM + (int)I)>::value], v[IntC<tile_col(NT, FROM + (int)I)>::value], acc[I], 0, 0, 0)), ...);
+}
+
+template <int NT, int H, bool VEC, int TPW>
+__device__ __forceinline__ void rows_tiles(const DirectArgs& a, floatx4 (&acc)[TPW], unsigned char* mine, unsigned mine_lds, int pass, int m,
+                                           int r_begin, int r_end, int lane)
+{
+    constexpr int TILES = NT * (NT + 1) / 2;
+    constexpr int FIRST = tile_row(NT, H * TPW);     // the first tile row, and with it the first 16 columns, that this group needs
+    constexpr int W = NT - FIRST;                    // 16-column blocks of a staged row
+    constexpr int kChunk = kChunkRows * W * 64;      // bytes of a chunk
+    constexpr int NI = VEC ? (W + 1) / 2 : 2 * W;    // load instructions of a chunk: the last one by half a wavefront if VEC and W is odd
+    constexpr int kYAt = kRing * kChunkRows * NT * 64, kIdxAt = kYAt + 512;
+    const int p = a.L.p, i16 = lane & 15, quad = lane >> 4;
+    const bool is_y = 16 * (NT - 1) + i16 == p;
+    // where in a chunk this lane's element of load q goes, and so which row (as a byte offset for the exchange of lanes) and columns it is
+    int vrow[NI], vcol[NI];
 #pragma unroll
-        for (int t = 0; t < TILES; ++t) red[((wave - 2) * TILES + t) * 64 + lane] = acc[t];
+    for (int q = 0; q < NI; ++q) {
+        const int e = lane + 64 * q;
+        vrow[q] = 4 * (VEC ? e / (4 * W) : e / (16 * W));
+        vcol[q] = 16 * FIRST + (VEC ? min(4 * (e % (4 * W)), p - 4 - 16 * FIRST) : min(e % (16 * W), p - 1 - 16 * FIRST));   // (beyond p: values that go into entries nobody reads)
     }
-    __syncthreads();
-    if (wave < 2) {
+    const int* const from = a.perm + (size_t)pass * a.perm_stride + (size_t)m * a.n;
+    auto uniform = [](unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); };
+    auto request_entries = [&](int block) {          // rows 64 block .. of the share (clamped)
+        load_word_to_lds(from + min(r_begin + kBlockRows * block + lane, r_end - 1), uniform(mine_lds + kIdxAt + (unsigned)(block & 1) * 256u));
+    };
+    auto request_y = [&](int block) {
+        const int row = *reinterpret_cast<const int*>(mine + kIdxAt + (block & 1) * 256 + 4 * lane);
+        load_word_to_lds(reinterpret_cast<const int*>(a.y) + row, uniform(mine_lds + kYAt + (unsigned)(block & 1) * 256u));
+    };
+    unsigned row_of[NI];
+    auto look_up = [&](int block, int k) {           // the rows of chunk k of a block
 #pragma unroll
-        for (int t = 0; t < TILES; ++t) {
-            acc[t] += red[(wave * TILES + t) * 64 + lane];
-            red[(wave * TILES + t) * 64 + lane] = acc[t];
-        }
-    }
-    __syncthreads();
-    float* o = a.out + (size_t)item * (a.dense_q > 0 ? (size_t)a.dense_q * a.dense_q : (size_t)a.L.step_floats);
-    auto where = [&](int r, int c) { return a.dense_q > 0 ? r * a.dense_q + c : c == p ? a.L.b_off + r : gram_pos(a.L, r, c); };
-    constexpr int MINE = (TILES + kDirectWaves - 1) / kDirectWaves;
-    float s[MINE][4];
-    int tI[MINE], tJ[MINE];
+        for (int q = 0; q < NI; ++q) row_of[q] = *reinterpret_cast<const unsigned*>(mine + kIdxAt + (block & 1) * 256 + 4 * kChunkRows * k + vrow[q]);
+    };
+    auto request = [&](int k) {                      // ... which have been looked up
+        const unsigned to = uniform(mine_lds + (unsigned)(k % kRing) * kChunk);
 #pragma unroll
-    for (int q = 0; q < MINE; ++q) {
-        const int t = min(q * kDirectWaves + wave, TILES - 1);
-        const floatx4 v = red[t * 64 + lane] + red[(TILES + t) * 64 + lane];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[q][e] = v[e];
-        int I = 0, first = 0;                        // tile t is (I, J): rows of tiles have NT, NT - 1, ... entries
-#pragma unroll
-        for (int k = 0; k < NT - 1; ++k)
-            if (t - first >= NT - I) { first += NT - I; ++I; }
-        tI[q] = 16 * I;
-        tJ[q] = 16 * (I + t - first);
-    }
-    auto each = [&](auto&& f) {
-#pragma unroll
-        for (int q = 0; q < MINE; ++q) {
-            const int c = tJ[q] + i16;
-            const bool here = q * kDirectWaves + wave < TILES && c <= p;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int r = tI[q] + 4 * quad + e;
-                if (here && r < p) f(q, e, r, c);
-            }
+        for (int q = 0; q < NI; ++q) {
+            const float* src = a.X + (size_t)row_of[q] * (size_t)p + vcol[q];
+            if constexpr (!VEC) load_word_to_lds(reinterpret_cast<const int*>(src), to + 256u * q);
+            else if (64 * (q + 1) <= 4 * W * kChunkRows || lane < 32) load_to_lds(reinterpret_cast<const unsigned short*>(src), to + 1024u * q);
         }
     };
-    const float inv = 1.f / (float)nb;
-    const __amdgpu_buffer_rsrc_t ob = __builtin_amdgcn_make_buffer_rsrc(o, 0, (int)((a.dense_q > 0 ? a.dense_q * a.dense_q : a.L.step_floats) * 4), 0x00020000);
-    constexpr int kAgent = 0x10;                     // cache policy sc1: past this die's cache
-    if constexpr (S == 2) {
-        // Per wavefront and mini-batch two words: who comes first leaves its sums and then says so; who comes second (the first one is past
-        // the ticket and waits for nothing, so this wait ends) adds them to its own and clears the words.
-        unsigned* ticket = a.tickets + 2 * (item * kDirectWaves + wave);
-        unsigned order = 0u;
-        if (lane == 0) order = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        order = (unsigned)__builtin_amdgcn_readfirstlane((int)order);
-        if (order == 0u) {
-            each([&](int q, int e, int r, int c) { __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, s[q][e]), ob, (unsigned)where(r, c) * 4u, 0, kAgent); });
-            __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
-            asm volatile("" ::: "memory");
-            if (lane == 0) __hip_atomic_store(ticket + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return;
+    auto read = [&](float (&v)[NT], int block, int k, int g) {       // four rows
+        const float* row = reinterpret_cast<const float*>(mine + (k % kRing) * kChunk) + (4 * g + quad) * (16 * W) + i16;
+        const float* end = is_y ? reinterpret_cast<const float*>(mine + kYAt + (block & 1) * 256) + kChunkRows * k + 4 * g + quad : row + 16 * (W - 1);
+#pragma unroll
+        for (int f = FIRST; f < NT - 1; ++f) v[f] = row[16 * (f - FIRST)];
+        v[NT - 1] = *end;
+    };
+    auto use = [&](float (&v)[NT], int left) {       // left: rows from these on
+        if (left <= 0) return;
+        if (left < 4) {                              // (uniform) the last ones: rows beyond the share count as zero
+#pragma unroll
+            for (int f = FIRST; f < NT; ++f) v[f] = quad < left ? v[f] : 0.f;
         }
-        while (__hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) __builtin_amdgcn_s_sleep(1);
-        asm volatile("" ::: "memory");
-        float other[MINE][4];
-        each([&](int q, int e, int r, int c) { other[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ob, (unsigned)where(r, c) * 4u, 0, kAgent)); });
-        each([&](int q, int e, int, int) { s[q][e] += other[q][e]; });
-        if (lane == 0) {
-            __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(ticket + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        multiply_tiles<NT, H * TPW>(acc, v, std::make_index_sequence<TPW < TILES - H * TPW ? TPW : TILES - H * TPW>{});
+    };
+    auto landed = [&]() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
+    request_entries(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    request_y(0);
+#pragma unroll
+    for (int k = 0; k < kRing; ++k) {
+        look_up(0, k);
+        request(k);
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kRing - 1) * NI) : "memory");
+    float first[NT], second[NT];
+    read(first, 0, 0, 0);
+    for (int block = 0; r_begin + kBlockRows * block < r_end; ++block) {
+        const int left = r_end - r_begin - kBlockRows * block;
+        request_entries(block + 1);
+#pragma unroll
+        for (int k = 0; k < kBlockChunks; ++k) {
+            // Operands of the next four rows, and the rows of the chunk that is requested next, are read from shared memory while four rows are
+            // multiplied.  Chunk k + kRing goes where chunk k is, whose reads have returned by then; the rows of chunk k + 1, requested before
+            // kRing - 1 others, have come behind the wait (and by k = kRing - 1 the next entries, requested before chunk kRing).
+            constexpr int kNext = kBlockChunks - kRing;
+            read(second, block, k, 1);
+            look_up(block + (k + kRing) / kBlockChunks, (k + kRing) % kBlockChunks);
+            use(first, left - kChunkRows * k);
+            landed();
+            if (k == kNext) request_y(block + 1);
+            request((k + kRing) % kBlockChunks);
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"((kRing - 1) * NI) : "memory");
+            read(first, block + (k + 1) / kBlockChunks, (k + 1) % kBlockChunks, 0);
+            use(second, left - kChunkRows * k - 4);
         }
     }
-    // (written past this die's cache as well: a plain store could leave one behind it that the other workgroup's sums would be merged into)
-    each([&](int q, int e, int r, int c) {
-        const float val = s[q][e] * inv;
-        const float put = c == p && a.dense_q > 0 ? -val : val;   // dense: [Sxx | -Sxy], for the kernel that multiplies steps together
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, put), ob, (unsigned)where(r, c) * 4u, 0, S == 2 ? kAgent : 0);
-        if (tI[q] != tJ[q] && c < p)
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, val), ob, (unsigned)where(c, r) * 4u, 0, S == 2 ? kAgent : 0);
-    });
+}
+
+template <int NT>
+constexpr int rows_lds_bytes()
+{
+    constexpr int TPW = (NT * (NT + 1) / 2 + kTileGroups - 1) / kTileGroups;
+    const int ring = kDirectWaves * (kRing * kChunkRows * NT * 64 + 1024), sums = 2 * (TPW < kSumTiles ? TPW : kSumTiles) * 1024;
+    return ring > sums ? ring : sums;
+}
+
+template <int NT, int S, bool VEC>
+__global__ void __launch_bounds__(64 * kDirectWaves, 2) gram_rows_kernel(DirectArgs a)
+{
+    constexpr int T = kTileGroups, TPW = (NT * (NT + 1) / 2 + T - 1) / T;
+    extern __shared__ __align__(16) unsigned char smem[];
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int h = slot % T, part = slot / T % S, item = slot / (T * S) * 8 + xcd;
+    if (item >= a.n_items) return;
+    const int pass = item / a.M, m = item - pass * a.M;
+    const int nb = min(a.n, a.rows - m * a.n);
+    // this wavefront's rows: whole groups of four, one share of S * kDirectWaves
+    const int share = (nb + 4 * S * kDirectWaves - 1) / (4 * S * kDirectWaves) * 4;
+    const int r_begin = min(nb, (part * kDirectWaves + wave) * share), r_end = min(nb, r_begin + share);
+    constexpr int kMine = kRing * kChunkRows * NT * 64 + 1024;
+    unsigned char* const mine = smem + wave * kMine;
+    const unsigned mine_lds = (unsigned)(size_t)(lds_byte*)smem + (unsigned)(wave * kMine);
+    floatx4 acc[TPW];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (r_begin < r_end) {
+        if (h == 0) rows_tiles<NT, 0, VEC, TPW>(a, acc, mine, mine_lds, pass, m, r_begin, r_end, lane);
+        else rows_tiles<NT, 1, VEC, TPW>(a, acc, mine, mine_lds, pass, m, r_begin, r_end, lane);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (rows requested beyond the last ones)
+    __syncthreads();
+    finish_tiles<NT, TPW, S>(a, acc, h * TPW, h, reinterpret_cast<float*>(smem), item, nb, wave, lane);
 }
 
 using DirectFn = void (*)(DirectArgs);
@@ -467,6 +652,28 @@ hipError_t launch_gram_mfma(bool wide, dim3 grid, size_t lds, hipStream_t stream
 #undef GRAM_LAUNCH
     return hipGetLastError();
 }
+
+// p > 95 (seven to nine tile rows): the kernel, its shared memory
+template <int S>
+DirectFn rows_kernel(int NT, bool vec, int* lds)
+{
+    switch (NT) {
+    case 7: *lds = rows_lds_bytes<7>(); return vec ? gram_rows_kernel<7, S, true> : gram_rows_kernel<7, S, false>;
+    case 8: *lds = rows_lds_bytes<8>(); return vec ? gram_rows_kernel<8, S, true> : gram_rows_kernel<8, S, false>;
+    case 9: *lds = rows_lds_bytes<9>(); return vec ? gram_rows_kernel<9, S, true> : nullptr;     // (p = 128)
+    }
+    return nullptr;
+}
+
+// Where the kernel above takes p > 95 from the staged one: many mini-batches, or few long ones, which it splits over two workgroups by rows.
+// With few rows in a mini-batch the staged kernel's more workgroups, each with fewer tiles, get going sooner.  (By the mini-batches of one pass, as
+// above.)  us of moments for one pass / three, staged kernel and this one: p = 100: 36 / 84 and 35 / 77 (100 mini-batches of 1,000 rows), 25 / 63 and
+// 25 / 49 (128, 500), 32 / 71 and 25 / 54 (200, 300), 17 / 37 and 19 / 33 (100, 256: not chosen), 28 / 58 and 35 / 53 (64, 1000: not chosen); split:
+// 136 / 139 and 101 / 102 (8, 8000), 73 / 77 and 61 / 64 (16, 4000), 43 / 63 and 42 / 60 (32, 2000), 36 / 76 and 38 / 67 (48, 1500: not chosen);
+// p = 127: 51 / 125 and 46 / 116 (100, 1000), 33 / 85 and 31 / 71 (128, 500), 225 / 229 and 136 / 137 (8, 8000), 118 / 125 and 81 / 84 (16, 4000).
+bool rows_moments(int p, int M, int n) { return p > 95 && (n >= 2000 || (M >= 85 && (int64_t)M * n >= 50000)); }
+
+int rows_split(int M) { return M < 85 ? 2 : 1; }
 
 template <int TPR, int KQ, int KS>
 hipError_t launch_chain(const GramLayout& L, const float* gram, float* theta, int nsteps, int period, float alpha, const float* lr_tab,
@@ -531,6 +738,20 @@ int gram_chain_threads(int64_t p)
     return make_layout((int)p).nthr;
 }
 
+hipError_t gram_moments_prepare(int64_t p)
+{
+    if (p <= 95) return hipSuccess;
+    const int NT = (int)((p + 1 + 15) / 16);
+    for (int S = 1; S <= 2; ++S) {
+        int lds = 0;
+        DirectFn fn = S == 2 ? rows_kernel<2>(NT, p % 4 == 0, &lds) : rows_kernel<1>(NT, p % 4 == 0, &lds);
+        if (!fn) return hipErrorInvalidValue;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 bool gram_moments_draw(int64_t p, int64_t rows, int64_t n) { return direct_moments((int)p, (int)((rows + n - 1) / n)); }
 
 hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* perm, const GramPartition& from, float* gram, unsigned* tickets,
@@ -542,20 +763,28 @@ hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* pe
     const GramLayout L = make_layout(p);
     const int M = (rows + n - 1) / n;
     const int gpass = perm_stride == 0 ? 1 : npass;      // one partition for all passes: one set of matrices
-    if (direct_moments(p, M)) {
-        DirectArgs a{};
-        a.X = X; a.y = y; a.keys = from.keys; a.h = (uint32_t)perm_half_width(rows);
-        a.subset = from.subset; a.limit = (uint32_t)from.limit; a.bad = from.bad;
-        a.out = gram; a.tickets = tickets; a.L = L;
-        a.rows = rows; a.n = n; a.M = M; a.dense_q = dense_q;
-        const int S = direct_split(M, n);
-        DirectFn fn = S == 2 ? direct_kernel<2>((p + 1 + 15) / 16) : direct_kernel<1>((p + 1 + 15) / 16);
+    const int NT = (p + 1 + 15) / 16;                    // tile rows of the moment matrix of [X y]
+    DirectArgs a{};
+    a.X = X; a.y = y; a.keys = from.keys; a.h = (uint32_t)perm_half_width(rows);
+    a.subset = from.subset; a.limit = (uint32_t)from.limit; a.bad = from.bad;
+    a.out = gram; a.tickets = tickets; a.L = L;
+    a.rows = rows; a.n = n; a.M = M; a.dense_q = dense_q; a.n_items = M * gpass; a.perm = perm; a.perm_stride = perm_stride;
+    const bool direct = direct_moments(p, M);
+    const int S = direct ? direct_split(M, n) : rows_split(M);
+    if (direct) {
+        DirectFn fn = S == 2 ? direct_kernel<2>(NT) : direct_kernel<1>(NT);
         if (!fn || (S == 2 && !tickets)) return hipErrorInvalidValue;
-        hipExtLaunchKernelGGL(fn, dim3((unsigned)(M * gpass * S)), dim3(64 * kDirectWaves), 0u, stream, start, stop, 0u, a);
+        hipExtLaunchKernelGGL(fn, dim3((unsigned)(a.n_items * S)), dim3(64 * kDirectWaves), 0u, stream, start, stop, 0u, a);
         return hipGetLastError();
     }
     if (!perm) return hipErrorInvalidValue;
-    const int NT = (p + 1 + 15) / 16;                    // tile rows of the moment matrix of [X y]
+    if (rows_moments(p, M, n)) {
+        int lds = 0;
+        DirectFn fn = S == 2 ? rows_kernel<2>(NT, p % 4 == 0, &lds) : rows_kernel<1>(NT, p % 4 == 0, &lds);
+        if (!fn || (S == 2 && !tickets)) return hipErrorInvalidValue;
+        hipExtLaunchKernelGGL(fn, dim3((unsigned)((a.n_items + 7) / 8 * 8 * kTileGroups * S)), dim3(64 * kDirectWaves), (uint32_t)lds, stream, start, stop, 0u, a);
+        return hipGetLastError();
+    }
     GramTiles T{};
     T.ntiles = NT * (NT + 1) / 2;
     int tpw = 0;
@@ -570,7 +799,7 @@ hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* pe
     int stride = NT * 16;
     if (stride % 32 == 0) stride += 16;                  // rows k and k + 1 of an operand read fall on different banks
     const size_t lds = sizeof(float) * (size_t)std::max(kGramWaves * kRowsPerChunk * stride, kGramWaves * tpw * 64 * 4);
-    const int n_items = M * gpass;
+    const int n_items = a.n_items;
     const dim3 grid((unsigned)((n_items + 7) / 8 * 8 * T.tsplit));
     const bool wide = p > 64;
     hipError_t e = hipErrorInvalidValue;
