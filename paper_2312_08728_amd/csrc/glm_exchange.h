@@ -1,7 +1,7 @@
 // The exchange wavefronts of the persistent GLM kernels, and what they share around them.
 //
 // A workgroup of these kernels is a set of "row" wavefronts, which read rows and accumulate the gradient sums of a
-// step of eq. (2.1), and one or four exchange wavefronts, which carry those sums to the other workgroups and bring the
+// step of eq. (2.1), and three or four exchange wavefronts, which carry those sums to the other workgroups and bring the
 // new theta back.  The two kinds meet only through flags in shared memory:
 //   s_published      counts publications of row wavefronts over all steps (each stores its sums to shared memory first);
 //   s_theta_version  versions of theta the exchange wavefronts have delivered to shared memory (version v = theta
@@ -35,16 +35,7 @@
 namespace bmgd {
 namespace {
 
-// Eleven wavefronts are launched and three roles handed out by wavefront index.  The hardware deals the wavefronts of a
-// workgroup out to the four SIMDs of a compute unit in turn (0, 4, 8 share the first one), and every SIMD feeds its memory
-// instructions into a queue of its own, in order.  The exchange wavefront must not stand in such a queue behind row
-// loads, so it is wavefront 0 and its two SIMD mates (4 and 8) leave right after the start-up barrier; the other
-// eight are the row wavefronts.  (Only speed depends on the dealing order; the roles are correct for any.)
-constexpr int kRowWaves = 8;
-constexpr int kRoleWaves = 11;
-constexpr int kRoleBlock = 64 * kRoleWaves;
-// wavefront index -> row wavefront 0 .. 7 (1, 2, 3, 5, 6, 7, 9, 10), -1 for the exchange wavefront, -2 for the two that leave
-__device__ __forceinline__ int role_of(int wave) { return wave == 0 ? -1 : (wave & 3) == 0 ? -2 : wave - 1 - (wave >> 2); }
+constexpr int kRowWaves = 8;                          // (glm_split_kernel.hip)
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // (pointers into shared memory carry its address space, so that accesses through them are shared-memory
@@ -180,14 +171,14 @@ struct ExchangeLds {
     int th_stride;
     lds_f32* state;               // [NX][3][64][2]: for each exchange wavefront Adam's bias corrections of the coming steps, and the state
                                   //   of the pairs of columns it updates
-    lds_f32* red;                 // [2][NX][64][2]: the exchange wavefronts' partial sums, by parity (NX > 1 only)
+    lds_f32* red;                 // [2][NX][64][2]: the exchange wavefronts' partial sums, by parity
     const lds_f32* sums;          // [NSUM][sums_stride]: the workgroup's gradient sums of a step; column c is the sum over
     int sums_stride;              //   the NSUM arrays (even; columns [p, p rounded up to even) hold 0)
     unsigned publishers;          // publications of row wavefronts that complete a step
     lds_u32* s_published;
     lds_u32* s_theta_version;     // raised by every exchange wavefront once per step: NX v when version v is complete
     lds_i32* s_abort;
-    lds_u32* s_xarrived;          // NX > 1: [NX] sets of partial sums each exchange wavefront has left in `red`
+    lds_u32* s_xarrived;          // [NX] sets of partial sums each exchange wavefront has left in `red`
     lds_u32* s_xconsumed;         //         sets that the first one has added up (two-trip form)
 };
 constexpr int kExchangeState = 3 * 128, kExchangeRed = 2 * 128;     // floats of `state` and `red` per exchange wavefront
@@ -292,9 +283,9 @@ struct ExchangeCommon {
             }
         };
         asm volatile("" ::: "memory");
-        if constexpr (NX == 1) {
+        if constexpr (NSUM == 1) {                   // (their reads of shared memory go out together)
 #pragma unroll 8
-            for (int c = 2 * lane; c < p; c += 128) send(c);
+            for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) send(c0 + 2 * lane);
         } else {
 #pragma unroll 1
             for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) send(c0 + 2 * lane);
@@ -391,10 +382,10 @@ __device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
 // All steps [a.s_begin, a.s_end) of a launch in two trips over the fabric each, by exchange wavefront xw of NX of workgroup
 // blockIdx.x of gridDim.x (a multiple of 8).  Returns when the last version of theta has been delivered (workgroup 0 also writes it
 // to a.theta), or with s_abort and the global abort flag set when a wait ran out.
-// With NX > 1 the wavefronts share every phase: each sends a part of the workgroup's sums, adds up a part of the
+// The wavefronts share every phase: each sends a part of the workgroup's sums, adds up a part of the
 // workgroups for the slice (the first one then adds the NX partial sums in their order and applies the update) and
-// collects a part of theta.  A wavefront pulls freshly written lines at a fraction of what a compute unit can take,
-// so where no row traffic competes (narrow rows) four wavefronts on the four SIMDs finish a trip sooner.
+// collects a part of theta.  A wavefront pulls freshly written lines at a fraction of what a compute unit can take, so several on as
+// many SIMDs finish a trip sooner, beside row traffic too (glm_split_kernel.hip has both figures).
 // U1, U2: pairs of words a lane requests per trip when it sums the slice / collects theta.
 template <bool OPT, int NX, int NSUM, int U1, int U2>
 __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
@@ -446,7 +437,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
         // This workgroup's own rows first: until they have been summed nothing can be complete, and polling the
         // fabric meanwhile would only take bandwidth from the rows.  (The rows were multiplied by a complete theta, so
         // every exchange wavefront has delivered its part of the version that this step's update starts from.)
-        dead |= ex.template wait_ge<(NX == 1)>(x.s_published, (ver + 1u) * x.publishers);
+        dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
         // 0. this workgroup's sums out of shared memory
         ex.send_sums(part, tag);
 
@@ -462,9 +453,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
                     load_state(c);
                     // two sets of partial sums alternate: a wavefront does not overwrite a set before the first one has added
                     // it up (a slice of one chunk cannot come to that: its theta has been collected since)
-                    if constexpr (NX > 1) {
-                        if (phase >= 2u) dead |= ex.template wait_ge<false>(x.s_xconsumed, phase - 1u);
-                    }
+                    if (phase >= 2u) dead |= ex.template wait_ge<false>(x.s_xconsumed, phase - 1u);
                 }
                 // One address register per lane (its pair of columns in the row of words of workgroup my_sg); what differs
                 // between a lane's loads is uniform and goes into the scalar offset.  Load u of wavefront xw takes the
@@ -488,21 +477,19 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
                     i0 += SG * NX * U1;
                 } while (i0 - SG * xw < G && dead == 0u);
                 t = pair_slot_sum(t, PPc);           // the SG groups' sums meet over the lanes: every lane has its pair's
-                if constexpr (NX > 1) {
-                    // the NX wavefronts' sums meet in the first one
-                    lds_f32x2* set = (lds_f32x2*)(x.red + (phase & 1u) * NX * 128);
-                    if (xw != 0) {
-                        if (lane < PPc) set[xw * 64 + lane] = t;
-                        ex.mark_arrived(phase + 1u);
-                    } else {
-                        dead |= ex.template wait_ge<false>(x.s_xarrived + 1 + min(lane, NX - 2), phase + 1u);
-                        asm volatile("" ::: "memory");
-                        f32x2 v[NX - 1];
+                // the NX wavefronts' sums meet in the first one
+                lds_f32x2* set = (lds_f32x2*)(x.red + (phase & 1u) * NX * 128);
+                if (xw != 0) {
+                    if (lane < PPc) set[xw * 64 + lane] = t;
+                    ex.mark_arrived(phase + 1u);
+                } else {
+                    dead |= ex.template wait_ge<false>(x.s_xarrived + 1 + min(lane, NX - 2), phase + 1u);
+                    asm volatile("" ::: "memory");
+                    f32x2 v[NX - 1];
 #pragma unroll
-                        for (int k = 1; k < NX; ++k) v[k - 1] = set[k * 64 + my_pair];
+                    for (int k = 1; k < NX; ++k) v[k - 1] = set[k * 64 + my_pair];
 #pragma unroll
-                        for (int k = 1; k < NX; ++k) { t.x += v[k - 1].x; t.y += v[k - 1].y; }
-                    }
+                    for (int k = 1; k < NX; ++k) { t.x += v[k - 1].x; t.y += v[k - 1].y; }
                 }
                 if (own && xw == 0) {
                     const f32x2 old = *(const lds_f32x2*)(th_old + c);
@@ -517,10 +504,8 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
                 }
                 if (!one_chunk) {
                     store_state(c);
-                    if constexpr (NX > 1) {
-                        asm volatile("" ::: "memory");
-                        if (xw == 0 && lane == 0) __hip_atomic_store(x.s_xconsumed, phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                    }
+                    asm volatile("" ::: "memory");
+                    if (xw == 0 && lane == 0) __hip_atomic_store(x.s_xconsumed, phase + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
                 }
                 ++phase;
                 pb += PPc;

@@ -16,14 +16,18 @@
 //     rows of the next step keep arriving.  Loads return to a wavefront in the order it issued them, so a wavefront
 //     that has rows in flight must not poll for the exchange (its poll would come back behind its newest rows):
 //     row wavefronts issue no load but their rows (and, right behind them, the responses and the next row indices), and
-//   * a ninth wavefront does the exchange (glm_exchange.h).  It has no rows in flight, so its polls return at the latency
-//     of the fabric.  Two trips over the fabric per step.  (Measured: under the row traffic a trip costs about 2 us
+//   * three more wavefronts, on three of the four SIMDs, do the exchange (glm_exchange.h).  They have no rows in flight, so their polls return
+//     at the latency of the fabric, and they share a trip's words: one wavefront pulls freshly written lines at a fraction of what a compute
+//     unit can take.  Two trips over the fabric per step.  us per update with one (whose SIMD had no row wavefronts) and with three: 7.6 / 6.2 at
+//     p = 1028, n = 1500 (256 workgroups, 6 rows each), 9.1 / 7.9 at 2048, 2048, 10.3 / 9.1 at 2500, 1500, 15.0 / 13.7 at 2500, 4096, 19.0 / 18.0 at
+//     4096, 4096, 30.6 / 29.9 at 4096, 8192: the fewer the rows, the less stands in the queues that the exchange now shares with them.  With four:
+//     at most 2 % less.  (Measured: under the row traffic a trip costs about 2 us
 //     whether the words come from the same die or another, and a wavefront that asks for a phase's words in two
 //     batches pays twice, so a die-local first stage - one more trip - loses; loads that would be served from a
 //     die's L2 without leaving it, other than atomics, do not exist in this mode of the hardware.)
 //
-// Waits: row wavefronts only ever wait on shared-memory flags (which the exchange wavefront always releases, also
-// when it gives up); the exchange wavefront's polls are bounded by the wall clock (ExchangeCommon::go_on).
+// Waits: row wavefronts only ever wait on shared-memory flags (which the exchange wavefronts always release, also
+// when they give up); their polls are bounded by the wall clock (ExchangeCommon::go_on).
 #include "glm_exchange.h"
 
 #include <hip/hip_ext.h>
@@ -34,7 +38,8 @@ namespace bmgd {
 
 namespace {
 
-constexpr int kSplitBlock = kRoleBlock;
+constexpr int NX = 3;                                // exchange wavefronts, on three SIMDs (wavefronts are dealt out to the four in turn)
+constexpr int kSplitBlock = 64 * (NX + kRowWaves);
 constexpr int kGroupRows = 4;                        // rows whose partial dot products are exchanged together
 constexpr int kGroups = 3;                           // groups of rows a row wavefront holds (used, or in flight)
 
@@ -60,9 +65,10 @@ template <int CH, bool OPT>
 __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
 {
     extern __shared__ __align__(16) float smem[];
-    __shared__ int s_abort;                          // set by the exchange wavefront when a wait ran out
+    __shared__ int s_abort;                          // set by an exchange wavefront when a wait ran out
     __shared__ unsigned s_theta_version;             // versions of theta delivered to shared memory so far
     __shared__ unsigned s_published;                 // row wavefronts that have stored their sums, counted over all steps
+    __shared__ unsigned s_xarrived[NX], s_xconsumed; // hand-over of partial sums between the exchange wavefronts
 
     constexpr int WCOLS = 256 * CH;                  // columns a row wavefront owns
     constexpr int P_PAD = kRowWaves * WCOLS;
@@ -78,22 +84,22 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     // instructions and are counted apart from the row loads)
     volatile lds_f32* pd = (volatile lds_f32*)(smem + 2 * P_PAD);   // [2][kRowWaves][GR]: partial dot products of a group, by group parity
     volatile lds_u32* pd_seq = (volatile lds_u32*)(smem + 2 * P_PAD + 2 * kRowWaves * GR);   // [2][kRowWaves]: their sequence numbers
-    lds_f32* xstate = (lds_f32*)(smem + 2 * P_PAD + 2 * kRowWaves * GR + 2 * kRowWaves);   // scratch of the exchange wavefront
-    lds_f32* sums = xstate + kExchangeState;                  // [P_PAD]: the workgroup's gradient sums of a step, on their way out
+    lds_f32* xstate = (lds_f32*)(smem + 2 * P_PAD + 2 * kRowWaves * GR + 2 * kRowWaves);   // scratch of the exchange wavefronts
+    lds_f32* sums = xstate + (kExchangeState + kExchangeRed) * NX;   // [P_PAD]: the workgroup's gradient sums of a step, on their way out
     const int first = a.s_begin, last = a.s_end;
 
     // both copies of theta: columns beyond p stay zero for good (rows are read at column 0 there)
     for (int c = tid; c < 2 * P_PAD; c += kSplitBlock) th[c] = c < p ? a.theta[c] : 0.f;
     if (tid < 2 * kRowWaves) pd_seq[tid] = 0u;
-    if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; }
+    if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_xconsumed = 0u; }
+    if (tid < NX) s_xarrived[tid] = 0u;
     __syncthreads();                                 // the only barrier: from here on the wavefronts meet through flags
 
     const StepGeometry geo(a);
     auto batch_rows = [&](int s) { return geo.batch_rows(s); };
     auto batch_base = [&](int s) { return geo.batch_base(s); };
 
-    const int rw = role_of(wave);
-    if (rw == -2) return;                            // they only keep the exchange wavefront's SIMD free of row loads
+    const int rw = wave - NX;
     if (rw >= 0) {
         // ------------------------------------------------------------------------------------ row wavefronts
         // Workgroup g takes rows g, g + G, g + 2 G, ... of a mini-batch, in groups of GR; a step has at least one
@@ -171,9 +177,9 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
         auto process = [&](Slot& S) {
             const bool live = su < last;
             if (ku == 0) {
-                // theta of this step: version su - first, delivered by the exchange wavefront
+                // theta of this step: version su - first, delivered by the exchange wavefronts
                 const unsigned want = (unsigned)(min(su, last) - first);
-                lds_wait_ge(version_addr, want, abort_addr);
+                lds_wait_ge(version_addr, NX * want, abort_addr);
                 const lds_f32* src = th + (want & 1u) * P_PAD + col0;
 #pragma unroll
                 for (int ch = 0; ch < CH; ++ch)
@@ -219,7 +225,7 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
             kg += 1u;
             const bool step_ends = live && ku + 1 >= nu;
             if (step_ends) {
-                // This lane's columns of the workgroup's sums go to shared memory; the exchange wavefront sends them
+                // This lane's columns of the workgroup's sums go to shared memory; the exchange wavefronts send them
                 // out (a store issued here would stand in this SIMD's queue behind the rows requested for the next
                 // step, for microseconds).
 #pragma unroll
@@ -244,10 +250,10 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
         return;                                      // rows requested beyond the last step land in registers that die here
     }
 
-    // ------------------------------------------------------------------------------------ exchange wavefront
-    const ExchangeLds x{th, P_PAD, xstate, nullptr, sums, P_PAD, (unsigned)kRowWaves,
-                        (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, nullptr, nullptr};
-    exchange_wavefront<OPT, 1, 1, 32, 32>(a, x, lane, 0);
+    // ------------------------------------------------------------------------------------ exchange wavefronts
+    const ExchangeLds x{th, P_PAD, xstate, xstate + kExchangeState * NX, sums, P_PAD, (unsigned)kRowWaves,
+                        (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
+    exchange_wavefront<OPT, NX, 1, 11, CH == 1 ? 6 : 11>(a, x, lane, wave);   // (a trip's words at once, for up to 256 workgroups and p columns)
 }
 
 using KernelFn = void (*)(GlmArgs);
@@ -262,7 +268,7 @@ KernelFn split_kernel(int ch, bool opt)
 
 size_t glm_split_lds_bytes(int ch)
 {
-    return (size_t)(3 * kRowWaves * 256 * ch + 2 * kRowWaves * kGroupRows + 2 * kRowWaves + kExchangeState + 16) * sizeof(float);
+    return (size_t)(3 * kRowWaves * 256 * ch + 2 * kRowWaves * kGroupRows + 2 * kRowWaves + (kExchangeState + kExchangeRed) * NX + 16) * sizeof(float);
 }
 
 int glm_split_block() { return kSplitBlock; }
