@@ -171,38 +171,49 @@ struct Deal {
     }
 };
 
-// KB groups of 512 classes, SP partial sums: every load of a row is issued up front
+// KB groups of 512 classes: the sum of the partial sums of row j, in their order.  Every load is issued up front, or as many as leave the
+// registers to what the whole kernel keeps in them.
 template <int KB, int SP>
+__device__ __forceinline__ void residual_sums(const SoftmaxPassArgs& a, __amdgpu_buffer_rsrc_t U, int j, int half, int lane, f32x4 (&sum)[KB])
+{
+    constexpr int G = SP * KB > 16 ? 16 / KB : SP;
+#pragma unroll
+    for (int s0 = 0; s0 < SP; s0 += G) {
+        f32x4 q[G][KB];
+#pragma unroll
+        for (int sp = 0; sp < G; ++sp)
+#pragma unroll
+            for (int k = 0; k < KB; ++k) {
+                const int c = min(4 * (lane + 64 * (half + 2 * k)), a.ldw - 4);
+                q[sp][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(U, (unsigned)c * 4u, (unsigned)(((size_t)(s0 + sp) * a.m_pad + j) * a.ldw * 4), kAgentScope));
+            }
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+            sum[k] = s0 == 0 ? q[0][k] : sum[k] + q[0][k];
+#pragma unroll
+            for (int sp = 1; sp < G; ++sp) sum[k] += q[sp][k];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// (One piece of code behind the sums, whatever their number: twelve copies were half of the kernel, and a kernel of 100 KB ran 5 % slower or faster
+// with where it came to lie in memory.)
+template <int KB>
 __device__ __forceinline__ void residual_rows(const SoftmaxPassArgs& a, __amdgpu_buffer_rsrc_t U, __amdgpu_buffer_rsrc_t R, const int* idx, int nb, int j0,
                                               float* red, int wave, int lane_)
 {
     const int lane = here(lane_);
     const int rr = wave >> 1, half = wave & 1, j = j0 + rr;
     const bool real = j < nb;
-    // (as many loads up front as leave the registers to what the whole kernel keeps in them)
-    constexpr int G = SP * KB > 16 ? 16 / KB : SP;
     f32x4 sum_q[KB];
     int label = -1;
     if (real) {
         label = a.y[idx[j]];
-#pragma unroll
-        for (int s0 = 0; s0 < SP; s0 += G) {
-            f32x4 q[G][KB];
-#pragma unroll
-            for (int sp = 0; sp < G; ++sp)
-#pragma unroll
-                for (int k = 0; k < KB; ++k) {
-                    const int c = min(4 * (lane + 64 * (half + 2 * k)), a.ldw - 4);
-                    q[sp][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(U, (unsigned)c * 4u, (unsigned)(((size_t)(s0 + sp) * a.m_pad + j) * a.ldw * 4), kAgentScope));
-                }
-#pragma unroll
-            for (int k = 0; k < KB; ++k) {
-                sum_q[k] = s0 == 0 ? q[0][k] : sum_q[k] + q[0][k];
-#pragma unroll
-                for (int sp = 1; sp < G; ++sp) sum_q[k] += q[sp][k];
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        if (a.splits == 1) residual_sums<KB, 1>(a, U, j, half, lane, sum_q);
+        else if (a.splits == 2) residual_sums<KB, 2>(a, U, j, half, lane, sum_q);
+        else if (a.splits == 4) residual_sums<KB, 4>(a, U, j, half, lane, sum_q);
+        else residual_sums<KB, 8>(a, U, j, half, lane, sum_q);
     }
     float u[KB][4], mx = -INFINITY;
     if (real) {
@@ -243,16 +254,6 @@ __device__ __forceinline__ void residual_rows(const SoftmaxPassArgs& a, __amdgpu
         for (int v = 0; v < 4; ++v) r[v] = real && c + v < a.C ? u[k][v] * inv - (c + v == label ? 1.f : 0.f) : 0.f;
         if (c < a.ldw) __builtin_amdgcn_raw_buffer_store_b64(to_bf16x4(r), R, (unsigned)c * 2u, (unsigned)((size_t)j * a.ldw * 2), kAgentScope);
     }
-}
-
-template <int KB>
-__device__ __forceinline__ void residual_splits(const SoftmaxPassArgs& a, __amdgpu_buffer_rsrc_t U, __amdgpu_buffer_rsrc_t R, const int* idx, int nb, int j0,
-                                                float* red, int wave, int lane)
-{
-    if (a.splits == 1) residual_rows<KB, 1>(a, U, R, idx, nb, j0, red, wave, lane);
-    else if (a.splits == 2) residual_rows<KB, 2>(a, U, R, idx, nb, j0, red, wave, lane);
-    else if (a.splits == 4) residual_rows<KB, 4>(a, U, R, idx, nb, j0, red, wave, lane);
-    else residual_rows<KB, 8>(a, U, R, idx, nb, j0, red, wave, lane);
 }
 
 // FT: features of an update tile; OPT: an update rule other than the plain step.
@@ -376,6 +377,23 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         for (int t = 0; t < kStages - 1; ++t)
             if (t < L.nt) l_request_x(t);
     };
+    // The rows of X that the next update's logits read here, into this die's L2 (a word from every line of 128 bytes, but for the first tiles,
+    // which come straight behind): each of the CG workgroups that have the rows in common takes its share, as far as kAhead loads go.
+    // us per update without and with: 32.0 / 30.8 (3072 features, 1024 rows, 1000 classes: products of the logits 8.4 / 5.6), 103 / 95 (4096, 2048,
+    // 2000); with seven tiles 22.6 / 23.3 (800, 1024, 1000, Adam).
+    constexpr int kAhead = 2, kAheadTiles = 8;       // loads of a thread; tiles of the logits' depth from which it pays
+    struct Ahead {
+        unsigned v[kAhead];
+    };
+    auto l_ahead = [&](Ahead& w, const int* idx, int nb, int cc) {
+        const int lines = TR * (L.nt - (kStages - 1)), tid_ = here(tid);
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) {
+            const int e = (cc + CG * h) * kThreads + tid_, r = e % TR, t = kStages - 1 + e / TR;
+            w.v[h] = 0;
+            if (e < lines) w.v[h] = *reinterpret_cast<const unsigned*>(a.X + (size_t)idx[min(L.rt * TR + r, nb - 1)] * a.p + L.kb + t * TK);
+        }
+    };
     // the sums of the two wavefronts of a pair over the halves of the depth: each adds up and keeps two of its four rows of tiles
     // (classes); acc[0], acc[1] hold them afterwards
     auto meet_halves = [&](auto& acc) {
@@ -478,12 +496,15 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         gx_row[h] = r;
         gx_col[h] = ((q % NCX) ^ (2 * (r & kSwz))) * 8;
     }
+    auto g_put = [&](const unsigned short* src, int t, int h) {
+        load_to_lds(src, lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
+    };
     auto g_src = [&](int row, int col) { return a.X + (size_t)row * a.p + min(g_ft * FT + col, a.p - 8); };
     auto g_request_x = [&](int t, const int* idx, int nb) {
 #pragma unroll
         for (int h = 0; h < LX; ++h) {
             if (wave + kWaves * h >= NCX) continue;
-            load_to_lds(g_src(idx[min(t * TK + here(gx_row[h]), nb - 1)], here(gx_col[h])), lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
+            g_put(g_src(idx[min(t * TK + here(gx_row[h]), nb - 1)], here(gx_col[h])), t, h);
         }
     };
     // (the residual of rows beyond the mini-batch is zero)
@@ -502,16 +523,28 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
 #pragma unroll
         for (int j = 0; j < NF; ++j) rd_x[q][j] = (unsigned)(row * FT * 2 + ((2 * (NF * wm + j) + half) ^ (2 * (row & kSwz))) * 16 + (l16 & 1) * 8);
     }
-    // master weights (from clamped addresses): this lane's four classes of each of its features
-    auto g_weights = [&](f32x4 (&w)[2][NF]) {
+    // master weights: this lane's four classes of each of its features
+    struct Block {
+        f32x4 v[2][NF];
+    };
+    auto g_load = [&](Block& b, const float* from) { // (from clamped addresses)
         const int lane = here(tid) & 63, l16 = lane & 15, lq = lane >> 4;
         const int f0 = g_ft * FT + wm * FW + l16, c0 = g_ct * TC + wn * 64 + 32 * kh + 4 * lq;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < NF; ++j) w[i][j] = *reinterpret_cast<const f32x4*>(a.W + (size_t)min(f0 + 16 * j, a.p - 1) * a.ldw + c0 + 16 * i);
+            for (int j = 0; j < NF; ++j) b.v[i][j] = *reinterpret_cast<const f32x4*>(from + (size_t)min(f0 + 16 * j, a.p - 1) * a.ldw + c0 + 16 * i);
     };
-    auto g_rest = [&](int s, const int* idx, int nb, f32x4 (&w)[2][NF]) {
+    auto g_store = [&](const Block& b, float* to) {
+        const int lane = here(tid) & 63, l16 = lane & 15, lq = lane >> 4;
+        const int f0 = g_ft * FT + wm * FW + l16, c0 = g_ct * TC + wn * 64 + 32 * kh + 4 * lq;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NF; ++j)
+                if (f0 + 16 * j < a.p) *reinterpret_cast<f32x4*>(to + (size_t)(f0 + 16 * j) * a.ldw + c0 + 16 * i) = b.v[i][j];
+    };
+    auto g_rest = [&](int s, const int* idx, int nb, Block& w) {
         const int nt = (nb + TK - 1) / TK;
         const int lane = here(tid) & 63, rrow = 4 * wave + (lane >> 4);
         const unsigned short* const rs = a.R + (size_t)rrow * a.ldw + g_ct * TC + ((lane & 15) ^ (2 * (rrow & 7))) * 8;
@@ -541,7 +574,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
 #pragma unroll
             for (int h = 0; h < LX; ++h) {
                 if (wave + kWaves * h >= NCX) continue;
-                load_to_lds(g_src(ahead[h], gx_col[h]), lds0 + (unsigned)(t % kStages) * kStageBytes + (unsigned)(wave + kWaves * h) * 1024);
+                g_put(g_src(ahead[h], gx_col[h]), t, h);
             }
             request_r(t);
             look_up(t + 1);
@@ -576,7 +609,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         };
         if (LX == LXLess || wave < kMoreLoads) walk_tiles<LX + 2, Rows>(nt, request, read, begin, multiply);
         else walk_tiles<LXLess + 2, Rows>(nt, request, read, begin, multiply);
-        if constexpr (!kEarlyWeights) g_weights(w);
+        if constexpr (!kEarlyWeights) g_load(w, a.W);
         meet_halves(acc);
         const int tid_ = here(tid), l16 = tid_ & 15, lq = (tid_ & 63) >> 4;
         const int f0 = g_ft * FT + wm * FW + l16, c0 = g_ct * TC + wn * 64 + 32 * kh + 4 * lq;
@@ -590,18 +623,18 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
 #pragma unroll
             for (int j = 0; j < NF; ++j) {
                 const int f = f0 + 16 * j, c = c0 + 16 * i;
-                const size_t at = (size_t)min(f, a.p - 1) * a.ldw + c;
                 float nw[4];
                 if constexpr (!OPT) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) nw[v] = w[i][j][v] - scale * acc[i][j][v];
+                    for (int v = 0; v < 4; ++v) nw[v] = w.v[i][j][v] - scale * acc[i][j][v];
                 } else {
+                    const size_t at = (size_t)min(f, a.p - 1) * a.ldw + c;
                     f32x4 m = *reinterpret_cast<const f32x4*>(a.opt.m + at), sv = {0.f, 0.f, 0.f, 0.f};
                     if (a.opt.kind == kOptAdam) sv = *reinterpret_cast<const f32x4*>(a.opt.s + at);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         float mv = m[v], s2 = sv[v];
-                        nw[v] = opt_update(a.opt, w[i][j][v], acc[i][j][v] * inv_nb, alpha, mv, s2, oc1, oc2);
+                        nw[v] = opt_update(a.opt, w.v[i][j][v], acc[i][j][v] * inv_nb, alpha, mv, s2, oc1, oc2);
                         m[v] = c + v < a.C ? mv : 0.f;
                         sv[v] = c + v < a.C ? s2 : 0.f;
                     }
@@ -613,7 +646,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
                 // (classes beyond C stay zero whatever the rows hold)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) nw[v] = c + v < a.C ? nw[v] : 0.f;
-                if (f < a.p) *reinterpret_cast<f32x4*>(a.W + at) = f32x4{nw[0], nw[1], nw[2], nw[3]};
+                w.v[i][j] = f32x4{nw[0], nw[1], nw[2], nw[3]};
                 const u32x2 b = to_bf16x4(nw);
                 const int cl = wn * 64 + 32 * kh + 16 * i + 4 * lq, fl = wm * FW + 16 * j + l16;
                 Ts[(cl + 0) * (FT + 8) + fl] = (unsigned short)b.x;
@@ -643,8 +676,13 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     request_idx(0, 0, min(a.n, a.rows), 0);
     wait_loads<0>();
     wg_barrier();
-    const int l_first = rank < dl.rounds() ? dl.item(rank) : -1, g_first = rank < dg.rounds() ? dg.item(rank) : -1;
-    if (l_first >= 0) { l_at(l_first); l_begin(idx_all, min(a.n, a.rows)); }
+    const int l_first = rank < dl.rounds() ? dl.item(rank) : -1, r_first = rank < dr.rounds() ? dr.item(rank) : -1, g_first = rank < dg.rounds() ? dg.item(rank) : -1;
+    // (where the first items of each update stand is worked out once: a division is 0.1 us)
+    if (l_first >= 0) l_at(l_first);
+    const Logits L_first = L;
+    if (g_first >= 0) g_at(g_first);
+    const int g_ft_first = g_ft, g_ct_first = g_ct, cc_first = max(l_first, 0) % CG;
+    if (l_first >= 0) l_begin(idx_all, min(a.n, a.rows));
     for (int s = 0, t = 0, m = 0; s < updates; ++s) {
         const int nb = min(a.n, a.rows - m * a.n);
         const int* const idx = idx_all + (s & 1) * kMaxRows;
@@ -659,34 +697,43 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         // the next update's row numbers, and the first rows of X for this one's update
         const int m1 = m + 1 < M ? m + 1 : 0, t1 = m + 1 < M ? t : t + 1, nb1 = min(a.n, a.rows - m1 * a.n);
         if (s + 1 < updates) request_idx(t1, m1, nb1, (s + 1) & 1);
-        if (g_first >= 0) { g_at(g_first); g_begin(idx, nb); }
+        if (g_first >= 0) { g_ft = g_ft_first; g_ct = g_ct_first; g_begin(idx, nb); }
         for (int k = rank; k < dr.rounds(); k += nwg) {
             const int item = dr.item(k);
             if (item < 0) continue;
             const int j0 = item * kRowsPerItem;
             if (!await(IntC<kSubs>{}, cnt_u + (size_t)(j0 / TR) * kSubs * kLine, S * tiles_c, (unsigned)s + 1)) return;
-            if (a.ldw <= 512) residual_splits<1>(a, U, R, idx, nb, j0, red, wave, lane);
-            else if (a.ldw <= 1024) residual_splits<2>(a, U, R, idx, nb, j0, red, wave, lane);
-            else residual_splits<4>(a, U, R, idx, nb, j0, red, wave, lane);
+            if (a.ldw <= 512) residual_rows<1>(a, U, R, idx, nb, j0, red, wave, lane);
+            else if (a.ldw <= 1024) residual_rows<2>(a, U, R, idx, nb, j0, red, wave, lane);
+            else residual_rows<4>(a, U, R, idx, nb, j0, red, wave, lane);
             arrive(cnt_r + (size_t)(item % kRSubs) * kLine);
+        }
+        Ahead ahead{};
+        if (r_first >= 0 && l_first >= 0 && L_first.nt >= kAheadTiles && s + 1 < updates && L_first.rt * TR < nb1) {
+            L = L_first;
+            l_ahead(ahead, idx_all + ((s + 1) & 1) * kMaxRows, nb1, cc_first);
         }
         for (int k = rank; k < dg.rounds(); k += nwg) {
             const int item = dg.item(k);
             if (item < 0) continue;
             if (k != rank) { g_at(item); g_begin(idx, nb); }
-            f32x4 w[2][NF];
-            if constexpr (kEarlyWeights) g_weights(w);
+            Block w;
+            if constexpr (kEarlyWeights) g_load(w, a.W);
             if (!await(IntC<kRSubs>{}, cnt_r, dr.items, (unsigned)s + 1)) return;
             g_rest(s, idx, nb, w);
             arrive(cnt_w + (size_t)(g_ct * kSubs + g_ft % kSubs) * kLine);
+            g_store(w, a.W);                         // what only this workgroup reads again leaves behind what the others wait for
         }
+        asm volatile("" :: "v"(ahead.v[0]), "v"(ahead.v[1]));
         t = t1;
         m = m1;
         if (s + 1 < updates) {
-            // (the row numbers have landed for this wavefront; for all behind the barrier)
-            wait_loads<0>();
-            wg_barrier();
-            if (l_first >= 0) { l_at(l_first); l_begin(idx_all + ((s + 1) & 1) * kMaxRows, nb1); }
+            // (behind an arrival the row numbers have landed for the whole workgroup)
+            if (g_first < 0) {
+                wait_loads<0>();
+                wg_barrier();
+            }
+            if (l_first >= 0) { L = L_first; l_begin(idx_all + ((s + 1) & 1) * kMaxRows, nb1); }
         }
     }
 }
