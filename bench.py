@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # HBM traffic of one launch of the chain kernel on the primary workload, from rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE (see profiles/), scaled by the copy calibration; valid only for the source of the kernel it was measured on
 # (the line reports null once that file has changed: measure again and update the entry).
-TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641623}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip'), "kernel_sha256": "1e0e0132e0bb7600e5e3758b5c3d08d03d9cc0199f344ec767e63606c273e4b2", "bytes_per_launch": 217067689}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "bb929c0c931a574a6211b12606292fef9f6024416c4e07e74403bfa9cdbe2256", "bytes_per_launch": 2473703590}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "cbf89e731fbcf2bca181eda6faffc944306b69253e0ac288b23bce5654809194", "bytes_per_launch": 9431031329}}
+TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641623}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip', 'lds_load.h'), "kernel_sha256": "8401295e3c269731060e1cd884d0fff3700bd010771e991cda55207d721b04b5", "bytes_per_launch": 216723379}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "abe5e236b3d084c47f2e084ee0de8da34ae914ab60878a7c07006d073e741fe2", "bytes_per_launch": 2473796640}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "700f40ce3bfed5ca7b61f023e2156aee3b75470d5bfe4169ce7e93076871af20", "bytes_per_launch": 9417697408}}
 
 
 def _kernel_sha(sources) -> str:
@@ -157,7 +157,7 @@ def _roofline(w, delta, traffic=None):
         achieved = flops / (delta["chain_ms"] / 1e3) / 1e12
         return {"bound": "mfma", "achieved": round(achieved, 2), "peak": 2500.0, "unit": "TFLOP/s",
                 "frac": round(achieved / 2500.0, 5), "traffic": None,
-                "kernel": "gemm_nt_kernel (logits, gradient+update) + softmax_residual_kernel"}
+                "kernel": "softmax_pass_kernel"}
     bytes_per_launch = _algorithmic_bytes_per_sample_gradient(w) * delta["sample_gradients"] / max(delta["chain_launches"], 1)
     if delta.get("chain") in (3, 5):
         # Least squares in the form of eq. (3.1): the rows are read by the kernel that forms the moment matrices
@@ -177,7 +177,7 @@ def _roofline(w, delta, traffic=None):
         return {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic,
                 "kernel": "gram_chain_kernel" if per_launch_s >= prep_s
-                          else ("gram_mfma_kernel + affine_pair_kernel" if delta.get("chain") == 5 else "gram_mfma_kernel"),
+                          else ("gram_rows_kernel + affine_pair_kernel" if delta.get("chain") == 5 else "gram_rows_kernel"),
                 "avg_launch_ms": round(dominant_s * 1e3, 4),
                 "algorithmic_bytes_per_launch": int(bytes_per_launch),
                 "moments_kernel": {"avg_launch_ms": round(prep_s * 1e3, 4),
@@ -193,7 +193,7 @@ def _roofline(w, delta, traffic=None):
     return {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic,
             # persistent kernels by their workgroup size: 11 wavefronts (rows wider than 1024 floats: eight row wavefronts
-            # and an exchange wavefront alone on its SIMD), 12 or 16 (narrower rows whose share of a step fits the registers:
+            # and three exchange wavefronts), 12 or 16 (narrower rows whose share of a step fits the registers:
             # eight or twelve row wavefronts and four exchange wavefronts; the general kernel has 16 as well, but no workload
             # here takes it in this mode); one launch per step: the general kernel
             "kernel": {704: "glm_split_kernel", 768: "glm_narrow_kernel", 1024: "glm_narrow_kernel"}[delta["threads_per_group"]]
