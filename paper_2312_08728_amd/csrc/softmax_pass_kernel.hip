@@ -197,8 +197,7 @@ __device__ __forceinline__ void residual_sums(const SoftmaxPassArgs& a, __amdgpu
     }
 }
 
-// (One piece of code behind the sums, whatever their number: twelve copies were half of the kernel, and a kernel of 100 KB ran 5 % slower or faster
-// with where it came to lie in memory.)
+// (One piece of code behind the sums, whatever their number: twelve copies were half of the kernel.)
 template <int KB>
 __device__ __forceinline__ void residual_rows(const SoftmaxPassArgs& a, __amdgpu_buffer_rsrc_t U, __amdgpu_buffer_rsrc_t R, const int* idx, int nb, int j0,
                                               float* red, int wave, int lane_)
