@@ -125,9 +125,10 @@ enum {
                                     state p <= 512 and batch_n p <= 2^17).  Its workgroups meet before the first update; where
                                     other work keeps some of them from running for as long as one alone would need for the pass,
                                     or for an eighth of barrier_timeout_us, one of them makes the pass alone: slower, the same
-                                    sums, and not an error.  Other mini-batches of up to 2,048 rows: all updates of up to four
-                                    passes in one persistent kernel, whose workgroups meet likewise; those that have come in time
-                                    share the work. */
+                                    sums, and not an error.  Other mini-batches of up to 2,048 rows: the updates of up
+                                    to four passes in persistent kernels whose workgroups meet likewise; those that have come in time
+                                    share the work.  Each makes as many updates as one workgroup alone makes in an eighth of
+                                    barrier_timeout_us (at most of the default), or one, and then lets go of the compute units. */
     BMGD_CHAIN_PRODUCT = 5       /* least squares with p <= 128 and plain steps (BMGD_OPT_SGD) only: the moment form of
                                     BMGD_CHAIN_GRAM with steps multiplied together.  A step of eq. (3.1) is the affine map
                                     [theta; 1] <- A_m [theta; 1], A_m = [[I - alpha Sxx_m, alpha Sxy_m], [0, 1]], and no A_m

@@ -61,6 +61,7 @@ constexpr size_t kMailFlags = 256;
 constexpr size_t kMailHead = kMailFlags + kEvalBlocks * sizeof(double);
 constexpr size_t kMailArea = size_t(1) << 20;      // at most; contexts with a smaller theta take what they need
 constexpr size_t kMaxOpenRuns = 4096;              // runs whose events are held before the oldest half is folded
+constexpr long long kDefaultTicks = 200000000;     // of the device's clock (100 MHz): limit on its waits where barrier_timeout_us is 0
 
 }  // namespace
 
@@ -632,7 +633,7 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
     const int64_t M = batches_of(rows, n);
     const bool fixed = c.reshuffle == BMGD_RESHUFFLE_FIXED;
     const uint32_t b = (uint32_t)(fixed && c.n_buffers > 0 ? ctx->buffer_counter % c.n_buffers : ctx->buffer_counter);
-    const long long ticks = (c.barrier_timeout_us > 0 ? c.barrier_timeout_us : 2000000) * 100LL;
+    const long long ticks = c.barrier_timeout_us > 0 ? c.barrier_timeout_us * 100LL : kDefaultTicks;
     const int lr_len = (int)ctx->lr_tab_host.size();
     // checked before anything is enqueued: step indices inside one launch stay below 2^23
     if (c.model != BMGD_SOFTMAX && ctx->chain != BMGD_CHAIN_GRAM &&
@@ -796,15 +797,15 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                 sa.ldwt = dmax.p_pad;
                 sa.rows = (int)rows; sa.n = (int)n; sa.p = (int)c.p; sa.C = c.n_classes;
                 sa.sync = ctx->sync;
-                // (limits as for the kernel of small mini-batches below; an update of all workgroups takes up to 25 us)
-                sa.timeout_ticks = 1000000000LL;
-                sa.meeting_ticks = ticks < 1000 ? 0 : std::min<long long>(std::min<long long>(ticks / 8, 200000000LL), std::max<long long>(100000, 2500 * M * np));
+                sa.timeout_ticks = 1000000000LL;     // (of waits that end by themselves: see below)
                 sa.alpha = (float)c.lr;
                 sa.lr_tab = lr_len ? ctx->lr_tab_dev : nullptr;
                 sa.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
                 sa.lr_len = lr_len;
                 sa.opt = opt_args(ctx, 0);
-                HIP_TRY(ctx, softmax_pass(sa, d, ctx->xt, ctx->num_cus, stream));
+                // Compute units are kept from other work, a persistent kernel of another context with the same limit or the default one
+                // among it, for an eighth of that limit at a time.
+                HIP_TRY(ctx, softmax_pass(sa, d, ctx->xt, ctx->num_cus, std::min(ticks, kDefaultTicks) / 8, stream));
                 ctx->lr_pos += (int64_t)np * M;
                 ctx->opt_k += (int64_t)np * M;
             }

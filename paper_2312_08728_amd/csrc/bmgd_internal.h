@@ -317,7 +317,7 @@ size_t softmax_chain_words_bytes(int64_t n, int64_t C);
 hipError_t softmax_chain_prepare(int64_t p, int64_t n, int64_t C, bool opt, int num_cus, bool* fits);
 // One pass (two launches in stream order): the mini-batches of `perm` packed into `pack`, then their updates.
 hipError_t softmax_chain_pass(const void* X, const int32_t* y, const int32_t* perm, void* pack, SoftmaxChainArgs args, hipStream_t stream);
-// Large mini-batches: the updates of up to kMaxPassesPerLaunch passes in one persistent kernel (softmax_pass_kernel.hip).
+// Large mini-batches: the updates of up to kMaxPassesPerLaunch passes in persistent kernels of many updates each (softmax_pass_kernel.hip).
 struct SoftmaxPassArgs {
     const unsigned short* X;    // bf16 [rows][p]
     const int* y;
@@ -330,22 +330,25 @@ struct SoftmaxPassArgs {
     int rows, n, p, C;
     unsigned* sync;         // [1] abort flag
     long long timeout_ticks;       // of a wait for workgroups known to be running
-    long long meeting_ticks;       // how long the first workgroup waits for the others; 0: not at all, it makes the passes alone
     float alpha;
     const float* lr_tab;    // optional learning rate per update: update s uses lr_tab[min(lr_base + s, lr_len - 1)]
     int lr_base, lr_len;
     OptArgs opt;            // state arrays laid out like W; k_base = updates made before the launch
     // filled in by softmax_pass
+    long long meeting_ticks;       // how long the first workgroup waits for the others; 0: not at all, it makes the updates alone
     int M, m_pad, n_pad, splits, k_per_split;
-    unsigned* meeting;
+    int s_begin, s_end;            // updates of this launch, counted from the first of all passes
+    unsigned* meeting;             // of this launch, and of the next, which this one clears
+    unsigned* next_meeting;
     unsigned* counters;
 };
 bool softmax_pass_eligible(int64_t p, int64_t n, int64_t C);
 size_t softmax_pass_counter_bytes(const SoftmaxDims& d);
 // *fits: the kernel can run on this device
 hipError_t softmax_pass_prepare(int64_t p, int64_t n, int64_t C, bool opt, int num_cus, bool* fits);
-// One launch (and one that clears the counters, in stream order); d: of the launch's mini-batch size, with ldw columns
-hipError_t softmax_pass(SoftmaxPassArgs args, const SoftmaxDims& d, void* counters, int num_cus, hipStream_t stream);
+// A launch that clears the counters and then as many as it takes for none to last longer than hold_ticks whatever workgroups come, but for one of
+// a single update; d: of the mini-batches' size, with ldw columns
+hipError_t softmax_pass(SoftmaxPassArgs args, const SoftmaxDims& d, void* counters, int num_cus, long long hold_ticks, hipStream_t stream);
 // WbT <- bf16(W) transposed, whole matrix.
 hipError_t softmax_refresh_shadow(const float* W, void* WbT, int p, const SoftmaxDims& d, hipStream_t stream);
 

@@ -22,6 +22,9 @@
 //
 // All workgroups that take part must be running.  They meet before the first update; if some have not come in time, those that are
 // there share the work among themselves (parts of a phase are dealt round): the same sums in the same order, down to one workgroup.
+// A workgroup keeps its compute unit to itself from the meeting to the end of the launch, and another persistent kernel that waits for
+// that unit gives up after its limit.  So a launch makes only as many updates as one workgroup alone makes in an eighth of the limit
+// (softmax_pass); the next one goes on from there, with the counters as they are, and meets again.
 #include "bmgd_internal.h"
 #include "glm_device.h"
 #include "lds_load.h"
@@ -313,6 +316,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     wg_barrier();
     const int rank = __builtin_amdgcn_readfirstlane(s_rank), nwg = __builtin_amdgcn_readfirstlane(s_nwg);
     if (rank >= nwg) return;                         // came too late
+    if (rank == 0 && tid == 0) *a.next_meeting = 0;  // (the word of the launch before, which has ended, is that of the next one)
 
     const int S = a.splits, tiles_c = a.ldw / TC, tiles_r = a.m_pad / TR, tiles_f = (a.p + FT - 1) / FT;
     const Deal dl(S * tiles_r * tiles_c), dr(a.n_pad / kRowsPerItem), dg(tiles_f * tiles_c);
@@ -671,8 +675,10 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
             load_word_to_lds(src + min(c * 64 + lane, nb - 1), lds0 + kIdxAt + (unsigned)which * (kMaxRows * 4) + (unsigned)c * 256);
     };
 
-    const int M = a.M, updates = a.npass * M;
-    request_idx(0, 0, min(a.n, a.rows), 0);
+    const int M = a.M, updates = a.s_end;
+    const int t_begin = a.s_begin / M, m_begin = a.s_begin - t_begin * M, nb_begin = min(a.n, a.rows - m_begin * a.n);
+    const int* const idx_begin = idx_all + (a.s_begin & 1) * kMaxRows;
+    request_idx(t_begin, m_begin, nb_begin, a.s_begin & 1);
     wait_loads<0>();
     wg_barrier();
     const int l_first = rank < dl.rounds() ? dl.item(rank) : -1, r_first = rank < dr.rounds() ? dr.item(rank) : -1, g_first = rank < dg.rounds() ? dg.item(rank) : -1;
@@ -681,8 +687,8 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     const Logits L_first = L;
     if (g_first >= 0) g_at(g_first);
     const int g_ft_first = g_ft, g_ct_first = g_ct, cc_first = max(l_first, 0) % CG;
-    if (l_first >= 0) l_begin(idx_all, min(a.n, a.rows));
-    for (int s = 0, t = 0, m = 0; s < updates; ++s) {
+    if (l_first >= 0) l_begin(idx_begin, nb_begin);
+    for (int s = a.s_begin, t = t_begin, m = m_begin; s < updates; ++s) {
         const int nb = min(a.n, a.rows - m * a.n);
         const int* const idx = idx_all + (s & 1) * kMaxRows;
         for (int k = rank; k < dl.rounds(); k += nwg) {
@@ -762,6 +768,17 @@ int pass_features(int p, int tiles_c, int num_cus)
     return best;
 }
 
+// Ticks of the device's clock (100 MHz) that one workgroup takes for an update alone: its tiles of both contractions, 64 deep or 64 rows long,
+// and what an item costs besides.  ms, measured / as here: 6.0 / 6.8 (3072 features, 1024 rows, 1000 classes; Adam 7.9 / 10.3), 20.4 / 24.0 (4096,
+// 2048, 2000; Adam 29.7 / 33.2), 30.9 / 29.2 (16384, 512, 2000), 3.7 / 2.9 (4096, 250, 1000), 1.15 / 1.47 (1160, 651, 247), 1.2 / 1.4 (8, 2048, 2).
+long long pass_alone_ticks(const SoftmaxDims& d, int p, int ft, bool opt)
+{
+    const long long tiles_c = d.c_pad / TC, tiles_r = d.m_pad / TR, tiles_f = (p + ft - 1) / ft;
+    const long long logits = d.splits * tiles_r * tiles_c, depth = tiles_r * tiles_c * ((p + TK - 1) / TK);
+    const long long residual = d.n_pad / kRowsPerItem, update = tiles_f * tiles_c;
+    return 400 * logits + 75 * depth + 250 * residual + update * (400 + 45 * (d.n_pad / TK) + (opt ? 14 * ft : 0));
+}
+
 int pass_groups(const SoftmaxDims& d, int p, int num_cus, int ft)
 {
     const int tiles_c = d.c_pad / TC;
@@ -773,7 +790,7 @@ int pass_groups(const SoftmaxDims& d, int p, int num_cus, int ft)
 
 size_t softmax_pass_counter_bytes(const SoftmaxDims& d)
 {
-    return (size_t)(1 + d.m_pad / TR * kSubs + kRSubs + d.c_pad / TC * kSubs) * kLine * 4;
+    return (size_t)(2 + d.m_pad / TR * kSubs + kRSubs + d.c_pad / TC * kSubs) * kLine * 4;
 }
 
 bool softmax_pass_eligible(int64_t p, int64_t n, int64_t C)
@@ -795,7 +812,7 @@ hipError_t softmax_pass_prepare(int64_t p, int64_t n, int64_t C, bool opt, int n
     return hipSuccess;
 }
 
-hipError_t softmax_pass(SoftmaxPassArgs a, const SoftmaxDims& d, void* counters, int num_cus, hipStream_t stream)
+hipError_t softmax_pass(SoftmaxPassArgs a, const SoftmaxDims& d, void* counters, int num_cus, long long hold_ticks, hipStream_t stream)
 {
     if (a.n > kMaxRows || d.c_pad != a.ldw || d.m_pad / TR * TR != d.m_pad) return hipErrorInvalidValue;
     a.M = (a.rows + a.n - 1) / a.n;
@@ -803,13 +820,26 @@ hipError_t softmax_pass(SoftmaxPassArgs a, const SoftmaxDims& d, void* counters,
     a.n_pad = d.n_pad;
     a.splits = d.splits;
     a.k_per_split = d.k_per_split;
-    a.meeting = static_cast<unsigned*>(counters);
-    a.counters = a.meeting + kLine;
+    unsigned* const meetings = static_cast<unsigned*>(counters);
+    a.counters = meetings + 2 * kLine;
     hipError_t e = launch_fill_zero(counters, softmax_pass_counter_bytes(d), stream);
     if (e != hipSuccess) return e;
     const int ft = pass_features(a.p, d.c_pad / TC, num_cus);
-    hipLaunchKernelGGL(pass_kernel(ft, a.opt.kind != kOptSgd), dim3((unsigned)pass_groups(d, a.p, num_cus, ft)), dim3(kThreads), kLds, stream, a);
-    return hipGetLastError();
+    const bool opt = a.opt.kind != kOptSgd;
+    const dim3 grid((unsigned)pass_groups(d, a.p, num_cus, ft));
+    const int updates = a.npass * a.M;
+    // (a launch of all workgroups then lasts 1 to 15 ms with the default limit; the start and end of each cost about 10 us: 1 % and less)
+    const int per_launch = (int)std::min<long long>(std::max(1LL, hold_ticks / pass_alone_ticks(d, a.p, ft, opt)), updates);
+    for (int s = 0, launch = 0; s < updates; s += per_launch, ++launch) {
+        a.s_begin = s;
+        a.s_end = std::min(updates, s + per_launch);
+        a.meeting = meetings + (launch & 1) * kLine;
+        a.next_meeting = meetings + (~launch & 1) * kLine;
+        a.meeting_ticks = hold_ticks < 125 ? 0 : std::min<long long>(hold_ticks, std::max(100000, 2500 * (a.s_end - s)));
+        hipLaunchKernelGGL(pass_kernel(ft, opt), grid, dim3(kThreads), kLds, stream, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace bmgd

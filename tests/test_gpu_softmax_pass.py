@@ -139,3 +139,78 @@ def test_values_that_are_not_finite(bad):
     ctx.run_device_buffer(clean, yd, 260, s)
     assert np.array_equal(again, ctx.get_theta()) and np.isfinite(again).all()
     ctx.close()
+
+
+def _streams(k):
+    """Streams whose work runs side by side (HIP spreads streams over a few hardware queues)."""
+    import time
+    import torch
+    got = []
+    for _ in range(10):
+        s, free = torch.cuda.Stream(), True
+        for other in got:
+            torch.cuda.synchronize()
+            with torch.cuda.stream(other):
+                torch.cuda._sleep(40_000_000)
+            e = torch.cuda.Event()
+            e.record(s)
+            time.sleep(0.003)
+            free = free and e.query()
+        torch.cuda.synchronize()
+        if free:
+            got.append(s)
+        if len(got) == k:
+            return got
+    pytest.fail("no streams that run side by side")
+
+
+class _Holder:
+    """A run of the logistic persistent kernel that keeps `units` compute units for about `ms` milliseconds in one launch: 3.1 us an update
+    on 152 to 256 of them."""
+
+    def __init__(self, units, ms):
+        import torch
+        import paper_2312_08728_amd as B
+        self.rows = 64 * int(ms / 4 / 3.13e-3)
+        self.x, self.y = torch.randn((self.rows, 16), device="cuda"), torch.ones(self.rows, device="cuda")
+        self.ctx = B.Context(16, self.rows, 64, 0.01, 4, model=B.BMGD_LOGISTIC, chain=B.BMGD_CHAIN_PERSISTENT, n_workgroups=units)
+        assert self.ctx.stats().n_workgroups == units
+        self.free = torch.cuda.Event(enable_timing=True)
+
+    def start(self, stream):
+        import time
+        self.ctx.run_device_buffer(self.x, self.y, self.rows, stream)
+        self.free.record(stream)
+        time.sleep(0.004)
+        assert not self.free.query()
+
+
+def test_a_persistent_kernel_gets_the_units_that_it_waits_for():
+    """Softmax runs on the eight compute units that another context leaves it, then the next run of that stream wants all of them, with a limit
+    of 50 ms: the softmax run (100 updates a pass, 0.7 ms each on eight units) lets go of them in time."""
+    import torch
+    import paper_2312_08728_amd as B
+    p, C, n, M = 2048, 1000, 1024, 100
+    x, y = torch.randn((M * n, p), device="cuda", dtype=torch.bfloat16), torch.arange(M * n, device="cuda", dtype=torch.int32) % C
+    gx, gy = torch.randn((4096, 16), device="cuda"), torch.ones(4096, device="cuda")
+    s, t = _streams(2)
+    results = []
+    for together in (False, True):
+        soft = B.Context(p, M * n, n, 0.01, 4, model=B.BMGD_SOFTMAX, n_classes=C, barrier_timeout_us=400_000)
+        glm = B.Context(16, 4096, 64, 0.01, 4, model=B.BMGD_LOGISTIC, chain=B.BMGD_CHAIN_PERSISTENT, n_workgroups=256, barrier_timeout_us=50_000)
+        holder = _Holder(248, 130)
+        torch.cuda.synchronize()
+        if together:
+            holder.start(s)
+        glm.run_device_buffer(gx, gy, 4096, s)
+        began = torch.cuda.Event(enable_timing=True)
+        began.record(t)
+        if not together:
+            glm.sync()
+        soft.run_device_buffer(x, y, M * n, t)
+        results.append((glm.get_theta(), soft.get_theta()))
+        assert not together or began.elapsed_time(holder.free) > 60
+        for c in (soft, glm, holder.ctx):
+            c.close()
+    for a, b in zip(*results):
+        assert np.isfinite(a).all() and np.array_equal(a, b)
