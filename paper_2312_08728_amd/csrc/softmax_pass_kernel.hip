@@ -829,13 +829,15 @@ hipError_t softmax_pass(SoftmaxPassArgs a, const SoftmaxDims& d, void* counters,
     const dim3 grid((unsigned)pass_groups(d, a.p, num_cus, ft));
     const int updates = a.npass * a.M;
     // (a launch of all workgroups then lasts 1 to 15 ms with the default limit; the start and end of each cost about 10 us: 1 % and less)
-    const int per_launch = (int)std::min<long long>(std::max(1LL, hold_ticks / pass_alone_ticks(d, a.p, ft, opt)), updates);
+    const long long alone = pass_alone_ticks(d, a.p, ft, opt);
+    const int per_launch = (int)std::min<long long>(std::max(1LL, hold_ticks / alone), updates);
     for (int s = 0, launch = 0; s < updates; s += per_launch, ++launch) {
         a.s_begin = s;
         a.s_end = std::min(updates, s + per_launch);
         a.meeting = meetings + (launch & 1) * kLine;
         a.next_meeting = meetings + (~launch & 1) * kLine;
-        a.meeting_ticks = hold_ticks < 125 ? 0 : std::min<long long>(hold_ticks, std::max(100000, 2500 * (a.s_end - s)));
+        // the others are waited for as long as one alone would take (1 ms at least), but not longer than a launch may last
+        a.meeting_ticks = hold_ticks < 125 ? 0 : std::min(hold_ticks, std::max(100000LL, alone * (a.s_end - s)));
         hipLaunchKernelGGL(pass_kernel(ft, opt), grid, dim3(kThreads), kLds, stream, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

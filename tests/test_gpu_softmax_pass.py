@@ -214,3 +214,42 @@ def test_a_persistent_kernel_gets_the_units_that_it_waits_for():
             c.close()
     for a, b in zip(*results):
         assert np.isfinite(a).all() and np.array_equal(a, b)
+
+
+def _workspace(p, rows, n, C, T, **limits):
+    """A workspace for a softmax context, of zeros, and the arguments that hand it over."""
+    import torch
+    import paper_2312_08728_amd as B
+    cfg = B.bmgd_default_config()
+    cfg.p, cfg.buffer_n, cfg.batch_n, cfg.lr, cfg.passes = p, rows, n, 0.01, T
+    cfg.model, cfg.n_classes, cfg.x_dtype = B.BMGD_SOFTMAX, C, B.BMGD_BF16
+    size = B.bmgd_workspace_bytes(cfg)
+    area = torch.zeros(size, dtype=torch.uint8, device="cuda")
+    return area, dict(workspace=area, workspace_bytes=size, **limits)
+
+
+def _came_in_time(area):
+    """What meetings of 256 workgroups that were closed before all had come have left in the workspace: how many had (bit 31, their number,
+    the tickets drawn by the end; as a float 1e-38 and less, which nothing else there is)."""
+    import torch
+    words = area[:area.numel() // 4 * 4].view(torch.int32)
+    high = (words >> 16) & 0xFFFF
+    return (high[(high > 0x8000) & (high < 0x8100) & ((words & 0xFFFF) == 256)] & 0xFF).tolist()
+
+
+def test_a_short_run_waits_for_units_that_are_free_soon():
+    """Four updates (20 ms by one workgroup alone, 0.1 ms by all) behind a kernel that keeps most units for another 4 ms."""
+    import torch
+    import paper_2312_08728_amd as B
+    p, C, n = 2048, 1000, 1024
+    x, y = torch.randn((2 * n, p), device="cuda", dtype=torch.bfloat16), torch.arange(2 * n, device="cuda", dtype=torch.int32) % C
+    s, t = _streams(2)
+    area, kw = _workspace(p, 2 * n, n, C, 2)
+    holder = _Holder(248, 8)
+    with B.Context(p, 2 * n, n, 0.01, 2, model=B.BMGD_SOFTMAX, n_classes=C, **kw) as ctx:
+        torch.cuda.synchronize()
+        holder.start(s)
+        ctx.run_device_buffer(x, y, 2 * n, t)
+        ctx.sync()
+        assert holder.free.query() and _came_in_time(area) == []
+    holder.ctx.close()
