@@ -836,8 +836,9 @@ hipError_t softmax_pass(SoftmaxPassArgs a, const SoftmaxDims& d, void* counters,
         a.s_end = std::min(updates, s + per_launch);
         a.meeting = meetings + (launch & 1) * kLine;
         a.next_meeting = meetings + (~launch & 1) * kLine;
-        // the others are waited for as long as one alone would take (1 ms at least), but not longer than a launch may last
-        a.meeting_ticks = hold_ticks < 125 ? 0 : std::min(hold_ticks, std::max(100000LL, alone * (a.s_end - s)));
+        // The others are waited for as long as one alone would take (1 ms at least), but not longer than a launch may last; though 0.1 ms in any
+        // case, in which all come to an idle device: a group without them would take longer for a single update.
+        a.meeting_ticks = hold_ticks < 125 ? 0 : std::max(10000LL, std::min(hold_ticks, std::max(100000LL, alone * (a.s_end - s))));
         hipLaunchKernelGGL(pass_kernel(ft, opt), grid, dim3(kThreads), kLds, stream, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

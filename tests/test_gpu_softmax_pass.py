@@ -253,3 +253,20 @@ def test_a_short_run_waits_for_units_that_are_free_soon():
         ctx.sync()
         assert holder.free.query() and _came_in_time(area) == []
     holder.ctx.close()
+
+
+@pytest.mark.parametrize("limit", [10, 16, 80])
+def test_a_small_limit_on_waits_leaves_an_idle_device_to_all_workgroups(limit):
+    """An eighth of 10 to 80 us is less than 256 workgroups may take to arrive."""
+    import torch
+    import paper_2312_08728_amd as B
+    p, C, n = 2048, 1000, 1024
+    x, y = torch.randn((n, p), device="cuda", dtype=torch.bfloat16), torch.arange(n, device="cuda", dtype=torch.int32) % C
+    area, kw = _workspace(p, n, n, C, 1, barrier_timeout_us=limit)
+    closed, s = 0, torch.cuda.Stream()
+    with B.Context(p, n, n, 0.01, 1, model=B.BMGD_SOFTMAX, n_classes=C, **kw) as ctx:
+        for _ in range(50):
+            ctx.run_device_buffer(x, y, n, s)
+            ctx.sync()
+            closed += len(_came_in_time(area))
+    assert closed == 0
