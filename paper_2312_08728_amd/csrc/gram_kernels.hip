@@ -666,12 +666,26 @@ DirectFn rows_kernel(int NT, bool vec, int* lds)
 }
 
 // Where the kernel above takes p > 95 from the staged one: many mini-batches, or few long ones, which it splits over two workgroups by rows.
-// With few rows in a mini-batch the staged kernel's more workgroups, each with fewer tiles, get going sooner.  (By the mini-batches of one pass, as
-// above.)  us of moments for one pass / three, staged kernel and this one: p = 100: 36 / 84 and 35 / 77 (100 mini-batches of 1,000 rows), 25 / 63 and
-// 25 / 49 (128, 500), 32 / 71 and 25 / 54 (200, 300), 17 / 37 and 19 / 33 (100, 256: not chosen), 28 / 58 and 35 / 53 (64, 1000: not chosen); split:
-// 136 / 139 and 101 / 102 (8, 8000), 73 / 77 and 61 / 64 (16, 4000), 43 / 63 and 42 / 60 (32, 2000), 36 / 76 and 38 / 67 (48, 1500: not chosen);
-// p = 127: 51 / 125 and 46 / 116 (100, 1000), 33 / 85 and 31 / 71 (128, 500), 225 / 229 and 136 / 137 (8, 8000), 118 / 125 and 81 / 84 (16, 4000).
-bool rows_moments(int p, int M, int n) { return p > 95 && (n >= 2000 || (M >= 85 && (int64_t)M * n >= 50000)); }
+// With few rows in a mini-batch the staged kernel's more workgroups, each with fewer tiles, get going sooner.  By the mini-batches of one pass, as
+// above, and so that launches of one to four passes come out at most 4 % slower (swept over M = 1 to 1000).  Two workgroups to a mini-batch
+// come out uneven on 256 compute units where the last round of a pass's is less than full (`even`): that costs more than the kernel gains with its
+// 45 tiles at p = 128, and where the staged kernel gains most from its finer shares, rows of up to 111 values that are not moved in fours.  us of
+// moments for one pass / three, staged kernel and this one (mini-batches, rows; -: not chosen).  p = 100: 36 / 84 and 35 / 77 (100, 1000), 32 / 71 and
+// 25 / 54 (200, 300), - 25 / 63 and 25 / 49 (128, 500), - 17 / 37 and 19 / 33 (100, 256), - 28 / 58 and 35 / 53 (64, 1000); split: 136 / 139 and 101 / 102
+// (8, 8000), 73 / 77 and 61 / 64 (16, 4000), 43 / 63 and 42 / 60 (32, 2000), - 36 / 76 and 38 / 67 (48, 1500).  p = 111: - 33 / 79 and 38 / 72 (150, 500).
+// p = 112: - 64 / 127 and 66 / 140 (84, 2000).  p = 127: 51 / 125 and 46 / 116 (100, 1000), 225 / 229 and 136 / 137 (8, 8000), 118 / 125 and 81 / 84 (16,
+// 4000).  p = 128: 59 / 157 and 50 / 131 (256, 500), - 39 / 98 and 47 / 89 (150, 500); split: 146 / 152 and 131 / 133 (8, 8000), - 44 / 46 and 55 / 56 (8, 2000).
+bool rows_moments(int p, int M, int n)
+{
+    if (p <= 95) return false;
+    if (M < 85) return n >= (p == 128 ? 8000 : M <= 48 ? 2000 : 5000);
+    if ((int64_t)M * n < 50000 || (M <= 128 && n < 560)) return false;
+    const int rounds = (2 * M + 255) / 256;
+    const bool even = 2 * M * 5 >= rounds * 256 * 4;
+    if (p == 128) return even;
+    if (p < 112 && p % 4 != 0) return even && (n >= 600 || M >= 600);
+    return true;
+}
 
 int rows_split(int M) { return M < 85 ? 2 : 1; }
 

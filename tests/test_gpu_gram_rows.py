@@ -14,7 +14,8 @@ def _case(p, N0, n, T=2):
 
 
 @pytest.mark.parametrize("chain", [3, 5])            # the chain's layout, and dense for the products
-@pytest.mark.parametrize("M,n", [(85, 601), (7, 2003)])      # one workgroup by rows, and two; a last mini-batch of 3 rows
+# one workgroup by rows, and two; a last mini-batch of 3 rows (at p = 97, 111 and 128 the first is for the staged kernel, at p = 128 the second too)
+@pytest.mark.parametrize("M,n", [(85, 601), (7, 2003), (105, 601), (7, 8003)])
 @pytest.mark.parametrize("p", [96, 97, 100, 111, 112, 127, 128])
 def test_tile_edges_against_the_oracle(p, M, n, chain):
     w = _case(p, M * n + 3, n)
@@ -28,7 +29,9 @@ def test_tile_edges_against_the_oracle(p, M, n, chain):
 @pytest.mark.parametrize("p,M,n", [(100, 84, 700), (100, 85, 588), (100, 85, 589),       # around the line to the staged kernel
                                    (101, 12, 1999), (101, 12, 2000),
                                    (100, 90, 577), (100, 86, 768), (127, 100, 769),      # shares of 148, 192 and 196 rows (48 at a time, eight to a chunk)
-                                   (128, 400, 257)])
+                                   (128, 400, 257),
+                                   (112, 48, 2000), (112, 49, 2000), (100, 105, 559), (100, 105, 560),      # ... and around its other lines
+                                   (97, 102, 700), (97, 103, 700), (99, 205, 599), (99, 205, 600), (128, 128, 600), (128, 129, 600)])
 def test_shapes_against_the_oracle(p, M, n):
     w = _case(p, M * n, n, T=1)
     X, y = wl.dataset(w)
@@ -36,11 +39,12 @@ def test_shapes_against_the_oracle(p, M, n):
     assert rel_l2(got, oracle_run(w, X, y)) <= 1e-4
 
 
-def test_a_pass_gives_the_same_bits_in_any_launch():
+@pytest.mark.parametrize("p,M", [(99, 90), (99, 105), (128, 110)])
+def test_a_pass_gives_the_same_bits_in_any_launch(p, M):
     """Five passes in launches of four and one, and one pass a launch; fixed partitions with cached matrices and without."""
     import torch
     import paper_2312_08728_amd as B
-    w = _case(99, 90 * 601, 601, T=5)
+    w = _case(p, M * 601, 601, T=5)
     X, y = wl.dataset(w)
     a, _ = gpu_run(w, X, y, chain=3, reshuffle=1)
     b, _ = gpu_run(w, X, y, chain=3, reshuffle=1, cache_moments=True)
