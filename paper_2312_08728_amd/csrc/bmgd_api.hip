@@ -91,10 +91,10 @@ struct bmgd_ctx {
     void* wbt = nullptr;                           // softmax: bf16 copy of W, transposed
     float* u = nullptr;                            // softmax: logits scratch
     void* rt = nullptr;                            // softmax: residual scratch
-    void* xt = nullptr;                            // softmax: transposed mini-batches of one pass (sm_chain: in the order of that kernel)
+    void* xt = nullptr;                            // softmax: transposed mini-batches of one pass (sm_chain: in the order of that kernel; sm_pass: its counters)
     bool sm_chain = false;                         // softmax: a pass is one persistent kernel (softmax_chain_kernel.hip)
     unsigned long long* sm_words = nullptr;        // ... and its flagged words
-    bool sm_pass = false;                          // softmax: up to four passes are one persistent kernel (softmax_pass_kernel.hip; its counters stand in xt)
+    bool sm_pass = false;                          // softmax: up to four passes are one persistent kernel (softmax_pass_kernel.hip)
     // eq. (3.1) form.  The pre-pass over the buffer (partitions, moment matrices) runs on the caller's compute
     // stream and the one-workgroup chain on a stream of the library's own, so that the pre-pass of the next
     // buffer overlaps the chain of this one; two sets of partitions and matrices alternate.
@@ -236,11 +236,15 @@ bool valid_config(const bmgd_config& c, std::string* why)
 
 int resolve_chain(const bmgd_config& c);
 
-// Softmax with small mini-batches, left to the library: one persistent kernel per pass.  The two modes that can be asked for
-// by name keep to their launches.
-bool wants_softmax_chain(const bmgd_config& c)
+// Softmax left to the library: one persistent kernel per pass for small mini-batches, persistent kernels of many updates for larger ones.
+// The two modes that can be asked for by name keep to their launches.
+enum class SoftmaxForm { kLaunches, kChain, kPass };
+
+SoftmaxForm wanted_softmax_form(const bmgd_config& c)
 {
-    return c.model == BMGD_SOFTMAX && c.chain == BMGD_CHAIN_AUTO && softmax_chain_eligible(c.p, c.batch_n, c.n_classes, c.optimizer != BMGD_OPT_SGD);
+    if (c.model != BMGD_SOFTMAX || c.chain != BMGD_CHAIN_AUTO) return SoftmaxForm::kLaunches;
+    if (softmax_chain_eligible(c.p, c.batch_n, c.n_classes, c.optimizer != BMGD_OPT_SGD)) return SoftmaxForm::kChain;
+    return softmax_pass_eligible(c.p, c.batch_n, c.n_classes) ? SoftmaxForm::kPass : SoftmaxForm::kLaunches;
 }
 
 // The moment form left to the library, with few features and few, small mini-batches: partitions, matrices and chain in one kernel.
@@ -265,8 +269,9 @@ bool wants_products(const bmgd_config& c)
     return steps >= 64 && gram_products_scratch_floats(c.p, (int64_t)kMaxPassesPerLaunch * M) <= (size_t(1) << 26);
 }
 
-// one_kernel: with room for the persistent softmax kernel (its mini-batches in operand order and its flagged words)
-Layout make_layout(const bmgd_config& c, bool one_kernel)
+// form: with room for the mini-batches in operand order and the flagged words of the persistent softmax kernel (kChain), or with the
+// counters of the one for larger mini-batches in the place of the transposed mini-batches, which it does without (kPass)
+Layout make_layout(const bmgd_config& c, SoftmaxForm form)
 {
     Layout l{};
     const size_t item = c.x_dtype == BMGD_BF16 ? 2 : 4;
@@ -287,8 +292,10 @@ Layout make_layout(const bmgd_config& c, bool one_kernel)
         l.wbt = off;     off += align_up((size_t)d.c_pad * d.p_pad * 2);
         l.u = off;       off += align_up((size_t)8 * d.m_pad * d.c_pad * 4);
         l.rt = off;      off += align_up((size_t)d.c_pad * d.n_pad * 2);
-        l.xt = off;      off += align_up(std::max(m_max * (size_t)c.p * d.n_pad * 2, one_kernel ? softmax_chain_pack_bytes(c.p, c.batch_n, (int64_t)m_max) : 0));
-        l.sm_words = off; off += one_kernel ? align_up(softmax_chain_words_bytes(c.batch_n, C)) : 0;
+        const bool chain = form == SoftmaxForm::kChain;
+        const size_t transposed = std::max(m_max * (size_t)c.p * d.n_pad * 2, chain ? softmax_chain_pack_bytes(c.p, c.batch_n, (int64_t)m_max) : 0);
+        l.xt = off;      off += align_up(form == SoftmaxForm::kPass ? softmax_pass_counter_bytes(d) : transposed);
+        l.sm_words = off; off += chain ? align_up(softmax_chain_words_bytes(c.batch_n, C)) : 0;
     } else {
         l.theta = off;   off += align_up((size_t)c.p * 4);
         l.partial = off; off += align_up((size_t)2 * kMaxGroups * c.p * 4);
@@ -1067,7 +1074,7 @@ BMGD_API size_t bmgd_workspace_bytes(const bmgd_config* cfg)
 {
     std::string why;
     if (!cfg || !valid_config(*cfg, &why)) return 0;
-    return make_layout(*cfg, wants_softmax_chain(*cfg)).total;
+    return make_layout(*cfg, wanted_softmax_form(*cfg)).total;
 }
 
 BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
@@ -1089,8 +1096,7 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     if (ctx->cfg.model != BMGD_SOFTMAX) ctx->cfg.n_classes = 1;
     ctx->x_itemsize = cfg->x_dtype == BMGD_BF16 ? 2 : 4;
     ctx->theta_len = cfg->p * ctx->cfg.n_classes;
-    bool one_kernel = wants_softmax_chain(ctx->cfg);
-    ctx->lay = make_layout(ctx->cfg, one_kernel);
+    SoftmaxForm form = wanted_softmax_form(ctx->cfg);
 
     auto bail = [&](int code) {
         g_create_error = ctx->err;
@@ -1107,23 +1113,31 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     hipDeviceProp_t prop;
     CREATE_TRY(hipGetDeviceProperties(&prop, ctx->device));
     ctx->num_cus = prop.multiProcessorCount;
-    // Softmax in one kernel needs more memory than separate launches (up to eight times the transposed mini-batches, for rows of 8
-    // features): where that is not to be had the context takes the launches.
-    auto without_one_kernel = [&]() {
-        if (!one_kernel) return false;
-        one_kernel = false;
-        ctx->lay = make_layout(ctx->cfg, false);
+    auto prepare_pass = [&]() {
+        return softmax_pass_prepare(cfg->p, cfg->batch_n, cfg->n_classes, cfg->optimizer != BMGD_OPT_SGD, ctx->num_cus, &ctx->sm_pass);
+    };
+    if (form == SoftmaxForm::kPass) {
+        CREATE_TRY(prepare_pass());
+        if (!ctx->sm_pass) form = SoftmaxForm::kLaunches;
+    }
+    ctx->lay = make_layout(ctx->cfg, form);
+    // The kernel of small mini-batches needs more memory than separate launches (up to eight times the transposed mini-batches, for rows
+    // of 8 features): where that is not to be had the context does without it.
+    auto without_chain = [&]() {
+        if (form != SoftmaxForm::kChain) return false;
+        form = SoftmaxForm::kLaunches;
+        ctx->lay = make_layout(ctx->cfg, form);
         return true;
     };
     if (cfg->workspace) {
-        if (cfg->workspace_bytes < ctx->lay.total && (!without_one_kernel() || cfg->workspace_bytes < ctx->lay.total)) {
+        if (cfg->workspace_bytes < ctx->lay.total && (!without_chain() || cfg->workspace_bytes < ctx->lay.total)) {
             ctx->err = "workspace smaller than bmgd_workspace_bytes()";
             return bail(BMGD_ENOMEM);
         }
         ctx->ws = cfg->workspace;
     } else {
         hipError_t me = hipMalloc(&ctx->ws, ctx->lay.total);
-        if (me == hipErrorOutOfMemory && without_one_kernel()) {
+        if (me == hipErrorOutOfMemory && without_chain()) {
             (void)hipGetLastError();
             me = hipMalloc(&ctx->ws, ctx->lay.total);
         }
@@ -1186,11 +1200,12 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     if (cfg->model == BMGD_SOFTMAX) {
         CREATE_TRY(softmax_prepare(softmax_dims(cfg->p, cfg->batch_n, cfg->n_classes)));
         ctx->chain = resolve_chain(ctx->cfg);        // three launches per mini-batch update, replayed from a graph or issued one by one
-        if (one_kernel)
+        if (form == SoftmaxForm::kChain)
             CREATE_TRY(softmax_chain_prepare(cfg->p, cfg->batch_n, cfg->n_classes, cfg->optimizer != BMGD_OPT_SGD, ctx->num_cus, &ctx->sm_chain));
-        if (cfg->chain == BMGD_CHAIN_AUTO && !ctx->sm_chain && softmax_pass_eligible(cfg->p, cfg->batch_n, cfg->n_classes) &&
+        // (a small mini-batch whose own kernel had no room, or does not fit the device: the counters stand where the launches' mini-batches would)
+        if (cfg->chain == BMGD_CHAIN_AUTO && !ctx->sm_chain && !ctx->sm_pass && softmax_pass_eligible(cfg->p, cfg->batch_n, cfg->n_classes) &&
             softmax_pass_counter_bytes(softmax_dims(cfg->p, cfg->batch_n, cfg->n_classes)) <= ctx->lay.sm_words - ctx->lay.xt)
-            CREATE_TRY(softmax_pass_prepare(cfg->p, cfg->batch_n, cfg->n_classes, cfg->optimizer != BMGD_OPT_SGD, ctx->num_cus, &ctx->sm_pass));
+            CREATE_TRY(prepare_pass());
         if (ctx->chain == BMGD_CHAIN_GRAPH && !ctx->sm_chain && !ctx->sm_pass) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
     } else {
         char msg[160];

@@ -74,6 +74,16 @@ def test_softmax_in_one_kernel_only_where_it_was_measured_to_be_faster(n, p, C, 
     assert sizes[1] > 0 and (sizes[0] > sizes[1]) == one_kernel
 
 
+@pytest.mark.parametrize("n,p,C,optimizer", [(1024, 3072, 1000, 0), (651, 1160, 247, 3), (2048, 8, 2, 0), (64, 1032, 10, 1)])
+def test_softmax_with_large_mini_batches_needs_no_room_for_transposed_ones(n, p, C, optimizer):
+    """All that a context of its own choice needs beyond the arrays both forms share is the counters of its kernel."""
+    M = 5
+    sizes = [B.bmgd_workspace_bytes(_cfg(p=p, buffer_n=M * n, batch_n=n, model=B.BMGD_SOFTMAX, n_classes=C, x_dtype=B.BMGD_BF16,
+                                         optimizer=optimizer, chain=chain)) for chain in (B.BMGD_CHAIN_AUTO, B.BMGD_CHAIN_LAUNCH)]
+    transposed = M * p * ((n + 63) // 64 * 64) * 2
+    assert 0 < sizes[0] <= sizes[1] - transposed + 32 * 1024
+
+
 def test_invalid_arguments_are_rejected_without_a_device():
     bad = [dict(p=0), dict(buffer_n=0), dict(buffer_n=1 << 30), dict(batch_n=0), dict(batch_n=1001),
            dict(lr=0.0), dict(lr=float("nan")), dict(lr=float("inf")), dict(lr=-1.0), dict(passes=0),
