@@ -1168,7 +1168,6 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
     ctx->prod[1] = reinterpret_cast<float*>(base + ctx->lay.prod[1]);
     ctx->products = wants_products(*cfg);
     ctx->fused = wants_fused(ctx->cfg);
-    if (ctx->chain == BMGD_CHAIN_GRAM) CREATE_TRY(gram_moments_prepare(ctx->cfg.p));
     if (ctx->products) CREATE_TRY(gram_products_prepare());
     ctx->gram_cache = base + ctx->lay.gram_cache;
     ctx->prod_cache = base + ctx->lay.prod_cache;

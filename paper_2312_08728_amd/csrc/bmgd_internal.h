@@ -191,8 +191,6 @@ struct GramPartition {
     unsigned* bad;
 };
 constexpr size_t gram_ticket_bytes = 32;
-// once per device with that device current, before the first launch for p features (raises the kernels' shared-memory limit)
-hipError_t gram_moments_prepare(int64_t p);
 bool gram_moments_draw(int64_t p, int64_t rows, int64_t n);
 hipError_t gram_launch_moments(const float* X, const float* y, const int32_t* perm, const GramPartition& from, float* gram, unsigned* tickets,
                                int rows, int p, int n, int npass, int perm_stride, hipStream_t stream, hipEvent_t start, hipEvent_t stop,

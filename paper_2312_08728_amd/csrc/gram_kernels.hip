@@ -562,7 +562,8 @@ template <int NT>
 constexpr int rows_lds_bytes()
 {
     constexpr int TPW = (NT * (NT + 1) / 2 + kTileGroups - 1) / kTileGroups;
-    const int ring = kDirectWaves * (kRing * kChunkRows * NT * 64 + 1024), sums = 2 * (TPW < kSumTiles ? TPW : kSumTiles) * 1024;
+    constexpr int ring = kDirectWaves * (kRing * kChunkRows * NT * 64 + 1024), sums = 2 * (TPW < kSumTiles ? TPW : kSumTiles) * 1024;
+    static_assert(ring <= 65536 && sums <= 65536, "more has to be asked for, kernel by kernel");
     return ring > sums ? ring : sums;
 }
 
@@ -750,20 +751,6 @@ size_t gram_dense_bytes_per_batch(int64_t p)
 int gram_chain_threads(int64_t p)
 {
     return make_layout((int)p).nthr;
-}
-
-hipError_t gram_moments_prepare(int64_t p)
-{
-    if (p <= 95) return hipSuccess;
-    const int NT = (int)((p + 1 + 15) / 16);
-    for (int S = 1; S <= 2; ++S) {
-        int lds = 0;
-        DirectFn fn = S == 2 ? rows_kernel<2>(NT, p % 4 == 0, &lds) : rows_kernel<1>(NT, p % 4 == 0, &lds);
-        if (!fn) return hipErrorInvalidValue;
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
 }
 
 bool gram_moments_draw(int64_t p, int64_t rows, int64_t n) { return direct_moments((int)p, (int)((rows + n - 1) / n)); }
