@@ -444,7 +444,8 @@ template <int N> struct IntC { static constexpr int value = N; };
 
 constexpr int kTileGroups = 2, kChunkRows = 8, kRing = 3;             // (a third workgroup fits a compute unit with a ring of three)
 static_assert(kChunkRows == 8, "two groups of four rows");
-constexpr int kBlockChunks = 2 * kRing, kBlockRows = kBlockChunks * kChunkRows;   // rows whose entries are fetched together: at most 64
+constexpr int kBlockChunks = 2 * kRing, kBlockRows = kBlockChunks * kChunkRows;   // rows whose entries are fetched together
+static_assert(kBlockRows <= 64, "one load of a wavefront fetches a block's entries, one its responses");
 
 constexpr int tile_row(int NT, int t)                // I of tile t of the upper triangle, row by row
 {
@@ -488,7 +489,7 @@ __device__ __forceinline__ void rows_tiles(const DirectArgs& a, floatx4 (&acc)[T
     }
     const int* const from = a.perm + (size_t)pass * a.perm_stride + (size_t)m * a.n;
     auto uniform = [](unsigned v) { return (unsigned)__builtin_amdgcn_readfirstlane((int)v); };
-    auto request_entries = [&](int block) {          // rows 64 block .. of the share (clamped)
+    auto request_entries = [&](int block) {          // rows kBlockRows * block .. of the share (clamped; lanes beyond the block's rows are not looked at)
         load_word_to_lds(from + min(r_begin + kBlockRows * block + lane, r_end - 1), uniform(mine_lds + kIdxAt + (unsigned)(block & 1) * 256u));
     };
     auto request_y = [&](int block) {
