@@ -52,6 +52,9 @@ def test_one_operand_tile_to_eight(p, n):
     (310, 1064, 129, 200, 65, 1),
     (900, 1296, 300, 700, 200, 2),
     (900, 2048, 1000, 700, 300, 3),
+    (500, 3072, 1000, 400, 200, 3),    # 96 features a tile
+    (500, 4096, 1000, 400, 200, 3),    # 128
+    (500, 4096, 1000, 400, 200, 1),
 ])
 def test_update_rules_and_one_workgroup_alone(N, p, C, N0, n, optimizer):
     """A table of rates, two buffers of different size and a run behind them, five passes (two launches a run), against the launches; and
@@ -238,15 +241,15 @@ def _came_in_time(area):
 
 
 def test_a_short_run_waits_for_units_that_are_free_soon():
-    """Four updates (20 ms by one workgroup alone, 0.1 ms by all) behind a kernel that keeps most units for another 4 ms."""
+    """Eight updates (41 ms by one workgroup alone, 0.2 ms by all) behind a kernel that keeps most units for another 20 ms."""
     import torch
     import paper_2312_08728_amd as B
     p, C, n = 2048, 1000, 1024
     x, y = torch.randn((2 * n, p), device="cuda", dtype=torch.bfloat16), torch.arange(2 * n, device="cuda", dtype=torch.int32) % C
     s, t = _streams(2)
-    area, kw = _workspace(p, 2 * n, n, C, 2)
-    holder = _Holder(248, 8)
-    with B.Context(p, 2 * n, n, 0.01, 2, model=B.BMGD_SOFTMAX, n_classes=C, **kw) as ctx:
+    area, kw = _workspace(p, 2 * n, n, C, 4)
+    holder = _Holder(248, 24)
+    with B.Context(p, 2 * n, n, 0.01, 4, model=B.BMGD_SOFTMAX, n_classes=C, **kw) as ctx:
         torch.cuda.synchronize()
         holder.start(s)
         ctx.run_device_buffer(x, y, 2 * n, t)
@@ -270,3 +273,29 @@ def test_a_small_limit_on_waits_leaves_an_idle_device_to_all_workgroups(limit):
             ctx.sync()
             closed += len(_came_in_time(area))
     assert closed == 0
+
+
+@pytest.mark.parametrize("units,limit", [(1, 400_000), (2, 400_000), (7, 400_000), (100, 400_000), (40, 8000), (100, 8000)])
+def test_workgroups_that_have_come_share_the_work(units, limit):
+    """On the units that a kernel of another context leaves free: some or many items of every phase for each workgroup, dealt unevenly, in
+    mini-batches of 1,024 and of 30 rows; the same bits as by all.  A limit of 0.4 s leaves all six updates to one launch, 8 ms one to each.
+    (Late workgroups have to be started and leave before a launch ends: where a shader engine has no unit left, once the other kernel has ended.)"""
+    import torch
+    import paper_2312_08728_amd as B
+    p, C, n = 2048, 1000, 1024
+    rows = 2 * n + 30
+    x, y = torch.randn((rows, p), device="cuda", dtype=torch.bfloat16), torch.arange(rows, device="cuda", dtype=torch.int32) % C
+    s, t = _streams(2)
+    holder, got = _Holder(256 - units, 150), []
+    for together in (False, True):
+        area, kw = _workspace(p, rows, n, C, 2, barrier_timeout_us=limit)
+        with B.Context(p, rows, n, 0.01, 2, model=B.BMGD_SOFTMAX, n_classes=C, **kw) as ctx:
+            torch.cuda.synchronize()
+            if together:
+                holder.start(s)
+            ctx.run_device_buffer(x, y, rows, t)
+            got.append(ctx.get_theta())
+            assert units < 40 or not (together and holder.free.query())
+        assert _came_in_time(area) == ([units] if together else [])
+    holder.ctx.close()
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
