@@ -51,8 +51,9 @@
  *   - A run that fails after part of its work has been enqueued, a device-side wait that exceeds
  *     barrier_timeout_us (the persistent kernels of least squares and logistic regression need all their
  *     workgroups resident at once: work of other streams that holds compute units for longer than the limit
- *     makes a run give up; it exits by itself and the next blocking call returns BMGD_EHIP) and a row subset with an index outside its
- *     buffer leave theta undefined.  From then on every run call returns BMGD_ESTATE until theta has been
+ *     makes a run give up; it exits by itself and the next blocking call returns BMGD_EHIP; the softmax kernels
+ *     of larger mini-batches let go of theirs several times within the limit, see BMGD_CHAIN_GRAPH) and a row
+ *     subset with an index outside its buffer leave theta undefined.  From then on every run call returns BMGD_ESTATE until theta has been
  *     set again with bmgd_set_theta() (bmgd_set_position() and bmgd_reset_optimizer() restore the rest of
  *     a checkpoint); nothing is retried automatically, because runs enqueued behind the failed one have
  *     already used its result.
@@ -125,9 +126,9 @@ enum {
                                     state p <= 512 and batch_n p <= 2^17).  Its workgroups meet before the first update; where
                                     other work keeps some of them from running for as long as one alone would need for the pass,
                                     or for an eighth of barrier_timeout_us, one of them makes the pass alone: slower, the same
-                                    sums, and not an error.  Other mini-batches of up to 2,048 rows: the updates of up
-                                    to four passes in persistent kernels whose workgroups meet likewise; those that have come in time
-                                    share the work.  Each makes as many updates as one workgroup alone makes in an eighth of
+                                    sums, and not an error.  Other mini-batches of up to 2,048 rows (two sets of row numbers have to fit
+                                    shared memory; longer ones take the launches): the updates of up to four passes in persistent
+                                    kernels whose workgroups meet likewise; those that have come in time share the work.  Each makes as many updates as one workgroup alone makes in an eighth of
                                     barrier_timeout_us (at most of the default), or one, and then lets go of the compute units.
                                     (A limit below some 50 ms thus costs large updates a launch each, 7 us; all workgroups have 0.1 ms
                                     to come whatever the limit, but a limit below 10 us means no meeting in either kernel: one

@@ -723,7 +723,7 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
     }
     s.chain_block = s.narrow ? glm_narrow_block(s.narrow_rw) : s.block;
     if (s.CPL >= 8 && s.V == 4 && G >= 8) {
-        // wide rows on eight or more workgroups: the kernel with an exchange wavefront and a two-level exchange
+        // wide rows on eight or more workgroups: the kernel with exchange wavefronts of its own
         s.split = 1;
         s.split_ch = s.CPL == 8 ? 1 : 2;
         s.G = G & ~7;

@@ -23,8 +23,8 @@
 //     4096, 4096, 30.6 / 29.9 at 4096, 8192: the fewer the rows, the less stands in the queues that the exchange now shares with them.  With four:
 //     at most 2 % less.  (Measured: under the row traffic a trip costs about 2 us
 //     whether the words come from the same die or another, and a wavefront that asks for a phase's words in two
-//     batches pays twice, so a die-local first stage - one more trip - loses; loads that would be served from a
-//     die's L2 without leaving it, other than atomics, do not exist in this mode of the hardware.)
+//     batches pays twice, so a die-local first stage - one more trip - loses; a word that was just written comes from
+//     beyond the die even where the same die wrote it: only atomics stay within.)
 //
 // Waits: row wavefronts only ever wait on shared-memory flags (which the exchange wavefronts always release, also
 // when they give up); their polls are bounded by the wall clock (ExchangeCommon::go_on).

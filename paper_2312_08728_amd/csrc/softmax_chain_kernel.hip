@@ -823,7 +823,8 @@ ChainKernel chain_kernel(bool opt, int rt, int ft) { return opt ? chain_kernel<t
 
 }  // namespace
 
-// Where one kernel is the faster way (us per update, this kernel / three launches; n, p, C).  Small mini-batches gain most: 3.4 / 14.9
+// Where one kernel is the faster way (us per update, this kernel / three launches; n, p, C).  What is left out here goes to the kernel of
+// larger mini-batches, at 0.5 to 0.86 of the launches' time; the lines have not been drawn against it.  Small mini-batches gain most: 3.4 / 14.9
 // at 100, 200, 10; 7.6 / 19.8 at 100, 200, 2000; 12.0 / 21.3 at 256, 512, 1000.  What a workgroup reads per update, 4 n p bytes, catches up
 // around n p = 2^18: 13.6 / 20.6 at 512, 512, 10 and 26.3 / 31.1 with 2,000 classes, 20.3 / 23.7 at 256, 1000, 1000.
 //   256 < n <= 512, p > 768 (eight feature tiles beside four row tiles: registers run out): 16.8 / 21.2 at 340, 760, 10, but 20.2 / 19.6

@@ -1,4 +1,4 @@
-// Softmax regression on large mini-batches: all updates of up to four passes in one persistent kernel.
+// Softmax regression on large mini-batches: the updates of up to four passes in persistent kernels of many updates each.
 //
 // One update of eq. (2.1) has three phases, each of which needs what all workgroups did in the one before:
 //   logits     U = X_b W               128 rows x 128 classes x a share of the features per workgroup; partial sums to memory
@@ -10,8 +10,9 @@
 //
 // Counters (arrive / await): a workgroup that has written its part waits for its stores, then adds one to the counter of the part;
 // readers poll.  What one workgroup writes and another reads (U, R, the bf16 copy of W) is stored and loaded at device scope, so it
-// is never found in a compute unit's own cache; a die's L2 serves such loads as fast as others (0.30 against 0.29 us per 32 KB and
-// compute unit), whereas invalidating caches between phases costs 2 us and more.  A phase's parts are counted in every update by
+// is never found in a compute unit's own cache.  A die's L2 serves such a load as fast as others if nobody has written the line since the die
+// last had it (0.30 against 0.29 us per 32 KB and compute unit; 90 ns for a load that depends on the one before); the first load of a freshly
+// written line goes beyond the die, whichever die wrote it (220 ns).  Invalidating caches between phases costs 2 us and more.  A phase's parts are counted in every update by
 // every workgroup, also where a short last mini-batch leaves nothing to do, and nothing is awaited less often than in every update:
 // so a count can only be reached by arrivals of the update that is waited for.
 //   (an arrival for update s + 1 follows, through the waits in front of it, all arrivals for update s at the same counter)
@@ -263,7 +264,8 @@ __device__ __forceinline__ void residual_rows(const SoftmaxPassArgs& a, __amdgpu
 // and its two wavefronts take half of every operand tile's depth each: an operand is read from shared memory twice, not four times, per
 // tile (64 + 32 KB per tile at 128 bytes a clock; 96 + 32 KB took 0.50 against 0.39 us).  Those reads run behind the matrix instructions of the tile
 // before (Walk): a tile of the update takes 0.45 us with that, 0.67 without; one of the logits 0.70 and 0.73, most of it the wait for rows of X from
-// memory (0.55 where they come from a die's L2).
+// memory (0.55 where they come from a die's L2).  All 256 registers are in use; FT = 128 spills 16 more (with state 17), FT = 64 and 96 with
+// state 3 each: reloads in the first requests and the last tiles of a walk, and for FT = 128 with state in every tile of the update.
 template <int FT, bool OPT>
 __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassArgs a)
 {
@@ -793,6 +795,10 @@ size_t softmax_pass_counter_bytes(const SoftmaxDims& d)
     return (size_t)(2 + d.m_pad / TR * kSubs + kRSubs + d.c_pad / TC * kSubs) * kLine * 4;
 }
 
+// Against the three launches, us per update, this kernel / launches: few features beside many rows 16.3 / 23.4 (8 features, 1100 rows, 10
+// classes), 20.2 / 32.2 (40, 2048, 10), 20.3 / 26.0 (136, 1100, 2; Adam 22.9 / 35.5), 26.7 / 45.1 (264, 2048, 1000); few rows 12.2 / 14.8 (1032, 8, 2);
+// 0.48 to 0.86 of them over 8 to 16384 features, 8 to 2048 rows and 2 to 2000 classes, and at most 0.96 for a run of one update.  More rows
+// than kMaxRows take the launches because their numbers, of this mini-batch and the next, would no longer fit shared memory.
 bool softmax_pass_eligible(int64_t p, int64_t n, int64_t C)
 {
     return n <= kMaxRows && p <= 16384 && C <= 2048;
