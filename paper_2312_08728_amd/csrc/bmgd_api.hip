@@ -94,7 +94,7 @@ struct bmgd_ctx {
     void* xt = nullptr;                            // softmax: transposed mini-batches of one pass (sm_chain: in the order of that kernel; sm_pass: its counters)
     bool sm_chain = false;                         // softmax: a pass is one persistent kernel (softmax_chain_kernel.hip)
     unsigned long long* sm_words = nullptr;        // ... and its flagged words
-    bool sm_pass = false;                          // softmax: up to four passes are one persistent kernel (softmax_pass_kernel.hip)
+    bool sm_pass = false;                          // softmax: persistent kernels of many updates (softmax_pass_kernel.hip)
     // eq. (3.1) form.  The pre-pass over the buffer (partitions, moment matrices) runs on the caller's compute
     // stream and the one-workgroup chain on a stream of the library's own, so that the pre-pass of the next
     // buffer overlaps the chain of this one; two sets of partitions and matrices alternate.
