@@ -333,9 +333,14 @@ struct SoftmaxPassArgs {
     int lr_base, lr_len;
     OptArgs opt;            // state arrays laid out like W; k_base = updates made before the launch
     // filled in by softmax_pass
-    long long meeting_ticks;       // how long the first workgroup waits for the others; 0: not at all, it makes the updates alone
+    long long meeting_ticks;       // what one workgroup takes for the launch: the first waits for the others for this long divided by those that
+                                   //   have come; 0: not at all, it makes the updates alone
     int M, m_pad, n_pad, splits, k_per_split;
-    int s_begin, s_end;            // updates of this launch, counted from the first of all passes
+    int updates;                   // of all passes
+    int updates_alone;             // at most this many in a launch by one workgroup,
+    float updates_each;            //   or this many times their number by several
+    const int* progress;           // updates made before this launch, and where it leaves the number for the next one
+    int* progress_next;
     unsigned* meeting;             // of this launch, and of the next, which this one clears
     unsigned* next_meeting;
     unsigned* counters;
@@ -344,8 +349,8 @@ bool softmax_pass_eligible(int64_t p, int64_t n, int64_t C);
 size_t softmax_pass_counter_bytes(const SoftmaxDims& d);
 // *fits: the kernel can run on this device
 hipError_t softmax_pass_prepare(int64_t p, int64_t n, int64_t C, bool opt, int num_cus, bool* fits);
-// A launch that clears the counters and then as many as it takes for none to last longer than hold_ticks whatever workgroups come, but for one of
-// a single update; d: of the mini-batches' size, with ldw columns
+// A launch that clears the counters, and then as many as it takes for none to last longer than hold_ticks whatever workgroups come (a single update
+// apart); those that find nothing left to do end at once.  d: of the mini-batches' size, with ldw columns
 hipError_t softmax_pass(SoftmaxPassArgs args, const SoftmaxDims& d, void* counters, int num_cus, long long hold_ticks, hipStream_t stream);
 // WbT <- bf16(W) transposed, whole matrix.
 hipError_t softmax_refresh_shadow(const float* W, void* WbT, int p, const SoftmaxDims& d, hipStream_t stream);

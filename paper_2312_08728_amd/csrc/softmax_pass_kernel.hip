@@ -24,8 +24,11 @@
 // All workgroups that take part must be running.  They meet before the first update; if some have not come in time, those that are
 // there share the work among themselves (parts of a phase are dealt round): the same sums in the same order, down to one workgroup.
 // A workgroup keeps its compute unit to itself from the meeting to the end of the launch, and another persistent kernel that waits for
-// that unit gives up after its limit.  So a launch makes only as many updates as one workgroup alone makes in an eighth of the limit
-// (softmax_pass); the next one goes on from there, with the counters as they are, and meets again.
+// that unit gives up after its limit.  So a launch makes only as many updates as those that have come make in about an eighth of the limit;
+// the next one goes on from there, with the counters as they are, and meets again.  All workgroups make everything in the first launch, or nearly
+// so, and leave the others nothing to do.  (Launches that end often even where all have come were tried: with runs of several contexts in
+// turn their workgroups stand on the device half and half most of the time, and a device that changes its queues at such a moment
+// puts them back in an order that keeps a third kernel waiting past its limit.)
 #include "bmgd_internal.h"
 #include "glm_device.h"
 #include "lds_load.h"
@@ -54,6 +57,7 @@ constexpr int kRedAt = kIdxAt + 2 * kMaxRows * 4;
 constexpr int kLds = kRedAt + 128;
 constexpr int kAgentScope = 16;                     // sc1
 constexpr int kLine = 32;                           // counters stand in lines of their own
+constexpr long long kMeeting = 10000;               // ticks: 0.1 ms
 constexpr int kSubs = 4, kRSubs = 32;               // counters a part's arrivals are spread over (one address takes 0.04 us per arrival)
 
 template <int N> struct IntC { static constexpr int value = N; };
@@ -264,7 +268,7 @@ __device__ __forceinline__ void residual_rows(const SoftmaxPassArgs& a, __amdgpu
 // and its two wavefronts take half of every operand tile's depth each: an operand is read from shared memory twice, not four times, per
 // tile (64 + 32 KB per tile at 128 bytes a clock; 96 + 32 KB took 0.50 against 0.39 us).  Those reads run behind the matrix instructions of the tile
 // before (Walk): a tile of the update takes 0.45 us with that, 0.67 without; one of the logits 0.70 and 0.73, most of it the wait for rows of X from
-// memory (0.55 where they come from a die's L2).  All 256 registers are in use; FT = 128 spills 16 more (with state 17), FT = 64 and 96 with
+// memory (0.55 where they come from a die's L2).  All 256 registers are in use; FT = 128 spills 16 more (with state 19), FT = 64 and 96 with
 // state 3 each: reloads in the first requests and the last tiles of a walk, and for FT = 128 with state in every tile of the update.
 template <int FT, bool OPT>
 __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassArgs a)
@@ -286,6 +290,12 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     int* const idx_all = reinterpret_cast<int*>(smem + kIdxAt);
     float* const red = reinterpret_cast<float*>(smem + kRedAt);
 
+    // (what a launch leaves for the next one is another word than what it reads: its wavefronts read at any time)
+    const int s_begin = *a.progress;
+    if (s_begin >= a.updates) {
+        if (blockIdx.x == 0 && tid == 0) *a.progress_next = s_begin;
+        return;
+    }
     // the meeting: word = closed (bit 31), workgroups that came in time (bits 16-30, once closed), tickets drawn (bits 0-15)
     PollGuard guard{a.sync + 1, a.timeout_ticks, 0, 0};
     if (a.meeting_ticks == 0) {                      // no time to meet: one workgroup alone
@@ -302,7 +312,10 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
         while (true) {
             if (seen >> 31) { nwg = (int)((seen >> 16) & 0x7FFFu); break; }
             if (seen == G) { nwg = (int)G; break; }
-            if (ticket == 0 && wall_clock64() - t0 >= a.meeting_ticks) {
+            // The first one waits for the others as long as those that have come would take for the launch: no more than is lost by going on with
+            // them, and two kernels that have half of the units each do not keep each other waiting.  (All come to an idle device in kMeeting.)
+            const long long waited = wall_clock64() - t0;
+            if (ticket == 0 && waited >= kMeeting && waited * (seen & 0xFFFFu) >= a.meeting_ticks) {
                 // (a workgroup that comes in between makes the exchange fail, and the loop looks again)
                 const unsigned closed = seen | seen << 16 | 1u << 31;
                 if (__hip_atomic_compare_exchange_strong(a.meeting, &seen, closed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) seen = closed;
@@ -318,7 +331,6 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     wg_barrier();
     const int rank = __builtin_amdgcn_readfirstlane(s_rank), nwg = __builtin_amdgcn_readfirstlane(s_nwg);
     if (rank >= nwg) return;                         // came too late
-    if (rank == 0 && tid == 0) *a.next_meeting = 0;  // (the word of the launch before, which has ended, is that of the next one)
 
     const int S = a.splits, tiles_c = a.ldw / TC, tiles_r = a.m_pad / TR, tiles_f = (a.p + FT - 1) / FT;
     const Deal dl(S * tiles_r * tiles_c), dr(a.n_pad / kRowsPerItem), dg(tiles_f * tiles_c);
@@ -677,10 +689,14 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
             load_word_to_lds(src + min(c * 64 + lane, nb - 1), lds0 + kIdxAt + (unsigned)which * (kMaxRows * 4) + (unsigned)c * 256);
     };
 
-    const int M = a.M, updates = a.s_end;
-    const int t_begin = a.s_begin / M, m_begin = a.s_begin - t_begin * M, nb_begin = min(a.n, a.rows - m_begin * a.n);
-    const int* const idx_begin = idx_all + (a.s_begin & 1) * kMaxRows;
-    request_idx(t_begin, m_begin, nb_begin, a.s_begin & 1);
+    const int M = a.M, updates = s_begin + min(a.updates - s_begin, max(a.updates_alone, (int)(a.updates_each * (float)nwg)));
+    if (rank == 0 && tid == 0) {
+        *a.progress_next = updates;
+        *a.next_meeting = 0;                         // (the word of the launch before, which has ended, is that of the next one)
+    }
+    const int t_begin = s_begin / M, m_begin = s_begin - t_begin * M, nb_begin = min(a.n, a.rows - m_begin * a.n);
+    const int* const idx_begin = idx_all + (s_begin & 1) * kMaxRows;
+    request_idx(t_begin, m_begin, nb_begin, s_begin & 1);
     wait_loads<0>();
     wg_barrier();
     const int l_first = rank < dl.rounds() ? dl.item(rank) : -1, r_first = rank < dr.rounds() ? dr.item(rank) : -1, g_first = rank < dg.rounds() ? dg.item(rank) : -1;
@@ -690,7 +706,7 @@ __global__ void __launch_bounds__(kThreads, 2) softmax_pass_kernel(SoftmaxPassAr
     if (g_first >= 0) g_at(g_first);
     const int g_ft_first = g_ft, g_ct_first = g_ct, cc_first = max(l_first, 0) % CG;
     if (l_first >= 0) l_begin(idx_begin, nb_begin);
-    for (int s = a.s_begin, t = t_begin, m = m_begin; s < updates; ++s) {
+    for (int s = s_begin, t = t_begin, m = m_begin; s < updates; ++s) {
         const int nb = min(a.n, a.rows - m * a.n);
         const int* const idx = idx_all + (s & 1) * kMaxRows;
         for (int k = rank; k < dl.rounds(); k += nwg) {
@@ -792,7 +808,7 @@ int pass_groups(const SoftmaxDims& d, int p, int num_cus, int ft)
 
 size_t softmax_pass_counter_bytes(const SoftmaxDims& d)
 {
-    return (size_t)(2 + d.m_pad / TR * kSubs + kRSubs + d.c_pad / TC * kSubs) * kLine * 4;
+    return (size_t)(3 + d.m_pad / TR * kSubs + kRSubs + d.c_pad / TC * kSubs) * kLine * 4;
 }
 
 // Against the three launches, us per update, this kernel / launches: few features beside many rows 16.3 / 23.4 (8 features, 1100 rows, 10
@@ -827,24 +843,24 @@ hipError_t softmax_pass(SoftmaxPassArgs a, const SoftmaxDims& d, void* counters,
     a.splits = d.splits;
     a.k_per_split = d.k_per_split;
     unsigned* const meetings = static_cast<unsigned*>(counters);
-    a.counters = meetings + 2 * kLine;
+    int* const progress = static_cast<int*>(counters) + 2 * kLine;
+    a.counters = meetings + 3 * kLine;
     hipError_t e = launch_fill_zero(counters, softmax_pass_counter_bytes(d), stream);
     if (e != hipSuccess) return e;
     const int ft = pass_features(a.p, d.c_pad / TC, num_cus);
     const bool opt = a.opt.kind != kOptSgd;
     const dim3 grid((unsigned)pass_groups(d, a.p, num_cus, ft));
-    const int updates = a.npass * a.M;
-    // (a launch of all workgroups then lasts 1 to 15 ms with the default limit; the start and end of each cost about 10 us: 1 % and less)
     const long long alone = pass_alone_ticks(d, a.p, ft, opt);
-    const int per_launch = (int)std::min<long long>(std::max(1LL, hold_ticks / alone), updates);
-    for (int s = 0, launch = 0; s < updates; s += per_launch, ++launch) {
-        a.s_begin = s;
-        a.s_end = std::min(updates, s + per_launch);
+    a.updates = a.npass * a.M;
+    a.updates_alone = (int)std::min<long long>(std::max(1LL, hold_ticks / alone), a.updates);
+    // (an update of all workgroups takes 1.2 to 4 times what one alone takes divided by their number, the more the less of it there is)
+    a.updates_each = (float)hold_ticks / (4.f * (float)alone);
+    a.meeting_ticks = hold_ticks < 125 ? 0 : std::min(hold_ticks, alone * a.updates_alone);
+    for (int s = 0, launch = 0; s < a.updates; s += a.updates_alone, ++launch) {
         a.meeting = meetings + (launch & 1) * kLine;
         a.next_meeting = meetings + (~launch & 1) * kLine;
-        // The others are waited for as long as one alone would take (1 ms at least), but not longer than a launch may last; though 0.1 ms in any
-        // case, in which all come to an idle device: a group without them would take longer for a single update.
-        a.meeting_ticks = hold_ticks < 125 ? 0 : std::max(10000LL, std::min(hold_ticks, std::max(100000LL, alone * (a.s_end - s))));
+        a.progress = progress + (launch & 1);
+        a.progress_next = progress + (~launch & 1);
         hipLaunchKernelGGL(pass_kernel(ft, opt), grid, dim3(kThreads), kLds, stream, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

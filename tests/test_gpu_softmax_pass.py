@@ -241,18 +241,19 @@ def _came_in_time(area):
 
 
 def test_a_short_run_waits_for_units_that_are_free_soon():
-    """Eight updates (41 ms by one workgroup alone, 0.2 ms by all) behind a kernel that keeps most units for another 20 ms."""
+    """Forty updates (26 ms by the eight workgroups that find a unit at once, 1 ms by all) behind a kernel that keeps the other units for another
+    20 ms."""
     import torch
     import paper_2312_08728_amd as B
     p, C, n = 2048, 1000, 1024
-    x, y = torch.randn((2 * n, p), device="cuda", dtype=torch.bfloat16), torch.arange(2 * n, device="cuda", dtype=torch.int32) % C
+    x, y = torch.randn((10 * n, p), device="cuda", dtype=torch.bfloat16), torch.arange(10 * n, device="cuda", dtype=torch.int32) % C
     s, t = _streams(2)
-    area, kw = _workspace(p, 2 * n, n, C, 4)
+    area, kw = _workspace(p, 10 * n, n, C, 4)
     holder = _Holder(248, 24)
-    with B.Context(p, 2 * n, n, 0.01, 4, model=B.BMGD_SOFTMAX, n_classes=C, **kw) as ctx:
+    with B.Context(p, 10 * n, n, 0.01, 4, model=B.BMGD_SOFTMAX, n_classes=C, **kw) as ctx:
         torch.cuda.synchronize()
         holder.start(s)
-        ctx.run_device_buffer(x, y, 2 * n, t)
+        ctx.run_device_buffer(x, y, 10 * n, t)
         ctx.sync()
         assert holder.free.query() and _came_in_time(area) == []
     holder.ctx.close()
