@@ -128,11 +128,12 @@ enum {
                                     or for an eighth of barrier_timeout_us, one of them makes the pass alone: slower, the same
                                     sums, and not an error.  Other mini-batches of up to 2,048 rows (two sets of row numbers have to fit
                                     shared memory; longer ones take the launches): the updates of up to four passes in persistent
-                                    kernels whose workgroups meet likewise; those that have come in time share the work.  Each makes as many updates as one workgroup alone makes in an eighth of
-                                    barrier_timeout_us (at most of the default), or one, and then lets go of the compute units.
-                                    (A limit below some 50 ms thus costs large updates a launch each, 7 us; all workgroups have 0.1 ms
-                                    to come whatever the limit, but a limit below 10 us means no meeting in either kernel: one
-                                    workgroup makes everything.) */
+                                    kernels whose workgroups meet likewise.  Those that have come wait for the others as long as they
+                                    would take without them, and share the work.  A kernel makes as many updates as they make in
+                                    an eighth of barrier_timeout_us (at most of the default), or one, and then lets go of the
+                                    compute units; the next goes on.  (A small limit thus costs launches: 7 us for each update below
+                                    some ms.  All workgroups have 0.1 ms to come whatever the limit, but a limit below 10 us means
+                                    no meeting in either kernel: one workgroup makes everything.) */
     BMGD_CHAIN_PRODUCT = 5       /* least squares with p <= 128 and plain steps (BMGD_OPT_SGD) only: the moment form of
                                     BMGD_CHAIN_GRAM with steps multiplied together.  A step of eq. (3.1) is the affine map
                                     [theta; 1] <- A_m [theta; 1], A_m = [[I - alpha Sxx_m, alpha Sxy_m], [0, 1]], and no A_m
