@@ -272,7 +272,7 @@ def test_rows_that_are_all_but_certain_keep_their_residual():
 
 
 def test_a_workspace_of_the_size_that_separate_launches_need_is_taken():
-    """Its size without the mini-batches in operand order and the exchange: then the updates are separate launches."""
+    """Its size without the mini-batches in operand order and the exchange: then another kernel makes the updates."""
     import torch
     import paper_2312_08728_amd as B
     w = _case(900, 8, 20, 900, 16)

@@ -1,4 +1,4 @@
-"""The persistent softmax kernel of large mini-batches (logits, residual and update of up to four passes in one launch) at the edges of
+"""The persistent softmax kernel of large mini-batches (logits, residual and update of many steps in one launch) at the edges of
 its tiles, against the fp64 oracle within the bound of the bf16 path (2e-3: bf16 copy of W, bf16 residual; 5e-3 with Adam, which
 normalises their rounding), and against the three launches, whose roundings are the same up to the order of fp32 sums."""
 import numpy as np
