@@ -300,3 +300,30 @@ def test_workgroups_that_have_come_share_the_work(units, limit):
         assert _came_in_time(area) == ([units] if together else [])
     holder.ctx.close()
     assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("form", ["fixed partitions", "short buffers", "row subset", "from the host"])
+def test_launches_that_go_on_where_the_one_before_ended(form):
+    """Five passes by launches of a few updates (a limit of 0.2 ms) and by as few as there can be: the same bits; and the sums of the three
+    launches, up to their order and the rounding to bf16 that it decides."""
+    import torch
+    import paper_2312_08728_amd as B
+    w = _case(3000, 1160, 250, 1000, 150, T=5)
+    X, y = wl.dataset(w)
+    xs, ys = [torch.from_numpy(X[k:k + 1000].view(np.int16)) for k in (0, 1000, 2000)], [torch.from_numpy(y[k:k + 1000]) for k in (0, 1000, 2000)]
+    xs, ys = ([v.pin_memory() for v in a] if form == "from the host" else [v.cuda() for v in a] for a in (xs, ys))
+    rows = torch.randint(0, 1000, (437,), generator=torch.Generator().manual_seed(1), dtype=torch.int32).cuda()
+    s, copy, got = torch.cuda.Stream(), torch.cuda.Stream(), []
+    kw = dict(reshuffle=B.BMGD_RESHUFFLE_FIXED, n_buffers=3) if form == "fixed partitions" else {}
+    for chain, limit in ((B.BMGD_CHAIN_AUTO, 0), (B.BMGD_CHAIN_AUTO, 200), (B.BMGD_CHAIN_LAUNCH, 0)):
+        with B.Context(w.p, 1000, w.n, 0.05, w.T, model=w.model, n_classes=w.C, chain=chain, barrier_timeout_us=limit, **kw) as ctx:
+            for xb, yb, short in zip(xs, ys, (7, 149, 151)):
+                if form == "from the host":
+                    ctx.load_buffer_async(xb, yb, 1000, copy)
+                    ctx.run_buffer(s)
+                    continue
+                if form == "row subset":
+                    ctx.set_row_subset(rows, len(rows))
+                ctx.run_device_buffer(xb, yb, short if form == "short buffers" else 1000, s)
+            got.append(ctx.get_theta())
+    assert np.isfinite(got[0]).all() and np.array_equal(got[0], got[1]) and rel_l2(got[0], got[2]) <= 2e-3
