@@ -830,7 +830,8 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
                     // Workgroups that have met are all running, so their waits end by themselves: the limit is only there to end a
                     // kernel on a device that fails.  They are given as long to meet as the pass takes a workgroup alone (about
                     // 10 us per update and share of the classes), but give way well before another persistent kernel of this
-                    // library, which may be waiting for the units they hold, runs out of its limit.
+                    // library, which may be waiting for the units they hold, runs out of its limit.  (That is the meeting; a pass by one
+                    // alone keeps its unit to the end, seconds for some thousand mini-batches of many classes.)
                     sa.timeout_ticks = 1000000000LL;
                     sa.meeting = ctx->sync + 8;
                     sa.meeting_ticks = ticks < 1000 ? 0 : std::min<long long>(std::min<long long>(ticks / 8, 200000000LL),
