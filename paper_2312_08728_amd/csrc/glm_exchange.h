@@ -23,8 +23,7 @@
 // What bounds a step of short rows is latency: two trips of about 0.6 us, in each the time until the slowest workgroup has stored
 // its words, and the instructions between them.  us per update before / now (the loops, waits and state of the exchange as it was
 // before / written as ExchangeCommon says, residuals worked out once per row): 4.3 / 3.5 at p = 200, n = 4096 (256 workgroups); 5.1 / 3.6
-// at p = 512, n = 1000 with Adam (160); one trip, 32 workgroups: 5.2 / 3.4 at p = 123, n = 777 with momentum, 4.5 / 2.9 at
-// p = 128, n = 1024 (before: two trips, 40).
+// at p = 512, n = 1000 with Adam (160).  One trip (PairExchange): see there.
 #pragma once
 
 #include "bmgd_internal.h"
@@ -67,23 +66,21 @@ __device__ __forceinline__ u32x4 word_pair(float v0, float v1, unsigned tag)
 // the row loop at such a place: it keeps count of the row loads in flight per path through the control-flow graph,
 // and every extra path (a poll loop, an early exit, which the structuriser routes through the loop's latch) makes
 // it wait for rows that the path actually taken does not need.
-// Wait until the word at shared-memory address `addr` is >= want, or the word at `abort_addr` is non-zero.
+// Wait until the word at shared-memory address `addr` is >= want, or the word at `abort_addr` is non-zero.  (Both are read in one trip, and
+// nothing sleeps: with two trips and a sleep in between 0.03 to 0.1 us more per update.)
 __device__ __forceinline__ void lds_wait_ge(unsigned addr, unsigned want, unsigned abort_addr)
 {
-    unsigned t;
+    unsigned t, stop;
     asm volatile("1:\n\t"
-                 "ds_read_b32 %0, %1\n\t"
+                 "ds_read_b32 %0, %2\n\t"
+                 "ds_read_b32 %1, %4\n\t"
                  "s_waitcnt lgkmcnt(0)\n\t"
-                 "v_cmp_ge_u32_e32 vcc, %0, %2\n\t"
+                 "v_cmp_ge_u32_e32 vcc, %0, %3\n\t"
                  "s_cbranch_vccnz 2f\n\t"
-                 "ds_read_b32 %0, %3\n\t"
-                 "s_waitcnt lgkmcnt(0)\n\t"
-                 "v_cmp_ne_u32_e32 vcc, 0, %0\n\t"
-                 "s_cbranch_vccnz 2f\n\t"
-                 "s_sleep 1\n\t"
-                 "s_branch 1b\n"
+                 "v_cmp_ne_u32_e32 vcc, 0, %1\n\t"
+                 "s_cbranch_vccz 1b\n"
                  "2:"
-                 : "=&v"(t) : "v"(addr), "v"(want), "v"(abort_addr) : "vcc", "memory");
+                 : "=&v"(t), "=&v"(stop) : "v"(addr), "v"(want), "v"(abort_addr) : "vcc", "memory");
 }
 
 // The same for an exchange wavefront, which must not go on with the step if a wait ran out anywhere in the workgroup: until every
@@ -164,6 +161,20 @@ struct StepGeometry {
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
+
+// The sum over the lanes with the same lane % PPc (8 <= PPc <= 64, uniform), in all of them.
+__device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
+{
+    if (PPc == 8) {                                  // the usual case as one straight line
+        v.x += dpp_mov<0x128>(v.x); v.y += dpp_mov<0x128>(v.y);
+        v.x = swap16_sum(v.x); v.y = swap16_sum(v.y);
+        v.x = swap32_sum(v.x); v.y = swap32_sum(v.y);
+    } else if (PPc < 64) {
+        if (PPc == 16) { v.x = swap16_sum(v.x); v.y = swap16_sum(v.y); }
+        v.x = swap32_sum(v.x); v.y = swap32_sum(v.y);
+    }
+    return v;
+}
 
 // The exchange wavefronts' view of the workgroup's shared memory.
 struct ExchangeLds {
@@ -273,22 +284,57 @@ struct ExchangeCommon {
         return v[0];
     }
 
-    // this wavefront's share of the workgroup's sums, as flagged words: what the others wait for
+    // The same of the pairs of columns PW xw + (0 .. PW - 1) where PW < 64: 64 / PW groups of lanes share the arrays, and their sums meet over
+    // the lanes.  c: the first column of this lane's pair, or where there is none any other's.
+    template <int PW>
+    __device__ __forceinline__ f32x2 shared_sum_of(int c) const
+    {
+        constexpr int SG = 64 / PW, J = (NSUM + SG - 1) / SG;
+        const int sg = lane / PW;
+        f32x2 v[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) v[j] = *(const lds_f32x2*)(x.sums + min(sg + SG * j, NSUM - 1) * x.sums_stride + c);
+        if constexpr (NSUM % SG != 0) {
+            if (sg + SG * (J - 1) >= NSUM) v[J - 1] = f32x2{0.f, 0.f};
+        }
+#pragma unroll
+        for (int w = 1; w < J; w *= 2) {
+#pragma unroll
+            for (int k = 0; k + w < J; k += 2 * w) { v[k].x += v[k + w].x; v[k].y += v[k + w].y; }
+        }
+        return pair_slot_sum(v[0], PW);
+    }
+
+    // this wavefront's share of the workgroup's sums as flagged words: what the others wait for
     __device__ __forceinline__ void send_sums(__amdgpu_buffer_rsrc_t part, unsigned tag) const
     {
-        auto send = [&](int c) {
-            if (c < p) {
-                const f32x2 v = sum_of(c);
-                __builtin_amdgcn_raw_buffer_store_b128(word_pair(v.x, v.y, tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, kAgentScope);
-            }
+        auto send = [&](int c, f32x2 v) {
+            __builtin_amdgcn_raw_buffer_store_b128(word_pair(v.x, v.y, tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, kAgentScope);
         };
         asm volatile("" ::: "memory");
         if constexpr (NSUM == 1) {                   // (their reads of shared memory go out together)
 #pragma unroll 8
-            for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) send(c0 + 2 * lane);
+            for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) {
+                const int c = c0 + 2 * lane;
+                if (c < p) send(c, sum_of(c));
+            }
         } else {
+            auto share = [&](auto pw) {
+                constexpr int PW = decltype(pw)::value;
+                const int c = 2 * (PW * xw + (lane & (PW - 1)));
+                const f32x2 v = shared_sum_of<PW>(min(c, pp - 2));
+                if (c < p && lane < PW) send(c, v);
+            };
+            if (p <= 16 * NX) share(std::integral_constant<int, 8>{});
+            else if (p <= 32 * NX) share(std::integral_constant<int, 16>{});
+            else if (p <= 64 * NX) share(std::integral_constant<int, 32>{});
+            else {
 #pragma unroll 1
-            for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) send(c0 + 2 * lane);
+                for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) {
+                    const int c = c0 + 2 * lane;
+                    if (c < p) send(c, sum_of(c));
+                }
+            }
         }
     }
 
@@ -364,20 +410,6 @@ struct ExchangeCommon {
         }
     }
 };
-
-// The sum over the lanes with the same lane % PPc (8 <= PPc <= 64, uniform), in all of them.
-__device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
-{
-    if (PPc == 8) {                                  // the usual case as one straight line
-        v.x += dpp_mov<0x128>(v.x); v.y += dpp_mov<0x128>(v.y);
-        v.x = swap16_sum(v.x); v.y = swap16_sum(v.y);
-        v.x = swap32_sum(v.x); v.y = swap32_sum(v.y);
-    } else if (PPc < 64) {
-        if (PPc == 16) { v.x = swap16_sum(v.x); v.y = swap16_sum(v.y); }
-        v.x = swap32_sum(v.x); v.y = swap32_sum(v.y);
-    }
-    return v;
-}
 
 // All steps [a.s_begin, a.s_end) of a launch in two trips over the fabric each, by exchange wavefront xw of NX of workgroup
 // blockIdx.x of gridDim.x (a multiple of 8).  Returns when the last version of theta has been delivered (workgroup 0 also writes it
@@ -546,35 +578,58 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
     ex.finish(last - first);
 }
 
+// Columns dealt out to the NX exchange wavefronts of a workgroup as pairs: wavefront xw holds the pairs PW xw + (0 .. PW - 1), PW a power of
+// two, in SG = 64 / PW groups of lanes, which share what there is to add up for a pair; their sums meet over the lanes, and nothing is handed
+// from wavefront to wavefront.  For the exchange in which every workgroup makes the whole update.
+// us per update with chunks of 64 pairs, whose workgroups the wavefronts shared and whose partial sums met in shared memory (a hand-over, with
+// twelve arrays of sums read by one wavefront, was 0.6 of the 2.9 us) / now: 3.40 / 2.89 at p = 123, n = 777 with momentum, 2.93 / 2.49 at
+// p = 128, n = 1024, 2.88 / 2.22 at p = 30, n = 3000, 2.84 / 2.12 at p = 512, n = 90 on 8 workgroups; one workgroup 1.43 / 1.30 at p = 128, n = 96.
+template <bool OPT, int NX, int NSUM, int PW>
+struct PairExchange : ExchangeCommon<OPT, NX, NSUM> {
+    static constexpr int SG = 64 / PW;
+    const int pair, sg;                              // this lane's
+    const int c;                                     // first column of its pair,
+    const int cc;                                    //   or where there is none the last one
+    const bool own;
+    __device__ __forceinline__ PairExchange(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
+        : ExchangeCommon<OPT, NX, NSUM>(a, x, lane, xw), pair(lane & (PW - 1)), sg(lane / PW), c(2 * (PW * xw + pair)), cc(min(c, this->pp - 2)), own(c < a.p)
+    {
+    }
+
+    // the workgroup's sums of this lane's pair, in all groups of lanes
+    __device__ __forceinline__ f32x2 own_sum() const
+    {
+        asm volatile("" ::: "memory");
+        return this->template shared_sum_of<PW>(cc);
+    }
+    __device__ __forceinline__ void send(f32x2 v, __amdgpu_buffer_rsrc_t part, unsigned tag) const
+    {
+        if (own && sg == 0)
+            __builtin_amdgcn_raw_buffer_store_b128(word_pair(v.x, v.y, tag), part, (unsigned)(((size_t)this->g * this->pp + c) * 8), 0, kAgentScope);
+    }
+    // the new values of this lane's pair to shared memory
+    __device__ __forceinline__ void apply(const lds_f32* th_old, lds_f32* th_new, f32x2 sum, float nb, float scale, float alpha, int done)
+    {
+        const f32x2 old = *(const lds_f32x2*)(th_old + cc);
+        const f32x2 now = this->update(old, sum, nb, scale, alpha, done, pair, own && sg == 0);
+        if (own && sg == 0) *(lds_f32x2*)(th_new + c) = f32x2{now.x, c + 1 < this->p ? now.y : 0.f};
+    }
+};
+
 // The same steps in ONE trip over the fabric: every workgroup adds up all sums of all workgroups itself, in the same order, and keeps
 // its own copy of theta and of an update rule's state (at m + g pp).  For few words (G p of them come in per step and workgroup).
-// p <= 128 NX.  The NX wavefronts split the columns into chunks of 64 pairs and, where there are fewer chunks than wavefronts, the
-// workgroups of a chunk; the partial sums meet in shared memory, and every wavefront updates its part of theta.
-template <bool OPT, int NX, int NSUM>
+template <bool OPT, int NX, int NSUM, int PW>
 __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
 {
-    ExchangeCommon<OPT, NX, NSUM> ex(a, x, lane, xw);
-    const int G = ex.G, g = ex.g, p = ex.p, pp = ex.pp;
+    PairExchange<OPT, NX, NSUM, PW> ex(a, x, lane, xw);
+    constexpr int SG = 64 / PW;
+    const int G = ex.G, g = ex.g, pp = ex.pp;
     const int first = a.s_begin, last = a.s_end;
-    const int npair = (p + 1) / 2;
-    int nc = 1;                                      // chunks of columns (a power of two <= NX)
-    while (64 * nc < npair) nc *= 2;
-    int PPc = 64;                                    // pairs side by side (a power of two >= 2 NX)
-    while (nc == 1 && PPc > 2 * NX && PPc / 2 >= npair) PPc /= 2;
-    const int SG = 64 / PPc;                         // groups of lanes, each taking every SG-th workgroup
-    const int my_pair = lane & (PPc - 1), my_sg = lane / PPc;
-    const int wpc = NX / nc;                         // wavefronts per chunk
-    const int chunk = xw / wpc, share = xw % wpc;
-    const int c = 2 * (64 * chunk + my_pair);        // the pair of columns this lane adds up
-    const bool mine = c < p && my_sg < G;
-    const unsigned voff = (unsigned)min(c, pp - 2) * 8u + (unsigned)min(my_sg, G - 1) * (unsigned)(pp * 8);
-    const int loads = (G + SG * wpc - 1) / (SG * wpc);            // pairs of words a lane asks for per step (as one, two, four, or eight at a time)
-    const int PW = PPc / wpc;                        // pairs a wavefront of a chunk updates
-    const int up = share * PW + lane;                // the pair of the chunk this lane updates (lane < PW)
-    const int uc = 2 * (64 * chunk + up);
-    const bool upd = lane < PW && uc < p;
+    const bool mine = ex.own && ex.sg < G;
+    const unsigned voff = (unsigned)ex.cc * 8u + (unsigned)min(ex.sg, G - 1) * (unsigned)(pp * 8);
+    const int loads = (G + SG - 1) / SG;             // pairs of words a lane asks for per step (as one, two, four, or eight at a time)
     if constexpr (OPT) {
-        if (upd) ex.load_state(lane, a.opt.m + (size_t)g * pp + uc, a.opt.s + (size_t)g * pp + uc);   // (the arrays reach to p rounded up to 16, per workgroup)
+        if (ex.own && ex.sg == 0) ex.load_state(ex.pair, a.opt.m + (size_t)g * pp + ex.c, a.opt.s + (size_t)g * pp + ex.c);   // (the arrays reach to p rounded up to 16, per workgroup)
     }
     unsigned dead = 0u;
     int s = first;
@@ -590,63 +645,41 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
         ex.corrections(s - first);
         const __amdgpu_buffer_rsrc_t part = words_rsrc(a.ll_part + (size_t)(s & 1) * G * pp, ex.words_bytes);
         dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
-        f32x2 t = {0.f, 0.f};
-        if (G == 1) {
-            asm volatile("" ::: "memory");
-            if (upd) t = ex.sum_of(uc);
-        } else {
-            ex.send_sums(part, tag);
+        f32x2 t = ex.own_sum();
+        if (G > 1) {
+            ex.send(t, part, tag);
             // Words of many workgroups take a wavefront long to fetch: asked for at once they would be fetched twice, none of the others'
-            // having come yet (2.91 against 3.18 us per update with 32 workgroups at p = 128, n = 1024; nothing with few)
+            // having come yet (0.27 us per update with 32 workgroups at p = 128, n = 1024; nothing with few)
             if (loads > 2) __builtin_amdgcn_s_sleep(15);
-            // Load u of this wavefront takes the workgroups i + my_sg, i = i0 + SG wpc u.  The last loads start at G - SG at most;
+            // Load u of a lane takes the workgroup i + sg, i = i0 + SG u.  The last loads start at G - SG at most;
             // what they bring a second time (workgroups below i) is not added.
             f32x2 r = {0.f, 0.f};
             auto trips = [&](auto count) {
                 constexpr int U = decltype(count)::value;
-                int i0 = SG * share;
+                int i0 = 0;
 #pragma clang loop unroll(disable)
                 do {
                     u32x4 w[U];
                     dead |= ex.poll(tag, w,
-                        [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(part, voff, (unsigned)max(0, min(i0 + SG * wpc * u, G - SG)) * (unsigned)(pp * 8), kAgentScope); },
+                        [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(part, voff, (unsigned)max(0, min(i0 + SG * u, G - SG)) * (unsigned)(pp * 8), kAgentScope); },
                         [&](const u32x4& v, int) { return mine ? min(v.y, v.w) : tag; });
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
-                        const int i = i0 + SG * wpc * u;
-                        const bool add = mine && i < G && max(0, min(i, G - SG)) + my_sg >= i;
+                        const int i = i0 + SG * u;
+                        const bool add = mine && i < G && max(0, min(i, G - SG)) + ex.sg >= i;
                         r.x += add ? as_float(w[u].x) : 0.f;
                         r.y += add ? as_float(w[u].z) : 0.f;
                     }
-                    i0 += SG * wpc * U;
-                } while (i0 - SG * share < G && dead == 0u);
+                    i0 += SG * U;
+                } while (i0 < G && dead == 0u);
             };
             if (loads <= 1) trips(std::integral_constant<int, 1>{});
             else if (loads <= 2) trips(std::integral_constant<int, 2>{});
             else if (loads <= 4) trips(std::integral_constant<int, 4>{});
             else trips(std::integral_constant<int, 8>{});
-            r = pair_slot_sum(r, PPc);
-            // The chunk's wavefronts meet in shared memory.  (Two sets alternate; a set is written again two steps later, behind
-            // rows that waited for the theta made from it.)
-            lds_f32x2* set = (lds_f32x2*)(x.red + (ver & 1u) * NX * 128) + chunk * wpc * 64;
-            if (lane < PPc) set[share * 64 + lane] = r;
-            ex.mark_arrived(ver + 1u);
-            dead |= ex.template wait_ge<false>(x.s_xarrived + chunk * wpc + min(lane, wpc - 1), ver + 1u);
-            asm volatile("" ::: "memory");
-            f32x2 v[NX];
-#pragma unroll
-            for (int k = 0; k < NX; ++k) v[k] = set[min(k, wpc - 1) * 64 + min(up, PPc - 1)];
-#pragma unroll
-            for (int k = 0; k < NX; ++k) {
-                t.x += k < wpc ? v[k].x : 0.f;
-                t.y += k < wpc ? v[k].y : 0.f;
-            }
+            t = pair_slot_sum(r, PW);
         }
-        if (upd) {
-            const f32x2 old = *(const lds_f32x2*)(th_old + uc);
-            const f32x2 now = ex.update(old, t, nb, scale, alpha_s, s - first, lane, true);
-            *(lds_f32x2*)(th_new + uc) = f32x2{now.x, uc + 1 < p ? now.y : 0.f};
-        }
+        ex.apply(th_old, th_new, t, nb, scale, alpha_s, s - first);
         if (dead != 0u) ex.give_up();
         ex.raise_version();
         ++s;
@@ -654,7 +687,7 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
     if (dead != 0u) return;
     if constexpr (OPT) {
         asm volatile("" ::: "memory");
-        if (upd) ex.store_state(lane, a.opt.m + (size_t)g * pp + uc, a.opt.s + (size_t)g * pp + uc);
+        if (ex.own && ex.sg == 0) ex.store_state(ex.pair, a.opt.m + (size_t)g * pp + ex.c, a.opt.s + (size_t)g * pp + ex.c);
     }
     ex.finish(last - first);
 }

@@ -241,7 +241,15 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     const ExchangeLds x{th, stride, xstate, xstate + kExchangeState * kXWaves, sums, stride, (unsigned)RW,
                         (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort,
                         (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
-    if constexpr (ONE) exchange_one_trip<OPT, kXWaves, RW>(a, x, lane, wave);
+    if constexpr (ONE) {
+        // the columns dealt out as few pairs to a wavefront as hold them all
+        constexpr int most = 8 * V * CPL < 64 ? 8 * V * CPL : 64;
+        auto with_pairs = [&](auto pw) { exchange_one_trip<OPT, kXWaves, RW, decltype(pw)::value>(a, x, lane, wave); };
+        if (most >= 64 && p > 256) with_pairs(std::integral_constant<int, most < 64 ? most : 64>{});
+        else if (most >= 32 && p > 128) with_pairs(std::integral_constant<int, most < 32 ? most : 32>{});
+        else if (most >= 16 && p > 64) with_pairs(std::integral_constant<int, most < 16 ? most : 16>{});
+        else with_pairs(std::integral_constant<int, 8>{});
+    }
     else exchange_wavefront<OPT, kXWaves, RW, 8, 2>(a, x, lane, wave);   // (p <= 1024: two loads per lane collect theta; eight cover the slice for up to 256 workgroups)
 }
 
