@@ -902,6 +902,7 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
         a.single_step = -1;
         a.ll_part = ctx->ll_part;
         a.ll_theta = ctx->ll_theta;
+        a.ll_dies = reinterpret_cast<unsigned long long*>(ctx->partial);   // (sums as plain floats are for steps launched one by one)
         a.lr_tab = lr_len ? ctx->lr_tab_dev : nullptr;
         a.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
         a.lr_len = lr_len;
@@ -911,7 +912,7 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
             const int64_t nsteps = (int64_t)np * M;
             if ((uint64_t)ctx->tag_epoch + (uint64_t)nsteps + 1 >= 0xFFFFFFFFull) {
                 // tag space used up: clear the flagged words (stream-ordered) and start over
-                HIP_TRY(ctx, launch_fill_zero(ctx->ll_part, ctx->lay.sync - ctx->lay.ll_part, stream));
+                HIP_TRY(ctx, launch_fill_zero(ctx->partial, ctx->lay.sync - ctx->lay.partial, stream));
                 ctx->tag_epoch = 0;
             }
             a.tag_base = ctx->tag_epoch;

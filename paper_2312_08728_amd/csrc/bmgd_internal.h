@@ -120,6 +120,7 @@ struct GlmArgs {
     float* partial;         // [2][G][p] per-workgroup gradient sums (step-per-launch mode)
     unsigned long long* ll_part;   // [2][G][p] the same sums as flagged words {tag : float}, by step parity
     unsigned long long* ll_theta;  // [2][kThetaCopies][p] updated theta as flagged words (sliced reduction)
+    unsigned long long* ll_dies;   // [2][8][8][p] sums of the workgroups of a die as flagged words, by the die they go to and the one they are from
     unsigned* sync;         // [1] abort flag ([0] unused)
     unsigned tag_base;      // tag of step s is tag_base + (s - s_begin) + 1
     int s_begin, s_end;     // steps of this launch: s in [s_begin, s_end), s = pass * M + batch, all < 2^23
@@ -128,6 +129,7 @@ struct GlmArgs {
     int model;
     int L, logL;
     int reduce_mode;
+    int by_die;             // sliced reduction: 1: over two levels, 0: in two trips (filled in by the kernels' launches)
     float alpha;
     long long timeout_ticks;
     int single_step;        // >= 0: process only that step and stop after writing partial sums
@@ -136,6 +138,9 @@ struct GlmArgs {
     const float* lr_tab;    // optional learning rate per step: step s uses lr_tab[min(lr_base + s, lr_len - 1)]
     int lr_base, lr_len;
 };
+
+// Whether the `lines` wavefronts of each workgroup that add up a line of 16 columns at a time can hold all lines (exchange_by_die).
+inline bool glm_by_die(int64_t p, int G, int lines) { return G % 8 == 0 && (p + 15) / 16 <= (int64_t)(G / 8) * lines; }
 
 // Pick V/CPL/PF/L/block/G/reduce mode for a shape; returns false if p is outside the supported range.
 // persistent: for the chain's kernels (false: for one launch per step, by the general kernel).

@@ -189,6 +189,7 @@ struct ExchangeLds {
     lds_u32* s_published;
     lds_u32* s_theta_version;     // raised by every exchange wavefront once per step: NX v when version v is complete
     lds_i32* s_abort;
+    lds_u32* s_sent;              // raised by every exchange wavefront once per step: the rows of a later step may be requested
     lds_u32* s_xarrived;          // [NX] sets of partial sums each exchange wavefront has left in `red`
     lds_u32* s_xconsumed;         //         sets that the first one has added up (two-trip form)
 };
@@ -305,34 +306,35 @@ struct ExchangeCommon {
         return pair_slot_sum(v[0], PW);
     }
 
-    // this wavefront's share of the workgroup's sums as flagged words: what the others wait for
-    __device__ __forceinline__ void send_sums(__amdgpu_buffer_rsrc_t part, unsigned tag) const
+    // this wavefront's share of the workgroup's sums of the columns below `cover`, as flagged words: what the others wait for
+    template <int SCOPE = kAgentScope>
+    __device__ __forceinline__ void send_sums(__amdgpu_buffer_rsrc_t part, unsigned tag, int cover) const
     {
         auto send = [&](int c, f32x2 v) {
-            __builtin_amdgcn_raw_buffer_store_b128(word_pair(v.x, v.y, tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, kAgentScope);
+            __builtin_amdgcn_raw_buffer_store_b128(word_pair(v.x, v.y, tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, SCOPE);
         };
         asm volatile("" ::: "memory");
         if constexpr (NSUM == 1) {                   // (their reads of shared memory go out together)
 #pragma unroll 8
-            for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) {
+            for (int c0 = 128 * xw; c0 < cover; c0 += 128 * NX) {
                 const int c = c0 + 2 * lane;
-                if (c < p) send(c, sum_of(c));
+                if (c < cover) send(c, sum_of(c));
             }
         } else {
             auto share = [&](auto pw) {
                 constexpr int PW = decltype(pw)::value;
                 const int c = 2 * (PW * xw + (lane & (PW - 1)));
                 const f32x2 v = shared_sum_of<PW>(min(c, pp - 2));
-                if (c < p && lane < PW) send(c, v);
+                if (c < cover && lane < PW) send(c, v);
             };
-            if (p <= 16 * NX) share(std::integral_constant<int, 8>{});
-            else if (p <= 32 * NX) share(std::integral_constant<int, 16>{});
-            else if (p <= 64 * NX) share(std::integral_constant<int, 32>{});
+            if (cover <= 16 * NX) share(std::integral_constant<int, 8>{});
+            else if (cover <= 32 * NX) share(std::integral_constant<int, 16>{});
+            else if (cover <= 64 * NX) share(std::integral_constant<int, 32>{});
             else {
 #pragma unroll 1
-                for (int c0 = 128 * xw; c0 < p; c0 += 128 * NX) {
+                for (int c0 = 128 * xw; c0 < cover; c0 += 128 * NX) {
                     const int c = c0 + 2 * lane;
-                    if (c < p) send(c, sum_of(c));
+                    if (c < cover) send(c, sum_of(c));
                 }
             }
         }
@@ -392,6 +394,11 @@ struct ExchangeCommon {
     {
         asm volatile("" ::: "memory");
         if (lane == 0) lds_add_one(lds_address(x.s_theta_version));
+    }
+    __device__ __forceinline__ void mark_sent() const
+    {
+        asm volatile("" ::: "memory");
+        if (lane == 0) lds_add_one(lds_address(x.s_sent));
     }
     __device__ __forceinline__ void mark_arrived(unsigned count) const
     {
@@ -471,7 +478,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
         // every exchange wavefront has delivered its part of the version that this step's update starts from.)
         dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
         // 0. this workgroup's sums out of shared memory
-        ex.send_sums(part, tag);
+        ex.send_sums(part, tag, p);
 
         // 1. this workgroup's slice, if it has one: sum over all workgroups, in a fixed order; the update; the new
         //    values into every copy of theta
@@ -648,6 +655,7 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
         f32x2 t = ex.own_sum();
         if (G > 1) {
             ex.send(t, part, tag);
+            ex.mark_sent();
             // Words of many workgroups take a wavefront long to fetch: asked for at once they would be fetched twice, none of the others'
             // having come yet (0.27 us per update with 32 workgroups at p = 128, n = 1024; nothing with few)
             if (loads > 2) __builtin_amdgcn_s_sleep(15);
@@ -688,6 +696,160 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
     if constexpr (OPT) {
         asm volatile("" ::: "memory");
         if (ex.own && ex.sg == 0) ex.store_state(ex.pair, a.opt.m + (size_t)g * pp + ex.c, a.opt.s + (size_t)g * pp + ex.c);
+    }
+    ex.finish(last - first);
+}
+
+// The same steps over two levels: the workgroups g with the same g mod 8 first add up their sums among themselves, line by line (16 columns);
+// the eight sums of a line meet in the eight wavefronts that made them, each of which makes the line's update and hands the new values to
+// its own workgroups.  The hardware deals the workgroups of a launch out to its eight dies in turn, so the first and the last of these
+// three trips stay on a die, and their words in the die's L2: they are stored without a scope, which leaves them there, and read at device
+// scope, which passes the unit's own cache by.  Whether the workgroups are where they should be is looked at in every launch (`near`).
+//
+// What it is for: a trip between workgroups of one die takes 0.4 to 0.6 us, one over the fabric 1.0 and more, and a slice of 16 columns is 256 words
+// a column there, which four wavefronts fetch and hand over to one (0.7 us); here a wavefront asks for 4 of them a lane and then for one.  us per
+// update, two trips / this: 3.48 / 2.86 at p = 200, n = 4096 (256 workgroups), 3.64 / 3.27 at p = 512, n = 1000 with Adam (160), 3.19 / 2.83 at 128, 900 (40),
+// 3.91 / 3.61 at 1000, 500 (160), 5.06 / 4.70 at 1024, 2000 (256); rows of more than 1024 floats 5.54 / 5.01 at 1500, 1000, 5.57 / 4.67 at 2048, 300.
+// The eight sums of a line go to every die separately: a line that all dies ask for took 1.45 us instead of 1.18, one that four wavefronts
+// write a quarter of 2.6.  Every workgroup making the whole update from the dies' sums costs a trip less and more for its words: 3.5 us at p = 200.
+// It is the faster way as long as a wavefront has one line (up to 1024 floats) or two: each line more is two trips one behind the other (4.20
+// against 3.32 at p = 200 on 24 workgroups, 16.3 against 3.7 at p = 1000 on 16), which the callers' rule sees to (glm_by_die).
+// LW: lines a wavefront takes at a time.  U2: pairs of words a lane requests at a time when it collects theta.
+template <bool OPT, int NX, int NSUM, int LW, int U2>
+__device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
+{
+    ExchangeCommon<OPT, NX, NSUM> ex(a, x, lane, xw);
+    const int G = ex.G, g = ex.g, p = ex.p, pp = ex.pp;
+    const int first = a.s_begin, last = a.s_end;
+    const int die = g & 7, i_die = g >> 3, G_die = G >> 3;
+    // line l: wavefront l / G_die of workgroup l mod G_die of each die; eight pairs by eight groups of lanes, each taking every eighth
+    // workgroup in the first trip and one die's sum in the second
+    const int lines = pp / 16;
+    const int lpair = lane & 7, lsg = lane >> 3;
+    const int l0 = i_die + G_die * xw, dl = G_die * NX;
+    const unsigned lrow = (unsigned)(8 * min(lsg, G_die - 1) + die) * (unsigned)(pp * 8);
+    const unsigned drow = (unsigned)(8 * die + lsg) * (unsigned)(pp * 8);
+    const unsigned dies_bytes = (unsigned)(64u * (unsigned)pp * 8u);
+    if constexpr (OPT) {                             // (what a wavefront reads here is written back behind sums that it has contributed to)
+        int k = 0;
+        for (int l = l0; l < lines; l += dl, ++k)
+            if (lane < 8) ex.load_state(8 * k + lane, a.opt.m + 16 * l + 2 * lane, a.opt.s + 16 * l + 2 * lane);
+    }
+    unsigned dead = 0u;
+    // Which die is this workgroup on, and are the others of its first level there as well?  (In the row of words that the second step uses.)
+    bool near;
+    {
+        const unsigned tag = a.tag_base + 1u;
+        const unsigned xcc = (unsigned)__builtin_amdgcn_s_getreg(6164);          // XCC_ID, bits 0 .. 3
+        unsigned long long* row0 = a.ll_part + (size_t)((first + 1) & 1) * G * pp;
+        if (xw == 0 && lane == 0) ll_store(row0 + (size_t)g * pp, as_float(xcc), tag);
+        const __amdgpu_buffer_rsrc_t rows = words_rsrc(row0, ex.words_bytes);
+        u32x4 w[1];
+        const unsigned from = (unsigned)(8 * min(lane, G_die - 1) + die) * (unsigned)(pp * 8);
+        dead |= ex.poll(tag, w, [&](int) { return __builtin_amdgcn_raw_buffer_load_b128(rows, from, 0u, kAgentScope); }, [&](const u32x4& v, int) { return v.y; });
+        near = __builtin_amdgcn_ballot_w64(w[0].x != xcc) == 0ull;
+    }
+    int s = first;
+#pragma clang loop unroll(disable)
+    do {
+        const unsigned tag = a.tag_base + (unsigned)(s - first) + 1u;
+        const float alpha_s = a.lr_tab ? a.lr_tab[min(a.lr_base + s, a.lr_len - 1)] : a.alpha;
+        const float nb = (float)ex.geo.batch_rows(s);
+        const float scale = alpha_s / nb;
+        const unsigned ver = (unsigned)(s - first);
+        const lds_f32* th_old = x.th + (ver & 1u) * x.th_stride;
+        lds_f32* th_new = x.th + ((ver + 1u) & 1u) * x.th_stride;
+        ex.corrections(s - first);
+        const __amdgpu_buffer_rsrc_t part = words_rsrc(a.ll_part + (size_t)(s & 1) * G * pp, ex.words_bytes);
+        const __amdgpu_buffer_rsrc_t dies = words_rsrc(a.ll_dies + (size_t)(s & 1) * 64 * pp, dies_bytes);
+        const __amdgpu_buffer_rsrc_t mine = words_rsrc(a.ll_theta + ((size_t)(s & 1) * kThetaCopies + (size_t)die) * pp, (unsigned)(pp * 8));
+        dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
+        if (near) ex.template send_sums<0>(part, tag, pp);
+        else ex.template send_sums<kAgentScope>(part, tag, pp);
+        if (l0 >= lines) ex.mark_sent();
+        for (int l = l0, k0 = 0; l < lines && dead == 0u; l += LW * dl, k0 += 8 * LW) {
+            f32x2 r[LW];
+            {
+                u32x4 w[4 * LW];
+                dead |= ex.poll(tag, w,
+                    [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(part, lrow + (unsigned)lpair * 16u, (unsigned)(8 * max(0, min(8 * (u & 3), G_die - 8))) * (unsigned)(pp * 8) + (unsigned)min(l + dl * (u >> 2), lines - 1) * 128u, kAgentScope); },
+                    [&](const u32x4& v, int) { return min(v.y, v.w); });
+#pragma unroll
+                for (int j = 0; j < LW; ++j) {
+                    r[j] = f32x2{0.f, 0.f};
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const bool add = 8 * u < G_die && lsg < G_die && max(0, min(8 * u, G_die - 8)) + lsg >= 8 * u;
+                        r[j].x += add ? as_float(w[4 * j + u].x) : 0.f;
+                        r[j].y += add ? as_float(w[4 * j + u].z) : 0.f;
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < LW; ++j) {
+                r[j] = pair_slot_sum(r[j], 8);
+                if (j == 0 || l + dl * j < lines)    // (to the eight dies)
+                    __builtin_amdgcn_raw_buffer_store_b128(word_pair(r[j].x, r[j].y, tag), dies, (unsigned)((8 * lsg + die) * pp + 2 * lpair) * 8u, (unsigned)(l + dl * j) * 128u, kAgentScope);
+            }
+            if (l == l0) ex.mark_sent();
+            {
+                u32x4 w[LW];
+                dead |= ex.poll(tag, w,
+                    [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(dies, drow + (unsigned)lpair * 16u, (unsigned)min(l + dl * u, (l + dl * u < lines ? lines - 1 : l)) * 128u, kAgentScope); },
+                    [&](const u32x4& v, int) { return min(v.y, v.w); });
+#pragma unroll
+                for (int j = 0; j < LW; ++j) r[j] = pair_slot_sum(f32x2{as_float(w[j].x), as_float(w[j].z)}, 8);
+            }
+#pragma unroll
+            for (int j = 0; j < LW; ++j)
+                if (j == 0 || l + dl * j < lines) {
+                    const int c = 16 * (l + dl * j) + 2 * lpair;
+                    const f32x2 old = *(const lds_f32x2*)(th_old + c);
+                    const f32x2 now = ex.update(old, r[j], nb, scale, alpha_s, s - first, k0 + 8 * j + lpair, lane < 8);
+                    if (lane < 8) {
+                        if (near) __builtin_amdgcn_raw_buffer_store_b128(word_pair(now.x, now.y, tag), mine, (unsigned)c * 8u, 0u, 0);
+                        else __builtin_amdgcn_raw_buffer_store_b128(word_pair(now.x, now.y, tag), mine, (unsigned)c * 8u, 0u, kAgentScope);
+                    }
+                }
+        }
+        // the whole new theta, from this die's copy
+        if (128 * xw < p && dead == 0u) {
+            const unsigned copy_off = (unsigned)lane * 16u;
+            auto collect = [&](auto count, int c0) {
+                constexpr int U = decltype(count)::value;
+                u32x4 w[U];
+                dead |= ex.poll(tag, w,
+                    [&](int u) { return __builtin_amdgcn_raw_buffer_load_b128(mine, copy_off, (unsigned)(c0 + 128 * NX * u) * 8u, kAgentScope); },
+                    [&](const u32x4& v, int u) { return c0 + 2 * (lane + 64 * NX * u) < p ? min(v.y, v.w) : tag; });
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int c = c0 + 2 * (lane + 64 * NX * u);
+                    if (c < p) *(lds_f32x2*)(th_new + c) = f32x2{as_float(w[u].x), c + 1 < p ? as_float(w[u].z) : 0.f};
+                }
+            };
+            if (p <= 128 * NX) {
+                collect(std::integral_constant<int, 1>{}, 128 * xw);
+            } else {
+                int c0 = 128 * xw;
+#pragma clang loop unroll(disable)
+                do {
+                    collect(std::integral_constant<int, U2>{}, c0);
+                    c0 += 128 * NX * U2;
+                } while (c0 < p && dead == 0u);
+            }
+        }
+        if (dead != 0u) ex.give_up();
+        ex.raise_version();
+        ++s;
+    } while (s < last && dead == 0u);
+    if (dead != 0u) return;
+    if constexpr (OPT) {
+        asm volatile("" ::: "memory");
+        if (die == 0) {
+            int k = 0;
+            for (int l = l0; l < lines; l += dl, ++k)
+                if (lane < 8) ex.store_state(8 * k + lane, a.opt.m + 16 * l + 2 * lane, a.opt.s + 16 * l + 2 * lane);
+        }
     }
     ex.finish(last - first);
 }

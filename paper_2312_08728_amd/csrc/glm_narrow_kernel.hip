@@ -56,6 +56,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     extern __shared__ __align__(16) float smem[];
     __shared__ int s_abort;                          // set by the exchange wavefront when a wait ran out
     __shared__ unsigned s_theta_version;             // versions of theta delivered to shared memory so far
+    __shared__ unsigned s_sent;                      // raised by the exchange wavefronts: a step's sums are on their way
     __shared__ unsigned s_published;                 // publications of row wavefronts, counted over all steps
     __shared__ unsigned s_xarrived[kXWaves], s_xconsumed;   // hand-over of partial sums between the exchange wavefronts
 
@@ -75,7 +76,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
 
     // theta (version 0 in copy 0) and the sums; columns beyond p stay zero for good (rows are read at column 0 there)
     for (int c = tid; c < (2 + RW) * stride; c += narrow_block(RW)) th[c] = c < p ? a.theta[c] : 0.f;
-    if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_xconsumed = 0u; }
+    if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_sent = 0u; s_xconsumed = 0u; }
     if (tid < kXWaves) s_xarrived[tid] = 0u;
     __syncthreads();                                 // the only barrier: from here on the wavefronts meet through flags
 
@@ -144,6 +145,8 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
 
         const unsigned abort_addr = (unsigned)(uintptr_t)(lds_u32*)&s_abort;
         const unsigned version_addr = (unsigned)(uintptr_t)(lds_u32*)&s_theta_version;
+        const bool gated = ONE ? G > 1 : a.by_die != 0;
+        const unsigned sent_addr = (unsigned)(uintptr_t)(lds_u32*)&s_sent;
         lds_f32* my_sums = sums + rw * stride;
         // Step s on the rows in S, then S is refilled.  Straight-line code with one conditional (the publication).  A
         // step past the end uses rows requested beyond the end, publishes nothing and waits for the last version only.
@@ -219,6 +222,9 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
                 asm volatile("" ::: "memory");
                 if (lane == 0) lds_add_one(lds_address((lds_u32*)&s_published));
             }
+            // What the exchange sends and asks for first would stand behind these requests in the unit's memory pipeline; they go out while
+            // its words are under way.
+            lds_wait_ge(sent_addr, gated ? (unsigned)(min(s + 1, last) - first) * kXWaves : 0u, abort_addr);
             request(S);
         };
         int su = first;
@@ -239,7 +245,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     // ------------------------------------------------------------------------------------ exchange wavefronts
     __builtin_amdgcn_s_setprio(3);                   // (they share their SIMDs with row wavefronts that are requesting rows)
     const ExchangeLds x{th, stride, xstate, xstate + kExchangeState * kXWaves, sums, stride, (unsigned)RW,
-                        (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort,
+                        (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)&s_sent,
                         (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
     if constexpr (ONE) {
         // the columns dealt out as few pairs to a wavefront as hold them all
@@ -250,7 +256,8 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
         else if (most >= 16 && p > 64) with_pairs(std::integral_constant<int, most < 16 ? most : 16>{});
         else with_pairs(std::integral_constant<int, 8>{});
     }
-    else exchange_wavefront<OPT, kXWaves, RW, 8, 2>(a, x, lane, wave);   // (p <= 1024: two loads per lane collect theta; eight cover the slice for up to 256 workgroups)
+    else if (a.by_die) exchange_by_die<OPT, kXWaves, RW, 1, 2>(a, x, lane, wave);   // (p <= 1024: two loads per lane collect theta ...
+    else exchange_wavefront<OPT, kXWaves, RW, 8, 2>(a, x, lane, wave);   // ... and eight cover the slice for up to 256 workgroups)
 }
 
 using KernelFn = void (*)(GlmArgs);
@@ -352,7 +359,9 @@ hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipSt
     if (one_trip ? s.narrow_rw == kRowWaves || args.p > kNarrowOneTripMaxP || s.G < 1
                  : s.G < 8 || s.G % 8 != 0 || (s.narrow_rw != kRowWaves && s.V != 1))
         return hipErrorInvalidValue;
-    hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), (uint32_t)narrow_lds_bytes(s, args.p), stream, nullptr, stop, 0u, args);
+    GlmArgs a = args;
+    a.by_die = !one_trip && glm_by_die(args.p, s.G, kXWaves);
+    hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), (uint32_t)narrow_lds_bytes(s, args.p), stream, nullptr, stop, 0u, a);
     return hipGetLastError();
 }
 

@@ -67,6 +67,7 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     extern __shared__ __align__(16) float smem[];
     __shared__ int s_abort;                          // set by an exchange wavefront when a wait ran out
     __shared__ unsigned s_theta_version;             // versions of theta delivered to shared memory so far
+    __shared__ unsigned s_sent;                      // (nobody waits for it: the rows in flight are many steps' here)
     __shared__ unsigned s_published;                 // row wavefronts that have stored their sums, counted over all steps
     __shared__ unsigned s_xarrived[NX], s_xconsumed; // hand-over of partial sums between the exchange wavefronts
 
@@ -91,7 +92,7 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     // both copies of theta: columns beyond p stay zero for good (rows are read at column 0 there)
     for (int c = tid; c < 2 * P_PAD; c += kSplitBlock) th[c] = c < p ? a.theta[c] : 0.f;
     if (tid < 2 * kRowWaves) pd_seq[tid] = 0u;
-    if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_xconsumed = 0u; }
+    if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_sent = 0u; s_xconsumed = 0u; }
     if (tid < NX) s_xarrived[tid] = 0u;
     __syncthreads();                                 // the only barrier: from here on the wavefronts meet through flags
 
@@ -252,8 +253,9 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
 
     // ------------------------------------------------------------------------------------ exchange wavefronts
     const ExchangeLds x{th, P_PAD, xstate, xstate + kExchangeState * NX, sums, P_PAD, (unsigned)kRowWaves,
-                        (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
-    exchange_wavefront<OPT, NX, 1, 11, CH == 1 ? 6 : 11>(a, x, lane, wave);   // (a trip's words at once, for up to 256 workgroups and p columns)
+                        (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)&s_sent, (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
+    if (CH == 1 && a.by_die) exchange_by_die<OPT, NX, 1, 2, 6>(a, x, lane, wave);
+    else exchange_wavefront<OPT, NX, 1, 11, CH == 1 ? 6 : 11>(a, x, lane, wave);   // (a trip's words at once, for up to 256 workgroups and p columns)
 }
 
 using KernelFn = void (*)(GlmArgs);
@@ -293,7 +295,12 @@ hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStr
 {
     if (G < 8 || G % 8 != 0 || args.s_begin >= args.s_end || args.p % 4 != 0 || args.p > kRowWaves * 256 * ch)
         return hipErrorInvalidValue;
-    hipExtLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, args);
+    // Three short trips instead of two where a wavefront has two lines at most and a step few rows, so that little stands in the queues that
+    // the trips share with them.  us per update, two trips / three: 6.1 / 5.7 at p = 1028, n = 1500, 8.1 / 8.0 at 1500, 3000, 7.89 / 7.84 at 2048, 2048
+    // (256 workgroups), but 16.9 / 17.6 at 2048, 8192; 9.23 / 9.33 at 2500, 1500 and 12.3 / 13.0 at 4096, 2048 with three lines at a time.
+    GlmArgs a = args;
+    a.by_die = ch == 1 && glm_by_die(args.p, G, 2 * NX) && args.n <= 12 * G;
+    hipExtLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, a);
     return hipGetLastError();
 }
 

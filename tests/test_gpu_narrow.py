@@ -168,3 +168,37 @@ def test_one_workgroup_is_chosen_for_the_chain_kernel_alone(p, n, launched):
         got, st = gpu_run(w, X, y, chain=chain)
         assert st.chain == chain and st.n_workgroups == G
         assert rel_l2(got, want) <= TOL
+
+
+# (model, p, n, G, N0): sums added up over two levels, on the dies first.  A line of 16 columns belongs to one wavefront of one workgroup of each
+# die (four take part, three for rows of more than 1024 floats, which may have two lines), which asks for four workgroups' words a lane.
+BY_DIE = [
+    (wl.LOGISTIC, 20, 9000, 256, 20_000),    # two lines, the second of four columns; 32 workgroups a die
+    (wl.LINEAR, 128, 900, 40, 3_000),        # 5 workgroups a die: fewer than a wavefront has groups of lanes
+    (wl.LOGISTIC, 500, 700, 64, 2_000),      # 8 a die, 32 lines: every wavefront has one
+    (wl.LINEAR, 200, 1500, 72, 4_000),       # 9 a die: the second load repeats seven
+    (wl.LOGISTIC, 1024, 600, 128, 2_000),    # 64 lines for 64 wavefronts
+    (wl.LINEAR, 300, 2400, 200, 6_000),      # 25 a die
+    (wl.LOGISTIC, 1028, 500, 88, 1_500),     # 65 lines for 33 wavefronts, two each but one
+    (wl.LINEAR, 2048, 400, 176, 1_000),      # 128 for 66
+    (wl.LOGISTIC, 1500, 900, 256, 2_500),    # 94 for 96: the second line of each is beyond the end
+]
+
+
+@pytest.mark.parametrize("optimizer", [0, 2, 3])
+@pytest.mark.parametrize("model,p,n,G,N0", BY_DIE)
+def test_sums_added_up_on_the_dies_first(model, p, n, G, N0, optimizer):
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    w = _case(model, 2 * N0 - 77, p, N0, n, T=5, R=1, alpha=0.01 if optimizer == 3 else 0.05 if model == wl.LOGISTIC else 0.2 / (p + 10))
+    X, y = wl.dataset(w)
+    ref = O.BMGD(w.model, w.p, w.n, w.alpha, w.T)
+    if optimizer:
+        ref.set_optimizer(optimizer)
+    for k in range(2):
+        ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
+    got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
+    assert st.threads_per_group == (704 if p > 1024 else NARROW_THREADS) and st.n_workgroups == G
+    assert rel_l2(got, ref.theta) <= TOL
+    again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
+    assert np.array_equal(got, again)
