@@ -88,6 +88,14 @@ __device__ __forceinline__ float opt_update(const OptArgs& o, float th, float g,
 
 enum { kReduceRedundant = 0, kReduceSliced = 1 };
 
+// How the lanes of a wavefront hold a row in the kernel for rows of up to 1024 floats.
+struct NarrowLayout {
+    int V;              // floats per vector load (4; 2 or 1 for rows of fewer than eight floats)
+    int CPL;            // vectors of a row per lane
+    int L;              // lanes cooperating on one row (power of two, 4 .. 64)
+    int width;          // positions of a row: theirs, an even number
+};
+
 struct GlmLaunchShape {
     int V;              // floats per vector load (1, 2, 4)
     int CPL;            // vector chunks of a row held per lane
@@ -105,8 +113,9 @@ struct GlmLaunchShape {
     int split_ch;
     int narrow;         // 1: the persistent chain runs the kernel for rows of up to 1024 floats whose share of a step fits a
                         // workgroup's registers (glm_narrow_kernel.hip): narrow_pf rows per row slot of narrow_rw row wavefronts
-                        // (8: sliced reduction, G a multiple of 8; 12: redundant reduction, or odd p)
+                        // (8: sliced reduction, G a multiple of 8; 12: redundant reduction, or sliced with odd p)
     int narrow_pf, narrow_rw;
+    NarrowLayout narrow_layout;
     int64_t n;          // mini-batch size and row length the shape was planned for
     int p;
     int chain_block;    // threads per workgroup of the persistent chain's kernel
@@ -129,9 +138,11 @@ struct GlmArgs {
     int model;
     int L, logL;
     int reduce_mode;
-    int by_die;             // sliced reduction: 1: over two levels, 0: in two trips (filled in by the kernels' launches)
+    int by_die;             // rows of more than 1024 floats: 1: sums over two levels, 0: in two trips (filled in by the kernel's launch)
     float alpha;
     long long timeout_ticks;
+    int width, shift;       // positions of a row in shared memory, and how many of the last four stand for no column (filled in by
+                            //   the launches of the kernels that lay rows out so, glm_exchange.h)
     int single_step;        // >= 0: process only that step and stop after writing partial sums
     OptArgs opt;            // kind == kOptSgd: plain steps, no state.  Redundant reduction: every workgroup keeps a
                             // private copy of the state at m + blockIdx.x * pp (all copies stay identical)
@@ -166,7 +177,8 @@ hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStr
 constexpr int kNarrowMoreRows = 12;        // row wavefronts where the sums are added up by every workgroup, or p is odd
 constexpr int kNarrowOneTripMaxP = 512;    // widest rows of the redundant reduction in this kernel
 int glm_narrow_block(int rw);
-int glm_narrow_rows_in_flight(int v, int cpl, int L, int rw, int G, int64_t n);
+NarrowLayout glm_narrow_layout(int64_t p);
+int glm_narrow_rows_in_flight(const NarrowLayout& l, int rw, int G, int64_t n);
 hipError_t glm_narrow_prepare(const GlmLaunchShape& shape, int p, int* max_groups);
 hipError_t glm_narrow_launch(const GlmLaunchShape& shape, const GlmArgs& args, hipStream_t stream, hipEvent_t stop);
 

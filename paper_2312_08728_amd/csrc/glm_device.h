@@ -99,6 +99,19 @@ __device__ __forceinline__ void load_vec(const float* __restrict__ src, float* d
     }
 }
 
+// The same from any multiple of four bytes (one load instruction all the same).
+template <int V>
+__device__ __forceinline__ void load_vec_unaligned(const float* __restrict__ src, float* dst)
+{
+    if constexpr (V == 4) {
+        struct __attribute__((packed, aligned(4))) Four { float x, y, z, w; };
+        const Four t = *reinterpret_cast<const Four*>(src);
+        dst[0] = t.x; dst[1] = t.y; dst[2] = t.z; dst[3] = t.w;
+    } else {
+        load_vec<V>(src, dst);
+    }
+}
+
 __device__ __forceinline__ float residual(int model, float u, float y)
 {
     if (model == kLogistic) {

@@ -162,6 +162,23 @@ struct StepGeometry {
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
 
+// A row is taken as whole vectors of four floats whatever its length: its last vector starts four columns before its end, so that it may repeat
+// up to three columns of the one before.  Theta, sums, words and the state of an update rule are laid out the same way, by position: width of
+// them (an even number), the first `shift` of the last four standing for no column.  These hold 0 in theta; what is added up there is
+// not looked at.  (Rows of fewer than eight floats that are no multiple of four keep to smaller vectors, and have no such positions.)
+// The hardware loads vectors from any multiple of four bytes; rows loaded float by float or in pairs took 5.5 instead of 3.3 us per update at
+// p = 301, n = 1000, 9.5 instead of 5.6 at 1502, 1000, 3.5 instead of 2.9 at 201, 1500: these then did not fit the registers, or took as many
+// times the loads.
+__device__ __forceinline__ int position_of(const GlmArgs& a, int c) { return c + (c >= a.width - 4 ? a.shift : 0); }
+// the column of a position (below `width`), or one below 0 where there is none
+__device__ __forceinline__ int column_of(const GlmArgs& a, int pos)
+{
+    const int k = pos - (a.width - 4);
+    return k < 0 ? pos : k < a.shift ? -1 : pos - a.shift;
+}
+// where the vector of a row that starts at a position is loaded from; beyond the row (theta is 0 there) its start
+__device__ __forceinline__ int vector_from(const GlmArgs& a, int pos) { return pos >= a.width ? 0 : pos - (pos >= a.width - 4 ? a.shift : 0); }
+
 // The sum over the lanes with the same lane % PPc (8 <= PPc <= 64, uniform), in all of them.
 __device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
 {
@@ -178,13 +195,13 @@ __device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
 
 // The exchange wavefronts' view of the workgroup's shared memory.
 struct ExchangeLds {
-    lds_f32* th;                  // [2][th_stride]: theta by version parity (th_stride even, >= p rounded up to even)
+    lds_f32* th;                  // [2][th_stride]: theta by version parity (th_stride even, >= the positions of a row)
     int th_stride;
     lds_f32* state;               // [NX][3][64][2]: for each exchange wavefront Adam's bias corrections of the coming steps, and the state
                                   //   of the pairs of columns it updates
     lds_f32* red;                 // [2][NX][64][2]: the exchange wavefronts' partial sums, by parity
     const lds_f32* sums;          // [NSUM][sums_stride]: the workgroup's gradient sums of a step; column c is the sum over
-    int sums_stride;              //   the NSUM arrays (even; columns [p, p rounded up to even) hold 0)
+    int sums_stride;              //   the NSUM arrays (even)
     unsigned publishers;          // publications of row wavefronts that complete a step
     lds_u32* s_published;
     lds_u32* s_theta_version;     // raised by every exchange wavefront once per step: NX v when version v is complete
@@ -208,14 +225,16 @@ struct ExchangeCommon {
     const GlmArgs& a;
     const ExchangeLds& x;
     const int lane, xw;
-    const int G, g, p, pp;
+    const int G, g;
+    const int p;                                     // positions of a row, for columns (as everywhere in the exchange)
+    const int pp;
     const StepGeometry geo;
     const unsigned words_bytes;
     const unsigned abort_addr;
     long long poll_start = 0;                        // when the words of a trip were first asked for
 
     __device__ __forceinline__ ExchangeCommon(const GlmArgs& a_, const ExchangeLds& x_, int lane_, int xw_)
-        : a(a_), x(x_), lane(lane_), xw(xw_), G(gridDim.x), g(blockIdx.x), p(a_.p), pp((a_.p + 15) & ~15), geo(a_),
+        : a(a_), x(x_), lane(lane_), xw(xw_), G(gridDim.x), g(blockIdx.x), p(a_.width), pp((a_.p + 15) & ~15), geo(a_),
           words_bytes((unsigned)((size_t)gridDim.x * (size_t)((a_.p + 15) & ~15) * 8)), abort_addr(lds_address(x_.s_abort))
     {
     }
@@ -367,26 +386,43 @@ struct ExchangeCommon {
         m[0] = v.x; m[1] = v.y;
         if (a.opt.kind == kOptAdam) { s[0] = w.x; s[1] = w.y; }
     }
-    // The update of one pair of columns: new values from the old ones and the pair's sums.  k: where its state is kept (`writes`: by
-    // this lane; lanes that hold the same pair make the same update).
-    __device__ __forceinline__ f32x2 update(f32x2 old, f32x2 sum, float nb, float scale, float alpha, int done, int k, bool writes) const
+    // The update of the pair of columns c, c + 1: new values from the old ones and the pair's sums.  k: where its state is kept (`writes`: by
+    // this lane; lanes that hold the same pair make the same update).  HALVES: lanes 32 apart hold the same pair, so each of them works out
+    // one column (Adam's square root and divisions: 0.15 us of a step for a pair).
+    template <bool HALVES>
+    __device__ __forceinline__ f32x2 update(f32x2 old, f32x2 sum, float nb, float scale, float alpha, int done, int k, bool writes, int c) const
     {
+        f32x2 now;
         if constexpr (!OPT) {
-            return f32x2{old.x - scale * sum.x, old.y - scale * sum.y};
+            now = f32x2{old.x - scale * sum.x, old.y - scale * sum.y};
         } else {
             asm volatile("" ::: "memory");
-            lds_f32x2* keep = (lds_f32x2*)(x.state + xw * 384 + 128) + k;
-            const f32x2 c = ((const lds_f32x2*)(x.state + xw * 384))[done & 63];   // (not looked at but by Adam)
-            const f32x2 m = keep[0], s = keep[64];
-            float m0 = m.x, m1 = m.y, s0 = s.x, s1 = s.y;
-            const float n0 = opt_update(a.opt, old.x, sum.x / nb, alpha, m0, s0, c.x, c.y);
-            const float n1 = opt_update(a.opt, old.y, sum.y / nb, alpha, m1, s1, c.x, c.y);
-            if (writes) {
-                keep[0] = f32x2{m0, m1};
-                if (a.opt.kind == kOptAdam) keep[64] = f32x2{s0, s1};
+            const f32x2 f = ((const lds_f32x2*)(x.state + xw * 384))[done & 63];   // (not looked at but by Adam)
+            if constexpr (HALVES) {
+                const bool second = lane >= 32;
+                lds_f32* keep = x.state + xw * 384 + 128 + 2 * k + (second ? 1 : 0);
+                float m = keep[0], s = keep[128];
+                now.x = opt_update(a.opt, second ? old.y : old.x, (second ? sum.y : sum.x) / nb, alpha, m, s, f.x, f.y);
+                if (writes) {
+                    keep[0] = m;
+                    if (a.opt.kind == kOptAdam) keep[128] = s;
+                }
+                now.y = now.x;
+                asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1\n\ts_nop 1" : "+v"(now.x), "+v"(now.y));
+            } else {
+                lds_f32x2* keep = (lds_f32x2*)(x.state + xw * 384 + 128) + k;
+                const f32x2 m = keep[0], s = keep[64];
+                float m0 = m.x, m1 = m.y, s0 = s.x, s1 = s.y;
+                now.x = opt_update(a.opt, old.x, sum.x / nb, alpha, m0, s0, f.x, f.y);
+                now.y = opt_update(a.opt, old.y, sum.y / nb, alpha, m1, s1, f.x, f.y);
+                if (writes) {
+                    keep[0] = f32x2{m0, m1};
+                    if (a.opt.kind == kOptAdam) keep[64] = f32x2{s0, s1};
+                }
             }
-            return f32x2{n0, n1};
         }
+        const int hole = c - (p - 4);
+        return f32x2{(unsigned)hole < (unsigned)a.shift ? 0.f : now.x, (unsigned)(hole + 1) < (unsigned)a.shift ? 0.f : now.y};
     }
 
     // (everything this wavefront has stored to shared memory stays in front of the count)
@@ -413,7 +449,7 @@ struct ExchangeCommon {
             if (wait_ge<true>(x.s_theta_version, NX * (unsigned)steps)) return;
             asm volatile("" ::: "memory");
             const lds_f32* fin = x.th + ((unsigned)steps & 1u) * x.th_stride;
-            for (int c = lane; c < p; c += 64) a.theta[c] = fin[c];
+            for (int c = lane; c < a.p; c += 64) a.theta[c] = fin[position_of(a, c)];
         }
     }
 };
@@ -532,7 +568,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
                 }
                 if (own && xw == 0) {
                     const f32x2 old = *(const lds_f32x2*)(th_old + c);
-                    const f32x2 now = ex.update(old, t, nb, scale, alpha_s, s - first, my_pair, my_sg == 0);
+                    const f32x2 now = ex.template update<false>(old, t, nb, scale, alpha_s, s - first, my_pair, my_sg == 0, c);
                     const u32x4 nw = word_pair(now.x, now.y, tag);
                     // the groups of lanes share the copies between them
                     const unsigned to = (unsigned)c * 8u + (unsigned)(my_sg * pp * 8);
@@ -562,7 +598,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int c = c0 + 2 * (lane + 64 * NX * u);
-                    if (c < p) *(lds_f32x2*)(th_new + c) = f32x2{as_float(w[u].x), c + 1 < p ? as_float(w[u].z) : 0.f};
+                    if (c < p) *(lds_f32x2*)(th_new + c) = f32x2{as_float(w[u].x), as_float(w[u].z)};
                 }
             };
             if (p <= 128 * NX) {
@@ -599,7 +635,7 @@ struct PairExchange : ExchangeCommon<OPT, NX, NSUM> {
     const int cc;                                    //   or where there is none the last one
     const bool own;
     __device__ __forceinline__ PairExchange(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
-        : ExchangeCommon<OPT, NX, NSUM>(a, x, lane, xw), pair(lane & (PW - 1)), sg(lane / PW), c(2 * (PW * xw + pair)), cc(min(c, this->pp - 2)), own(c < a.p)
+        : ExchangeCommon<OPT, NX, NSUM>(a, x, lane, xw), pair(lane & (PW - 1)), sg(lane / PW), c(2 * (PW * xw + pair)), cc(min(c, this->pp - 2)), own(c < this->p)
     {
     }
 
@@ -618,8 +654,8 @@ struct PairExchange : ExchangeCommon<OPT, NX, NSUM> {
     __device__ __forceinline__ void apply(const lds_f32* th_old, lds_f32* th_new, f32x2 sum, float nb, float scale, float alpha, int done)
     {
         const f32x2 old = *(const lds_f32x2*)(th_old + cc);
-        const f32x2 now = this->update(old, sum, nb, scale, alpha, done, pair, own && sg == 0);
-        if (own && sg == 0) *(lds_f32x2*)(th_new + c) = f32x2{now.x, c + 1 < this->p ? now.y : 0.f};
+        const f32x2 now = this->template update<(PW <= 32)>(old, sum, nb, scale, alpha, done, pair, own && (this->lane & 31) < PW, c);
+        if (own && sg == 0) *(lds_f32x2*)(th_new + c) = now;
     }
 };
 
@@ -713,7 +749,8 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
 // The eight sums of a line go to every die separately: a line that all dies ask for took 1.45 us instead of 1.18, one that four wavefronts
 // write a quarter of 2.6.  Every workgroup making the whole update from the dies' sums costs a trip less and more for its words: 3.5 us at p = 200.
 // It is the faster way as long as a wavefront has one line (up to 1024 floats) or two: each line more is two trips one behind the other (4.20
-// against 3.32 at p = 200 on 24 workgroups, 16.3 against 3.7 at p = 1000 on 16), which the callers' rule sees to (glm_by_die).
+// against 3.32 at p = 200 on 24 workgroups, 16.3 against 3.7 at p = 1000 on 16; both lines in the same trips: 3.60 against 3.23 at p = 400 on 32,
+// 4.26 against 3.76 at p = 1000 on 64), which the callers' rule sees to (glm_by_die).
 // LW: lines a wavefront takes at a time.  U2: pairs of words a lane requests at a time when it collects theta.
 template <bool OPT, int NX, int NSUM, int LW, int U2>
 __device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
@@ -805,7 +842,7 @@ __device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const Exchange
                 if (j == 0 || l + dl * j < lines) {
                     const int c = 16 * (l + dl * j) + 2 * lpair;
                     const f32x2 old = *(const lds_f32x2*)(th_old + c);
-                    const f32x2 now = ex.update(old, r[j], nb, scale, alpha_s, s - first, k0 + 8 * j + lpair, lane < 8);
+                    const f32x2 now = ex.template update<true>(old, r[j], nb, scale, alpha_s, s - first, k0 + 8 * j + lpair, (lane & 31) < 8, c);
                     if (lane < 8) {
                         if (near) __builtin_amdgcn_raw_buffer_store_b128(word_pair(now.x, now.y, tag), mine, (unsigned)c * 8u, 0u, 0);
                         else __builtin_amdgcn_raw_buffer_store_b128(word_pair(now.x, now.y, tag), mine, (unsigned)c * 8u, 0u, kAgentScope);
@@ -824,7 +861,7 @@ __device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const Exchange
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const int c = c0 + 2 * (lane + 64 * NX * u);
-                    if (c < p) *(lds_f32x2*)(th_new + c) = f32x2{as_float(w[u].x), c + 1 < p ? as_float(w[u].z) : 0.f};
+                    if (c < p) *(lds_f32x2*)(th_new + c) = f32x2{as_float(w[u].x), as_float(w[u].z)};
                 }
             };
             if (p <= 128 * NX) {

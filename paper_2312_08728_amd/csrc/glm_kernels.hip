@@ -679,15 +679,15 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
     if (G < 1) G = 1;
     if (G > num_cus) G = num_cus;
     // Narrow rows, a step's rows fitting the registers: the kernel with exchange wavefronts.  Where the sums of all workgroups are few
-    // enough every workgroup adds them up itself, in one trip over the fabric per step instead of two.
-    const int L = std::max(s.L, 4);                  // (that kernel's lanes work out residuals in fours)
-    auto rows_held = [&](int rw, int groups) { return s.CPL < 8 ? glm_narrow_rows_in_flight(s.V, s.CPL, L, rw, groups, n) : 0; };
+    // enough every workgroup adds them up itself, in one trip over the fabric per step instead of two or three.
+    s.narrow_layout = glm_narrow_layout(p);
+    auto rows_held = [&](int rw, int groups) { return p <= 1024 ? glm_narrow_rows_in_flight(s.narrow_layout, rw, groups, n) : 0; };
     if (requested_G <= 0 && p <= kNarrowOneTripMaxP) {
-        // Left to choose: one workgroup if it holds a step's rows (no exchange: with as many rows as it can hold 1.6 to 2.2 us per update
-        // at p = 4 to 63 and 1.1 to 1.5 at p = 64 to 512, against 2.2 to 2.9 on two to sixteen; the general kernel, which steps launched
+        // Left to choose: one workgroup if it holds a step's rows (no exchange: with as many rows as it can hold 1.3 to 2.3 us per update
+        // at p = 3 to 63 and 1.3 at p = 128, against 1.8 to 2.4 on four to sixteen; the general kernel, which steps launched
         // one by one keep to, has no such gain: 209 against 176 us for 16 of them at p = 16, n = 768), and not more than 32 for rows of up to
-        // 128 floats (one trip: 3.1 us at p = 128, n = 1536, 3.4 on 64 workgroups in two trips; 3.1 against 3.2 at p = 50, n = 3072; with
-        // eight rows per lane slot they gather for longer than two trips take: 4.0 against 3.5 at p = 90, n = 2304; launched step by step
+        // 128 floats (one trip: 2.4 us at p = 128, n = 1536, 2.75 on 64 workgroups and more over two levels; 2.4 against 2.6 at p = 50, n = 3000; with
+        // eight rows per lane slot they gather for longer than that takes; launched step by step
         // 312 against 576 us for 16 at p = 128, n = 3000, with 120).  More rows than those hold need more workgroups.
         const int held = rows_held(kNarrowMoreRows, 32);
         if (persistent && rows_held(kNarrowMoreRows, 1) > 0) G = 1;
@@ -695,15 +695,15 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
     }
     const bool few_sums = (int64_t)G * p <= kRedundantMaxWords;
     if (few_sums ? p <= kNarrowOneTripMaxP : G >= 8) {
-        const int rw = few_sums || s.V == 1 ? kNarrowMoreRows : 8;
         const int Gn = few_sums ? G : G & ~7;
-        const int pf = rows_held(rw, Gn);
+        int rw = few_sums || (p % 2 != 0 && p <= 256) ? kNarrowMoreRows : 8;
+        int pf = rows_held(rw, Gn);
+        if (pf == 0 && !few_sums && rw != 8) pf = rows_held(rw = 8, Gn);
         if (pf > 0 && (persistent || s.V >= 2)) G = Gn;
         if (pf > 0 && persistent) {
             s.narrow = 1;
             s.narrow_pf = pf;
             s.narrow_rw = rw;
-            s.L = L;
         }
     }
     s.G = G;
@@ -722,10 +722,10 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
         s.PF = max_pf(s.V, s.CPL); s.pipe = kPipeGroups;
     }
     s.chain_block = s.narrow ? glm_narrow_block(s.narrow_rw) : s.block;
-    if (s.CPL >= 8 && s.V == 4 && G >= 8) {
+    if (p > 1024 && G >= 8 && (persistent || s.V == 4)) {
         // wide rows on eight or more workgroups: the kernel with exchange wavefronts of its own
         s.split = 1;
-        s.split_ch = s.CPL == 8 ? 1 : 2;
+        s.split_ch = p <= 2048 ? 1 : 2;
         s.G = G & ~7;
         s.chain_block = glm_split_block();
     }
@@ -776,7 +776,7 @@ hipError_t glm_prepare(GlmLaunchShape* s)
         cap = std::min(cap, cus) & (sliced ? ~7 : ~0);
         const int G = std::min(s->G, cap) & (sliced ? ~7 : ~0);
         // fewer workgroups than planned hold fewer rows: only if the step still fits
-        if (G >= (sliced ? 8 : 1) && glm_narrow_rows_in_flight(s->V, s->CPL, s->L, s->narrow_rw, G, s->n) == s->narrow_pf) {
+        if (G >= (sliced ? 8 : 1) && glm_narrow_rows_in_flight(s->narrow_layout, s->narrow_rw, G, s->n) == s->narrow_pf) {
             s->max_G = std::min(s->max_G, cap);
             s->G = G;
         } else {

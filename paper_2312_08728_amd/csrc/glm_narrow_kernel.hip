@@ -17,10 +17,11 @@
 //     exchange wavefronts (glm_exchange.h), one per SIMD, carry them to the other workgroups and bring the new theta
 //     back.  Row wavefronts wait for theta on a flag in shared memory.
 //
-// Two forms.  Eight row wavefronts, sums added up slice by slice in two trips over the fabric per step (G a multiple of 8): where G p
+// Two forms.  Eight row wavefronts, sums added up slice by slice, over two levels or in two trips over the fabric per step (G a multiple of 8): where G p
 // is large.  Twelve row wavefronts (the workgroup's sixteen fill the unit), one trip per step, any G, p <= 512: where every workgroup
 // can add up the few sums itself; they hold fewer floats of a row each (registers), but fewer workgroups are what is wanted there.
-// Odd rows in two trips take twelve as well.
+// Odd rows of up to 256 floats in the first form take twelve as well where these hold them (2.96 us per update at p = 201, n = 1500, 2.81 at 202 with
+// eight; callers read the number of threads in the statistics).
 #include "glm_exchange.h"
 
 #include <hip/hip_ext.h>
@@ -36,7 +37,7 @@ namespace {
 // loads in flight can hold.
 constexpr bool narrow_shape_ok(int v, int cpl, int pf, int rw)
 {
-    return (v >= 2 || rw > kRowWaves) && cpl <= 4 && pf <= 8 && v * cpl * pf <= (rw > kRowWaves ? 16 : 32) && pf * (cpl + 2) <= 24;
+    return (v == 4 || (rw > kRowWaves && cpl == 1)) && cpl <= 4 && pf <= 8 && v * cpl * pf <= (rw > kRowWaves ? 16 : 32) && pf * (cpl + 2) <= 24;
 }
 
 // Wavefronts 0 .. 3 are the exchange wavefronts (the hardware deals the wavefronts of a workgroup out to the four
@@ -49,8 +50,11 @@ constexpr int narrow_block(int rw) { return 64 * (kXWaves + rw); }
 __device__ __forceinline__ float pick2(int k, float v0, float v1) { return k == 1 ? v1 : v0; }
 __device__ __forceinline__ float pick4(int k, float v0, float v1, float v2, float v3) { return (k & 2) != 0 ? pick2(k & 1, v2, v3) : pick2(k & 1, v0, v1); }
 
-// ONE: the redundant reduction, one trip over the fabric per step; else the sliced one, two trips.
-template <int V, int CPL, int PF, int RW, bool ONE, bool OPT>
+// EX: how the sums are exchanged: in one trip, with so many pairs of columns to an exchange wavefront (8, 16, 32, 64), over two levels or in two
+// trips.  (A kernel each: the code of several in one needs more scalar registers than there are, and reads them back in the middle of
+// a step.)
+constexpr int kTwoTrips = 0, kByDie = 1;
+template <int V, int CPL, int PF, int RW, int EX, bool OPT>
 __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
 {
     extern __shared__ __align__(16) float smem[];
@@ -60,6 +64,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     __shared__ unsigned s_published;                 // publications of row wavefronts, counted over all steps
     __shared__ unsigned s_xarrived[kXWaves], s_xconsumed;   // hand-over of partial sums between the exchange wavefronts
 
+    constexpr bool ONE = EX >= 8;
     constexpr int E = CPL * V;                       // floats of a row held per lane
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -68,14 +73,18 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     const int g = blockIdx.x;
     const int p = a.p;
     const int L = a.L;
+    const int width = a.width;                       // positions of a row (glm_exchange.h)
     const int stride = max((p + 15) & ~15, V * L * CPL);          // of theta and of the sums in shared memory
     lds_f32* th = (lds_f32*)smem;                    // [2][stride]: theta, by version parity
     lds_f32* sums = th + 2 * stride;                 // [RW][stride]: each row wavefront's gradient sums of a step
     lds_f32* xstate = sums + RW * stride;            // scratch of the exchange wavefronts
     const int first = a.s_begin, last = a.s_end;
 
-    // theta (version 0 in copy 0) and the sums; columns beyond p stay zero for good (rows are read at column 0 there)
-    for (int c = tid; c < (2 + RW) * stride; c += narrow_block(RW)) th[c] = c < p ? a.theta[c] : 0.f;
+    // theta (version 0 in copy 0) and the sums; positions beyond the row stay zero for good (rows are read at column 0 there)
+    for (int c = tid; c < (2 + RW) * stride; c += narrow_block(RW)) {
+        const int col = c < width ? column_of(a, c) : -1;
+        th[c] = col >= 0 && col < p ? a.theta[col] : 0.f;
+    }
     if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_sent = 0u; s_xconsumed = 0u; }
     if (tid < kXWaves) s_xarrived[tid] = 0u;
     __syncthreads();                                 // the only barrier: from here on the wavefronts meet through flags
@@ -89,9 +98,12 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
         const int rpw = 64 >> a.logL;                // rows side by side in a wavefront
         const int S_total = G * RW * rpw;    // row slots of the grid: row j of a mini-batch goes to slot j mod S_total
         const int myslot = (g * RW + rw) * rpw + slot;
-        int col[CPL];
+        int col[CPL], from[CPL];                     // positions of this lane's vectors, and where in a row they are loaded from
 #pragma unroll
-        for (int k = 0; k < CPL; ++k) col[k] = V * (lsub + L * k);
+        for (int k = 0; k < CPL; ++k) {
+            col[k] = V * (lsub + L * k);
+            from[k] = V == 4 ? vector_from(a, col[k]) : col[k] < p ? col[k] : 0;
+        }
 
         // A group: the rows of one step.  Besides the rows it carries their responses and the indices of the rows
         // that take their place at the group's next request; both are loaded right behind the rows, so they have
@@ -123,7 +135,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
             for (int q = 0; q < PF; ++q) {
                 const float* row = a.X + (size_t)S.idx_next[q] * (size_t)p;
 #pragma unroll
-                for (int k = 0; k < CPL; ++k) load_vec<V>(row + (col[k] < p ? col[k] : 0), &S.x[q][k * V]);   // beyond p: theta is 0 there
+                for (int k = 0; k < CPL; ++k) load_vec_unaligned<V>(row + from[k], &S.x[q][k * V]);
             }
 #pragma unroll
             for (int q = 0; q < PF; ++q) S.y[q] = a.y[S.idx_next[q]];
@@ -145,7 +157,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
 
         const unsigned abort_addr = (unsigned)(uintptr_t)(lds_u32*)&s_abort;
         const unsigned version_addr = (unsigned)(uintptr_t)(lds_u32*)&s_theta_version;
-        const bool gated = ONE ? G > 1 : a.by_die != 0;
+        const bool gated = ONE ? EX > 8 && G > 1 : EX == kByDie;
         const unsigned sent_addr = (unsigned)(uintptr_t)(lds_u32*)&s_sent;
         lds_f32* my_sums = sums + rw * stride;
         // Step s on the rows in S, then S is refilled.  Straight-line code with one conditional (the publication).  A
@@ -212,7 +224,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
                 if (lane < L) {
 #pragma unroll
                     for (int k = 0; k < CPL; ++k)
-                        if (col[k] < p) {
+                        if (col[k] < (V == 4 ? width : p)) {
 #pragma unroll
                             for (int v = 0; v < V; ++v) my_sums[col[k] + v] = acc[k * V + v];
                         }
@@ -247,73 +259,69 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     const ExchangeLds x{th, stride, xstate, xstate + kExchangeState * kXWaves, sums, stride, (unsigned)RW,
                         (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)&s_sent,
                         (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
-    if constexpr (ONE) {
-        // the columns dealt out as few pairs to a wavefront as hold them all
-        constexpr int most = 8 * V * CPL < 64 ? 8 * V * CPL : 64;
-        auto with_pairs = [&](auto pw) { exchange_one_trip<OPT, kXWaves, RW, decltype(pw)::value>(a, x, lane, wave); };
-        if (most >= 64 && p > 256) with_pairs(std::integral_constant<int, most < 64 ? most : 64>{});
-        else if (most >= 32 && p > 128) with_pairs(std::integral_constant<int, most < 32 ? most : 32>{});
-        else if (most >= 16 && p > 64) with_pairs(std::integral_constant<int, most < 16 ? most : 16>{});
-        else with_pairs(std::integral_constant<int, 8>{});
-    }
-    else if (a.by_die) exchange_by_die<OPT, kXWaves, RW, 1, 2>(a, x, lane, wave);   // (p <= 1024: two loads per lane collect theta ...
+    if constexpr (ONE) exchange_one_trip<OPT, kXWaves, RW, EX>(a, x, lane, wave);
+    else if constexpr (EX == kByDie) exchange_by_die<OPT, kXWaves, RW, 1, 2>(a, x, lane, wave);   // (p <= 1024: two loads per lane collect theta ...
     else exchange_wavefront<OPT, kXWaves, RW, 8, 2>(a, x, lane, wave);   // ... and eight cover the slice for up to 256 workgroups)
 }
 
 using KernelFn = void (*)(GlmArgs);
 
-template <bool OPT, int RW, bool ONE, int V, int CPL, int PF>
+template <bool OPT, int RW, int EX, int V, int CPL, int PF>
 KernelFn pick()
 {
-    if constexpr (!narrow_shape_ok(V, CPL, PF, RW) || (!ONE && (RW == kRowWaves) == (V == 1))) return nullptr;
-    else return glm_narrow_kernel<V, CPL, PF, RW, ONE, OPT>;
+    // (one trip: up to 8 EX columns, more than 4 EX of them)
+    constexpr bool fits = EX < 8 ? V == 4 : RW > kRowWaves && (EX == 64 ? V == 4 && CPL == 2 : CPL == 1 && (EX == 8 || V == 4));
+    if constexpr (!narrow_shape_ok(V, CPL, PF, RW) || !fits) return nullptr;
+    else return glm_narrow_kernel<V, CPL, PF, RW, EX, OPT>;
 }
 
-template <bool OPT, int RW, bool ONE, int V, int CPL>
+template <bool OPT, int RW, int EX, int V, int CPL>
 KernelFn pick_pf(int pf)
 {
     switch (pf) {
-    case 1: return pick<OPT, RW, ONE, V, CPL, 1>();
-    case 2: return pick<OPT, RW, ONE, V, CPL, 2>();
-    case 3: return pick<OPT, RW, ONE, V, CPL, 3>();
-    case 4: return pick<OPT, RW, ONE, V, CPL, 4>();
-    case 8: return pick<OPT, RW, ONE, V, CPL, 8>();
+    case 1: return pick<OPT, RW, EX, V, CPL, 1>();
+    case 2: return pick<OPT, RW, EX, V, CPL, 2>();
+    case 3: return pick<OPT, RW, EX, V, CPL, 3>();
+    case 4: return pick<OPT, RW, EX, V, CPL, 4>();
+    case 8: return pick<OPT, RW, EX, V, CPL, 8>();
     }
     return nullptr;
 }
 
-template <bool OPT, int RW, bool ONE, int V>
-KernelFn pick_cpl(int cpl, int pf)
+template <bool OPT, int RW, int EX>
+KernelFn pick_row(int v, int cpl, int pf)
 {
-    switch (cpl) {
-    case 1: return pick_pf<OPT, RW, ONE, V, 1>(pf);
-    case 2: return pick_pf<OPT, RW, ONE, V, 2>(pf);
-    case 4: return pick_pf<OPT, RW, ONE, V, 4>(pf);
-    }
-    return nullptr;
+    if (v == 4) return cpl == 1 ? pick_pf<OPT, RW, EX, 4, 1>(pf) : cpl == 2 ? pick_pf<OPT, RW, EX, 4, 2>(pf) : pick_pf<OPT, RW, EX, 4, 4>(pf);
+    if (v == 2) return pick_pf<OPT, RW, EX, 2, 1>(pf);
+    return pick_pf<OPT, RW, EX, 1, 1>(pf);
 }
 
-template <bool OPT, int RW, bool ONE>
-KernelFn pick_v(int v, int cpl, int pf)
+template <bool OPT, int RW>
+KernelFn pick_sliced(const GlmLaunchShape& s, int ex)
 {
-    if (v == 4) return pick_cpl<OPT, RW, ONE, 4>(cpl, pf);
-    if (v == 2) return pick_cpl<OPT, RW, ONE, 2>(cpl, pf);
-    return pick_cpl<OPT, RW, ONE, 1>(cpl, pf);
+    const NarrowLayout& l = s.narrow_layout;
+    if (ex == kByDie) return pick_row<OPT, RW, kByDie>(l.V, l.CPL, s.narrow_pf);
+    return pick_row<OPT, RW, kTwoTrips>(l.V, l.CPL, s.narrow_pf);
 }
 
 template <bool OPT>
-KernelFn narrow_kernel_opt(const GlmLaunchShape& s)
+KernelFn narrow_kernel_opt(const GlmLaunchShape& s, int ex)
 {
-    if (s.narrow_rw == kRowWaves) return s.reduce_mode == kReduceSliced ? pick_v<OPT, kRowWaves, false>(s.V, s.CPL, s.narrow_pf) : nullptr;
-    return s.reduce_mode == kReduceSliced ? pick_v<OPT, kNarrowMoreRows, false>(s.V, s.CPL, s.narrow_pf)
-                                          : pick_v<OPT, kNarrowMoreRows, true>(s.V, s.CPL, s.narrow_pf);
+    const NarrowLayout& l = s.narrow_layout;
+    if (s.reduce_mode == kReduceSliced) return s.narrow_rw == kRowWaves ? pick_sliced<OPT, kRowWaves>(s, ex) : pick_sliced<OPT, kNarrowMoreRows>(s, ex);
+    if (l.width > 256) return pick_row<OPT, kNarrowMoreRows, 64>(l.V, l.CPL, s.narrow_pf);
+    if (l.width > 128) return pick_row<OPT, kNarrowMoreRows, 32>(l.V, l.CPL, s.narrow_pf);
+    if (l.width > 64) return pick_row<OPT, kNarrowMoreRows, 16>(l.V, l.CPL, s.narrow_pf);
+    return pick_row<OPT, kNarrowMoreRows, 8>(l.V, l.CPL, s.narrow_pf);
 }
 
-KernelFn narrow_kernel(const GlmLaunchShape& s) { return s.with_optimizer ? narrow_kernel_opt<true>(s) : narrow_kernel_opt<false>(s); }
+// ex: of the sliced reduction, which of its exchanges
+KernelFn narrow_kernel(const GlmLaunchShape& s, int ex) { return s.with_optimizer ? narrow_kernel_opt<true>(s, ex) : narrow_kernel_opt<false>(s, ex); }
+int sliced_exchange(const GlmLaunchShape& s) { return glm_by_die(s.p, s.G, kXWaves) ? kByDie : kTwoTrips; }
 
 size_t narrow_lds_bytes(const GlmLaunchShape& s, int p)
 {
-    const int stride = std::max((p + 15) & ~15, s.V * s.L * s.CPL);
+    const int stride = std::max((p + 15) & ~15, s.narrow_layout.V * s.narrow_layout.L * s.narrow_layout.CPL);
     return (size_t)((2 + s.narrow_rw) * stride + (kExchangeState + kExchangeRed) * kXWaves + 16) * sizeof(float);
 }
 
@@ -321,21 +329,39 @@ size_t narrow_lds_bytes(const GlmLaunchShape& s, int p)
 
 int glm_narrow_block(int rw) { return narrow_block(rw); }
 
-int glm_narrow_rows_in_flight(int v, int cpl, int L, int rw, int G, int64_t n)
+NarrowLayout glm_narrow_layout(int64_t p)
 {
-    const int64_t slots = (int64_t)G * rw * (64 / L);
+    NarrowLayout l;
+    // Vectors of four (of what shorter rows are a multiple of where four would leave most lanes idle)
+    l.V = p >= 8 || p % 4 == 0 ? 4 : p % 2 == 0 ? 2 : 1;
+    const int64_t vectors = (p + l.V - 1) / l.V;
+    l.L = 4;                                         // (the kernel's lanes work out residuals in fours)
+    while (l.L < vectors && l.L < 64) l.L *= 2;
+    l.CPL = 1;
+    while (l.CPL * 64 < vectors) l.CPL *= 2;
+    l.width = (int)(l.V == 1 ? (p + 1) / 2 * 2 : vectors * l.V);
+    return l;
+}
+
+int glm_narrow_rows_in_flight(const NarrowLayout& l, int rw, int G, int64_t n)
+{
+    const int64_t slots = (int64_t)G * rw * (64 / l.L);
     const int64_t need = (n + slots - 1) / slots;
     const int pf = need <= 4 ? (int)need : need <= 8 ? 8 : 16;
-    return narrow_shape_ok(v, cpl, pf, rw) ? pf : 0;
+    return narrow_shape_ok(l.V, l.CPL, pf, rw) ? pf : 0;
 }
 
 hipError_t glm_narrow_prepare(const GlmLaunchShape& s, int p, int* max_groups)
 {
-    KernelFn fn = narrow_kernel(s);
-    if (!fn) return hipErrorInvalidValue;
     const size_t lds = narrow_lds_bytes(s, p);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
+    KernelFn fn = nullptr;
+    for (const int ex : {kTwoTrips, kByDie}) {   // (fewer workgroups than planned may take the other)
+        fn = narrow_kernel(s, ex);
+        if (!fn) return hipErrorInvalidValue;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipError_t e = hipSuccess;
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), narrow_block(s.narrow_rw), lds);
     if (e != hipSuccess) return e;
@@ -348,19 +374,24 @@ hipError_t glm_narrow_prepare(const GlmLaunchShape& s, int p, int* max_groups)
 
 hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipStream_t stream, hipEvent_t stop)
 {
-    KernelFn fn = narrow_kernel(s);
-    const int64_t slots = (int64_t)s.G * s.narrow_rw * (64 / s.L);
+    KernelFn fn = narrow_kernel(s, sliced_exchange(s));
+    const NarrowLayout& l = s.narrow_layout;
+    const int64_t slots = (int64_t)s.G * s.narrow_rw * (64 / l.L);
     const bool one_trip = s.reduce_mode == kReduceRedundant;
-    // what the kernel assumes: whole vector chunks, every row of a step in a register slot; two trips: slices of whole groups of
+    // what the kernel assumes: a row in the lanes' vectors, every row of a step in a register slot; two trips: slices of whole groups of
     // eight workgroups; one trip: columns that the exchange wavefronts hold as pairs
-    if (!fn || args.s_begin >= args.s_end || args.p % s.V != 0 || args.reduce_mode != s.reduce_mode ||
-        args.p > s.V * s.L * s.CPL || args.L != s.L || (1 << args.logL) != s.L || (int64_t)args.n > slots * s.narrow_pf)
+    if (!fn || args.s_begin >= args.s_end || args.reduce_mode != s.reduce_mode || args.p != s.p ||
+        l.width > l.V * l.L * l.CPL + (l.V == 1) || (int64_t)args.n > slots * s.narrow_pf)
         return hipErrorInvalidValue;
     if (one_trip ? s.narrow_rw == kRowWaves || args.p > kNarrowOneTripMaxP || s.G < 1
-                 : s.G < 8 || s.G % 8 != 0 || (s.narrow_rw != kRowWaves && s.V != 1))
+                 : s.G < 8 || s.G % 8 != 0 || l.V != 4)
         return hipErrorInvalidValue;
     GlmArgs a = args;
-    a.by_die = !one_trip && glm_by_die(args.p, s.G, kXWaves);
+    a.L = l.L;
+    a.logL = 0;
+    while ((1 << a.logL) < a.L) ++a.logL;
+    a.width = l.width;
+    a.shift = l.V == 4 ? l.width - args.p : 0;
     hipExtLaunchKernelGGL(fn, dim3(s.G), dim3(narrow_block(s.narrow_rw)), (uint32_t)narrow_lds_bytes(s, args.p), stream, nullptr, stop, 0u, a);
     return hipGetLastError();
 }

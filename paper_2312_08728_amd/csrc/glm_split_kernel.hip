@@ -89,8 +89,11 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     lds_f32* sums = xstate + (kExchangeState + kExchangeRed) * NX;   // [P_PAD]: the workgroup's gradient sums of a step, on their way out
     const int first = a.s_begin, last = a.s_end;
 
-    // both copies of theta: columns beyond p stay zero for good (rows are read at column 0 there)
-    for (int c = tid; c < 2 * P_PAD; c += kSplitBlock) th[c] = c < p ? a.theta[c] : 0.f;
+    // theta (version 0 in copy 0): positions (glm_exchange.h) beyond the row stay zero for good (rows are read at column 0 there)
+    for (int c = tid; c < 2 * P_PAD; c += kSplitBlock) {
+        const int col = c < a.width ? column_of(a, c) : -1;
+        th[c] = col >= 0 ? a.theta[col] : 0.f;
+    }
     if (tid < 2 * kRowWaves) pd_seq[tid] = 0u;
     if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_sent = 0u; s_xconsumed = 0u; }
     if (tid < NX) s_xarrived[tid] = 0u;
@@ -110,7 +113,10 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
             const int mine = g < nb ? (nb - g + G - 1) / G : 0;
             return max(1, (mine + GR - 1) / GR);
         };
-        const int col0 = rw * WCOLS + 4 * lane;    // first column of this lane's chunk 0; chunk ch starts 256 ch further
+        const int col0 = rw * WCOLS + 4 * lane;    // first position of this lane's chunk 0; chunk ch starts 256 ch further
+        int from[CH];                                // where in a row they are loaded from
+#pragma unroll
+        for (int ch = 0; ch < CH; ++ch) from[ch] = vector_from(a, col0 + 256 * ch);
 
         // A slot of the ring: one group of rows.  Besides the rows it carries, in lanes r < GR, the response of row r
         // and the index of the row that takes its place at the slot's next request.  Both are loaded right behind
@@ -151,10 +157,7 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
                 const int idx = __builtin_amdgcn_readlane(idxv, r);
                 const float* row = a.X + (size_t)idx * (size_t)p;
 #pragma unroll
-                for (int ch = 0; ch < CH; ++ch) {
-                    const int c = col0 + 256 * ch;
-                    S.x[r][ch] = *reinterpret_cast<const float4*>(row + (c < p ? c : 0));   // beyond p: theta is 0 there
-                }
+                for (int ch = 0; ch < CH; ++ch) load_vec_unaligned<4>(row + from[ch], &S.x[r][ch].x);
             }
             S.y = a.y[idxv];
             S.ok = S.ok_next;
@@ -293,12 +296,14 @@ hipError_t glm_split_prepare(int ch, bool opt, int* max_groups)
 
 hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream, hipEvent_t stop)
 {
-    if (G < 8 || G % 8 != 0 || args.s_begin >= args.s_end || args.p % 4 != 0 || args.p > kRowWaves * 256 * ch)
+    if (G < 8 || G % 8 != 0 || args.s_begin >= args.s_end || args.p < 4 || args.p > kRowWaves * 256 * ch)
         return hipErrorInvalidValue;
     // Three short trips instead of two where a wavefront has two lines at most and a step few rows, so that little stands in the queues that
     // the trips share with them.  us per update, two trips / three: 6.1 / 5.7 at p = 1028, n = 1500, 8.1 / 8.0 at 1500, 3000, 7.89 / 7.84 at 2048, 2048
     // (256 workgroups), but 16.9 / 17.6 at 2048, 8192; 9.23 / 9.33 at 2500, 1500 and 12.3 / 13.0 at 4096, 2048 with three lines at a time.
     GlmArgs a = args;
+    a.width = (args.p + 3) / 4 * 4;
+    a.shift = a.width - args.p;
     a.by_die = ch == 1 && glm_by_die(args.p, G, 2 * NX) && args.n <= 12 * G;
     hipExtLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, a);
     return hipGetLastError();

@@ -202,3 +202,44 @@ def test_sums_added_up_on_the_dies_first(model, p, n, G, N0, optimizer):
     assert rel_l2(got, ref.theta) <= TOL
     again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
     assert np.array_equal(got, again)
+
+
+# (model, p, n, G, N0): rows whose length is no multiple of four floats, taken as vectors of four of which the last starts four columns before
+# the row's end and repeats one to three columns.
+ANY_LENGTH = [
+    (wl.LOGISTIC, 9, 300, 2, 700),        # three vectors, the last repeats three columns; one trip
+    (wl.LINEAR, 10, 900, 5, 2_000),       # two
+    (wl.LOGISTIC, 11, 700, 3, 2_000),     # one
+    (wl.LINEAR, 61, 500, 12, 1_500),      # the last line of 16 holds one vector of which one column counts
+    (wl.LOGISTIC, 129, 300, 8, 900),      # 33 vectors: a lane's second half is empty
+    (wl.LINEAR, 257, 200, 8, 600),        # 65 vectors: the second of a lane but one
+    (wl.LOGISTIC, 511, 150, 8, 700),      # the widest odd rows of one trip
+    (wl.LINEAR, 62, 6000, 128, 14_000),   # sums over two levels
+    (wl.LOGISTIC, 302, 1000, 96, 3_000),
+    (wl.LINEAR, 513, 700, 80, 2_000),     # four vectors a lane, three of them empty but for one lane
+    (wl.LOGISTIC, 1023, 500, 128, 1_500),
+    (wl.LINEAR, 1022, 100, 16, 400),      # two trips
+    (wl.LOGISTIC, 1026, 300, 64, 900),    # rows split over the wavefronts: in two trips
+    (wl.LINEAR, 1030, 500, 96, 1_500),    # and over two levels
+    (wl.LOGISTIC, 2046, 600, 256, 1_500),
+]
+
+
+@pytest.mark.parametrize("optimizer", [0, 1, 3])
+@pytest.mark.parametrize("model,p,n,G,N0", ANY_LENGTH)
+def test_rows_of_any_length(model, p, n, G, N0, optimizer):
+    """Two buffers of five passes (two launches each): theta and state carry over by position."""
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    w = _case(model, 2 * N0 - 77, p, N0, n, T=5, R=1, alpha=0.01 if optimizer == 3 else 0.05 if model == wl.LOGISTIC else 0.2 / (p + 10))
+    X, y = wl.dataset(w)
+    ref = O.BMGD(w.model, w.p, w.n, w.alpha, w.T)
+    if optimizer:
+        ref.set_optimizer(optimizer)
+    for k in range(2):
+        ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
+    got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
+    assert st.threads_per_group == (704 if p > 1024 else 1024 if G * p <= 4096 else NARROW_THREADS) and st.n_workgroups == G
+    assert rel_l2(got, ref.theta) <= TOL and coord_err(got, ref.theta) <= 10 * TOL
+    again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
+    assert np.array_equal(got, again)
