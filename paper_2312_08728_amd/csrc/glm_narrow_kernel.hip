@@ -37,7 +37,7 @@ namespace {
 // loads in flight can hold.
 constexpr bool narrow_shape_ok(int v, int cpl, int pf, int rw)
 {
-    return (v == 4 || (rw > kRowWaves && cpl == 1)) && cpl <= 4 && pf <= 8 && v * cpl * pf <= (rw > kRowWaves ? 16 : 32) && pf * (cpl + 2) <= 24;
+    return (v == 4 || (rw > kRowWaves && cpl == 1)) && cpl <= 4 && pf <= 8 && v * cpl * pf <= (rw > kRowWaves ? 24 : 32) && pf * (cpl + 2) <= 24;
 }
 
 // Wavefronts 0 .. 3 are the exchange wavefronts (the hardware deals the wavefronts of a workgroup out to the four

@@ -213,7 +213,7 @@ ANY_LENGTH = [
     (wl.LINEAR, 61, 500, 12, 1_500),      # the last line of 16 holds one vector of which one column counts
     (wl.LOGISTIC, 129, 300, 8, 900),      # 33 vectors: a lane's second half is empty
     (wl.LINEAR, 257, 200, 8, 600),        # 65 vectors: the second of a lane but one
-    (wl.LOGISTIC, 511, 150, 8, 700),      # the widest odd rows of one trip
+    (wl.LOGISTIC, 511, 250, 8, 700),      # the widest odd rows of one trip, three rows a lane
     (wl.LINEAR, 62, 6000, 128, 14_000),   # sums over two levels
     (wl.LOGISTIC, 302, 1000, 96, 3_000),
     (wl.LINEAR, 513, 700, 80, 2_000),     # four vectors a lane, three of them empty but for one lane
@@ -243,3 +243,15 @@ def test_rows_of_any_length(model, p, n, G, N0, optimizer):
     assert rel_l2(got, ref.theta) <= TOL and coord_err(got, ref.theta) <= 10 * TOL
     again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
     assert np.array_equal(got, again)
+
+
+@pytest.mark.parametrize("p,n,G,threads", [(200, 192, 8, 1024), (200, 193, 16, 1024), (256, 768, 16, 1024), (256, 769, 64, NARROW_THREADS),
+                                           (400, 96, 4, 1024), (401, 97, 8, 1024), (512, 288, 8, 1024), (300, 289, 24, NARROW_THREADS)])
+def test_workgroups_chosen_for_rows_of_129_to_512_floats(p, n, G, threads):
+    """As few as let every workgroup add up all sums, where they hold the rows."""
+    import paper_2312_08728_amd as B
+    w = _case(wl.LOGISTIC, 4 * n, p, 2 * n + 5, n, T=2, R=1, alpha=0.05)
+    X, y = wl.dataset(w)
+    got, st = gpu_run(w, X, y, chain=B.BMGD_CHAIN_PERSISTENT)
+    assert (st.n_workgroups, st.threads_per_group) == (G, threads)
+    assert rel_l2(got, oracle_run(w, X, y)) <= TOL
