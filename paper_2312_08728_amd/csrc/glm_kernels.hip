@@ -689,14 +689,15 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
         // 128 floats (one trip: 2.4 us at p = 128, n = 1536, 2.75 on 64 workgroups and more over two levels; 2.4 against 2.6 at p = 50, n = 3000; with
         // eight rows per lane slot they gather for longer than that takes; launched step by step
         // 312 against 576 us for 16 at p = 128, n = 3000, with 120).  More rows than those hold need more workgroups.
-        // Rows of 129 to 512 floats: as many workgroups as the lanes of an exchange wavefront ask for in one go, or half of them where a lane slot
-        // then has two rows at most: 2.0 us on 8 against 2.9 on the 12 that have 12 KB each at p = 200, n = 180, 2.3 on 16 against 3.2 on 24 at n = 370,
+        // Rows of 65 to 512 floats: no more workgroups than a wavefront's lanes ask for four or eight of each in one go, where these hold the rows
+        // (2.1 us on 16 against 2.4 on the 20 that have 12 KB each at p = 100, n = 600, 2.2 against 2.4 on 26 and 32 at n = 777 and 1024); beyond 128 floats
+        // half of them where a lane slot then has two rows at most: 2.0 us on 8 against 2.9 on the 12 that have 12 KB each at p = 200, n = 180, 2.3 on 16 against 3.2 on 24 at n = 370,
         // 2.7 against 3.3 on 48 at n = 760; 2.0 on 4 against 3.3 on 8 at p = 400, n = 90, 2.3 on 8 against 3.2 on 24 at n = 190, 2.5 against 3.2 on 32 at n = 250.
         const int held = rows_held(kNarrowMoreRows, 32);
-        const int few = p <= 256 ? 16 : 8;           // workgroups whose words an exchange wavefront's lanes ask for in one go
+        const int few = p <= 256 ? 16 : 8;
         if (persistent && rows_held(kNarrowMoreRows, 1) > 0) G = 1;
-        else if (persistent && p > 128 && G > few / 2 && rows_held(kNarrowMoreRows, few) > 0)
-            G = rows_held(kNarrowMoreRows, few / 2) > 0 && rows_held(kNarrowMoreRows, few / 2) <= 2 ? few / 2 : few;
+        else if (persistent && p > 64 && G > (p > 128 ? few / 2 : few) && rows_held(kNarrowMoreRows, few) > 0)
+            G = p > 128 && rows_held(kNarrowMoreRows, few / 2) > 0 && rows_held(kNarrowMoreRows, few / 2) <= 2 ? few / 2 : few;
         else if (G > 32 && 32 * p <= kRedundantMaxWords && held > 0 && held <= 4) G = 32;
     }
     const bool few_sums = (int64_t)G * p <= kRedundantMaxWords;

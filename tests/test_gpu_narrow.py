@@ -245,9 +245,9 @@ def test_rows_of_any_length(model, p, n, G, N0, optimizer):
     assert np.array_equal(got, again)
 
 
-@pytest.mark.parametrize("p,n,G,threads", [(200, 192, 8, 1024), (200, 193, 16, 1024), (256, 768, 16, 1024), (256, 769, 64, NARROW_THREADS),
+@pytest.mark.parametrize("p,n,G,threads", [(65, 1152, 16, 1024), (128, 1536, 16, 1024), (128, 1537, 32, 1024), (64, 1200, 25, 1024), (200, 192, 8, 1024), (200, 193, 16, 1024), (256, 768, 16, 1024), (256, 769, 64, NARROW_THREADS),
                                            (400, 96, 4, 1024), (401, 97, 8, 1024), (512, 288, 8, 1024), (300, 289, 24, NARROW_THREADS)])
-def test_workgroups_chosen_for_rows_of_129_to_512_floats(p, n, G, threads):
+def test_workgroups_chosen_for_rows_of_65_to_512_floats(p, n, G, threads):
     """As few as let every workgroup add up all sums, where they hold the rows."""
     import paper_2312_08728_amd as B
     w = _case(wl.LOGISTIC, 4 * n, p, 2 * n + 5, n, T=2, R=1, alpha=0.05)
