@@ -21,9 +21,6 @@ namespace {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-constexpr int kPairThreads = 256;
-constexpr int kMaxTilesPerWave = 3;                  // Q <= 144: nine tile columns over four wavefronts
-
 struct FirstLevel {                                  // where the steps' moment matrices are, and their learning rates
     const float* dense;                              // per mini-batch [Sxx | -Sxy], dense of order Q (gram_launch_moments, dense)
     int p;
@@ -34,33 +31,33 @@ struct FirstLevel {                                  // where the steps' moment 
 };
 
 constexpr int kMaxOrder = (kGramMaxP + 1 + 15) / 16 * 16;                       // 144
-constexpr int kMaxRightVec = (kMaxOrder * kMaxOrder / 4 + kPairThreads - 1) / kPairThreads;   // float4 of the right factor per thread
-constexpr int kTileRows = 2;                          // 16-row tile rows of a product per workgroup (the right factor is staged once for both)
-constexpr int kMaxLeftVec = (16 * kTileRows * kMaxOrder / 4 + kPairThreads - 1) / kPairThreads;   // of the left factor's rows
+constexpr int pair_waves(int nt) { return (nt + 1) / 2; }                      // of a workgroup: half of a product's tile rows
+constexpr size_t pair_lds(int nt) { return sizeof(float) * (size_t)(16 * nt) * (16 * nt + 4); }
 
 // out[j] = in[2 j + 1] * in[2 j] (the later step on the left); a missing in[2 j + 1] counts as the identity.  Dense
-// Q x Q matrices, row-major, Q a multiple of 16.  Workgroup (x, y) computes the tile rows 2 x and 2 x + 1 of out[y]: it stages
-// their 32 rows of the left factor and the whole right factor in shared memory and each wavefront takes every fourth 16 x 16
-// tile of both rows.  Everything a thread stages is requested first and stored afterwards (unconditional loads from clamped
-// addresses), so the staging costs one trip to memory, not one per element; row and column of a float4 come from a
-// multiplication (qv_inv = 2^20 / (Q / 4) + 1: exact for the 5184 float4 of the largest matrix).  MFMA operand layout
-// (v_mfma_f32_16x16x4_f32): a = A[lane % 16][lane / 16], b = B[lane / 16][lane % 16], c[v] = C[4 (lane / 16) + v][lane % 16].
+// Q x Q matrices, row-major, Q = 16 NT.  Two workgroups a product, a wavefront to each 16-row tile row of it: the right factor stands in
+// shared memory, where every wavefront reads it; a wavefront's rows of the left factor go straight from memory to the operands of
+// its matrix instructions, 16 bytes a lane.  For that the sum over k takes in step q of a block of 16 the k = 4 (lane / 16) + q, in both
+// operands.  MFMA operand layout (v_mfma_f32_16x16x4_f32): a = A[lane % 16][lane / 16], b = B[lane / 16][lane % 16],
+// c[v] = C[4 (lane / 16) + v][lane % 16].  Row stride Q + 4 of the right factor: rows four apart are 16 banks apart, so the 32 lanes that
+// are served together meet no bank twice.
+// What bounds it is a trip to memory for what the kernel before wrote, 50 KB a unit and product at Q = 112, and 28 matrix instructions for each of
+// the 49 tiles (2.8 us for a wavefront's seven).  150 products of order 112: PLACEHOLDER (four workgroups a product that stage 32 rows
+// of the left factor as well, with the loads of the largest order whatever the order was: 600 workgroups in two rounds).
 // FIRST: the factors are the steps themselves, A_s = [[I - alpha_s Sxx_s, alpha_s Sxy_s], [0, 1]] padded with zeros:
 // entry (r, c) is (r == c and r <= p) - alpha_s D_s(r, c) with D_s the dense matrix the moments kernel wrote.
 // CHAIN_OUT: the product P goes out as [I - P | last column of P] in the layout the chain kernel reads (GramLayout), so
 // that the chain's step theta - 1 * ((I - P) theta - d) applies it.
-template <bool FIRST, bool CHAIN_OUT = false>
-__global__ void __launch_bounds__(kPairThreads) affine_pair_kernel(FirstLevel f, const float* __restrict__ in, float* __restrict__ out,
-                                                                   int count_in, int Q, int rs, unsigned qv_inv, GramLayout L)
+template <int NT, bool FIRST, bool CHAIN_OUT>
+__global__ void __launch_bounds__(64 * pair_waves(NT)) affine_pair_kernel(FirstLevel f, const float* __restrict__ in, float* __restrict__ out,
+                                                                         int count_in, GramLayout L)
 {
-    extern __shared__ __align__(16) float lds[];
-    const int ls = Q + 4;                            // row stride of the left factor's rows: float4 stores stay aligned, and a
-    float* Ls = lds;                                 // column read (16 rows, one k) meets each bank at most twice
-    float* Rs = lds + 16 * kTileRows * ls;           // right factor, row stride rs = 16 (mod 32): four rows of 16 columns apart
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int NT = Q / 16, QV = Q / 4;
-    const int tr = kTileRows * blockIdx.x, j = blockIdx.y;   // first tile row of this workgroup
-    const int nrows = 16 * min(kTileRows, NT - tr);  // rows of the left factor it needs
+    extern __shared__ __align__(16) float Rs[];      // right factor
+    constexpr int Q = 16 * NT, QV = Q / 4, rs = Q + 4, threads = 64 * pair_waves(NT);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int j = blockIdx.y;
+    const int tr = pair_waves(NT) * blockIdx.x + wave;           // this wavefront's tile row (NT, where it has none)
     const int right = 2 * j, left = 2 * j + 1;
     const bool has_left = left < count_in;
     const int lc = has_left ? left : right;          // (clamped: not used when the left factor is the identity)
@@ -70,21 +67,20 @@ __global__ void __launch_bounds__(kPairThreads) affine_pair_kernel(FirstLevel f,
     float a_r = 0.f, a_l = 0.f;
     if constexpr (FIRST) {
         Rm = f.dense + (size_t)(right % f.period) * Q * Q;
-        Lm = f.dense + (size_t)(lc % f.period) * Q * Q + (size_t)16 * tr * Q;
+        Lm = f.dense + (size_t)(lc % f.period) * Q * Q;
         a_r = f.lr_tab ? f.lr_tab[min(f.lr_base + right, f.lr_len - 1)] : f.alpha;
         a_l = f.lr_tab ? f.lr_tab[min(f.lr_base + lc, f.lr_len - 1)] : f.alpha;
     } else {
         Rm = in + (size_t)right * Q * Q;
-        Lm = in + (size_t)lc * Q * Q + (size_t)16 * tr * Q;        // its 16 rows are contiguous
+        Lm = in + (size_t)lc * Q * Q;
     }
-    const int nR = Q * QV, nL = nrows * QV;
-    float4 rv[kMaxRightVec], lv[kMaxLeftVec];
+    constexpr int nR = Q * QV, kRight = (nR + threads - 1) / threads;
+    float4 rv[kRight], lv[NT];
+    const int lrow = 16 * min(tr, NT - 1) + l16;
 #pragma unroll
-    for (int i = 0; i < kMaxRightVec; ++i)
-        rv[i] = *reinterpret_cast<const float4*>(Rm + (size_t)4 * min(tid + kPairThreads * i, nR - 1));
+    for (int i = 0; i < kRight; ++i) rv[i] = *reinterpret_cast<const float4*>(Rm + 4 * min(tid + threads * i, nR - 1));
 #pragma unroll
-    for (int i = 0; i < kMaxLeftVec; ++i)
-        lv[i] = *reinterpret_cast<const float4*>(Lm + (size_t)4 * min(tid + kPairThreads * i, nL - 1));
+    for (int i = 0; i < NT; ++i) lv[i] = *reinterpret_cast<const float4*>(Lm + (size_t)lrow * Q + 16 * i + 4 * lq);
     // entry (r, c .. c + 3) of a factor from what was loaded for it
     auto entry = [&](float4 v, float alpha, int r, int c) {
         if constexpr (FIRST) {
@@ -97,74 +93,92 @@ __global__ void __launch_bounds__(kPairThreads) affine_pair_kernel(FirstLevel f,
         return v;
     };
 #pragma unroll
-    for (int i = 0; i < kMaxRightVec; ++i) {
-        const int e = tid + kPairThreads * i;
+    for (int i = 0; i < kRight; ++i) {
+        const int e = tid + threads * i;
         if (e < nR) {
-            const int r = (int)(((unsigned)e * qv_inv) >> 20), c = 4 * (e - r * QV);
-            const float4 v = entry(rv[i], a_r, r, c);
-            *reinterpret_cast<float4*>(Rs + r * rs + c) = v;
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < kMaxLeftVec; ++i) {
-        const int e = tid + kPairThreads * i;
-        if (e < nL) {
-            const int ii = (int)(((unsigned)e * qv_inv) >> 20), c = 4 * (e - ii * QV), r = 16 * tr + ii;
-            float4 v = entry(lv[i], a_l, r, c);
-            if (!has_left) v = make_float4(r == c ? 1.f : 0.f, r == c + 1 ? 1.f : 0.f, r == c + 2 ? 1.f : 0.f, r == c + 3 ? 1.f : 0.f);
-            *reinterpret_cast<float4*>(Ls + ii * ls + c) = v;
+            const int r = e / QV, c = 4 * (e - r * QV);
+            float4 v = entry(rv[i], a_r, r, c);
+            float* to = Rs + r * rs + c;
+            if constexpr (FIRST) {
+                // A step but for its last row and column is symmetric.  What stands here is its transpose: row p holds column p, and
+                // column p row p (zeros and a one).
+                const int e4 = f.p - c;              // column p is the e4-th of these four
+                if (r == f.p) {
+                    if (e4 <= 0) to[0] = v.x;
+                    if (e4 <= 1) to[1] = v.y;
+                    if (e4 <= 2) to[2] = v.z;
+                    if (e4 <= 3) to[3] = v.w;
+                    continue;
+                }
+                if (r < f.p && (unsigned)e4 < 4u) {
+                    Rs[f.p * rs + r] = e4 == 0 ? v.x : e4 == 1 ? v.y : e4 == 2 ? v.z : v.w;
+                    if (e4 == 0) v.x = 0.f;
+                    if (e4 == 1) v.y = 0.f;
+                    if (e4 == 2) v.z = 0.f;
+                    if (e4 == 3) v.w = 0.f;
+                }
+            }
+            *reinterpret_cast<float4*>(to) = v;
         }
     }
     __syncthreads();
+    if (tr >= NT) return;
 
-    floatx4 acc[kTileRows][kMaxTilesPerWave];
+    floatx4 acc[NT];
 #pragma unroll
-    for (int h = 0; h < kTileRows; ++h)
+    for (int t = 0; t < NT; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const float* bp = FIRST ? Rs + l16 * rs + 4 * lq : Rs + 4 * lq * rs + l16;
 #pragma unroll
-        for (int t = 0; t < kMaxTilesPerWave; ++t) acc[h][t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const float* ap = Ls + (lane & 15) * ls + (lane >> 4);
-    const float* bp = Rs + (lane >> 4) * rs + (lane & 15);
-    const bool two = nrows > 16;                     // (the same for the whole workgroup)
-    // (Q is a multiple of 16: four K steps per trip, their operand reads issued together)
-    for (int k0 = 0; k0 < Q; k0 += 16) {
-        float a[4][kTileRows], b[4][kMaxTilesPerWave];
+    for (int i = 0; i < NT; ++i) {
+        const int c = 16 * i + 4 * lq;
+        const float4 v = has_left ? entry(lv[i], a_l, lrow, c)
+                                  : make_float4(lrow == c ? 1.f : 0.f, lrow == c + 1 ? 1.f : 0.f, lrow == c + 2 ? 1.f : 0.f, lrow == c + 3 ? 1.f : 0.f);
+        const float a[4] = {v.x, v.y, v.z, v.w};
+        float4 b[NT];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-#pragma unroll
-            for (int h = 0; h < kTileRows; ++h) a[q][h] = ap[(two ? 16 * h : 0) * ls + k0 + 4 * q];
-#pragma unroll
-            for (int t = 0; t < kMaxTilesPerWave; ++t) b[q][t] = bp[(k0 + 4 * q) * rs + 16 * min(wave + 4 * t, NT - 1)];
+        for (int t = 0; t < NT; ++t) {
+            if constexpr (FIRST) b[t] = *reinterpret_cast<const float4*>(bp + 16 * t * rs + 16 * i);
+            else b[t] = make_float4(bp[16 * i * rs + 16 * t], bp[(16 * i + 1) * rs + 16 * t], bp[(16 * i + 2) * rs + 16 * t], bp[(16 * i + 3) * rs + 16 * t]);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int t = 0; t < kMaxTilesPerWave; ++t)
-                if (wave + 4 * t < NT) {             // (the same for the whole wavefront)
-                    acc[0][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][0], b[q][t], acc[0][t], 0, 0, 0);
-                    if (two) acc[1][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q][1], b[q][t], acc[1][t], 0, 0, 0);
-                }
+            for (int t = 0; t < NT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(q == 0 ? b[t].x : q == 1 ? b[t].y : q == 2 ? b[t].z : b[t].w, a[q], acc[t], 0, 0, 0);
     }
+    // lane: row r, columns 16 t + 4 lq .. + 3
     float* o = out + (size_t)j * (CHAIN_OUT ? (size_t)L.step_floats : (size_t)Q * Q);
+    const int r = 16 * tr + l16;
 #pragma unroll
-    for (int h = 0; h < kTileRows; ++h) {
-        if (16 * h >= nrows) break;
+    for (int t = 0; t < NT; ++t) {
+        const int c = 16 * t + 4 * lq;
+        if constexpr (CHAIN_OUT) {
+            if (r >= L.p) continue;
+            float v[4];
 #pragma unroll
-        for (int t = 0; t < kMaxTilesPerWave; ++t) {
-            const int tc = wave + 4 * t;
-            if (tc < NT) {
+            for (int i = 0; i < 4; ++i) v[i] = c + i == L.p ? acc[t][i] : (r == c + i ? 1.f : 0.f) - acc[t][i];
+            if (c + 3 < 4 * L.tpr * L.kq) {          // whole vectors of the chain's layout
+                *reinterpret_cast<float4*>(o + gram_pos(L, r, c)) = make_float4(v[0], v[1], v[2], v[3]);
+            } else {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int r = 16 * (tr + h) + 4 * (lane >> 4) + v, c = 16 * tc + (lane & 15);
-                    if constexpr (CHAIN_OUT) {
-                        if (r < L.p && c < L.p) o[gram_pos(L, r, c)] = (r == c ? 1.f : 0.f) - acc[h][t][v];
-                        else if (r < L.p && c == L.p) o[L.b_off + r] = acc[h][t][v];
-                    } else {
-                        o[(size_t)r * Q + c] = acc[h][t][v];
-                    }
-                }
+                for (int i = 0; i < 4; ++i)
+                    if (c + i <= L.p) o[c + i == L.p ? L.b_off + r : gram_pos(L, r, c + i)] = v[i];
             }
+        } else {
+            *reinterpret_cast<float4*>(o + (size_t)r * Q + c) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
         }
     }
+}
+
+typedef void (*PairKernel)(FirstLevel, const float*, float*, int, GramLayout);
+template <bool FIRST, bool CHAIN_OUT>
+PairKernel pair_kernel(int nt)
+{
+    static const PairKernel table[] = {affine_pair_kernel<1, FIRST, CHAIN_OUT>, affine_pair_kernel<2, FIRST, CHAIN_OUT>, affine_pair_kernel<3, FIRST, CHAIN_OUT>,
+                                       affine_pair_kernel<4, FIRST, CHAIN_OUT>, affine_pair_kernel<5, FIRST, CHAIN_OUT>, affine_pair_kernel<6, FIRST, CHAIN_OUT>,
+                                       affine_pair_kernel<7, FIRST, CHAIN_OUT>, affine_pair_kernel<8, FIRST, CHAIN_OUT>, affine_pair_kernel<9, FIRST, CHAIN_OUT>};
+    static_assert(sizeof(table) / sizeof(table[0]) * 16 == kMaxOrder, "a kernel for every order");
+    return table[nt - 1];
 }
 
 // theta <- P[0 .. p) [theta; 1]: one workgroup; wavefront w takes rows w, w + 4, ..., its lanes the columns (all of a
@@ -218,11 +232,19 @@ namespace {
 
 // what every launch of the pair kernel needs
 struct PairSetup {
-    int N, Q, NT, rs;
-    size_t lds;
-    unsigned qv_inv;
+    int N, Q, NT;
     FirstLevel f;
 };
+
+template <bool FIRST, bool CHAIN_OUT>
+hipError_t launch_pair_round(const PairSetup& s, const float* in, float* out, int count, int p, hipStream_t stream, hipEvent_t start, hipEvent_t stop)
+{
+    const dim3 grid(s.NT > 1 ? 2 : 1, (unsigned)((count + 1) / 2)), block(64 * pair_waves(s.NT));
+    const PairKernel k = pair_kernel<FIRST, CHAIN_OUT>(s.NT);
+    if (start || stop) hipExtLaunchKernelGGL(k, grid, block, (uint32_t)pair_lds(s.NT), stream, start, stop, 0u, s.f, in, out, count, make_layout(p));
+    else hipLaunchKernelGGL(k, grid, block, pair_lds(s.NT), stream, s.f, in, out, count, make_layout(p));
+    return hipGetLastError();
+}
 
 hipError_t pair_setup(const float* gram, int rows, int p, int n, int npass, int perm_stride, float alpha, const float* lr_tab,
                       int lr_base, int lr_len, PairSetup* out)
@@ -233,10 +255,7 @@ hipError_t pair_setup(const float* gram, int rows, int p, int n, int npass, int 
     s.N = M * npass;
     s.Q = padded_order(p);
     s.NT = s.Q / 16;
-    if (s.NT > 4 * kMaxTilesPerWave) return hipErrorInvalidValue;
-    s.rs = s.Q % 32 == 0 ? s.Q + 16 : s.Q;
-    s.lds = sizeof(float) * (size_t)(16 * kTileRows * (s.Q + 4) + s.Q * s.rs);
-    s.qv_inv = (1u << 20) / (unsigned)(s.Q / 4) + 1u;
+    if (s.Q > kMaxOrder) return hipErrorInvalidValue;
     s.f.dense = gram;
     s.f.p = p;
     s.f.period = perm_stride == 0 ? M : s.N;
@@ -252,14 +271,13 @@ hipError_t pair_setup(const float* gram, int rows, int p, int n, int npass, int 
 
 hipError_t gram_products_prepare()
 {
-    // the pair kernel stages up to 92 KB in shared memory (order 144): above the default limit of a launch
-    const int bytes = 160 * 1024 - 64;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(affine_pair_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(affine_pair_kernel<false>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(affine_pair_kernel<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    return e;
+    // the pair kernel stages up to 85 KB in shared memory (order 144): above the default limit of a launch
+    for (int nt = 1; nt <= kMaxOrder / 16; ++nt)
+        for (const PairKernel k : {pair_kernel<true, true>(nt), pair_kernel<true, false>(nt), pair_kernel<false, false>(nt)}) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds(nt));
+            if (e != hipSuccess) return e;
+        }
+    return hipSuccess;
 }
 
 hipError_t gram_launch_pairs(const float* gram, float* pairs_out, int rows, int p, int n, int npass, int perm_stride, float alpha,
@@ -268,9 +286,7 @@ hipError_t gram_launch_pairs(const float* gram, float* pairs_out, int rows, int 
     PairSetup s;
     hipError_t e = pair_setup(gram, rows, p, n, npass, perm_stride, alpha, lr_tab, lr_base, lr_len, &s);
     if (e != hipSuccess) return e;
-    hipExtLaunchKernelGGL((affine_pair_kernel<true, true>), dim3((s.NT + kTileRows - 1) / kTileRows, (s.N + 1) / 2), dim3(kPairThreads), (uint32_t)s.lds, stream, start,
-                          stop, 0u, s.f, static_cast<const float*>(nullptr), pairs_out, s.N, s.Q, s.rs, s.qv_inv, make_layout(p));
-    return hipGetLastError();
+    return launch_pair_round<true, true>(s, nullptr, pairs_out, s.N, p, stream, start, stop);
 }
 
 hipError_t gram_launch_products(const float* gram, float* theta, float* scratch, float* product_out, int rows, int p, int n, int npass,
@@ -282,11 +298,7 @@ hipError_t gram_launch_products(const float* gram, float* theta, float* scratch,
         hipError_t e0 = pair_setup(gram, rows, p, n, npass, perm_stride, alpha, lr_tab, lr_base, lr_len, &ps);
         if (e0 != hipSuccess) return e0;
     }
-    const int N = ps.N, Q = ps.Q, NT = ps.NT, rs = ps.rs;
-    const size_t lds = ps.lds;
-    const unsigned qv_inv = ps.qv_inv;
-    const FirstLevel f = ps.f;
-    const GramLayout L = make_layout(p);
+    const int N = ps.N, Q = ps.Q;
     if (pairs_then_chain) {
         // one round of products into the chain's layout, then the chain over half as many steps, each applied with rate 1
         hipError_t e = gram_launch_pairs(gram, scratch, rows, p, n, npass, perm_stride, alpha, lr_tab, lr_base, lr_len, stream, start,
@@ -302,18 +314,14 @@ hipError_t gram_launch_products(const float* gram, float* theta, float* scratch,
     float* fin = product_out ? product_out : buf[0];
     int count = N, which = 0;
     // round 0 reads the moment matrices; the start event rides on its dispatch, the stop event on the last one's
-    hipExtLaunchKernelGGL(affine_pair_kernel<true>, dim3((NT + kTileRows - 1) / kTileRows, (count + 1) / 2), dim3(kPairThreads), (uint32_t)lds, stream, start, nullptr,
-                          0u, f, static_cast<const float*>(nullptr), count <= 2 ? fin : buf[0], count, Q, rs, qv_inv, L);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_pair_round<true, false>(ps, nullptr, count <= 2 ? fin : buf[0], count, p, stream, start, nullptr);
     if (e != hipSuccess) return e;
     const float* cur = count <= 2 ? fin : buf[0];
     count = (count + 1) / 2;
     while (count > 1) {
         float* dst = count <= 2 ? fin : buf[which ^ 1];
         if (dst == cur) dst = buf[which ^ 1];        // (no product_out: the last round must not write what it reads)
-        hipLaunchKernelGGL(affine_pair_kernel<false>, dim3((NT + kTileRows - 1) / kTileRows, (count + 1) / 2), dim3(kPairThreads), lds, stream, f, cur, dst, count, Q,
-                           rs, qv_inv, L);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if ((e = launch_pair_round<false, false>(ps, cur, dst, count, p, stream, nullptr, nullptr)) != hipSuccess) return e;
         cur = dst;
         count = (count + 1) / 2;
         which ^= 1;
