@@ -38,12 +38,13 @@ constexpr size_t pair_lds(int nt) { return sizeof(float) * (size_t)(16 * nt) * (
 // Q x Q matrices, row-major, Q = 16 NT.  Two workgroups a product, a wavefront to each 16-row tile row of it: the right factor stands in
 // shared memory, where every wavefront reads it; a wavefront's rows of the left factor go straight from memory to the operands of
 // its matrix instructions, 16 bytes a lane.  For that the sum over k takes in step q of a block of 16 the k = 4 (lane / 16) + q, in both
-// operands.  MFMA operand layout (v_mfma_f32_16x16x4_f32): a = A[lane % 16][lane / 16], b = B[lane / 16][lane % 16],
-// c[v] = C[4 (lane / 16) + v][lane % 16].  Row stride Q + 4 of the right factor: rows four apart are 16 banks apart, so the 32 lanes that
-// are served together meet no bank twice.
-// What bounds it is a trip to memory for what the kernel before wrote, 50 KB a unit and product at Q = 112, and 28 matrix instructions for each of
-// the 49 tiles (2.8 us for a wavefront's seven).  150 products of order 112: PLACEHOLDER (four workgroups a product that stage 32 rows
-// of the left factor as well, with the loads of the largest order whatever the order was: 600 workgroups in two rounds).
+// operands.  The instruction (v_mfma_f32_16x16x4_f32: a = A[lane % 16][lane / 16], b = B[lane / 16][lane % 16], c[v] = C[4 (lane / 16) + v][lane % 16])
+// forms the product's transpose, so that a lane ends with four neighbouring columns of a row and stores 16 bytes.  Row stride Q + 4 of the right
+// factor: the eight or 32 lanes that are served together meet no bank twice.
+// What bounds it is a trip to memory for what the kernel before wrote (6 us with the launch, 50 KB a product and workgroup at Q = 112), the
+// matrix instructions (28 for each of a wavefront's seven tiles, 2.8 us) and the way out, one after the other in a workgroup and little more than
+// one workgroup to a unit.  150 products of order 112: 17.3 us; four workgroups a product that staged 32 rows of the left factor too, with
+// the loads of the largest order whatever the order was and stores of 4 bytes, 24.4.
 // FIRST: the factors are the steps themselves, A_s = [[I - alpha_s Sxx_s, alpha_s Sxy_s], [0, 1]] padded with zeros:
 // entry (r, c) is (r == c and r <= p) - alpha_s D_s(r, c) with D_s the dense matrix the moments kernel wrote.
 // CHAIN_OUT: the product P goes out as [I - P | last column of P] in the layout the chain kernel reads (GramLayout), so
