@@ -491,6 +491,9 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
         }
     };
     if (one_chunk) load_state(c_lo + 2 * my_pair);
+    // Rows wait until the first trip's words have come in, where these are many (us per update at p = 2500, n = 1500: 9.10 not at all, 8.94 until this
+    // workgroup's sums are out, 8.29 so; but 4.22, 4.18 and 4.35 on 64 workgroups at p = 1028, n = 200)
+    const bool early = G < 128;
     unsigned dead = 0u;
     unsigned phase = 0u;                             // chunks of slices summed so far (the same in all NX wavefronts)
     int s = first;
@@ -515,6 +518,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
         dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
         // 0. this workgroup's sums out of shared memory
         ex.send_sums(part, tag, p);
+        if (early) ex.mark_sent();
 
         // 1. this workgroup's slice, if it has one: sum over all workgroups, in a fixed order; the update; the new
         //    values into every copy of theta
@@ -586,6 +590,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
                 pb += PPc;
             } while (pb < npair && dead == 0u);
         }
+        if (!early) ex.mark_sent();
         // 2. the whole new theta, from this workgroup's copy
         if (128 * xw < p && dead == 0u) {
             const unsigned copy_off = (unsigned)lane * 16u;

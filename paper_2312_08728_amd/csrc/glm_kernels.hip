@@ -785,7 +785,9 @@ hipError_t glm_prepare(GlmLaunchShape* s)
         // fewer workgroups than planned hold fewer rows: only if the step still fits
         if (G >= (sliced ? 8 : 1) && glm_narrow_rows_in_flight(s->narrow_layout, s->narrow_rw, G, s->n) == s->narrow_pf) {
             s->max_G = std::min(s->max_G, cap);
+            const bool fewer = G != s->G;
             s->G = G;
+            if (fewer && (e = glm_narrow_prepare(*s, s->p, &cap)) != hipSuccess) return e;   // (another exchange is another kernel)
         } else {
             s->narrow = 0;
             s->chain_block = s->block;

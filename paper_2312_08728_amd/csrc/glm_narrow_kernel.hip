@@ -354,14 +354,10 @@ int glm_narrow_rows_in_flight(const NarrowLayout& l, int rw, int G, int64_t n)
 hipError_t glm_narrow_prepare(const GlmLaunchShape& s, int p, int* max_groups)
 {
     const size_t lds = narrow_lds_bytes(s, p);
-    KernelFn fn = nullptr;
-    for (const int ex : {kTwoTrips, kByDie}) {   // (fewer workgroups than planned may take the other)
-        fn = narrow_kernel(s, ex);
-        if (!fn) return hipErrorInvalidValue;
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    hipError_t e = hipSuccess;
+    KernelFn fn = narrow_kernel(s, sliced_exchange(s));
+    if (!fn) return hipErrorInvalidValue;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
     int per_cu = 0;
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), narrow_block(s.narrow_rw), lds);
     if (e != hipSuccess) return e;

@@ -270,14 +270,15 @@ hipError_t pair_setup(const float* gram, int rows, int p, int n, int npass, int 
 
 }  // namespace
 
-hipError_t gram_products_prepare()
+hipError_t gram_products_prepare(int64_t p)
 {
-    // the pair kernel stages up to 85 KB in shared memory (order 144): above the default limit of a launch
-    for (int nt = 1; nt <= kMaxOrder / 16; ++nt)
-        for (const PairKernel k : {pair_kernel<true, true>(nt), pair_kernel<true, false>(nt), pair_kernel<false, false>(nt)}) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds(nt));
-            if (e != hipSuccess) return e;
-        }
+    // the pair kernel stages up to 85 KB in shared memory (order 144): above the default limit of a launch for more than seven tile rows
+    const int nt = padded_order((int)p) / 16;
+    if (pair_lds(nt) <= 64 * 1024) return hipSuccess;
+    for (const PairKernel k : {pair_kernel<true, true>(nt), pair_kernel<true, false>(nt), pair_kernel<false, false>(nt)}) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)pair_lds(nt));
+        if (e != hipSuccess) return e;
+    }
     return hipSuccess;
 }
 
