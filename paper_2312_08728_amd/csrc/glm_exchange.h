@@ -753,7 +753,7 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
 // 3.91 / 3.61 at 1000, 500 (160), 5.06 / 4.70 at 1024, 2000 (256); rows of more than 1024 floats 5.54 / 5.01 at 1500, 1000, 5.57 / 4.67 at 2048, 300.
 // The eight sums of a line go to every die separately: a line that all dies ask for took 1.45 us instead of 1.18, one that four wavefronts
 // write a quarter of 2.6.  Every workgroup making the whole update from the dies' sums costs a trip less and more for its words: 3.5 us at p = 200.
-// It is the faster way as long as a wavefront has one line (up to 1024 floats) or two: each line more is two trips one behind the other (4.20
+// It is the faster way as long as a wavefront has one line (up to 1024 floats), two or three: each line more is two trips one behind the other (4.20
 // against 3.32 at p = 200 on 24 workgroups, 16.3 against 3.7 at p = 1000 on 16; both lines in the same trips: 3.60 against 3.23 at p = 400 on 32,
 // 4.26 against 3.76 at p = 1000 on 64), which the callers' rule sees to (glm_by_die).
 // LW: lines a wavefront takes at a time.  U2: pairs of words a lane requests at a time when it collects theta.

@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     // ------------------------------------------------------------------------------------ exchange wavefronts
     const ExchangeLds x{th, P_PAD, xstate, xstate + kExchangeState * NX, sums, P_PAD, (unsigned)kRowWaves,
                         (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)&s_sent, (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
-    if (CH == 1 && a.by_die) exchange_by_die<OPT, NX, 1, 2, 6>(a, x, lane, wave);
+    if (a.by_die) exchange_by_die<OPT, NX, 1, CH + 1, CH == 1 ? 6 : 11>(a, x, lane, wave);
     else exchange_wavefront<OPT, NX, 1, 11, CH == 1 ? 6 : 11>(a, x, lane, wave);   // (a trip's words at once, for up to 256 workgroups and p columns)
 }
 
@@ -302,13 +302,14 @@ hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStr
 {
     if (G < 8 || G % 8 != 0 || args.s_begin >= args.s_end || args.p < 4 || args.p > kRowWaves * 256 * ch)
         return hipErrorInvalidValue;
-    // Three short trips instead of two where a wavefront has two lines at most and a step few rows, so that little stands in the queues that
-    // the trips share with them.  us per update, two trips / three: 6.1 / 5.7 at p = 1028, n = 1500, 8.1 / 8.0 at 1500, 3000, 7.89 / 7.84 at 2048, 2048
-    // (256 workgroups), but 16.9 / 17.6 at 2048, 8192; 9.23 / 9.33 at 2500, 1500 and 12.3 / 13.0 at 4096, 2048 with three lines at a time.
+    // Three short trips instead of two where a wavefront has two lines at most (three beyond 2048 floats) and a step few rows, so that little stands
+    // in the queues that the trips share with them.  us per update, two trips / three: 6.1 / 5.6 at p = 1028, n = 1500, 8.1 / 7.7 at 1500, 3000, 7.47 / 7.46 at
+    // 2048, 2048 (256 workgroups), but 16.3 / 17.3 at 2048, 8192; 8.4 / 6.7 at 4096, 300, 7.7 / 6.6 at 3000, 500 with Adam, 6.9 / 5.7 at 3200, 200 (208), but
+    // 6.7 / 6.9 at 2500, 1000, 7.5 / 8.2 at 4096, 700.
     GlmArgs a = args;
     a.width = (args.p + 3) / 4 * 4;
     a.shift = a.width - args.p;
-    a.by_die = ch == 1 && glm_by_die(args.p, G, 2 * NX) && args.n <= 12 * G;
+    a.by_die = glm_by_die(args.p, G, (ch + 1) * NX) && args.n <= (ch == 1 ? 12 : 2) * G;
     hipExtLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, a);
     return hipGetLastError();
 }

@@ -182,6 +182,8 @@ BY_DIE = [
     (wl.LOGISTIC, 1028, 500, 88, 1_500),     # 65 lines for 33 wavefronts, two each but one
     (wl.LINEAR, 2048, 400, 176, 1_000),      # 128 for 66
     (wl.LOGISTIC, 1500, 900, 256, 2_500),    # 94 for 96: the second line of each is beyond the end
+    (wl.LINEAR, 2052, 300, 168, 900),        # 129 lines for 63 wavefronts, up to three each
+    (wl.LOGISTIC, 4096, 250, 256, 600),      # 256 for 96
 ]
 
 
