@@ -10,20 +10,20 @@
 // A row wavefront must not poll global memory itself: loads return to a wavefront in the order it issued them, so
 // its poll would come back behind the newest rows it has in flight.
 //
-// Two forms.  exchange_wavefront: two trips over the fabric per step, asking for everything a trip needs at once:
+// Three forms.  exchange_wavefront: two trips over the fabric per step, asking for everything a trip needs at once:
 //   0. the workgroup's sums leave as flagged words {value : tag};
 //   1. workgroup g adds up, for the g-th slice of the columns (whole 128-byte lines of words), the words of all G
 //      workgroups in a fixed order, applies the update to its slice of theta and publishes the new values in
 //      kThetaCopies copies of theta (a workgroup later reads copy g mod kThetaCopies, so no set of words is polled
 //      by the whole grid);
 //   2. it collects the whole new theta from its copy into shared memory and raises the version.
+// exchange_by_die: the same with the sums added up on each die first, three shorter trips.
 // exchange_one_trip: every workgroup adds up all words itself and makes the whole update.
 // Polls are bounded by the wall clock.
 //
-// What bounds a step of short rows is latency: two trips of about 0.6 us, in each the time until the slowest workgroup has stored
-// its words, and the instructions between them.  us per update before / now (the loops, waits and state of the exchange as it was
-// before / written as ExchangeCommon says, residuals worked out once per row): 4.3 / 3.5 at p = 200, n = 4096 (256 workgroups); 5.1 / 3.6
-// at p = 512, n = 1000 with Adam (160).  One trip (PairExchange): see there.
+// What bounds a step of short rows is latency: each trip is the time until the slowest workgroup has stored its words, the way there and back, 0.6 us
+// over the fabric and half of that within a die, and the instructions between them; and all that a compute unit asks for passes through one memory
+// pipeline in turn, so rows are requested when the exchange has nothing to send or to ask for (s_sent).
 #pragma once
 
 #include "bmgd_internal.h"

@@ -21,10 +21,9 @@
 //     unit can take.  Two trips over the fabric per step.  us per update with one (whose SIMD had no row wavefronts) and with three: 7.6 / 6.2 at
 //     p = 1028, n = 1500 (256 workgroups, 6 rows each), 9.1 / 7.9 at 2048, 2048, 10.3 / 9.1 at 2500, 1500, 15.0 / 13.7 at 2500, 4096, 19.0 / 18.0 at
 //     4096, 4096, 30.6 / 29.9 at 4096, 8192: the fewer the rows, the less stands in the queues that the exchange now shares with them.  With four:
-//     at most 2 % less.  (Measured: under the row traffic a trip costs about 2 us
-//     whether the words come from the same die or another, and a wavefront that asks for a phase's words in two
-//     batches pays twice, so a die-local first stage - one more trip - loses; a word that was just written comes from
-//     beyond the die even where the same die wrote it: only atomics stay within.)
+//     at most 2 % less.  (With words stored at device scope a trip costs the same whether they come from the same die or another: the first load
+//     of a word that was just written goes beyond the die.  Stored without a scope they stay in the die's L2, which exchange_by_die uses where a
+//     workgroup has few rows.)
 //
 // Waits: row wavefronts only ever wait on shared-memory flags (which the exchange wavefronts always release, also
 // when they give up); their polls are bounded by the wall clock (ExchangeCommon::go_on).
