@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # HBM traffic of one launch of the chain kernel on the primary workload, from rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE (see profiles/), scaled by the copy calibration; valid only for the source of the kernel it was measured on
 # (the line reports null once that file has changed: measure again and update the entry).
-TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641623}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip', 'lds_load.h'), "kernel_sha256": "72e918c22d690b02dd7601c56f4d43ea13720f6a264e2c0d16859e562fc1d772", "bytes_per_launch": 216719082}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "abe5e236b3d084c47f2e084ee0de8da34ae914ab60878a7c07006d073e741fe2", "bytes_per_launch": 2473796640}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "c453f233be03bde52844585da6e0938c25656b18463865cbd964552da155e3f4", "bytes_per_launch": 9417469781}}
+TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641623}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip', 'lds_load.h'), "kernel_sha256": "b60340cb0c9dcf9d1cf2f376b4c1e4cb1a000538512debf820cec72930f0f884", "bytes_per_launch": 201608619}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "d1e748ed3b7b089df9edc5e9caf415c1c81a4bdf5ae93de72183b0bc3b9030ef", "bytes_per_launch": 2162630261}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "56adc46b845bb3dee593ed4aa30a68ed7b589434e1d6ef69ec0ee28f339a93f2", "bytes_per_launch": 9467897771}}
 
 
 def _kernel_sha(sources) -> str:
