@@ -1723,4 +1723,21 @@ BMGD_API const char* bmgd_last_error(const bmgd_ctx* ctx)
 
 BMGD_API void bmgd_destroy(bmgd_ctx* ctx) { destroy_ctx(ctx); }
 
+// Not part of the C interface: the launch shape of a row-form configuration with mini-batches of n rows, for a run whose mini-batches have run_n of them,
+// where nothing limits the workgroups but their number.  out: workgroups, threads of each, kernel (0 general, 1 rows of up to 1024 floats, 2 wider),
+// exchange (kExchangeOneTrip ...), rows per row slot and launch of the second kernel.
+BMGD_API int bmgd_internal_plan(int64_t p, int64_t n, int32_t n_workgroups, int32_t chain, int64_t run_n, int32_t out[5])
+{
+    GlmLaunchShape s;
+    char msg[160];
+    const bool persistent = chain != BMGD_CHAIN_LAUNCH;
+    if (!glm_plan(p, n, n_workgroups, kMaxGroups, persistent, &s, msg, sizeof msg)) return BMGD_EINVAL;
+    out[0] = s.G;
+    out[1] = persistent ? s.chain_block : s.block;
+    out[2] = !persistent ? 0 : s.split ? 2 : s.narrow;
+    out[3] = glm_exchange(s, run_n);
+    out[4] = persistent && s.narrow ? s.narrow_pf : 0;
+    return BMGD_OK;
+}
+
 }  // extern "C"

@@ -153,6 +153,10 @@ struct GlmArgs {
 // Whether the `lines` wavefronts of each workgroup that add up a line of 16 columns at a time can hold all lines (exchange_by_die).
 inline bool glm_by_die(int64_t p, int G, int lines) { return G % 8 == 0 && (p + 15) / 16 <= (int64_t)(G / 8) * lines; }
 
+// How the workgroups of a persistent launch exchange their sums, for a run with mini-batches of n rows.
+enum { kExchangeOneTrip = 0, kExchangeByDie = 1, kExchangeTwoTrips = 2 };
+int glm_exchange(const GlmLaunchShape& shape, int64_t n);
+
 // Pick V/CPL/PF/L/block/G/reduce mode for a shape; returns false if p is outside the supported range.
 // persistent: for the chain's kernels (false: for one launch per step, by the general kernel).
 bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persistent, GlmLaunchShape* out, char* why, size_t why_len);
@@ -168,6 +172,7 @@ hipError_t glm_launch_step(const GlmLaunchShape& shape, const GlmArgs& args, int
 // and threads per workgroup, co-resident capacity, one launch covering steps [s_begin, s_end).
 size_t glm_split_lds_bytes(int ch);
 int glm_split_block();
+bool glm_split_by_die(int ch, int64_t p, int G, int64_t n);
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups);
 hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream, hipEvent_t stop);
 
@@ -177,6 +182,7 @@ hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStr
 constexpr int kNarrowMoreRows = 12;        // row wavefronts where the sums are added up by every workgroup, or p is odd
 constexpr int kNarrowOneTripMaxP = 512;    // widest rows of the redundant reduction in this kernel
 int glm_narrow_block(int rw);
+bool glm_narrow_by_die(int64_t p, int G);
 NarrowLayout glm_narrow_layout(int64_t p);
 int glm_narrow_rows_in_flight(const NarrowLayout& l, int rw, int G, int64_t n);
 hipError_t glm_narrow_prepare(const GlmLaunchShape& shape, int p, int* max_groups);

@@ -646,6 +646,17 @@ namespace {
 // Words that a workgroup fetches per step when every workgroup adds up the sums of all of them.
 constexpr int64_t kRedundantMaxWords = 4096;
 
+// Steps launched one by one: rows that each row slot of rw wavefronts on `groups` workgroups would take, in the general kernel's vectors, or 0 where
+// these are more than 32 floats a lane (16 with more than eight wavefronts).  What the number of workgroups goes by there.
+int launched_rows_held(const GlmLaunchShape& s, int rw, int groups, int64_t n)
+{
+    const int64_t slots = (int64_t)groups * rw * (64 / std::max(s.L, 4));
+    const int64_t need = (n + slots - 1) / slots;
+    const int pf = need <= 4 ? (int)need : 8;
+    const bool fits = need <= 8 && s.CPL <= 4 && (s.V >= 2 || rw > 8) && s.V * s.CPL * pf <= (rw > 8 ? 16 : 32) && pf * (s.CPL + 2) <= 24;
+    return fits ? pf : 0;
+}
+
 }  // namespace
 
 bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persistent, GlmLaunchShape* out, char* why, size_t why_len)
@@ -681,7 +692,10 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
     // Narrow rows, a step's rows fitting the registers: the kernel with exchange wavefronts.  Where the sums of all workgroups are few
     // enough every workgroup adds them up itself, in one trip over the fabric per step instead of two or three.
     s.narrow_layout = glm_narrow_layout(p);
-    auto rows_held = [&](int rw, int groups) { return p <= 1024 ? glm_narrow_rows_in_flight(s.narrow_layout, rw, groups, n) : 0; };
+    auto rows_held = [&](int rw, int groups) {
+        if (!persistent) return launched_rows_held(s, rw, groups, n);
+        return p <= 1024 ? glm_narrow_rows_in_flight(s.narrow_layout, rw, groups, n) : 0;
+    };
     if (requested_G <= 0 && p <= kNarrowOneTripMaxP) {
         // Left to choose: one workgroup if it holds a step's rows (no exchange: with as many rows as it can hold 1.3 to 2.3 us per update
         // at p = 3 to 63 and 1.3 at p = 128, against 1.8 to 2.4 on four to sixteen; the general kernel, which steps launched
@@ -741,6 +755,13 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
     s.lds_bytes = (size_t)(th_len + (int64_t)(s.block / 64) * p + s.block + 64) * sizeof(float);
     *out = s;
     return true;
+}
+
+int glm_exchange(const GlmLaunchShape& s, int64_t n)
+{
+    if (s.reduce_mode == kReduceRedundant) return kExchangeOneTrip;
+    const bool by_die = s.split ? glm_split_by_die(s.split_ch, s.p, s.G, n) : s.narrow && glm_narrow_by_die(s.p, s.G);
+    return by_die ? kExchangeByDie : kExchangeTwoTrips;
 }
 
 hipError_t glm_prepare(GlmLaunchShape* s)

@@ -317,7 +317,7 @@ KernelFn narrow_kernel_opt(const GlmLaunchShape& s, int ex)
 
 // ex: of the sliced reduction, which of its exchanges
 KernelFn narrow_kernel(const GlmLaunchShape& s, int ex) { return s.with_optimizer ? narrow_kernel_opt<true>(s, ex) : narrow_kernel_opt<false>(s, ex); }
-int sliced_exchange(const GlmLaunchShape& s) { return glm_by_die(s.p, s.G, kXWaves) ? kByDie : kTwoTrips; }
+int sliced_exchange(const GlmLaunchShape& s) { return glm_narrow_by_die(s.p, s.G) ? kByDie : kTwoTrips; }
 
 size_t narrow_lds_bytes(const GlmLaunchShape& s, int p)
 {
@@ -328,6 +328,8 @@ size_t narrow_lds_bytes(const GlmLaunchShape& s, int p)
 }  // namespace
 
 int glm_narrow_block(int rw) { return narrow_block(rw); }
+
+bool glm_narrow_by_die(int64_t p, int G) { return glm_by_die(p, G, kXWaves); }
 
 NarrowLayout glm_narrow_layout(int64_t p)
 {

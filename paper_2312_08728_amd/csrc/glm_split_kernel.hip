@@ -281,6 +281,12 @@ size_t glm_split_lds_bytes(int ch)
 
 int glm_split_block() { return kSplitBlock; }
 
+// Three short trips instead of two where a wavefront has two lines at most (three beyond 2048 floats) and a step few rows, so that little stands
+// in the queues that the trips share with them.  us per update, two trips / three: 6.1 / 5.6 at p = 1028, n = 1500, 8.1 / 7.7 at 1500, 3000, 7.47 / 7.46 at
+// 2048, 2048 (256 workgroups), but 16.3 / 17.3 at 2048, 8192; 8.4 / 6.7 at 4096, 300, 7.7 / 6.6 at 3000, 500 with Adam, 6.9 / 5.7 at 3200, 200 (208), but
+// 6.7 / 6.9 at 2500, 1000, 7.5 / 8.2 at 4096, 700.
+bool glm_split_by_die(int ch, int64_t p, int G, int64_t n) { return glm_by_die(p, G, (ch + 1) * NX) && n <= (ch == 1 ? 12 : 2) * G; }
+
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups)
 {
     KernelFn fn = split_kernel(ch, opt);
@@ -301,14 +307,10 @@ hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStr
 {
     if (G < 8 || G % 8 != 0 || args.s_begin >= args.s_end || args.p < 4 || args.p > kRowWaves * 256 * ch)
         return hipErrorInvalidValue;
-    // Three short trips instead of two where a wavefront has two lines at most (three beyond 2048 floats) and a step few rows, so that little stands
-    // in the queues that the trips share with them.  us per update, two trips / three: 6.1 / 5.6 at p = 1028, n = 1500, 8.1 / 7.7 at 1500, 3000, 7.47 / 7.46 at
-    // 2048, 2048 (256 workgroups), but 16.3 / 17.3 at 2048, 8192; 8.4 / 6.7 at 4096, 300, 7.7 / 6.6 at 3000, 500 with Adam, 6.9 / 5.7 at 3200, 200 (208), but
-    // 6.7 / 6.9 at 2500, 1000, 7.5 / 8.2 at 4096, 700.
     GlmArgs a = args;
     a.width = (args.p + 3) / 4 * 4;
     a.shift = a.width - args.p;
-    a.by_die = glm_by_die(args.p, G, (ch + 1) * NX) && args.n <= (ch == 1 ? 12 : 2) * G;
+    a.by_die = glm_split_by_die(ch, args.p, G, args.n);
     hipExtLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, a);
     return hipGetLastError();
 }
