@@ -179,6 +179,31 @@ __device__ __forceinline__ int column_of(const GlmArgs& a, int pos)
 // where the vector of a row that starts at a position is loaded from; beyond the row (theta is 0 there) its start
 __device__ __forceinline__ int vector_from(const GlmArgs& a, int pos) { return pos >= a.width ? 0 : pos - (pos >= a.width - 4 ? a.shift : 0); }
 
+// Theta into the first `stride` floats of `th`, by position (0 where there is no column), and zeros into the others up to `total`.  (Multiples of
+// 16; MAX: the largest stride.)  All that a thread loads is asked for at once and comes while the zeros go out: with a load and its position to
+// work out in each turn of one loop over everything, a launch of one update took 10.1 us instead of 9.1 at p = 1000, n = 200, 19.0 instead of 17.0 at
+// 4096, 200.
+typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+template <int BLOCK, int MAX>
+__device__ __forceinline__ void load_theta(const GlmArgs& a, lds_f32* th, int stride, int total, int tid)
+{
+    constexpr int K = (MAX + BLOCK - 1) / BLOCK;
+    float v[K];
+    int col[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int c = tid + BLOCK * k;
+        col[k] = c < a.width ? column_of(a, c) : -1;
+        v[k] = a.theta[max(0, min(col[k], a.p - 1))];
+    }
+    for (int c = stride + 4 * tid; c < total; c += 4 * BLOCK) *(lds_u32x4*)(th + c) = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const int c = tid + BLOCK * k;
+        if (c < stride) th[c] = col[k] >= 0 && col[k] < a.p ? v[k] : 0.f;
+    }
+}
+
 // The sum over the lanes with the same lane % PPc (8 <= PPc <= 64, uniform), in all of them.
 __device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
 {

@@ -74,17 +74,14 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     const int p = a.p;
     const int L = a.L;
     const int width = a.width;                       // positions of a row (glm_exchange.h)
-    const int stride = max((p + 15) & ~15, V * L * CPL);          // of theta and of the sums in shared memory
+    const int stride = max((p + 15) & ~15, V * L * CPL);          // of theta and of the sums in shared memory (rows of up to 7 floats: 16)
     lds_f32* th = (lds_f32*)smem;                    // [2][stride]: theta, by version parity
     lds_f32* sums = th + 2 * stride;                 // [RW][stride]: each row wavefront's gradient sums of a step
     lds_f32* xstate = sums + RW * stride;            // scratch of the exchange wavefronts
     const int first = a.s_begin, last = a.s_end;
 
     // theta (version 0 in copy 0) and the sums; positions beyond the row stay zero for good (rows are read at column 0 there)
-    for (int c = tid; c < (2 + RW) * stride; c += narrow_block(RW)) {
-        const int col = c < width ? column_of(a, c) : -1;
-        th[c] = col >= 0 && col < p ? a.theta[col] : 0.f;
-    }
+    load_theta<narrow_block(RW), V == 4 ? 256 * CPL : 16>(a, th, stride, (2 + RW) * stride, tid);
     if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_sent = 0u; s_xconsumed = 0u; }
     if (tid < kXWaves) s_xarrived[tid] = 0u;
     __syncthreads();                                 // the only barrier: from here on the wavefronts meet through flags

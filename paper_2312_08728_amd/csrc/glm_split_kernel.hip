@@ -89,10 +89,7 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     const int first = a.s_begin, last = a.s_end;
 
     // theta (version 0 in copy 0): positions (glm_exchange.h) beyond the row stay zero for good (rows are read at column 0 there)
-    for (int c = tid; c < 2 * P_PAD; c += kSplitBlock) {
-        const int col = c < a.width ? column_of(a, c) : -1;
-        th[c] = col >= 0 ? a.theta[col] : 0.f;
-    }
+    load_theta<kSplitBlock, P_PAD>(a, th, P_PAD, 2 * P_PAD, tid);
     if (tid < 2 * kRowWaves) pd_seq[tid] = 0u;
     if (tid == 0) { s_abort = 0; s_theta_version = 0u; s_published = 0u; s_sent = 0u; s_xconsumed = 0u; }
     if (tid < NX) s_xarrived[tid] = 0u;
