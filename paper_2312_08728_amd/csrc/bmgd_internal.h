@@ -138,7 +138,6 @@ struct GlmArgs {
     int model;
     int L, logL;
     int reduce_mode;
-    int by_die;             // rows of more than 1024 floats: 1: sums over two levels, 0: in two trips (filled in by the kernel's launch)
     float alpha;
     long long timeout_ticks;
     int width, shift;       // positions of a row in shared memory, and how many of the last four stand for no column (filled in by

@@ -486,8 +486,8 @@ struct ExchangeCommon {
 // workgroups for the slice (the first one then adds the NX partial sums in their order and applies the update) and
 // collects a part of theta.  A wavefront pulls freshly written lines at a fraction of what a compute unit can take, so several on as
 // many SIMDs finish a trip sooner, beside row traffic too (glm_split_kernel.hip has both figures).
-// U1, U2: pairs of words a lane requests per trip when it sums the slice / collects theta.
-template <bool OPT, int NX, int NSUM, int U1, int U2>
+// GATED: the row wavefronts wait for s_sent.  U1, U2: pairs of words a lane requests per trip when it sums the slice / collects theta.
+template <bool OPT, int NX, int NSUM, bool GATED, int U1, int U2>
 __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
 {
     ExchangeCommon<OPT, NX, NSUM> ex(a, x, lane, xw);
@@ -518,7 +518,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
     if (one_chunk) load_state(c_lo + 2 * my_pair);
     // Rows wait until the first trip's words have come in, where these are many (us per update at p = 2500, n = 1500: 9.10 not at all, 8.94 until this
     // workgroup's sums are out, 8.29 so; but 4.22, 4.18 and 4.35 on 64 workgroups at p = 1028, n = 200)
-    const bool early = G < 128;
+    const bool early = G * p <= (1 << 18);
     unsigned dead = 0u;
     unsigned phase = 0u;                             // chunks of slices summed so far (the same in all NX wavefronts)
     int s = first;
@@ -543,7 +543,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
         dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
         // 0. this workgroup's sums out of shared memory
         ex.send_sums(part, tag, p);
-        if (early) ex.mark_sent();
+        if (GATED && early) ex.mark_sent();
 
         // 1. this workgroup's slice, if it has one: sum over all workgroups, in a fixed order; the update; the new
         //    values into every copy of theta
@@ -615,7 +615,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
                 pb += PPc;
             } while (pb < npair && dead == 0u);
         }
-        if (!early) ex.mark_sent();
+        if (GATED && !early) ex.mark_sent();
         // 2. the whole new theta, from this workgroup's copy
         if (128 * xw < p && dead == 0u) {
             const unsigned copy_off = (unsigned)lane * 16u;
@@ -691,7 +691,7 @@ struct PairExchange : ExchangeCommon<OPT, NX, NSUM> {
 
 // The same steps in ONE trip over the fabric: every workgroup adds up all sums of all workgroups itself, in the same order, and keeps
 // its own copy of theta and of an update rule's state (at m + g pp).  For few words (G p of them come in per step and workgroup).
-template <bool OPT, int NX, int NSUM, int PW>
+template <bool OPT, int NX, int NSUM, bool GATED, int PW>
 __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
 {
     PairExchange<OPT, NX, NSUM, PW> ex(a, x, lane, xw);
@@ -721,7 +721,7 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
         f32x2 t = ex.own_sum();
         if (G > 1) {
             ex.send(t, part, tag);
-            ex.mark_sent();
+            if constexpr (GATED) ex.mark_sent();
             // Words of many workgroups take a wavefront long to fetch: asked for at once they would be fetched twice, none of the others'
             // having come yet (0.27 us per update with 32 workgroups at p = 128, n = 1024; nothing with few)
             if (loads > 2) __builtin_amdgcn_s_sleep(15);

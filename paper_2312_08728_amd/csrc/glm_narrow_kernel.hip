@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     __shared__ unsigned s_published;                 // publications of row wavefronts, counted over all steps
     __shared__ unsigned s_xarrived[kXWaves], s_xconsumed;   // hand-over of partial sums between the exchange wavefronts
 
-    constexpr bool ONE = EX >= 8;
+    constexpr bool ONE = EX >= 8, kGated = ONE ? EX > 8 : EX == kByDie;   // (whether rows wait for s_sent)
     constexpr int E = CPL * V;                       // floats of a row held per lane
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -154,7 +154,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
 
         const unsigned abort_addr = (unsigned)(uintptr_t)(lds_u32*)&s_abort;
         const unsigned version_addr = (unsigned)(uintptr_t)(lds_u32*)&s_theta_version;
-        const bool gated = ONE ? EX > 8 && G > 1 : EX == kByDie;
+        const bool gated = kGated && (!ONE || G > 1);
         const unsigned sent_addr = (unsigned)(uintptr_t)(lds_u32*)&s_sent;
         lds_f32* my_sums = sums + rw * stride;
         // Step s on the rows in S, then S is refilled.  Straight-line code with one conditional (the publication).  A
@@ -230,10 +230,10 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
                 // a release here would wait for the rows in flight as well)
                 asm volatile("" ::: "memory");
                 if (lane == 0) lds_add_one(lds_address((lds_u32*)&s_published));
+                // What the exchange sends and asks for first would stand behind the coming requests in the unit's memory pipeline; they go out
+                // while its words are under way.
+                if (gated) lds_wait_ge(sent_addr, (unsigned)(s + 1 - first) * kXWaves, abort_addr);
             }
-            // What the exchange sends and asks for first would stand behind these requests in the unit's memory pipeline; they go out while
-            // its words are under way.
-            lds_wait_ge(sent_addr, gated ? (unsigned)(min(s + 1, last) - first) * kXWaves : 0u, abort_addr);
             request(S);
         };
         int su = first;
@@ -256,9 +256,9 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     const ExchangeLds x{th, stride, xstate, xstate + kExchangeState * kXWaves, sums, stride, (unsigned)RW,
                         (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)&s_sent,
                         (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
-    if constexpr (ONE) exchange_one_trip<OPT, kXWaves, RW, EX>(a, x, lane, wave);
+    if constexpr (ONE) exchange_one_trip<OPT, kXWaves, RW, kGated, EX>(a, x, lane, wave);
     else if constexpr (EX == kByDie) exchange_by_die<OPT, kXWaves, RW, 1, 2>(a, x, lane, wave);   // (p <= 1024: two loads per lane collect theta ...
-    else exchange_wavefront<OPT, kXWaves, RW, 8, 2>(a, x, lane, wave);   // ... and eight cover the slice for up to 256 workgroups)
+    else exchange_wavefront<OPT, kXWaves, RW, kGated, 8, 2>(a, x, lane, wave);   // ... and eight cover the slice for up to 256 workgroups)
 }
 
 using KernelFn = void (*)(GlmArgs);

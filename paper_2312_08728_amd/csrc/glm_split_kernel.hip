@@ -60,7 +60,9 @@ __device__ __forceinline__ void lds_wait_all_eq(unsigned addr, unsigned want, un
                  : "=&v"(t) : "v"(addr), "v"(want), "v"(abort_addr) : "vcc", "memory");
 }
 
-template <int CH, bool OPT>
+// BY_DIE: how the sums are exchanged, over two levels or in two trips.  (A kernel each: with both in one the row wavefronts' loop read six more scalar
+// values back from vector registers for every group of rows, 3 % of an update with 48 rows a workgroup at p = 1500.)
+template <int CH, bool OPT, bool BY_DIE>
 __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
 {
     extern __shared__ __align__(16) float smem[];
@@ -236,10 +238,10 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
                     acc[ch] = make_float4(0.f, 0.f, 0.f, 0.f);
                 }
                 if (lane == 0) __hip_atomic_fetch_add(&s_published, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                // (what is requested behind a step's last group would stand in front of the exchange's words in the unit's memory pipeline; us per
+                // update at 4096, 2048: 12.3 without this wait, 11.5 with it, 30.0 and 29.0 at 4096, 8192, 7.84 and 7.46 at 2048, 2048)
+                lds_wait_ge(sent_addr, (unsigned)(su + 1 - first) * NX, abort_addr);
             }
-            // (what is requested behind a step's last group would stand in front of the exchange's words in the unit's memory pipeline; us per
-            // update at 4096, 2048: 12.3 without this wait, 11.5 with it, 30.0 and 29.0 at 4096, 8192, 7.84 and 7.46 at 2048, 2048)
-            lds_wait_ge(sent_addr, step_ends ? (unsigned)(su + 1 - first) * NX : 0u, abort_addr);
             request(S);
             ku = step_ends ? 0 : (live ? ku + 1 : 0);
             su += step_ends ? 1 : 0;
@@ -257,17 +259,19 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     // ------------------------------------------------------------------------------------ exchange wavefronts
     const ExchangeLds x{th, P_PAD, xstate, xstate + kExchangeState * NX, sums, P_PAD, (unsigned)kRowWaves,
                         (lds_u32*)&s_published, (lds_u32*)&s_theta_version, (lds_i32*)&s_abort, (lds_u32*)&s_sent, (lds_u32*)s_xarrived, (lds_u32*)&s_xconsumed};
-    if (a.by_die) exchange_by_die<OPT, NX, 1, CH + 1, CH == 1 ? 6 : 11>(a, x, lane, wave);
-    else exchange_wavefront<OPT, NX, 1, 11, CH == 1 ? 6 : 11>(a, x, lane, wave);   // (a trip's words at once, for up to 256 workgroups and p columns)
+    if constexpr (BY_DIE) exchange_by_die<OPT, NX, 1, CH + 1, CH == 1 ? 6 : 11>(a, x, lane, wave);
+    else exchange_wavefront<OPT, NX, 1, true, 11, CH == 1 ? 6 : 11>(a, x, lane, wave);   // (a trip's words at once, for up to 256 workgroups and p columns)
 }
 
 using KernelFn = void (*)(GlmArgs);
 
+template <bool BY_DIE>
 KernelFn split_kernel(int ch, bool opt)
 {
-    if (ch == 1) return opt ? glm_split_kernel<1, true> : glm_split_kernel<1, false>;
-    return opt ? glm_split_kernel<2, true> : glm_split_kernel<2, false>;
+    if (ch == 1) return opt ? glm_split_kernel<1, true, BY_DIE> : glm_split_kernel<1, false, BY_DIE>;
+    return opt ? glm_split_kernel<2, true, BY_DIE> : glm_split_kernel<2, false, BY_DIE>;
 }
+KernelFn split_kernel(int ch, bool opt, bool by_die) { return by_die ? split_kernel<true>(ch, opt) : split_kernel<false>(ch, opt); }
 
 }  // namespace
 
@@ -286,13 +290,18 @@ bool glm_split_by_die(int ch, int64_t p, int G, int64_t n) { return glm_by_die(p
 
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups)
 {
-    KernelFn fn = split_kernel(ch, opt);
+    // (which of the exchanges a launch uses follows its mini-batches: glm_split_by_die)
     const size_t lds = glm_split_lds_bytes(ch);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    int per_cu = 0;
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), kSplitBlock, lds);
-    if (e != hipSuccess) return e;
+    int per_cu = 1 << 20;
+    hipError_t e;
+    for (const KernelFn fn : {split_kernel(ch, opt, false), split_kernel(ch, opt, true)}) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        int of_this = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&of_this, reinterpret_cast<const void*>(fn), kSplitBlock, lds);
+        if (e != hipSuccess) return e;
+        per_cu = std::min(per_cu, of_this);
+    }
     int dev = 0, cus = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
@@ -307,8 +316,7 @@ hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStr
     GlmArgs a = args;
     a.width = (args.p + 3) / 4 * 4;
     a.shift = a.width - args.p;
-    a.by_die = glm_split_by_die(ch, args.p, G, args.n);
-    hipExtLaunchKernelGGL(split_kernel(ch, opt), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, a);
+    hipExtLaunchKernelGGL(split_kernel(ch, opt, glm_split_by_die(ch, args.p, G, args.n)), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, a);
     return hipGetLastError();
 }
 
