@@ -129,7 +129,6 @@ struct GlmArgs {
     float* partial;         // [2][G][p] per-workgroup gradient sums (step-per-launch mode)
     unsigned long long* ll_part;   // [2][G][p] the same sums as flagged words {tag : float}, by step parity
     unsigned long long* ll_theta;  // [2][kThetaCopies][p] updated theta as flagged words (sliced reduction)
-    unsigned long long* ll_dies;   // [2][8][8][p] sums of the workgroups of a die as flagged words, by the die they go to and the one they are from
     unsigned* sync;         // [1] abort flag ([0] unused)
     unsigned tag_base;      // tag of step s is tag_base + (s - s_begin) + 1
     int s_begin, s_end;     // steps of this launch: s in [s_begin, s_end), s = pass * M + batch, all < 2^23
@@ -140,13 +139,16 @@ struct GlmArgs {
     int reduce_mode;
     float alpha;
     long long timeout_ticks;
-    int width, shift;       // positions of a row in shared memory, and how many of the last four stand for no column (filled in by
-                            //   the launches of the kernels that lay rows out so, glm_exchange.h)
     int single_step;        // >= 0: process only that step and stop after writing partial sums
     OptArgs opt;            // kind == kOptSgd: plain steps, no state.  Redundant reduction: every workgroup keeps a
                             // private copy of the state at m + blockIdx.x * pp (all copies stay identical)
     const float* lr_tab;    // optional learning rate per step: step s uses lr_tab[min(lr_base + s, lr_len - 1)]
     int lr_base, lr_len;
+    // What only the kernels with exchange wavefronts use stands last: between the others it moved the general kernel's arguments, whose loads and
+    // scalar registers the compiler then laid out 2 to 4 % slower (19.7 against 20.5 us per update at p = 1026, n = 300 on three workgroups).
+    unsigned long long* ll_dies;   // [2][8][8][p] sums of the workgroups of a die as flagged words, by the die they go to and the one they are from
+    int width, shift;       // positions of a row in shared memory, and how many of the last four stand for no column (filled in by
+                            //   the launches of the kernels that lay rows out so, glm_exchange.h)
 };
 
 // Whether the `lines` wavefronts of each workgroup that add up a line of 16 columns at a time can hold all lines (exchange_by_die).
