@@ -350,19 +350,24 @@ struct ExchangeCommon {
         return pair_slot_sum(v[0], PW);
     }
 
-    // this wavefront's share of the workgroup's sums of the columns below `cover`, as flagged words: what the others wait for
-    template <int SCOPE = kAgentScope>
+    // this wavefront's share of the workgroup's sums of the columns below `cover`, as flagged words: what the others wait for.  U: pairs a lane sends
+    // of sums that are one array, all read at once; stores beyond `cover` go to an address that the buffer's range check drops.  (As a loop over the
+    // columns that there are, unrolled in eights, the compiler waited for the stores of the odd turns before the others': 0.2 us per update at p = 4096.)
+    template <int SCOPE, int U>
     __device__ __forceinline__ void send_sums(__amdgpu_buffer_rsrc_t part, unsigned tag, int cover) const
     {
         auto send = [&](int c, f32x2 v) {
             __builtin_amdgcn_raw_buffer_store_b128(word_pair(v.x, v.y, tag), part, (unsigned)(((size_t)g * pp + c) * 8), 0, SCOPE);
         };
         asm volatile("" ::: "memory");
-        if constexpr (NSUM == 1) {                   // (their reads of shared memory go out together)
-#pragma unroll 8
-            for (int c0 = 128 * xw; c0 < cover; c0 += 128 * NX) {
-                const int c = c0 + 2 * lane;
-                if (c < cover) send(c, sum_of(c));
+        if constexpr (NSUM == 1) {
+            f32x2 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = *(const lds_f32x2*)(x.sums + min(2 * lane + 128 * (xw + NX * u), pp - 2));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int c = 2 * lane + 128 * (xw + NX * u);
+                __builtin_amdgcn_raw_buffer_store_b128(word_pair(v[u].x, v[u].y, tag), part, c < cover ? (unsigned)(((size_t)g * pp + c) * 8) : 0x7ffffff0u, 0, SCOPE);
             }
         } else {
             auto share = [&](auto pw) {
@@ -486,7 +491,7 @@ struct ExchangeCommon {
 // workgroups for the slice (the first one then adds the NX partial sums in their order and applies the update) and
 // collects a part of theta.  A wavefront pulls freshly written lines at a fraction of what a compute unit can take, so several on as
 // many SIMDs finish a trip sooner, beside row traffic too (glm_split_kernel.hip has both figures).
-// GATED: the row wavefronts wait for s_sent.  U1, U2: pairs of words a lane requests per trip when it sums the slice / collects theta.
+// GATED: the row wavefronts wait for s_sent.  U1, U2: pairs of words a lane requests per trip when it sums the slice / collects theta (sums that are one array: all of them).
 template <bool OPT, int NX, int NSUM, bool GATED, int U1, int U2>
 __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
 {
@@ -542,7 +547,7 @@ __device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const Excha
         // every exchange wavefront has delivered its part of the version that this step's update starts from.)
         dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
         // 0. this workgroup's sums out of shared memory
-        ex.send_sums(part, tag, p);
+        ex.template send_sums<kAgentScope, U2>(part, tag, p);
         if (GATED && early) ex.mark_sent();
 
         // 1. this workgroup's slice, if it has one: sum over all workgroups, in a fixed order; the update; the new
@@ -781,7 +786,7 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
 // It is the faster way as long as a wavefront has one line (up to 1024 floats), two or three: each line more is two trips one behind the other (4.20
 // against 3.32 at p = 200 on 24 workgroups, 16.3 against 3.7 at p = 1000 on 16; both lines in the same trips: 3.60 against 3.23 at p = 400 on 32,
 // 4.26 against 3.76 at p = 1000 on 64), which the callers' rule sees to (glm_by_die).
-// LW: lines a wavefront takes at a time.  U2: pairs of words a lane requests at a time when it collects theta.
+// LW: lines a wavefront takes at a time.  U2: pairs of words a lane requests at a time when it collects theta (sums that are one array: all of them).
 template <bool OPT, int NX, int NSUM, int LW, int U2>
 __device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
 {
@@ -831,8 +836,8 @@ __device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const Exchange
         const __amdgpu_buffer_rsrc_t dies = words_rsrc(a.ll_dies + (size_t)(s & 1) * 64 * pp, dies_bytes);
         const __amdgpu_buffer_rsrc_t mine = words_rsrc(a.ll_theta + ((size_t)(s & 1) * kThetaCopies + (size_t)die) * pp, (unsigned)(pp * 8));
         dead |= ex.template wait_ge<false>(x.s_published, (ver + 1u) * x.publishers);
-        if (near) ex.template send_sums<0>(part, tag, pp);
-        else ex.template send_sums<kAgentScope>(part, tag, pp);
+        if (near) ex.template send_sums<0, U2>(part, tag, pp);
+        else ex.template send_sums<kAgentScope, U2>(part, tag, pp);
         if (l0 >= lines) ex.mark_sent();
         for (int l = l0, k0 = 0; l < lines && dead == 0u; l += LW * dl, k0 += 8 * LW) {
             f32x2 r[LW];
