@@ -151,8 +151,9 @@ struct GlmArgs {
                             //   the launches of the kernels that lay rows out so, glm_exchange.h)
 };
 
-// Whether the `lines` wavefronts of each workgroup that add up a line of 16 columns at a time can hold all lines (exchange_by_die).
-inline bool glm_by_die(int64_t p, int G, int lines) { return G % 8 == 0 && (p + 15) / 16 <= (int64_t)(G / 8) * lines; }
+// Whether the `lines` wavefronts of each workgroup that add up a line of 16 columns at a time can hold all lines (exchange_by_die), and the
+// dies' sums, 1 KB for each of p rounded up to 16, the room they share with the sums of launched steps, 2 KB for each of p.
+inline bool glm_by_die(int64_t p, int G, int lines) { return p >= 8 && G % 8 == 0 && (p + 15) / 16 <= (int64_t)(G / 8) * lines; }
 
 // How the workgroups of a persistent launch exchange their sums, for a run with mini-batches of n rows.
 enum { kExchangeOneTrip = 0, kExchangeByDie = 1, kExchangeTwoTrips = 2 };

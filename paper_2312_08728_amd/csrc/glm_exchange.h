@@ -217,6 +217,14 @@ __device__ __forceinline__ f32x2 pair_slot_sum(f32x2 v, int PPc)
     }
     return v;
 }
+// The same for PW (2 .. 64) known when compiled.
+template <int PW>
+__device__ __forceinline__ f32x2 lane_groups_sum(f32x2 v)
+{
+    if constexpr (PW == 2) { v.x += dpp_mov<0x122>(v.x); v.y += dpp_mov<0x122>(v.y); }
+    if constexpr (PW <= 4) { v.x += dpp_mov<0x124>(v.x); v.y += dpp_mov<0x124>(v.y); }
+    return pair_slot_sum(v, PW <= 8 ? 8 : PW);
+}
 
 // The exchange wavefronts' view of the workgroup's shared memory.
 struct ExchangeLds {
@@ -347,7 +355,7 @@ struct ExchangeCommon {
 #pragma unroll
             for (int k = 0; k + w < J; k += 2 * w) { v[k].x += v[k + w].x; v[k].y += v[k + w].y; }
         }
-        return pair_slot_sum(v[0], PW);
+        return lane_groups_sum<PW>(v[0]);
     }
 
     // this wavefront's share of the workgroup's sums of the columns below `cover`, as flagged words: what the others wait for.  U: pairs a lane sends
@@ -733,6 +741,7 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
             // Load u of a lane takes the workgroup i + sg, i = i0 + SG u.  The last loads start at G - SG at most;
             // what they bring a second time (workgroups below i) is not added.
             f32x2 r = {0.f, 0.f};
+            const bool columns = 2 * PW * xw < ex.p;             // (does this wavefront have any?)
             auto trips = [&](auto count) {
                 constexpr int U = decltype(count)::value;
                 int i0 = 0;
@@ -752,11 +761,12 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
                     i0 += SG * U;
                 } while (i0 < G && dead == 0u);
             };
-            if (loads <= 1) trips(std::integral_constant<int, 1>{});
+            if (!columns) {}
+            else if (loads <= 1) trips(std::integral_constant<int, 1>{});
             else if (loads <= 2) trips(std::integral_constant<int, 2>{});
             else if (loads <= 4) trips(std::integral_constant<int, 4>{});
             else trips(std::integral_constant<int, 8>{});
-            t = pair_slot_sum(r, PW);
+            t = lane_groups_sum<PW>(r);
         }
         ex.apply(th_old, th_new, t, nb, scale, alpha_s, s - first);
         if (dead != 0u) ex.give_up();

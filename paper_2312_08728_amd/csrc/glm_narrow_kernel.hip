@@ -50,7 +50,7 @@ constexpr int narrow_block(int rw) { return 64 * (kXWaves + rw); }
 __device__ __forceinline__ float pick2(int k, float v0, float v1) { return k == 1 ? v1 : v0; }
 __device__ __forceinline__ float pick4(int k, float v0, float v1, float v2, float v3) { return (k & 2) != 0 ? pick2(k & 1, v2, v3) : pick2(k & 1, v0, v1); }
 
-// EX: how the sums are exchanged: in one trip, with so many pairs of columns to an exchange wavefront (8, 16, 32, 64), over two levels or in two
+// EX: how the sums are exchanged: in one trip, with so many pairs of columns to an exchange wavefront (2, 4, 8, ... 64), over two levels or in two
 // trips.  (A kernel each: the code of several in one needs more scalar registers than there are, and reads them back in the middle of
 // a step.)
 constexpr int kTwoTrips = 0, kByDie = 1;
@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     __shared__ unsigned s_published;                 // publications of row wavefronts, counted over all steps
     __shared__ unsigned s_xarrived[kXWaves], s_xconsumed;   // hand-over of partial sums between the exchange wavefronts
 
-    constexpr bool ONE = EX >= 8, kGated = ONE ? EX > 8 : EX == kByDie;   // (whether rows wait for s_sent)
+    constexpr bool ONE = EX >= 2, kGated = ONE ? EX > 8 : EX == kByDie;   // (whether rows wait for s_sent)
     constexpr int E = CPL * V;                       // floats of a row held per lane
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -266,8 +266,8 @@ using KernelFn = void (*)(GlmArgs);
 template <bool OPT, int RW, int EX, int V, int CPL, int PF>
 KernelFn pick()
 {
-    // (one trip: up to 8 EX columns, more than 4 EX of them)
-    constexpr bool fits = EX < 8 ? V == 4 : RW > kRowWaves && (EX == 64 ? V == 4 && CPL == 2 : CPL == 1 && (EX == 8 || V == 4));
+    // (one trip: up to 8 EX columns, more than 4 EX of them but where EX is the smallest)
+    constexpr bool fits = EX < 2 ? V == 4 : RW > kRowWaves && (EX == 64 ? V == 4 && CPL == 2 : CPL == 1 && (EX == 2 || V == 4));
     if constexpr (!narrow_shape_ok(V, CPL, PF, RW) || !fits) return nullptr;
     else return glm_narrow_kernel<V, CPL, PF, RW, EX, OPT>;
 }
@@ -309,7 +309,12 @@ KernelFn narrow_kernel_opt(const GlmLaunchShape& s, int ex)
     if (l.width > 256) return pick_row<OPT, kNarrowMoreRows, 64>(l.V, l.CPL, s.narrow_pf);
     if (l.width > 128) return pick_row<OPT, kNarrowMoreRows, 32>(l.V, l.CPL, s.narrow_pf);
     if (l.width > 64) return pick_row<OPT, kNarrowMoreRows, 16>(l.V, l.CPL, s.narrow_pf);
-    return pick_row<OPT, kNarrowMoreRows, 8>(l.V, l.CPL, s.narrow_pf);
+    // (Few columns: as few pairs a wavefront as give all four some, so that a lane asks for eight workgroups' words at most.  With eight pairs a
+    // wavefront for all of these, asked for by wavefronts without columns too: 2.9 against 2.3 us per update at p = 16 on 64 workgroups, 3.1 / 2.4 on 100, 3.2 / 2.3
+    // at p = 30 on 100.)
+    if (l.width > 32) return pick_row<OPT, kNarrowMoreRows, 8>(l.V, l.CPL, s.narrow_pf);
+    if (l.width > 16) return pick_row<OPT, kNarrowMoreRows, 4>(l.V, l.CPL, s.narrow_pf);
+    return pick_row<OPT, kNarrowMoreRows, 2>(l.V, l.CPL, s.narrow_pf);
 }
 
 // ex: of the sliced reduction, which of its exchanges

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import workloads as wl
-from gpu_util import gpu_run, oracle_run, rel_l2, coord_err
+from gpu_util import gpu_run, oracle_run, rel_l2, coord_err, row_plan, GENERAL, NARROW, SPLIT, ONE_TRIP, BY_DIE as OVER_DIES, TWO_TRIPS
 
 pytestmark = pytest.mark.gpu
 
@@ -173,6 +173,8 @@ def test_one_workgroup_is_chosen_for_the_chain_kernel_alone(p, n, launched):
 # (model, p, n, G, N0): sums added up over two levels, on the dies first.  A line of 16 columns belongs to one wavefront of one workgroup of each
 # die (four take part, three for rows of more than 1024 floats, which may have two lines), which asks for four workgroups' words a lane.
 BY_DIE = [
+    (wl.LINEAR, 9, 3000, 136, 7_000),        # one line; 17 workgroups a die
+    (wl.LOGISTIC, 16, 4000, 256, 9_000),     # a full line
     (wl.LOGISTIC, 20, 9000, 256, 20_000),    # two lines, the second of four columns; 32 workgroups a die
     (wl.LINEAR, 128, 900, 40, 3_000),        # 5 workgroups a die: fewer than a wavefront has groups of lanes
     (wl.LOGISTIC, 500, 700, 64, 2_000),      # 8 a die, 32 lines: every wavefront has one
@@ -257,3 +259,37 @@ def test_workgroups_chosen_for_rows_of_65_to_512_floats(p, n, G, threads):
     got, st = gpu_run(w, X, y, chain=B.BMGD_CHAIN_PERSISTENT)
     assert (st.n_workgroups, st.threads_per_group) == (G, threads)
     assert rel_l2(got, oracle_run(w, X, y)) <= TOL
+
+
+# (model, p, n, G, N0): one trip with few columns: two, four or eight pairs to an exchange wavefront, of which the last may have none, and up to
+# eight words a lane; beyond 128 workgroups nine to sixteen columns go over two levels.
+FEW_COLUMNS = [
+    (wl.LOGISTIC, 3, 900, 100, 2_000),     # two pairs: one wavefront has columns
+    (wl.LINEAR, 5, 2_000, 255, 4_500),     # three pairs: two; eight words a lane, the last loads repeat one workgroup
+    (wl.LOGISTIC, 8, 1_500, 200, 3_500),   # vectors of four
+    (wl.LINEAR, 13, 1_500, 128, 3_500),    # four words a lane; the last pair has no column but a place
+    (wl.LOGISTIC, 16, 600, 33, 1_500),     # two words a lane
+    (wl.LINEAR, 17, 1_200, 65, 3_000),     # four pairs: nine of them, three wavefronts
+    (wl.LOGISTIC, 32, 1_500, 128, 3_500),  # eight words a lane
+    (wl.LINEAR, 33, 1_000, 64, 2_500),     # eight pairs
+]
+
+
+@pytest.mark.parametrize("optimizer", [0, 1, 3])
+@pytest.mark.parametrize("model,p,n,G,N0", FEW_COLUMNS)
+def test_few_columns_on_many_workgroups(model, p, n, G, N0, optimizer):
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    w = _case(model, 2 * N0 - 77, p, N0, n, T=5, R=1, alpha=0.01 if optimizer == 3 else 0.05 if model == wl.LOGISTIC else 0.2 / (p + 10))
+    X, y = wl.dataset(w)
+    ref = O.BMGD(w.model, w.p, w.n, w.alpha, w.T)
+    if optimizer:
+        ref.set_optimizer(optimizer)
+    for k in range(2):
+        ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
+    assert row_plan(p, n, G, optimizer=optimizer)[:4] == (G, 1024, NARROW, ONE_TRIP)
+    got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
+    assert st.n_workgroups == G
+    assert rel_l2(got, ref.theta) <= TOL
+    again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
+    assert np.array_equal(got, again)

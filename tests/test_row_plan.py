@@ -2,7 +2,7 @@
 import pytest
 
 import paper_2312_08728_amd as B
-from gpu_util import row_plan
+from gpu_util import NARROW, ONE_TRIP, BY_DIE, row_plan
 
 
 @pytest.mark.parametrize("p,n,asked,G", [
@@ -13,3 +13,12 @@ from gpu_util import row_plan
 def test_steps_launched_one_by_one_do_not_follow_the_persistent_kernels_limits(p, n, asked, G):
     """The kernels of a persistent chain hold other numbers of rows, and take multiples of eight workgroups."""
     assert row_plan(p, n, asked, B.BMGD_CHAIN_LAUNCH)[:3] == (G, 512 if p > 512 and (p % 4 or p > 1024) else 1024, 0)
+
+
+@pytest.mark.parametrize("p,n,asked,G,exchange", [
+    (16, 600, 255, 248, BY_DIE), (9, 600, 136, 136, BY_DIE), (16, 600, 128, 128, ONE_TRIP), (8, 600, 255, 255, ONE_TRIP), (17, 600, 128, 128, ONE_TRIP),
+    (7, 600, 256, 256, ONE_TRIP),
+])
+def test_exchange_of_few_columns(p, n, asked, G, exchange):
+    plan = row_plan(p, n, asked)
+    assert plan[2:4] == (NARROW, exchange) and plan[0] == G
