@@ -225,7 +225,7 @@ bool valid_config(const bmgd_config& c, std::string* why)
     if (c.model != BMGD_SOFTMAX) {
         GlmLaunchShape s;
         char msg[160];
-        if (!glm_plan(c.p, c.batch_n, c.n_workgroups, kMaxGroups, c.chain != BMGD_CHAIN_LAUNCH, &s, msg, sizeof msg)) {
+        if (!glm_plan(c.p, c.batch_n, c.n_workgroups, kMaxGroups, c.chain != BMGD_CHAIN_LAUNCH, c.optimizer != BMGD_OPT_SGD, &s, msg, sizeof msg)) {
             *why = msg;
             return false;
         }
@@ -1210,7 +1210,7 @@ BMGD_API int bmgd_create_ex(const bmgd_config* cfg, bmgd_ctx** out)
         if (ctx->chain == BMGD_CHAIN_GRAPH && !ctx->sm_chain && !ctx->sm_pass) CREATE_TRY(hipStreamCreateWithFlags(&ctx->capture_stream, hipStreamNonBlocking));
     } else {
         char msg[160];
-        if (!glm_plan(cfg->p, cfg->batch_n, cfg->n_workgroups, ctx->num_cus, cfg->chain != BMGD_CHAIN_LAUNCH, &ctx->shape, msg, sizeof msg)) {
+        if (!glm_plan(cfg->p, cfg->batch_n, cfg->n_workgroups, ctx->num_cus, cfg->chain != BMGD_CHAIN_LAUNCH, cfg->optimizer != BMGD_OPT_SGD, &ctx->shape, msg, sizeof msg)) {
             ctx->err = msg;
             return bail(BMGD_EINVAL);
         }
@@ -1726,12 +1726,12 @@ BMGD_API void bmgd_destroy(bmgd_ctx* ctx) { destroy_ctx(ctx); }
 // Not part of the C interface: the launch shape of a row-form configuration with mini-batches of n rows, for a run whose mini-batches have run_n of them,
 // where nothing limits the workgroups but their number.  out: workgroups, threads of each, kernel (0 general, 1 rows of up to 1024 floats, 2 wider),
 // exchange (kExchangeOneTrip ...), rows per row slot and launch of the second kernel.
-BMGD_API int bmgd_internal_plan(int64_t p, int64_t n, int32_t n_workgroups, int32_t chain, int64_t run_n, int32_t out[5])
+BMGD_API int bmgd_internal_plan(int64_t p, int64_t n, int32_t n_workgroups, int32_t chain, int32_t optimizer, int64_t run_n, int32_t out[5])
 {
     GlmLaunchShape s;
     char msg[160];
     const bool persistent = chain != BMGD_CHAIN_LAUNCH;
-    if (!glm_plan(p, n, n_workgroups, kMaxGroups, persistent, &s, msg, sizeof msg)) return BMGD_EINVAL;
+    if (!glm_plan(p, n, n_workgroups, kMaxGroups, persistent, optimizer != BMGD_OPT_SGD, &s, msg, sizeof msg)) return BMGD_EINVAL;
     out[0] = s.G;
     out[1] = persistent ? s.chain_block : s.block;
     out[2] = !persistent ? 0 : s.split ? 2 : s.narrow;

@@ -160,8 +160,8 @@ enum { kExchangeOneTrip = 0, kExchangeByDie = 1, kExchangeTwoTrips = 2 };
 int glm_exchange(const GlmLaunchShape& shape, int64_t n);
 
 // Pick V/CPL/PF/L/block/G/reduce mode for a shape; returns false if p is outside the supported range.
-// persistent: for the chain's kernels (false: for one launch per step, by the general kernel).
-bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persistent, GlmLaunchShape* out, char* why, size_t why_len);
+// persistent: for the chain's kernels (false: for one launch per step, by the general kernel); with_state: for an update rule with state.
+bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persistent, bool with_state, GlmLaunchShape* out, char* why, size_t why_len);
 // Query co-residency and set attributes; fills shape->max_G and clamps shape->G.
 hipError_t glm_prepare(GlmLaunchShape* shape);
 // One launch of the persistent chain kernel covering steps [s_begin, s_end) of the buffer.

@@ -126,13 +126,13 @@ GENERAL, NARROW, SPLIT = 0, 1, 2                # kernels of the row form: the g
 ONE_TRIP, BY_DIE, TWO_TRIPS = 0, 1, 2           # how a launch's workgroups exchange their sums
 
 
-def row_plan(p, n, G=0, chain=1, run_n=None):
+def row_plan(p, n, G=0, chain=1, run_n=None, optimizer=0):
     """(workgroups, threads, kernel, exchange, rows per row slot) the library launches a row-form configuration as, for a run with
     mini-batches of run_n rows.  Host code only."""
     import ctypes
     import paper_2312_08728_amd as B
     out = (ctypes.c_int32 * 5)()
     f = ctypes.CDLL(B.LIB_PATH).bmgd_internal_plan
-    f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.POINTER(ctypes.c_int32)]
-    assert f(p, n, G, chain, n if run_n is None else run_n, out) == 0
+    f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.POINTER(ctypes.c_int32)]
+    assert f(p, n, G, chain, optimizer, n if run_n is None else run_n, out) == 0
     return tuple(out)

@@ -2,7 +2,7 @@
 import pytest
 
 import paper_2312_08728_amd as B
-from gpu_util import NARROW, ONE_TRIP, BY_DIE, row_plan
+from gpu_util import GENERAL, NARROW, SPLIT, ONE_TRIP, BY_DIE, row_plan
 
 
 @pytest.mark.parametrize("p,n,asked,G", [
@@ -13,6 +13,20 @@ from gpu_util import NARROW, ONE_TRIP, BY_DIE, row_plan
 def test_steps_launched_one_by_one_do_not_follow_the_persistent_kernels_limits(p, n, asked, G):
     """The kernels of a persistent chain hold other numbers of rows, and take multiples of eight workgroups."""
     assert row_plan(p, n, asked, B.BMGD_CHAIN_LAUNCH)[:3] == (G, 512 if p > 512 and (p % 4 or p > 1024) else 1024, 0)
+
+
+@pytest.mark.parametrize("p,n,asked,optimizer,G,kernel", [
+    (1026, 300, 8, 0, 8, GENERAL), (1026, 300, 12, 0, 12, GENERAL), (1030, 600, 16, 0, 16, GENERAL), (2046, 300, 8, 0, 8, GENERAL),
+    (1026, 96, 8, 0, 8, SPLIT), (1026, 97, 8, 0, 8, GENERAL), (1026, 192, 8, 3, 8, SPLIT), (1026, 193, 8, 3, 8, GENERAL),
+    (1502, 400, 16, 0, 16, SPLIT), (1502, 401, 16, 0, 16, GENERAL), (1502, 592, 16, 1, 16, SPLIT), (1502, 593, 16, 1, 16, GENERAL),
+    (1502, 7_165, 128, 0, 128, GENERAL), (1502, 12_000, 256, 0, 256, SPLIT), (1502, 600, 25, 0, 24, SPLIT), (1502, 600, 37, 0, 32, SPLIT),
+    (1500, 300, 8, 0, 8, SPLIT), (2048, 20_000, 64, 0, 64, SPLIT), (2500, 300, 8, 0, 8, SPLIT),      # multiples of four: as ever
+    (1502, 300, 7, 0, 7, GENERAL),
+])
+def test_wide_rows_that_are_no_multiple_of_four_take_the_kernel_that_is_faster(p, n, asked, optimizer, G, kernel):
+    """Many rows a workgroup: the general kernel, on the workgroups asked for."""
+    plan = row_plan(p, n, asked, optimizer=optimizer)
+    assert plan[0] == G and plan[2] == kernel
 
 
 @pytest.mark.parametrize("p,n,asked,G,exchange", [
