@@ -137,6 +137,7 @@ struct bmgd_ctx {
     int64_t swa_count = 0;
     float* opt_m = nullptr;
     float* opt_s = nullptr;
+    int test_far = 0;                                // (bmgd_internal_far)
     int64_t opt_k = 0;
     uint32_t tag_epoch = 0;                        // tags handed out so far for flagged-word exchanges
     GlmLaunchShape shape{};
@@ -902,6 +903,7 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
         a.single_step = -1;
         a.ll_part = ctx->ll_part;
         a.ll_theta = ctx->ll_theta;
+        a.far = ctx->test_far;
         a.ll_dies = reinterpret_cast<unsigned long long*>(ctx->partial);   // (sums as plain floats are for steps launched one by one)
         a.lr_tab = lr_len ? ctx->lr_tab_dev : nullptr;
         a.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
@@ -1723,20 +1725,44 @@ BMGD_API const char* bmgd_last_error(const bmgd_ctx* ctx)
 
 BMGD_API void bmgd_destroy(bmgd_ctx* ctx) { destroy_ctx(ctx); }
 
-// Not part of the C interface: the launch shape of a row-form configuration with mini-batches of n rows, for a run whose mini-batches have run_n of them,
-// where nothing limits the workgroups but their number.  out: workgroups, threads of each, kernel (0 general, 1 rows of up to 1024 floats, 2 wider),
-// exchange (kExchangeOneTrip ...), rows per row slot and launch of the second kernel.
+// Not part of the C interface, for tests.
+namespace {
+
+// workgroups, threads of each, kernel (0 general, 1 rows of up to 1024 floats, 2 wider), exchange (kExchangeOneTrip ...), rows per row slot and launch
+// of the second kernel
+void describe(const GlmLaunchShape& s, bool persistent, int64_t run_n, int32_t out[5])
+{
+    out[0] = s.G;
+    out[1] = persistent ? s.chain_block : s.block;
+    out[2] = !persistent ? 0 : s.split ? 2 : s.narrow;
+    out[3] = glm_exchange(s, run_n);
+    out[4] = persistent && s.narrow ? s.narrow_pf : 0;
+}
+
+}  // namespace
+
+// How a row-form configuration with mini-batches of n rows is launched, for a run whose mini-batches have run_n of them, where nothing limits the
+// workgroups but their number (host code only); and how a context's runs are.
 BMGD_API int bmgd_internal_plan(int64_t p, int64_t n, int32_t n_workgroups, int32_t chain, int32_t optimizer, int64_t run_n, int32_t out[5])
 {
     GlmLaunchShape s;
     char msg[160];
     const bool persistent = chain != BMGD_CHAIN_LAUNCH;
     if (!glm_plan(p, n, n_workgroups, kMaxGroups, persistent, optimizer != BMGD_OPT_SGD, &s, msg, sizeof msg)) return BMGD_EINVAL;
-    out[0] = s.G;
-    out[1] = persistent ? s.chain_block : s.block;
-    out[2] = !persistent ? 0 : s.split ? 2 : s.narrow;
-    out[3] = glm_exchange(s, run_n);
-    out[4] = persistent && s.narrow ? s.narrow_pf : 0;
+    describe(s, persistent, run_n, out);
+    return BMGD_OK;
+}
+BMGD_API int bmgd_internal_launched(const bmgd_ctx* ctx, int64_t run_n, int32_t out[5])
+{
+    if (!ctx || ctx->cfg.model == BMGD_SOFTMAX) return BMGD_EINVAL;
+    describe(ctx->shape, ctx->chain != BMGD_CHAIN_LAUNCH, run_n, out);
+    return BMGD_OK;
+}
+// The context's runs take the workgroups of a die to be on several (exchange_by_die).
+BMGD_API int bmgd_internal_far(bmgd_ctx* ctx)
+{
+    if (!ctx) return BMGD_EINVAL;
+    ctx->test_far = 1;
     return BMGD_OK;
 }
 

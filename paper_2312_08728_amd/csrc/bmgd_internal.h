@@ -147,6 +147,7 @@ struct GlmArgs {
     // What only the kernels with exchange wavefronts use stands last: between the others it moved the general kernel's arguments, whose loads and
     // scalar registers the compiler then laid out 2 to 4 % slower (19.7 against 20.5 us per update at p = 1026, n = 300 on three workgroups).
     unsigned long long* ll_dies;   // [2][8][8][p] sums of the workgroups of a die as flagged words, by the die they go to and the one they are from
+    int far;                // 1: the two-level exchange takes the workgroups of a die to be on several (tests)
     int width, shift;       // positions of a row in shared memory, and how many of the last four stand for no column (filled in by
                             //   the launches of the kernels that lay rows out so, glm_exchange.h)
 };

@@ -838,7 +838,7 @@ __device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const Exchange
         u32x4 w[1];
         const unsigned from = (unsigned)(8 * min(lane, G_die - 1) + die) * (unsigned)(pp * 8);
         dead |= ex.poll(tag, w, [&](int) { return __builtin_amdgcn_raw_buffer_load_b128(rows, from, 0u, kAgentScope); }, [&](const u32x4& v, int) { return v.y; });
-        near = __builtin_amdgcn_ballot_w64(w[0].x != xcc) == 0ull;
+        near = a.far == 0 && __builtin_amdgcn_ballot_w64(w[0].x != xcc) == 0ull;
     }
     int s = first;
 #pragma clang loop unroll(disable)

@@ -1,6 +1,8 @@
 """Helpers shared by the GPU parity tests: drive libbmgd through its C ABI and the oracle on the same bytes."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 
 import workloads as wl
@@ -12,12 +14,13 @@ def rel_l2(a, b) -> float:
     return float(np.linalg.norm(a - b) / max(np.linalg.norm(b), 1e-300))
 
 
-def gpu_run(w: wl.Workload, X: np.ndarray, y: np.ndarray, R=None, resident=False, theta0=None, **opts):
+def gpu_run(w: wl.Workload, X: np.ndarray, y: np.ndarray, R=None, resident=False, theta0=None, far=False, **opts):
     """Run workload w on the GPU: R iterations over the K contiguous buffers of (X, y).
 
     resident=False goes through bmgd_load_buffer_async (pinned host memory, a copy stream and a compute
     stream); resident=True puts the data in device memory first and uses bmgd_run_device_buffer.
-    Returns (theta, stats).
+    far: sums over two levels as if the workgroups of a die were on several.
+    Returns (theta, stats); stats.launched is (workgroups, threads, kernel, exchange, rows per row slot) of a row-form run.
     """
     import torch
     import paper_2312_08728_amd as B
@@ -28,6 +31,8 @@ def gpu_run(w: wl.Workload, X: np.ndarray, y: np.ndarray, R=None, resident=False
     ctx = B.Context(w.p, min(w.N0, N), min(w.n, min(w.N0, N)), w.alpha, w.T, model=w.model, n_classes=w.C,
                     seed=w.seed, n_buffers=K, **opts)
     try:
+        if far:
+            assert B.lib.bmgd_internal_far(ctypes.c_void_p(ctx.h)) == 0
         if theta0 is not None:
             ctx.set_theta(theta0)
         xt = torch.from_numpy(X.view(np.int16) if X.dtype == np.uint16 else X)
@@ -49,6 +54,7 @@ def gpu_run(w: wl.Workload, X: np.ndarray, y: np.ndarray, R=None, resident=False
                     ctx.run_buffer(ks)
         theta = ctx.get_theta()
         st = ctx.stats()
+        st.launched = None if w.model == wl.SOFTMAX else launched(ctx, min(w.n, w.N0, N))
         return theta, st
     finally:
         ctx.close()
@@ -126,13 +132,22 @@ GENERAL, NARROW, SPLIT = 0, 1, 2                # kernels of the row form: the g
 ONE_TRIP, BY_DIE, TWO_TRIPS = 0, 1, 2           # how a launch's workgroups exchange their sums
 
 
+def launched(ctx, run_n):
+    """(workgroups, threads, kernel, exchange, rows per row slot) of a context's runs with mini-batches of run_n rows."""
+    import paper_2312_08728_amd as B
+    out = (ctypes.c_int32 * 5)()
+    f = B.lib.bmgd_internal_launched
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.POINTER(ctypes.c_int32)]
+    assert f(ctx.h, run_n, out) == 0
+    return tuple(out)
+
+
 def row_plan(p, n, G=0, chain=1, run_n=None, optimizer=0):
     """(workgroups, threads, kernel, exchange, rows per row slot) the library launches a row-form configuration as, for a run with
     mini-batches of run_n rows.  Host code only."""
-    import ctypes
     import paper_2312_08728_amd as B
     out = (ctypes.c_int32 * 5)()
-    f = ctypes.CDLL(B.LIB_PATH).bmgd_internal_plan
+    f = B.lib.bmgd_internal_plan
     f.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_int64, ctypes.POINTER(ctypes.c_int32)]
     assert f(p, n, G, chain, optimizer, n if run_n is None else run_n, out) == 0
     return tuple(out)

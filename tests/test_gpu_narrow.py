@@ -4,12 +4,13 @@ import numpy as np
 import pytest
 
 import workloads as wl
-from gpu_util import gpu_run, oracle_run, rel_l2, coord_err, row_plan, GENERAL, NARROW, SPLIT, ONE_TRIP, BY_DIE as OVER_DIES, TWO_TRIPS
+import gpu_util as U
+from gpu_util import gpu_run, oracle_run, rel_l2, coord_err
 
 pytestmark = pytest.mark.gpu
 
 TOL = 1e-4
-NARROW_THREADS = 768          # 12 wavefronts: what tells this kernel from the others in the statistics
+NARROW_THREADS = 768          # 12 wavefronts
 
 
 def _case(model, N, p, N0, n, T, R, alpha):
@@ -39,6 +40,7 @@ def test_register_shapes_against_the_oracle(model, p, n, G, N0):
     want = oracle_run(w, X, y)
     got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT)
     assert st.threads_per_group == NARROW_THREADS and st.n_workgroups == G, (st.threads_per_group, st.n_workgroups)
+    assert st.launched[2:4] == (U.NARROW, U.TWO_TRIPS if G <= 24 else U.BY_DIE)
     assert st.steps == w.steps
     assert rel_l2(got, want) <= TOL and coord_err(got, want) <= 10 * TOL
 
@@ -73,18 +75,22 @@ def test_is_reproducible_and_equals_the_loader_path():
 
 
 def test_other_kernels_keep_their_cases():
-    """Few workgroups, sums small enough for every workgroup to add up itself, odd p, a step that does not fit the
-    registers: the general kernel (1024 threads)."""
+    """Few workgroups or sums few enough for every workgroup to add up itself: one trip; odd p: twelve row wavefronts; steps that do not fit
+    the registers, and wide rows on few workgroups: the general kernel.  (1024 threads, 512 for the last.)"""
     import paper_2312_08728_amd as B
-    for kw, p, n, N0 in ((dict(n_workgroups=4), 200, 1000, 4000),          # fewer than eight workgroups
-                         (dict(n_workgroups=16), 100, 1000, 4000),         # 16 * 100 words: one trip, redundant sums
-                         (dict(n_workgroups=64), 201, 1000, 4000),         # odd p
-                         (dict(n_workgroups=8), 200, 4096, 9000)):         # 64 slots: 64 rows per slot
+    for kw, p, n, N0, launched in ((dict(n_workgroups=4), 200, 1000, 4000, (U.GENERAL, U.ONE_TRIP)),      # 1000 rows on 48 row slots
+                                   (dict(n_workgroups=4), 200, 130, 1000, (U.NARROW, U.ONE_TRIP)),        # fewer than eight workgroups
+                                   (dict(n_workgroups=16), 100, 1000, 4000, (U.NARROW, U.ONE_TRIP)),      # 16 * 100 words
+                                   (dict(n_workgroups=64), 201, 1000, 4000, (U.NARROW, U.BY_DIE)),        # odd p
+                                   (dict(n_workgroups=8), 200, 4096, 9000, (U.GENERAL, U.ONE_TRIP)),      # 64 slots: 64 rows per slot
+                                   (dict(n_workgroups=32), 200, 4096, 9000, (U.GENERAL, U.TWO_TRIPS)),
+                                   (dict(n_workgroups=8), 1026, 300, 700, (U.GENERAL, U.TWO_TRIPS))):     # 38 rows of more than 1024 floats each
         w = _case(wl.LINEAR, 2 * N0, p, N0, n, T=2, R=1, alpha=0.5 / (p + 10))
         X, y = wl.dataset(w)
         want = oracle_run(w, X, y)
         got, st = gpu_run(w, X, y, chain=B.BMGD_CHAIN_PERSISTENT, **kw)
-        assert st.threads_per_group == 1024, (kw, p, st.threads_per_group)
+        assert st.threads_per_group == (1024 if p <= 1024 else 512), (kw, p, st.threads_per_group)
+        assert st.launched[2:4] == launched, (kw, p, st.launched)
         assert rel_l2(got, want) <= TOL
 
 
@@ -115,25 +121,24 @@ def test_more_passes_than_one_launch_holds_and_a_rate_per_update():
 
 
 # (model, p, n, G, N0): the form with one trip over the fabric per step (G p <= 4096: twelve row wavefronts, 1024 threads), and odd rows
-# in two trips.  Columns travel as pairs, in chunks of 64 pairs split over four exchange wavefronts; 64 / (pairs, 8 to 64) workgroups
-# side by side.
+# over two levels.  Columns travel as pairs, 2 to 64 of them to an exchange wavefront, and 64 / (pairs) workgroups side by side.
 ONE_TRIP = [
     (wl.LOGISTIC, 1, 40, 1, 500),        # one column, one workgroup: no exchange
-    (wl.LOGISTIC, 2, 300, 3, 1_000),     # one pair; fewer workgroups than lane groups (8)
-    (wl.LINEAR, 15, 500, 7, 1_700),      # eight pairs, the last one half; 7 of 8 lane groups
-    (wl.LOGISTIC, 16, 900, 9, 2_000),    # 9 workgroups in groups of 8: the second load repeats seven
-    (wl.LINEAR, 17, 2000, 33, 5_000),    # 16 lanes per pair row; odd G
-    (wl.LOGISTIC, 64, 700, 11, 2_100),   # 32 pairs, two lane groups
-    (wl.LINEAR, 65, 1200, 63, 3_000),    # 33 pairs in a chunk of 64; 16 loads per lane, in two rounds
-    (wl.LOGISTIC, 123, 777, 32, 3_000),  # V 1, CPL 2, PF 3
-    (wl.LOGISTIC, 128, 1024, 32, 3_000), # a full chunk
-    (wl.LINEAR, 129, 600, 31, 2_000),    # two chunks, the second of one half pair: two wavefronts each
-    (wl.LOGISTIC, 255, 300, 16, 1_000),  # V 1, CPL 4
-    (wl.LINEAR, 256, 350, 16, 1_000),    # two full chunks
-    (wl.LOGISTIC, 258, 200, 15, 700),    # three chunks: one wavefront each, the last with nothing
+    (wl.LOGISTIC, 2, 300, 3, 1_000),     # one pair; fewer workgroups than lane groups (32)
+    (wl.LINEAR, 15, 500, 7, 1_700),      # eight pairs, one with a place that stands for no column; 7 of 32 lane groups
+    (wl.LOGISTIC, 16, 900, 9, 2_000),    # eight pairs, two to a wavefront
+    (wl.LINEAR, 17, 2000, 33, 5_000),    # four pairs to a wavefront, 16 lane groups: the third load repeats fifteen; odd G
+    (wl.LOGISTIC, 64, 700, 11, 2_100),   # 32 pairs, eight lane groups: the second load repeats five
+    (wl.LINEAR, 65, 1200, 63, 3_000),    # 34 pairs, sixteen to a wavefront; 16 loads per lane, in two rounds
+    (wl.LOGISTIC, 123, 777, 32, 3_000),  # 62 pairs
+    (wl.LOGISTIC, 128, 1024, 32, 3_000), # 64: sixteen to each wavefront
+    (wl.LINEAR, 129, 600, 31, 2_000),    # 66, 32 to a wavefront: the third has two, the last none
+    (wl.LOGISTIC, 255, 300, 16, 1_000),  # 128, one with a place that stands for no column
+    (wl.LINEAR, 256, 350, 16, 1_000),    # 32 to each wavefront
+    (wl.LOGISTIC, 258, 200, 15, 700),    # 130, 64 to a wavefront: the third has two, the last none
     (wl.LOGISTIC, 512, 90, 8, 400),      # the widest rows
-    (wl.LOGISTIC, 201, 1500, 64, 4_000), # odd rows in two trips
-    (wl.LINEAR, 33, 4000, 128, 9_000),   # odd rows in two trips, two rows side by side in a wavefront
+    (wl.LOGISTIC, 201, 1500, 64, 4_000), # odd rows over two levels
+    (wl.LINEAR, 33, 4000, 128, 9_000),   # odd rows over two levels, four rows side by side in a wavefront
 ]
 
 
@@ -152,6 +157,7 @@ def test_one_trip_and_odd_rows_against_the_oracle(model, p, n, G, N0, optimizer)
         ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
     got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
     assert st.threads_per_group == 1024 and st.n_workgroups == G, (st.threads_per_group, st.n_workgroups)
+    assert st.launched[2:4] == (U.NARROW, U.ONE_TRIP if G * p <= 4096 else U.BY_DIE)
     assert rel_l2(got, ref.theta) <= TOL
     again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
     assert np.array_equal(got, again)
@@ -173,7 +179,7 @@ def test_one_workgroup_is_chosen_for_the_chain_kernel_alone(p, n, launched):
 # (model, p, n, G, N0): sums added up over two levels, on the dies first.  A line of 16 columns belongs to one wavefront of one workgroup of each
 # die (four take part, three for rows of more than 1024 floats, which may have two lines), which asks for four workgroups' words a lane.
 BY_DIE = [
-    (wl.LINEAR, 9, 3000, 136, 7_000),        # one line; 17 workgroups a die
+    (wl.LINEAR, 10, 3000, 136, 7_000),       # one line; 17 workgroups a die
     (wl.LOGISTIC, 16, 4000, 256, 9_000),     # a full line
     (wl.LOGISTIC, 20, 9000, 256, 20_000),    # two lines, the second of four columns; 32 workgroups a die
     (wl.LINEAR, 128, 900, 40, 3_000),        # 5 workgroups a die: fewer than a wavefront has groups of lanes
@@ -202,10 +208,43 @@ def test_sums_added_up_on_the_dies_first(model, p, n, G, N0, optimizer):
     for k in range(2):
         ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
     got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
-    assert st.threads_per_group == (704 if p > 1024 else NARROW_THREADS) and st.n_workgroups == G
+    assert st.launched[:4] == (G, *((704, U.SPLIT) if p > 1024 else (NARROW_THREADS, U.NARROW)), U.BY_DIE)
     assert rel_l2(got, ref.theta) <= TOL
     again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
     assert np.array_equal(got, again)
+    # words at device scope, as where the workgroups of a die are on several: the same sums in the same order
+    far, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, far=True)
+    assert np.array_equal(got, far)
+
+
+# (p, batch, G, rows of the short buffer): mini-batches of a full buffer in two trips, a short one's over two levels
+BOTH = [(1030, 1_200, 96, 1_000), (2044, 2_200, 176, 2_100), (3000, 600, 256, 500)]
+
+
+@pytest.mark.parametrize("optimizer", [0, 1, 3])
+@pytest.mark.parametrize("p,n,G,short", BOTH)
+def test_runs_of_a_context_that_exchange_in_both_ways(p, n, G, short, optimizer):
+    """Tags, words, theta and the state of an update rule go from one to the other and back."""
+    import torch
+    import paper_2312_08728_amd as B
+    from oracle import bmgd as O
+    N0 = 2 * n + 77
+    w = _case(wl.LOGISTIC, 3 * N0, p, N0, n, T=2, R=1, alpha=0.01 if optimizer == 3 else 0.05)
+    X, y = wl.dataset(w)
+    ref = O.BMGD(w.model, w.p, w.n, w.alpha, w.T)
+    if optimizer:
+        ref.set_optimizer(optimizer)
+    ctx = B.Context(w.p, w.N0, w.n, w.alpha, w.T, model=w.model, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
+    s = torch.cuda.Stream()
+    assert U.launched(ctx, n)[:4] == (G, 704, U.SPLIT, U.TWO_TRIPS) and U.launched(ctx, short)[3] == U.BY_DIE
+    for k, rows in enumerate((N0, short, N0, short, short)):
+        lo = k % 3 * N0
+        xb, yb = np.ascontiguousarray(X[lo:lo + rows]), np.ascontiguousarray(y[lo:lo + rows])
+        ref.run_buffer(xb, yb)
+        xd, yd = torch.from_numpy(xb).cuda(), torch.from_numpy(yb).cuda()
+        ctx.run_device_buffer(xd, yd, rows, s)
+        assert rel_l2(ctx.get_theta(), ref.theta) <= TOL, (k, rows)
+    ctx.close()
 
 
 # (model, p, n, G, N0): rows whose length is no multiple of four floats, taken as vectors of four of which the last starts four columns before
@@ -243,7 +282,8 @@ def test_rows_of_any_length(model, p, n, G, N0, optimizer):
     for k in range(2):
         ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
     got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
-    assert st.threads_per_group == (704 if p > 1024 else 1024 if G * p <= 4096 else NARROW_THREADS) and st.n_workgroups == G
+    assert st.launched[:3] == (G, *((704, U.SPLIT) if p > 1024 else (1024 if G * p <= 4096 else NARROW_THREADS, U.NARROW)))
+    assert st.launched[3] == (U.ONE_TRIP if G * p <= 4096 else U.TWO_TRIPS if p in (1022, 1026) else U.BY_DIE)
     assert rel_l2(got, ref.theta) <= TOL and coord_err(got, ref.theta) <= 10 * TOL
     again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
     assert np.array_equal(got, again)
@@ -257,7 +297,8 @@ def test_workgroups_chosen_for_rows_of_65_to_512_floats(p, n, G, threads):
     w = _case(wl.LOGISTIC, 4 * n, p, 2 * n + 5, n, T=2, R=1, alpha=0.05)
     X, y = wl.dataset(w)
     got, st = gpu_run(w, X, y, chain=B.BMGD_CHAIN_PERSISTENT)
-    assert (st.n_workgroups, st.threads_per_group) == (G, threads)
+    assert (st.n_workgroups, st.threads_per_group, st.launched[2]) == (G, threads, U.NARROW)
+    assert st.launched[3] == (U.ONE_TRIP if threads == 1024 else U.TWO_TRIPS if p == 300 else U.BY_DIE)
     assert rel_l2(got, oracle_run(w, X, y)) <= TOL
 
 
@@ -287,9 +328,8 @@ def test_few_columns_on_many_workgroups(model, p, n, G, N0, optimizer):
         ref.set_optimizer(optimizer)
     for k in range(2):
         ref.run_buffer(X[k * N0:(k + 1) * N0], y[k * N0:(k + 1) * N0])
-    assert row_plan(p, n, G, optimizer=optimizer)[:4] == (G, 1024, NARROW, ONE_TRIP)
     got, st = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer)
-    assert st.n_workgroups == G
+    assert st.launched[:4] == (G, 1024, U.NARROW, U.ONE_TRIP)
     assert rel_l2(got, ref.theta) <= TOL
     again, _ = gpu_run(w, X, y, n_workgroups=G, chain=B.BMGD_CHAIN_PERSISTENT, optimizer=optimizer, resident=True)
     assert np.array_equal(got, again)
