@@ -727,9 +727,9 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
             G = p > 128 && rows_held(kNarrowMoreRows, few / 2) > 0 && rows_held(kNarrowMoreRows, few / 2) <= 2 ? few / 2 : few;
         else if (G > 32 && 32 * p <= kRedundantMaxWords && held > 0 && held <= 4) G = 32;
     }
-    // Nine to 16 columns on more than 128 workgroups: sums over two levels, as with more columns (2.7 us per update, 3.0 with Adam, at p = 16 on 160 to 256; one
+    // Nine to 16 columns on more than 128 workgroups (in eights, if so many were asked for): sums over two levels, as with more columns (2.7 us per update, 3.0 with Adam, at p = 16 on 160 to 256; one
     // trip 3.3 to 3.4 and 4.4 to 4.5, as every wavefront's requests are for a quarter of each line that they touch).
-    const bool few_sums = (int64_t)G * p <= kRedundantMaxWords && !(persistent && p > 8 && p <= 16 && G > 128 && rows_held(8, G & ~7) > 0);
+    const bool few_sums = (int64_t)G * p <= kRedundantMaxWords && !(persistent && p > 8 && p <= 16 && G > 128 && (requested_G <= 0 || G % 8 == 0) && rows_held(8, G & ~7) > 0);
     if (few_sums ? p <= kNarrowOneTripMaxP : G >= 8) {
         const int Gn = few_sums ? G : G & ~7;
         int rw = few_sums || (p % 2 != 0 && p <= 256) ? kNarrowMoreRows : 8;

@@ -313,7 +313,8 @@ KernelFn narrow_kernel_opt(const GlmLaunchShape& s, int ex)
     // wavefront for all of these, asked for by wavefronts without columns too: 2.9 against 2.3 us per update at p = 16 on 64 workgroups, 3.1 / 2.4 on 100, 3.2 / 2.3
     // at p = 30 on 100.)
     if (l.width > 32) return pick_row<OPT, kNarrowMoreRows, 8>(l.V, l.CPL, s.narrow_pf);
-    if (l.width > 16) return pick_row<OPT, kNarrowMoreRows, 4>(l.V, l.CPL, s.narrow_pf);
+    // (With state and eight words a lane four pairs: 3.9 against 4.2 to 4.6 at p = 16 on 129 to 255 workgroups.)
+    if (l.width > 16 || (OPT && l.width > 8 && s.G > 128)) return pick_row<OPT, kNarrowMoreRows, 4>(l.V, l.CPL, s.narrow_pf);
     return pick_row<OPT, kNarrowMoreRows, 2>(l.V, l.CPL, s.narrow_pf);
 }
 

@@ -308,6 +308,7 @@ FEW_COLUMNS = [
     (wl.LOGISTIC, 3, 900, 100, 2_000),     # two pairs: one wavefront has columns
     (wl.LINEAR, 5, 2_000, 255, 4_500),     # three pairs: two; eight words a lane, the last loads repeat one workgroup
     (wl.LOGISTIC, 8, 1_500, 200, 3_500),   # vectors of four
+    (wl.LOGISTIC, 11, 1_200, 131, 2_500),  # eight words a lane; with state four pairs a wavefront, in two rounds
     (wl.LINEAR, 13, 1_500, 128, 3_500),    # four words a lane; the last pair has no column but a place
     (wl.LOGISTIC, 16, 600, 33, 1_500),     # two words a lane
     (wl.LINEAR, 17, 1_200, 65, 3_000),     # four pairs: nine of them, three wavefronts

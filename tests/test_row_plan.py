@@ -30,7 +30,7 @@ def test_wide_rows_that_are_no_multiple_of_four_take_the_kernel_that_is_faster(p
 
 
 @pytest.mark.parametrize("p,n,asked,G,exchange", [
-    (16, 600, 255, 248, BY_DIE), (9, 600, 136, 136, BY_DIE), (16, 600, 128, 128, ONE_TRIP), (8, 600, 255, 255, ONE_TRIP), (17, 600, 128, 128, ONE_TRIP),
+    (16, 600, 255, 255, ONE_TRIP), (16, 600, 248, 248, BY_DIE), (16, 40_000, 0, 208, BY_DIE), (9, 600, 136, 136, BY_DIE), (16, 600, 128, 128, ONE_TRIP), (8, 600, 255, 255, ONE_TRIP), (17, 600, 128, 128, ONE_TRIP),
     (7, 600, 256, 256, ONE_TRIP),
 ])
 def test_exchange_of_few_columns(p, n, asked, G, exchange):
