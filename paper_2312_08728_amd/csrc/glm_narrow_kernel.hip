@@ -266,8 +266,8 @@ using KernelFn = void (*)(GlmArgs);
 template <bool OPT, int RW, int EX, int V, int CPL, int PF>
 KernelFn pick()
 {
-    // (one trip: up to 8 EX columns, more than 4 EX of them but where EX is the smallest)
-    constexpr bool fits = EX < 2 ? V == 4 : RW > kRowWaves && (EX == 64 ? V == 4 && CPL == 2 : CPL == 1 && (EX == 2 || V == 4));
+    // (one trip: up to 8 EX columns; rows of fewer than eight floats have two or eight pairs)
+    constexpr bool fits = EX < 2 ? V == 4 : RW > kRowWaves && (EX == 64 ? V == 4 && CPL == 2 : CPL == 1 && (EX == 2 || EX == 8 || V == 4));
     if constexpr (!narrow_shape_ok(V, CPL, PF, RW) || !fits) return nullptr;
     else return glm_narrow_kernel<V, CPL, PF, RW, EX, OPT>;
 }
@@ -309,11 +309,10 @@ KernelFn narrow_kernel_opt(const GlmLaunchShape& s, int ex)
     if (l.width > 256) return pick_row<OPT, kNarrowMoreRows, 64>(l.V, l.CPL, s.narrow_pf);
     if (l.width > 128) return pick_row<OPT, kNarrowMoreRows, 32>(l.V, l.CPL, s.narrow_pf);
     if (l.width > 64) return pick_row<OPT, kNarrowMoreRows, 16>(l.V, l.CPL, s.narrow_pf);
-    // (Few columns: as few pairs a wavefront as give all four some, so that a lane asks for eight workgroups' words at most.  With eight pairs a
-    // wavefront for all of these, asked for by wavefronts without columns too: 2.9 against 2.3 us per update at p = 16 on 64 workgroups, 3.1 / 2.4 on 100, 3.2 / 2.3
-    // at p = 30 on 100.)
-    if (l.width > 32) return pick_row<OPT, kNarrowMoreRows, 8>(l.V, l.CPL, s.narrow_pf);
-    // (With state and eight words a lane four pairs: 3.9 against 4.2 to 4.6 at p = 16 on 129 to 255 workgroups.)
+    // Few columns, by more than 64 workgroups: as few pairs a wavefront as give all four some, so that a lane asks for eight workgroups' words at most.  us per
+    // update with eight pairs a wavefront / so: 3.15 / 2.4 at p = 16 on 100, 3.2 / 2.3 at p = 30 on 100; but 2.1 / 2.3 and 2.15 / 2.35 on 32, 2.45 / 2.6 at p = 16 on 64.  (With state
+    // and eight words a lane four pairs: 3.9 against 4.2 to 4.6 with two at p = 16 on 129 to 255.)
+    if (l.width > 32 || s.G <= 64) return pick_row<OPT, kNarrowMoreRows, 8>(l.V, l.CPL, s.narrow_pf);
     if (l.width > 16 || (OPT && l.width > 8 && s.G > 128)) return pick_row<OPT, kNarrowMoreRows, 4>(l.V, l.CPL, s.narrow_pf);
     return pick_row<OPT, kNarrowMoreRows, 2>(l.V, l.CPL, s.narrow_pf);
 }

@@ -121,13 +121,13 @@ def test_more_passes_than_one_launch_holds_and_a_rate_per_update():
 
 
 # (model, p, n, G, N0): the form with one trip over the fabric per step (G p <= 4096: twelve row wavefronts, 1024 threads), and odd rows
-# over two levels.  Columns travel as pairs, 2 to 64 of them to an exchange wavefront, and 64 / (pairs) workgroups side by side.
+# over two levels.  Columns travel as pairs, 8 to 64 of them to an exchange wavefront, and 64 / (pairs) workgroups side by side.
 ONE_TRIP = [
     (wl.LOGISTIC, 1, 40, 1, 500),        # one column, one workgroup: no exchange
-    (wl.LOGISTIC, 2, 300, 3, 1_000),     # one pair; fewer workgroups than lane groups (32)
-    (wl.LINEAR, 15, 500, 7, 1_700),      # eight pairs, one with a place that stands for no column; 7 of 32 lane groups
-    (wl.LOGISTIC, 16, 900, 9, 2_000),    # eight pairs, two to a wavefront
-    (wl.LINEAR, 17, 2000, 33, 5_000),    # four pairs to a wavefront, 16 lane groups: the third load repeats fifteen; odd G
+    (wl.LOGISTIC, 2, 300, 3, 1_000),     # one pair; fewer workgroups than lane groups (8)
+    (wl.LINEAR, 15, 500, 7, 1_700),      # eight pairs, one with a place that stands for no column; 7 of 8 lane groups
+    (wl.LOGISTIC, 16, 900, 9, 2_000),    # 9 workgroups in groups of 8: the second load repeats seven
+    (wl.LINEAR, 17, 2000, 33, 5_000),    # two wavefronts have columns; five loads a lane, the last repeats seven workgroups; odd G
     (wl.LOGISTIC, 64, 700, 11, 2_100),   # 32 pairs, eight lane groups: the second load repeats five
     (wl.LINEAR, 65, 1200, 63, 3_000),    # 34 pairs, sixteen to a wavefront; 16 loads per lane, in two rounds
     (wl.LOGISTIC, 123, 777, 32, 3_000),  # 62 pairs
@@ -302,18 +302,19 @@ def test_workgroups_chosen_for_rows_of_65_to_512_floats(p, n, G, threads):
     assert rel_l2(got, oracle_run(w, X, y)) <= TOL
 
 
-# (model, p, n, G, N0): one trip with few columns: two, four or eight pairs to an exchange wavefront, of which the last may have none, and up to
-# eight words a lane; beyond 128 workgroups nine to sixteen columns go over two levels.
+# (model, p, n, G, N0): one trip with few columns on more than 64 workgroups: two or four pairs to an exchange wavefront, of which the last may have
+# none, and up to eight words a lane; beyond 128 workgroups nine to sixteen columns go over two levels if the workgroups are whole eights.
 FEW_COLUMNS = [
     (wl.LOGISTIC, 3, 900, 100, 2_000),     # two pairs: one wavefront has columns
     (wl.LINEAR, 5, 2_000, 255, 4_500),     # three pairs: two; eight words a lane, the last loads repeat one workgroup
     (wl.LOGISTIC, 8, 1_500, 200, 3_500),   # vectors of four
     (wl.LOGISTIC, 11, 1_200, 131, 2_500),  # eight words a lane; with state four pairs a wavefront, in two rounds
     (wl.LINEAR, 13, 1_500, 128, 3_500),    # four words a lane; the last pair has no column but a place
-    (wl.LOGISTIC, 16, 600, 33, 1_500),     # two words a lane
+    (wl.LOGISTIC, 16, 800, 66, 1_900),     # three words a lane
+    (wl.LOGISTIC, 16, 800, 64, 1_900),     # eight pairs: one wavefront, eight words a lane
     (wl.LINEAR, 17, 1_200, 65, 3_000),     # four pairs: nine of them, three wavefronts
     (wl.LOGISTIC, 32, 1_500, 128, 3_500),  # eight words a lane
-    (wl.LINEAR, 33, 1_000, 64, 2_500),     # eight pairs
+    (wl.LINEAR, 33, 1_000, 80, 2_500),     # eight pairs
 ]
 
 
