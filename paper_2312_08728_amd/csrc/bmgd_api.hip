@@ -137,7 +137,6 @@ struct bmgd_ctx {
     int64_t swa_count = 0;
     float* opt_m = nullptr;
     float* opt_s = nullptr;
-    int test_far = 0;                                // (bmgd_internal_far)
     int64_t opt_k = 0;
     uint32_t tag_epoch = 0;                        // tags handed out so far for flagged-word exchanges
     GlmLaunchShape shape{};
@@ -903,8 +902,6 @@ int enqueue_passes(bmgd_ctx* ctx, const void* x, const void* y, int64_t rows, hi
         a.single_step = -1;
         a.ll_part = ctx->ll_part;
         a.ll_theta = ctx->ll_theta;
-        a.far = ctx->test_far;
-        a.ll_dies = reinterpret_cast<unsigned long long*>(ctx->partial);   // (sums as plain floats are for steps launched one by one)
         a.lr_tab = lr_len ? ctx->lr_tab_dev : nullptr;
         a.lr_base = (int)std::min<int64_t>(ctx->lr_pos, std::max(lr_len - 1, 0));
         a.lr_len = lr_len;
@@ -1762,7 +1759,7 @@ BMGD_API int bmgd_internal_launched(const bmgd_ctx* ctx, int64_t run_n, int32_t 
 BMGD_API int bmgd_internal_far(bmgd_ctx* ctx)
 {
     if (!ctx) return BMGD_EINVAL;
-    ctx->test_far = 1;
+    ctx->shape.far = 1;
     return BMGD_OK;
 }
 

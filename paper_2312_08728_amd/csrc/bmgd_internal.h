@@ -119,9 +119,14 @@ struct GlmLaunchShape {
     int64_t n;          // mini-batch size and row length the shape was planned for
     int p;
     int chain_block;    // threads per workgroup of the persistent chain's kernel
+    int far;            // set by tests after glm_plan: 1: see ExchangeArgsFar
 };
 
-struct GlmArgs {
+// Arguments of the row form's kernels.  Those with exchange wavefronts (ExchangeArgs) have a few more, in between: the order decides which arguments
+// the compiler loads together and so how it lays out their scalar registers.  With these few among the general kernel's (GlmArgs) that one took 2 to 4 %
+// longer (19.7 against 20.5 us per update at p = 1026, n = 300 on three workgroups), with them last for all the others took up to 3 % longer (3.20
+// against 3.27 at p = 512, n = 1000 with Adam).
+struct GlmArgsData {
     const float* X;         // [rows][p]
     const float* y;         // [rows]
     const int32_t* perm;    // [npass][perm_stride]: partition of pass t at perm + t * perm_stride
@@ -129,6 +134,8 @@ struct GlmArgs {
     float* partial;         // [2][G][p] per-workgroup gradient sums (step-per-launch mode)
     unsigned long long* ll_part;   // [2][G][p] the same sums as flagged words {tag : float}, by step parity
     unsigned long long* ll_theta;  // [2][kThetaCopies][p] updated theta as flagged words (sliced reduction)
+};
+struct GlmArgsShape {
     unsigned* sync;         // [1] abort flag ([0] unused)
     unsigned tag_base;      // tag of step s is tag_base + (s - s_begin) + 1
     int s_begin, s_end;     // steps of this launch: s in [s_begin, s_end), s = pass * M + batch, all < 2^23
@@ -137,20 +144,37 @@ struct GlmArgs {
     int model;
     int L, logL;
     int reduce_mode;
+};
+struct GlmArgsRate {
     float alpha;
     long long timeout_ticks;
+};
+struct GlmArgsSteps {
     int single_step;        // >= 0: process only that step and stop after writing partial sums
     OptArgs opt;            // kind == kOptSgd: plain steps, no state.  Redundant reduction: every workgroup keeps a
                             // private copy of the state at m + blockIdx.x * pp (all copies stay identical)
     const float* lr_tab;    // optional learning rate per step: step s uses lr_tab[min(lr_base + s, lr_len - 1)]
     int lr_base, lr_len;
-    // What only the kernels with exchange wavefronts use stands last: between the others it moved the general kernel's arguments, whose loads and
-    // scalar registers the compiler then laid out 2 to 4 % slower (19.7 against 20.5 us per update at p = 1026, n = 300 on three workgroups).
-    unsigned long long* ll_dies;   // [2][8][8][p] sums of the workgroups of a die as flagged words, by the die they go to and the one they are from
-    int far;                // 1: the two-level exchange takes the workgroups of a die to be on several (tests)
-    int width, shift;       // positions of a row in shared memory, and how many of the last four stand for no column (filled in by
-                            //   the launches of the kernels that lay rows out so, glm_exchange.h)
 };
+struct GlmArgs : GlmArgsData, GlmArgsShape, GlmArgsRate, GlmArgsSteps {};
+
+struct ExchangeArgsDies {
+    unsigned long long* ll_dies;   // [2][8][8][p] sums of the workgroups of a die as flagged words, by the die they go to and the one they are from
+};
+struct ExchangeArgsFar {
+    int far;                // 1: the two-level exchange takes the workgroups of a die to be on several (tests)
+};
+struct ExchangeArgsRow {
+    int width, shift;       // positions of a row in shared memory, and how many of the last four stand for no column (glm_exchange.h; filled in by
+                            //   the launches of the kernels)
+};
+struct ExchangeArgs : GlmArgsData, ExchangeArgsDies, GlmArgsShape, ExchangeArgsFar, GlmArgsRate, ExchangeArgsRow, GlmArgsSteps {
+};
+inline ExchangeArgs exchange_args(const GlmArgs& g, int far)
+{
+    // (the dies' sums stand where steps launched one by one have theirs as plain floats)
+    return ExchangeArgs{g, {reinterpret_cast<unsigned long long*>(g.partial)}, g, {far}, g, {}, g};
+}
 
 // Whether the `lines` wavefronts of each workgroup that add up a line of 16 columns at a time can hold all lines (exchange_by_die), and the
 // dies' sums, 1 KB for each of p rounded up to 16, the room they share with the sums of launched steps, 2 KB for each of p.
@@ -177,7 +201,7 @@ size_t glm_split_lds_bytes(int ch);
 int glm_split_block();
 bool glm_split_by_die(int ch, int64_t p, int G, int64_t n);
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups);
-hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream, hipEvent_t stop);
+hipError_t glm_split_launch(int ch, bool opt, int G, int far, const GlmArgs& args, hipStream_t stream, hipEvent_t stop);
 
 // Persistent chain for rows of up to 1024 floats when a step's rows fit the registers of the grid (glm_narrow_kernel.hip), with
 // rw row wavefronts per workgroup.  glm_narrow_rows_in_flight: rows per row slot that a step of n rows needs on G workgroups, 0 if

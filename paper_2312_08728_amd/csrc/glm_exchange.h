@@ -133,7 +133,7 @@ __device__ __forceinline__ unsigned lds_address(const T* word) { return (unsigne
 struct StepGeometry {
     int M, n, n_tail, perm_stride;
     float rcpM;
-    __device__ __forceinline__ explicit StepGeometry(const GlmArgs& a)
+    __device__ __forceinline__ explicit StepGeometry(const ExchangeArgs& a)
     {
         M = (a.rows + a.n - 1) / a.n;
         n = a.n;
@@ -169,15 +169,15 @@ typedef __attribute__((address_space(3))) f32x2 lds_f32x2;
 // The hardware loads vectors from any multiple of four bytes; rows loaded float by float or in pairs took 5.5 instead of 3.3 us per update at
 // p = 301, n = 1000, 9.5 instead of 5.6 at 1502, 1000, 3.5 instead of 2.9 at 201, 1500: these then did not fit the registers, or took as many
 // times the loads.
-__device__ __forceinline__ int position_of(const GlmArgs& a, int c) { return c + (c >= a.width - 4 ? a.shift : 0); }
+__device__ __forceinline__ int position_of(const ExchangeArgs& a, int c) { return c + (c >= a.width - 4 ? a.shift : 0); }
 // the column of a position (below `width`), or one below 0 where there is none
-__device__ __forceinline__ int column_of(const GlmArgs& a, int pos)
+__device__ __forceinline__ int column_of(const ExchangeArgs& a, int pos)
 {
     const int k = pos - (a.width - 4);
     return k < 0 ? pos : k < a.shift ? -1 : pos - a.shift;
 }
 // where the vector of a row that starts at a position is loaded from; beyond the row (theta is 0 there) its start
-__device__ __forceinline__ int vector_from(const GlmArgs& a, int pos) { return pos >= a.width ? 0 : pos - (pos >= a.width - 4 ? a.shift : 0); }
+__device__ __forceinline__ int vector_from(const ExchangeArgs& a, int pos) { return pos >= a.width ? 0 : pos - (pos >= a.width - 4 ? a.shift : 0); }
 
 // Theta into the first `stride` floats of `th`, by position (0 where there is no column), and zeros into the others up to `total`.  (Multiples of
 // 16; MAX: the largest stride.)  All that a thread loads is asked for at once and comes while the zeros go out: with a load and its position to
@@ -185,7 +185,7 @@ __device__ __forceinline__ int vector_from(const GlmArgs& a, int pos) { return p
 // 4096, 200.
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 template <int BLOCK, int MAX>
-__device__ __forceinline__ void load_theta(const GlmArgs& a, lds_f32* th, int stride, int total, int tid)
+__device__ __forceinline__ void load_theta(const ExchangeArgs& a, lds_f32* th, int stride, int total, int tid)
 {
     constexpr int K = (MAX + BLOCK - 1) / BLOCK;
     float v[K];
@@ -255,7 +255,7 @@ constexpr int kExchangeState = 3 * 128, kExchangeRed = 2 * 128;     // floats of
 // would wait for stores to global memory as well.
 template <bool OPT, int NX, int NSUM>
 struct ExchangeCommon {
-    const GlmArgs& a;
+    const ExchangeArgs& a;
     const ExchangeLds& x;
     const int lane, xw;
     const int G, g;
@@ -266,7 +266,7 @@ struct ExchangeCommon {
     const unsigned abort_addr;
     long long poll_start = 0;                        // when the words of a trip were first asked for
 
-    __device__ __forceinline__ ExchangeCommon(const GlmArgs& a_, const ExchangeLds& x_, int lane_, int xw_)
+    __device__ __forceinline__ ExchangeCommon(const ExchangeArgs& a_, const ExchangeLds& x_, int lane_, int xw_)
         : a(a_), x(x_), lane(lane_), xw(xw_), G(gridDim.x), g(blockIdx.x), p(a_.width), pp((a_.p + 15) & ~15), geo(a_),
           words_bytes((unsigned)((size_t)gridDim.x * (size_t)((a_.p + 15) & ~15) * 8)), abort_addr(lds_address(x_.s_abort))
     {
@@ -501,7 +501,7 @@ struct ExchangeCommon {
 // many SIMDs finish a trip sooner, beside row traffic too (glm_split_kernel.hip has both figures).
 // GATED: the row wavefronts wait for s_sent.  U1, U2: pairs of words a lane requests per trip when it sums the slice / collects theta (sums that are one array: all of them).
 template <bool OPT, int NX, int NSUM, bool GATED, int U1, int U2>
-__device__ __forceinline__ void exchange_wavefront(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
+__device__ __forceinline__ void exchange_wavefront(const ExchangeArgs& a, const ExchangeLds& x, int lane, int xw)
 {
     ExchangeCommon<OPT, NX, NSUM> ex(a, x, lane, xw);
     const int G = ex.G, g = ex.g, p = ex.p, pp = ex.pp;
@@ -677,7 +677,7 @@ struct PairExchange : ExchangeCommon<OPT, NX, NSUM> {
     const int c;                                     // first column of its pair,
     const int cc;                                    //   or where there is none the last one
     const bool own;
-    __device__ __forceinline__ PairExchange(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
+    __device__ __forceinline__ PairExchange(const ExchangeArgs& a, const ExchangeLds& x, int lane, int xw)
         : ExchangeCommon<OPT, NX, NSUM>(a, x, lane, xw), pair(lane & (PW - 1)), sg(lane / PW), c(2 * (PW * xw + pair)), cc(min(c, this->pp - 2)), own(c < this->p)
     {
     }
@@ -705,7 +705,7 @@ struct PairExchange : ExchangeCommon<OPT, NX, NSUM> {
 // The same steps in ONE trip over the fabric: every workgroup adds up all sums of all workgroups itself, in the same order, and keeps
 // its own copy of theta and of an update rule's state (at m + g pp).  For few words (G p of them come in per step and workgroup).
 template <bool OPT, int NX, int NSUM, bool GATED, int PW>
-__device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
+__device__ __forceinline__ void exchange_one_trip(const ExchangeArgs& a, const ExchangeLds& x, int lane, int xw)
 {
     PairExchange<OPT, NX, NSUM, PW> ex(a, x, lane, xw);
     constexpr int SG = 64 / PW;
@@ -800,7 +800,7 @@ __device__ __forceinline__ void exchange_one_trip(const GlmArgs& a, const Exchan
 // 4.26 against 3.76 at p = 1000 on 64), which the callers' rule sees to (glm_by_die).
 // LW: lines a wavefront takes at a time.  U2: pairs of words a lane requests at a time when it collects theta (sums that are one array: all of them).
 template <bool OPT, int NX, int NSUM, int LW, int U2>
-__device__ __forceinline__ void exchange_by_die(const GlmArgs& a, const ExchangeLds& x, int lane, int xw)
+__device__ __forceinline__ void exchange_by_die(const ExchangeArgs& a, const ExchangeLds& x, int lane, int xw)
 {
     ExchangeCommon<OPT, NX, NSUM> ex(a, x, lane, xw);
     const int G = ex.G, g = ex.g, p = ex.p, pp = ex.pp;

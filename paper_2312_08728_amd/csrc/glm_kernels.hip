@@ -838,7 +838,7 @@ hipError_t glm_launch_chain(const GlmLaunchShape& s, const GlmArgs& args, hipStr
         if (s.G < 8 || s.G > s.max_G) return hipErrorInvalidValue;
         GlmArgs a = args;
         a.single_step = -1;
-        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, a, stream, stop);
+        return glm_split_launch(s.split_ch, s.with_optimizer != 0, s.G, s.far, a, stream, stop);
     }
     if (s.narrow) {
         if (s.G > s.max_G) return hipErrorInvalidValue;

@@ -55,7 +55,7 @@ __device__ __forceinline__ float pick4(int k, float v0, float v1, float v2, floa
 // a step.)
 constexpr int kTwoTrips = 0, kByDie = 1;
 template <int V, int CPL, int PF, int RW, int EX, bool OPT>
-__global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
+__global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(ExchangeArgs a)
 {
     extern __shared__ __align__(16) float smem[];
     __shared__ int s_abort;                          // set by the exchange wavefront when a wait ran out
@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(GlmArgs a)
     else exchange_wavefront<OPT, kXWaves, RW, kGated, 8, 2>(a, x, lane, wave);   // ... and eight cover the slice for up to 256 workgroups)
 }
 
-using KernelFn = void (*)(GlmArgs);
+using KernelFn = void (*)(ExchangeArgs);
 
 template <bool OPT, int RW, int EX, int V, int CPL, int PF>
 KernelFn pick()
@@ -386,7 +386,7 @@ hipError_t glm_narrow_launch(const GlmLaunchShape& s, const GlmArgs& args, hipSt
     if (one_trip ? s.narrow_rw == kRowWaves || args.p > kNarrowOneTripMaxP || s.G < 1
                  : s.G < 8 || s.G % 8 != 0 || l.V != 4)
         return hipErrorInvalidValue;
-    GlmArgs a = args;
+    ExchangeArgs a = exchange_args(args, s.far);
     a.L = l.L;
     a.logL = 0;
     while ((1 << a.logL) < a.L) ++a.logL;

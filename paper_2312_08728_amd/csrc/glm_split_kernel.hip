@@ -63,7 +63,7 @@ __device__ __forceinline__ void lds_wait_all_eq(unsigned addr, unsigned want, un
 // BY_DIE: how the sums are exchanged, over two levels or in two trips.  (A kernel each: with both in one the row wavefronts' loop read six more scalar
 // values back from vector registers for every group of rows, 3 % of an update with 48 rows a workgroup at p = 1500.)
 template <int CH, bool OPT, bool BY_DIE>
-__global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
+__global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(ExchangeArgs a)
 {
     extern __shared__ __align__(16) float smem[];
     __shared__ int s_abort;                          // set by an exchange wavefront when a wait ran out
@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(kSplitBlock) glm_split_kernel(GlmArgs a)
     else exchange_wavefront<OPT, NX, 1, true, 11, CH == 1 ? 6 : 11>(a, x, lane, wave);   // (a trip's words at once, for up to 256 workgroups and p columns)
 }
 
-using KernelFn = void (*)(GlmArgs);
+using KernelFn = void (*)(ExchangeArgs);
 
 template <bool BY_DIE>
 KernelFn split_kernel(int ch, bool opt)
@@ -309,11 +309,11 @@ hipError_t glm_split_prepare(int ch, bool opt, int* max_groups)
     return hipSuccess;
 }
 
-hipError_t glm_split_launch(int ch, bool opt, int G, const GlmArgs& args, hipStream_t stream, hipEvent_t stop)
+hipError_t glm_split_launch(int ch, bool opt, int G, int far, const GlmArgs& args, hipStream_t stream, hipEvent_t stop)
 {
     if (G < 8 || G % 8 != 0 || args.s_begin >= args.s_end || args.p < 4 || args.p > kRowWaves * 256 * ch)
         return hipErrorInvalidValue;
-    GlmArgs a = args;
+    ExchangeArgs a = exchange_args(args, far);
     a.width = (args.p + 3) / 4 * 4;
     a.shift = a.width - args.p;
     hipExtLaunchKernelGGL(split_kernel(ch, opt, glm_split_by_die(ch, args.p, G, args.n)), dim3(G), dim3(kSplitBlock), (uint32_t)glm_split_lds_bytes(ch), stream, nullptr, stop, 0u, a);
