@@ -230,10 +230,10 @@ __global__ void __launch_bounds__(narrow_block(RW)) glm_narrow_kernel(ExchangeAr
                 // a release here would wait for the rows in flight as well)
                 asm volatile("" ::: "memory");
                 if (lane == 0) lds_add_one(lds_address((lds_u32*)&s_published));
-                // What the exchange sends and asks for first would stand behind the coming requests in the unit's memory pipeline; they go out
-                // while its words are under way.
-                if (gated) lds_wait_ge(sent_addr, (unsigned)(s + 1 - first) * kXWaves, abort_addr);
             }
+            // What the exchange sends and asks for first would stand behind these requests in the unit's memory pipeline; they go out while
+            // its words are under way.
+            if constexpr (kGated) lds_wait_ge(sent_addr, gated ? (unsigned)(min(s + 1, last) - first) * kXWaves : 0u, abort_addr);
             request(S);
         };
         int su = first;
