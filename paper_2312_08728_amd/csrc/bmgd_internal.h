@@ -113,7 +113,7 @@ struct GlmLaunchShape {
     int split_ch;
     int narrow;         // 1: the persistent chain runs the kernel for rows of up to 1024 floats whose share of a step fits a
                         // workgroup's registers (glm_narrow_kernel.hip): narrow_pf rows per row slot of narrow_rw row wavefronts
-                        // (8: sliced reduction, G a multiple of 8; 12: redundant reduction, or sliced with odd p)
+                        // (8: sliced reduction, G a multiple of 8; 12: redundant reduction, or sliced with odd p of up to 256)
     int narrow_pf, narrow_rw;
     NarrowLayout narrow_layout;
     int64_t n;          // mini-batch size and row length the shape was planned for
@@ -206,7 +206,7 @@ hipError_t glm_split_launch(int ch, bool opt, int G, int far, const GlmArgs& arg
 // Persistent chain for rows of up to 1024 floats when a step's rows fit the registers of the grid (glm_narrow_kernel.hip), with
 // rw row wavefronts per workgroup.  glm_narrow_rows_in_flight: rows per row slot that a step of n rows needs on G workgroups, 0 if
 // that is more than the kernel holds.
-constexpr int kNarrowMoreRows = 12;        // row wavefronts where the sums are added up by every workgroup, or p is odd
+constexpr int kNarrowMoreRows = 12;        // row wavefronts where the sums are added up by every workgroup, or p is odd and at most 256
 constexpr int kNarrowOneTripMaxP = 512;    // widest rows of the redundant reduction in this kernel
 int glm_narrow_block(int rw);
 bool glm_narrow_by_die(int64_t p, int G);

@@ -21,8 +21,8 @@
 // exchange_one_trip: every workgroup adds up all words itself and makes the whole update.
 // Polls are bounded by the wall clock.
 //
-// What bounds a step of short rows is latency: each trip is the time until the slowest workgroup has stored its words, the way there and back, 0.6 us
-// over the fabric and half of that within a die, and the instructions between them; and all that a compute unit asks for passes through one memory
+// What bounds a step of short rows is latency: each trip is the time until the slowest workgroup has stored its words, the way there and back, and the
+// instructions between them, 1.0 us and more over the fabric, 0.4 to 0.6 within a die; and all that a compute unit asks for passes through one memory
 // pipeline in turn, so rows are requested when the exchange has nothing to send or to ask for (s_sent).
 #pragma once
 
@@ -239,13 +239,13 @@ struct ExchangeLds {
     lds_u32* s_published;
     lds_u32* s_theta_version;     // raised by every exchange wavefront once per step: NX v when version v is complete
     lds_i32* s_abort;
-    lds_u32* s_sent;              // raised by every exchange wavefront once per step: the rows of a later step may be requested
+    lds_u32* s_sent;              // raised by every exchange wavefront once per step, where rows wait for it: those of a later step may be requested
     lds_u32* s_xarrived;          // [NX] sets of partial sums each exchange wavefront has left in `red`
     lds_u32* s_xconsumed;         //         sets that the first one has added up (two-trip form)
 };
 constexpr int kExchangeState = 3 * 128, kExchangeRed = 2 * 128;     // floats of `state` and `red` per exchange wavefront
 
-// What the exchange wavefronts of both forms do the same way.  NSUM: arrays of sums in shared memory.
+// What the exchange wavefronts of all forms do the same way.  NSUM: arrays of sums in shared memory.
 //
 // All of this stands on the critical path of a step, between the last row and the first of the next step, where one wavefront
 // on its SIMD issues an instruction in four clocks at best and a branch taken costs more: 100 instructions are 0.2 us.  So it is written

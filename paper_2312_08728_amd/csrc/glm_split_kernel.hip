@@ -18,7 +18,7 @@
 //     row wavefronts issue no load but their rows (and, right behind them, the responses and the next row indices), and
 //   * three more wavefronts, on three of the four SIMDs, do the exchange (glm_exchange.h).  They have no rows in flight, so their polls return
 //     at the latency of the fabric, and they share a trip's words: one wavefront pulls freshly written lines at a fraction of what a compute
-//     unit can take.  Two trips over the fabric per step.  us per update with one (whose SIMD had no row wavefronts) and with three: 7.6 / 6.2 at
+//     unit can take.  Two trips over the fabric per step, or three shorter ones.  us per update with one (whose SIMD had no row wavefronts) and with three: 7.6 / 6.2 at
 //     p = 1028, n = 1500 (256 workgroups, 6 rows each), 9.1 / 7.9 at 2048, 2048, 10.3 / 9.1 at 2500, 1500, 15.0 / 13.7 at 2500, 4096, 19.0 / 18.0 at
 //     4096, 4096, 30.6 / 29.9 at 4096, 8192: the fewer the rows, the less stands in the queues that the exchange now shares with them.  With four:
 //     at most 2 % less.  (With words stored at device scope a trip costs the same whether they come from the same die or another: the first load

@@ -43,7 +43,7 @@ constexpr size_t pair_lds(int nt) { return sizeof(float) * (size_t)(16 * nt) * (
 // factor: the eight or 32 lanes that are served together meet no bank twice.
 // What bounds it is a trip to memory for what the kernel before wrote (6 us with the launch, 50 KB a product and workgroup at Q = 112), the
 // matrix instructions (28 for each of a wavefront's seven tiles, 2.8 us) and the way out, one after the other in a workgroup and little more than
-// one workgroup to a unit.  150 products of order 112: 17.3 us; four workgroups a product that staged 32 rows of the left factor too, with
+// one workgroup to a unit.  150 products of order 112: 17.3 us (19.1 under a profiler); four workgroups a product that staged 32 rows of the left factor too, with
 // the loads of the largest order whatever the order was and stores of 4 bytes, 24.4.
 // FIRST: the factors are the steps themselves, A_s = [[I - alpha_s Sxx_s, alpha_s Sxy_s], [0, 1]] padded with zeros:
 // entry (r, c) is (r == c and r <= p) - alpha_s D_s(r, c) with D_s the dense matrix the moments kernel wrote.

@@ -11,8 +11,8 @@
 // Counters (arrive / await): a workgroup that has written its part waits for its stores, then adds one to the counter of the part;
 // readers poll.  What one workgroup writes and another reads (U, R, the bf16 copy of W) is stored and loaded at device scope, so it
 // is never found in a compute unit's own cache.  A die's L2 serves such a load as fast as others if nobody has written the line since the die
-// last had it (0.30 against 0.29 us per 32 KB and compute unit; 90 ns for a load that depends on the one before); the first load of a freshly
-// written line goes beyond the die, whichever die wrote it (220 ns).  Invalidating caches between phases costs 2 us and more.  A phase's parts are counted in every update by
+// last had it (0.30 against 0.29 us per 32 KB and compute unit; 90 ns for a load that depends on the one before); the first load of a line
+// freshly written at device scope goes beyond the die, whichever die wrote it (220 ns; words stored without a scope stay in the die's L2).  Invalidating caches between phases costs 2 us and more.  A phase's parts are counted in every update by
 // every workgroup, also where a short last mini-batch leaves nothing to do, and nothing is awaited less often than in every update:
 // so a count can only be reached by arrivals of the update that is waited for.
 //   (an arrival for update s + 1 follows, through the waits in front of it, all arrivals for update s at the same counter)
