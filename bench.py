@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 # HBM traffic of one launch of the chain kernel on the primary workload, from rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE (see profiles/), scaled by the copy calibration; valid only for the source of the kernel it was measured on
 # (the line reports null once that file has changed: measure again and update the entry).
-TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641623}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip', 'lds_load.h'), "kernel_sha256": "15fb8c15565c984bb82a931528c0fc05a13f0ebe4a11c4e4eb4424656666dc88", "bytes_per_launch": 201608619}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "1fe490d81b3c31cc9b32fb703ed0b374242bc2e665518ba5b3e26a71273a7303", "bytes_per_launch": 2162466848}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "132cb5af616dccebc21462d3c7255199dd106950861de58f596747f2628d0c32", "bytes_per_launch": 9495706026}}
+TRAFFIC = {"cfg1": {"sources": ('gram_fused_kernel.hip', 'gram_chain.h', 'gram_layout.h', 'perm_device.h'), "kernel_sha256": "68229ccd856e66435e513a8c7bdcc38e5deebfc14c1b0f5717c85152a62a2d42", "bytes_per_launch": 641623}, "cfg2": {"sources": ('gram_kernels.hip', 'gram_chain.h', 'gram_layout.h', 'gram_products.hip', 'lds_load.h'), "kernel_sha256": "15fb8c15565c984bb82a931528c0fc05a13f0ebe4a11c4e4eb4424656666dc88", "bytes_per_launch": 201608619}, "cfg3": {"sources": ('glm_narrow_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "1fe490d81b3c31cc9b32fb703ed0b374242bc2e665518ba5b3e26a71273a7303", "bytes_per_launch": 2162466848}, "cfg4": {"sources": ('glm_split_kernel.hip', 'glm_exchange.h', 'glm_device.h'), "kernel_sha256": "71684f44c755b30904d4d2dd237aa64af62b926780c7fd2262e6a9ed6cb1270d", "bytes_per_launch": 9495706026}}
 
 
 def _kernel_sha(sources) -> str:

@@ -643,17 +643,18 @@ KernelFn pick_kernel(const GlmLaunchShape& s)
 
 namespace {
 
-// Rows of more than 1024 floats that are no multiple of four, on G (a multiple of 8) workgroups: the kernel for wide rows takes less time for an
+// Rows of more than 1024 floats that are no multiple of four, on `asked` workgroups, or the eights among them: the kernel for wide rows takes less time for an
 // update than the general one, but more for every further row, which the general kernel's wavefronts take one each.  Where the lines cross, in rows
 // a workgroup, plain steps / Adam: 13 / 25 on 8 workgroups, 26 / 39 on 16 and 32, 28 / 40 on 64, 31 / 45 on 128, 36 / 65 on 192 (p = 1502 and 2046; at 1026,
 // where the general kernel exchanges its sums more slowly, 30 / 50, 40 / 60 and 55 / 75 on 64, 128 and 192), nowhere with 360,000 sums a step.
 // us per update, general / wide, plain: 8.4 / 7.4 at 1502, 93 on 8; 12.6 / 17.8 at 1026, 381 on 8; 9.6 / 8.8 and 11.7 / 14.5 at 1502, 317 and 637 on 16; 15.4 /
 // 19.9 at 1502, 7165 on 128.
-bool wide_rows_pay(int64_t p, int64_t n, int G, bool with_state)
+bool wide_rows_pay(int64_t p, int64_t n, int asked, bool with_state)
 {
+    const int G = asked & ~7;
     const int64_t rows = (n + G - 1) / G;
-    if (G < 16) return rows <= (with_state ? 24 : 12);
-    return (int64_t)G * p >= 360000 || rows <= 24 + (p > 1280 ? G / 16 : G * G / 1200) + (with_state ? 12 + G / 32 : 0);
+    if (G < 16) return rows * asked <= (with_state ? 24 : 12) * G;   // (the general kernel takes all that are asked for)
+    return (int64_t)G * p >= 360000 || rows <= 24 + (p > 1280 ? G / 16 : std::max(G / 10, G * G / 1200)) + (with_state ? 12 + G / 32 : 0);
 }
 
 // Words that a workgroup fetches per step when every workgroup adds up the sums of all of them.
@@ -758,7 +759,7 @@ bool glm_plan(int64_t p, int64_t n, int requested_G, int num_cus, bool persisten
         s.PF = max_pf(s.V, s.CPL); s.pipe = kPipeGroups;
     }
     s.chain_block = s.narrow ? glm_narrow_block(s.narrow_rw) : s.block;
-    if (p > 1024 && G >= 8 && (s.V == 4 || (persistent && wide_rows_pay(p, n, G & ~7, with_state)))) {
+    if (p > 1024 && G >= 8 && (s.V == 4 || (persistent && wide_rows_pay(p, n, G, with_state)))) {
         // wide rows on eight or more workgroups: the kernel with exchange wavefronts of its own
         s.split = 1;
         s.split_ch = p <= 2048 ? 1 : 2;

@@ -283,9 +283,9 @@ size_t glm_split_lds_bytes(int ch)
 int glm_split_block() { return kSplitBlock; }
 
 // Three short trips instead of two where a wavefront has two lines at most (three beyond 2048 floats) and a step few rows, so that little stands
-// in the queues that the trips share with them.  us per update, two trips / three: 6.1 / 5.6 at p = 1028, n = 1500, 8.1 / 7.7 at 1500, 3000, 7.47 / 7.46 at
-// 2048, 2048 (256 workgroups), but 16.3 / 17.3 at 2048, 8192; 8.4 / 6.7 at 4096, 300, 7.7 / 6.6 at 3000, 500 with Adam, 6.9 / 5.7 at 3200, 200 (208), but
-// 6.7 / 6.9 at 2500, 1000, 7.5 / 8.2 at 4096, 700.
+// in the queues that the trips share with them.  us per update on 256 workgroups, two trips / three: 5.9 / 5.3 at p = 1028, n = 1500, 7.3 / 6.9 at 1500, 3000, 6.8 / 6.4
+// at 2048, 2048, 7.9 / 7.8 at 2048, 3000, 9.5 / 9.2 at 2048, 4000, but 20.4 / 20.8 at 2048, 12000; 8.3 / 6.3 at 4096, 250, 7.35 / 6.15 at 3200, 500, but 6.75 / 7.1 at 3200, 1000,
+// 7.8 / 8.4 at 4096, 1000.
 bool glm_split_by_die(int ch, int64_t p, int G, int64_t n) { return glm_by_die(p, G, (ch + 1) * NX) && n <= (ch == 1 ? 12 : 2) * G; }
 
 hipError_t glm_split_prepare(int ch, bool opt, int* max_groups)

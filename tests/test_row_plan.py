@@ -20,6 +20,7 @@ def test_steps_launched_one_by_one_do_not_follow_the_persistent_kernels_limits(p
     (1026, 96, 8, 0, 8, SPLIT), (1026, 97, 8, 0, 8, GENERAL), (1026, 192, 8, 3, 8, SPLIT), (1026, 193, 8, 3, 8, GENERAL),
     (1502, 400, 16, 0, 16, SPLIT), (1502, 401, 16, 0, 16, GENERAL), (1502, 592, 16, 1, 16, SPLIT), (1502, 593, 16, 1, 16, GENERAL),
     (1502, 7_165, 128, 0, 128, GENERAL), (1502, 12_000, 256, 0, 256, SPLIT), (1502, 600, 25, 0, 24, SPLIT), (1502, 600, 37, 0, 32, SPLIT),
+    (1502, 141, 12, 3, 12, GENERAL), (1502, 120, 12, 3, 8, SPLIT), (1026, 1_789, 64, 0, 64, SPLIT),
     (1500, 300, 8, 0, 8, SPLIT), (2048, 20_000, 64, 0, 64, SPLIT), (2500, 300, 8, 0, 8, SPLIT),      # multiples of four: as ever
     (1502, 300, 7, 0, 7, GENERAL),
 ])
